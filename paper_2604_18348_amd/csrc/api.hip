@@ -27,7 +27,7 @@ thread_local char g_err[256] = "";
 // from the event in from[] (default: the previous recorded stage boundary); the fused call runs
 // the two clusterings side by side, so both of those are timed from the start of the call.
 enum { EV_START = 0, EV_QCLUSTER, EV_KCLUSTER, EV_SELECT, EV_PERMUTE, EV_PLAN, EV_ATTN, EV_KREDUCE, EV_STAGES,
-       EV_JOIN = EV_STAGES, EV_JOIN2, EV_KSORT, EV_COUNT };
+       EV_JOIN = EV_STAGES, EV_KSORT, EV_COUNT };
 struct Profiler {
   bool enabled = false;
   bool recorded[EV_COUNT] = {};
@@ -55,7 +55,7 @@ void prof_mark(int which, hipStream_t st, int from = -1) {
 struct AuxStream {
   bool ready = false;
   hipStream_t s = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr, join2 = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr;
 };
 thread_local AuxStream g_aux[64];
 
@@ -97,7 +97,6 @@ AuxStream* aux_stream() {
     if (hipStreamCreateWithFlags(&a.s, hipStreamNonBlocking) != hipSuccess) return nullptr;
     if (hipEventCreateWithFlags(&a.fork, hipEventDisableTiming) != hipSuccess) return nullptr;
     if (hipEventCreateWithFlags(&a.join, hipEventDisableTiming) != hipSuccess) return nullptr;
-    if (hipEventCreateWithFlags(&a.join2, hipEventDisableTiming) != hipSuccess) return nullptr;
     a.ready = true;
   }
   return &a;
@@ -180,11 +179,10 @@ struct WS {
   // scratch of the query clustering (its own set: it runs beside the key clustering)
   void* q_cent_lp; float* q_bias; SortScratch q_sort; int32_t* q_poff; float* q_psum; float* q_pnorm;
   float* q_wsum; int32_t* q_wcnt;     // walk sums and counts of the one-read passes of the query clustering
-  void* Kp; void* Vp;
   double* scores;       // [H][Cq][cap] centroid scores between the kernels of the selection step
   int32_t* rng_start; int32_t* rng_pre; int32_t* rng_cnt; int32_t* tiles; int32_t* ntiles;
   int32_t* merge; int32_t* nmerge; float* part_o; float* part_ml;   // cut key lists of the attention step
-  int32_t* krow;        // [H][Cq][kstride] byte offset of every key row of a query cluster's list
+  int32_t* krow;        // [H][Cq][kstride] every key row of a query cluster's list (see key_row_scale)
   // homes for outputs of the fused call the caller did not ask for
   int32_t* q_labels; float* q_centroids; float* q_assign; int32_t* q_sizes; float* q_mean_norm;
   int32_t* k_labels; float* k_centroids; float* k_assign; float* k_bmin; float* k_bmax;
@@ -215,11 +213,11 @@ Dims dims_of(const adacluster_params* p) {
   return D;
 }
 
-// bf16: the attention kernel takes every key row by its byte offset, so K and V stay where they are and the
-// row-offset table of a query cluster is written through the key permutation (no permuted copies; measured
-// against gathering K and V into cluster order first: the same attention time, and the gather with its 4 bytes
-// of HBM traffic per input byte gone).  fp32: the kernel walks row ranges of the permuted copies.
-static bool rows_in_place(const adacluster_params* p) { return p->dtype == ADACLUSTER_BF16; }
+// K and V stay where they are: the planning step writes, per query cluster, the list of its key rows through the key
+// permutation, and the attention kernels load by it (measured against gathering K and V into cluster order first: the
+// same attention time, and the gather with its 4 bytes of HBM traffic per input byte gone).  bf16 entries are byte
+// offsets inside a head, fp32 entries row numbers.
+static int key_row_scale(const adacluster_params* p) { return p->dtype == ADACLUSTER_BF16 ? p->d * 2 : 1; }
 
 size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   const Dims D = dims_of(p);
@@ -273,19 +271,21 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(offs_q, int32_t*, H * (size_t)(D.Cq + 1) * 4);
   TAKE(perm_k, int32_t*, H * N * 4);
   TAKE(offs_k, int32_t*, H * (size_t)(D.cap + 1) * 4);
-  TAKE(Kp, void*, rows_in_place(p) ? 256 : H * N * d * es);      // permuted copies: fp32 only
-  TAKE(Vp, void*, rows_in_place(p) ? 256 : H * N * d * es);
   TAKE(scores, double*, H * (size_t)D.Cq * D.cap * 8);
   TAKE(rng_start, int32_t*, H * (size_t)D.Cq * D.maxr * 4);
   TAKE(rng_pre, int32_t*, H * (size_t)D.Cq * (D.maxr + 1) * 4);
   TAKE(rng_cnt, int32_t*, H * (size_t)D.Cq * 4);
-  TAKE(tiles, int32_t*, H * (size_t)D.maxtiles * 6 * 4);
+  TAKE(tiles, int32_t*, H * (size_t)D.maxtiles * attn_tile_record() * 4);
   TAKE(merge, int32_t*, H * (size_t)attn_split_slots() * 4 * 4);
   TAKE(nmerge, int32_t*, H * 4);
-  TAKE(part_o, float*, H * (size_t)attn_split_slots() * D.BMmax * d * 4);
-  TAKE(part_ml, float*, H * (size_t)attn_split_slots() * D.BMmax * 2 * 4);
+  {  // partial results of split key lists: slots of cut lists (bf16), or a row per query and split (fp32; the dense call
+     // counts as one cluster, which never makes fewer splits)
+    const size_t rows = p->dtype == ADACLUSTER_BF16 ? H * (size_t)attn_split_slots() * D.BMmax : H * N * attn_f32_splits(D.H, D.N, 1);
+    TAKE(part_o, float*, rows * d * 4);
+    TAKE(part_ml, float*, rows * 2 * 4);
+  }
   TAKE(ntiles, int32_t*, H * 4);
-  TAKE(krow, int32_t*, p->dtype == ADACLUSTER_BF16 ? H * (size_t)D.Cq * attn_krow_stride(D.N) * 4 : 256);
+  TAKE(krow, int32_t*, H * (size_t)D.Cq * attn_krow_stride(D.N) * 4);
   TAKE(q_labels, int32_t*, H * N * 4);
   TAKE(q_centroids, float*, H * (size_t)D.Cq * d * 4);
   TAKE(q_assign, float*, H * (size_t)D.Cq * d * 4);
@@ -365,7 +365,7 @@ int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
 int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const void* K, int32_t* k_labels,
                  float* k_centroids, float* k_assign, float* k_bmin, float* k_bmax, int32_t* k_sizes,
                  int32_t* k_count, int32_t* full_flag, int32_t* k_stage_offs, int32_t* k_stage_of,
-                 float* tau_used, int* kc_bound_out, hipEvent_t sorted_ev = nullptr) {
+                 float* tau_used, int* kc_bound_out) {
   const Dims D = dims_of(p);
   int kc_bound = 0;   // sum over stages of the largest stage centre count: an upper bound of every |C|
   hipEvent_t pending_ev = nullptr;   // the last report may still be in flight when the stage loop ends
@@ -509,8 +509,6 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   }
   RET_IF(launch_sort(st, D.H, D.N, D.N, D.cap, k_labels, nullptr, nullptr, 0, &w.kstate->ccount, sizeof(KState) / 4,
                      nullptr, 0, w.perm_k, w.offs_k, D.cap + 1, w.sort, w.poff, reduce_part_rows(), &poff_done));
-  // the key permutation is final here: work that needs nothing else of the clustering may start
-  if (sorted_ev && hipEventRecord(sorted_ev, st) != hipSuccess) return fail(ADACLUSTER_E_INTERNAL, "stream fork failed");
   const int want_box = (k_bmin && k_bmax) ? 1 : 0;
   const int P = parts_for(D.N, D.cap);
   if (!poff_done) {       // the cut into reduction parts belongs to the sort's side of the profile mark
@@ -532,33 +530,20 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
 }
 
 // ---- attention over selected clusters, given both sorts ---------------------------------------
-// K and V rows into cluster order (needs only the key label sort)
-int run_permute(const adacluster_params* p, const WS& w, hipStream_t st, const void* K, const void* V, int prof_from) {
-  const Dims D = dims_of(p);
-  RET_IF(launch_permute_kv(st, D.H, D.N, D.d * (int)esize(p), K, V, w.perm_k, w.Kp, w.Vp));
-  prof_mark(EV_PERMUTE, st, prof_from);
-  return 0;
-}
-
 // range lists, row offsets and query tiles from the selection, then the attention kernel
 int run_plan_attention(const adacluster_params* p, const WS& w, hipStream_t st, const void* Q, void* O,
                        const int32_t* k_count, const int32_t* sel_idx, const int32_t* sel_cnt, int prof_from,
-                       hipEvent_t permute_done, const void* K = nullptr, const void* V = nullptr) {
+                       const void* K, const void* V) {
   const Dims D = dims_of(p);
-  const bool inplace = K && V && rows_in_place(p);
   const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)D.d);
   RET_IF(launch_plan_sparse(st, p->dtype, D.H, D.Cq, D.cap, D.maxr, D.maxtiles, D.BM, w.offs_q, D.Cq + 1, w.offs_k,
                             D.cap + 1, k_count, sel_idx, sel_cnt, w.rng_start, w.rng_pre, w.rng_cnt, w.tiles, w.ntiles,
-                            w.merge, w.nmerge, D.d * (int)esize(p), p->dtype == ADACLUSTER_BF16 ? w.krow : nullptr,
-                            attn_krow_stride(D.N), inplace ? w.perm_k : nullptr, D.N));
+                            w.merge, w.nmerge, key_row_scale(p), w.krow, attn_krow_stride(D.N), w.perm_k, D.N));
   prof_mark(EV_PLAN, st, prof_from);
-  if (permute_done && hipStreamWaitEvent(st, permute_done, 0) != hipSuccess)
-    return fail(ADACLUSTER_E_INTERNAL, "stream join failed");
-  if (permute_done) prof_mark(EV_JOIN2, st);
-  RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, D.Cq, D.maxtiles, D.maxr, scale, Q, inplace ? K : w.Kp, inplace ? V : w.Vp, O, w.perm_q,
-                          w.tiles, w.ntiles, w.rng_start, w.rng_pre, w.rng_cnt, w.part_o, w.part_ml, w.merge, w.nmerge,
+  RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, D.Cq, D.maxtiles, D.maxr, scale, Q, K, V, O, w.perm_q,
+                          w.tiles, w.ntiles, w.rng_pre, w.rng_cnt, w.part_o, w.part_ml, w.merge, w.nmerge,
                           w.krow, attn_krow_stride(D.N)));
-  prof_mark(EV_ATTN, st, permute_done ? EV_JOIN2 : -1);
+  prof_mark(EV_ATTN, st);
   return 0;
 }
 
@@ -704,8 +689,7 @@ int adacluster_sparse_attn(const adacluster_params* p, const void* Q, const void
   RET_IF(launch_sort(st, D.H, D.N, D.N, D.cap, k_labels, nullptr, nullptr, 0, k_count, 1, nullptr, 0, w.perm_k, w.offs_k,
                      D.cap + 1, w.sort));
   prof_mark(EV_SELECT, st);   // (time of the two label sorts when called stand-alone)
-  if (!rows_in_place(p) && (rc = run_permute(p, w, st, K, V, -1))) return rc;
-  return run_plan_attention(p, w, st, Q, O, k_count, sel_idx, sel_cnt, -1, nullptr, K, V);
+  return run_plan_attention(p, w, st, Q, O, k_count, sel_idx, sel_cnt, -1, K, V);
 }
 
 int adacluster_attn(const adacluster_params* p, const void* Q, const void* K, const void* V, void* O,
@@ -753,25 +737,10 @@ int adacluster_attn(const adacluster_params* p, const void* Q, const void* K, co
   if (hipEventRecord(aux->join, qs) != hipSuccess) return drained(fail(ADACLUSTER_E_INTERNAL, "stream join failed"));
   int kc_bound = capacity(p);
   int rck = rc ? 0 : run_kcluster(p, w, st, K, k_labels, k_centroids, k_assign_centroids, k_bmin, k_bmax, k_sizes,
-                                   k_count, full_flag, o.k_stage_offs, o.k_stage_of, tau_used, &kc_bound, aux->fork);
+                                   k_count, full_flag, o.k_stage_offs, o.k_stage_of, tau_used, &kc_bound);
   prof_mark(EV_KCLUSTER, st, EV_START);
-  // The K/V permutation needs only the key label sort, which is final before the last centroid
-  // update of the key clustering: it goes to the second stream too (behind the query clustering
-  // there) and runs beside that update, the selection and the planning.
-  const bool fork2 = !rc && !rck && !rows_in_place(p);     // (bf16 has no permutation step)
-  int rcp = 0;
-  if (fork2) {
-    if (hipStreamWaitEvent(aux->s, aux->fork, 0) != hipSuccess)
-      return drained(fail(ADACLUSTER_E_INTERNAL, "stream fork failed: %s", hipGetErrorString(hipGetLastError())));
-    rcp = run_permute(p, w, aux->s, K, V, EV_KSORT);
-    if (hipEventRecord(aux->join2, aux->s) != hipSuccess) return drained(fail(ADACLUSTER_E_INTERNAL, "stream join failed"));
-  }
   if (hipStreamWaitEvent(st, aux->join, 0) != hipSuccess) return drained(fail(ADACLUSTER_E_INTERNAL, "stream join failed"));
-  if (rc || rck || rcp) {
-    // whatever was queued on the second stream is joined before the error is reported
-    if (fork2 && hipStreamWaitEvent(st, aux->join2, 0) != hipSuccess) return drained(fail(ADACLUSTER_E_INTERNAL, "stream join failed"));
-    return rc ? rc : (rck ? rck : rcp);
-  }
+  if (rc || rck) return rc ? rc : rck;      // (what was queued on the second stream has been joined)
   prof_mark(EV_JOIN, st);
   const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)p->d);
   rc = launch_select(st, p->H, p->q_clusters, capacity(p), p->d, p->score_mode, p->select_mode, p->topk, p->top_p,
@@ -779,9 +748,8 @@ int adacluster_attn(const adacluster_params* p, const void* Q, const void* K, co
                      sel_idx, sel_cnt, kc_bound, w.scores);
   if (rc) return drained(rc == ADACLUSTER_E_INTERNAL ? fail(rc, "HIP launch failed: %s", hipGetErrorString(hipGetLastError())) : rc);
   prof_mark(EV_SELECT, st, EV_JOIN);
-  // both label sorts were left in the workspace by the clustering steps; the attention step joins the
-  // permutation of K and V (second stream) before its first kernel that reads it
-  rc = run_plan_attention(p, w, st, Q, O, k_count, sel_idx, sel_cnt, EV_SELECT, fork2 ? aux->join2 : nullptr, K, V);
+  // both label sorts were left in the workspace by the clustering steps
+  rc = run_plan_attention(p, w, st, Q, O, k_count, sel_idx, sel_cnt, EV_SELECT, K, V);
   return rc ? drained(rc) : 0;
 }
 
@@ -797,10 +765,10 @@ int adacluster_dense_attn(const adacluster_params* p, const void* Q, const void*
   const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)D.d);
   prof_begin(st);
   RET_IF(launch_plan_dense(st, D.H, D.N, D.maxtiles, attn_block_rows(p->dtype, D.d, D.N, 1), w.rng_start, w.rng_pre, w.rng_cnt, w.tiles, w.ntiles,
-                           D.d * (int)esize(p), p->dtype == ADACLUSTER_BF16 ? w.krow : nullptr, attn_krow_stride(D.N)));
+                           key_row_scale(p), w.krow, attn_krow_stride(D.N)));
   prof_mark(EV_PLAN, st);
   RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, 1, D.maxtiles, 1, scale, Q, K, V, O, nullptr, w.tiles,
-                          w.ntiles, w.rng_start, w.rng_pre, w.rng_cnt, nullptr, nullptr, nullptr, nullptr,
+                          w.ntiles, w.rng_pre, w.rng_cnt, w.part_o, w.part_ml, nullptr, nullptr,
                           w.krow, attn_krow_stride(D.N)));
   prof_mark(EV_ATTN, st);
   return 0;

@@ -1,8 +1,8 @@
 // Attention over the selected key clusters (Alg. 3 lines 9-10) and the dense branch.
 //
-// The label sort puts the keys in cluster order (a permutation, no copy for bf16: the planning step writes,
-// per query cluster, the byte offset of every selected key row in K and V as they are, and the kernel loads
-// its tiles through that table; fp32 gathers K and V into cluster order first and walks row ranges).  For
+// The label sort puts the keys in cluster order (a permutation, no copy: the planning step writes, per query
+// cluster, where every selected key row sits in K and V as they are, and the kernels load their tiles through
+// that table).  For
 // every query cluster the selected key clusters form a short list of row ranges in that order; a
 // query tile walks the concatenation of its ranges in full 64-key tiles, so cluster raggedness
 // costs nothing but one masked tail tile.  The flash-style kernel keeps the S^T = K Q^T
@@ -17,58 +17,11 @@
 
 namespace adac {
 
-static constexpr int TILE_REC = 6;       // ints per query-tile record
+static constexpr int TILE_REC = 8;       // ints per query-tile record (32 bytes)
 static constexpr int SPLIT_SLOTS = 128;  // partial slots per head for the chunks of cut key lists
+static constexpr int F32_WAVES = 4;      // waves of a workgroup of the fp32 kernel
+static constexpr int F32_MAX_SPLITS = 4; // most workgroups the fp32 kernel splits a key list over
 static constexpr int KROW_PAD = 8 * 64;  // entries of the row-offset table a key list is padded by: the kernel reads up to 7 tiles ahead
-
-// ------------------------------------------------------------------------------------------
-// permutation of K and V rows (fp32 inputs)
-// ------------------------------------------------------------------------------------------
-// dst[h][i][:] = src[h][perm[h][i]][:], 16-byte pieces, one row per group of ROWB/16 lanes; a thread
-// moves its piece of RPT rows of both tensors, all loads issued before the first store.
-#ifndef GATHER_RPT
-#define GATHER_RPT 4
-#endif
-template <int ROWB>
-__global__ __launch_bounds__(256) void gather_rows2(const uint8_t* __restrict__ a, const uint8_t* __restrict__ b,
-                                                    const int32_t* __restrict__ perm, int N,
-                                                    uint8_t* __restrict__ ao, uint8_t* __restrict__ bo) {
-  constexpr int LPR = ROWB / 16, RPB = 256 / LPR, RPT = GATHER_RPT;
-  const int h = blockIdx.y;
-  const int r0 = blockIdx.x * (RPB * RPT) + threadIdx.x / LPR;
-  const int q = threadIdx.x % LPR;
-  const int32_t* pm = perm + (size_t)h * N;
-  int src[RPT];
-#pragma unroll
-  for (int k = 0; k < RPT; ++k) { const int r = r0 + k * RPB; src[k] = r < N ? pm[r] : 0; }
-  uint4 va[RPT], vb[RPT];
-#pragma unroll
-  for (int k = 0; k < RPT; ++k) {
-    const size_t so = ((size_t)h * N + src[k]) * ROWB + q * 16;
-    va[k] = *reinterpret_cast<const uint4*>(a + so);
-    vb[k] = *reinterpret_cast<const uint4*>(b + so);
-  }
-#pragma unroll
-  for (int k = 0; k < RPT; ++k) {
-    const int r = r0 + k * RPB;
-    if (r >= N) continue;
-    const size_t dd = ((size_t)h * N + r) * ROWB + q * 16;
-    *reinterpret_cast<uint4*>(ao + dd) = va[k];
-    *reinterpret_cast<uint4*>(bo + dd) = vb[k];
-  }
-}
-
-int launch_permute_kv(hipStream_t s, int H, int N, int row_bytes, const void* K, const void* V,
-                      const int32_t* perm, void* Kp, void* Vp) {
-  auto A = (const uint8_t*)K; auto B = (const uint8_t*)V; auto Ao = (uint8_t*)Kp; auto Bo = (uint8_t*)Vp;
-  const int rows_per_block = 256 / (row_bytes / 16) * GATHER_RPT;
-  const dim3 g((N + rows_per_block - 1) / rows_per_block, H);
-  if (row_bytes == 128) gather_rows2<128><<<g, 256, 0, s>>>(A, B, perm, N, Ao, Bo);
-  else if (row_bytes == 256) gather_rows2<256><<<g, 256, 0, s>>>(A, B, perm, N, Ao, Bo);
-  else if (row_bytes == 512) gather_rows2<512><<<g, 256, 0, s>>>(A, B, perm, N, Ao, Bo);
-  else return ADACLUSTER_E_BADSHAPE;
-  return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
-}
 
 // ------------------------------------------------------------------------------------------
 // plan: per query cluster the merged key ranges; per head the list of query tiles
@@ -77,8 +30,8 @@ int launch_permute_kv(hipStream_t s, int H, int N, int row_bytes, const void* K,
 // rng_pre   [H][Cq][maxr+1] keys before range r in the concatenation (last = total)
 // rng_cnt   [H][Cq]
 // tiles     [H][maxtiles] x {cluster, first sorted query position, rows, first key tile, end key
-//           tile, partial slot or -1}; ntiles [H]
-__global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, int row_bytes,
+//           tile, partial slot or -1, keys of the cluster's whole list, 0}; ntiles [H]
+__global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, int row_scale,
                             const int32_t* __restrict__ k_offs, int k_offs_stride,
                             const int32_t* __restrict__ k_count,
                             const int32_t* __restrict__ sel_idx, const int32_t* __restrict__ sel_cnt,
@@ -145,14 +98,13 @@ __global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, in
     }
   }
   __syncthreads();        // the ranges are visible to the whole workgroup
-  // Byte offset of every key row of the concatenation, in order: what a key tile of the attention kernel
-  // loads its 64 rows by.  Entries past the end (up to the padding the kernel may read ahead) repeat the
+  // Every key row of the concatenation, in order, as a byte offset (bf16) or a row number (fp32, row_scale 1): what
+  // a key tile of the attention kernel loads its rows by.  Entries past the end (up to the padding the kernel may read ahead) repeat the
   // first row: they are loaded and never used.
-  if (!krow) return;       // (the fp32 kernel walks the ranges itself)
   const int nr = s_nr, total = s_total;
   int32_t* kr = krow + ((size_t)h * Cq + i) * kstride;
-  const int32_t* pk = perm_k ? perm_k + (size_t)h * N : nullptr;      // sorted position -> token (rows stay where they are)
-  const int first = nr > 0 ? (pk ? pk[rs[0]] : rs[0]) * row_bytes : 0;
+  const int32_t* pk = perm_k + (size_t)h * N;      // sorted position -> token (rows stay where they are)
+  const int first = nr > 0 ? pk[rs[0]] * row_scale : 0;
   const int padded = (total + 63) / 64 * 64 + KROW_PAD;
   // the search runs on a copy of the range table in LDS when it fits: its steps depend on one another, and
   // from global memory each of them is a trip to the L2
@@ -170,7 +122,7 @@ __global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, in
         int lo = 0, hi = nr - 1;                 // last range whose first position is <= p
         while (lo < hi) { const int mid = (lo + hi + 1) >> 1; if (srp[mid] <= p) lo = mid; else hi = mid - 1; }
         const int row = srs[lo] + (p - srp[lo]);
-        off = (pk ? pk[row] : row) * row_bytes;
+        off = pk[row] * row_scale;
       }
       kr[p] = off;
     }
@@ -195,13 +147,14 @@ __global__ __launch_bounds__(256) void plan_tiles(int Cq, int maxr, int maxtiles
   const int32_t* qo = q_offs + (size_t)h * q_offs_stride;
   int32_t* tl = tiles + (size_t)h * maxtiles * TILE_REC;
   int32_t* ml = merge + (size_t)h * slots * 4;
-  __shared__ int32_t s_T[MAXC], s_nq[MAXC], s_pieces[MAXC], s_tile0[MAXC], s_slot0[MAXC], s_merge0[MAXC];
+  __shared__ int32_t s_T[MAXC], s_nq[MAXC], s_pieces[MAXC], s_tile0[MAXC], s_slot0[MAXC], s_merge0[MAXC], s_tot[MAXC];
   __shared__ int32_t s_chunk;
   const int C = min(Cq, MAXC);
   for (int c = tid; c < C; c += 256) {
     s_nq[c] = (qo[c + 1] - qo[c] + BM - 1) / BM;
     const int tot = rng_pre[((size_t)h * Cq + c) * (maxr + 1) + rng_cnt[(size_t)h * Cq + c]];
     s_T[c] = (tot + 63) / 64;
+    s_tot[c] = tot;
   }
   __syncthreads();
   if (tid == 0) {
@@ -247,7 +200,7 @@ __global__ __launch_bounds__(256) void plan_tiles(int Cq, int maxr, int maxtiles
         int32_t* t6 = tl + (size_t)nt * TILE_REC;
         t6[0] = c; t6[1] = r0; t6[2] = rows;
         t6[3] = pieces > 1 ? k * per : 0; t6[4] = pieces > 1 ? min(T, (k + 1) * per) : T;
-        t6[5] = pieces > 1 ? slot + k : -1;
+        t6[5] = pieces > 1 ? slot + k : -1; t6[6] = s_tot[c]; t6[7] = 0;
         ++nt;
       }
       if (pieces > 1) slot += pieces;
@@ -256,17 +209,16 @@ __global__ __launch_bounds__(256) void plan_tiles(int Cq, int maxr, int maxtiles
 }
 
 // dense: one query "cluster" over all rows, one key range [0,N)
-__global__ void plan_dense(int N, int maxtiles, int BM, int row_bytes, int32_t* __restrict__ rng_start,
+__global__ void plan_dense(int N, int maxtiles, int BM, int row_scale, int32_t* __restrict__ rng_start,
                            int32_t* __restrict__ rng_pre, int32_t* __restrict__ rng_cnt,
                            int32_t* __restrict__ tiles, int32_t* __restrict__ ntiles,
                            int32_t* __restrict__ krow, size_t kstride) {
   const int h = blockIdx.x;
   if (blockIdx.y > 0) {       // the other workgroups of a head fill its row-offset table (the identity)
-    if (!krow) return;
     int32_t* kr = krow + (size_t)h * kstride;
     const int padded = (N + 63) / 64 * 64 + KROW_PAD;
     for (int p = (blockIdx.y - 1) * blockDim.x + threadIdx.x; p < padded; p += (gridDim.y - 1) * blockDim.x)
-      kr[p] = p < N ? p * row_bytes : 0;
+      kr[p] = p < N ? p * row_scale : 0;
     return;
   }
   if (threadIdx.x == 0) {
@@ -276,7 +228,7 @@ __global__ void plan_dense(int N, int maxtiles, int BM, int row_bytes, int32_t* 
   int32_t* tl = tiles + (size_t)h * maxtiles * TILE_REC;
   for (int t = threadIdx.x; t * BM < N; t += blockDim.x) {
     int32_t* t6 = tl + (size_t)t * TILE_REC;
-    t6[0] = 0; t6[1] = t * BM; t6[2] = min(BM, N - t * BM); t6[3] = 0; t6[4] = (N + 63) / 64; t6[5] = -1;
+    t6[0] = 0; t6[1] = t * BM; t6[2] = min(BM, N - t * BM); t6[3] = 0; t6[4] = (N + 63) / 64; t6[5] = -1; t6[6] = N; t6[7] = 0;
   }
 }
 
@@ -325,37 +277,47 @@ int launch_attn_stats(hipStream_t s, int H, int Cq, int maxr, int maxtiles, cons
 }
 
 struct AttnArgs {
-  const void* Q; const void* Kp; const void* Vp; void* O;
+  const void* Q; const void* K; const void* V; void* O;
   const int32_t* perm_q;        // sorted query position -> token (NULL: identity)
   const int32_t* tiles; const int32_t* ntiles;
-  const int32_t* rng_start; const int32_t* rng_pre; const int32_t* rng_cnt;
-  int N, Cq, maxtiles, maxr;
+  const int32_t* rng_pre; const int32_t* rng_cnt;
+  int H, N, Cq, maxtiles, maxr;
   float scale_log2e;            // softmax scale x log2(e)
   int head_major;               // workgroup -> (head, tile) mapping, see attn_mfma
   float* part_o; float* part_ml;   // partial slots of cut key lists: [H][slots][BM][d], [H][slots][BM][2]
   int slots, BM;
-  const int32_t* krow; size_t kstride;   // byte offset of every key row of a query cluster's list: [H][Cq][kstride]
+  const int32_t* krow; size_t kstride;   // every key row of a query cluster's list (byte offset, fp32: row number): [H][Cq][kstride]
 };
 
-// position in the concatenation of ranges -> permuted key row; a cursor that only moves forward
-template <typename PTR>
-struct RangeCursorT {
-  PTR rs; PTR rp; int nr; int r; int cur_end; int delta;
-  __device__ __forceinline__ void init(PTR rs_, PTR rp_, int nr_) {
-    rs = rs_; rp = rp_; nr = nr_; r = 0;
-    cur_end = nr > 0 ? rp[1] : 0;
-    delta = nr > 0 ? rs[0] - rp[0] : 0;
-  }
-  __device__ __forceinline__ int row(int p) {      // p is non-decreasing across calls
-    while (r < nr && p >= cur_end) {
-      ++r;
-      if (r < nr) { cur_end = rp[r + 1]; delta = rs[r] - rp[r]; }
+// Workgroup -> (head, query tile).  Workgroups go to the 8 XCDs round-robin in launch order, each with its own L2, so
+// XCD = blockIdx.x % 8 and blockIdx.x / 8 is a slot in that XCD's own list of tiles: of every head, in head order, the
+// XCD takes a contiguous eighth (the tiles of one query cluster stream the same K/V rows, and so do it behind the
+// same L2).  Only the device knows how many tiles a head has; the list is cut from those counts here, so that the
+// workgroups without work are the last of the grid.  (With a grid row per head, sized for the most tiles a head
+// could have, more than half of the workgroups were empty ones between the heads, and each takes its turn on a
+// CU.)
+// `parts`: workgroups per tile.  Returns false where the list has ended.
+__device__ __forceinline__ bool pick_tile(const int32_t* __restrict__ ntiles, int H, int parts, int& h, int& tile) {
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, lane = threadIdx.x & 63;
+  int base = 0;
+  for (int h0 = 0; h0 < H; h0 += 64) {                     // 64 heads at a time, one per lane
+    const int nt = h0 + lane < H ? parts * ntiles[h0 + lane] : 0;
+    const int w = (nt + 7) >> 3;                           // this XCD's share of the head (the last XCD's may be short)
+    int incl = w;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
+    const uint64_t past = __ballot(base + incl > slot);
+    if (past) {
+      const int l = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)past) - 1);
+      const int wl = __builtin_amdgcn_readlane(w, l);
+      h = h0 + l;
+      tile = xcd * wl + slot - base - __builtin_amdgcn_readlane(incl, l) + wl;
+      return tile < __builtin_amdgcn_readlane(nt, l);
     }
-    return r < nr ? p + delta : -1;
+    base += __builtin_amdgcn_readlane(incl, 63);
   }
-};
-typedef RangeCursorT<const int32_t*> RangeCursor;
-typedef __attribute__((address_space(3))) const int32_t lds_ci32_t;
+  return false;
+}
 
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA kernel
@@ -379,6 +341,9 @@ __device__ __forceinline__ s16x4_t lds_read_tr16(const char* p) {
 // loads `bytes` at sbase + voff; the wave's data land at lds_addr + lane * bytes (M0 carries the LDS address).
 __device__ __forceinline__ void dma_b128(uint32_t lds_addr, uint32_t voff, const void* sbase) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(sbase) : "memory", "m0");
+}
+__device__ __forceinline__ void dma_b128(uint32_t lds_addr, const void* src) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(src) : "memory", "m0");
 }
 __device__ __forceinline__ void dma_b32(uint32_t lds_addr, uint32_t voff, const void* sbase) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(sbase) : "memory", "m0");
@@ -466,8 +431,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
   const int32_t* krow = a.krow + ((size_t)h * a.Cq + qc) * a.kstride + pbase;   // byte offsets of the key rows
 
   const bf16raw* Qh = (const bf16raw*)a.Q + (size_t)h * a.N * D;
-  const char* Kh = (const char*)a.Kp + (size_t)h * a.N * ROWB;
-  const char* Vh = (const char*)a.Vp + (size_t)h * a.N * ROWB;
+  const char* Kh = (const char*)a.K + (size_t)h * a.N * ROWB;
+  const char* Vh = (const char*)a.V + (size_t)h * a.N * ROWB;
   bf16raw* Oh = (bf16raw*)a.O + (size_t)h * a.N * D;
   const int32_t* pq = a.perm_q ? a.perm_q + (size_t)h * a.N : nullptr;
 
@@ -799,42 +764,79 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
 // fp32 kernel (the accuracy path of fp32 inputs): the same S^T = K Q^T / O^T += V^T P^T walk on the
 // matrix cores with v_mfma_f32_32x32x2_f32 (fp32 products, fp32 accumulation)
 // ------------------------------------------------------------------------------------------
-// A workgroup is two waves of 32 queries; key tiles of 32 rows go through LDS.  In the 32x32 accumulator a
-// lane (c = lane % 32, hb = lane / 32) owns query c and the keys 8*(v/4) + 4*hb + v%4 of the tile, v = 0..15.
-// The two values a lane pair supplies per product step may be any pair of the contraction index as long as
-// both operands agree: for S the pair is (dim ks, dim D/2 + ks), so a lane keeps one contiguous half of its
-// query row; for P.V step j contracts exactly the keys of accumulator value j, so the probabilities are the
-// B operand as they stand and no value crosses the half-waves.  K rows are padded to D + 1 floats and V rows
-// to D + 8, which spreads the operand reads of a step over the banks.
-template <int D>
-__global__ __launch_bounds__(128) void attn_f32(AttnArgs a) {
-  constexpr int BN = 32, HD = D / 2, KP = D + 1, VP = D + 8, DB = D / 32, NT = 128;
-  const int h = blockIdx.y, tile = blockIdx.x;
-  if (tile >= a.ntiles[h]) return;
-  const int32_t* tl = a.tiles + ((size_t)h * a.maxtiles + tile) * TILE_REC;   // (key lists are never cut for fp32)
-  const int qc = tl[0], row0 = tl[1], nrows = tl[2];
+// A workgroup is half a query tile, 32 queries; its four waves take every fourth 32-key tile of the key list, each
+// with an accumulator and soft-max state of its own, and meet once at the end.  In the 32x32 accumulator a lane
+// (c = lane % 32, hb = lane / 32) owns query c and the keys 8*(v/4) + 4*hb + v%4 of the tile, v = 0..15.  The
+// two values a lane pair supplies per product step may be any pair of the contraction index as long as both
+// operands agree: for S step 4*i + j the pair is (dim 8*i + j, dim 8*i + 4 + j), so that a lane takes a 16-byte piece of
+// its row for four steps; for P V step j contracts exactly the keys of accumulator value j, so the probabilities
+// are the B operand as they stand, and the A operand takes the columns c*DB .. +DB-1 of a V row per lane (column
+// block db of the accumulator is then the columns i*DB + db), one coalesced vector load a key and no LDS.
+// K tiles go global -> LDS directly into an area of the wave's own, row by row (loaded straight into registers a
+// lane would have to fetch its own row, 64 lines per load): the next tile is requested in the middle of the P V
+// products; V rows are requested around the S products.  No barrier inside the loop.
+// Slot s (16 bytes) of row r holds piece s ^ (r & 15): the operand reads of 16 consecutive rows hit 16 bank groups.
+// What bounds the path: the fp32 matrix rate (a product of 32x32x2 holds the pipe for 64 cycles) once there are
+// workgroups enough, which is why the key list is split: over the waves, and where the launch is small (4 096
+// queries are 128 half tiles for 256 CUs) over gridDim.z workgroups as well, which leave unnormalised partial results
+// that attn_merge_f32 combines (see attn_f32_splits).  Vector instructions do not run under an fp32 product on this chip
+// (the co-execution counter reads 0), so every one of them adds its four cycles: the masks are for the last tile
+// only, the accumulator is rescaled only when the maximum has moved, and addresses inside a head are 32-bit offsets
+// (WIDE: 64-bit, for heads of 4 GiB and more).  Without these the 545 vector instructions a tile took a fifth of the time.
+// Measured against a kernel of two waves of 32 queries a workgroup with K and V through LDS and three barriers a tile:
+// dense, d=128, 4 heads x 8 192 rows 71 -> 130 TFLOP/s (of 153 that an fp32 GEMM reaches), 1 x 4 096 9 -> 103; one head of
+// 4 096 queries (d=64) against a quarter of its keys 190 -> 33 us, three of 5 007 (d=128) against a third 533 -> 225 us.
+// (Eight waves a workgroup, one workgroup a CU: 37 and 237 us.)
+template <int D, bool WIDE>
+__global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
+  constexpr int BN = 32, DB = D / 32, NW = F32_WAVES, SROW = D + 4, PPR = D / 4, RPI = 64 / PPR;   // 16-byte pieces a row, rows a load
+  int h, tile;                                             // (tile: half of a 64-query tile)
+  if (!pick_tile(a.ntiles, a.H, 2, h, tile)) return;
+  const int32_t* tl = a.tiles + ((size_t)h * a.maxtiles + (tile >> 1)) * TILE_REC;   // (key lists are never cut for fp32)
+  const int qc = tl[0], row0 = tl[1] + (tile & 1) * 32, nrows = min(tl[2] - (tile & 1) * 32, 32);
+  if (nrows <= 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, hb = lane >> 5;
-  const int nr = a.rng_cnt[(size_t)h * a.Cq + qc];
-  const int32_t* rs = a.rng_start + ((size_t)h * a.Cq + qc) * a.maxr;
-  const int32_t* rp = a.rng_pre + ((size_t)h * a.Cq + qc) * (a.maxr + 1);
-  const int total = rp[nr];
+  const int total = tl[6], T = (total + BN - 1) / BN;
+  const int32_t* kr = a.krow + ((size_t)h * a.Cq + qc) * a.kstride;           // key rows of the list, in order
   const float* Qh = (const float*)a.Q + (size_t)h * a.N * D;
-  const float* Kh = (const float*)a.Kp + (size_t)h * a.N * D;
-  const float* Vh = (const float*)a.Vp + (size_t)h * a.N * D;
-  float* Oh = (float*)a.O + (size_t)h * a.N * D;
-  __shared__ float Ks[BN * KP];
-  __shared__ __attribute__((aligned(16))) float Vs[BN * VP];
-  __shared__ int32_t ridx[BN];
-  const int qrow = wave * 32 + c;
-  int tok = -1;
-  if (qrow < nrows) tok = a.perm_q ? a.perm_q[(size_t)h * a.N + row0 + qrow] : row0 + qrow;
-  float q[HD];
+  const char* Kh = (const char*)((const float*)a.K + (size_t)h * a.N * D);
+  const char* Vh = (const char*)((const float*)a.V + (size_t)h * a.N * D);
+  typedef typename std::conditional<WIDE, size_t, uint32_t>::type off_t;
+  // a wave's K tile in the loop; after it, its accumulator, a (padded) row per query
+  __shared__ __attribute__((aligned(16))) float sk[NW * 32 * SROW];
+  __shared__ float sm[NW][32], sl[NW][32];
+  char* const kt = reinterpret_cast<char*>(sk) + __builtin_amdgcn_readfirstlane(wave) * (BN * D * 4);
+  const uint32_t kt_lds = (uint32_t)(uintptr_t)(lds_void_t*)kt;
+  const int32_t* pq = a.perm_q ? a.perm_q + (size_t)h * a.N : nullptr;
+  // The addresses of a tile are worked out anew for every tile (the empty asm statements hide that they do not
+  // change): hoisted out of the loop they would take 50 registers that are not there.
+  auto issue_k = [&](int idx) __attribute__((always_inline)) {                // idx: row number of key c, in every lane
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const int lr = ln / PPR, lp = ln % PPR;                // row and piece of the RPI rows that one direct load brings
 #pragma unroll
-  for (int j = 0; j < HD; j += 4) {
-    float4 v = {0.f, 0.f, 0.f, 0.f};
-    if (tok >= 0) v = *reinterpret_cast<const float4*>(Qh + (size_t)tok * D + hb * HD + j);
-    q[j] = v.x; q[j + 1] = v.y; q[j + 2] = v.z; q[j + 3] = v.w;
+    for (int n = 0; n < BN / RPI; ++n) {
+      const int row = __builtin_amdgcn_ds_bpermute(lr * 4 + n * RPI * 4, idx);
+      const uint32_t piece = (uint32_t)(lp ^ ((n * RPI + lr) & 15)) * 16;
+      const off_t off = (off_t)(uint32_t)row * (D * 4) + piece;
+      if constexpr (WIDE) dma_b128(kt_lds + n * 1024, Kh + off);
+      else dma_b128(kt_lds + n * 1024, off, Kh);
+    }
+  };
+  // (the table is padded: entries past the list are rows that exist, and masked)
+  const int t0 = blockIdx.z * NW + wave, tstep = gridDim.z * NW;
+  int kidx = 0;
+  if (t0 < T) { kidx = kr[t0 * BN + c]; issue_k(kidx); }
+  float q[D / 2];
+  {
+    const int r = row0 + min(c, nrows - 1);                // (rows past the end repeat the last one and are not stored)
+    const float* qp = Qh + (size_t)(pq ? pq[r] : r) * D + hb * 4;
+#pragma unroll
+    for (int i = 0; i < D / 8; ++i) {
+      const float4 v = *reinterpret_cast<const float4*>(qp + 8 * i);
+      q[4 * i] = v.x; q[4 * i + 1] = v.y; q[4 * i + 2] = v.z; q[4 * i + 3] = v.w;
+    }
   }
   f32x16_t o[DB];
 #pragma unroll
@@ -842,70 +844,170 @@ __global__ __launch_bounds__(128) void attn_f32(AttnArgs a) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
   float m = -INFINITY, l = 0.f;
-  RangeCursor cur;
-  if (tid < BN) cur.init(rs, rp, nr);
-  for (int k0 = 0; k0 < total; k0 += BN) {
-    __syncthreads();                                   // the previous tile has been consumed
-    if (tid < BN) ridx[tid] = cur.row(k0 + tid);
-    __syncthreads();
-    for (int i = tid; i < BN * D / 4; i += NT) {
-      const int r = i / (D / 4), qd = i % (D / 4);
-      const int row = ridx[r];
-      float4 kv = {0.f, 0.f, 0.f, 0.f}, vv = {0.f, 0.f, 0.f, 0.f};
-      if (row >= 0) {
-        kv = reinterpret_cast<const float4*>(Kh + (size_t)row * D)[qd];
-        vv = reinterpret_cast<const float4*>(Vh + (size_t)row * D)[qd];
+  for (int t = t0; t < T; t += tstep) {
+    wait_vmcnt<0>();                                       // the K tile has landed
+    asm volatile("" ::: "memory");
+    float vv[16][DB];
+    const int vidx = kidx;
+    auto load_v = [&](int j) __attribute__((always_inline)) {      // key 8*(j/4) + 4*hb + j%4: its row number is in that lane
+      const int row = __builtin_amdgcn_ds_bpermute(hb * 16 + (8 * (j >> 2) + (j & 3)) * 4, vidx);
+      const char* vp = Vh + ((off_t)(uint32_t)row * (D * 4) + (uint32_t)(c * DB * 4));
+      if constexpr (DB == 4) {
+        const float4 x = *reinterpret_cast<const float4*>(vp);
+        vv[j][0] = x.x; vv[j][1] = x.y; vv[j][2] = x.z; vv[j][3] = x.w;
+      } else {
+        const float2 x = *reinterpret_cast<const float2*>(vp);
+        vv[j][0] = x.x; vv[j][1] = x.y;
       }
-      float* kd = &Ks[r * KP + 4 * qd];
-      kd[0] = kv.x; kd[1] = kv.y; kd[2] = kv.z; kd[3] = kv.w;
-      *reinterpret_cast<float4*>(&Vs[r * VP + 4 * qd]) = vv;
+    };
+    // Half of the V rows are requested here, half behind the S products (they are needed last): with all of them in
+    // flight the K operands would be left a single register quad, and every fourth product would wait out an LDS read.
+#pragma unroll
+    for (int j = 0; j < 8; ++j) load_v(j);
+    if (t + tstep < T) kidx = kr[(t + tstep) * BN + c];
+    __builtin_amdgcn_sched_barrier(0);
+    f32x16_t s;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[v] = 0.f;
+    // piece 2*i + hb of row c: slot (2*i + hb) ^ (c & 15) below 16 (d=128: pieces 16 .. 31 lie 256 bytes on)
+    int ka0 = c * (D * 4) + ((hb ^ (c & 15)) * 16);
+    asm volatile("" : "+v"(ka0));
+    auto k_piece = [&](int i) __attribute__((always_inline)) {
+      return *reinterpret_cast<const float4*>(kt + (ka0 ^ ((i & 7) * 32)) + (i >> 3) * 256);
+    };
+    constexpr int KA = 4;                                  // K pieces read ahead
+    float4 kb[KA];
+#pragma unroll
+    for (int i = 0; i < KA; ++i) kb[i] = k_piece(i);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < D / 8; ++i) {
+      const float4 k4 = kb[i % KA];
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(k4.x, q[4 * i], s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(k4.y, q[4 * i + 1], s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(k4.z, q[4 * i + 2], s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(k4.w, q[4 * i + 3], s, 0, 0, 0);
+      if (i + KA < D / 8) kb[i % KA] = k_piece(i + KA);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();
-    f32x16_t sacc;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
+    for (int j = 8; j < 16; ++j) load_v(j);
+    __builtin_amdgcn_sched_barrier(0);
+    const int kn = total - t * BN;                         // keys of this tile that exist (>= 1)
+    if (kn < BN) {
 #pragma unroll
-    for (int ks = 0; ks < HD; ++ks)
-      sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(Ks[c * KP + hb * HD + ks], q[ks], sacc, 0, 0, 0);
-    const int kn = total - k0;                          // keys of this tile that exist (>= 1)
-    float tmax = -INFINITY;
+      for (int v = 0; v < 16; ++v)
+        if (8 * (v >> 2) + 4 * hb + (v & 3) >= kn) s[v] = -INFINITY;
+    }
+    // m is the running maximum of the raw scores; probabilities are 2^((s - m) scale)
+    float tmax = fmaxf(fmaxf(s[0], s[1]), s[2]);
+#pragma unroll
+    for (int v = 3; v < 15; v += 2) tmax = fmaxf(fmaxf(tmax, s[v]), s[v + 1]);
+    tmax = fmaxf(tmax, s[15]);
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+    if (__any(tmax > m)) {
+      const float mnew = fmaxf(m, tmax);                   // finite: the tile holds at least one key
+      const float alpha = __builtin_amdgcn_exp2f((m - mnew) * a.scale_log2e);
+      m = mnew;
+      l *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
+    }
+    const float moff = m * a.scale_log2e;
+    float lsum[2] = {0.f, 0.f};
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int key = 8 * (v >> 2) + 4 * hb + (v & 3);
-      sacc[v] = key < kn ? sacc[v] * a.scale_log2e : -INFINITY;
-      tmax = fmaxf(tmax, sacc[v]);
+      s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], a.scale_log2e, -moff));
+      lsum[v & 1] += s[v];
     }
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-    const float mnew = fmaxf(m, tmax);                  // finite: the tile holds at least one key
-    const float alpha = exp2f(m - mnew);
-    float lsum = 0.f;
+    l += lsum[0] + lsum[1];                                // (this half-wave's keys; the halves meet at the end)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) { sacc[v] = exp2f(sacc[v] - mnew); lsum += sacc[v]; }
-    lsum += __shfl_xor(lsum, 32);
-    l = l * alpha + lsum;
-    m = mnew;
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int key = 8 * (j >> 2) + 4 * hb + (j & 3);
-        o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(Vs[key * VP + db * 32 + c], sacc[j], o[db], 0, 0, 0);
+    for (int j = 0; j < 16; ++j) {
+      if (j == 8) {
+        // All V rows have landed before the next K tile is requested: the compiler does not know of the direct
+        // loads, so a wait of its own for a V row would wait for them too.
+        wait_vmcnt<0>();
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + tstep < T) issue_k(kidx);
+        __builtin_amdgcn_sched_barrier(0);
       }
+#pragma unroll
+      for (int db = 0; db < DB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[j][db], s[j], o[db], 0, 0, 0);
     }
   }
-  // value v of dim block db is dim db*32 + 8*(v/4) + 4*hb + v%4 of query c
-  if (tok >= 0) {
-    const float inv = l > 0.f ? 1.0f / l : 0.f;
+  __syncthreads();                                         // every wave is done with its K tile: the area changes its use
+  // value v of column block db is column i*DB + db, i = 8*(v/4) + 4*hb + v%4, of query c
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float4 o4 = {o[db][4 * g] * inv, o[db][4 * g + 1] * inv, o[db][4 * g + 2] * inv, o[db][4 * g + 3] * inv};
-        *reinterpret_cast<float4*>(Oh + (size_t)tok * D + db * 32 + 8 * g + 4 * hb) = o4;
-      }
+  for (int v = 0; v < 16; ++v) {
+    float* out = &sk[(wave * 32 + c) * SROW + (8 * (v >> 2) + 4 * hb + (v & 3)) * DB];
+    if constexpr (DB == 4) *reinterpret_cast<float4*>(out) = float4{o[0][v], o[1][v], o[2][v], o[3][v]};
+    else *reinterpret_cast<float2*>(out) = float2{o[0][v], o[1][v]};
   }
+  l += __shfl_xor(l, 32);
+  if (hb == 0) { sm[wave][c] = m * a.scale_log2e; sl[wave][c] = l; }
+  __syncthreads();
+  // O = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w, 2 NW threads a query; a wave without a tile has m = -inf and
+  // l = 0, and if none had one (empty list) the output is zero
+  constexpr int TPQ = 2 * NW;
+  const int r = tid / TPQ, col = (tid % TPQ) * 4;
+  if (r >= nrows) return;
+  float M = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) M = fmaxf(M, sm[w][r]);
+  float wt[NW], L = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    wt[w] = M > -INFINITY ? exp2f(sm[w][r] - M) : 0.f;
+    L = fmaf(wt[w], sl[w][r], L);
+  }
+  float inv = L > 0.f ? 1.0f / L : 0.f;
+  float* out = (float*)a.O + ((size_t)h * a.N + (pq ? pq[row0 + r] : row0 + r)) * D;
+  if (gridDim.z > 1) {                                     // a partial result: as it is, with its reference and sum
+    const size_t pr = ((size_t)h * gridDim.z + blockIdx.z) * a.N + row0 + r;
+    inv = 1.f;
+    out = a.part_o + pr * D;
+    if (col == 0) { a.part_ml[pr * 2] = M; a.part_ml[pr * 2 + 1] = L; }
+  }
+#pragma unroll
+  for (int cc = 0; cc < D; cc += TPQ * 4) {
+    float4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float4 y = *reinterpret_cast<const float4*>(&sk[(w * 32 + r) * SROW + col + cc]);
+      x.x = fmaf(wt[w], y.x, x.x); x.y = fmaf(wt[w], y.y, x.y); x.z = fmaf(wt[w], y.z, x.z); x.w = fmaf(wt[w], y.w, x.w);
+    }
+    *reinterpret_cast<float4*>(out + col + cc) = float4{x.x * inv, x.y * inv, x.z * inv, x.w * inv};
+  }
+}
+
+// The partial results of a row's `splits` workgroups: O = sum_z 2^(M_z - M) O_z / sum_z 2^(M_z - M) L_z.
+template <int D>
+__global__ __launch_bounds__(256) void attn_merge_f32(AttnArgs a, int splits) {
+  constexpr int LPR = D / 4;
+  const int h = blockIdx.y, pos = blockIdx.x * (256 / LPR) + threadIdx.x / LPR, col = (threadIdx.x % LPR) * 4;
+  if (pos >= a.N) return;
+  float M = -INFINITY, L = 0.f, ms[F32_MAX_SPLITS], ls[F32_MAX_SPLITS];
+  float4 os[F32_MAX_SPLITS], x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int z = 0; z < F32_MAX_SPLITS; ++z) {
+    const size_t pr = ((size_t)h * splits + min(z, splits - 1)) * a.N + pos;
+    ms[z] = z < splits ? a.part_ml[pr * 2] : -INFINITY;
+    ls[z] = a.part_ml[pr * 2 + 1];
+    os[z] = *reinterpret_cast<const float4*>(a.part_o + pr * D + col);
+  }
+#pragma unroll
+  for (int z = 0; z < F32_MAX_SPLITS; ++z) M = fmaxf(M, ms[z]);
+#pragma unroll
+  for (int z = 0; z < F32_MAX_SPLITS; ++z) {
+    const float w = ms[z] > -INFINITY ? exp2f(ms[z] - M) : 0.f;
+    L = fmaf(w, ls[z], L);
+    x.x = fmaf(w, os[z].x, x.x); x.y = fmaf(w, os[z].y, x.y); x.z = fmaf(w, os[z].z, x.z); x.w = fmaf(w, os[z].w, x.w);
+  }
+  const float inv = L > 0.f ? 1.0f / L : 0.f;
+  const int tok = a.perm_q ? a.perm_q[(size_t)h * a.N + pos] : pos;
+  *reinterpret_cast<float4*>((float*)a.O + ((size_t)h * a.N + tok) * D + col) = float4{x.x * inv, x.y * inv, x.z * inv, x.w * inv};
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1003,15 +1105,25 @@ int attn_block_rows_max(int dtype) { return dtype == ADACLUSTER_BF16 ? 256 : 64;
 
 size_t attn_krow_stride(int N) { return (size_t)(N + 63) / 64 * 64 + KROW_PAD; }
 
+int attn_tile_record() { return TILE_REC; }
 int attn_split_slots() { return SPLIT_SLOTS; }
+
+// Workgroups a key list of the fp32 kernel is split over, enough for four a CU: a CU holds two (d=128), and with fewer
+// the CUs that are left over, or the last workgroups to run, are what the launch waits for.  Kernel and merge with
+// targets of 128, 512 and 1 024 workgroups: one head of 4 096 queries (d=64, a quarter of the keys) 39, 32 and 33 us,
+// three of 5 007 (d=128, a third of the keys) 267, 263 and 225 us, dense 1 x 4 096 (d=128) 149, 83 and 83 us.
+int attn_f32_splits(int H, int N, int Cq) {
+  const long long wgs = (long long)H * (N / 32 + Cq / 2 + 1);
+  return (int)min((long long)F32_MAX_SPLITS, (1024 + wgs - 1) / wgs);
+}
 
 int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
                        const int32_t* q_offs, int q_offs_stride, const int32_t* k_offs, int k_offs_stride,
                        const int32_t* k_count, const int32_t* sel_idx, const int32_t* sel_cnt,
                        int32_t* rng_start, int32_t* rng_pre, int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles,
-                       int32_t* merge, int32_t* nmerge, int row_bytes, int32_t* krow, size_t kstride,
+                       int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride,
                        const int32_t* perm_k, int N) {
-  plan_sparse<<<dim3(Cq, H), 256, 0, s>>>(Cq, cap, maxr, row_bytes, k_offs, k_offs_stride, k_count, sel_idx, sel_cnt,
+  plan_sparse<<<dim3(Cq, H), 256, 0, s>>>(Cq, cap, maxr, row_scale, k_offs, k_offs_stride, k_count, sel_idx, sel_cnt,
                                          rng_start, rng_pre, rng_cnt, krow, kstride, perm_k, N);
   plan_tiles<<<H, 256, 0, s>>>(Cq, maxr, maxtiles, BM, SPLIT_SLOTS, dtype == ADACLUSTER_BF16 ? 1 : 0, q_offs,
                               q_offs_stride, rng_pre, rng_cnt, tiles, ntiles, merge, nmerge);
@@ -1019,17 +1131,17 @@ int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int max
 }
 
 int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, int BM, int32_t* rng_start, int32_t* rng_pre,
-                      int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles, int row_bytes, int32_t* krow, size_t kstride) {
-  plan_dense<<<dim3(H, 9), 256, 0, s>>>(N, maxtiles, BM, row_bytes, rng_start, rng_pre, rng_cnt, tiles, ntiles, krow, kstride);
+                      int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles, int row_scale, int32_t* krow, size_t kstride) {
+  plan_dense<<<dim3(H, 9), 256, 0, s>>>(N, maxtiles, BM, row_scale, rng_start, rng_pre, rng_cnt, tiles, ntiles, krow, kstride);
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
 }
 
 int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int maxtiles, int maxr, float scale,
-                     const void* Q, const void* Kp, const void* Vp, void* O, const int32_t* perm_q,
-                     const int32_t* tiles, const int32_t* ntiles, const int32_t* rng_start,
-                     const int32_t* rng_pre, const int32_t* rng_cnt, float* part_o, float* part_ml,
+                     const void* Q, const void* K, const void* V, void* O, const int32_t* perm_q,
+                     const int32_t* tiles, const int32_t* ntiles, const int32_t* rng_pre,
+                     const int32_t* rng_cnt, float* part_o, float* part_ml,
                      const int32_t* merge, const int32_t* nmerge, const int32_t* krow, size_t kstride) {
-  AttnArgs a{Q, Kp, Vp, O, perm_q, tiles, ntiles, rng_start, rng_pre, rng_cnt, N, Cq, maxtiles, maxr,
+  AttnArgs a{Q, K, V, O, perm_q, tiles, ntiles, rng_pre, rng_cnt, H, N, Cq, maxtiles, maxr,
              scale * 1.4426950408889634f,
              (Cq == 1 || (size_t)4 * N * d <= ((size_t)8 << 20)) ? 1 : 0,
              part_o, part_ml, SPLIT_SLOTS, attn_block_rows(dtype, d, N, Cq), krow, kstride};
@@ -1047,8 +1159,15 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
       else attn_merge<128><<<dim3(SPLIT_SLOTS, H, 4), 256, 0, s>>>(a, merge, nmerge);
     }
   } else {
-    if (d == 64) attn_f32<64><<<g, 128, 0, s>>>(a);
-    else attn_f32<128><<<g, 128, 0, s>>>(a);
+    const int splits = attn_f32_splits(H, N, Cq);
+    const bool wide = (size_t)N * d * 4 >= ((size_t)1 << 32);
+    const dim3 g2(8 * H * ((2 * (N / 64 + Cq + 1) + 7) / 8), 1, splits), gm((N + 1024 / d - 1) / (1024 / d), H);
+    if (d == 64) { if (wide) attn_f32<64, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<64, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
+    else { if (wide) attn_f32<128, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<128, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
+    if (splits > 1) {
+      if (d == 64) attn_merge_f32<64><<<gm, 256, 0, s>>>(a, splits);
+      else attn_merge_f32<128><<<gm, 256, 0, s>>>(a, splits);
+    }
   }
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
 }

@@ -92,28 +92,28 @@ int launch_select(hipStream_t s, int H, int Cq, int cap, int d, int score_mode, 
 int attn_block_rows(int dtype, int d, int N, int Cq);   // queries per workgroup of the attention launch
 int attn_block_rows_min(int dtype);
 int attn_block_rows_max(int dtype);
-int launch_permute_kv(hipStream_t s, int H, int N, int row_bytes, const void* K, const void* V,
-                      const int32_t* perm, void* Kp, void* Vp);
 int launch_quest_scores(hipStream_t s, int dtype, int form, int clamp, int H, int Lq, int Lk, int d, const void* Q,
                         const void* Rp, const void* Rn, float* S);
 // register-only loop of bf16 MFMAs on every SIMD of the chip (measures what the matrix cores sustain)
 int launch_mfma_probe(hipStream_t s, int iters, float* sink, size_t sink_floats, double* flops);
+int attn_f32_splits(int H, int N, int Cq);   // workgroups a key list of the fp32 kernel is split over
+int attn_tile_record();      // ints per query-tile record
 int attn_split_slots();      // partial slots per head for the chunks of cut key lists (also extra tile records)
 int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
                        const int32_t* q_offs, int q_offs_stride, const int32_t* k_offs, int k_offs_stride,
                        const int32_t* k_count, const int32_t* sel_idx, const int32_t* sel_cnt,
                        int32_t* rng_start, int32_t* rng_pre, int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles,
-                       int32_t* merge, int32_t* nmerge, int row_bytes, int32_t* krow, size_t kstride, const int32_t* perm_k = nullptr, int N = 0);
+                       int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride, const int32_t* perm_k, int N);
 int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, int BM, int32_t* rng_start, int32_t* rng_pre,
-                      int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles, int row_bytes, int32_t* krow, size_t kstride);
-// entries per (head, query cluster) of the table of key-row byte offsets the bf16 attention kernel loads by
+                      int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles, int row_scale, int32_t* krow, size_t kstride);
+// entries per (head, query cluster) of the table of key rows (times row_scale) that the attention kernels load by
 size_t attn_krow_stride(int N);
 int launch_attn_stats(hipStream_t s, int H, int Cq, int maxr, int maxtiles, const KState* st, const int32_t* tiles,
                       const int32_t* ntiles, const int32_t* rng_pre, const int32_t* rng_cnt, adacluster_head_stats* out);
 int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int maxtiles, int maxr, float scale,
-                     const void* Q, const void* Kp, const void* Vp, void* O, const int32_t* perm_q,
-                     const int32_t* tiles, const int32_t* ntiles, const int32_t* rng_start,
-                     const int32_t* rng_pre, const int32_t* rng_cnt, float* part_o, float* part_ml,
+                     const void* Q, const void* K, const void* V, void* O, const int32_t* perm_q,
+                     const int32_t* tiles, const int32_t* ntiles, const int32_t* rng_pre,
+                     const int32_t* rng_cnt, float* part_o, float* part_ml,
                      const int32_t* merge /* NULL: no cut lists */, const int32_t* nmerge,
                      const int32_t* krow, size_t kstride);
 

@@ -88,7 +88,7 @@ def mfma_microbench_tflops(B, iters=20000):
 def measure(name, steps, warmup, spinup_ms=500.0, dense_steps=3, profile_reps=None, want_hbm=True):
     """One configuration, end to end: the fused call cold and warm-started, its stage times, the dense call
     on the same kernel, the attention kernel against the bf16 MFMA peak, and the HBM-bound passes (label
-    sorts, segmented reduction, and for fp32 inputs the K/V row gather) against the HBM peak.  Returns a
+    sorts, segmented reduction) against the HBM peak.  Returns a
     dict of plain numbers."""
     import torch
     from . import binding as B
@@ -182,8 +182,6 @@ def measure(name, steps, warmup, spinup_ms=500.0, dense_steps=3, profile_reps=No
             if ms_ and ms_ > 0:
                 gbs = nbytes / (ms_ * 1e-3) / 1e9
                 hbm[key] = {"ms": ms_, "bytes": nbytes, "GB/s": gbs, "frac": gbs / HBM_PEAK_GBS, "what": what}
-        entry("gather_rows2", pr.get("permute"), 4.0 * rows * d * es + 4.0 * rows,
-              "K and V rows read and written once, permutation read")
         sort_bytes = lambda passes: (16.0 + 20.0 * (passes - 1)) * rows
         entry("label_sorts", pr.get("select"), sort_bytes(q_passes) + sort_bytes(k_passes),
               "query labels (%d radix pass) and key labels (%d): per item and pass 4 B read to count, 4 B (first "

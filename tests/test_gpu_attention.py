@@ -181,3 +181,21 @@ def test_large_logits_do_not_overflow():
     O = to_np(B.adacluster_dense_attn(p, to_dev(Q, B.BF16), to_dev(K, B.BF16), to_dev(V, B.BF16)))
     assert np.all(np.isfinite(O))
     check(O[0], orc.dense_attention(Q[0], K[0], V[0]), B.BF16)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N", [1, 31, 33, 256, 257, 545])
+def test_fp32_key_lists_split_over_the_waves(d, N):
+    """The fp32 kernel deals 32-key tiles to the waves of up to four workgroups: fewer tiles than waves, exactly as many,
+    one more, a ragged last tile, and query tiles of one row and of 32; the dense form and a selection with an
+    empty list."""
+    Q, K, V, ql, kl, sel = make_case(17, N, d, B.F32, H=2, Cq=1 if N == 1 else 3, Ck=6, M=max(1, min(12, N)))
+    Cq = len(sel[0])
+    sel[1][Cq - 1] = np.zeros(0, dtype=np.int64)
+    got = run_sparse(Q, K, V, ql, kl, sel, B.F32, Cq, 6)
+    for h in range(2):
+        check(got[h], orc.sparse_attention_gather(Q[h], K[h], V[h], ql[h], kl[h], sel[h]), B.F32)
+    p = B.Params(H=2, N=N, d=d, dtype=B.F32, q_clusters=1, k_m0=1, k_m_min=1, k_max_clusters=1)
+    O = to_np(B.adacluster_dense_attn(p, to_dev(Q, B.F32), to_dev(K, B.F32), to_dev(V, B.F32)))
+    for h in range(2):
+        check(O[h], orc.dense_attention(Q[h], K[h], V[h]), B.F32)
