@@ -333,38 +333,6 @@ __device__ __forceinline__ s16x4_t lds_read_tr16(const char* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p);
 }
 
-// Direct global -> LDS loads, written as inline assembly on purpose.  The compiler orders every LDS read
-// behind an outstanding direct-to-LDS load that it cannot prove to touch another object (it then drains ALL
-// loads in flight: vmcnt(0)), and its proof is fragile (it fails across the branches of a four-stage ring).
-// The tile pipeline below keeps several tiles in flight and waits for exactly the one it needs, by count,
-// before a workgroup barrier; hiding the loads from the compiler leaves that protocol in charge.  Each lane
-// loads `bytes` at sbase + voff; the wave's data land at lds_addr + lane * bytes (M0 carries the LDS address).
-__device__ __forceinline__ void dma_b128(uint32_t lds_addr, uint32_t voff, const void* sbase) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(sbase) : "memory", "m0");
-}
-__device__ __forceinline__ void dma_b128(uint32_t lds_addr, const void* src) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(src) : "memory", "m0");
-}
-__device__ __forceinline__ void dma_b32(uint32_t lds_addr, uint32_t voff, const void* sbase) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(sbase) : "memory", "m0");
-}
-
-// s_waitcnt with only the vector-memory counter set (gfx9 encoding: vmcnt[3:0] and [15:14])
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
-// Workgroup barrier that orders LDS traffic only.  __syncthreads() carries a release fence over global memory
-// as well, which makes every wave drain all of its loads in flight (vmcnt(0)) at every barrier; the tile
-// pipeline below waits for exactly the loads it needs by count and must keep the rest in flight.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // this wave's LDS reads and writes are done
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");                         // nothing that touches memory moves across
-}
-
 // One workgroup = NW waves of 32 queries each; all waves share 64-key K and V tiles.  Tiles go global -> LDS
 // directly (no register staging) as 16-byte chunks into a ring of NBUF stages, NBUF-1 tiles ahead of the
 // arithmetic, one barrier per tile.  A tile row is unpadded and its 16-byte chunks are permuted by a row-dependent

@@ -39,6 +39,38 @@ template <> struct Elem<bf16raw> {
   static __device__ __forceinline__ float load(const bf16raw* p) { return bf16_to_f32(*p); }
 };
 
+// Direct global -> LDS loads, written as inline assembly on purpose.  The compiler orders every LDS read
+// behind an outstanding direct-to-LDS load that it cannot prove to touch another object (it then drains ALL
+// loads in flight: vmcnt(0)), and its proof is fragile (it fails across the branches of a four-stage ring).
+// The tile pipelines keep several tiles in flight and wait for exactly the one they need, by count,
+// before a workgroup barrier; hiding the loads from the compiler leaves that protocol in charge.  Each lane
+// loads `bytes` at sbase + voff; the wave's data land at lds_addr + lane * bytes (M0 carries the LDS address).
+__device__ __forceinline__ void dma_b128(uint32_t lds_addr, uint32_t voff, const void* sbase) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(sbase) : "memory", "m0");
+}
+__device__ __forceinline__ void dma_b128(uint32_t lds_addr, const void* src) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(src) : "memory", "m0");
+}
+__device__ __forceinline__ void dma_b32(uint32_t lds_addr, uint32_t voff, const void* sbase) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(sbase) : "memory", "m0");
+}
+
+// s_waitcnt with only the vector-memory counter set (gfx9 encoding: vmcnt[3:0] and [15:14])
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+// Workgroup barrier that orders LDS traffic only.  __syncthreads() carries a release fence over global memory
+// as well, which makes every wave drain all of its loads in flight (vmcnt(0)) at every barrier; kernels
+// that wait for exactly the loads they need by count, or for none of their stores, use this one.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // this wave's LDS reads and writes are done
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");                         // nothing that touches memory moves across
+}
+
 // per-head state of the multi-stage key clustering (Algorithm 1), device resident
 struct KState {
   int32_t ucount;      // |U|

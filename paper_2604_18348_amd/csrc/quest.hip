@@ -61,94 +61,115 @@ __global__ __launch_bounds__(256) void quest_alu(int Lq, int Lk, int d, int clam
       if (q0 + tq + i < Lq && k0 + tk + j < Lk) Sh[(size_t)(q0 + tq + i) * Lk + k0 + tk + j] = acc[i][j];
 }
 
-// ---- Eq. 2 on the matrix cores (bf16): S^T[32 pages x 32 queries] += R+[32 x 16] Q+^T[16 x 32] + R-[32 x 16] Q-^T.
-// A wave keeps the positive and negative parts of its 32 query rows in registers as B operands; page
-// rows are staged through LDS 64 at a time (clamped while staging when asked to) and are the A operands.
-template <int D>
-__global__ __launch_bounds__(256, 2) void quest_mfma(int Lq, int Lk, int clamp, const bf16raw* __restrict__ Q,
-                                                     const bf16raw* __restrict__ Rp, const bf16raw* __restrict__ Rn,
-                                                     float* __restrict__ S) {
-  constexpr int CB = 64, LDW = D + 8, KS = D / 16;
-  __shared__ __attribute__((aligned(16))) bf16raw ps[CB * LDW], ns[CB * LDW];
-  __shared__ float ts[4][32 * 33];          // a wave's finished tile, for the turn before the store
-  const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// A bf16 value is negative where it is negative as a 16-bit integer: two packed integer operations per pair.
+typedef short s16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void split_signs(uint4& pos, uint4& neg) {
+  uint32_t* a = reinterpret_cast<uint32_t*>(&pos);
+  uint32_t* b = reinterpret_cast<uint32_t*>(&neg);
+  const s16x2_t zero = {0, 0};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    a[i] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2_t, a[i]), zero));
+    b[i] = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(s16x2_t, b[i]), zero));
+  }
+}
+
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64) void quest_mfma(int Lq, int Lk, int clamp, const bf16raw* __restrict__ Q,
+                                                      const bf16raw* __restrict__ Rp, const bf16raw* __restrict__ Rn,
+                                                      float* __restrict__ S) {
+  constexpr int KS = D / 16, CH = D / 8, NT = NW * 64, ROWB = D * 2, QB = 32 * ROWB;
+  constexpr int LOADS = KS > NW ? KS / NW : 1;            // direct-to-LDS loads a loading wave issues per query block
+  // rows of span + 8 floats: a store of the accumulator layout touches two rows 4 apart, and 4 rows are 32 banks away
+  constexpr int SPAN = NW * 32, STRIDE = SPAN + 8;
+  __shared__ __attribute__((aligned(16))) char qs[3 * QB];
+  __shared__ float ts[32 * STRIDE];
+  const int h = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 31, hb = lane >> 5;
-  const int q = blockIdx.x * 128 + wave * 32 + c;
-  const bf16raw* Qh = Q + (size_t)h * Lq * D;
-  bf16x8_t qp[KS], qn[KS];
+  // More pages than the span: a workgroup row of the grid computes `SPAN` pages, of which a score row writes those of
+  // the lines that start inside all but the last 32; the next one starts there.
+  const int k0 = blockIdx.y * (SPAN - 32);
+  const bool single = Lk <= SPAN, last = k0 + SPAN >= Lk;
+  const int nblocks = (Lq + 31) / 32;
+  const int b0 = (int)((long long)nblocks * blockIdx.x / gridDim.x), b1 = (int)((long long)nblocks * (blockIdx.x + 1) / gridDim.x);
+  if (b0 >= b1) return;
+
+  // chunk q of row r sits in slot q ^ swz(r) of its LDS row: operand reads free of bank conflicts
+  auto swz = [](int r) __attribute__((always_inline)) { return D == 128 ? (r & 15) : ((r >> 1) & 7); };
+  const char* Qh = (const char*)(Q + (size_t)h * Lq * D);
+  const uint32_t qs0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)qs;
+  const bool loads = wave < KS;                           // (KS kilobytes a block, one per load)
+  auto issue = [&](int slot, int b) __attribute__((always_inline)) {     // rows past the end repeat the last one
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    uint4 raw = {0, 0, 0, 0};
-    if (q < Lq) raw = *reinterpret_cast<const uint4*>(Qh + (size_t)q * D + ks * 16 + hb * 8);
-    // bf16 pairs: keep the elements whose sign bit is clear (positive part) or set (negative part)
-    const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-    uint32_t wp[4], wn[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t lo_neg = (w[i] & 0x8000u) ? 0xFFFFu : 0u, hi_neg = (w[i] & 0x80000000u) ? 0xFFFF0000u : 0u;
-      const uint32_t negmask = lo_neg | hi_neg;
-      wn[i] = w[i] & negmask; wp[i] = w[i] & ~negmask;
+    for (int i = 0; i < LOADS; ++i) {
+      const int item = (wave * LOADS + i) * 64 + lane, r = item / CH;
+      dma_b128(qs0 + slot * QB + (wave * LOADS + i) * 1024,
+               Qh + (size_t)min(b * 32 + r, Lq - 1) * ROWB + (((item % CH) ^ swz(r)) * 16));
     }
-    const uint4 up = {wp[0], wp[1], wp[2], wp[3]}, un = {wn[0], wn[1], wn[2], wn[3]};
-    qp[ks] = *reinterpret_cast<const bf16x8_t*>(&up);
-    qn[ks] = *reinterpret_cast<const bf16x8_t*>(&un);
-  }
-  const bf16raw* Ph = Rp + (size_t)h * Lk * D;
-  const bf16raw* Nh = Rn + (size_t)h * Lk * D;
-  float* Sh = S + (size_t)h * Lq * Lk;
-  for (int k0 = 0; k0 < Lk; k0 += CB) {
-    __syncthreads();
-    constexpr int CHUNKS = D / 8;
-    for (int i = tid; i < CB * CHUNKS; i += 256) {
-      const int r = i / CHUNKS, g = i % CHUNKS;
-      uint4 vp = {0, 0, 0, 0}, vn = {0, 0, 0, 0};
-      if (k0 + r < Lk) {
-        vp = *reinterpret_cast<const uint4*>(Ph + (size_t)(k0 + r) * D + g * 8);
-        vn = *reinterpret_cast<const uint4*>(Nh + (size_t)(k0 + r) * D + g * 8);
-        if (clamp) {
-          uint32_t* a = reinterpret_cast<uint32_t*>(&vp);
-          uint32_t* b = reinterpret_cast<uint32_t*>(&vn);
+  };
+  if (loads) { issue(0, b0); issue(1, b0 + 1); }
+  bf16x8_t P[KS], N[KS];
+  {
+    const size_t r = ((size_t)h * Lk + min(k0 + wave * 32 + c, Lk - 1)) * D + hb * 8;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const uint32_t negmask = ((a[e] & 0x8000u) ? 0xFFFFu : 0u) | ((a[e] & 0x80000000u) ? 0xFFFF0000u : 0u);
-            const uint32_t negmask_b = ((b[e] & 0x8000u) ? 0xFFFFu : 0u) | ((b[e] & 0x80000000u) ? 0xFFFF0000u : 0u);
-            a[e] &= ~negmask; b[e] &= negmask_b;
-          }
-        }
-      }
-      *reinterpret_cast<uint4*>(&ps[r * LDW + g * 8]) = vp;
-      *reinterpret_cast<uint4*>(&ns[r * LDW + g * 8]) = vn;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int rb = 0; rb < CB / 32; ++rb) {
-      if (k0 + rb * 32 >= Lk) break;
-      f32x16_t acc;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8_t ap = *reinterpret_cast<const bf16x8_t*>(&ps[(rb * 32 + c) * LDW + ks * 16 + hb * 8]);
-        const bf16x8_t an = *reinterpret_cast<const bf16x8_t*>(&ns[(rb * 32 + c) * LDW + ks * 16 + hb * 8]);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ap, qp[ks], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(an, qn[ks], acc, 0, 0, 0);
-      }
-      // value v of the tile is page k0 + rb*32 + 8*(v/4) + 4*hb + v%4 for query q: turned through LDS, so
-      // that a half-wave writes 32 consecutive pages of one query row
-      float* tw = &ts[wave][0];
-#pragma unroll
-      for (int v = 0; v < 16; ++v) tw[c * 33 + 8 * (v >> 2) + 4 * hb + (v & 3)] = acc[v];
-      __builtin_amdgcn_wave_barrier();
-      const int q_base = blockIdx.x * 128 + wave * 32;
-      const int page = k0 + rb * 32 + c;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int qq = 2 * r + hb;
-        if (q_base + qq < Lq && page < Lk) Sh[(size_t)(q_base + qq) * Lk + page] = tw[qq * 33 + c];
-      }
-      __builtin_amdgcn_wave_barrier();
+    for (int ks = 0; ks < KS; ++ks) {
+      uint4 up = *reinterpret_cast<const uint4*>(Rp + r + ks * 16), un = *reinterpret_cast<const uint4*>(Rn + r + ks * 16);
+      if (clamp) split_signs(up, un);
+      P[ks] = *reinterpret_cast<const bf16x8_t*>(&up);
+      N[ks] = *reinterpret_cast<const bf16x8_t*>(&un);
     }
   }
+  int qaddr[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) qaddr[ks] = c * ROWB + (((ks * 2 + hb) ^ swz(c)) * 16);
+  wait_vmcnt<0>();
+  lds_barrier();
+  const int scores = 32 * Lk;                             // of a block of whole rows (single)
+  const int stores = single ? scores / NT : 0;            // store instructions a wave issues per whole block, at least
+  int slot = 0;
+  for (int b = b0; b < b1; ++b) {
+    if (loads) issue(slot >= 1 ? slot - 1 : 2, b + 2);    // the slot of block b - 1, which every wave has read
+    const char* q = qs + slot * QB;
+    f32x16_t acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      uint4 pos = *reinterpret_cast<const uint4*>(q + qaddr[ks]), neg = pos;
+      split_signs(pos, neg);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(&pos), P[ks], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(&neg), N[ks], acc, 0, 0, 0);
+    }
+    lds_barrier();                                        // the scores of block b - 1 have left LDS
+    // value v of the tile is query 8*(v/4) + 4*hb + v%4 of the block, page slot wave*32 + c
+    float* tw = ts + 4 * hb * STRIDE + wave * 32 + c;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) tw[(8 * (v >> 2) + (v & 3)) * STRIDE] = acc[v];
+    // the rows of block b + 1 have landed: younger than their request are the stores of block b - 1 and the request above
+    if (loads) { if (stores >= 12) wait_vmcnt<12 + LOADS>(); else if (stores >= 6) wait_vmcnt<6 + LOADS>(); else wait_vmcnt<LOADS>(); }
+    lds_barrier();
+    float* Sb = S + ((size_t)h * Lq + (size_t)b * 32) * Lk;
+    const int nrows = min(32, Lq - b * 32);
+    if (single) {                 // whole rows: one run over all of them
+      const int dr = NT / Lk, dc = NT % Lk, n = nrows * Lk;
+      int r = tid / Lk, k = tid % Lk;
+      for (int e = tid; e < n; e += NT) {
+        Sb[e] = ts[r * STRIDE + k];
+        r += dr; k += dc;
+        if (k >= Lk) { k -= Lk; ++r; }
+      }
+    } else {
+      for (int r = wave; r < nrows; r += NW) {
+        float* row = Sb + (size_t)r * Lk;
+        // first page at or after p that starts a line of S
+        auto line = [&](int p) __attribute__((always_inline)) { return p + (int)((0u - (uint32_t)((uintptr_t)(row + p) >> 2)) & 31u); };
+        const int from = k0 == 0 ? 0 : line(k0), to = last ? Lk : line(k0 + SPAN - 32);
+        for (int k = from + lane; k < to; k += 64) row[k] = ts[r * STRIDE + k - k0];
+      }
+    }
+    slot = slot == 2 ? 0 : slot + 1;
+  }
+  wait_vmcnt<0>();       // nothing of this wave is still on its way to LDS when it ends
 }
 
 int launch_quest_scores(hipStream_t s, int dtype, int form, int clamp, int H, int Lq, int Lk, int d, const void* Q,
@@ -161,9 +182,20 @@ int launch_quest_scores(hipStream_t s, int dtype, int form, int clamp, int H, in
       quest_alu<float><<<g, 256, 0, s>>>(Lq, Lk, d, clamp, (const float*)Q, (const float*)Rp, (const float*)Rn, S);
   } else {
     if (dtype != ADACLUSTER_BF16) return ADACLUSTER_E_UNSUPPORTED;
-    const dim3 g((Lq + 127) / 128, H);
-    if (d == 64) quest_mfma<64><<<g, 256, 0, s>>>(Lq, Lk, clamp, (const bf16raw*)Q, (const bf16raw*)Rp, (const bf16raw*)Rn, S);
-    else quest_mfma<128><<<g, 256, 0, s>>>(Lq, Lk, clamp, (const bf16raw*)Q, (const bf16raw*)Rp, (const bf16raw*)Rn, S);
+    // One page tile a wave and no more waves than the pages fill, up to 16: with four waves for 60 pages 1 x 180 000 rows
+    // took 24 us, with two 17.  The grid is what the chip holds at once (bounded by LDS and registers), every workgroup
+    // with an equal run of query blocks, because a workgroup loads its pages once.
+    const int nw = Lk <= 64 ? 2 : Lk <= 128 ? 4 : Lk <= 256 ? 8 : 16, span = nw * 32;
+    const int resident = 256 * (nw >= 8 ? 16 / nw : nw == 4 ? 3 : d == 64 ? 6 : 4);
+    const int spans = Lk <= span ? 1 : 1 + (Lk - span + span - 33) / (span - 32);
+    const int nblocks = (Lq + 31) / 32;
+    const long long per = resident / ((long long)H * spans);
+    const dim3 g((unsigned)(per < 1 ? 1 : per > nblocks ? nblocks : per), spans, H);
+    auto go = [&](auto kernel) {
+      kernel<<<g, nw * 64, 0, s>>>(Lq, Lk, clamp, (const bf16raw*)Q, (const bf16raw*)Rp, (const bf16raw*)Rn, S);
+    };
+    if (d == 64) { if (nw == 2) go(quest_mfma<64, 2>); else if (nw == 4) go(quest_mfma<64, 4>); else if (nw == 8) go(quest_mfma<64, 8>); else go(quest_mfma<64, 16>); }
+    else { if (nw == 2) go(quest_mfma<128, 2>); else if (nw == 4) go(quest_mfma<128, 4>); else if (nw == 8) go(quest_mfma<128, 8>); else go(quest_mfma<128, 16>); }
   }
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
 }

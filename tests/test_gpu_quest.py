@@ -41,6 +41,22 @@ def test_box_scores_match_eq1(form, bf16, Lq, Lk, d):
         assert np.all(np.abs(S[h] - ref) <= 1e-5 * mag + 1e-6), float(np.abs(S[h] - ref).max())
 
 
+@pytest.mark.parametrize("Lq,Lk,d", [(257, 64, 64), (300, 65, 128), (70, 128, 64), (33, 129, 128), (65, 256, 64),
+                                     (31, 512, 128), (40, 513, 64), (64, 993, 128), (97, 1201, 64)])
+def test_matrix_core_form_at_the_edges_of_its_spans(Lq, Lk, d):
+    """Page counts around the spans a workgroup collects (64, 128, 256, 512 slots) and past the largest, where rows leave
+    in line-aligned pieces; same bound as above.  Scores are written once: S starts as NaN."""
+    H = 2
+    Q, _, lo, hi = inputs(11, H, Lq, Lk, d, True)
+    S = torch.full((H, Lq, Lk), float("nan"), device="cuda")
+    B.adacluster_quest_scores(dev(Q, True), dev(hi, True), dev(lo, True), B.QUEST_MFMA, out=S)
+    S = S.cpu().numpy()
+    for h in range(H):
+        ref = orc.score_box(Q[h].astype(np.float64), lo[h].astype(np.float64), hi[h].astype(np.float64))
+        mag = np.abs(Q[h].astype(np.float64)) @ np.maximum(np.abs(lo[h]), np.abs(hi[h])).astype(np.float64).T
+        assert np.all(np.abs(S[h] - ref) <= 1e-5 * mag + 1e-6)
+
+
 @pytest.mark.parametrize("form", [B.QUEST_ALU, B.QUEST_MFMA])
 def test_clamped_centroids_are_algorithm_2(form):
     """One vector per page: R+ = max(c, 0), R- = min(c, 0), taken on the fly from the centroid tensor."""
