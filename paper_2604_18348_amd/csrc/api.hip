@@ -192,7 +192,7 @@ struct WS {
 };
 
 struct Dims {
-  int H, N, d, Cq, cap, capmax, nblk, nseg, maxtiles, maxr, prow, brow, BM, BMmax;
+  int H, N, d, Cq, cap, capmax, nblk, maxtiles, maxr, prow, brow, BM, BMmax;
 };
 
 Dims dims_of(const adacluster_params* p) {
@@ -200,7 +200,6 @@ Dims dims_of(const adacluster_params* p) {
   D.H = p->H; D.N = p->N; D.d = p->d; D.Cq = p->q_clusters; D.cap = capacity(p);
   D.capmax = D.cap > D.Cq ? D.cap : D.Cq;
   D.nblk = (p->N + 1023) / 1024;
-  D.nseg = (p->N + 511) / 512;
   D.BM = attn_block_rows(p->dtype, p->d, p->N, D.Cq);
   D.BMmax = attn_block_rows_max(p->dtype);
   D.maxtiles = p->N / attn_block_rows_min(p->dtype) + D.Cq + 1 + attn_split_slots();   // (sized for the smaller tile shape)
@@ -237,7 +236,7 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(ulist[1], int32_t*, H * N * 4);
   TAKE(blockcnt, int32_t*, H * D.nblk * 4);
   TAKE(tau_part, double*, H * D.nblk * 8);
-  TAKE(sort.hist, int32_t*, H * D.nseg * 128 * 4);
+  TAKE(sort.hist, int32_t*, H * sort_table_ints(D.N, D.capmax) * 4);
   TAKE(sort.lab_a, int32_t*, H * N * 4);
   TAKE(sort.val_a, int32_t*, H * N * 4);
   TAKE(sort.lab_b, int32_t*, H * N * 4);
@@ -255,7 +254,7 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(pmax, float*, H * (size_t)D.prow * d * 4);
   TAKE(q_cent_lp, void*, H * (size_t)D.Cq * d * es);
   TAKE(q_bias, float*, H * (size_t)D.Cq * 4);
-  TAKE(q_sort.hist, int32_t*, H * D.nseg * 128 * 4);
+  TAKE(q_sort.hist, int32_t*, H * sort_table_ints(D.N, D.Cq) * 4);
   TAKE(q_sort.lab_a, int32_t*, H * N * 4);
   TAKE(q_sort.val_a, int32_t*, H * N * 4);
   TAKE(q_sort.lab_b, int32_t*, H * N * 4);
@@ -344,7 +343,7 @@ int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, 0, D.Cq, D.Cq, nullptr, nullptr, Q, w.q_cent_lp, w.q_bias,
                          q_labels, nullptr));
     RET_IF(launch_sort(st, D.H, D.N, D.N, D.Cq, q_labels, nullptr, nullptr, 0, nullptr, 0, nullptr, 0, w.perm_q,
-                       w.offs_q, D.Cq + 1, w.q_sort, w.q_poff, reduce_part_rows(), &poff_done));
+                       w.offs_q, D.Cq + 1, w.q_sort, w.q_poff, reduce_part_rows(), nullptr, 0, &poff_done));
     RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, 0, D.Cq, D.Cq, P, nullptr, sph, 0, Q, w.perm_q, w.offs_q,
                              D.Cq + 1, w.q_poff, nullptr, w.q_psum, w.q_pnorm, nullptr, nullptr, poff_done));
     const bool last = it == p->q_iters - 1;
@@ -385,7 +384,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                                     w.cent_lp, k_assign, w.bias));
       } else if (it < p->k_iters - 1) {
         RET_IF(launch_sort(st, D.H, D.N, D.N, D.cap, k_labels, nullptr, nullptr, 0, &w.kstate->m_t, sizeof(KState) / 4,
-                           nullptr, 0, w.perm_tmp, w.offs_tmp, D.capmax + 1, w.sort, w.poff, reduce_part_rows(), &poff_done));
+                           nullptr, 0, w.perm_tmp, w.offs_tmp, D.capmax + 1, w.sort, w.poff, reduce_part_rows(), w.pcl, Pw, &poff_done));
         RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, 1, 0, D.cap, Pw, w.kstate, 0, 0, K, w.perm_tmp,
                                  w.offs_tmp, D.capmax + 1, w.poff, w.pcl, w.psum, w.pnorm, w.pmin, w.pmax, poff_done));
         RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, D.cap, Pw, D.cap, D.cap, w.kstate, 0, 1, 0, w.offs_tmp,
@@ -394,7 +393,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       }
     }
     RET_IF(launch_kstate_commit(st, w.kstate, D.H));
-    if (kc_bound_out) *kc_bound_out = D.cap;
+    kc_bound = D.cap;
     RET_IF(launch_kstate_export(st, w.kstate, D.H, k_count, full_flag, k_stage_offs));
   } else {
   const int u_min = (int)floor((double)p->min_unassigned_frac * (double)p->N);
@@ -483,7 +482,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       } else if (update) {
         RET_IF(launch_sort(st, D.H, D.N, n_bound, m_bound, w.labels_tmp, ul, &w.kstate->ucount,
                            sizeof(KState) / 4, &w.kstate->m_t, sizeof(KState) / 4, &w.kstate->active,
-                           sizeof(KState) / 4, w.perm_tmp, w.offs_tmp, D.capmax + 1, w.sort, w.poff, reduce_part_rows(), &poff_done));
+                           sizeof(KState) / 4, w.perm_tmp, w.offs_tmp, D.capmax + 1, w.sort, w.poff, reduce_part_rows(), w.pcl, P, &poff_done));
         RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, 1, 0, m_bound, P, w.kstate, 0, 0, K, w.perm_tmp,
                                  w.offs_tmp, D.capmax + 1, w.poff, w.pcl, w.psum, w.pnorm, w.pmin, w.pmax, poff_done));
         RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, P, D.cap, p->k_m0, w.kstate, 0, 1, 0,
@@ -496,7 +495,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     RET_IF(launch_filter(st, w.kstate, D.H, D.N, n_bound, w.dist2, w.tau, w.blockcnt, w.u_prev, ul, ul_next,
                          k_stage_of, t));
   }
-  if (kc_bound_out) *kc_bound_out = kc_bound < D.cap ? kc_bound : D.cap;
+  kc_bound = kc_bound < D.cap ? kc_bound : D.cap;
   RET_IF(launch_kstate_export(st, w.kstate, D.H, k_count, full_flag, k_stage_offs, w.tau, tau_used));
   // last step of Algorithm 1: nearest centre among all stage centres, then member statistics.  bf16: the
   // nearest first-stage centre of every point is known from stage 0, so only the later stages' centres are visited.
@@ -507,19 +506,16 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, 2, 0, D.cap, w.kstate, nullptr, K, w.cent_lp, w.bias,
                          k_labels, nullptr));
   }
-  RET_IF(launch_sort(st, D.H, D.N, D.N, D.cap, k_labels, nullptr, nullptr, 0, &w.kstate->ccount, sizeof(KState) / 4,
-                     nullptr, 0, w.perm_k, w.offs_k, D.cap + 1, w.sort, w.poff, reduce_part_rows(), &poff_done));
   const int want_box = (k_bmin && k_bmax) ? 1 : 0;
-  const int P = parts_for(D.N, D.cap);
-  if (!poff_done) {       // the cut into reduction parts belongs to the sort's side of the profile mark
-    RET_IF(launch_part_scan(st, D.H, D.N, 2, 0, D.cap, P, w.kstate, w.offs_k, D.cap + 1, w.poff, w.pcl));
-    poff_done = 2;
-  }
+  if (kc_bound_out) *kc_bound_out = kc_bound;
+  const int P = parts_for(D.N, kc_bound);
+  RET_IF(launch_sort(st, D.H, D.N, D.N, kc_bound, k_labels, nullptr, nullptr, 0, &w.kstate->ccount, sizeof(KState) / 4,
+                     nullptr, 0, w.perm_k, w.offs_k, D.cap + 1, w.sort, w.poff, reduce_part_rows(), w.pcl, P, &poff_done));
   prof_mark(EV_KSORT, st);
-  RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, 2, 0, D.cap, P, w.kstate, 0, want_box, K, w.perm_k, w.offs_k,
+  RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, 2, 0, kc_bound, P, w.kstate, 0, want_box, K, w.perm_k, w.offs_k,
                            D.cap + 1, w.poff, w.pcl, w.psum, w.pnorm, w.pmin, w.pmax, poff_done));
   prof_mark(EV_KREDUCE, st, EV_KSORT);
-  RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 2, 0, D.cap, P, D.cap, D.cap, w.kstate, 0, 0, want_box, w.offs_k,
+  RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 2, 0, kc_bound, P, D.cap, D.cap, w.kstate, 0, 0, want_box, w.offs_k,
                          D.cap + 1, w.poff, w.psum, w.pnorm, w.pmin, w.pmax, nullptr, nullptr, nullptr, nullptr, k_centroids,
                          k_assign, k_sizes, nullptr, k_bmin, k_bmax));
   // the pinned report slots are reused by the next call of this thread: let the last report land

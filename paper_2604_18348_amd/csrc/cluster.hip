@@ -643,43 +643,6 @@ __device__ __forceinline__ bool reduce_setup(const ReduceCfg& c, int h, int& m) 
 // psum [H][m_bound][P][D]; pnorm [H][m_bound][P]; pmin/pmax like psum.
 static constexpr int REDUCE_ROWS = 128;   // rows summed by one wave (64, 96 and 192 measured the same)
 
-// poff[j] = number of parts of the clusters before j (a cluster of n rows has ceil(n/REDUCE_ROWS)
-// parts), j = 0..m.  One block per head.
-// pcl[b] = cluster of part b (written when there are more than 128 clusters: seg_reduce then reads its
-// cluster instead of searching poff, ten dependent round trips at 1024 clusters).
-__global__ __launch_bounds__(1024) void part_scan(ReduceCfg cfg, const int32_t* __restrict__ offs, int offs_stride,
-                                                  int32_t* __restrict__ poff, int32_t* __restrict__ pcl) {
-  const int h = blockIdx.x, tid = threadIdx.x;
-  int m;
-  if (!reduce_setup(cfg, h, m)) return;
-  const int32_t* of = offs + (size_t)h * offs_stride;
-  int32_t* po = poff + (size_t)h * offs_stride;
-  const int per = (m + 1023) / 1024;
-  const int j0 = tid * per, j1 = min(m, j0 + per);
-  int run = 0;
-  for (int j = j0; j < j1; ++j) run += (of[j + 1] - of[j] + REDUCE_ROWS - 1) / REDUCE_ROWS;
-  // inclusive scan over the 1024 threads: inside a wave by shuffles, across the 16 waves through LDS
-  const int lane = tid & 63, wave = tid >> 6;
-  int incl = run;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
-  __shared__ int32_t wtot[16];
-  if (lane == 63) wtot[wave] = incl;
-  __syncthreads();
-  int before = 0, total = 0;
-#pragma unroll
-  for (int w = 0; w < 16; ++w) { const int v = wtot[w]; if (w < wave) before += v; total += v; }
-  int base = before + incl - run;
-  int32_t* pc = (pcl && m > 128) ? pcl + (size_t)h * cfg.P : nullptr;
-  for (int j = j0; j < j1; ++j) {
-    po[j] = base;
-    const int np = (of[j + 1] - of[j] + REDUCE_ROWS - 1) / REDUCE_ROWS;
-    if (pc) for (int q = 0; q < np && base + q < cfg.P; ++q) pc[base + q] = j;
-    base += np;
-  }
-  if (tid == 1023) po[m] = total;
-}
-
 template <typename T> struct Vec16;
 template <> struct Vec16<bf16raw> {
   static constexpr int N = 8;
@@ -1862,10 +1825,7 @@ int launch_seg_reduce(hipStream_t s, int dtype, int d, int H, int N, int mode, i
                       const int32_t* offs, int offs_stride, int32_t* poff, int32_t* pcl, float* psum, float* pnorm,
                       float* pmin, float* pmax, int poff_ready) {
   ReduceCfg c{mode, m_const, N, P, m_bound, st, normalize, want_box};
-  // poff_ready: 0 the parts are cut here; 1 the one-launch sort of small heads has cut them (and left no part ->
-  // cluster table); 2 launch_part_scan has
-  if (!poff_ready) part_scan<<<H, 1024, 0, s>>>(c, offs, offs_stride, poff, pcl);
-  else if (poff_ready == 1) pcl = nullptr;
+  if (poff_ready == 1) pcl = nullptr;
   dim3 g(P, H);
   if (dtype == ADACLUSTER_BF16) {
     if (d == 64) seg_reduce<bf16raw, 64><<<g, 64, 0, s>>>((const bf16raw*)X, c, perm, offs, offs_stride, poff, pcl, psum, pnorm, pmin, pmax);
@@ -1874,13 +1834,6 @@ int launch_seg_reduce(hipStream_t s, int dtype, int d, int H, int N, int mode, i
     if (d == 64) seg_reduce<float, 64><<<g, 64, 0, s>>>((const float*)X, c, perm, offs, offs_stride, poff, pcl, psum, pnorm, pmin, pmax);
     else seg_reduce<float, 128><<<g, 64, 0, s>>>((const float*)X, c, perm, offs, offs_stride, poff, pcl, psum, pnorm, pmin, pmax);
   }
-  return chk();
-}
-
-int launch_part_scan(hipStream_t s, int H, int N, int mode, int m_const, int m_bound, int P, const KState* st,
-                     const int32_t* offs, int offs_stride, int32_t* poff, int32_t* pcl) {
-  ReduceCfg c{mode, m_const, N, P, m_bound, st, 0, 0};
-  part_scan<<<H, 1024, 0, s>>>(c, offs, offs_stride, poff, pcl);
   return chk();
 }
 

@@ -6,21 +6,25 @@
 namespace adac {
 
 struct SortScratch {
-  int32_t* hist;                     // [H][nseg][128]
-  int32_t* lab_a; int32_t* val_a;    // [H][N] intermediate pass
-  int32_t* lab_b;                    // [H][N] sorted labels
+  int32_t* hist;                     // [H][sort_table_ints]: counts of a segment's labels
+  int32_t* lab_a; int32_t* val_a;    // [H][N] intermediate pass of the one-workgroup sort
+  int32_t* lab_b;                    // [H][N] its sorted labels
 };
+size_t sort_table_ints(int N, int m);    // for heads of up to N items and up to m labels
 
 // Stable sort of the first n_h items of every head by label (labels are indexed by position in
 // the item list; the items are token ids from `ulist`, or the positions themselves).
 //   n_dev / m_dev: per-head item and label counts read on the device (NULL: n_bound / m_bound)
 //   active_dev:    per-head flag; heads with 0 are skipped (NULL: all heads)
 // Outputs: perm [H][N] token ids ordered by (label, position); offs [H][offs_stride] with
-// offs[j] = first sorted position of label j for j = 0..m_h.
+// offs[j] = first sorted position of label j for j = 0..m_h.  With poff, the clusters are also cut into parts of part_rows
+// rows for the centroid reduction: poff [H][offs_stride], and pcl [H][P], the cluster of every part, of heads with more
+// than 128 labels.  *poff_done says what was left: 1 poff, 2 pcl as well.
 int launch_sort(hipStream_t st, int H, int N, int n_bound, int m_bound, const int32_t* labels,
                 const int32_t* ulist, const int32_t* n_dev, int n_stride, const int32_t* m_dev, int m_stride,
                 const int32_t* active_dev, int active_stride, int32_t* perm, int32_t* offs, int offs_stride,
-                const SortScratch& sc, int32_t* poff = nullptr, int part_rows = 0, int* poff_done = nullptr);
+                const SortScratch& sc, int32_t* poff = nullptr, int part_rows = 0, int32_t* pcl = nullptr, int P = 0,
+                int* poff_done = nullptr);
 
 int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, int mode, int m_const, int cap,
                   const KState* st, const int32_t* ulist, const void* X, const void* cent_lp, const float* bias,
@@ -31,11 +35,8 @@ int assign_block_sum_centres();   // most centres the assignment kernel keeps bl
 int launch_seg_reduce(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int P,
                       const KState* st, int normalize, int want_box, const void* X, const int32_t* perm,
                       const int32_t* offs, int offs_stride, int32_t* poff, int32_t* pcl, float* psum, float* pnorm, float* pmin,
-                      float* pmax, int poff_ready = 0);
+                      float* pmax, int poff_ready /* what launch_sort left, 1 or 2 */);
 int reduce_part_rows();
-// Cuts the clusters of a sorted head into reduction parts on its own (launch_seg_reduce then takes poff_ready = 2).
-int launch_part_scan(hipStream_t s, int H, int N, int mode, int m_const, int m_bound, int P, const KState* st,
-                     const int32_t* offs, int offs_stride, int32_t* poff, int32_t* pcl);
 int launch_finalize(hipStream_t s, int dtype, int d, int H, int mode, int m_const, int m_bound, int P, int cap,
                     int master_stride, const KState* st, int spherical, int update_assign, int want_box,
                     const int32_t* offs, int offs_stride, const int32_t* poff, const float* psum, const float* pnorm,
