@@ -59,13 +59,15 @@ struct AuxStream {
 };
 thread_local AuxStream g_aux[64];
 
-// Pinned host slots for the per-stage report of Algorithm 1 and two events to wait on, per thread.
+// Pinned host slots for the per-stage report of Algorithm 1, per thread.  The host polls the last word of a slot, which
+// the device writes behind the others: an event would put a barrier between the stage head and the kernels behind it
+// (5-8 us a stage).
 struct StageReadback {
   bool ready = false;
   int device = -1;
-  int32_t* host = nullptr;     // [ADACLUSTER_MAX_STAGES + 2][4], pinned and mapped
+  int epoch = 0;               // of the call that uses the slots: tells its reports from those of the call before
+  int32_t* host = nullptr;     // [ADACLUSTER_MAX_STAGES + 2][4], pinned, mapped and coherent
   int32_t* dev = nullptr;      // the same memory as the device sees it
-  hipEvent_t ev[2] = {nullptr, nullptr};
 };
 thread_local StageReadback t_readback;
 
@@ -73,20 +75,32 @@ StageReadback* stage_readback() {
   StageReadback& r = t_readback;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return nullptr;
-  if (r.ready && r.device != dev) {        // events belong to the device they were created on
-    for (int i = 0; i < 2; ++i) (void)hipEventDestroy(r.ev[i]);
+  if (r.ready && r.device != dev) {
     (void)hipHostFree(r.host);
     r.ready = false;
   }
   if (!r.ready) {
     r.device = dev;
-    if (hipHostMalloc((void**)&r.host, (ADACLUSTER_MAX_STAGES + 2) * 4 * sizeof(int32_t), hipHostMallocMapped) != hipSuccess) return nullptr;
-    if (hipHostGetDevicePointer((void**)&r.dev, r.host, 0) != hipSuccess) return nullptr;
-    for (int i = 0; i < 2; ++i)
-      if (hipEventCreateWithFlags(&r.ev[i], hipEventDisableTiming) != hipSuccess) return nullptr;
+    const size_t bytes = (ADACLUSTER_MAX_STAGES + 2) * 4 * sizeof(int32_t);
+    if (hipHostMalloc((void**)&r.host, bytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) return nullptr;
+    memset(r.host, 0, bytes);
+    r.epoch = 0;
+    if (hipHostGetDevicePointer((void**)&r.dev, r.host, 0) != hipSuccess) { (void)hipHostFree(r.host); return nullptr; }
     r.ready = true;
   }
+  r.epoch = r.epoch == INT32_MAX ? 1 : r.epoch + 1;
   return &r;
+}
+
+// Waits for the report of stage t.  A stream that has run dry (or failed) without it ends the wait with an error.
+bool stage_report_landed(const StageReadback& r, int t, hipStream_t st) {
+  const int32_t* word = r.host + 4 * t + 3;
+  for (unsigned spin = 1;; ++spin) {
+    if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == r.epoch) return true;
+    if ((spin & 0xFFF) == 0 && hipStreamQuery(st) != hipErrorNotReady)
+      return __atomic_load_n(word, __ATOMIC_ACQUIRE) == r.epoch;
+    __builtin_ia32_pause();
+  }
 }
 
 AuxStream* aux_stream() {
@@ -170,7 +184,7 @@ struct Layout {
 
 struct WS {
   unsigned char* base;
-  KState* kstate; int32_t* summary; float* tau; int32_t* u_prev;
+  KState* kstate; KState* kstate2; int32_t* summary; float* tau;
   void* cent_lp; float* bias; float* master;
   int32_t* labels_tmp; float* dist2; int32_t* ulist[2]; int32_t* blockcnt; double* tau_part;
   SortScratch sort; int32_t* perm_tmp; int32_t* offs_tmp; int32_t* poff; int32_t* pcl; int32_t* lab0; float* score0;
@@ -192,7 +206,7 @@ struct WS {
 };
 
 struct Dims {
-  int H, N, d, Cq, cap, capmax, nblk, maxtiles, maxr, prow, brow, BM, BMmax;
+  int H, N, d, Cq, cap, capmax, nblk, ncnt, maxtiles, maxr, prow, brow, BM, BMmax;
 };
 
 Dims dims_of(const adacluster_params* p) {
@@ -200,6 +214,7 @@ Dims dims_of(const adacluster_params* p) {
   D.H = p->H; D.N = p->N; D.d = p->d; D.Cq = p->q_clusters; D.cap = capacity(p);
   D.capmax = D.cap > D.Cq ? D.cap : D.Cq;
   D.nblk = (p->N + 1023) / 1024;
+  D.ncnt = (p->N + stage_points_per_count(p->dtype) - 1) / stage_points_per_count(p->dtype);
   D.BM = attn_block_rows(p->dtype, p->d, p->N, D.Cq);
   D.BMmax = attn_block_rows_max(p->dtype);
   D.maxtiles = p->N / attn_block_rows_min(p->dtype) + D.Cq + 1 + attn_split_slots();   // (sized for the smaller tile shape)
@@ -224,9 +239,9 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   Layout L;
 #define TAKE(field, type, bytes) { size_t o_ = L.take(bytes); if (w) w->field = (type)(base + o_); }
   TAKE(kstate, KState*, H * sizeof(KState));
+  TAKE(kstate2, KState*, H * sizeof(KState));
   TAKE(summary, int32_t*, 64);
   TAKE(tau, float*, 64);
-  TAKE(u_prev, int32_t*, H * 4);
   TAKE(cent_lp, void*, H * D.capmax * d * es);
   TAKE(bias, float*, H * D.capmax * 4);
   TAKE(master, float*, H * (size_t)(p->k_m0 > D.Cq ? p->k_m0 : D.Cq) * d * 4);
@@ -234,7 +249,7 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(dist2, float*, H * N * 4);
   TAKE(ulist[0], int32_t*, H * N * 4);
   TAKE(ulist[1], int32_t*, H * N * 4);
-  TAKE(blockcnt, int32_t*, H * D.nblk * 4);
+  TAKE(blockcnt, int32_t*, H * D.ncnt * 4);
   TAKE(tau_part, double*, H * D.nblk * 8);
   TAKE(sort.hist, int32_t*, H * sort_table_ints(D.N, D.capmax) * 4);
   TAKE(sort.lab_a, int32_t*, H * N * 4);
@@ -367,7 +382,8 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                  float* tau_used, int* kc_bound_out) {
   const Dims D = dims_of(p);
   int kc_bound = 0;   // sum over stages of the largest stage centre count: an upper bound of every |C|
-  hipEvent_t pending_ev = nullptr;   // the last report may still be in flight when the stage loop ends
+  int pending = 0;                   // the last report (of this stage) may still be in flight when the stage loop ends
+  StageReadback* rb = nullptr;
   int poff_done = 0;                 // set when the sort has already cut the clusters into reduction parts
   if (p->k_init_mode == 1) {
     // warm start: one pseudo-stage over all tokens with the previous centres, count fixed
@@ -394,11 +410,10 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     }
     RET_IF(launch_kstate_commit(st, w.kstate, D.H));
     kc_bound = D.cap;
-    RET_IF(launch_kstate_export(st, w.kstate, D.H, k_count, full_flag, k_stage_offs));
+    RET_IF(launch_kstate_export(st, w.kstate, D.H, w.kstate, k_count, full_flag, k_stage_offs));
   } else {
   const int u_min = (int)floor((double)p->min_unassigned_frac * (double)p->N);
   const bool seeded = p->dtype == ADACLUSTER_BF16;
-  RET_IF(launch_kstate_init(st, w.kstate, D.H, D.N));
   if (k_stage_of) RET_IF(launch_fill_i32(st, k_stage_of, (size_t)D.H * D.N, -1));
   if (p->tau_abs > 0.f) RET_IF(launch_tau(st, D.H, D.N, nullptr, nullptr, 0.f, p->tau_abs, w.tau));
   // The stage loop has a data-dependent trip count, and grids are sized by what the stage head
@@ -406,25 +421,28 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   // would drain the queue once per stage, so the host stays one stage behind: stage t is
   // enqueued with the report of stage t-1 (|U| and m_t never grow, so the older figures are
   // valid bounds; every kernel takes the true counts from the device state), and a stage whose
-  // heads all turn out finished runs as empty kernels, once, at the end.
-  StageReadback* rb = stage_readback();
+  // heads all turn out finished runs as empty kernels, once, at the end.  What stage 0 reports the
+  // host knows: every head starts alike.
+  rb = stage_readback();
   if (!rb) return fail(ADACLUSTER_E_INTERNAL, "stage read-back set-up failed: %s", hipGetErrorString(hipGetLastError()));
   int n_bound = D.N, m_bound = p->k_m0 < D.N ? p->k_m0 : D.N;
+  KState *cur = w.kstate, *other = w.kstate2;      // the stage head reads one and writes the other
+  StageFilter filter{};                            // how the stage before ended
   for (int t = 0; t <= p->k_max_stages; ++t) {
-    pending_ev = rb->ev[t & 1];
     // the stage head writes its report straight into the pinned slot (no copy in between)
-    RET_IF(launch_kstage_begin(st, w.kstate, D.H, D.N, p->k_max_clusters, p->k_m0, p->k_m_min, p->k_max_stages,
-                               u_min, rb->dev + 4 * t));
-    if (hipEventRecord(rb->ev[t & 1], st) != hipSuccess)
-      return fail(ADACLUSTER_E_INTERNAL, "stage read-back failed: %s", hipGetErrorString(hipGetLastError()));
-    if (t > 0) {
-      if (hipEventSynchronize(rb->ev[(t - 1) & 1]) != hipSuccess)
+    if (t > 0) { KState* x = cur; cur = other; other = x; }
+    RET_IF(launch_stage_open(st, p->dtype, D.d, D.H, D.N, D.cap, p->k_max_clusters, p->k_m0, p->k_m_min, p->k_max_stages,
+                             u_min, n_bound, m_bound, other, cur, t > 0 ? &filter : nullptr, w.summary,
+                             t > 0 ? rb->dev + 4 * t : nullptr, rb->epoch, p->k_m0, K, w.master, w.cent_lp, k_assign, w.bias));
+    pending = t;
+    if (t > 1) {
+      if (!stage_report_landed(*rb, t - 1, st))
         return fail(ADACLUSTER_E_INTERNAL, "stage read-back failed: %s", hipGetErrorString(hipGetLastError()));
       const int32_t* summ = rb->host + 4 * (t - 1);
       if (summ[0] == 0) break;                 // stage t-1 had no active head: the loop ended there
       n_bound = summ[1]; m_bound = summ[2];
-      kc_bound += m_bound;
     }
+    if (t > 0) kc_bound += m_bound;
     if (t == p->k_max_stages) break;           // the stage head has just closed every head
     if (t == 1 && !(p->dtype == ADACLUSTER_BF16 && (n_bound + 255) / 256 <= STAGE_SUM_BLOCKS &&
                     m_bound <= assign_block_sum_centres())) {
@@ -433,7 +451,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       // points through the launch chain sized for all of them (two radix passes, segmented
       // reduction).  Then, once per call, the host waits for the report of the stage it is about to
       // enqueue; the other stream keeps the device busy meanwhile.
-      if (hipEventSynchronize(rb->ev[1]) != hipSuccess)
+      if (!stage_report_landed(*rb, 1, st))
         return fail(ADACLUSTER_E_INTERNAL, "stage read-back failed: %s", hipGetErrorString(hipGetLastError()));
       const int32_t* cur = rb->host + 4;
       if (cur[0] == 0) break;                  // no head needs a second stage
@@ -443,15 +461,13 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       // few points and few centres left in every head: one launch runs this and every later stage
       // (|U| and m_t never grow, so the bounds hold for all of them)
       RET_IF(launch_kstages_small(st, D.d, D.H, D.N, D.cap, p->k_max_clusters, p->k_m0, p->k_m_min, p->k_max_stages,
-                                  u_min, p->k_iters, w.kstate, w.tau, w.ulist[0], w.ulist[1], K, w.cent_lp, k_assign,
+                                  u_min, p->k_iters, cur, w.tau, w.ulist[0], w.ulist[1], K, w.cent_lp, k_assign,
                                   w.bias, k_stage_of));
       kc_bound += m_bound * (p->k_max_stages - t);
       break;
     }
     const int32_t* ul = (t == 0) ? nullptr : w.ulist[t & 1];
     int32_t* ul_next = w.ulist[(t + 1) & 1];
-    RET_IF(launch_init_centroids(st, p->dtype, D.d, D.H, D.N, 1, 0, m_bound, w.kstate, ul, 0, 0, D.cap, p->k_m0, K,
-                                 w.master, w.cent_lp, k_assign, w.bias));
     const int P = parts_for(n_bound, m_bound);
     // A small stage (few blocks of points, few centres) updates its centres from sums that the
     // assignment kernel leaves per block: no label sort and no segmented reduction in between.
@@ -462,9 +478,9 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     for (int it = 0; it < p->k_iters; ++it) {
       const bool update = it < p->k_iters - 1;
       if (block_sums && update) {
-        RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, n_bound, 1, 0, D.cap, w.kstate, ul, K, w.cent_lp, w.bias,
+        RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, n_bound, 1, 0, D.cap, cur, ul, K, w.cent_lp, w.bias,
                              w.labels_tmp, nullptr, w.bsum, w.bcnt, Pb));        // (distances: last pass only)
-        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, Pb, D.cap, p->k_m0, w.kstate, 0, 1, 0,
+        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, Pb, D.cap, p->k_m0, cur, 0, 1, 0,
                                nullptr, 0, nullptr, w.bsum, w.pnorm, w.pmin, w.pmax, w.master, w.cent_lp,
                                k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.bcnt, nblk));
         continue;
@@ -472,31 +488,32 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       // (the last pass of stage 0 runs over all points against the first-stage centres as they will stay:
       // it keeps a copy of its labels and best scores, which the final pass starts from)
       const bool keep = seeded && t == 0 && !update;
-      RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, n_bound, 1, 0, D.cap, w.kstate, ul, K, w.cent_lp, w.bias,
+      RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, n_bound, 1, 0, D.cap, cur, ul, K, w.cent_lp, w.bias,
                            w.labels_tmp, update ? nullptr : w.dist2, nullptr, nullptr, 0, keep ? w.lab0 : nullptr,
-                           keep ? w.score0 : nullptr));
+                           keep ? w.score0 : nullptr, nullptr, nullptr, w.tau,
+                           !update && t > 0 ? w.blockcnt : nullptr, D.ncnt));
       if (update && direct_update_fits(p->dtype, n_bound, m_bound)) {
         // few points (fp32): every centre gathers its members from the label list itself, one launch
-        RET_IF(launch_update_direct(st, D.d, D.H, D.N, m_bound, D.cap, p->k_m0, w.kstate, w.labels_tmp, ul, K, w.master,
+        RET_IF(launch_update_direct(st, D.d, D.H, D.N, m_bound, D.cap, p->k_m0, cur, w.labels_tmp, ul, K, w.master,
                                     w.cent_lp, k_assign, w.bias));
       } else if (update) {
-        RET_IF(launch_sort(st, D.H, D.N, n_bound, m_bound, w.labels_tmp, ul, &w.kstate->ucount,
-                           sizeof(KState) / 4, &w.kstate->m_t, sizeof(KState) / 4, &w.kstate->active,
+        RET_IF(launch_sort(st, D.H, D.N, n_bound, m_bound, w.labels_tmp, ul, &cur->ucount,
+                           sizeof(KState) / 4, &cur->m_t, sizeof(KState) / 4, &cur->active,
                            sizeof(KState) / 4, w.perm_tmp, w.offs_tmp, D.capmax + 1, w.sort, w.poff, reduce_part_rows(), w.pcl, P, &poff_done));
-        RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, 1, 0, m_bound, P, w.kstate, 0, 0, K, w.perm_tmp,
+        RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, 1, 0, m_bound, P, cur, 0, 0, K, w.perm_tmp,
                                  w.offs_tmp, D.capmax + 1, w.poff, w.pcl, w.psum, w.pnorm, w.pmin, w.pmax, poff_done));
-        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, P, D.cap, p->k_m0, w.kstate, 0, 1, 0,
+        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, P, D.cap, p->k_m0, cur, 0, 1, 0,
                                w.offs_tmp, D.capmax + 1, w.poff, w.psum, w.pnorm, w.pmin, w.pmax, w.master, w.cent_lp,
                                k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr));
       }
     }
     if (t == 0 && !(p->tau_abs > 0.f))
       RET_IF(launch_tau(st, D.H, D.N, w.dist2, w.tau_part, p->tau_factor, 0.f, w.tau));
-    RET_IF(launch_filter(st, w.kstate, D.H, D.N, n_bound, w.dist2, w.tau, w.blockcnt, w.u_prev, ul, ul_next,
-                         k_stage_of, t));
+    filter = StageFilter{w.dist2, w.tau, w.blockcnt, D.ncnt, stage_points_per_count(p->dtype), ul, ul_next, k_stage_of, t};
+    if (t == 0) RET_IF(launch_keep_count(st, cur, D.H, D.N, w.dist2, w.tau, w.blockcnt, D.ncnt, &filter.items));
   }
   kc_bound = kc_bound < D.cap ? kc_bound : D.cap;
-  RET_IF(launch_kstate_export(st, w.kstate, D.H, k_count, full_flag, k_stage_offs, w.tau, tau_used));
+  RET_IF(launch_kstate_export(st, cur, D.H, w.kstate, k_count, full_flag, k_stage_offs, w.tau, tau_used));
   // last step of Algorithm 1: nearest centre among all stage centres, then member statistics.  bf16: the
   // nearest first-stage centre of every point is known from stage 0, so only the later stages' centres are visited.
   if (seeded)
@@ -520,7 +537,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                          k_assign, k_sizes, nullptr, k_bmin, k_bmax));
   // the pinned report slots are reused by the next call of this thread: let the last report land
   // (its kernel was queued ahead of everything above, so this does not drain the stream)
-  if (pending_ev && hipEventSynchronize(pending_ev) != hipSuccess)
+  if (pending && !stage_report_landed(*rb, pending, st))
     return fail(ADACLUSTER_E_INTERNAL, "stage read-back failed: %s", hipGetErrorString(hipGetLastError()));
   return 0;
 }

@@ -26,7 +26,10 @@ struct AssignCfg {
   const KState* st; const int32_t* ulist;
   int32_t* keep_lab; float* keep_score;
   const int32_t* seed_lab; const float* seed_score;
+  const float* tau; int32_t* keep_cnt; int keep_stride;   // points of this workgroup that the threshold leaves in U (a late
+                                                          // stage's last pass): keep_cnt[h * keep_stride + workgroup]
 };
+constexpr int ASSIGN_POINTS_LP = 256, ASSIGN_POINTS_F32 = 128;     // points of an assignment workgroup
 
 __device__ __forceinline__ bool assign_setup(const AssignCfg& c, int h, int& n, int& m, int& row_off) {
   if (c.mode == 0) { n = c.N; m = c.m_const; row_off = 0; return true; }
@@ -234,6 +237,9 @@ __global__ __launch_bounds__(256, (ACC && D == 128) ? 1 : 2) void assign_mfma(co
     if (c0 + CB < m) step(c0 + CB, cs1, bs1, cs0, bs0);
   }
   int blab[PB];
+  int kept = 0;
+  const bool counts = !ACC && cfg.keep_cnt && dist2;
+  const float t2 = counts ? cfg.tau[1] : 0.f;
 #pragma unroll
   for (int pb = 0; pb < PB; ++pb) {
     // accumulator value v of a tile is centre  32*tile + 8*(v/4) + 4*hb + v%4
@@ -244,12 +250,20 @@ __global__ __launch_bounds__(256, (ACC && D == 128) ? 1 : 2) void assign_mfma(co
     const float ob = __shfl_xor(bv, 32);
     const int oi = __shfl_xor(bidx, 32);
     if (ob > bv || (ob == bv && oi < bidx)) { bv = ob; bidx = oi; }
+    const float d2 = fmaxf(xn2[pb] - 2.f * bv, 0.f);
+    if (counts) kept += __popcll(__ballot(hb == 0 && pos[pb] < n && !(d2 < t2)));
     if (hb == 0 && pos[pb] < n) {
       labels[(size_t)h * cfg.N + pos[pb]] = bidx;
-      if (dist2) dist2[(size_t)h * cfg.N + pos[pb]] = fmaxf(xn2[pb] - 2.f * bv, 0.f);
+      if (dist2) dist2[(size_t)h * cfg.N + pos[pb]] = d2;
       if (!ACC && cfg.keep_lab) { cfg.keep_lab[(size_t)h * cfg.N + pos[pb]] = bidx; cfg.keep_score[(size_t)h * cfg.N + pos[pb]] = bv; }
     }
     if (ACC) blab[pb] = pos[pb] < n ? bidx : -1;
+  }
+  if (counts) {
+    __shared__ int32_t wkept[4];
+    if (lane == 0) wkept[wave] = kept;
+    __syncthreads();
+    if (tid == 0) cfg.keep_cnt[(size_t)h * cfg.keep_stride + blockIdx.x] = wkept[0] + wkept[1] + wkept[2] + wkept[3];
   }
   if constexpr (ACC) {
     constexpr int ROWB = D * 2, DT = D / 32;
@@ -613,9 +627,17 @@ __global__ __launch_bounds__(128) void assign_f32(const float* __restrict__ X, A
       if (s > best) { best = s; bidx = c0 + r; }
     }
   }
+  const float d2 = fmaxf(xn2 - 2.f * best, 0.f);
   if (p < n) {
     labels[(size_t)h * cfg.N + p] = bidx;
-    if (dist2) dist2[(size_t)h * cfg.N + p] = fmaxf(xn2 - 2.f * best, 0.f);
+    if (dist2) dist2[(size_t)h * cfg.N + p] = d2;
+  }
+  if (cfg.keep_cnt && dist2) {
+    __shared__ int32_t wkept[2];
+    const uint64_t kept = __ballot(p < n && !(d2 < cfg.tau[1]));
+    if ((tid & 63) == 0) wkept[tid >> 6] = __popcll(kept);
+    __syncthreads();
+    if (tid == 0) cfg.keep_cnt[(size_t)h * cfg.keep_stride + blockIdx.x] = wkept[0] + wkept[1];
   }
 }
 
@@ -1103,16 +1125,6 @@ __global__ __launch_bounds__(64) void init_centroids(const T* __restrict__ X, in
 // ------------------------------------------------------------------------------------------
 // Algorithm 1 bookkeeping
 // ------------------------------------------------------------------------------------------
-__global__ void kstate_init(KState* st, int H, int N) {
-  const int h = blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= H) return;
-  KState s;
-  s.ucount = N; s.ccount = 0; s.m_t = 0; s.stage = 0; s.done = 0; s.full = 0; s.active = 0; s.pad = 0;
-  for (int i = 0; i <= ADACLUSTER_MAX_STAGES; ++i) { s.stage_offs[i] = 0; s.u_hist[i] = 0; }
-  s.u_hist[0] = N;
-  st[h] = s;
-}
-
 // Warm start (Sec. 3.2.2, "Efficient initialization"): one stage over all tokens, centre count given.
 __global__ void kstate_warm(KState* st, int H, int N, int cap, const int32_t* __restrict__ k_count,
                             const int32_t* __restrict__ full_flag) {
@@ -1131,37 +1143,6 @@ __global__ void kstate_commit(KState* st, int H) {
   KState s = st[h];
   s.ccount = s.m_t; s.stage = 1; s.stage_offs[1] = s.ccount; s.ucount = 0; s.active = 0; s.done = 1;
   st[h] = s;
-}
-
-// Head of the while-loop of Algorithm 1: U empty? |C| >= N_max (flag F)?  stage / leftover limits?
-// then the centre count m_t of the next stage.  summary = {active heads, max |U|, max m_t}.
-__global__ void kstage_begin(KState* st, int H, int N, int n_max, int m0, int m_min, int max_stages,
-                             int u_min, int32_t* summary) {
-  __shared__ int32_t s_act, s_u, s_m;
-  if (threadIdx.x == 0) { s_act = 0; s_u = 0; s_m = 0; }
-  __syncthreads();
-  for (int h = threadIdx.x; h < H; h += blockDim.x) {
-    KState s = st[h];
-    if (!s.done) {
-      if (s.ucount == 0) s.done = 1;
-      else if (s.ccount >= n_max) { s.full = 1; s.done = 1; }
-      else if (s.stage >= max_stages || s.ucount <= u_min) s.done = 1;
-    }
-    s.active = !s.done;
-    if (s.active) {
-      long long mm = ((long long)m0 * s.ucount + N - 1) / N;
-      int m = (int)mm;
-      m = max(m_min, min(m0, m));
-      m = min(m, s.ucount);
-      s.m_t = m;
-      atomicAdd(&s_act, 1); atomicMax(&s_u, s.ucount); atomicMax(&s_m, m);
-    } else {
-      s.m_t = 0;
-    }
-    st[h] = s;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) { summary[0] = s_act; summary[1] = s_u; summary[2] = s_m; }
 }
 
 // tau = factor x mean first-stage distance over all heads and tokens (Sec. 4.1).
@@ -1205,18 +1186,20 @@ __global__ void tau_set(float tau, float* __restrict__ tau_out) {
   if (threadIdx.x == 0 && blockIdx.x == 0) { tau_out[0] = tau; tau_out[1] = tau * tau; }
 }
 
-// threshold filter of Algorithm 1: tokens with d < tau leave U.  Three passes keep U ascending.
-__global__ __launch_bounds__(256) void filter_count(const KState* __restrict__ st, const float* __restrict__ dist2,
-                                                    int N, int nblk, const float* __restrict__ tau,
-                                                    int32_t* __restrict__ blockcnt) {
+// Threshold filter of Algorithm 1: tokens with d < tau leave U.  Survivors per KEEP_ITEMS points of the first stage, whose
+// threshold is known only after its last pass (a later stage's last pass counts them itself).
+constexpr int KEEP_ITEMS = 1024;
+__global__ __launch_bounds__(256) void keep_count(const KState* __restrict__ st, const float* __restrict__ dist2, int N,
+                                                  const float* __restrict__ tau, int32_t* __restrict__ cnt, int cnt_stride) {
   const int h = blockIdx.y, b = blockIdx.x, tid = threadIdx.x;
   const KState& s = st[h];
   if (!s.active) return;
   const int n = s.ucount;
   const float t2 = tau[1];
   int c = 0;
-  for (int i = 0; i < 4; ++i) {
-    const int p = b * 1024 + i * 256 + tid;
+#pragma unroll
+  for (int i = 0; i < KEEP_ITEMS / 256; ++i) {
+    const int p = b * KEEP_ITEMS + i * 256 + tid;
     if (p < n && !(dist2[(size_t)h * N + p] < t2)) ++c;
   }
 #pragma unroll
@@ -1224,127 +1207,201 @@ __global__ __launch_bounds__(256) void filter_count(const KState* __restrict__ s
   __shared__ int32_t ws[4];
   if ((tid & 63) == 0) ws[tid >> 6] = c;
   __syncthreads();
-  if (tid == 0) blockcnt[(size_t)h * nblk + b] = ws[0] + ws[1] + ws[2] + ws[3];
+  if (tid == 0) cnt[(size_t)h * cnt_stride + b] = ws[0] + ws[1] + ws[2] + ws[3];
 }
 
-__global__ __launch_bounds__(64) void filter_scan(KState* __restrict__ st, int nblk_used, int nblk,
-                                                  int32_t* __restrict__ blockcnt, int32_t* __restrict__ u_prev) {
-  // one wave per head: a lane takes a run of consecutive blocks, the runs are chained by a wave scan
-  const int h = blockIdx.x, lane = threadIdx.x;
-  KState s = st[h];
-  if (!s.active) return;
-  const int nb = min((s.ucount + 1023) / 1024, nblk_used);
-  const int per = (nb + 63) / 64;
-  const int b0 = min(lane * per, nb), b1 = min(b0 + per, nb);
-  int32_t* bc = blockcnt + (size_t)h * nblk;
-  int mine = 0;
-  for (int b = b0; b < b1; ++b) mine += bc[b];
-  int incl = mine;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
-  const int total = __shfl(incl, 63);
-  int run = incl - mine;
-  for (int b = b0; b < b1; ++b) { const int c = bc[b]; bc[b] = run; run += c; }
-  if (lane != 0) return;
-  u_prev[h] = s.ucount;
-  s.ucount = total;
-  s.ccount += s.m_t;
-  s.stage += 1;
-  s.stage_offs[s.stage] = s.ccount;
-  s.u_hist[s.stage] = total;
-  st[h] = s;
-}
+// Between two stages of Algorithm 1, in one launch: the threshold filter of the stage that ends, the head of the
+// while-loop (U empty?  |C| >= N_max, flag F?  stage and leftover limits; then the centre count m_t), and the initial
+// centres of the stage that opens, a strided sample of the U being written.  Nothing waits for another workgroup: the
+// survivors were counted per `items` points, so every workgroup sums those counts for itself and knows the new |U|,
+// the loop's decision, where its own points go (the first `nblk` workgroups) or which point is the j-th survivor (the
+// others, a wave per centre).  The state is read from `in` and written, by workgroup 0 of a head, to `out`, another
+// array.  The last head to report writes {active heads, max |U|, max m_t, epoch} to `report`.
+// Bound by launch latency and five dependent trips to the L2: 8-10 us.  In three launches (the filter by one workgroup per
+// head 13-27 us, the loop head 4, the centres 4) and with an event for the host behind the second, a late stage of
+// 30 x 5 000 points took 68 us in all; it takes 47.
+struct OpenCfg {
+  int N, cap, n_max, m0, m_min, max_stages, u_min;
+  int first;                       // the first stage opens: no filter, U is every token (`in` is not read)
+  int items, nblk, cnt_stride;     // points per count; workgroups that move survivors
+  const KState* in; KState* out;
+  const float* dist2; const float* tau; const int32_t* cnt;
+  const int32_t* uin; int32_t* uout; int32_t* stage_of; int stage;      // `stage`: the one that ends
+  int32_t* sums; int32_t* report; int epoch;   // [4] device counters, zero between launches (`first` clears them); host slot
+  int master_stride; float* master; void* lp; float* f32; float* bias;
+};
 
-__global__ __launch_bounds__(256) void filter_scatter(const KState* __restrict__ st, const int32_t* __restrict__ u_prev,
-                                                      const float* __restrict__ dist2, int N, int nblk,
-                                                      const float* __restrict__ tau,
-                                                      const int32_t* __restrict__ blockbase,
-                                                      const int32_t* __restrict__ ulist_in,
-                                                      int32_t* __restrict__ ulist_out,
-                                                      int32_t* __restrict__ stage_of, int stage) {
-  const int h = blockIdx.y, b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const KState& s = st[h];
-  if (!s.active) return;
-  const int n = u_prev[h];
-  if (b * 1024 >= n) return;
-  const float t2 = tau[1];
-  int run = blockbase[(size_t)h * nblk + b];
-  __shared__ int32_t ws[4];
-  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int i = 0; i < 4; ++i) {
-    const int p = b * 1024 + i * 256 + tid;
-    const bool valid = p < n;
-    const bool keep = valid && !(dist2[(size_t)h * N + p] < t2);
-    const int tok = valid ? (ulist_in ? ulist_in[(size_t)h * N + p] : p) : 0;
-    const uint64_t bal = __ballot(keep);
-    __syncthreads();
-    if (lane == 0) ws[wave] = __popcll(bal);
-    __syncthreads();
-    int before = 0;
-    for (int w = 0; w < wave; ++w) before += ws[w];
-    const int total = ws[0] + ws[1] + ws[2] + ws[3];
-    if (keep) ulist_out[(size_t)h * N + run + before + __popcll(bal & lt_mask)] = tok;
-    if (valid && !keep && stage_of) stage_of[(size_t)h * N + tok] = stage;
-    run += total;
-  }
-}
-
-// The three filter passes in one workgroup per head, for heads whose |U| is small.  A thread takes
-// four consecutive items per step (4096 per workgroup step), so most heads need one step.
-__global__ __launch_bounds__(1024) void filter_small(KState* __restrict__ st, const float* __restrict__ dist2, int N,
-                                                     const float* __restrict__ tau,
-                                                     const int32_t* __restrict__ ulist_in,
-                                                     int32_t* __restrict__ ulist_out, int32_t* __restrict__ stage_of,
-                                                     int stage) {
-  const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const KState s0 = st[h];
-  if (!s0.active) return;
-  const int n = min(s0.ucount, N);
-  const float t2 = tau[1];
-  __shared__ int32_t ws[16];
-  const float* dh = dist2 + (size_t)h * N;
-  const int32_t* uin = ulist_in ? ulist_in + (size_t)h * N : nullptr;
-  int32_t* uout = ulist_out + (size_t)h * N;
-  int32_t* sof = stage_of ? stage_of + (size_t)h * N : nullptr;
-  int run = 0;
-  for (int base = 0; base < n; base += 4096) {
-    const int p0 = base + 4 * tid;
-    bool keep[4]; int tok[4]; int c = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int p = p0 + i;
-      const bool valid = p < n;
-      keep[i] = valid && !(dh[p < n ? p : 0] < t2);
-      tok[i] = valid ? (uin ? uin[p] : p) : -1;
-      c += keep[i] ? 1 : 0;
+template <typename T, int D>
+__global__ __launch_bounds__(256) void stage_open(const T* __restrict__ X, OpenCfg c) {
+  constexpr int CPL = D / 64;
+  const int h = blockIdx.y, bx = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  struct { int ucount, ccount, m_t, stage, done, full, active; } s;      // the new state without its tables
+  auto report = [&](bool act) __attribute__((always_inline)) {
+    if (!c.report) return;
+    if (act) { atomicAdd(&c.sums[0], 1); atomicMax(&c.sums[1], s.ucount); atomicMax(&c.sums[2], s.m_t); }
+    __threadfence();
+    if (atomicAdd(&c.sums[3], 1) == (int)gridDim.y - 1) {
+      __threadfence();
+      for (int i = 0; i < 3; ++i) c.report[i] = atomicExch(&c.sums[i], 0);
+      atomicExch(&c.sums[3], 0);
+      __hip_atomic_store(&c.report[3], c.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);     // (the host polls this word)
     }
-    // exclusive prefix of the per-thread counts: inside the wave by shuffles, across waves through LDS
-    int incl = c;
+  };
+  __shared__ int32_t wtot[4], s_before, s_blk[4], s_rank[4];
+  int total = c.N, ex = 0, mine = 0, b0 = 0, b1 = 0, n = c.N;
+  const int32_t* cnt = c.cnt + (size_t)h * c.cnt_stride;
+  // this thread's points, where the workgroup moves survivors
+  constexpr int IPT = KEEP_ITEMS / 256;
+  const float* dh = c.dist2 + (size_t)h * c.N;
+  const int ipt = c.items >> 8 ? c.items >> 8 : 1, p0 = bx * c.items + tid * ipt;
+  const bool has = tid * ipt < c.items;
+  float d2[IPT]; int tok_in[IPT];
+  if (c.first) {
+    s.ucount = c.N; s.ccount = 0; s.m_t = 0; s.stage = 0; s.done = 0; s.full = 0;
+    if (c.sums && h == 0 && bx == 0 && tid < 4) c.sums[tid] = 0;
+  } else {
+    const KState& o = c.in[h];
+    const int c0 = cnt[min(tid, c.cnt_stride - 1)];          // (ahead of the state: one trip for both)
+    if (!o.active) {               // closed before: carried over
+      if (bx == 0) {
+        if (tid < (int)(sizeof(KState) / 4)) reinterpret_cast<int32_t*>(&c.out[h])[tid] = reinterpret_cast<const int32_t*>(&o)[tid];
+        if (tid == 0) report(false);
+      }
+      return;
+    }
+    s.ucount = o.ucount; s.ccount = o.ccount; s.m_t = o.m_t; s.stage = o.stage; s.full = o.full; s.done = 0;
+    n = min(s.ucount, c.N);
+    const int nb = (n + c.items - 1) / c.items;
+    if (bx < c.nblk) {
+      if (bx >= nb) return;        // (bx 0 stays: an active head has a point)
+#pragma unroll
+      for (int i = 0; i < IPT; ++i) {
+        const int p = p0 + i;
+        const bool valid = has && i < ipt && p < n;
+        d2[i] = dh[valid ? p : 0];
+        tok_in[i] = valid ? (c.uin ? c.uin[(size_t)h * c.N + p] : p) : -1;
+      }
+    }
+    int before = 0;
+    if (nb <= 256) {
+      b0 = min(nb, tid); b1 = min(nb, tid + 1);
+      mine = tid < nb ? c0 : 0;
+    } else {
+      const int per = (nb + 255) / 256;
+      b0 = min(nb, tid * per); b1 = min(nb, b0 + per);
+      for (int b = b0; b < b1; ++b) { const int v = cnt[b]; mine += v; before += b < bx ? v : 0; }
+    }
+    int incl = mine;
+#pragma unroll
+    for (int o2 = 1; o2 < 64; o2 <<= 1) { const int v = __shfl_up(incl, o2); if (lane >= o2) incl += v; }
+    if (lane == 63) wtot[wave] = incl;
+    __syncthreads();
+    total = 0;
+    ex = incl - mine;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) { const int v = wtot[w]; if (w < wave) ex += v; total += v; }
+    if (bx >= b0 && bx < b1) s_before = ex + before;
+    s.ucount = total; s.ccount += s.m_t; s.stage += 1;
+  }
+  // head of the while-loop
+  if (s.ucount == 0) s.done = 1;
+  else if (s.ccount >= c.n_max) { s.full = 1; s.done = 1; }
+  else if (s.stage >= c.max_stages || s.ucount <= c.u_min) s.done = 1;
+  s.active = !s.done;
+  if (s.active) {
+    const int m = (int)(((long long)c.m0 * s.ucount + c.N - 1) / c.N);
+    s.m_t = min(max(c.m_min, min(c.m0, m)), s.ucount);
+  } else s.m_t = 0;
+  if (bx == 0 && tid == 0) {
+    KState& o = c.out[h];
+    o.ucount = s.ucount; o.ccount = s.ccount; o.m_t = s.m_t; o.stage = s.stage; o.done = s.done; o.full = s.full;
+    o.active = s.active; o.pad = 0;
+    report(s.active);
+  }
+  if (bx == 0 && tid <= ADACLUSTER_MAX_STAGES) {
+    const int i = tid;
+    c.out[h].stage_offs[i] = c.first ? 0 : i == s.stage ? s.ccount : c.in[h].stage_offs[i];
+    c.out[h].u_hist[i] = c.first ? (i == 0 ? c.N : 0) : i == s.stage ? total : c.in[h].u_hist[i];
+  }
+
+  if (bx < c.nblk) {               // the survivors of this workgroup's points move up, in order
+    __syncthreads();
+    const float t2 = c.tau[1];
+    bool keep[IPT]; int k = 0;
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) { keep[i] = tok_in[i] >= 0 && !(d2[i] < t2); k += keep[i] ? 1 : 0; }
+    int incl = k;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
+    const int before = s_before;
+    __syncthreads();               // every thread has its use of the wave totals behind it
+    if (lane == 63) wtot[wave] = incl;
     __syncthreads();
-    if (lane == 63) ws[wave] = incl;
-    __syncthreads();
-    int before = 0, total = 0;
-    for (int w = 0; w < 16; ++w) { const int v = ws[w]; if (w < wave) before += v; total += v; }
-    int pos = run + before + incl - c;
+    int pos = before + incl - k;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (keep[i]) uout[pos++] = tok[i];
-      else if (tok[i] >= 0 && sof) sof[tok[i]] = stage;
+    for (int w = 0; w < 4; ++w) if (w < wave) pos += wtot[w];
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+      if (keep[i]) c.uout[(size_t)h * c.N + pos++] = tok_in[i];
+      else if (tok_in[i] >= 0 && c.stage_of) c.stage_of[(size_t)h * c.N + tok_in[i]] = c.stage;
     }
-    run += total;
+    return;
   }
-  __syncthreads();      // every thread has taken its copy of the state
-  if (tid == 0) {
-    KState s = s0;
-    s.ucount = run;
-    s.ccount += s.m_t;
-    s.stage += 1;
-    s.stage_offs[s.stage] = s.ccount;
-    s.u_hist[s.stage] = run;
-    st[h] = s;
+
+  // initial centre j: survivor number floor((2j+1)|U| / 2m)
+  const int j0 = (bx - c.nblk) * 4, j = j0 + wave;
+  if (!s.active || j0 >= s.m_t) return;
+  long long pos = ((2ll * j + 1) * (long long)total) / (2ll * s.m_t);
+  int tok = (int)pos;
+  if (!c.first) {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {  // the thread whose run of counts holds it says in which count and how far into it
+      const long long q = ((2ll * (j0 + w) + 1) * (long long)total) / (2ll * s.m_t);
+      if (j0 + w < s.m_t && q >= ex && q < ex + mine) {
+        int b = b0, left = (int)q - ex;
+        for (; left >= cnt[b]; ++b) left -= cnt[b];
+        s_blk[w] = b; s_rank[w] = left;
+      }
+    }
+    __syncthreads();
+    if (j >= s.m_t) return;
+    const float t2 = c.tau[1];
+    const int base = s_blk[wave] * c.items;
+    int left = s_rank[wave], at = -1;
+    for (int q0 = 0; q0 < c.items && at < 0; q0 += 256) {      // 256 points at a time, their loads together
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = dh[min(base + q0 + 64 * u + lane, n - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int p = base + q0 + 64 * u + lane;
+        const uint64_t mask = __ballot(q0 + 64 * u < c.items && p < n && !(v[u] < t2));
+        const int here = __popcll(mask);
+        if (at < 0 && left < here) {
+          const bool it = ((mask >> lane) & 1) && __popcll(mask & (lane ? ~0ull >> (64 - lane) : 0ull)) == left;
+          at = base + q0 + 64 * u + __ffsll((unsigned long long)__ballot(it)) - 1;
+        }
+        left -= here;
+      }
+    }
+    tok = c.uin ? c.uin[(size_t)h * c.N + at] : at;
+  } else if (j >= s.m_t) return;
+  const T* row = X + ((size_t)h * c.N + tok) * D;
+  float bsum = 0.f;
+#pragma unroll
+  for (int q = 0; q < CPL; ++q) {          // the rows are of the I/O type: their copy for the assignment is exact
+    const int col = lane + 64 * q;
+    const T raw = row[col];
+    const float v = Elem<T>::load(&raw);
+    const size_t ao = ((size_t)h * c.cap + s.ccount + j) * D + col;
+    c.master[((size_t)h * c.master_stride + j) * D + col] = v;
+    reinterpret_cast<T*>(c.lp)[ao] = raw;
+    c.f32[ao] = v;
+    bsum = fmaf(v, v, bsum);
   }
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) bsum += __shfl_xor(bsum, o);
+  if (lane == 0) c.bias[(size_t)h * c.cap + s.ccount + j] = -0.5f * bsum;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1411,7 +1468,7 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
 
   for (bool first = true;; first = false) {
     if (!first) {
-      // head of the while-loop of Algorithm 1 (as kstage_begin)
+      // head of the while-loop of Algorithm 1 (as stage_open)
       if (tid == 0) {
         KState s = s_st;
         if (s.ucount == 0) s.done = 1;
@@ -1713,12 +1770,14 @@ __global__ void fill_i32(int32_t* p, size_t n, int32_t v) {
 }
 
 // k_count, full_flag and stage offsets out of the state; the threshold in use, if asked for
-__global__ void kstate_export(const KState* __restrict__ st, int H, int32_t* k_count, int32_t* full_flag,
+// (`home`: where later steps and calls look for the state, when the last stage left it elsewhere)
+__global__ void kstate_export(const KState* st, int H, KState* home, int32_t* k_count, int32_t* full_flag,
                               int32_t* stage_offs, const float* __restrict__ tau, float* __restrict__ tau_used) {
   const int h = blockIdx.x * blockDim.x + threadIdx.x;
   if (h == 0 && tau_used) tau_used[0] = tau[0];
   if (h >= H) return;
   const KState& s = st[h];
+  if (home != st) for (int i = 0; i < (int)(sizeof(KState) / 4); ++i) reinterpret_cast<int32_t*>(&home[h])[i] = reinterpret_cast<const int32_t*>(&s)[i];
   if (k_count) k_count[h] = s.ccount;
   if (full_flag) full_flag[h] = s.full;
   if (stage_offs)
@@ -1787,11 +1846,12 @@ int assign_block_sum_centres() { return ACC_MAXM; }
 int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, int mode, int m_const, int cap,
                   const KState* st, const int32_t* ulist, const void* X, const void* cent_lp, const float* bias,
                   int32_t* labels, float* dist2, float* blk_sum, int32_t* blk_cnt, int P, int32_t* keep_lab,
-                  float* keep_score, const int32_t* seed_lab, const float* seed_score) {
+                  float* keep_score, const int32_t* seed_lab, const float* seed_score, const float* tau, int32_t* keep_cnt,
+                  int keep_stride) {
   if ((mode == 3 || keep_lab || seed_lab) && (dtype != ADACLUSTER_BF16 || blk_sum)) return ADACLUSTER_E_INTERNAL;
-  AssignCfg c{mode, m_const, N, cap, st, ulist, keep_lab, keep_score, seed_lab, seed_score};
+  AssignCfg c{mode, m_const, N, cap, st, ulist, keep_lab, keep_score, seed_lab, seed_score, tau, keep_cnt, keep_stride};
   if (dtype == ADACLUSTER_BF16) {
-    dim3 g((n_bound + 255) / 256, H);
+    dim3 g((n_bound + ASSIGN_POINTS_LP - 1) / ASSIGN_POINTS_LP, H);
     const AccumOut ao{blk_sum, blk_cnt, P, (int)g.x};
     if (blk_sum) {
       if (d == 64) assign_mfma<64, true><<<g, 256, 0, s>>>((const bf16raw*)X, c, (const bf16raw*)cent_lp, bias, labels, dist2, ao);
@@ -1802,7 +1862,7 @@ int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, in
     }
   } else {
     if (blk_sum) return ADACLUSTER_E_INTERNAL;     // block sums exist for bf16 only
-    dim3 g((n_bound + 127) / 128, H);
+    dim3 g((n_bound + ASSIGN_POINTS_F32 - 1) / ASSIGN_POINTS_F32, H);
     if (d == 64) assign_f32<64><<<g, 128, 0, s>>>((const float*)X, c, (const float*)cent_lp, bias, labels, dist2);
     else assign_f32<128><<<g, 128, 0, s>>>((const float*)X, c, (const float*)cent_lp, bias, labels, dist2);
   }
@@ -1887,11 +1947,6 @@ int launch_init_centroids(hipStream_t s, int dtype, int d, int H, int N, int mod
   return chk();
 }
 
-int launch_kstate_init(hipStream_t s, KState* st, int H, int N) {
-  kstate_init<<<(H + 63) / 64, 64, 0, s>>>(st, H, N);
-  return chk();
-}
-
 int launch_kstate_warm(hipStream_t s, KState* st, int H, int N, int cap, const int32_t* k_count,
                        const int32_t* full_flag) {
   kstate_warm<<<(H + 63) / 64, 64, 0, s>>>(st, H, N, cap, k_count, full_flag);
@@ -1900,12 +1955,6 @@ int launch_kstate_warm(hipStream_t s, KState* st, int H, int N, int cap, const i
 
 int launch_kstate_commit(hipStream_t s, KState* st, int H) {
   kstate_commit<<<(H + 63) / 64, 64, 0, s>>>(st, H);
-  return chk();
-}
-
-int launch_kstage_begin(hipStream_t s, KState* st, int H, int N, int n_max, int m0, int m_min, int max_stages,
-                        int u_min, int32_t* summary) {
-  kstage_begin<<<1, 256, 0, s>>>(st, H, N, n_max, m0, m_min, max_stages, u_min, summary);
   return chk();
 }
 
@@ -1921,22 +1970,37 @@ int launch_tau(hipStream_t s, int H, int N, const float* dist2, double* part, fl
   return chk();
 }
 
-int launch_filter(hipStream_t s, KState* st, int H, int N, int n_bound, const float* dist2, const float* tau,
-                  int32_t* blockcnt, int32_t* u_prev, const int32_t* ulist_in, int32_t* ulist_out,
-                  int32_t* stage_of, int stage) {
-#ifndef FILTER_SMALL_LIMIT
-#define FILTER_SMALL_LIMIT 32768
-#endif
-  if (n_bound <= FILTER_SMALL_LIMIT) {
-    filter_small<<<H, 1024, 0, s>>>(st, dist2, N, tau, ulist_in, ulist_out, stage_of, stage);
-    return chk();
+int stage_points_per_count(int dtype) { return dtype == ADACLUSTER_BF16 ? ASSIGN_POINTS_LP : ASSIGN_POINTS_F32; }
+int launch_keep_count(hipStream_t s, const KState* st, int H, int N, const float* dist2, const float* tau, int32_t* cnt,
+                      int cnt_stride, int* items) {
+  keep_count<<<dim3((N + KEEP_ITEMS - 1) / KEEP_ITEMS, H), 256, 0, s>>>(st, dist2, N, tau, cnt, cnt_stride);
+  *items = KEEP_ITEMS;
+  return chk();
+}
+
+int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, int n_max, int m0, int m_min, int max_stages,
+                      int u_min, int n_bound, int m_bound, const KState* in, KState* out, const StageFilter* f,
+                      int32_t* sums, int32_t* report, int epoch, int master_stride, const void* X, float* master,
+                      void* assign_lp, float* assign_f32, float* bias) {
+  OpenCfg c{};
+  c.N = N; c.cap = cap; c.n_max = n_max; c.m0 = m0; c.m_min = m_min; c.max_stages = max_stages; c.u_min = u_min;
+  c.first = f == nullptr;
+  c.items = KEEP_ITEMS;
+  c.in = in; c.out = out; c.sums = sums; c.report = report; c.epoch = epoch;
+  c.master_stride = master_stride; c.master = master; c.lp = assign_lp; c.f32 = assign_f32; c.bias = bias;
+  if (f) {
+    if (f->items > KEEP_ITEMS) return ADACLUSTER_E_INTERNAL;
+    c.items = f->items; c.nblk = (n_bound + f->items - 1) / f->items; c.cnt_stride = f->cnt_stride;
+    c.dist2 = f->dist2; c.tau = f->tau; c.cnt = f->cnt; c.uin = f->uin; c.uout = f->uout; c.stage_of = f->stage_of; c.stage = f->stage;
   }
-  const int nblk = (N + 1023) / 1024;
-  const int nb = (n_bound + 1023) / 1024;
-  filter_count<<<dim3(nb, H), 256, 0, s>>>(st, dist2, N, nblk, tau, blockcnt);
-  filter_scan<<<H, 64, 0, s>>>(st, nb, nblk, blockcnt, u_prev);
-  filter_scatter<<<dim3(nb, H), 256, 0, s>>>(st, u_prev, dist2, N, nblk, tau, blockcnt, ulist_in, ulist_out,
-                                             stage_of, stage);
+  const dim3 g(c.nblk + (m_bound + 3) / 4, H);
+  if (dtype == ADACLUSTER_BF16) {
+    if (d == 64) stage_open<bf16raw, 64><<<g, 256, 0, s>>>((const bf16raw*)X, c);
+    else stage_open<bf16raw, 128><<<g, 256, 0, s>>>((const bf16raw*)X, c);
+  } else {
+    if (d == 64) stage_open<float, 64><<<g, 256, 0, s>>>((const float*)X, c);
+    else stage_open<float, 128><<<g, 256, 0, s>>>((const float*)X, c);
+  }
   return chk();
 }
 
@@ -1976,9 +2040,9 @@ int launch_fill_i32(hipStream_t s, int32_t* p, size_t n, int32_t v) {
   return chk();
 }
 
-int launch_kstate_export(hipStream_t s, const KState* st, int H, int32_t* k_count, int32_t* full_flag,
+int launch_kstate_export(hipStream_t s, const KState* st, int H, KState* home, int32_t* k_count, int32_t* full_flag,
                          int32_t* stage_offs, const float* tau, float* tau_used) {
-  kstate_export<<<(H + 63) / 64, 64, 0, s>>>(st, H, k_count, full_flag, stage_offs, tau, tau_used);
+  kstate_export<<<(H + 63) / 64, 64, 0, s>>>(st, H, home, k_count, full_flag, stage_offs, tau, tau_used);
   return chk();
 }
 

@@ -30,7 +30,8 @@ int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, in
                   const KState* st, const int32_t* ulist, const void* X, const void* cent_lp, const float* bias,
                   int32_t* labels, float* dist2, float* blk_sum = nullptr, int32_t* blk_cnt = nullptr, int P = 0,
                   int32_t* keep_lab = nullptr, float* keep_score = nullptr, const int32_t* seed_lab = nullptr,
-                  const float* seed_score = nullptr);
+                  const float* seed_score = nullptr,
+                  const float* tau = nullptr, int32_t* keep_cnt = nullptr, int keep_stride = 0);
 int assign_block_sum_centres();   // most centres the assignment kernel keeps block sums for
 int launch_seg_reduce(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int P,
                       const KState* st, int normalize, int want_box, const void* X, const int32_t* perm,
@@ -61,16 +62,27 @@ int launch_init_centroids(hipStream_t s, int dtype, int d, int H, int N, int mod
                           const KState* st, const int32_t* ulist, int spherical, int source_master, int cap,
                           int master_stride, const void* X, float* master, void* assign_lp, float* assign_f32,
                           float* bias);
-int launch_kstate_init(hipStream_t s, KState* st, int H, int N);
 int launch_kstate_warm(hipStream_t s, KState* st, int H, int N, int cap, const int32_t* k_count, const int32_t* full_flag);
 int launch_kstate_commit(hipStream_t s, KState* st, int H);
-int launch_kstage_begin(hipStream_t s, KState* st, int H, int N, int n_max, int m0, int m_min, int max_stages,
-                        int u_min, int32_t* summary);
 int launch_tau(hipStream_t s, int H, int N, const float* dist2, double* part, float factor, float tau_abs,
                float* tau_out);
-int launch_filter(hipStream_t s, KState* st, int H, int N, int n_bound, const float* dist2, const float* tau,
-                  int32_t* blockcnt, int32_t* u_prev, const int32_t* ulist_in, int32_t* ulist_out,
-                  int32_t* stage_of, int stage);
+// What the end of a stage leaves behind for launch_stage_open: squared distances of its last pass and the survivors per
+// `items` points (launch_assign with keep_cnt counts per stage_points_per_count(), launch_keep_count per its own).
+struct StageFilter {
+  const float* dist2; const float* tau; const int32_t* cnt; int cnt_stride; int items;
+  const int32_t* uin /* NULL: every token */; int32_t* uout; int32_t* stage_of /* may be NULL */; int stage;
+};
+int stage_points_per_count(int dtype);
+int launch_keep_count(hipStream_t s, const KState* st, int H, int N, const float* dist2, const float* tau, int32_t* cnt,
+                      int cnt_stride, int* items);
+// Filter of the stage that ends (f; NULL: none, the first stage opens), head of the loop of Algorithm 1, initial centres of
+// the stage that opens.  n_bound, m_bound: no head has more points in the stage that ends, or centres in the one that opens.
+// The state goes from `in` to `out`, which must differ; sums: 4 device integers; report (mapped host memory, may be
+// NULL): {active heads, max |U|, max m_t, epoch}, the epoch behind the rest.
+int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, int n_max, int m0, int m_min, int max_stages,
+                      int u_min, int n_bound, int m_bound, const KState* in, KState* out, const StageFilter* f,
+                      int32_t* sums, int32_t* report, int epoch, int master_stride, const void* X, float* master,
+                      void* assign_lp, float* assign_f32, float* bias);
 // Every remaining stage of Algorithm 1 in one launch, one workgroup per head (bf16 only).  Valid once every
 // active head has at most small_stage_points() unassigned points and small_stage_centres() centres per
 // stage, and never for stage 0 (it needs a list of U and a known tau).
@@ -82,7 +94,7 @@ int launch_kstages_small(hipStream_t s, int d, int H, int N, int cap, int n_max,
 int launch_mse(hipStream_t s, int dtype, int d, int H, int N, int cap, const void* X, const int32_t* labels,
                const float* cent, double* part, float* mse);
 int launch_fill_i32(hipStream_t s, int32_t* p, size_t n, int32_t v);
-int launch_kstate_export(hipStream_t s, const KState* st, int H, int32_t* k_count, int32_t* full_flag,
+int launch_kstate_export(hipStream_t s, const KState* st, int H, KState* home, int32_t* k_count, int32_t* full_flag,
                          int32_t* stage_offs, const float* tau = nullptr, float* tau_used = nullptr);
 
 int launch_select(hipStream_t s, int H, int Cq, int cap, int d, int score_mode, int select_mode, int topk,

@@ -1,0 +1,47 @@
+"""The head of a stage of Algorithm 1 (filter of the stage before, new U, its strided sample) where its work is cut: lengths
+around the counted blocks (128, 256 and 1024 points), more blocks than threads, both dtypes.  With one assignment pass
+per stage the stage's centres are the strided sample itself, so they are compared exactly."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import adacluster_oracle as orc
+from paper_2604_18348_amd import binding as B
+from paper_2604_18348_amd import workloads as wl
+from tests.helpers import to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,d,N", [(B.BF16, 64, 1023), (B.BF16, 64, 1024), (B.BF16, 128, 1025), (B.F32, 64, 257),
+                                       (B.F32, 128, 2049), (B.BF16, 64, 4097), (B.BF16, 64, 270001), (B.F32, 64, 140001)])
+def test_stage_centres_are_the_strided_sample_of_what_was_left(dtype, d, N):
+    H = 2 if N < 10000 else 1
+    K = np.random.default_rng(N).standard_normal((H, N, d)).astype(np.float32)
+    if dtype == B.BF16:
+        K = wl.round_bf16_f32(K)
+    # more than 32 centres in every stage: the stages stay out of the one-launch kernel for short lists
+    p = B.Params(H=H, N=N, d=d, dtype=dtype, q_clusters=4, k_iters=1, k_m0=64, k_m_min=40, k_max_clusters=400,
+                 k_max_stages=4, tau_abs=1.30 * d ** 0.5)
+    out = B.adacluster_kcluster(p, to_dev(K, dtype))
+    torch.cuda.synchronize()
+    offs, stage_of = out["k_stage_offs"].cpu().numpy(), out["k_stage_of"].cpu().numpy()
+    ca, kc = to_np(out["k_assign_centroids"]), out["k_count"].cpu().numpy()
+    for h in range(H):
+        left = np.arange(N)
+        stages = int(np.searchsorted(offs[h], kc[h]))
+        assert stages >= 2, offs[h]
+        for t in range(stages):
+            m = offs[h, t + 1] - offs[h, t]
+            assert m == orc.stage_cluster_count(left.size, N, p.k_m0, p.k_m_min)
+            C = ca[h, offs[h, t]:offs[h, t + 1]]
+            assert np.array_equal(C, K[h][left[orc.strided_indices(left.size, m)]])
+            # removed exactly where the nearest centre is nearer than tau, up to fp32 rounding of the distances
+            X = K[h][left].astype(np.float64)
+            xx = (X * X).sum(1)
+            d2 = (xx[:, None] + (C.astype(np.float64) ** 2).sum(1)[None] - 2.0 * X @ C.T.astype(np.float64)).min(1)
+            gone = stage_of[h, left] == t
+            wrong = gone != (d2 < p.tau_abs ** 2)
+            assert np.all(np.abs(d2[wrong] - p.tau_abs ** 2) <= 1e-5 * (xx[wrong] + xx.max()))
+            left = left[~gone]
+        assert np.all(stage_of[h, left] == -1)
