@@ -553,8 +553,8 @@ int run_plan_attention(const adacluster_params* p, const WS& w, hipStream_t st, 
                             D.cap + 1, k_count, sel_idx, sel_cnt, w.rng_start, w.rng_pre, w.rng_cnt, w.tiles, w.ntiles,
                             w.merge, w.nmerge, key_row_scale(p), w.krow, attn_krow_stride(D.N), w.perm_k, D.N));
   prof_mark(EV_PLAN, st, prof_from);
-  RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, D.Cq, D.maxtiles, D.maxr, scale, Q, K, V, O, w.perm_q,
-                          w.tiles, w.ntiles, w.rng_pre, w.rng_cnt, w.part_o, w.part_ml, w.merge, w.nmerge,
+  RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, D.Cq, D.maxtiles, scale, Q, K, V, O, w.perm_q,
+                          w.tiles, w.ntiles, w.part_o, w.part_ml, w.merge, w.nmerge,
                           w.krow, attn_krow_stride(D.N)));
   prof_mark(EV_ATTN, st);
   return 0;
@@ -780,8 +780,8 @@ int adacluster_dense_attn(const adacluster_params* p, const void* Q, const void*
   RET_IF(launch_plan_dense(st, D.H, D.N, D.maxtiles, attn_block_rows(p->dtype, D.d, D.N, 1), w.rng_start, w.rng_pre, w.rng_cnt, w.tiles, w.ntiles,
                            key_row_scale(p), w.krow, attn_krow_stride(D.N)));
   prof_mark(EV_PLAN, st);
-  RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, 1, D.maxtiles, 1, scale, Q, K, V, O, nullptr, w.tiles,
-                          w.ntiles, w.rng_pre, w.rng_cnt, w.part_o, w.part_ml, nullptr, nullptr,
+  RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, 1, D.maxtiles, scale, Q, K, V, O, nullptr, w.tiles,
+                          w.ntiles, w.part_o, w.part_ml, nullptr, nullptr,
                           w.krow, attn_krow_stride(D.N)));
   prof_mark(EV_ATTN, st);
   return 0;

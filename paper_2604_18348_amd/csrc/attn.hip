@@ -148,7 +148,6 @@ __global__ __launch_bounds__(256) void plan_tiles(int Cq, int maxr, int maxtiles
   int32_t* tl = tiles + (size_t)h * maxtiles * TILE_REC;
   int32_t* ml = merge + (size_t)h * slots * 4;
   __shared__ int32_t s_T[MAXC], s_nq[MAXC], s_pieces[MAXC], s_tile0[MAXC], s_slot0[MAXC], s_merge0[MAXC], s_tot[MAXC];
-  __shared__ int32_t s_chunk;
   const int C = min(Cq, MAXC);
   for (int c = tid; c < C; c += 256) {
     s_nq[c] = (qo[c + 1] - qo[c] + BM - 1) / BM;
@@ -157,39 +156,75 @@ __global__ __launch_bounds__(256) void plan_tiles(int Cq, int maxr, int maxtiles
     s_tot[c] = tot;
   }
   __syncthreads();
-  if (tid == 0) {
+  // A thread looks after the clusters tid * per .., so that prefix sums over the threads are in cluster order.  Only the
+  // lists that are cut are dealt with one after the other (all of them by one thread: 15 us at 65 clusters, now 6).
+  const int per = (C + 255) / 256, c0 = min(C, tid * per), c1 = min(C, c0 + per), lane = tid & 63, wave = tid >> 6;
+  __shared__ long long w_work[4];
+  __shared__ int32_t w_a[4], w_b[4];
+  __shared__ int32_t s_cut, s_list[MAXC];
+  auto wave_prefix = [&](int v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) { const int u = __shfl_up(v, o); if (lane >= o) v += u; }
+    return v;
+  };
+  {
     // key tiles per chunk of a list that is cut: twice the average list of the head, at least 16
     long long work = 0; int qtiles = 0;
-    for (int c = 0; c < C; ++c) { work += (long long)s_nq[c] * s_T[c]; qtiles += s_nq[c]; }
-    const int mean_t = qtiles > 0 ? (int)((work + qtiles - 1) / qtiles) : 0;
-    const int chunk = max(16, 2 * mean_t);
-    s_chunk = chunk;
-    // which lists are cut (in cluster order, while slots last), and where every cluster's records start
-    int nt = 0, used = 0, nm = 0;
-    for (int c = 0; c < C; ++c) {
-      const int T = s_T[c];
-      int pieces = 1;
-      if (allow_split && T > 2 * chunk) {
-        pieces = min(16, (T + chunk - 1) / chunk);
-        if (used + pieces * s_nq[c] > slots) pieces = max(1, (slots - used) / max(s_nq[c], 1));   // fewer, longer chunks
-      }
+    for (int c = c0; c < c1; ++c) { work += (long long)s_nq[c] * s_T[c]; qtiles += s_nq[c]; }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) { work += __shfl_xor(work, o); qtiles += __shfl_xor(qtiles, o); }
+    if (lane == 0) { w_work[wave] = work; w_a[wave] = qtiles; }
+  }
+  __syncthreads();
+  const long long work = w_work[0] + w_work[1] + w_work[2] + w_work[3];
+  const int qtiles = w_a[0] + w_a[1] + w_a[2] + w_a[3];
+  const int chunk = max(16, 2 * (qtiles > 0 ? (int)((work + qtiles - 1) / qtiles) : 0));
+  // which lists are cut: the long ones are listed in cluster order, and one thread deals the slots out while they last
+  int cuts = 0;
+  for (int c = c0; c < c1; ++c) { s_pieces[c] = 1; cuts += allow_split && s_T[c] > 2 * chunk; }
+  const int cin = wave_prefix(cuts);
+  if (lane == 63) w_b[wave] = cin;
+  __syncthreads();
+  {
+    int at = cin - cuts;
+    for (int w = 0; w < wave; ++w) at += w_b[w];
+    for (int c = c0; c < c1; ++c) if (allow_split && s_T[c] > 2 * chunk) s_list[at++] = c;
+    if (tid == 255) s_cut = at;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    int used = 0, nm = 0;
+    for (int i = 0; i < s_cut; ++i) {
+      const int c = s_list[i], T = s_T[c];
+      int pieces = min(16, (T + chunk - 1) / chunk);
+      if (used + pieces * s_nq[c] > slots) pieces = max(1, (slots - used) / max(s_nq[c], 1));   // fewer, longer chunks
       if (pieces > 1) {
-        const int per = (T + pieces - 1) / pieces;
-        pieces = max(1, (T + per - 1) / max(per, 1));          // no empty chunk
+        const int per_piece = (T + pieces - 1) / pieces;
+        pieces = max(1, (T + per_piece - 1) / max(per_piece, 1));          // no empty chunk
       }
-      s_pieces[c] = pieces; s_tile0[c] = nt; s_slot0[c] = used; s_merge0[c] = nm;
-      nt += s_nq[c] * pieces;
+      s_pieces[c] = pieces; s_slot0[c] = used; s_merge0[c] = nm;
       if (pieces > 1) { used += s_nq[c] * pieces; nm += s_nq[c]; }
     }
-    ntiles[h] = nt;
     nmerge[h] = nm;
+  }
+  __syncthreads();
+  {                                              // where every cluster's records start
+    int mine = 0;
+    for (int c = c0; c < c1; ++c) mine += s_nq[c] * s_pieces[c];
+    const int incl = wave_prefix(mine);
+    if (lane == 63) w_a[wave] = incl;
+    __syncthreads();
+    int nt = incl - mine;
+    for (int w = 0; w < wave; ++w) nt += w_a[w];
+    for (int c = c0; c < c1; ++c) { s_tile0[c] = nt; nt += s_nq[c] * s_pieces[c]; }
+    if (tid == 255) ntiles[h] = nt;
   }
   __syncthreads();
   // records of every cluster, one thread per cluster
   for (int c = tid; c < C; c += 256) {
     const int s0 = qo[c], e0 = qo[c + 1], T = s_T[c], pieces = s_pieces[c];
     const int per = (T + pieces - 1) / pieces;
-    int nt = s_tile0[c], slot = s_slot0[c], nm = s_merge0[c];
+    int nt = s_tile0[c], slot = pieces > 1 ? s_slot0[c] : 0, nm = pieces > 1 ? s_merge0[c] : 0;
     for (int r0 = s0; r0 < e0; r0 += BM) {
       const int rows = min(BM, e0 - r0);
       if (pieces > 1) {
@@ -280,8 +315,7 @@ struct AttnArgs {
   const void* Q; const void* K; const void* V; void* O;
   const int32_t* perm_q;        // sorted query position -> token (NULL: identity)
   const int32_t* tiles; const int32_t* ntiles;
-  const int32_t* rng_pre; const int32_t* rng_cnt;
-  int H, N, Cq, maxtiles, maxr;
+  int H, N, Cq, maxtiles;
   float scale_log2e;            // softmax scale x log2(e)
   int head_major;               // workgroup -> (head, tile) mapping, see attn_mfma
   float* part_o; float* part_ml;   // partial slots of cut key lists: [H][slots][BM][d], [H][slots][BM][2]
@@ -390,11 +424,9 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, hb = lane >> 5;
 
-  const int nr = a.rng_cnt[(size_t)h * a.Cq + qc];
-  const int32_t* rp = a.rng_pre + ((size_t)h * a.Cq + qc) * (a.maxr + 1);
   // positions below are relative to the first key of the share
   const int pbase = kt0 * BN;
-  const int total = max(0, min(rp[nr], kt1 * BN) - pbase);
+  const int total = max(0, min(tl[6], kt1 * BN) - pbase);     // (tl[6]: keys of the whole list; two dependent loads fewer than from the ranges)
   const int T = (total + BN - 1) / BN;
   const int32_t* krow = a.krow + ((size_t)h * a.Cq + qc) * a.kstride + pbase;   // byte offsets of the key rows
 
@@ -1104,12 +1136,11 @@ int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, int BM, int32_t
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
 }
 
-int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int maxtiles, int maxr, float scale,
+int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int maxtiles, float scale,
                      const void* Q, const void* K, const void* V, void* O, const int32_t* perm_q,
-                     const int32_t* tiles, const int32_t* ntiles, const int32_t* rng_pre,
-                     const int32_t* rng_cnt, float* part_o, float* part_ml,
+                     const int32_t* tiles, const int32_t* ntiles, float* part_o, float* part_ml,
                      const int32_t* merge, const int32_t* nmerge, const int32_t* krow, size_t kstride) {
-  AttnArgs a{Q, K, V, O, perm_q, tiles, ntiles, rng_pre, rng_cnt, H, N, Cq, maxtiles, maxr,
+  AttnArgs a{Q, K, V, O, perm_q, tiles, ntiles, H, N, Cq, maxtiles,
              scale * 1.4426950408889634f,
              (Cq == 1 || (size_t)4 * N * d <= ((size_t)8 << 20)) ? 1 : 0,
              part_o, part_ml, SPLIT_SLOTS, attn_block_rows(dtype, d, N, Cq), krow, kstride};

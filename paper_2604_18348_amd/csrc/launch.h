@@ -123,10 +123,9 @@ int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, int BM, int32_t
 size_t attn_krow_stride(int N);
 int launch_attn_stats(hipStream_t s, int H, int Cq, int maxr, int maxtiles, const KState* st, const int32_t* tiles,
                       const int32_t* ntiles, const int32_t* rng_pre, const int32_t* rng_cnt, adacluster_head_stats* out);
-int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int maxtiles, int maxr, float scale,
+int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int maxtiles, float scale,
                      const void* Q, const void* K, const void* V, void* O, const int32_t* perm_q,
-                     const int32_t* tiles, const int32_t* ntiles, const int32_t* rng_pre,
-                     const int32_t* rng_cnt, float* part_o, float* part_ml,
+                     const int32_t* tiles, const int32_t* ntiles, float* part_o, float* part_ml,
                      const int32_t* merge /* NULL: no cut lists */, const int32_t* nmerge,
                      const int32_t* krow, size_t kstride);
 
