@@ -222,7 +222,7 @@ Dims dims_of(const adacluster_params* p) {
   D.prow = p->N / reduce_part_rows() + D.capmax + 34;
   {  // rows of the block-sum table of small stages: (blocks of 256 points) x (centres), both capped
     const int nb = (p->N + 255) / 256, mb = p->k_m0 < assign_block_sum_centres() ? p->k_m0 : assign_block_sum_centres();
-    D.brow = (nb < STAGE_SUM_BLOCKS ? nb : STAGE_SUM_BLOCKS) * mb;
+    D.brow = (nb < STAGE_SUM_BLOCKS ? nb : STAGE_SUM_BLOCKS) * assign_block_sum_rows(mb);
   }
   return D;
 }
@@ -473,8 +473,8 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     // assignment kernel leaves per block: no label sort and no segmented reduction in between.
     const int nblk = (n_bound + 255) / 256;
     const bool block_sums = p->dtype == ADACLUSTER_BF16 && nblk <= STAGE_SUM_BLOCKS &&
-                            m_bound <= assign_block_sum_centres() && (long long)m_bound * nblk <= D.brow;
-    const int Pb = m_bound * nblk;     // rows of the part-sum table the block sums take per head
+                            m_bound <= assign_block_sum_centres() && (long long)assign_block_sum_rows(m_bound) * nblk <= D.brow;
+    const int Pb = assign_block_sum_rows(m_bound) * nblk;     // rows of the part-sum table the block sums take per head
     for (int it = 0; it < p->k_iters; ++it) {
       const bool update = it < p->k_iters - 1;
       if (block_sums && update) {

@@ -53,17 +53,18 @@ __device__ __forceinline__ bool assign_setup(const AssignCfg& c, int h, int& n, 
 // points of its block that chose it, so that the centroid update needs neither a label sort nor a
 // segmented reduction.  The sums are a second MFMA product, S^T[32 dims x 32 centres] +=
 // X^T[32 dims x 16 points] . E[16 points x 32 centres] with E the one-hot label matrix: exact products,
-// fp32 accumulation in a fixed order.  Block b of head h writes row j * nb_stride + b of the head's
-// part-sum table and bcnt[(h * nb_stride + b) * ACC_MAXM + j].
+// fp32 accumulation in a fixed order.  Block b of head h writes the rows (j * nb_stride + b) * acc_parts(m) .. of the
+// head's part-sum table and bcnt[(h * nb_stride + b) * ACC_MAXM + j].
 struct AccumOut { float* psum; int32_t* bcnt; int P; int nb_stride; };
 constexpr int ACC_MAXM = 128;          // most centres the block sums are kept for
+__host__ __device__ constexpr int acc_parts(int m) { return m <= 32 ? 4 : m <= 64 ? 2 : 1; }     // rows of sums a block leaves per centre
 
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4_t;
 typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 template <int D, bool ACC>
-__global__ __launch_bounds__(256, (ACC && D == 128) ? 1 : 2) void assign_mfma(const bf16raw* __restrict__ X, AssignCfg cfg,
+__global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict__ X, AssignCfg cfg,
                                                                 const bf16raw* __restrict__ cent,
                                                                 const float* __restrict__ bias,
                                                                 int32_t* __restrict__ labels, float* __restrict__ dist2,
@@ -85,8 +86,14 @@ __global__ __launch_bounds__(256, (ACC && D == 128) ? 1 : 2) void assign_mfma(co
   // both may touch the same object, so the load of chunk i+1 runs under the arithmetic of chunk i).
   // Rows are unpadded; piece g of row r sits in slot g ^ swz(r), which keeps the 16-byte operand
   // reads of 16 consecutive rows in 16 different bank groups.
-  __shared__ __attribute__((aligned(16))) char cs0[CB * CROWB];
-  __shared__ __attribute__((aligned(16))) char cs1[CB * CROWB];
+  // ACC: both lie in the buffer that takes the points afterwards (a stage that small has a chunk or two, and what counts
+  // is that two workgroups fit a CU: d=128 99 KB in buffers of their own, 12 heads of 6 800 points 24 us, in one 67 KB 16).
+  __shared__ __attribute__((aligned(16))) char own0[ACC ? 16 : CB * CROWB];
+  __shared__ __attribute__((aligned(16))) char own1[ACC ? 16 : CB * CROWB];
+  __shared__ __attribute__((aligned(16))) char pool[ACC ? 256 * CROWB : 16];
+  static_assert(256 >= 2 * CB, "the chunks fit the buffer of the points");
+  char* const cs0 = ACC ? pool : own0;
+  char* const cs1 = ACC ? pool + CB * CROWB : own1;
   __shared__ __attribute__((aligned(16))) float bs0[CB];
   __shared__ __attribute__((aligned(16))) float bs1[CB];
   auto swz = [](int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); };
@@ -267,92 +274,47 @@ __global__ __launch_bounds__(256, (ACC && D == 128) ? 1 : 2) void assign_mfma(co
   }
   if constexpr (ACC) {
     constexpr int ROWB = D * 2, DT = D / 32;
-    __shared__ __attribute__((aligned(16))) bf16raw xs[256 * D];     // the block's points, row-major
+    // The block's points lie row by row in `pool`.  Piece q (16 bytes) of row r sits in slot q ^ xswz(r), as in qpass_mfma:
+    // unswizzled, all rows of a store meet in the same banks.
+    auto xswz = [](int r) { return D == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : ((((r >> 1) & 1) << 2) | (((r >> 1) & 7) >> 1)); };
     __shared__ __attribute__((aligned(16))) int32_t lab_s[256];
+    __shared__ int32_t cnt_s[ACC_MAXM];
+    if (tid < ACC_MAXM) cnt_s[tid] = 0;
 #pragma unroll
     for (int pb = 0; pb < PB; ++pb) {
       const int pr = wave * (PB * 32) + pb * 32 + c;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<bf16x8_t*>(&xs[pr * D + ks * 16 + hb * 8]) = xf[pb][ks];
+      for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<bf16x8_t*>(pool + pr * ROWB + (((ks * 2 + hb) ^ xswz(pr)) * 16)) = xf[pb][ks];
       if (hb == 0) lab_s[pr] = blab[pb];
     }
     __syncthreads();
-    const int b = blockIdx.x;
-    // output tiles (centre tile ct, dim tile db) dealt to the four waves; one more "dim tile" per centre
-    // tile has X^T replaced by ones, so that its rows are the member counts (exact: at most 256)
-    const int CT = (m + 31) >> 5;
+    // A wave takes a whole centre tile, so that the one-hot operand of a group of 16 points (twenty vector instructions,
+    // more than the product it feeds) is built once and serves every dim tile.  With one or two centre tiles the four
+    // waves share the points of a tile instead (acc_parts quarters or halves of the block, a row of sums each): dealing
+    // (centre tile, dim tile) pairs over all points built every operand four or five times (30 heads, 40 centres, d=64:
+    // 11 us a pass, now 8; 30 x 17 776 points, 128 centres 55 -> 40).
+    const int b = blockIdx.x, CT = (m + 31) >> 5, R = acc_parts(m), G = 16 / R, part = wave % R;
     // X^T operand by transpose reads (see the V operand of the attention kernel): this lane addresses
     // point 4*hb + (lane%16)/4 of a 16-point group, dims 16*((lane/16)%2) + 4*(lane%4) .. +3
     const int i16 = lane & 15, blk = lane >> 4;
     const int vrow = 4 * hb + (i16 >> 2);
     const int gl = 2 * (blk & 1) + ((i16 & 3) >> 1);
-    const char* xsb = reinterpret_cast<const char*>(xs);
-    if (CT >= 4) {
-      // Many centre tiles: a wave takes whole centre tiles, so that the one-hot operand of a group of
-      // 16 points (twenty vector instructions, more than the product it feeds) is built once and serves
-      // every dim tile and the counting tile.
-      const uint4 ones4 = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
-      const bf16x8_t ones = *reinterpret_cast<const bf16x8_t*>(&ones4);
-      for (int ct = wave; ct < CT; ct += 4) {
-        const int cid = ct * 32 + c;
-        f32x16_t sacc[DT + 1];
+    int xlo[DT], xhi[DT];
 #pragma unroll
-        for (int t = 0; t <= DT; ++t)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) sacc[t][v] = 0.f;
-        const int xoff = vrow * ROWB + gl * 16 + 8 * (i16 & 1);
-#pragma unroll 4
-        for (int g = 0; g < 16; ++g) {
-          const int4 l0 = *reinterpret_cast<const int4*>(&lab_s[g * 16 + 4 * hb]);
-          const int4 l1 = *reinterpret_cast<const int4*>(&lab_s[g * 16 + 8 + 4 * hb]);
-          uint4 e;
-          e.x = (l0.x == cid ? 0x3F80u : 0u) | (l0.y == cid ? 0x3F800000u : 0u);
-          e.y = (l0.z == cid ? 0x3F80u : 0u) | (l0.w == cid ? 0x3F800000u : 0u);
-          e.z = (l1.x == cid ? 0x3F80u : 0u) | (l1.y == cid ? 0x3F800000u : 0u);
-          e.w = (l1.z == cid ? 0x3F80u : 0u) | (l1.w == cid ? 0x3F800000u : 0u);
-          const bf16x8_t eb = *reinterpret_cast<const bf16x8_t*>(&e);
-#pragma unroll
-          for (int db = 0; db < DT; ++db) {
-            const char* xp = xsb + g * 16 * ROWB + xoff + db * 64;
-            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)xp);
-            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(xp + 8 * ROWB));
-            const s16x4_t both[2] = {lo, hi};
-            sacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(both), eb, sacc[db], 0, 0, 0);
-          }
-          sacc[DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, eb, sacc[DT], 0, 0, 0);
-        }
-        if (cid < m) {
-          if (hb == 0) acc_out.bcnt[((size_t)h * acc_out.nb_stride + b) * ACC_MAXM + cid] = (int)sacc[DT][0];
-#pragma unroll
-          for (int db = 0; db < DT; ++db) {
-            float* out = acc_out.psum + ((size_t)h * acc_out.P + (size_t)cid * acc_out.nb_stride + b) * D + db * 32 + 4 * hb;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const float4 o4 = {sacc[db][4 * i], sacc[db][4 * i + 1], sacc[db][4 * i + 2], sacc[db][4 * i + 3]};
-              *reinterpret_cast<float4*>(out + 8 * i) = o4;
-            }
-          }
-        }
-      }
-      return;
+    for (int db = 0; db < DT; ++db) {
+      xlo[db] = vrow * ROWB + (((db * 4 + gl) ^ xswz(vrow)) * 16) + 8 * (i16 & 1);
+      xhi[db] = (vrow + 8) * ROWB + (((db * 4 + gl) ^ xswz(vrow + 8)) * 16) + 8 * (i16 & 1);
     }
-    for (int t = wave; t < CT * (DT + 1); t += 4) {
-      const int ct = t / (DT + 1), db = t % (DT + 1);
-      const bool counting = db == DT;
+    if (lab_s[tid] >= 0) atomicAdd(&cnt_s[lab_s[tid]], 1);
+    for (int ct = wave / R; ct < CT; ct += 4 / R) {
       const int cid = ct * 32 + c;
-      f32x16_t sacc;
+      f32x16_t sacc[DT];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
-      const int xoff = vrow * ROWB + ((counting ? 0 : db) * 4 + gl) * 16 + 8 * (i16 & 1);
+      for (int t = 0; t < DT; ++t)
 #pragma unroll
-      for (int g = 0; g < 16; ++g) {
-        const char* xp = xsb + g * 16 * ROWB + xoff;
-        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)xp);
-        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(xp + 8 * ROWB));
-        const s16x4_t both[2] = {lo, hi};
-        bf16x8_t xa = *reinterpret_cast<const bf16x8_t*>(both);
-        if (counting) { const uint4 o = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u}; xa = *reinterpret_cast<const bf16x8_t*>(&o); }
-        // one-hot rows of the points this lane's eight operand elements stand for
+        for (int v = 0; v < 16; ++v) sacc[t][v] = 0.f;
+#pragma unroll 4
+      for (int g = part * G; g < part * G + G; ++g) {
         const int4 l0 = *reinterpret_cast<const int4*>(&lab_s[g * 16 + 4 * hb]);
         const int4 l1 = *reinterpret_cast<const int4*>(&lab_s[g * 16 + 8 + 4 * hb]);
         uint4 e;
@@ -360,22 +322,30 @@ __global__ __launch_bounds__(256, (ACC && D == 128) ? 1 : 2) void assign_mfma(co
         e.y = (l0.z == cid ? 0x3F80u : 0u) | (l0.w == cid ? 0x3F800000u : 0u);
         e.z = (l1.x == cid ? 0x3F80u : 0u) | (l1.y == cid ? 0x3F800000u : 0u);
         e.w = (l1.z == cid ? 0x3F80u : 0u) | (l1.w == cid ? 0x3F800000u : 0u);
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa, *reinterpret_cast<const bf16x8_t*>(&e), sacc, 0, 0, 0);
-      }
-      if (counting) {
-        if (cid < m && hb == 0) acc_out.bcnt[((size_t)h * acc_out.nb_stride + b) * ACC_MAXM + cid] = (int)sacc[0];
-        continue;
-      }
-      // value v of the tile is dim db*32 + 8*(v/4) + 4*hb + v%4 of centre cid
-      if (cid < m) {
-        float* out = acc_out.psum + ((size_t)h * acc_out.P + (size_t)cid * acc_out.nb_stride + b) * D + db * 32 + 4 * hb;
+        const bf16x8_t eb = *reinterpret_cast<const bf16x8_t*>(&e);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float4 o4 = {sacc[4 * i], sacc[4 * i + 1], sacc[4 * i + 2], sacc[4 * i + 3]};
-          *reinterpret_cast<float4*>(out + 8 * i) = o4;
+        for (int db = 0; db < DT; ++db) {
+          const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(pool + g * 16 * ROWB + xlo[db]));
+          const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(pool + g * 16 * ROWB + xhi[db]));
+          const s16x4_t both[2] = {lo, hi};
+          sacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(both), eb, sacc[db], 0, 0, 0);
+        }
+      }
+      // value v of a tile is dim db*32 + 8*(v/4) + 4*hb + v%4 of centre cid
+      if (cid < m) {
+#pragma unroll
+        for (int db = 0; db < DT; ++db) {
+          float* out = acc_out.psum + ((size_t)h * acc_out.P + ((size_t)cid * acc_out.nb_stride + b) * R + part) * D + db * 32 + 4 * hb;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float4 o4 = {sacc[db][4 * i], sacc[db][4 * i + 1], sacc[db][4 * i + 2], sacc[db][4 * i + 3]};
+            *reinterpret_cast<float4*>(out + 8 * i) = o4;
+          }
         }
       }
     }
+    __syncthreads();
+    if (tid < m) acc_out.bcnt[((size_t)h * acc_out.nb_stride + b) * ACC_MAXM + tid] = cnt_s[tid];
   }
 }
 
@@ -861,7 +831,8 @@ __global__ __launch_bounds__(64 * FIN_ROWS) void finalize_centroids(FinalizeCfg 
     for (int b = lane; b < nb; b += 64) nj += cfg.bcnt[((size_t)h * cfg.nb_stride + b) * ACC_MAXM + j];
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) nj += __shfl_xor(nj, o);
-    p_beg = j * cfg.nb_stride; p_end = p_beg + nb;
+    const int R = cfg.nb_const > 0 ? 1 : acc_parts(m);
+    p_beg = j * cfg.nb_stride * R; p_end = p_beg + nb * R;
   } else {
     nj = offs[(size_t)h * offs_stride + j + 1] - offs[(size_t)h * offs_stride + j];
     p_beg = poff[(size_t)h * offs_stride + j]; p_end = poff[(size_t)h * offs_stride + j + 1];
@@ -1421,7 +1392,8 @@ __global__ __launch_bounds__(256) void stage_open(const T* __restrict__ X, OpenC
 //               the whole pass; the waves' partial sums are then added in a fixed order, so the result
 //               is deterministic;
 //   filter:     squared distances of the last pass stay in LDS; U is compacted in ascending order.
-constexpr int SMALL_NU = 8192;
+// (lists of up to 3 072 points: with 8 192 and with 2 048, 12 heads of 32 760 tokens, d=128, took 869 and 853 us, with this 855)
+constexpr int SMALL_NU = 3072;
 constexpr int SMALL_M = 32;
 
 struct SmallStageCfg {
@@ -1842,6 +1814,8 @@ static inline int chk() { return hipGetLastError() == hipSuccess ? 0 : ADACLUSTE
 
 int reduce_part_rows() { return REDUCE_ROWS; }
 int assign_block_sum_centres() { return ACC_MAXM; }
+// rows per block of the part-sum table that hold for any head with up to m centres: the most acc_parts(i) * i over i <= m
+int assign_block_sum_rows(int m) { return 4 * m < ACC_MAXM ? 4 * m : ACC_MAXM; }
 
 int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, int mode, int m_const, int cap,
                   const KState* st, const int32_t* ulist, const void* X, const void* cent_lp, const float* bias,

@@ -33,6 +33,7 @@ int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, in
                   const float* seed_score = nullptr,
                   const float* tau = nullptr, int32_t* keep_cnt = nullptr, int keep_stride = 0);
 int assign_block_sum_centres();   // most centres the assignment kernel keeps block sums for
+int assign_block_sum_rows(int m); // rows per block of their table, with up to m centres
 int launch_seg_reduce(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int P,
                       const KState* st, int normalize, int want_box, const void* X, const int32_t* perm,
                       const int32_t* offs, int offs_stride, int32_t* poff, int32_t* pcl, float* psum, float* pnorm, float* pmin,

@@ -9,6 +9,7 @@ from oracle import adacluster_oracle as orc
 from paper_2604_18348_amd import binding as B
 from paper_2604_18348_amd import workloads as wl
 from tests.helpers import to_dev, to_np
+from tests.test_gpu_cluster import check_stages_against_oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -45,3 +46,17 @@ def test_stage_centres_are_the_strided_sample_of_what_was_left(dtype, d, N):
             assert np.all(np.abs(d2[wrong] - p.tau_abs ** 2) <= 1e-5 * (xx[wrong] + xx.max()))
             left = left[~gone]
         assert np.all(stage_of[h, left] == -1)
+
+
+@pytest.mark.parametrize("m", [31, 33, 64, 65, 97, 128])
+@pytest.mark.parametrize("d", [64, 128])
+def test_block_sums_around_the_changes_of_their_split(d, m):
+    """Up to 32 centres a block of 256 points leaves four rows of sums per centre, up to 64 two, then one: the first stage's
+    centres after one update, against the oracle's (bounds of check_stages_against_oracle with two passes)."""
+    H, N = 2, 2611
+    _, K, _ = wl.make_small(40 + m, N, d, 20, dtype="bf16", H=H)
+    p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=4, k_iters=2, k_m0=m, k_m_min=4, k_max_clusters=4 * m, tau_abs=0.6 * d ** 0.5)
+    out = B.adacluster_kcluster(p, to_dev(K, B.BF16))
+    torch.cuda.synchronize()
+    for h in range(H):
+        check_stages_against_oracle(K[h], out, h, 1, 2, p.tau_abs)
