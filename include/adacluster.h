@@ -23,8 +23,8 @@
  *     result, so work queued on `stream` after the call still waits for all of it.
  *     Calls are asynchronous
  *     except adacluster_kcluster and adacluster_attn with k_init_mode 0, which block
- *     the calling thread once per clustering stage on an event, to read a few
- *     integers back through pinned host memory the library keeps per thread (the
+ *     the calling thread once per clustering stage, polling a few integers that the
+ *     device writes to pinned host memory the library keeps per thread (the
  *     stage loop of Algorithm 1 has a data-dependent trip count; the host runs one
  *     stage behind the device, so the stream is not drained, except once, before the
  *     second stage, when the first stage's sizes would be a poor bound for it).
