@@ -698,9 +698,9 @@ int adacluster_sparse_attn(const adacluster_params* p, const void* Q, const void
   hipStream_t st = (hipStream_t)stream;
   prof_begin(st);
   RET_IF(launch_sort(st, D.H, D.N, D.N, D.Cq, q_labels, nullptr, nullptr, 0, nullptr, 0, nullptr, 0, w.perm_q, w.offs_q,
-                     D.Cq + 1, w.sort));
+                     D.Cq + 1, w.sort, nullptr, 0, nullptr, 0, nullptr, 1));
   RET_IF(launch_sort(st, D.H, D.N, D.N, D.cap, k_labels, nullptr, nullptr, 0, k_count, 1, nullptr, 0, w.perm_k, w.offs_k,
-                     D.cap + 1, w.sort));
+                     D.cap + 1, w.sort, nullptr, 0, nullptr, 0, nullptr, 1));
   prof_mark(EV_SELECT, st);   // (time of the two label sorts when called stand-alone)
   return run_plan_attention(p, w, st, Q, O, k_count, sel_idx, sel_cnt, -1, K, V);
 }

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, in
     const int32_t* sel = sel_idx + ((size_t)h * Cq + i) * cap;
     const int cnt = sel_cnt[(size_t)h * Cq + i];
     const int32_t* ko = k_offs + (size_t)h * k_offs_stride;
-    const int kc = k_count[h];
+    const int kc = min(k_count[h], cap);                      // (a caller's count: the offsets end at the capacity)
     const int lane = tid & 63, wave = tid >> 6;
     int carry_e = -1, carry_total = 0, carry_nr = 0;          // identical in every thread
     for (int base = 0; base < cnt; base += 256) {

@@ -19,12 +19,13 @@ size_t sort_table_ints(int N, int m);    // for heads of up to N items and up to
 // Outputs: perm [H][N] token ids ordered by (label, position); offs [H][offs_stride] with
 // offs[j] = first sorted position of label j for j = 0..m_h.  With poff, the clusters are also cut into parts of part_rows
 // rows for the centroid reduction: poff [H][offs_stride], and pcl [H][P], the cluster of every part, of heads with more
-// than 128 labels.  *poff_done says what was left: 1 poff, 2 pcl as well.
+// than 128 labels.  *poff_done says what was left: 1 poff, 2 pcl as well.  A label count above m_bound is taken as m_bound;
+// `foreign`: labels outside [0, m) may occur, and their items go to the end of the order, where no offset points.
 int launch_sort(hipStream_t st, int H, int N, int n_bound, int m_bound, const int32_t* labels,
                 const int32_t* ulist, const int32_t* n_dev, int n_stride, const int32_t* m_dev, int m_stride,
                 const int32_t* active_dev, int active_stride, int32_t* perm, int32_t* offs, int offs_stride,
                 const SortScratch& sc, int32_t* poff = nullptr, int part_rows = 0, int32_t* pcl = nullptr, int P = 0,
-                int* poff_done = nullptr);
+                int* poff_done = nullptr, int foreign = 0);
 
 int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, int mode, int m_const, int cap,
                   const KState* st, const int32_t* ulist, const void* X, const void* cent_lp, const float* bias,

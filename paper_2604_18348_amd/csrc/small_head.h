@@ -10,6 +10,9 @@ static constexpr int RBITS = 7;
 static constexpr int RBINS = 1 << RBITS;
 static constexpr int SMALL_SEGS = 32;   // the one-workgroup sort holds at most this many segments
 
+// Label -> bin: the labels 0..m-1, and m for every label outside of that range.
+__device__ __forceinline__ int label_bin(int l, int m) { return (int)min((uint32_t)l, (uint32_t)m); }
+
 // The whole sort of one head's n <= SMALL_SEGS * SEG labels in one workgroup (all 1024 threads must
 // call it): every radix pass, the label offsets offs[0..m] and, if poff is given, the part offsets
 // of the centroid reduction, which otherwise take five launches per pass of a few microseconds
@@ -47,7 +50,7 @@ __device__ __forceinline__ void sort_one_head(const int32_t* __restrict__ labels
 #pragma unroll
       for (int k = 0; k < SEG / 64; ++k) {
         const int p = (wave + 16 * i) * SEG + 64 * k + lane;
-        lab[i][k] = p < n ? lin[p] : 0;
+        lab[i][k] = p < n ? label_bin(lin[p], m) : 0;      // (a later pass reads bins: unchanged)
         val[i][k] = p < n ? (vin ? vin[p] : p) : 0;
       }
     __syncthreads();

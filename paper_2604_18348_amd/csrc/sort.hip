@@ -35,15 +35,13 @@ __device__ __forceinline__ int head_items(const SortArgs& a, int h) {
 // eight launches that moved every item and its label twice.  Final key sort of 30 x 75 600 tokens, about 580 labels:
 // 69 -> 34 us; 24 x 180 000, about 1 270: 130 -> 53; 12 x 32 760, about 365: 43 -> 20.)
 // Bins are the labels 0..m-1 and one last bin m for labels outside of that range (a caller's labels of clusters past
-// its own count): they stay at the end of the order, where no offset points.
+// its own count): they stay at the end of the order, where no offset points.  The one-workgroup sort has the same bins.
 // ------------------------------------------------------------------------------------------
 constexpr int CS_ITEMS = 2048, CS_WAVES = 4, CS_NT = CS_WAVES * 64, CS_STEPS = CS_ITEMS / CS_NT;
 
 __device__ __forceinline__ int label_limit(const int32_t* m_dev, int m_stride, int m_const, int h) {
   return m_dev ? max(0, min(m_dev[(size_t)h * m_stride], m_const)) : m_const;       // (the tables are sized for m_const)
 }
-__device__ __forceinline__ int label_bin(int l, int m) { return (int)min((uint32_t)l, (uint32_t)m); }
-
 __global__ __launch_bounds__(CS_NT) void label_count(const int32_t* __restrict__ labels, int N, SortArgs a,
                                                      const int32_t* __restrict__ m_dev, int m_stride, int m_const,
                                                      int nseg, int stride, int32_t* __restrict__ hist) {
@@ -230,7 +228,7 @@ __global__ __launch_bounds__(1024) void sort_small(const int32_t* __restrict__ l
   const int h = blockIdx.x;
   if (a.active_dev && !a.active_dev[(size_t)h * a.active_stride]) return;
   const int n = head_items(a, h);
-  const int m = m_dev ? m_dev[(size_t)h * m_stride] : m_const;
+  const int m = label_limit(m_dev, m_stride, m_const, h);
   const size_t o = (size_t)h * N;
   sort_one_head(labels + o, vals_in ? vals_in + o : nullptr, n, passes, m, lab_a + o, val_a + o, lab_b + o, perm + o,
                 offs + (size_t)h * offs_stride, poff ? poff + (size_t)h * offs_stride : nullptr, part_rows);
@@ -244,7 +242,7 @@ int launch_sort(hipStream_t st, int H, int N, int n_bound, int m_bound,
                 const int32_t* n_dev, int n_stride, const int32_t* m_dev, int m_stride,
                 const int32_t* active_dev, int active_stride,
                 int32_t* perm, int32_t* offs, int offs_stride, const SortScratch& sc, int32_t* poff,
-                int part_rows, int32_t* pcl, int P, int* poff_done) {
+                int part_rows, int32_t* pcl, int P, int* poff_done, int foreign) {
   SortArgs a{n_dev, n_stride, n_bound, active_dev, active_stride};
   if (poff_done) *poff_done = 0;
 #ifndef SORT_SMALL_LIMIT
@@ -253,7 +251,7 @@ int launch_sort(hipStream_t st, int H, int N, int n_bound, int m_bound,
   static_assert(SORT_SMALL_LIMIT <= SMALL_SEGS, "the one-workgroup sort holds SMALL_SEGS segments");
   if (n_bound <= SORT_SMALL_LIMIT * SEG) {
     int bits = 1;
-    while ((1 << bits) < m_bound) ++bits;
+    while ((1 << bits) < m_bound + (foreign ? 1 : 0)) ++bits;       // (the digits of the last bin too)
     const int passes = (bits + RBITS - 1) / RBITS;
     sort_small<<<H, 1024, 0, st>>>(labels, ulist, N, passes, a, m_dev, m_stride, m_bound, sc.lab_a, sc.val_a, sc.lab_b,
                                    perm, offs, offs_stride, poff, part_rows);

@@ -44,3 +44,51 @@ def test_rows_follow_their_labels(N, kc, cap, past):
         ref = torch.softmax(S, 1) @ V[h].float()
         rel = float((O[h] - ref).norm() / ref.norm())
         assert rel < 1e-2, rel
+
+
+@pytest.mark.parametrize("kc_extra", [0, 5])
+@pytest.mark.parametrize("N,kc,cap", [(700, 40, 64), (1500, 127, 128), (1500, 128, 128), (4096, 300, 384), (4097, 128, 128),
+                                      (4097, 300, 384)])
+def test_labels_and_counts_outside_their_range(N, kc, cap, kc_extra):
+    """Either form of the sort: labels below zero, at the count, at and past the capacity, and with the low digits of a valid
+    label belong to no cluster and leave the others in place; a count above the capacity (kc_extra) is taken as the capacity,
+    and a selected cluster past it is left out.  Query labels outside [0, Cq): those rows are not written."""
+    H, d, Cq = 2, 64, 5
+    rng = np.random.default_rng(N + kc)
+    m0 = min(cap // 2, 16)
+    p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=Cq, k_m0=m0, k_m_min=1, k_max_clusters=cap - m0)
+    Q, K, V = (torch.from_numpy(rng.standard_normal((H, N, d)).astype(np.float32)).cuda().to(torch.bfloat16) for _ in range(3))
+    good = rng.integers(0, kc, (H, N)).astype(np.int64)
+    kl, ql = good.copy(), rng.integers(0, Cq, (H, N)).astype(np.int64)
+    strange = [-1, -127, -2 ** 31, cap, cap + 3, 2 ** 31 - 1, 128 * 7 + 1, 16384 * 3 + 2, 2 ** 24]
+    for h in range(H):
+        at = rng.permutation(N)[:N // 8]
+        kl[h, at] = rng.choice([s for s in strange if not 0 <= s < cap], at.size)
+        at = rng.permutation(N)[:N // 16]
+        ql[h, at] = rng.choice([-1, -128, Cq, 128 + 1, 2 ** 31 - 1], at.size)
+    sel = np.zeros((H, Cq, cap), dtype=np.int32)
+    cnt = np.zeros((H, Cq), dtype=np.int32)
+    pick = rng.random((H, Cq, kc)) < 0.3
+    pick[:, :, 0] = True
+    for h in range(H):
+        for i in range(Cq):
+            j = np.append(np.nonzero(pick[h, i])[0], cap + 2)[:cap]
+            sel[h, i, :len(j)], cnt[h, i] = j, len(j)
+    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    count = cap + kc_extra if kc_extra else kc
+    O = torch.full((H, N, d), -7.0, dtype=torch.bfloat16, device="cuda")
+    B.adacluster_sparse_attn(p, Q, K, V, dev(ql.astype(np.int32)), dev(kl.astype(np.int32)),
+                             torch.full((H,), count, dtype=torch.int32, device="cuda"), dev(sel), dev(cnt), out=O)
+    for h in range(H):
+        rows = (ql[h] >= 0) & (ql[h] < Cq)
+        keys = (kl[h] >= 0) & (kl[h] < kc)
+        S = (Q[h].float() @ K[h].float().T) / d ** 0.5
+        allowed = np.zeros((N, N), dtype=bool)
+        allowed[np.ix_(rows, keys)] = pick[h][ql[h][rows]][:, kl[h][keys]]
+        S.masked_fill_(~dev(allowed), float("-inf"))
+        r = dev(np.flatnonzero(rows))
+        ref = torch.softmax(S[r], 1) @ V[h].float()
+        got = O[h].float()
+        rel = float((got[r] - ref).norm() / ref.norm())
+        assert rel < 1e-2, rel
+        assert bool((got[dev(np.flatnonzero(~rows))] == -7.0).all())
