@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, in
     // keeps the right operand when it is non-empty, then run starts and lengths by prefix sums; the state
     // after a round (last end, keys so far, ranges so far) is carried into the next.
     const int32_t* sel = sel_idx + ((size_t)h * Cq + i) * cap;
-    const int cnt = sel_cnt[(size_t)h * Cq + i];
+    const int cnt = min(sel_cnt[(size_t)h * Cq + i], cap);
     const int32_t* ko = k_offs + (size_t)h * k_offs_stride;
     const int kc = min(k_count[h], cap);                      // (a caller's count: the offsets end at the capacity)
     const int lane = tid & 63, wave = tid >> 6;
@@ -91,6 +91,7 @@ __global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, in
       for (int w = 0; w < 4; ++w) { if (s_wh[w]) carry_e = s_we[w]; carry_total += s_wlen[w]; carry_nr += s_wst[w]; }
       __syncthreads();                         // the wave totals are free again
     }
+    carry_total = min(carry_total, N);      // (a list that names clusters twice ends here: its row of krow holds N keys)
     if (tid == 0) {
       rp[carry_nr] = carry_total;
       rng_cnt[(size_t)h * Cq + i] = carry_nr;

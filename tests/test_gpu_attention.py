@@ -199,3 +199,20 @@ def test_fp32_key_lists_split_over_the_waves(d, N):
     O = to_np(B.adacluster_dense_attn(p, to_dev(Q, B.F32), to_dev(K, B.F32), to_dev(V, B.F32)))
     for h in range(2):
         check(O[h], orc.dense_attention(Q[h], K[h], V[h]), B.F32)
+
+
+@pytest.mark.parametrize("dtype", [B.BF16, B.F32])
+def test_a_list_that_names_clusters_twice_stays_inside_its_row(dtype):
+    """A selection whose clusters hold more than N keys in all (the interface asks for distinct ones) is cut at N keys: the
+    lists of the other query clusters, whose rows of the key-row table lie before and behind it, are not touched."""
+    Cq, Ck, N = 5, 23, 900
+    Q, K, V, ql, kl, sel = make_case(21, N, 64, dtype)
+    for h in range(Q.shape[0]):
+        sel[h][2] = np.tile(np.arange(Ck // 2, dtype=np.int64), 2)       # fits the capacity, nearly all keys of it twice
+    kl[kl >= Ck // 2] = 4
+    got = run_sparse(Q, K, V, ql, kl, sel, dtype, Cq, Ck)
+    for h in range(Q.shape[0]):
+        rows = ql[h] != 2
+        ref = orc.sparse_attention_gather(Q[h], K[h], V[h], ql[h], kl[h], [np.unique(s) for s in sel[h]])
+        check(got[h][rows], ref[rows], dtype)
+        assert np.all(np.isfinite(got[h]))
