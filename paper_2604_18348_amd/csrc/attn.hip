@@ -907,8 +907,9 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
     tmax = fmaxf(tmax, s[15]);
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
     if (__any(tmax > m)) {
-      const float mnew = fmaxf(m, tmax);                   // finite: the tile holds at least one key
-      const float alpha = __builtin_amdgcn_exp2f((m - mnew) * a.scale_log2e);
+      const float mnew = fmaxf(m, tmax);
+      // (both -inf: no score of this query above -inf so far, and nothing to rescale)
+      const float alpha = mnew > m ? __builtin_amdgcn_exp2f((m - mnew) * a.scale_log2e) : 1.f;
       m = mnew;
       l *= alpha;
 #pragma unroll
@@ -916,7 +917,7 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
     }
-    const float moff = m * a.scale_log2e;
+    const float moff = m > -INFINITY ? m * a.scale_log2e : 0.f;
     float lsum[2] = {0.f, 0.f};
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -949,8 +950,8 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
   l += __shfl_xor(l, 32);
   if (hb == 0) { sm[wave][c] = m * a.scale_log2e; sl[wave][c] = l; }
   __syncthreads();
-  // O = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w, 2 NW threads a query; a wave without a tile has m = -inf and
-  // l = 0, and if none had one (empty list) the output is zero
+  // O = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w, 2 NW threads a query; a wave without a tile, or all of whose
+  // scores are -inf, has m = -inf and l = 0.  An empty list gives zero, one whose every score is -inf NaN (as 0 / 0).
   constexpr int TPQ = 2 * NW;
   const int r = tid / TPQ, col = (tid % TPQ) * 4;
   if (r >= nrows) return;
@@ -963,7 +964,8 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
     wt[w] = M > -INFINITY ? exp2f(sm[w][r] - M) : 0.f;
     L = fmaf(wt[w], sl[w][r], L);
   }
-  float inv = L > 0.f ? 1.0f / L : 0.f;
+  if (!(M > -INFINITY) && total > 0) L = NAN;
+  float inv = L > 0.f ? 1.0f / L : L;
   float* out = (float*)a.O + ((size_t)h * a.N + (pq ? pq[row0 + r] : row0 + r)) * D;
   if (gridDim.z > 1) {                                     // a partial result: as it is, with its reference and sum
     const size_t pr = ((size_t)h * gridDim.z + blockIdx.z) * a.N + row0 + r;
@@ -1003,10 +1005,11 @@ __global__ __launch_bounds__(256) void attn_merge_f32(AttnArgs a, int splits) {
 #pragma unroll
   for (int z = 0; z < F32_MAX_SPLITS; ++z) {
     const float w = ms[z] > -INFINITY ? exp2f(ms[z] - M) : 0.f;
-    L = fmaf(w, ls[z], L);
+    if (ms[z] > -INFINITY) L = fmaf(w, ls[z], L);
     x.x = fmaf(w, os[z].x, x.x); x.y = fmaf(w, os[z].y, x.y); x.z = fmaf(w, os[z].z, x.z); x.w = fmaf(w, os[z].w, x.w);
   }
-  const float inv = L > 0.f ? 1.0f / L : 0.f;
+  if (!(M > -INFINITY)) L = ls[0];                         // 0 (empty list) or NaN, the same in every split
+  const float inv = L > 0.f ? 1.0f / L : L;
   const int tok = a.perm_q ? a.perm_q[(size_t)h * a.N + pos] : pos;
   *reinterpret_cast<float4*>((float*)a.O + ((size_t)h * a.N + tok) * D + col) = float4{x.x * inv, x.y * inv, x.z * inv, x.w * inv};
 }

@@ -216,3 +216,26 @@ def test_a_list_that_names_clusters_twice_stays_inside_its_row(dtype):
         ref = orc.sparse_attention_gather(Q[h], K[h], V[h], ql[h], kl[h], [np.unique(s) for s in sel[h]])
         check(got[h][rows], ref[rows], dtype)
         assert np.all(np.isfinite(got[h]))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N,H", [(33, 1), (600, 2), (545, 70)])
+def test_fp32_scores_of_minus_infinity_weigh_nothing(d, N, H):
+    """Whole key tiles whose every score is -inf (queries are positive, those keys -inf): the waves and workgroups that see
+    nothing else add nothing, and a query all of whose scores are -inf gets NaN, as exp(-inf) / sum exp(-inf) is.  With 70
+    heads the lists are not split over workgroups (and the heads are dealt in two rounds of 64)."""
+    rng = np.random.default_rng(31)
+    Q = rng.random((H, N, d)).astype(np.float32) + 0.1
+    K, V = (rng.standard_normal((H, N, d)).astype(np.float32) for _ in range(2))
+    for dead in (np.arange(32), np.arange(32, min(N, 161)), np.arange(N - 1), np.arange(0, N, 3)):
+        K2 = K.copy()
+        K2[:, dead] = -np.inf
+        p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=1, k_m0=1, k_m_min=1, k_max_clusters=1)
+        O = to_np(B.adacluster_dense_attn(p, to_dev(Q, B.F32), to_dev(K2, B.F32), to_dev(V, B.F32)))
+        live = np.setdiff1d(np.arange(N), dead)
+        for h in (0, H - 1):
+            S = Q[h].astype(np.float64) @ K[h][live].astype(np.float64).T / d ** 0.5
+            P = np.exp(S - S.max(1, keepdims=True))
+            check(O[h], (P / P.sum(1, keepdims=True)) @ V[h][live].astype(np.float64), B.F32)
+    K2[:] = -np.inf
+    assert np.all(np.isnan(to_np(B.adacluster_dense_attn(p, to_dev(Q, B.F32), to_dev(K2, B.F32), to_dev(V, B.F32)))))
