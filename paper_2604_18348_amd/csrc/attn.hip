@@ -324,34 +324,37 @@ struct AttnArgs {
   const int32_t* krow; size_t kstride;   // every key row of a query cluster's list (byte offset, fp32: row number): [H][Cq][kstride]
 };
 
-// Workgroup -> (head, query tile).  Workgroups go to the 8 XCDs round-robin in launch order, each with its own L2, so
-// XCD = blockIdx.x % 8 and blockIdx.x / 8 is a slot in that XCD's own list of tiles: of every head, in head order, the
-// XCD takes a contiguous eighth (the tiles of one query cluster stream the same K/V rows, and so do it behind the
-// same L2).  Only the device knows how many tiles a head has; the list is cut from those counts here, so that the
-// workgroups without work are the last of the grid.  (With a grid row per head, sized for the most tiles a head
-// could have, more than half of the workgroups were empty ones between the heads, and each takes its turn on a
-// CU.)
+// Workgroup -> (head, query tile) of a launch of pick_tile_grid.  Workgroups go to the 8 XCDs round-robin in launch order,
+// each with its own L2, so XCD = blockIdx.x % 8 and blockIdx.x / 8 is a slot in that XCD's own list of tiles: of every
+// head, in head order, the XCD takes a contiguous eighth (the tiles of one query cluster stream the same K/V rows, and so
+// do it behind the same L2).
+// Only the device knows how many tiles a head has.  Up to PICK_HEADS heads the list is cut from those counts here, a lane
+// per head, so that the workgroups without work are the last of the grid.  (With a grid row per head, sized for the most
+// tiles a head could have, more than half of the workgroups were empty ones between the heads, and each takes its turn on
+// a CU.)  More heads fill the chip anyway and have a grid row each: searched 64 at a time, a workgroup's head costs a trip
+// to memory per 64 heads (fp32 calls of 256 x 512 rows 203 us by rows, 260 by search, 1 024 x 128 825 and 1 625 us,
+// 4 096 x 256, d=128, 4.41 and 6.87 ms; 70 and 128 x 1 024 within 2 %), and past 2^32 threads the grid dimension ends.
 // `parts`: workgroups per tile.  Returns false where the list has ended.
+constexpr int PICK_HEADS = 64;
 __device__ __forceinline__ bool pick_tile(const int32_t* __restrict__ ntiles, int H, int parts, int& h, int& tile) {
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, lane = threadIdx.x & 63;
-  int base = 0;
-  for (int h0 = 0; h0 < H; h0 += 64) {                     // 64 heads at a time, one per lane
-    const int nt = h0 + lane < H ? parts * ntiles[h0 + lane] : 0;
-    const int w = (nt + 7) >> 3;                           // this XCD's share of the head (the last XCD's may be short)
-    int incl = w;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
-    const uint64_t past = __ballot(base + incl > slot);
-    if (past) {
-      const int l = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)past) - 1);
-      const int wl = __builtin_amdgcn_readlane(w, l);
-      h = h0 + l;
-      tile = xcd * wl + slot - base - __builtin_amdgcn_readlane(incl, l) + wl;
-      return tile < __builtin_amdgcn_readlane(nt, l);
-    }
-    base += __builtin_amdgcn_readlane(incl, 63);
+  if (H > PICK_HEADS) {
+    h = blockIdx.y;
+    const int nt = parts * ntiles[h], w = (nt + 7) >> 3;
+    tile = xcd * w + slot;
+    return slot < w && tile < nt;
   }
-  return false;
+  const int nt = lane < H ? parts * ntiles[lane] : 0;
+  const int w = (nt + 7) >> 3;                             // this XCD's share of the head (the last XCD's may be short)
+  int incl = w;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
+  const uint64_t past = __ballot(incl > slot);
+  if (!past) return false;
+  h = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)past) - 1);
+  const int wl = __builtin_amdgcn_readlane(w, h);
+  tile = xcd * wl + slot - __builtin_amdgcn_readlane(incl, h) + wl;
+  return tile < __builtin_amdgcn_readlane(nt, h);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1107,6 +1110,12 @@ int attn_block_rows(int dtype, int d, int N, int Cq) {
 int attn_block_rows_min(int dtype) { return dtype == ADACLUSTER_BF16 ? 128 : 64; }
 int attn_block_rows_max(int dtype) { return dtype == ADACLUSTER_BF16 ? 256 : 64; }
 
+// The launch of a kernel that takes its tiles by pick_tile: `most` bounds parts x tiles of a head.
+static dim3 pick_tile_grid(int H, int most, int z) {
+  const unsigned x = (most + 7) / 8 * 8;
+  return H > PICK_HEADS ? dim3(x, H, z) : dim3(H * x, 1, z);
+}
+
 size_t attn_krow_stride(int N) { return (size_t)(N + 63) / 64 * 64 + KROW_PAD; }
 
 int attn_tile_record() { return TILE_REC; }
@@ -1164,7 +1173,7 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
   } else {
     const int splits = attn_f32_splits(H, N, Cq);
     const bool wide = (size_t)N * d * 4 >= ((size_t)1 << 32);
-    const dim3 g2(8 * H * ((2 * (N / 64 + Cq + 1) + 7) / 8), 1, splits), gm((N + 1024 / d - 1) / (1024 / d), H);
+    const dim3 g2 = pick_tile_grid(H, 2 * (N / 64 + Cq + 1), splits), gm((N + 1024 / d - 1) / (1024 / d), H);
     if (d == 64) { if (wide) attn_f32<64, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<64, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
     else { if (wide) attn_f32<128, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<128, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
     if (splits > 1) {

@@ -223,7 +223,7 @@ def test_a_list_that_names_clusters_twice_stays_inside_its_row(dtype):
 def test_fp32_scores_of_minus_infinity_weigh_nothing(d, N, H):
     """Whole key tiles whose every score is -inf (queries are positive, those keys -inf): the waves and workgroups that see
     nothing else add nothing, and a query all of whose scores are -inf gets NaN, as exp(-inf) / sum exp(-inf) is.  With 70
-    heads the lists are not split over workgroups (and the heads are dealt in two rounds of 64)."""
+    heads the lists are not split over workgroups."""
     rng = np.random.default_rng(31)
     Q = rng.random((H, N, d)).astype(np.float32) + 0.1
     K, V = (rng.standard_normal((H, N, d)).astype(np.float32) for _ in range(2))
@@ -239,3 +239,46 @@ def test_fp32_scores_of_minus_infinity_weigh_nothing(d, N, H):
             check(O[h], (P / P.sum(1, keepdims=True)) @ V[h][live].astype(np.float64), B.F32)
     K2[:] = -np.inf
     assert np.all(np.isnan(to_np(B.adacluster_dense_attn(p, to_dev(Q, B.F32), to_dev(K2, B.F32), to_dev(V, B.F32)))))
+
+
+def test_fp32_more_workgroups_than_one_grid_dimension_takes():
+    """65 535 heads of 130 one-query clusters: 17.8 million workgroups of 256 threads, more than 2^32 threads.  (Past 64 heads
+    each has a grid row of its own.)"""
+    H, N, d = 65535, 130, 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    Q, K, V = (torch.randn((H, N, d), generator=gen, device="cuda") for _ in range(3))
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=N, k_m0=1, k_m_min=1, k_max_clusters=1)
+    labels = torch.arange(N, dtype=torch.int32, device="cuda").repeat(H, 1)
+    sel = torch.zeros((H, N, p.cap), dtype=torch.int32, device="cuda")
+    one = torch.ones((H, N), dtype=torch.int32, device="cuda")
+    O = B.adacluster_sparse_attn(p, Q, K, V, labels, (labels > 99).int(), 2 * one[:, 0].contiguous(), sel, one)
+    for h in range(0, H, 8192):                    # every query takes the keys of cluster 0, the first 100
+        S = torch.bmm(Q[h:h + 8192], K[h:h + 8192, :100].transpose(1, 2).contiguous()) / d ** 0.5
+        ref = torch.bmm(torch.softmax(S, 2), V[h:h + 8192, :100].contiguous())
+        assert float((O[h:h + 8192] - ref).abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("H,N,d,splits", [(64, 545, 64, 1), (65, 545, 128, 1), (45, 545, 64, 2), (21, 545, 128, 3), (5, 545, 64, 4)])
+def test_fp32_lists_whole_and_split_over_up_to_four_workgroups(H, N, d, splits):
+    """A launch that fills the chip leaves key lists whole (the kernel writes the output itself), smaller ones split them over
+    two, three and four workgroups; 64 heads are dealt from the tile counts, 65 have a grid row each.  Sparse, with an empty
+    list and an empty cluster, and dense; every output element is written."""
+    Cq = 5
+    for clusters in (Cq, 1):                       # (the dense call counts as one)
+        assert min(4, -(-1024 // (H * (N // 32 + clusters // 2 + 1)))) == splits
+    Q, K, V, ql, kl, sel = make_case(41, N, d, B.F32, H=H)
+    for h in range(0, H, 3):
+        sel[h][2] = np.zeros(0, dtype=np.int64)
+    ql[1][ql[1] == 4] = 0
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=Cq, k_m0=4, k_m_min=1, k_max_clusters=23)
+    si, sc = sel_to_dev(sel, Cq, p.cap)
+    Qd, Kd, Vd = to_dev(Q, B.F32), to_dev(K, B.F32), to_dev(V, B.F32)
+    O = torch.full_like(Qd, float("nan"))
+    B.adacluster_sparse_attn(p, Qd, Kd, Vd, torch.from_numpy(ql).cuda(), torch.from_numpy(kl).cuda(),
+                             torch.full((H,), 23, dtype=torch.int32, device="cuda"), si, sc, out=O)
+    D = B.adacluster_dense_attn(p, Qd, Kd, Vd, out=torch.full_like(Qd, float("nan")))
+    for h in sorted({0, 1, H // 2, H - 2, H - 1}):
+        check(to_np(O[h]), orc.sparse_attention_gather(Q[h], K[h], V[h], ql[h], kl[h], sel[h]), B.F32)
+        check(to_np(D[h]), orc.dense_attention(Q[h], K[h], V[h]), B.F32)
+    assert bool(torch.isfinite(O).all()) and bool(torch.isfinite(D).all())
