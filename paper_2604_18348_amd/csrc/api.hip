@@ -294,12 +294,15 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(nmerge, int32_t*, H * 4);
   {  // partial results of split key lists: slots of cut lists (bf16), or a row per query and split (fp32; the dense call
      // counts as one cluster, which never makes fewer splits)
-    const size_t rows = p->dtype == ADACLUSTER_BF16 ? H * (size_t)attn_split_slots() * D.BMmax : H * N * attn_f32_splits(D.H, D.N, 1);
+    const size_t splits = attn_f32_splits(D.H, D.N, 1);     // (1: the kernel writes the output itself)
+    const size_t rows = p->dtype == ADACLUSTER_BF16 ? H * (size_t)attn_split_slots() * D.BMmax : splits > 1 ? H * N * splits : 0;
     TAKE(part_o, float*, rows * d * 4);
     TAKE(part_ml, float*, rows * 2 * 4);
   }
   TAKE(ntiles, int32_t*, H * 4);
-  TAKE(krow, int32_t*, H * (size_t)D.Cq * attn_krow_stride(D.N) * 4);
+  const bool listed = attn_rows_listed(p->dtype, D.d, D.H, D.N, D.Cq);
+  TAKE(krow, int32_t*, listed ? H * (size_t)D.Cq * attn_krow_stride(D.N) * 4 : 0);
+  if (w && !listed) w->krow = nullptr;
   TAKE(q_labels, int32_t*, H * N * 4);
   TAKE(q_centroids, float*, H * (size_t)D.Cq * d * 4);
   TAKE(q_assign, float*, H * (size_t)D.Cq * d * 4);
@@ -555,7 +558,7 @@ int run_plan_attention(const adacluster_params* p, const WS& w, hipStream_t st, 
   prof_mark(EV_PLAN, st, prof_from);
   RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, D.Cq, D.maxtiles, scale, Q, K, V, O, w.perm_q,
                           w.tiles, w.ntiles, w.part_o, w.part_ml, w.merge, w.nmerge,
-                          w.krow, attn_krow_stride(D.N)));
+                          w.krow, attn_krow_stride(D.N), w.rng_start, w.rng_pre, w.rng_cnt, D.maxr, w.perm_k));
   prof_mark(EV_ATTN, st);
   return 0;
 }
@@ -782,7 +785,7 @@ int adacluster_dense_attn(const adacluster_params* p, const void* Q, const void*
   prof_mark(EV_PLAN, st);
   RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, 1, D.maxtiles, scale, Q, K, V, O, nullptr, w.tiles,
                           w.ntiles, w.part_o, w.part_ml, nullptr, nullptr,
-                          w.krow, attn_krow_stride(D.N)));
+                          w.krow, attn_krow_stride(D.N), w.rng_start, w.rng_pre, w.rng_cnt, 1, nullptr));
   prof_mark(EV_ATTN, st);
   return 0;
 }

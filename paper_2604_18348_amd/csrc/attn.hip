@@ -98,6 +98,7 @@ __global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, in
       s_nr = carry_nr; s_total = carry_total;
     }
   }
+  if (!krow) return;      // (the fp32 kernel finds its rows from the ranges: see attn_rows_listed)
   __syncthreads();        // the ranges are visible to the whole workgroup
   // Every key row of the concatenation, in order, as a byte offset (bf16) or a row number (fp32, row_scale 1): what
   // a key tile of the attention kernel loads its rows by.  Entries past the end (up to the padding the kernel may read ahead) repeat the
@@ -251,6 +252,7 @@ __global__ void plan_dense(int N, int maxtiles, int BM, int row_scale, int32_t* 
                            int32_t* __restrict__ krow, size_t kstride) {
   const int h = blockIdx.x;
   if (blockIdx.y > 0) {       // the other workgroups of a head fill its row-offset table (the identity)
+    if (!krow) return;
     int32_t* kr = krow + (size_t)h * kstride;
     const int padded = (N + 63) / 64 * 64 + KROW_PAD;
     for (int p = (blockIdx.y - 1) * blockDim.x + threadIdx.x; p < padded; p += (gridDim.y - 1) * blockDim.x)
@@ -322,6 +324,8 @@ struct AttnArgs {
   float* part_o; float* part_ml;   // partial slots of cut key lists: [H][slots][BM][d], [H][slots][BM][2]
   int slots, BM;
   const int32_t* krow; size_t kstride;   // every key row of a query cluster's list (byte offset, fp32: row number): [H][Cq][kstride]
+  const int32_t* rng_start; const int32_t* rng_pre; const int32_t* rng_cnt; int maxr;   // the ranges it was written from, and
+  const int32_t* perm_k;                 // their order -> token (NULL: identity): for the fp32 kernel without a table
 };
 
 // Workgroup -> (head, query tile) of a launch of pick_tile_grid.  Workgroups go to the 8 XCDs round-robin in launch order,
@@ -785,13 +789,15 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
 // queries are 128 half tiles for 256 CUs) over gridDim.z workgroups as well, which leave unnormalised partial results
 // that attn_merge_f32 combines (see attn_f32_splits).  Vector instructions do not run under an fp32 product on this chip
 // (the co-execution counter reads 0), so every one of them adds its four cycles: the masks are for the last tile
-// only, the accumulator is rescaled only when the maximum has moved, and addresses inside a head are 32-bit offsets
-// (WIDE: 64-bit, for heads of 4 GiB and more).  Without these the 545 vector instructions a tile took a fifth of the time.
+// only, the accumulator is rescaled only when the maximum has moved, and addresses inside a head are 32-bit offsets.
+// Without these the 545 vector instructions a tile took a fifth of the time.
+// LISTED: the key rows of a tile come from the table of the planning step, and a head has less than 4 GiB; else they are
+// searched in the ranges of the list, tile by tile, and offsets are 64-bit (attn_rows_listed says which).
 // Measured against a kernel of two waves of 32 queries a workgroup with K and V through LDS and three barriers a tile:
 // dense, d=128, 4 heads x 8 192 rows 71 -> 130 TFLOP/s (of 153 that an fp32 GEMM reaches), 1 x 4 096 9 -> 103; one head of
 // 4 096 queries (d=64) against a quarter of its keys 190 -> 33 us, three of 5 007 (d=128) against a third 533 -> 225 us.
 // (Eight waves a workgroup, one workgroup a CU: 37 and 237 us.)
-template <int D, bool WIDE>
+template <int D, bool LISTED>
 __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
   constexpr int BN = 32, DB = D / 32, NW = F32_WAVES, SROW = D + 4, PPR = D / 4, RPI = 64 / PPR;   // 16-byte pieces a row, rows a load
   int h, tile;                                             // (tile: half of a 64-query tile)
@@ -806,7 +812,7 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
   const float* Qh = (const float*)a.Q + (size_t)h * a.N * D;
   const char* Kh = (const char*)((const float*)a.K + (size_t)h * a.N * D);
   const char* Vh = (const char*)((const float*)a.V + (size_t)h * a.N * D);
-  typedef typename std::conditional<WIDE, size_t, uint32_t>::type off_t;
+  typedef typename std::conditional<LISTED, uint32_t, size_t>::type off_t;
   // a wave's K tile in the loop; after it, its accumulator, a (padded) row per query
   __shared__ __attribute__((aligned(16))) float sk[NW * 32 * SROW];
   __shared__ float sm[NW][32], sl[NW][32];
@@ -824,14 +830,38 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
       const int row = __builtin_amdgcn_ds_bpermute(lr * 4 + n * RPI * 4, idx);
       const uint32_t piece = (uint32_t)(lp ^ ((n * RPI + lr) & 15)) * 16;
       const off_t off = (off_t)(uint32_t)row * (D * 4) + piece;
-      if constexpr (WIDE) dma_b128(kt_lds + n * 1024, Kh + off);
-      else dma_b128(kt_lds + n * 1024, off, Kh);
+      if constexpr (LISTED) dma_b128(kt_lds + n * 1024, off, Kh);
+      else dma_b128(kt_lds + n * 1024, Kh + off);
     }
+  };
+  // Row number of key c of tile t, for a wave's tiles in order.  Without the table: r0 is a range that starts at or before
+  // the tile, b the starts of the 64 ranges behind it, one a lane; once at most 32 of them lie before the tile, its keys are
+  // in those ranges (every range has a key), and each lane counts the starts up to its own.
+  int r0 = 0;
+  auto key_row = [&](int t) __attribute__((always_inline)) {
+    if constexpr (LISTED) return kr[t * BN + c];
+    const size_t list = (size_t)h * a.Cq + qc;
+    const int32_t* rs = a.rng_start + list * a.maxr;
+    const int32_t* rp = a.rng_pre + list * (a.maxr + 1);
+    const int nr = a.rng_cnt[list], p = min(t * BN + c, total - 1);          // (keys past the end repeat the last: masked)
+    int b;
+    for (;;) {
+      b = r0 + 1 + lane < nr ? rp[r0 + 1 + lane] : INT32_MAX;
+      const int before = __popcll(__ballot(b <= t * BN));
+      if (before <= 32) break;
+      r0 += before;
+    }
+    int n = 0;
+#pragma unroll
+    for (int step = 32; step; step >>= 1)
+      if (__builtin_amdgcn_ds_bpermute((n + step - 1) * 4, b) <= p) n += step;
+    const int row = rs[r0 + n] + p - rp[r0 + n];
+    return a.perm_k ? a.perm_k[(size_t)h * a.N + row] : row;
   };
   // (the table is padded: entries past the list are rows that exist, and masked)
   const int t0 = blockIdx.z * NW + wave, tstep = gridDim.z * NW;
   int kidx = 0;
-  if (t0 < T) { kidx = kr[t0 * BN + c]; issue_k(kidx); }
+  if (t0 < T) { kidx = key_row(t0); issue_k(kidx); }
   float q[D / 2];
   {
     const int r = row0 + min(c, nrows - 1);                // (rows past the end repeat the last one and are not stored)
@@ -868,7 +898,7 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
     // flight the K operands would be left a single register quad, and every fourth product would wait out an LDS read.
 #pragma unroll
     for (int j = 0; j < 8; ++j) load_v(j);
-    if (t + tstep < T) kidx = kr[(t + tstep) * BN + c];
+    if (t + tstep < T) kidx = key_row(t + tstep);
     __builtin_amdgcn_sched_barrier(0);
     f32x16_t s;
 #pragma unroll
@@ -1118,6 +1148,18 @@ static dim3 pick_tile_grid(int H, int most, int z) {
 
 size_t attn_krow_stride(int N) { return (size_t)(N + 63) / 64 * 64 + KROW_PAD; }
 
+// Whether the planning step writes the key rows of every list to a table, [H][Cq][N + padding] integers.  The fp32 kernel can
+// also search them in the ranges, tile by tile: 6-7 % slower with tens of clusters (one head of 4 096, d=64, 32 clusters
+// 69 and 76 us for the call; three of 5 007, d=128, 65 clusters 251 and 266), 15-34 % with hundreds and thousands (4 x 12 000,
+// d=64, 1 024 clusters 1 365 and 1 832; 24 x 20 000, d=128, 512 clusters 6.5 and 7.5 ms).  So the table stays, unless it takes
+// more than 1 GiB and more than copies of K and V would (24 x 180 000 rows with 4 096 clusters: 71 GB; all else in the
+// workspace 11): a call has to fit the card.  Heads of 4 GiB and more need 64-bit offsets, which only the searching form has.
+bool attn_rows_listed(int dtype, int d, int H, int N, int Cq) {
+  if (dtype == ADACLUSTER_BF16) return true;
+  const bool large = Cq > 2 * d && (size_t)H * Cq * attn_krow_stride(N) * 4 > ((size_t)1 << 30);
+  return !large && (size_t)N * d * 4 < ((size_t)1 << 32);
+}
+
 int attn_tile_record() { return TILE_REC; }
 int attn_split_slots() { return SPLIT_SLOTS; }
 
@@ -1152,11 +1194,13 @@ int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, int BM, int32_t
 int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int maxtiles, float scale,
                      const void* Q, const void* K, const void* V, void* O, const int32_t* perm_q,
                      const int32_t* tiles, const int32_t* ntiles, float* part_o, float* part_ml,
-                     const int32_t* merge, const int32_t* nmerge, const int32_t* krow, size_t kstride) {
+                     const int32_t* merge, const int32_t* nmerge, const int32_t* krow, size_t kstride,
+                     const int32_t* rng_start, const int32_t* rng_pre, const int32_t* rng_cnt, int maxr, const int32_t* perm_k) {
   AttnArgs a{Q, K, V, O, perm_q, tiles, ntiles, H, N, Cq, maxtiles,
              scale * 1.4426950408889634f,
              (Cq == 1 || (size_t)4 * N * d <= ((size_t)8 << 20)) ? 1 : 0,
-             part_o, part_ml, SPLIT_SLOTS, attn_block_rows(dtype, d, N, Cq), krow, kstride};
+             part_o, part_ml, SPLIT_SLOTS, attn_block_rows(dtype, d, N, Cq), krow, kstride,
+             rng_start, rng_pre, rng_cnt, maxr, perm_k};
   dim3 g((maxtiles + 7) / 8 * 8, H);
   if (dtype == ADACLUSTER_BF16) {
     if (attn_small_shape(N, Cq)) {
@@ -1172,10 +1216,9 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
     }
   } else {
     const int splits = attn_f32_splits(H, N, Cq);
-    const bool wide = (size_t)N * d * 4 >= ((size_t)1 << 32);
     const dim3 g2 = pick_tile_grid(H, 2 * (N / 64 + Cq + 1), splits), gm((N + 1024 / d - 1) / (1024 / d), H);
-    if (d == 64) { if (wide) attn_f32<64, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<64, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
-    else { if (wide) attn_f32<128, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<128, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
+    if (d == 64) { if (krow) attn_f32<64, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<64, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
+    else { if (krow) attn_f32<128, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<128, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
     if (splits > 1) {
       if (d == 64) attn_merge_f32<64><<<gm, 256, 0, s>>>(a, splits);
       else attn_merge_f32<128><<<gm, 256, 0, s>>>(a, splits);

@@ -123,12 +123,14 @@ int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, int BM, int32_t
                       int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles, int row_scale, int32_t* krow, size_t kstride);
 // entries per (head, query cluster) of the table of key rows (times row_scale) that the attention kernels load by
 size_t attn_krow_stride(int N);
+bool attn_rows_listed(int dtype, int d, int H, int N, int Cq);    // the planning step writes every key row of a list to a table
 int launch_attn_stats(hipStream_t s, int H, int Cq, int maxr, int maxtiles, const KState* st, const int32_t* tiles,
                       const int32_t* ntiles, const int32_t* rng_pre, const int32_t* rng_cnt, adacluster_head_stats* out);
 int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int maxtiles, float scale,
                      const void* Q, const void* K, const void* V, void* O, const int32_t* perm_q,
                      const int32_t* tiles, const int32_t* ntiles, float* part_o, float* part_ml,
                      const int32_t* merge /* NULL: no cut lists */, const int32_t* nmerge,
-                     const int32_t* krow, size_t kstride);
+                     const int32_t* krow /* NULL: not attn_rows_listed */, size_t kstride, const int32_t* rng_start,
+                     const int32_t* rng_pre, const int32_t* rng_cnt, int maxr, const int32_t* perm_k /* NULL: identity */);
 
 }  // namespace adac

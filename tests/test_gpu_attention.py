@@ -282,3 +282,52 @@ def test_fp32_lists_whole_and_split_over_up_to_four_workgroups(H, N, d, splits):
         check(to_np(O[h]), orc.sparse_attention_gather(Q[h], K[h], V[h], ql[h], kl[h], sel[h]), B.F32)
         check(to_np(D[h]), orc.dense_attention(Q[h], K[h], V[h]), B.F32)
     assert bool(torch.isfinite(O).all()) and bool(torch.isfinite(D).all())
+
+
+@pytest.mark.parametrize("H,N,d,Cq", [(18, 3700, 64, 3600), (33, 3001, 128, 2700)])
+def test_fp32_key_rows_searched_in_the_ranges(H, N, d, Cq):
+    """So many query clusters that the table of key rows would take more than 1 GiB: the kernel finds its rows from the ranges
+    of a list.  Lists of a range per key cluster (every other one, up to 700 ranges), of one long range, of all keys, of
+    single keys, and an empty one; the dense call of the same params."""
+    Ck = 1400
+    assert Cq > 2 * d and 4 * H * Cq * ((N + 63) // 64 * 64 + 512) > 2 ** 30
+    Q, K, V, _, _, _ = make_case(51, N, d, B.F32, H=H)
+    rng = np.random.default_rng(52)
+    ql = np.sort(rng.integers(0, Cq, (H, N)), axis=1).astype(np.int32)
+    ql[:, N // 2:] %= 9                                             # some clusters of whole query tiles
+    kl = rng.permuted(np.minimum(np.arange(N) % Ck + (np.arange(N) % 7 == 0) * 3, Ck - 1).astype(np.int32)[None].repeat(H, 0), axis=1)
+    kinds = [np.arange(0, Ck, 2), np.arange(100, 900), np.arange(Ck), np.array([5]), np.zeros(0), np.arange(1, Ck, 3),
+             np.array([0, 1, 700, Ck - 1]), np.concatenate([np.arange(0, 600), np.arange(601, Ck, 2)])]
+    sel = [[kinds[(i + h) % len(kinds)].astype(np.int64) for i in range(Cq)] for h in range(H)]
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=Cq, k_m0=4, k_m_min=1, k_max_clusters=Ck)
+    si, sc = sel_to_dev(sel, Cq, p.cap)
+    Qd, Kd, Vd = to_dev(Q, B.F32), to_dev(K, B.F32), to_dev(V, B.F32)
+    O = torch.full_like(Qd, float("nan"))
+    ws = B.workspace(p)
+    B.adacluster_sparse_attn(p, Qd, Kd, Vd, torch.from_numpy(ql).cuda(), torch.from_numpy(kl).cuda(),
+                             torch.full((H,), Ck, dtype=torch.int32, device="cuda"), si, sc, out=O, ws=ws)
+    D = B.adacluster_dense_attn(p, Qd, Kd, Vd, out=torch.full_like(Qd, float("nan")), ws=ws)
+    for h in (0, H - 1):
+        check(to_np(O[h]), orc.sparse_attention_gather(Q[h], K[h], V[h], ql[h], kl[h], sel[h]), B.F32)
+    check(to_np(D[H - 1]), orc.dense_attention(Q[H - 1], K[H - 1], V[H - 1]), B.F32)
+    assert bool(torch.isfinite(O).all()) and bool(torch.isfinite(D).all())
+
+
+def test_fp32_head_of_more_than_4_gib():
+    """Byte offsets inside a head pass 2^32: 100 keys of 8.4 million, the last rows among them."""
+    H, N, d = 1, 2 ** 23 + 4001, 128
+    assert N * d * 4 > 2 ** 32
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    Q, K, V = (torch.randn((H, N, d), generator=gen, device="cuda") for _ in range(3))
+    at = torch.cat([torch.randint(0, N, (60,), generator=gen, device="cuda"), torch.arange(N - 40, N, device="cuda")]).unique()
+    kl = torch.zeros((H, N), dtype=torch.int32, device="cuda")
+    kl[0, at] = 1
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=1, k_m0=1, k_m_min=1, k_max_clusters=3)
+    sel = torch.ones((H, 1, p.cap), dtype=torch.int32, device="cuda")
+    one = torch.ones((H, 1), dtype=torch.int32, device="cuda")
+    O = torch.full_like(Q, float("nan"))
+    B.adacluster_sparse_attn(p, Q, K, V, torch.zeros_like(kl), kl, 2 * one[0], sel, one, out=O)
+    for n in range(0, N, 2 ** 20):
+        P = torch.softmax(Q[0, n:n + 2 ** 20] @ K[0, at].T.contiguous() / d ** 0.5, 1)
+        assert float((O[0, n:n + 2 ** 20] - P @ V[0, at]).abs().max()) < 1e-4
