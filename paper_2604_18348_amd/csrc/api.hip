@@ -2,6 +2,7 @@
 // order in which the kernels of Algorithm 3 are enqueued.  No device memory is allocated here.
 #include "common.h"
 #include "launch.h"
+#include "stage_report.h"
 
 #include <math.h>
 #include <stdarg.h>
@@ -92,15 +93,9 @@ StageReadback* stage_readback() {
   return &r;
 }
 
-// Waits for the report of stage t.  A stream that has run dry (or failed) without it ends the wait with an error.
+// Waits for the report of stage t.
 bool stage_report_landed(const StageReadback& r, int t, hipStream_t st) {
-  const int32_t* word = r.host + 4 * t + 3;
-  for (unsigned spin = 1;; ++spin) {
-    if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == r.epoch) return true;
-    if ((spin & 0xFFF) == 0 && hipStreamQuery(st) != hipErrorNotReady)
-      return __atomic_load_n(word, __ATOMIC_ACQUIRE) == r.epoch;
-    __builtin_ia32_pause();
-  }
+  return report_landed(r.host + 4 * t + 3, r.epoch, st);
 }
 
 AuxStream* aux_stream() {
