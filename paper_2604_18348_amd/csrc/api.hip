@@ -423,7 +423,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   // host knows: every head starts alike.
   rb = stage_readback();
   if (!rb) return fail(ADACLUSTER_E_INTERNAL, "stage read-back set-up failed: %s", hipGetErrorString(hipGetLastError()));
-  int n_bound = D.N, m_bound = p->k_m0 < D.N ? p->k_m0 : D.N;
+  int n_bound = D.N, m_bound = p->k_m0 < D.N ? p->k_m0 : D.N, heads = D.H;
   KState *cur = w.kstate, *other = w.kstate2;      // the stage head reads one and writes the other
   StageFilter filter{};                            // how the stage before ended
   for (int t = 0; t <= p->k_max_stages; ++t) {
@@ -438,7 +438,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
         return fail(ADACLUSTER_E_INTERNAL, "stage read-back failed: %s", hipGetErrorString(hipGetLastError()));
       const int32_t* summ = rb->host + 4 * (t - 1);
       if (summ[0] == 0) break;                 // stage t-1 had no active head: the loop ended there
-      n_bound = summ[1]; m_bound = summ[2];
+      heads = summ[0]; n_bound = summ[1]; m_bound = summ[2];
     }
     if (t > 0) kc_bound += m_bound;
     if (t == p->k_max_stages) break;           // the stage head has just closed every head
@@ -453,11 +453,11 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
         return fail(ADACLUSTER_E_INTERNAL, "stage read-back failed: %s", hipGetErrorString(hipGetLastError()));
       const int32_t* cur = rb->host + 4;
       if (cur[0] == 0) break;                  // no head needs a second stage
-      n_bound = cur[1]; m_bound = cur[2];
+      heads = cur[0]; n_bound = cur[1]; m_bound = cur[2];
     }
-    if (t > 0 && p->dtype == ADACLUSTER_BF16 && n_bound <= small_stage_points() && m_bound <= small_stage_centres()) {
+    if (t > 0 && p->dtype == ADACLUSTER_BF16 && n_bound <= small_stage_points(D.d, heads) && m_bound <= small_stage_centres()) {
       // few points and few centres left in every head: one launch runs this and every later stage
-      // (|U| and m_t never grow, so the bounds hold for all of them)
+      // (|U|, m_t and the active heads never grow, so the bounds hold for all of them)
       RET_IF(launch_kstages_small(st, D.d, D.H, D.N, D.cap, p->k_max_clusters, p->k_m0, p->k_m_min, p->k_max_stages,
                                   u_min, p->k_iters, cur, w.tau, w.ulist[0], w.ulist[1], K, w.cent_lp, k_assign,
                                   w.bias, k_stage_of));

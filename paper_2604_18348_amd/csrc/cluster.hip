@@ -1392,8 +1392,7 @@ __global__ __launch_bounds__(256) void stage_open(const T* __restrict__ X, OpenC
 //               the whole pass; the waves' partial sums are then added in a fixed order, so the result
 //               is deterministic;
 //   filter:     squared distances of the last pass stay in LDS; U is compacted in ascending order.
-// (lists of up to 3 072 points: with 8 192 and with 2 048, 12 heads of 32 760 tokens, d=128, took 869 and 853 us, with this 855)
-constexpr int SMALL_NU = 3072;
+constexpr int SMALL_NU = 8192;
 constexpr int SMALL_M = 32;
 
 struct SmallStageCfg {
@@ -1978,7 +1977,19 @@ int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, in
   return chk();
 }
 
-int small_stage_points() { return SMALL_NU; }
+// Up to how many points a list goes to the one-launch kernel.  A stage there costs a head's workgroup, whatever the number
+// of heads, about 11 us and 10.5 ns a point (21 at d=128); in six launches (block sums) it costs 33-37 us and, for every
+// head, 0.13-0.17 ns a point (0.27-0.34).  Of one head with 1 500, 2 500, 7 000 points, 30 centres, d=64, a stage takes 29,
+// 40, 86 us in the one and 33, 35, 40 in the other form, of 30 heads 30, 41, 88 and 40, 50, 68; d=128 48, 71, 164 and 39, 41,
+// 48, and 50, 72, 168 and 52, 65, 109.  With U as it is the lines cross at about 2 048 points (one head, d=64), further out
+// the more heads share the launches, and no more from about 64 heads on (72 at d=128): calls of nine stages, 200 heads
+// of 3 500 and 8 000 points, d=64, 763 and 1 385 us, in six launches a stage 1 576 and 3 450.  But the points are the bound
+// of the stage before, U shrinks, and what follows is in the one launch too: below 3 072 it is taken always (5 heads
+// of 9 247 tokens, d=128: the call 612 us, with the line at 1 100 636).
+int small_stage_points(int d, int heads) {
+  const int one = d == 64 ? 2048 : 1024, all = d == 64 ? 64 : 72;
+  return heads >= all ? SMALL_NU : min(SMALL_NU, max(3072, one * all / (all - heads)));
+}
 int small_stage_centres() { return SMALL_M; }
 
 int launch_kstages_small(hipStream_t s, int d, int H, int N, int cap, int n_max, int m0, int m_min, int max_stages,

@@ -88,7 +88,7 @@ int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, in
 // Every remaining stage of Algorithm 1 in one launch, one workgroup per head (bf16 only).  Valid once every
 // active head has at most small_stage_points() unassigned points and small_stage_centres() centres per
 // stage, and never for stage 0 (it needs a list of U and a known tau).
-int small_stage_points();
+int small_stage_points(int d, int heads);      // heads: still active
 int small_stage_centres();
 int launch_kstages_small(hipStream_t s, int d, int H, int N, int cap, int n_max, int m0, int m_min, int max_stages,
                          int u_min, int iters, KState* st, const float* tau, int32_t* ulist0, int32_t* ulist1,

@@ -60,3 +60,21 @@ def test_block_sums_around_the_changes_of_their_split(d, m):
     torch.cuda.synchronize()
     for h in range(H):
         check_stages_against_oracle(K[h], out, h, 1, 2, p.tau_abs)
+
+
+@pytest.mark.parametrize("d,H,N,iters", [(64, 1, 4000, 3), (64, 70, 4000, 3), (128, 72, 5000, 3), (128, 60, 5000, 3),
+                                         (128, 72, 8192, 1), (64, 66, 8192, 1), (64, 66, 8193, 1)])
+def test_late_stages_on_either_side_of_the_one_launch_kernel(d, H, N, iters):
+    """A list of thousands of points stays with the launch chain where few heads share it and goes to the one-launch kernel (up to
+    8 192 points) where many do: a threshold that removes next to nothing, so that every stage is that long; the oracle's
+    stages on the first and last head.  (U hardly changes, so all stages are alike, and the strict bound of two passes, which
+    leaves out centres with points within rounding of two of them, would leave out the same third in every stage: three
+    passes under their bound, and at the kernel's full length one pass, whose centres are rows of K and equal.)"""
+    _, K, _ = wl.make_small(60 + H, N, d, 14, dtype="bf16", H=H)
+    p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=4, k_iters=iters, k_m0=30, k_m_min=6, k_max_clusters=300, k_max_stages=4,
+                 tau_abs=0.1)
+    out = B.adacluster_kcluster(p, to_dev(K, B.BF16))
+    torch.cuda.synchronize()
+    assert int((out["k_stage_of"] == -1).sum()) > 0.9 * H * N
+    for h in sorted({0, H - 1}):
+        check_stages_against_oracle(K[h], out, h, 4, iters, p.tau_abs)
