@@ -26,7 +26,9 @@ def dt_name(dtype):
 @pytest.mark.parametrize("dtype,d,N,Cq", [(B.BF16, 64, 3000, 17), (B.BF16, 128, 2511, 65), (B.F32, 64, 1500, 9),
                                           (B.F32, 128, 700, 5), (B.BF16, 64, 70, 65),
                                           # both sides of the size at which the label sort changes from one
-                                          # workgroup per head to one wave per 512-item segment
+                                          # workgroup per head to the counting sort of 2 048-item segments, and
+                                          # a whole and a started last segment
+                                          (B.BF16, 64, 4096, 33), (B.BF16, 64, 4097, 33), (B.F32, 128, 4097, 150),
                                           (B.BF16, 64, 16384, 33), (B.BF16, 64, 16400, 33)])
 def test_qcluster_chained(dtype, d, N, Cq):
     H = 2
@@ -352,10 +354,13 @@ def test_kcluster_bf16_stage_centres_follow_the_oracle_trajectory(d, N, tau):
 
 
 @pytest.mark.parametrize("d,N,tau,iters", [(64, 7000, 2.2, 3), (128, 5000, 3.3, 3), (64, 7000, 2.2, 1),
-                                          (128, 5000, 3.3, 2), (64, 7000, 2.2, 2)])
+                                          (128, 5000, 3.3, 2), (64, 7000, 2.2, 2),
+                                          (64, 3072, 2.2, 3), (64, 3072, 2.2, 2), (64, 3072, 2.2, 1), (64, 2900, 2.2, 2),
+                                          (128, 3072, 3.3, 3), (128, 3000, 3.3, 2), (128, 3072, 3.3, 1)])
 def test_kcluster_many_late_stages_in_one_launch(d, N, tau, iters):
-    """A tight threshold leaves thousands of points unassigned stage after stage: from the second stage
-    on, one workgroup per head runs all the remaining stages in a single launch.  One more or one less
+    """A tight threshold leaves thousands of points unassigned stage after stage: with up to 3 072 points, from the second stage
+    on, one workgroup per head runs all the remaining stages in a single launch (the longer lists take the launch chain, at
+    d=128 until enough has been removed).  One more or one less
     point in U moves every strided initial sample of the next stage, so a free-running comparison over
     eight stages is meaningless; instead every stage is checked on its own: the oracle's k-means on the
     U the device had at that stage (read off k_stage_of) must give the device's stage centres.  A second
@@ -382,7 +387,7 @@ def test_kcluster_many_late_stages_in_one_launch(d, N, tau, iters):
         assert np.all(np.diff(offs[h][:9]) > 0) and not bool(out["full_flag"][h])      # eight stages ran
         for t in range(1, 8):
             U = np.flatnonzero((stage_of[h] >= t) | (stage_of[h] == -1))
-            assert 1000 < U.size <= 8192 and offs[h, t + 1] - offs[h, t] <= 32
+            assert 1000 < U.size <= (8192 if N > 3072 else 3072) and offs[h, t + 1] - offs[h, t] <= 32
         check_stages_against_oracle(K[h], out, h, 8, iters, tau)
 
 
@@ -392,7 +397,7 @@ def check_stages_against_oracle(Kh, out, h, n_stages, iters, tau):
     offs = out["k_stage_offs"].cpu().numpy()[h]
     stage_of = out["k_stage_of"].cpu().numpy()[h]
     C = to_np(out["k_assign_centroids"])[h]
-    worst_equal, worst_diff, worst_removed = 1.0, 0.0, 1.0
+    worst_equal, worst_diff, worst_removed, strict_equal = 1.0, 0.0, 1.0, 1.0
     excluded = 0
     for t in range(n_stages):
         U = np.flatnonzero((stage_of >= t) | (stage_of == -1))
@@ -414,6 +419,7 @@ def check_stages_against_oracle(Kh, out, h, n_stages, iters, tau):
             strict = np.ones(m_t, dtype=bool)
             strict[order[tied].ravel()] = False
             excluded += int((~strict).sum())
+            strict_equal = min(strict_equal, float((got == Ct)[strict].mean()))
             step = 2.0 ** -7 * np.maximum(np.abs(Ct), np.abs(got))
             assert np.all(np.abs(got - Ct)[strict] <= step[strict]), (t, float((np.abs(got - Ct) / np.maximum(step, 1e-30))[strict].max()))
         worst_equal = min(worst_equal, float((got == Ct).mean()))
@@ -425,7 +431,9 @@ def check_stages_against_oracle(Kh, out, h, n_stages, iters, tau):
     if iters == 1:
         assert worst_equal == 1.0                      # the strided sample itself
     if iters == 2:
-        assert worst_equal > 0.97 and worst_removed > 0.999
+        # (of the strictly checked centres: a point within rounding of two others moves both of them, and two of the 23
+        # centres of a late stage are 9 % of its entries)
+        assert strict_equal > 0.97 and worst_removed > 0.999
     # Both sides round the centres to bf16.  A mean that the fp32 and the fp64 sums put on different sides
     # of a rounding boundary differs by one bf16 step; in diffuse data that step flips a few points
     # on the centre's boundary in the next pass, which moves the means of both neighbours a little

@@ -8,6 +8,9 @@ import pytest
 import torch
 
 from paper_2604_18348_amd import binding as B
+from paper_2604_18348_amd import workloads as wl
+from tests.helpers import to_dev
+from tests.test_gpu_cluster import check_kcluster
 
 pytestmark = pytest.mark.gpu
 
@@ -92,3 +95,17 @@ def test_labels_and_counts_outside_their_range(N, kc, cap, kc_extra):
         rel = float((got[r] - ref).norm() / ref.norm())
         assert rel < 1e-2, rel
         assert bool((got[dev(np.flatnonzero(~rows))] == -7.0).all())
+
+
+@pytest.mark.parametrize("dtype,d,N,m0", [(B.BF16, 64, 4096, 140), (B.BF16, 64, 4097, 140), (B.BF16, 128, 6145, 129),
+                                          (B.F32, 64, 4096, 20), (B.F32, 64, 4097, 200)])
+def test_key_clustering_around_the_change_of_the_sort(dtype, d, N, m0):
+    """More than 128 first-stage centres are updated from sorted labels (fp32: by members up to a size), and the final sort has
+    more than 128 clusters, or fewer, on either side of one workgroup's 4 096 items: labels, member means, sizes and boxes
+    against the oracle (check_kcluster)."""
+    H = 2
+    _, K, _ = wl.make_small(61, N, d, 30, dtype="bf16" if dtype == B.BF16 else "f32", H=H)
+    p = B.Params(H=H, N=N, d=d, dtype=dtype, q_clusters=4, k_iters=3, k_m0=m0, k_m_min=4, k_max_clusters=3 * m0, tau_factor=1.1)
+    out = B.adacluster_kcluster(p, to_dev(K, dtype), want_box=True)
+    torch.cuda.synchronize()
+    check_kcluster(K, p, out, dtype)
