@@ -12,6 +12,8 @@ import numpy as np
 BF16_PEAK_TFLOPS = 2500.0      # MI355X dense bf16 MFMA, published
 FP32_VALU_PEAK_TFLOPS = 157.3  # MI355X fp32 vector, published
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
+SORT_ONE_WORKGROUP = 4096      # items of a head that csrc/sort.hip sorts in one workgroup, at most
+SORT_SEGMENT = 2048            # items of a segment of its counting sort
 
 
 def device_inputs(name, aligned=False):
@@ -69,6 +71,15 @@ def _profiled(fn, B, reps):
         for k, v in B.adacluster_profile_read().items():
             acc[k] = acc.get(k, 0.0) + v
     return {k: v / reps for k, v in acc.items()}
+
+
+def label_sort_bytes(n, labels, bound):
+    """Bytes that sorting one head's n labels (values below `labels`, the caller's bound `bound`) reads and writes."""
+    if n <= SORT_ONE_WORKGROUP:            # radix passes of 7 bits; one value more stands for labels out of range
+        passes = -(-bound.bit_length() // 7)
+        return (12 + 16 * (passes - 1)) * n                # the first pass reads no values
+    # Per segment and label: the count is written, read twice and replaced by its prefix, and read with the total.
+    return 12 * n + 4 * 6 * -(-n // SORT_SEGMENT) * (labels + 1)
 
 
 def mfma_microbench_tflops(B, iters=20000):
@@ -174,18 +185,19 @@ def measure(name, steps, warmup, spinup_ms=500.0, dense_steps=3, profile_reps=No
         B.adacluster_profile_enable(False)
         del kc
         rows = float(H) * N
-        cap = p.k_max_clusters + p.k_m0
-        q_passes, k_passes = -(-max(1, (p.q_clusters - 1).bit_length()) // 7), -(-max(1, (cap - 1).bit_length()) // 7)
         hbm = {}
 
         def entry(key, ms_, nbytes, what):
             if ms_ and ms_ > 0:
                 gbs = nbytes / (ms_ * 1e-3) / 1e9
                 hbm[key] = {"ms": ms_, "bytes": nbytes, "GB/s": gbs, "frac": gbs / HBM_PEAK_GBS, "what": what}
-        sort_bytes = lambda passes: (16.0 + 20.0 * (passes - 1)) * rows
-        entry("label_sorts", pr.get("select"), sort_bytes(q_passes) + sort_bytes(k_passes),
-              "query labels (%d radix pass) and key labels (%d): per item and pass 4 B read to count, 4 B (first "
-              "pass) or 8 B read and 8 B written to scatter" % (q_passes, k_passes))
+        sort_bytes = sum(label_sort_bytes(N, p.q_clusters, p.q_clusters) for _ in range(H)) + sum(
+            label_sort_bytes(N, s["k_count"], p.k_max_clusters + p.k_m0) for s in stats)
+        entry("label_sorts", pr.get("select"), float(sort_bytes),
+              "query labels and key labels, %s" % (
+                  "one workgroup a head: labels and values of every radix pass read and written" if N <= SORT_ONE_WORKGROUP else
+                  "counting sort: per item 8 B of labels read and 4 B of the permutation written, and the counts of the "
+                  "%d-item segments as they are written and read (mostly out of the caches)" % SORT_SEGMENT))
         entry("seg_reduce", t_red, rows * d * es + 4.0 * rows, "K rows and the permutation read once")
         out["hbm"] = hbm
     del Q, K, V, O, ws, outs
