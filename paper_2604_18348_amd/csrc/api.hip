@@ -247,9 +247,9 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(blockcnt, int32_t*, H * D.ncnt * 4);
   TAKE(tau_part, double*, H * D.nblk * 8);
   TAKE(sort.hist, int32_t*, H * sort_table_ints(D.N, D.capmax) * 4);
-  TAKE(sort.lab_a, int32_t*, H * N * 4);
-  TAKE(sort.val_a, int32_t*, H * N * 4);
-  TAKE(sort.lab_b, int32_t*, H * N * 4);
+  TAKE(sort.lab_a, int32_t*, H * sort_scratch_ints(D.N) * 4);
+  TAKE(sort.val_a, int32_t*, H * sort_scratch_ints(D.N) * 4);
+  TAKE(sort.lab_b, int32_t*, H * sort_scratch_ints(D.N) * 4);
   TAKE(perm_tmp, int32_t*, H * N * 4);
   TAKE(offs_tmp, int32_t*, H * (size_t)(D.capmax + 1) * 4);
   TAKE(poff, int32_t*, H * (size_t)(D.capmax + 1) * 4);
@@ -265,9 +265,9 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(q_cent_lp, void*, H * (size_t)D.Cq * d * es);
   TAKE(q_bias, float*, H * (size_t)D.Cq * 4);
   TAKE(q_sort.hist, int32_t*, H * sort_table_ints(D.N, D.Cq) * 4);
-  TAKE(q_sort.lab_a, int32_t*, H * N * 4);
-  TAKE(q_sort.val_a, int32_t*, H * N * 4);
-  TAKE(q_sort.lab_b, int32_t*, H * N * 4);
+  TAKE(q_sort.lab_a, int32_t*, H * sort_scratch_ints(D.N) * 4);
+  TAKE(q_sort.val_a, int32_t*, H * sort_scratch_ints(D.N) * 4);
+  TAKE(q_sort.lab_b, int32_t*, H * sort_scratch_ints(D.N) * 4);
   TAKE(q_poff, int32_t*, H * (size_t)(D.Cq + 1) * 4);
   TAKE(q_psum, float*, H * (size_t)(N / reduce_part_rows() + D.Cq + 34) * d * 4);
   TAKE(q_pnorm, float*, H * (size_t)(N / reduce_part_rows() + D.Cq + 34) * 4);

@@ -7,10 +7,11 @@ namespace adac {
 
 struct SortScratch {
   int32_t* hist;                     // [H][sort_table_ints]: counts of a segment's labels
-  int32_t* lab_a; int32_t* val_a;    // [H][N] intermediate pass of the one-workgroup sort
-  int32_t* lab_b;                    // [H][N] its sorted labels
+  int32_t* lab_a; int32_t* val_a;    // [H][sort_scratch_ints] intermediate pass of the one-workgroup sort
+  int32_t* lab_b;                    // [H][sort_scratch_ints] its sorted labels
 };
 size_t sort_table_ints(int N, int m);    // for heads of up to N items and up to m labels
+int sort_scratch_ints(int N);
 
 // Stable sort of the first n_h items of every head by label (labels are indexed by position in
 // the item list; the items are token ids from `ulist`, or the positions themselves).

@@ -1,23 +1,22 @@
-// Pieces shared by the label sort (sort.hip) and the clustering kernels (cluster.hip): the sort
-// of one head by ONE workgroup of 1024 threads.
+// The sort of one head by ONE workgroup of 1024 threads (sort.hip), and the bins both of its sorts use.
 #pragma once
 #include "common.h"
 
 namespace adac {
 
-static constexpr int SEG = 512;      // items per wave step of the label sort
+static constexpr int SEG = 256;      // items of a wave of the one-workgroup sort
 static constexpr int RBITS = 7;
 static constexpr int RBINS = 1 << RBITS;
-static constexpr int SMALL_SEGS = 32;   // the one-workgroup sort holds at most this many segments
+static constexpr int SMALL_SEGS = 16;                  // its waves
+static constexpr int SMALL_ITEMS = SMALL_SEGS * SEG;   // the most items it holds
 
 // Label -> bin: the labels 0..m-1, and m for every label outside of that range.
 __device__ __forceinline__ int label_bin(int l, int m) { return (int)min((uint32_t)l, (uint32_t)m); }
 
-// The whole sort of one head's n <= SMALL_SEGS * SEG labels in one workgroup (all 1024 threads must
+// The whole sort of one head's n <= SMALL_ITEMS labels in one workgroup (all 1024 threads must
 // call it): every radix pass, the label offsets offs[0..m] and, if poff is given, the part offsets
-// of the centroid reduction, which otherwise take five launches per pass of a few microseconds
-// each.  Same arithmetic and the same stable order as the multi-workgroup kernels: wave w takes
-// segments w and w+16 and holds their items in registers for the whole pass; the per-(segment,
+// of the centroid reduction.  The same stable order as the counting sort: wave w takes
+// segment w and holds its items in registers for the whole pass; the per-(segment,
 // digit) counts live in LDS.  All pointers are the head's own rows.  labels/vals_in are read,
 // lab_a/val_a are scratch, lab_b receives the sorted labels and perm the sorted values (vals_in
 // NULL: the item index).  Ends with every result written but NOT yet made visible to the other
@@ -28,7 +27,7 @@ __device__ __forceinline__ void sort_one_head(const int32_t* __restrict__ labels
                                               int32_t* __restrict__ perm_h, int32_t* __restrict__ of,
                                               int32_t* __restrict__ po, int part_rows) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  n = min(n, SMALL_SEGS * SEG);
+  n = min(n, SMALL_ITEMS);
   const int nseg = (n + SEG - 1) / SEG;
   __shared__ int32_t hist[SMALL_SEGS][RBINS];
   __shared__ int32_t gsum[8][RBINS];
@@ -43,26 +42,20 @@ __device__ __forceinline__ void sort_one_head(const int32_t* __restrict__ labels
     int32_t* vout = last ? perm_h : val_a_h;
     const int shift = ps * RBITS;
     for (int i = tid; i < nseg * RBINS; i += 1024) (&hist[0][0])[i] = 0;
-    // this wave's items of the pass, all loads in flight at once: segment wave + 16*i, item 64*k + lane
-    int lab[SMALL_SEGS / 16][SEG / 64], val[SMALL_SEGS / 16][SEG / 64];
+    // this wave's items of the pass, all loads in flight at once: item 64*k + lane of its segment
+    int lab[SEG / 64], val[SEG / 64];
 #pragma unroll
-    for (int i = 0; i < SMALL_SEGS / 16; ++i)
-#pragma unroll
-      for (int k = 0; k < SEG / 64; ++k) {
-        const int p = (wave + 16 * i) * SEG + 64 * k + lane;
-        lab[i][k] = p < n ? label_bin(lin[p], m) : 0;      // (a later pass reads bins: unchanged)
-        val[i][k] = p < n ? (vin ? vin[p] : p) : 0;
-      }
+    for (int k = 0; k < SEG / 64; ++k) {
+      const int p = wave * SEG + 64 * k + lane;
+      lab[k] = p < n ? label_bin(lin[p], m) : 0;           // (a later pass reads bins: unchanged)
+      val[k] = p < n ? (vin ? vin[p] : p) : 0;
+    }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < SMALL_SEGS / 16; ++i)
-#pragma unroll
-      for (int k = 0; k < SEG / 64; ++k) {
-        const int seg = wave + 16 * i, p = seg * SEG + 64 * k + lane;
-        if (p < n) atomicAdd(&hist[seg][(lab[i][k] >> shift) & (RBINS - 1)], 1);
-      }
+    for (int k = 0; k < SEG / 64; ++k)
+      if (wave * SEG + 64 * k + lane < n) atomicAdd(&hist[wave][(lab[k] >> shift) & (RBINS - 1)], 1);
     __syncthreads();
-    {   // exclusive scan, bins major, segments minor (as radix_scan)
+    {   // exclusive scan of the counts, bins major, segments minor: position of a segment's first item of a bin
       const int b = tid & (RBINS - 1), g = tid >> RBITS;
       const int per = (nseg + 7) / 8;
       const int s0 = min(nseg, g * per), s1 = min(nseg, s0 + per);
@@ -85,16 +78,12 @@ __device__ __forceinline__ void sort_one_head(const int32_t* __restrict__ labels
       for (int sg = s0; sg < s1; ++sg) hist[sg][b] += base;
     }
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < SMALL_SEGS / 16; ++i) {
-      const int seg = wave + 16 * i;
-      if (seg >= nseg) break;                        // wave-uniform
-      volatile int32_t* base = hist[seg];            // touched by this wave only, in program order
+    if (wave < nseg) {
+      volatile int32_t* base = hist[wave];           // touched by this wave only, in program order
 #pragma unroll
       for (int k = 0; k < SEG / 64; ++k) {
-        const int p = seg * SEG + 64 * k + lane;
-        const bool valid = p < n;
-        const int l = lab[i][k], v = val[i][k];
+        const bool valid = wave * SEG + 64 * k + lane < n;
+        const int l = lab[k], v = val[k];
         const int dig = (l >> shift) & (RBINS - 1);
         // lanes holding my digit: intersect, bit by bit, the ballots of lanes that agree with me
         uint64_t same = __ballot(valid);

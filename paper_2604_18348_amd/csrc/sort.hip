@@ -220,7 +220,7 @@ __global__ __launch_bounds__(CS_NT) void label_scatter(const int32_t* __restrict
 
 // One workgroup per head: see sort_one_head.
 __global__ __launch_bounds__(1024) void sort_small(const int32_t* __restrict__ labels, const int32_t* __restrict__ vals_in,
-                                                   int N, int passes, SortArgs a, const int32_t* __restrict__ m_dev,
+                                                   int N, int scratch, int passes, SortArgs a, const int32_t* __restrict__ m_dev,
                                                    int m_stride, int m_const, int32_t* __restrict__ lab_a,
                                                    int32_t* __restrict__ val_a, int32_t* __restrict__ lab_b,
                                                    int32_t* __restrict__ perm, int32_t* __restrict__ offs,
@@ -229,13 +229,14 @@ __global__ __launch_bounds__(1024) void sort_small(const int32_t* __restrict__ l
   if (a.active_dev && !a.active_dev[(size_t)h * a.active_stride]) return;
   const int n = head_items(a, h);
   const int m = label_limit(m_dev, m_stride, m_const, h);
-  const size_t o = (size_t)h * N;
-  sort_one_head(labels + o, vals_in ? vals_in + o : nullptr, n, passes, m, lab_a + o, val_a + o, lab_b + o, perm + o,
+  const size_t o = (size_t)h * N, so = (size_t)h * scratch;
+  sort_one_head(labels + o, vals_in ? vals_in + o : nullptr, n, passes, m, lab_a + so, val_a + so, lab_b + so, perm + o,
                 offs + (size_t)h * offs_stride, poff ? poff + (size_t)h * offs_stride : nullptr, part_rows);
 }
 
 int sort_segments(int N) { return (N + CS_ITEMS - 1) / CS_ITEMS; }
-size_t sort_table_ints(int N, int m) { return (size_t)(sort_segments(N) + 1) * ((m + 1 + 63) / 64 * 64); }
+size_t sort_table_ints(int N, int m) { return N <= SMALL_ITEMS ? 0 : (size_t)(sort_segments(N) + 1) * ((m + 1 + 63) / 64 * 64); }
+int sort_scratch_ints(int N) { return min(N, SMALL_ITEMS); }
 
 int launch_sort(hipStream_t st, int H, int N, int n_bound, int m_bound,
                 const int32_t* labels, const int32_t* ulist,
@@ -245,15 +246,11 @@ int launch_sort(hipStream_t st, int H, int N, int n_bound, int m_bound,
                 int part_rows, int32_t* pcl, int P, int* poff_done, int foreign) {
   SortArgs a{n_dev, n_stride, n_bound, active_dev, active_stride};
   if (poff_done) *poff_done = 0;
-#ifndef SORT_SMALL_LIMIT
-#define SORT_SMALL_LIMIT 8
-#endif
-  static_assert(SORT_SMALL_LIMIT <= SMALL_SEGS, "the one-workgroup sort holds SMALL_SEGS segments");
-  if (n_bound <= SORT_SMALL_LIMIT * SEG) {
+  if (n_bound <= SMALL_ITEMS) {
     int bits = 1;
     while ((1 << bits) < m_bound + (foreign ? 1 : 0)) ++bits;       // (the digits of the last bin too)
     const int passes = (bits + RBITS - 1) / RBITS;
-    sort_small<<<H, 1024, 0, st>>>(labels, ulist, N, passes, a, m_dev, m_stride, m_bound, sc.lab_a, sc.val_a, sc.lab_b,
+    sort_small<<<H, 1024, 0, st>>>(labels, ulist, N, sort_scratch_ints(N), passes, a, m_dev, m_stride, m_bound, sc.lab_a, sc.val_a, sc.lab_b,
                                    perm, offs, offs_stride, poff, part_rows);
     if (poff_done && poff) *poff_done = 1;
     return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;

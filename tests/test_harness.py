@@ -11,7 +11,7 @@ def test_label_sort_bytes_are_those_of_the_sort_in_the_library():
     sort = open(os.path.join(CSRC, "sort.hip")).read()
     head = open(os.path.join(CSRC, "small_head.h")).read()
     number = lambda name, text: int(re.search(r"\b%s(?: =)? (\d+)" % name, text).group(1))  # noqa: E731
-    assert harness.SORT_ONE_WORKGROUP == number("SORT_SMALL_LIMIT", sort) * number("SEG", head)
+    assert harness.SORT_ONE_WORKGROUP == number("SMALL_SEGS", head) * number("SEG", head)
     assert harness.SORT_SEGMENT == number("CS_ITEMS", sort)
     assert number("RBITS", head) == 7
     # labels read twice and the permutation written once, and the table of 37 x 66 counts six times
