@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the clustered sparse-attention call on one MI355X.
 
-A step is one adacluster_attn call (query clustering, Algorithm 1, selection, permutation, block-sparse
+A step is one adacluster_attn call (query clustering, Algorithm 1, selection, planning, block-sparse
 attention) over one synthetic Q/K/V batch, inputs resident in HBM.  The default workload is the largest
 configuration (config 5: 180 000 tokens, 24 heads of width 128).  Prints ONE JSON line: the call's latency,
 its stage times, the dense call beside it, the attention kernel against the bf16 MFMA peak (useful and issued

@@ -338,7 +338,7 @@ int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   const int P = parts_for(D.N, D.Cq);
   int poff_done = 0;   // set when the sort has already cut the clusters into reduction parts
   const int sph = p->q_no_norm ? 0 : 1;      // by angle on q/|q| (the paper), or Euclidean on raw queries (ablation)
-  RET_IF(launch_init_centroids(st, p->dtype, D.d, D.H, D.N, 0, D.Cq, D.Cq, nullptr, nullptr, sph, p->q_init_mode,
+  RET_IF(launch_init_centroids(st, p->dtype, D.d, D.H, D.N, 0, D.Cq, D.Cq, nullptr, sph, p->q_init_mode,
                                D.Cq, D.Cq, Q, q_centroids, w.q_cent_lp, q_assign, w.q_bias));
   // A pass that only updates the centres reads the queries once: assignment and (normalised) sums in one
   // kernel.  The last pass needs the labels sorted (for the attention step) and exact member statistics, and
@@ -387,7 +387,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     // warm start: one pseudo-stage over all tokens with the previous centres, count fixed
     RET_IF(launch_kstate_warm(st, w.kstate, D.H, D.N, D.cap, k_count, full_flag));
     if (k_stage_of) RET_IF(launch_fill_i32(st, k_stage_of, (size_t)D.H * D.N, 0));
-    RET_IF(launch_init_centroids(st, p->dtype, D.d, D.H, D.N, 1, 0, D.cap, w.kstate, nullptr, 0, 1, D.cap, D.cap, K,
+    RET_IF(launch_init_centroids(st, p->dtype, D.d, D.H, D.N, 1, 0, D.cap, w.kstate, 0, 1, D.cap, D.cap, K,
                                  k_centroids, w.cent_lp, k_assign, w.bias));
     const int Pw = parts_for(D.N, D.cap);
     for (int it = 0; it < p->k_iters; ++it) {
@@ -446,7 +446,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                     m_bound <= assign_block_sum_centres())) {
       // Stage 0 removes most points, so its figures (all N points, m_0 centres) are poor bounds for
       // stage 1: unless they still allow the short update (block sums), they would send a few thousand
-      // points through the launch chain sized for all of them (two radix passes, segmented
+      // points through the launch chain sized for all of them (label sort, segmented
       // reduction).  Then, once per call, the host waits for the report of the stage it is about to
       // enqueue; the other stream keeps the device busy meanwhile.
       if (!stage_report_landed(*rb, 1, st))

@@ -1031,23 +1031,23 @@ __global__ __launch_bounds__(256) void update_direct_f32(const float* __restrict
   if (cl == 0) bias[(size_t)h * cap + row_off + j] = -0.5f * bsum;
 }
 
-// Initial centres: strided sample of the current point list (or the rows of `master` as given).
-//   source_master = 1: master already holds the centres (warm start)
+// Initial centres of the query clustering, a strided sample of all points, or (source_master = 1, warm starts of either
+// side) the rows that `master` holds.  Mode 1: centre counts and rows from the state.  (A stage of Algorithm 1 takes its
+// sample in stage_open.)
 template <typename T, int D>
 __global__ __launch_bounds__(64) void init_centroids(const T* __restrict__ X, int N, int mode, int m_const,
-                                                     const KState* __restrict__ st,
-                                                     const int32_t* __restrict__ ulist, int spherical,
+                                                     const KState* __restrict__ st, int spherical,
                                                      int source_master, int cap, int master_stride,
                                                      int lp_is_bf16, float* __restrict__ master,
                                                      void* __restrict__ assign_lp, float* __restrict__ assign_f32,
                                                      float* __restrict__ bias) {
   constexpr int CPL = D / 64;
   const int h = blockIdx.y, j = blockIdx.x, lane = threadIdx.x;
-  int n = N, m = m_const, row_off = 0;
+  int m = m_const, row_off = 0;
   if (mode == 1) {
     const KState& s = st[h];
     if (!s.active) return;
-    n = s.ucount; m = s.m_t; row_off = s.ccount;
+    m = s.m_t; row_off = s.ccount;
   }
   if (j >= m) return;
   float val[CPL];
@@ -1055,8 +1055,7 @@ __global__ __launch_bounds__(64) void init_centroids(const T* __restrict__ X, in
 #pragma unroll
     for (int q = 0; q < CPL; ++q) val[q] = master[((size_t)h * master_stride + j) * D + lane + 64 * q];
   } else {
-    const long long pos = ((2ll * j + 1) * (long long)n) / (2ll * m);
-    const int tok = ulist ? ulist[(size_t)h * N + pos] : (int)pos;
+    const long long tok = ((2ll * j + 1) * (long long)N) / (2ll * m);
     const T* row = X + ((size_t)h * N + tok) * D;
 #pragma unroll
     for (int q = 0; q < CPL; ++q) val[q] = Elem<T>::load(row + lane + 64 * q);
@@ -1379,7 +1378,7 @@ __global__ __launch_bounds__(256) void stage_open(const T* __restrict__ X, OpenC
 // The late stages of Algorithm 1 in one launch.
 // ------------------------------------------------------------------------------------------
 // Once every head has few unassigned points left (|U| <= SMALL_NU) and at most SMALL_M centres per
-// stage, a stage is eight launches of a few microseconds each with next to no work in them, and
+// stage, a stage is six launches of a few microseconds each with next to no work in them, and
 // Algorithm 1 may run ten such stages.  Heads are independent, so here ONE workgroup per head runs
 // every remaining stage from the loop head to the threshold filter: strided initial sample, `iters`
 // assignment passes with the centre update in between, filter and compaction of U, stage
@@ -1463,7 +1462,7 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
     int32_t* uout = cfg.ulist[(stage + 1) & 1] + (size_t)h * cfg.N;
     const bf16raw* Xh = X + (size_t)h * cfg.N * D;
 
-    // initial centres: strided sample of U (as init_centroids); rows past m are zero with a bias that never wins
+    // initial centres: strided sample of U (as stage_open); rows past m are zero with a bias that never wins
     if (tid < SMALL_M) cnt_s[tid] = 0;
     for (int j = wave; j < SMALL_M; j += NW) {
       if (j < m) {
@@ -1693,7 +1692,7 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
       __syncthreads();
     }
 
-    // threshold filter: points with d < tau leave U; U stays ascending (as filter_small)
+    // threshold filter: points with d < tau leave U; U stays ascending (as in stage_open)
     __syncthreads();
     int run = 0;
     for (int base = 0; base < n; base += 4 * NT) {
@@ -1905,17 +1904,17 @@ int launch_update_direct(hipStream_t s, int d, int H, int N, int m_bound, int ca
 }
 
 int launch_init_centroids(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound,
-                          const KState* st, const int32_t* ulist, int spherical, int source_master, int cap,
+                          const KState* st, int spherical, int source_master, int cap,
                           int master_stride, const void* X, float* master, void* assign_lp, float* assign_f32,
                           float* bias) {
   dim3 g(m_bound, H);
   const int lp = dtype == ADACLUSTER_BF16;
   if (dtype == ADACLUSTER_BF16) {
-    if (d == 64) init_centroids<bf16raw, 64><<<g, 64, 0, s>>>((const bf16raw*)X, N, mode, m_const, st, ulist, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
-    else init_centroids<bf16raw, 128><<<g, 64, 0, s>>>((const bf16raw*)X, N, mode, m_const, st, ulist, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
+    if (d == 64) init_centroids<bf16raw, 64><<<g, 64, 0, s>>>((const bf16raw*)X, N, mode, m_const, st, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
+    else init_centroids<bf16raw, 128><<<g, 64, 0, s>>>((const bf16raw*)X, N, mode, m_const, st, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
   } else {
-    if (d == 64) init_centroids<float, 64><<<g, 64, 0, s>>>((const float*)X, N, mode, m_const, st, ulist, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
-    else init_centroids<float, 128><<<g, 64, 0, s>>>((const float*)X, N, mode, m_const, st, ulist, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
+    if (d == 64) init_centroids<float, 64><<<g, 64, 0, s>>>((const float*)X, N, mode, m_const, st, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
+    else init_centroids<float, 128><<<g, 64, 0, s>>>((const float*)X, N, mode, m_const, st, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
   }
   return chk();
 }

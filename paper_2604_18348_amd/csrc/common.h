@@ -79,7 +79,7 @@ struct KState {
   int32_t stage;       // t
   int32_t done;        // the stage loop has ended for this head
   int32_t full;        // F
-  int32_t active;      // this stage runs (set by stage_begin)
+  int32_t active;      // this stage runs (set by stage_open)
   int32_t pad;
   int32_t stage_offs[ADACLUSTER_MAX_STAGES + 1];
   int32_t u_hist[ADACLUSTER_MAX_STAGES + 1];   // |U| at the head of stage t; entry `stage` = what staging left over

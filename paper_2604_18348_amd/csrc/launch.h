@@ -62,7 +62,7 @@ int qpass_walks(int N);
 int launch_qpass(hipStream_t s, int d, int H, int N, int m, int cap, int weighted, const void* X, const void* cent_lp,
                  const float* bias, float* psum, int32_t* pcnt);
 int launch_init_centroids(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound,
-                          const KState* st, const int32_t* ulist, int spherical, int source_master, int cap,
+                          const KState* st, int spherical, int source_master, int cap,
                           int master_stride, const void* X, float* master, void* assign_lp, float* assign_f32,
                           float* bias);
 int launch_kstate_warm(hipStream_t s, KState* st, int H, int N, int cap, const int32_t* k_count, const int32_t* full_flag);

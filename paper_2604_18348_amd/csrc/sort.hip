@@ -3,8 +3,7 @@
 // The permutation that groups tokens by cluster label is what makes the centroid
 // reduction atomic-free and the K/V gathers cluster-contiguous.  It must be
 // deterministic, so ranks inside a segment are taken in item order (wave-wide
-// match on the digit, never "who won the atomic").  All passes are bound by HBM
-// traffic of 4-byte labels and indices.
+// match on the label or digit, never "who won the atomic").
 #include "common.h"
 #include "launch.h"
 #include "small_head.h"

@@ -274,8 +274,9 @@ def test_kcluster_fp32_direct_update_scans_in_rounds():
 
 
 def test_kcluster_more_than_128_stage_centres():
-    """Stage centre counts above 128 need two radix passes of the label sort, here inside the
-    one-workgroup-per-head kernels (small heads)."""
+    """Stage centre counts above 128 are updated from sorted labels: the counting sort with its table of the
+    reduction parts' clusters in the first stage and at the end, two radix passes of the one-workgroup sort in stages of
+    up to 4 096 points."""
     H, N, d = 2, 6144, 64
     _, K, _ = wl.make_small(23, N, d, 48, dtype="bf16", H=H)
     p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=8, k_iters=3, k_m0=160, k_m_min=8, k_max_clusters=480,
