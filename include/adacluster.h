@@ -211,7 +211,7 @@ typedef struct adacluster_head_stats {
   int32_t k_count;        /* |C|: key centres Algorithm 1 ended with                                   */
   int32_t full_flag;      /* F                                                                         */
   int32_t stages;         /* stages of Algorithm 1 that ran (1 for a warm start)                       */
-  int32_t q_tiles;        /* workgroups of the attention launch (query tiles, cut key lists counted per chunk) */
+  int32_t q_tiles;        /* query tiles of the attention launch (cut key lists counted per chunk; fp32: per 64 rows) */
   int32_t unassigned[ADACLUSTER_MAX_STAGES + 1]; /* |U| at the head of stage t for t < stages; entry
                              [stages] = keys still beyond tau of every centre when staging stopped      */
   int32_t reserved;

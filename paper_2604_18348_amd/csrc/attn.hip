@@ -21,6 +21,7 @@ static constexpr int TILE_REC = 8;       // ints per query-tile record (32 bytes
 static constexpr int SPLIT_SLOTS = 128;  // partial slots per head for the chunks of cut key lists
 static constexpr int F32_WAVES = 4;      // waves of a workgroup of the fp32 kernel
 static constexpr int F32_MAX_SPLITS = 4; // most workgroups the fp32 kernel splits a key list over
+static constexpr float PART_DONE = -1.f; // in place of the sum of a row's first partial result: the row is written
 static constexpr int KROW_PAD = 8 * 64;  // entries of the row-offset table a key list is padded by: the kernel reads up to 7 tiles ahead
 
 // ------------------------------------------------------------------------------------------
@@ -30,7 +31,7 @@ static constexpr int KROW_PAD = 8 * 64;  // entries of the row-offset table a ke
 // rng_pre   [H][Cq][maxr+1] keys before range r in the concatenation (last = total)
 // rng_cnt   [H][Cq]
 // tiles     [H][maxtiles] x {cluster, first sorted query position, rows, first key tile, end key
-//           tile, partial slot or -1, keys of the cluster's whole list, 0}; ntiles [H]
+//           tile, partial slot or -1, keys of the cluster's whole list, not 0: the second 32 rows of 64 (fp32)}; ntiles [H]
 __global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, int row_scale,
                             const int32_t* __restrict__ k_offs, int k_offs_stride,
                             const int32_t* __restrict__ k_count,
@@ -163,7 +164,7 @@ __global__ __launch_bounds__(256) void plan_tiles(int Cq, int maxr, int maxtiles
   const int per = (C + 255) / 256, c0 = min(C, tid * per), c1 = min(C, c0 + per), lane = tid & 63, wave = tid >> 6;
   __shared__ long long w_work[4];
   __shared__ int32_t w_a[4], w_b[4];
-  __shared__ int32_t s_cut, s_list[MAXC];
+  __shared__ int32_t s_cut, s_ntiles, s_list[MAXC];
   auto wave_prefix = [&](int v) __attribute__((always_inline)) {
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) { const int u = __shfl_up(v, o); if (lane >= o) v += u; }
@@ -219,28 +220,24 @@ __global__ __launch_bounds__(256) void plan_tiles(int Cq, int maxr, int maxtiles
     int nt = incl - mine;
     for (int w = 0; w < wave; ++w) nt += w_a[w];
     for (int c = c0; c < c1; ++c) { s_tile0[c] = nt; nt += s_nq[c] * s_pieces[c]; }
-    if (tid == 255) ntiles[h] = nt;
+    if (tid == 255) { ntiles[h] = nt; s_ntiles = nt; }
   }
   __syncthreads();
-  // records of every cluster, one thread per cluster
-  for (int c = tid; c < C; c += 256) {
-    const int s0 = qo[c], e0 = qo[c + 1], T = s_T[c], pieces = s_pieces[c];
-    const int per = (T + pieces - 1) / pieces;
-    int nt = s_tile0[c], slot = pieces > 1 ? s_slot0[c] : 0, nm = pieces > 1 ? s_merge0[c] : 0;
-    for (int r0 = s0; r0 < e0; r0 += BM) {
-      const int rows = min(BM, e0 - r0);
-      if (pieces > 1) {
-        ml[nm * 4 + 0] = r0; ml[nm * 4 + 1] = rows; ml[nm * 4 + 2] = slot; ml[nm * 4 + 3] = pieces;
-        ++nm;
-      }
-      for (int k = 0; k < pieces; ++k) {
-        int32_t* t6 = tl + (size_t)nt * TILE_REC;
-        t6[0] = c; t6[1] = r0; t6[2] = rows;
-        t6[3] = pieces > 1 ? k * per : 0; t6[4] = pieces > 1 ? min(T, (k + 1) * per) : T;
-        t6[5] = pieces > 1 ? slot + k : -1; t6[6] = s_tot[c]; t6[7] = 0;
-        ++nt;
-      }
-      if (pieces > 1) slot += pieces;
+  // The records, one a thread: the last cluster whose records start at or before it (an empty one shares its start with
+  // the next).  One thread per cluster wrote 625 records one after the other where 20 000 rows are a single cluster.
+  for (int t = tid; t < s_ntiles; t += 256) {
+    int c = 0, hi = C - 1;
+    while (c < hi) { const int mid = (c + hi + 1) >> 1; if (s_tile0[mid] <= t) c = mid; else hi = mid - 1; }
+    const int i = t - s_tile0[c], T = s_T[c], pieces = s_pieces[c], per_piece = (T + pieces - 1) / pieces;
+    const int group = i / pieces, k = i - group * pieces;                    // rows group * BM .. of the cluster, chunk k
+    const int r0 = qo[c] + group * BM, rows = min(BM, qo[c + 1] - r0);
+    int32_t* t6 = tl + (size_t)t * TILE_REC;
+    t6[0] = c; t6[1] = r0; t6[2] = rows;
+    t6[3] = pieces > 1 ? k * per_piece : 0; t6[4] = pieces > 1 ? min(T, (k + 1) * per_piece) : T;
+    t6[5] = pieces > 1 ? s_slot0[c] + i : -1; t6[6] = s_tot[c]; t6[7] = (group * BM) & 63;
+    if (pieces > 1 && k == 0) {
+      int32_t* m = ml + (size_t)(s_merge0[c] + group) * 4;
+      m[0] = r0; m[1] = rows; m[2] = s_slot0[c] + i; m[3] = pieces;
     }
   }
 }
@@ -266,7 +263,7 @@ __global__ void plan_dense(int N, int maxtiles, int BM, int row_scale, int32_t* 
   int32_t* tl = tiles + (size_t)h * maxtiles * TILE_REC;
   for (int t = threadIdx.x; t * BM < N; t += blockDim.x) {
     int32_t* t6 = tl + (size_t)t * TILE_REC;
-    t6[0] = 0; t6[1] = t * BM; t6[2] = min(BM, N - t * BM); t6[3] = 0; t6[4] = (N + 63) / 64; t6[5] = -1; t6[6] = N; t6[7] = 0;
+    t6[0] = 0; t6[1] = t * BM; t6[2] = min(BM, N - t * BM); t6[3] = 0; t6[4] = (N + 63) / 64; t6[5] = -1; t6[6] = N; t6[7] = (t * BM) & 63;
   }
 }
 
@@ -282,6 +279,7 @@ __global__ __launch_bounds__(256) void attn_stats(int Cq, int maxr, int maxtiles
   const int nt = min(ntiles[h], maxtiles);
   const int32_t* tl = tiles + (size_t)h * maxtiles * TILE_REC;
   long long ex = 0, is = 0;
+  int whole = 0;                          // (fp32 tiles are counted per 64 rows)
   for (int t = tid; t < nt; t += 256) {
     const int32_t* t6 = tl + (size_t)t * TILE_REC;
     const int c = t6[0], rows = t6[2], kt0 = t6[3], kt1 = t6[4];
@@ -289,18 +287,20 @@ __global__ __launch_bounds__(256) void attn_stats(int Cq, int maxr, int maxtiles
     const long long keys = max(0, min(total, kt1 * 64) - kt0 * 64);
     ex += (long long)rows * keys;
     is += (long long)((rows + 31) / 32 * 32) * ((keys + 63) / 64 * 64);
+    whole += t6[7] == 0;
   }
   __shared__ long long s_ex[256], s_is[256];
-  s_ex[tid] = ex; s_is[tid] = is;
+  __shared__ int s_nt[256];
+  s_ex[tid] = ex; s_is[tid] = is; s_nt[tid] = whole;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
-    if (tid < o) { s_ex[tid] += s_ex[tid + o]; s_is[tid] += s_is[tid + o]; }
+    if (tid < o) { s_ex[tid] += s_ex[tid + o]; s_is[tid] += s_is[tid + o]; s_nt[tid] += s_nt[tid + o]; }
     __syncthreads();
   }
   if (tid == 0) {
     adacluster_head_stats r;
     const KState& k = st[h];
-    r.k_count = k.ccount; r.full_flag = k.full; r.stages = k.stage; r.q_tiles = nt;
+    r.k_count = k.ccount; r.full_flag = k.full; r.stages = k.stage; r.q_tiles = s_nt[0];
     for (int i = 0; i <= ADACLUSTER_MAX_STAGES; ++i) r.unassigned[i] = i <= k.stage ? k.u_hist[i] : 0;
     r.reserved = 0;
     r.executed_pairs = s_ex[0]; r.issued_pairs = s_is[0];
@@ -332,33 +332,40 @@ struct AttnArgs {
 // each with its own L2, so XCD = blockIdx.x % 8 and blockIdx.x / 8 is a slot in that XCD's own list of tiles: of every
 // head, in head order, the XCD takes a contiguous eighth (the tiles of one query cluster stream the same K/V rows, and so
 // do it behind the same L2).
-// Only the device knows how many tiles a head has.  Up to PICK_HEADS heads the list is cut from those counts here, a lane
-// per head, so that the workgroups without work are the last of the grid.  (With a grid row per head, sized for the most
-// tiles a head could have, more than half of the workgroups were empty ones between the heads, and each takes its turn on
-// a CU.)  More heads fill the chip anyway and have a grid row each: searched 64 at a time, a workgroup's head costs a trip
-// to memory per 64 heads (fp32 calls of 256 x 512 rows 203 us by rows, 260 by search, 1 024 x 128 825 and 1 625 us,
-// 4 096 x 256, d=128, 4.41 and 6.87 ms; 70 and 128 x 1 024 within 2 %), and past 2^32 threads the grid dimension ends.
-// `parts`: workgroups per tile.  Returns false where the list has ended.
-constexpr int PICK_HEADS = 64;
-__device__ __forceinline__ bool pick_tile(const int32_t* __restrict__ ntiles, int H, int parts, int& h, int& tile) {
+// Only the device knows how many tiles a head has.  Up to PICK_HEADS heads the list is cut from those counts here, so that
+// the workgroups without work are the last of the grid.  (With a grid row per head, sized for the most tiles a head
+// could have, there are empty ones between the heads, and each takes its turn on a CU.)  More heads have a grid row each:
+// the search costs a trip to memory per 64 heads, and past 2^32 threads a grid dimension ends.  Calls of 70, 150 and 256
+// heads of 2 000 rows, d=64, 33 clusters 288, 579 and 975 us by search, 331, 664 and 1 107 by rows; of 1 000 rows and 200 clusters
+// 228, 456, 802 and 216, 417, 704; 1 024 heads of 128 rows 718 by rows (by search, when tiles were 64 rows, 1 625).
+// Returns false where the list has ended.
+constexpr int PICK_HEADS = 256;
+__device__ __forceinline__ bool pick_tile(const int32_t* __restrict__ ntiles, int H, int& h, int& tile) {
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, lane = threadIdx.x & 63;
   if (H > PICK_HEADS) {
     h = blockIdx.y;
-    const int nt = parts * ntiles[h], w = (nt + 7) >> 3;
+    const int nt = ntiles[h], w = (nt + 7) >> 3;
     tile = xcd * w + slot;
     return slot < w && tile < nt;
   }
-  const int nt = lane < H ? parts * ntiles[lane] : 0;
-  const int w = (nt + 7) >> 3;                             // this XCD's share of the head (the last XCD's may be short)
-  int incl = w;
+  int base = 0;
+  for (int h0 = 0; h0 < H; h0 += 64) {                     // 64 heads at a time, one per lane
+    const int nt = h0 + lane < H ? ntiles[h0 + lane] : 0;
+    const int w = (nt + 7) >> 3;                           // this XCD's share of the head (the last XCD's may be short)
+    int incl = w;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
-  const uint64_t past = __ballot(incl > slot);
-  if (!past) return false;
-  h = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)past) - 1);
-  const int wl = __builtin_amdgcn_readlane(w, h);
-  tile = xcd * wl + slot - __builtin_amdgcn_readlane(incl, h) + wl;
-  return tile < __builtin_amdgcn_readlane(nt, h);
+    for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
+    const uint64_t past = __ballot(base + incl > slot);
+    if (past) {
+      const int l = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)past) - 1);
+      const int wl = __builtin_amdgcn_readlane(w, l);
+      h = h0 + l;
+      tile = xcd * wl + slot - base - __builtin_amdgcn_readlane(incl, l) + wl;
+      return tile < __builtin_amdgcn_readlane(nt, l);
+    }
+    base += __builtin_amdgcn_readlane(incl, 63);
+  }
+  return false;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -772,7 +779,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
 // fp32 kernel (the accuracy path of fp32 inputs): the same S^T = K Q^T / O^T += V^T P^T walk on the
 // matrix cores with v_mfma_f32_32x32x2_f32 (fp32 products, fp32 accumulation)
 // ------------------------------------------------------------------------------------------
-// A workgroup is half a query tile, 32 queries; its four waves take every fourth 32-key tile of the key list, each
+// A workgroup is a query tile of 32 queries; its four waves take every fourth 32-key tile of the key list, each
 // with an accumulator and soft-max state of its own, and meet once at the end.  In the 32x32 accumulator a lane
 // (c = lane % 32, hb = lane / 32) owns query c and the keys 8*(v/4) + 4*hb + v%4 of the tile, v = 0..15.  The
 // two values a lane pair supplies per product step may be any pair of the contraction index as long as both
@@ -786,8 +793,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
 // Slot s (16 bytes) of row r holds piece s ^ (r & 15): the operand reads of 16 consecutive rows hit 16 bank groups.
 // What bounds the path: the fp32 matrix rate (a product of 32x32x2 holds the pipe for 64 cycles) once there are
 // workgroups enough, which is why the key list is split: over the waves, and where the launch is small (4 096
-// queries are 128 half tiles for 256 CUs) over gridDim.z workgroups as well, which leave unnormalised partial results
-// that attn_merge_f32 combines (see attn_f32_splits).  Vector instructions do not run under an fp32 product on this chip
+// queries are 128 tiles for 256 CUs) over gridDim.z workgroups as well, which leave unnormalised partial results
+// that attn_merge_f32 combines (see attn_f32_splits), lists too short for that aside.  Vector instructions do not run under an fp32 product on this chip
 // (the co-execution counter reads 0), so every one of them adds its four cycles: the masks are for the last tile
 // only, the accumulator is rescaled only when the maximum has moved, and addresses inside a head are 32-bit offsets.
 // Without these the 545 vector instructions a tile took a fifth of the time.
@@ -800,14 +807,17 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
 template <int D, bool LISTED>
 __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
   constexpr int BN = 32, DB = D / 32, NW = F32_WAVES, SROW = D + 4, PPR = D / 4, RPI = 64 / PPR;   // 16-byte pieces a row, rows a load
-  int h, tile;                                             // (tile: half of a 64-query tile)
-  if (!pick_tile(a.ntiles, a.H, 2, h, tile)) return;
-  const int32_t* tl = a.tiles + ((size_t)h * a.maxtiles + (tile >> 1)) * TILE_REC;   // (key lists are never cut for fp32)
-  const int qc = tl[0], row0 = tl[1] + (tile & 1) * 32, nrows = min(tl[2] - (tile & 1) * 32, 32);
-  if (nrows <= 0) return;
+  int h, tile;
+  if (!pick_tile(a.ntiles, a.H, h, tile)) return;
+  const int32_t* tl = a.tiles + ((size_t)h * a.maxtiles + tile) * TILE_REC;          // (key lists are never cut for fp32)
+  const int qc = tl[0], row0 = tl[1], nrows = tl[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, hb = lane >> 5;
   const int total = tl[6], T = (total + BN - 1) / BN;
+  // The workgroups that share this list: not more than its tiles give work to (the launch only knows the most), the
+  // others end here.  A list of a single one is written out by it.
+  const int z = blockIdx.z, splits = min((int)gridDim.z, max(1, (T + NW - 1) / NW));
+  if (z >= splits) return;
   const int32_t* kr = a.krow + ((size_t)h * a.Cq + qc) * a.kstride;           // key rows of the list, in order
   const float* Qh = (const float*)a.Q + (size_t)h * a.N * D;
   const char* Kh = (const char*)((const float*)a.K + (size_t)h * a.N * D);
@@ -859,7 +869,7 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
     return a.perm_k ? a.perm_k[(size_t)h * a.N + row] : row;
   };
   // (the table is padded: entries past the list are rows that exist, and masked)
-  const int t0 = blockIdx.z * NW + wave, tstep = gridDim.z * NW;
+  const int t0 = z * NW + wave, tstep = splits * NW;
   int kidx = 0;
   if (t0 < T) { kidx = key_row(t0); issue_k(kidx); }
   float q[D / 2];
@@ -997,14 +1007,23 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
     wt[w] = M > -INFINITY ? exp2f(sm[w][r] - M) : 0.f;
     L = fmaf(wt[w], sl[w][r], L);
   }
-  if (!(M > -INFINITY) && total > 0) L = NAN;
-  float inv = L > 0.f ? 1.0f / L : L;
-  float* out = (float*)a.O + ((size_t)h * a.N + (pq ? pq[row0 + r] : row0 + r)) * D;
-  if (gridDim.z > 1) {                                     // a partial result: as it is, with its reference and sum
-    const size_t pr = ((size_t)h * gridDim.z + blockIdx.z) * a.N + row0 + r;
+  float inv, *out;
+  const size_t pr = ((size_t)h * gridDim.z + z) * a.N + row0 + r;
+  if (splits > 1) {                                        // a partial result: as it is, with its reference and sum
     inv = 1.f;
     out = a.part_o + pr * D;
-    if (col == 0) { a.part_ml[pr * 2] = M; a.part_ml[pr * 2 + 1] = L; }
+    if (col == 0) {
+      a.part_ml[pr * 2] = M; a.part_ml[pr * 2 + 1] = L;
+      if (z == 0)                                          // what the workgroups without work leave
+        for (int u = splits; u < (int)gridDim.z; ++u) {
+          a.part_ml[(pr + (size_t)u * a.N) * 2] = -INFINITY; a.part_ml[(pr + (size_t)u * a.N) * 2 + 1] = 0.f;
+        }
+    }
+  } else {
+    if (!(M > -INFINITY) && total > 0) L = NAN;
+    inv = L > 0.f ? 1.0f / L : L;
+    out = (float*)a.O + ((size_t)h * a.N + (pq ? pq[row0 + r] : row0 + r)) * D;
+    if (gridDim.z > 1 && col == 0) a.part_ml[pr * 2 + 1] = PART_DONE;
   }
 #pragma unroll
   for (int cc = 0; cc < D; cc += TPQ * 4) {
@@ -1018,12 +1037,14 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
   }
 }
 
-// The partial results of a row's `splits` workgroups: O = sum_z 2^(M_z - M) O_z / sum_z 2^(M_z - M) L_z.
+// The partial results of a row's up to `splits` workgroups: O = sum_z 2^(M_z - M) O_z / sum_z 2^(M_z - M) L_z.  Their list
+// has a key: NaN where no score is above -inf.
 template <int D>
 __global__ __launch_bounds__(256) void attn_merge_f32(AttnArgs a, int splits) {
   constexpr int LPR = D / 4;
   const int h = blockIdx.y, pos = blockIdx.x * (256 / LPR) + threadIdx.x / LPR, col = (threadIdx.x % LPR) * 4;
   if (pos >= a.N) return;
+  if (a.part_ml[((size_t)h * splits * a.N + pos) * 2 + 1] == PART_DONE) return;
   float M = -INFINITY, L = 0.f, ms[F32_MAX_SPLITS], ls[F32_MAX_SPLITS];
   float4 os[F32_MAX_SPLITS], x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1037,12 +1058,12 @@ __global__ __launch_bounds__(256) void attn_merge_f32(AttnArgs a, int splits) {
   for (int z = 0; z < F32_MAX_SPLITS; ++z) M = fmaxf(M, ms[z]);
 #pragma unroll
   for (int z = 0; z < F32_MAX_SPLITS; ++z) {
-    const float w = ms[z] > -INFINITY ? exp2f(ms[z] - M) : 0.f;
-    if (ms[z] > -INFINITY) L = fmaf(w, ls[z], L);
+    if (!(ms[z] > -INFINITY)) { if (z < splits) L += ls[z]; continue; }      // 0, or NaN for scores that are
+    const float w = exp2f(ms[z] - M);
+    L = fmaf(w, ls[z], L);
     x.x = fmaf(w, os[z].x, x.x); x.y = fmaf(w, os[z].y, x.y); x.z = fmaf(w, os[z].z, x.z); x.w = fmaf(w, os[z].w, x.w);
   }
-  if (!(M > -INFINITY)) L = ls[0];                         // 0 (empty list) or NaN, the same in every split
-  const float inv = L > 0.f ? 1.0f / L : L;
+  const float inv = L > 0.f ? 1.0f / L : NAN;
   const int tok = a.perm_q ? a.perm_q[(size_t)h * a.N + pos] : pos;
   *reinterpret_cast<float4*>((float*)a.O + ((size_t)h * a.N + tok) * D + col) = float4{x.x * inv, x.y * inv, x.z * inv, x.w * inv};
 }
@@ -1133,14 +1154,14 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a, const int32_t* __r
 // the first without long tails (a cluster of 273 queries is 256 + 17 in one shape, 128 + 128 + 17 in the other).
 static bool attn_small_shape(int N, int Cq) { return Cq > 1 && N / Cq < 768; }
 int attn_block_rows(int dtype, int d, int N, int Cq) {
-  if (dtype != ADACLUSTER_BF16) return 64;
+  if (dtype != ADACLUSTER_BF16) return 32;
   if (attn_small_shape(N, Cq)) return 128;
   return d == 64 ? A64_NW * 32 : A128_NW * 32;
 }
-int attn_block_rows_min(int dtype) { return dtype == ADACLUSTER_BF16 ? 128 : 64; }
-int attn_block_rows_max(int dtype) { return dtype == ADACLUSTER_BF16 ? 256 : 64; }
+int attn_block_rows_min(int dtype) { return dtype == ADACLUSTER_BF16 ? 128 : 32; }
+int attn_block_rows_max(int dtype) { return dtype == ADACLUSTER_BF16 ? 256 : 32; }
 
-// The launch of a kernel that takes its tiles by pick_tile: `most` bounds parts x tiles of a head.
+// The launch of a kernel that takes its tiles by pick_tile: `most` bounds the tiles of a head.
 static dim3 pick_tile_grid(int H, int most, int z) {
   const unsigned x = (most + 7) / 8 * 8;
   return H > PICK_HEADS ? dim3(x, H, z) : dim3(H * x, 1, z);
@@ -1216,7 +1237,7 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
     }
   } else {
     const int splits = attn_f32_splits(H, N, Cq);
-    const dim3 g2 = pick_tile_grid(H, 2 * (N / 64 + Cq + 1), splits), gm((N + 1024 / d - 1) / (1024 / d), H);
+    const dim3 g2 = pick_tile_grid(H, min(N, N / 32 + Cq + 1), splits), gm((N + 1024 / d - 1) / (1024 / d), H);
     if (d == 64) { if (krow) attn_f32<64, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<64, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
     else { if (krow) attn_f32<128, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<128, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
     if (splits > 1) {

@@ -242,7 +242,7 @@ def test_fp32_scores_of_minus_infinity_weigh_nothing(d, N, H):
 
 
 def test_fp32_more_workgroups_than_one_grid_dimension_takes():
-    """65 535 heads of 130 one-query clusters: 17.8 million workgroups of 256 threads, more than 2^32 threads.  (Past 64 heads
+    """65 535 heads of 130 one-query clusters: 17.8 million workgroups of 256 threads, more than 2^32 threads.  (Past 256 heads
     each has a grid row of its own.)"""
     H, N, d = 65535, 130, 64
     gen = torch.Generator(device="cuda")
@@ -259,10 +259,10 @@ def test_fp32_more_workgroups_than_one_grid_dimension_takes():
         assert float((O[h:h + 8192] - ref).abs().max()) < 1e-4
 
 
-@pytest.mark.parametrize("H,N,d,splits", [(64, 545, 64, 1), (65, 545, 128, 1), (45, 545, 64, 2), (21, 545, 128, 3), (5, 545, 64, 4)])
+@pytest.mark.parametrize("H,N,d,splits", [(64, 545, 64, 1), (65, 545, 128, 1), (256, 330, 64, 1), (257, 330, 128, 1), (45, 545, 64, 2), (21, 545, 128, 3), (5, 545, 64, 4)])
 def test_fp32_lists_whole_and_split_over_up_to_four_workgroups(H, N, d, splits):
     """A launch that fills the chip leaves key lists whole (the kernel writes the output itself), smaller ones split them over
-    two, three and four workgroups; 64 heads are dealt from the tile counts, 65 have a grid row each.  Sparse, with an empty
+    two, three and four workgroups; up to 256 heads are dealt from the tile counts, 64 at a time, more have a grid row each.  Sparse, with an empty
     list and an empty cluster, and dense; every output element is written."""
     Cq = 5
     for clusters in (Cq, 1):                       # (the dense call counts as one)
@@ -331,3 +331,28 @@ def test_fp32_head_of_more_than_4_gib():
     for n in range(0, N, 2 ** 20):
         P = torch.softmax(Q[0, n:n + 2 ** 20] @ K[0, at].T.contiguous() / d ** 0.5, 1)
         assert float((O[0, n:n + 2 ** 20] - P @ V[0, at]).abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_lists_shorter_than_their_split(d):
+    """Two heads have their lists split over up to four workgroups of four waves: lists of 1 to 17 key tiles of 32 keys, so that
+    one workgroup writes the row, or two, three or four leave parts (and the first stands in for the others), beside an empty
+    list, with the workspace full of NaN before the call."""
+    H, tiles = 2, [0, 1, 4, 5, 8, 9, 12, 13, 16, 17]
+    Cq, Ck, N = len(tiles), len(tiles), 32 * sum(tiles) - 40
+    rng = np.random.default_rng(71)
+    Q, K, V = (rng.standard_normal((H, N, d)).astype(np.float32) for _ in range(3))
+    sizes = [max(0, 32 * t - (5 if t < 9 else 0)) for t in tiles]
+    kl = np.repeat(np.arange(Ck), sizes)[:N]
+    kl = np.concatenate([kl, np.full(N - kl.size, 1)])
+    kl = np.stack([rng.permutation(kl) for _ in range(H)]).astype(np.int32)
+    ql = rng.integers(0, Cq, (H, N)).astype(np.int32)
+    sel = [[np.array([i], dtype=np.int64) for i in range(Cq)] for _ in range(H)]
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=Cq, k_m0=4, k_m_min=1, k_max_clusters=Ck)
+    si, sc = sel_to_dev(sel, Cq, p.cap)
+    ws = B.workspace(p)
+    ws.fill_(0xFF)
+    O = to_np(B.adacluster_sparse_attn(p, to_dev(Q, B.F32), to_dev(K, B.F32), to_dev(V, B.F32), torch.from_numpy(ql).cuda(),
+                                       torch.from_numpy(kl).cuda(), torch.full((H,), Ck, dtype=torch.int32, device="cuda"), si, sc, ws=ws))
+    for h in range(H):
+        check(O[h], orc.sparse_attention_gather(Q[h], K[h], V[h], ql[h], kl[h], sel[h]), B.F32)
