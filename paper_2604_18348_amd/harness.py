@@ -13,7 +13,6 @@ BF16_PEAK_TFLOPS = 2500.0      # MI355X dense bf16 MFMA, published
 FP32_VALU_PEAK_TFLOPS = 157.3  # MI355X fp32 vector, published
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 SORT_ONE_WORKGROUP = 4096      # items of a head that csrc/sort.hip sorts in one workgroup, at most
-SORT_SEGMENT = 2048            # items of a segment of its counting sort
 
 
 def device_inputs(name, aligned=False):
@@ -73,13 +72,13 @@ def _profiled(fn, B, reps):
     return {k: v / reps for k, v in acc.items()}
 
 
-def label_sort_bytes(n, labels, bound):
-    """Bytes that sorting one head's n labels (values below `labels`, the caller's bound `bound`) reads and writes."""
-    if n <= SORT_ONE_WORKGROUP:            # radix passes of 7 bits; one value more stands for labels out of range
-        passes = -(-bound.bit_length() // 7)
-        return (12 + 16 * (passes - 1)) * n                # the first pass reads no values
-    # Per segment and label: the count is written, read twice and replaced by its prefix, and read with the total.
-    return 12 * n + 4 * 6 * -(-n // SORT_SEGMENT) * (labels + 1)
+def label_sort_bytes(n, bound):
+    """Bytes that sorting one head's n labels (the caller's bound of their values is `bound`) cannot help but read and write.
+    The counts per segment and label, which the counting sort writes and reads besides, are left out: the caches hold them."""
+    if n > SORT_ONE_WORKGROUP:             # the labels twice, the permutation once
+        return 12 * n
+    passes = -(-bound.bit_length() // 7)   # radix passes of 7 bits; one value more stands for labels out of range
+    return (12 + 16 * (passes - 1)) * n    # (the first pass reads no values)
 
 
 def mfma_microbench_tflops(B, iters=20000):
@@ -191,13 +190,11 @@ def measure(name, steps, warmup, spinup_ms=500.0, dense_steps=3, profile_reps=No
             if ms_ and ms_ > 0:
                 gbs = nbytes / (ms_ * 1e-3) / 1e9
                 hbm[key] = {"ms": ms_, "bytes": nbytes, "GB/s": gbs, "frac": gbs / HBM_PEAK_GBS, "what": what}
-        sort_bytes = sum(label_sort_bytes(N, p.q_clusters, p.q_clusters) for _ in range(H)) + sum(
-            label_sort_bytes(N, s["k_count"], p.k_max_clusters + p.k_m0) for s in stats)
-        entry("label_sorts", pr.get("select"), float(sort_bytes),
+        entry("label_sorts", pr.get("select"),
+              float(H * (label_sort_bytes(N, p.q_clusters) + label_sort_bytes(N, p.k_max_clusters + p.k_m0))),
               "query labels and key labels, %s" % (
                   "one workgroup a head: labels and values of every radix pass read and written" if N <= SORT_ONE_WORKGROUP else
-                  "counting sort: per item 8 B of labels read and 4 B of the permutation written, and the counts of the "
-                  "%d-item segments as they are written and read (mostly out of the caches)" % SORT_SEGMENT))
+                  "counting sort: per item 8 B of labels read and 4 B of the permutation written"))
         entry("seg_reduce", t_red, rows * d * es + 4.0 * rows, "K rows and the permutation read once")
         out["hbm"] = hbm
     del Q, K, V, O, ws, outs
