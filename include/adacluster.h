@@ -172,6 +172,9 @@ int adacluster_select(const adacluster_params* p,
  *   Q,K,V [H,N,d] in;  q_labels,k_labels [H,N] in (values in [0,Cq) and [0,k_count[h]));
  *   k_count [H] in;  sel_idx [H,Cq,cap], sel_cnt [H,Cq] in (ascending, distinct);
  *   O [H,N,d] out, original token order.
+ * Outside of these ranges: a key whose label is not in [0,k_count[h]) is in no cluster, a query whose label is not
+ * in [0,Cq) has its row of O left as it is, a count above the capacity is taken as the capacity, entries of
+ * sel_idx that are no cluster are skipped, and a list that names clusters twice ends after N keys.
  */
 int adacluster_sparse_attn(const adacluster_params* p,
                            const void* Q, const void* K, const void* V,

@@ -800,12 +800,13 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
 // Without these the 545 vector instructions a tile took a fifth of the time.
 // LISTED: the key rows of a tile come from the table of the planning step, and a head has less than 4 GiB; else they are
 // searched in the ranges of the list, tile by tile, and offsets are 64-bit (attn_rows_listed says which).
-// Measured against a kernel of two waves of 32 queries a workgroup with K and V through LDS and three barriers a tile:
-// dense, d=128, 4 heads x 8 192 rows 71 -> 130 TFLOP/s (of 153 that an fp32 GEMM reaches), 1 x 4 096 9 -> 103; one head of
-// 4 096 queries (d=64) against a quarter of its keys 190 -> 33 us, three of 5 007 (d=128) against a third 533 -> 225 us.
-// (Eight waves a workgroup, one workgroup a CU: 37 and 237 us.)
+// Measured against a kernel of two waves of 32 queries a workgroup with K and V through LDS and three barriers a tile
+// (kernel and merge): dense, d=128, 4 heads x 8 192 rows 75 -> 125 TFLOP/s (of 154 that an fp32 GEMM reaches), 1 x 4 096
+// 10 -> 104; one head of 4 096 queries (d=64) against a quarter of its keys 132 -> 28 us, three of 5 007 (d=128) against a
+// third 405 -> 197 us, six of 5 000 (d=64) against 57 keys 23 -> 22 us.  (Eight waves a workgroup, one workgroup a CU: a sixth
+// slower at 4 096.)  At d=64 three workgroups a CU (168 registers; at 172 two: 150 heads of 1 000 rows 319 and 400 us).
 template <int D, bool LISTED>
-__global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
+__global__ __launch_bounds__(F32_WAVES * 64, D == 64 ? 3 : 2) void attn_f32(AttnArgs a) {
   constexpr int BN = 32, DB = D / 32, NW = F32_WAVES, SROW = D + 4, PPR = D / 4, RPI = 64 / PPR;   // 16-byte pieces a row, rows a load
   int h, tile;
   if (!pick_tile(a.ntiles, a.H, h, tile)) return;
@@ -887,7 +888,9 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  // The running maximum starts at a number no score lies below, and that stays one as an exponent of 2: relative to it a
+  // score of -inf is a probability of 0 (relative to -inf it would be NaN).
+  float m = -3.4028234e38f / fmaxf(1.f, a.scale_log2e), l = 0.f;
   for (int t = t0; t < T; t += tstep) {
     wait_vmcnt<0>();                                       // the K tile has landed
     asm volatile("" ::: "memory");
@@ -951,8 +954,7 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
     if (__any(tmax > m)) {
       const float mnew = fmaxf(m, tmax);
-      // (both -inf: no score of this query above -inf so far, and nothing to rescale)
-      const float alpha = mnew > m ? __builtin_amdgcn_exp2f((m - mnew) * a.scale_log2e) : 1.f;
+      const float alpha = __builtin_amdgcn_exp2f((m - mnew) * a.scale_log2e);
       m = mnew;
       l *= alpha;
 #pragma unroll
@@ -960,7 +962,7 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
     }
-    const float moff = m > -INFINITY ? m * a.scale_log2e : 0.f;
+    const float moff = m * a.scale_log2e;
     float lsum[2] = {0.f, 0.f};
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -991,7 +993,7 @@ __global__ __launch_bounds__(F32_WAVES * 64, 2) void attn_f32(AttnArgs a) {
     else *reinterpret_cast<float2*>(out) = float2{o[0][v], o[1][v]};
   }
   l += __shfl_xor(l, 32);
-  if (hb == 0) { sm[wave][c] = m * a.scale_log2e; sl[wave][c] = l; }
+  if (hb == 0) { sm[wave][c] = l > 0.f ? m * a.scale_log2e : -INFINITY; sl[wave][c] = l; }
   __syncthreads();
   // O = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w, 2 NW threads a query; a wave without a tile, or all of whose
   // scores are -inf, has m = -inf and l = 0.  An empty list gives zero, one whose every score is -inf NaN (as 0 / 0).
@@ -1184,10 +1186,10 @@ bool attn_rows_listed(int dtype, int d, int H, int N, int Cq) {
 int attn_tile_record() { return TILE_REC; }
 int attn_split_slots() { return SPLIT_SLOTS; }
 
-// Workgroups a key list of the fp32 kernel is split over, enough for four a CU: a CU holds two (d=128), and with fewer
-// the CUs that are left over, or the last workgroups to run, are what the launch waits for.  Kernel and merge with
-// targets of 128, 512 and 1 024 workgroups: one head of 4 096 queries (d=64, a quarter of the keys) 39, 32 and 33 us,
-// three of 5 007 (d=128, a third of the keys) 267, 263 and 225 us, dense 1 x 4 096 (d=128) 149, 83 and 83 us.
+// Most workgroups a key list of the fp32 kernel is split over (a list takes no more than its tiles feed), enough for four a
+// CU: a CU holds two (d=128), and with fewer the CUs that are left over, or the last workgroups to run, are what a launch
+// with long lists waits for.  Kernel and merge with targets of 128, 512 and 1 024 workgroups: dense 1 x 4 096 (d=128) 149, 83
+// and 83 us; one head of 4 096 queries (d=64, a quarter of the keys) 28 us and three of 5 007 (d=128, a third) 197 us with any.
 int attn_f32_splits(int H, int N, int Cq) {
   const long long wgs = (long long)H * (N / 32 + Cq / 2 + 1);
   return (int)min((long long)F32_MAX_SPLITS, (1024 + wgs - 1) / wgs);

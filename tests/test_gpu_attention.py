@@ -227,14 +227,15 @@ def test_fp32_scores_of_minus_infinity_weigh_nothing(d, N, H):
     rng = np.random.default_rng(31)
     Q = rng.random((H, N, d)).astype(np.float32) + 0.1
     K, V = (rng.standard_normal((H, N, d)).astype(np.float32) for _ in range(2))
-    for dead in (np.arange(32), np.arange(32, min(N, 161)), np.arange(N - 1), np.arange(0, N, 3)):
+    for dead, scale in ((np.arange(32), d ** -0.5), (np.arange(32, min(N, 161)), d ** -0.5), (np.arange(N - 1), 2.0),
+                        (np.arange(0, N, 3), d ** -0.5)):
         K2 = K.copy()
         K2[:, dead] = -np.inf
-        p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=1, k_m0=1, k_m_min=1, k_max_clusters=1)
+        p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=1, k_m0=1, k_m_min=1, k_max_clusters=1, softmax_scale=scale)
         O = to_np(B.adacluster_dense_attn(p, to_dev(Q, B.F32), to_dev(K2, B.F32), to_dev(V, B.F32)))
         live = np.setdiff1d(np.arange(N), dead)
         for h in (0, H - 1):
-            S = Q[h].astype(np.float64) @ K[h][live].astype(np.float64).T / d ** 0.5
+            S = Q[h].astype(np.float64) @ K[h][live].astype(np.float64).T * scale
             P = np.exp(S - S.max(1, keepdims=True))
             check(O[h], (P / P.sum(1, keepdims=True)) @ V[h][live].astype(np.float64), B.F32)
     K2[:] = -np.inf
