@@ -10,6 +10,7 @@
 #include "launch.h"
 
 #include <atomic>
+#include <type_traits>
 
 #pragma clang fp contract(off)
 
@@ -46,8 +47,8 @@ __device__ __forceinline__ uint64_t order_key(double v) {
 }
 
 // Scores of every (query cluster, key cluster) pair: S[h][i][j], -inf for an empty key cluster, 0 for a head
-// that attends to everything.  A thread owns SCORE_ROWS key clusters and reads their rows (16 bytes at a time,
-// one step ahead) ONCE for SCORE_QG query clusters, whose centroids wait in LDS split by sign:
+// that attends to everything.  A thread owns a key cluster and reads its row ONCE for QG query clusters, whose
+// centroids wait in LDS split by sign:
 //   (q, 0) where q's sign bit is clear, (0, q) where it is set.
 // Every score is the pair of chains  sp += q+ * k+,  sn += q- * k-  in ascending dimension order with
 // k+/k- = max(c,0)/min(c,0) (Algorithm 2), box max/min (Eq. 1), or c itself with q- = 0 (plain dot product).
@@ -55,19 +56,17 @@ __device__ __forceinline__ uint64_t order_key(double v) {
 // exactly the terms it owns.  q and k are float values, so a product is exact in double (48 significant bits
 // at most, exponents far inside the range) and the fused multiply-add rounds once, exactly where the add of a
 // separately rounded product would: the same bits as multiply-then-add at twice the rate.
-// (One workgroup per query cluster reading every key row itself, as the selection kernel did before, was bound
-// by L2 traffic: 65 reads of a head's centroid table.)
-// Measured at 1171 / 500 key clusters per head (24 / 30 heads, d = 128 / 64), (QG, rows): (13,1) 61 / 30 us,
-// (7,1) 76 / 29, (13,2) 66 / 36, (9,2) 84 / 30, (7,2) 83 / 41, (5,2) 89 / 44; with one row the LDS pipe is the
-// limit (a 16-byte broadcast read per two fused multiply-adds), with more rows the registers and the smaller
-// number of waves are.  The query values as scalar operands (scalar loads from a table prepared by another
-// kernel, no LDS) took 165 / 75 us: the scalar cache delivers far less than the LDS.
-constexpr int SCORE_QG = 13;       // query clusters per thread (65 = 5 groups) ...
-constexpr int SCORE_QG_SMALL = 5;  // ... or 5 (13 groups) when the launch would otherwise leave SIMDs without a wave
-constexpr int SCORE_ROWS = 1;      // key clusters per thread
+// (One workgroup per query cluster reading every key row itself was bound by L2 traffic: 65 reads of a head's centroid table.)
+// What bounds it: large tables the LDS pipe (a 16-byte broadcast read per two fused multiply-adds; two rows a thread
+// halve the reads and cost as much in waves), small ones the trips to the rows, which finalize_centroids has just written
+// on other XCDs.  So eight pieces of a row are in flight a step, the first of them from the kernel's first instructions on
+// (four, behind the counts, sizes and flags before): 5 heads x 110 clusters, d=128, 17 -> 10 us (boxes 22 -> 10),
+// 12 x 330, d=128, 24 -> 18 (33 -> 20), 24 x 1171, d=128, 92 -> 69 (129 -> 73), 30 x 600, d=64, 33 -> 30 (42 -> 31).
+// The query values as scalar operands (scalar loads from a table prepared by another kernel, no LDS) took more than
+// twice as long: the scalar cache delivers far less than the LDS.
 constexpr int SCORE_THREADS = 128;
 
-template <int QG>
+template <int QG, int D, bool BOX>
 __global__ __launch_bounds__(SCORE_THREADS) void score_kernel(SelectCfg cfg, const float* __restrict__ q_cent,
                                                               const float* __restrict__ k_cent,
                                                               const float* __restrict__ k_bmin,
@@ -76,18 +75,23 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_kernel(SelectCfg cfg, con
                                                               const int32_t* __restrict__ k_count,
                                                               const int32_t* __restrict__ full_flag,
                                                               double* __restrict__ S) {
-  constexpr int R = SCORE_ROWS;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  double2* qs = reinterpret_cast<double2*>(smem);            // [QG][d]
+  constexpr int B4 = 8, STEPS = D / (4 * B4);      // 16-byte pieces of a row per step
+  __shared__ __attribute__((aligned(16))) double2 qs[QG * D];
   const int h = blockIdx.z, i0 = blockIdx.y * QG, tid = threadIdx.x;
-  const int d = cfg.d;
+  const int j = blockIdx.x * SCORE_THREADS + tid;
+  // (rows past the count exist: the tables hold `cap` of them)
+  const size_t row = ((size_t)h * cfg.cap + min(j, cfg.cap - 1)) * D;
+  const float4* rpos = reinterpret_cast<const float4*>((BOX ? k_bmax : k_cent) + row);
+  const float4* rneg = reinterpret_cast<const float4*>((BOX ? k_bmin : k_cent) + row);
+  float4 pb[B4], nb[B4];
+#pragma unroll
+  for (int u = 0; u < B4; ++u) { pb[u] = rpos[u]; if (BOX) nb[u] = rneg[u]; }
   const int kc = min(k_count[h], cfg.lds_cap);
-  if ((int)blockIdx.x * (R * SCORE_THREADS) >= kc) return;
-  const bool dot = cfg.score_mode == ADACLUSTER_SCORE_DOT, box = cfg.score_mode == ADACLUSTER_SCORE_BOX;
-  for (int e = tid; e < QG * d; e += SCORE_THREADS) {
-    const int g = e / d, t = e - g * d;
-    const int i = min(i0 + g, cfg.Cq - 1);        // (the last group repeats the last cluster; not stored)
-    const float q = q_cent[((size_t)h * cfg.Cq + i) * d + t];
+  if ((int)blockIdx.x * SCORE_THREADS >= kc) return;
+  const bool dot = cfg.score_mode == ADACLUSTER_SCORE_DOT, all = full_flag[h] != 0;
+  for (int e = tid; e < QG * D; e += SCORE_THREADS) {
+    const int i = min(i0 + e / D, cfg.Cq - 1);     // (the last group repeats the last cluster; not stored)
+    const float q = q_cent[((size_t)h * cfg.Cq + i) * D + e % D];
     const bool neg = (__float_as_uint(q) >> 31) != 0u;
     double2 v;
     v.x = (dot || !neg) ? (double)q : 0.0;
@@ -95,87 +99,43 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_kernel(SelectCfg cfg, con
     qs[e] = v;
   }
   __syncthreads();
-  // Row r of this thread is key cluster jb + r * SCORE_THREADS.  A row that needs no arithmetic (past the
-  // count, empty, or in a head that attends to everything) runs on row jb's data all the same and stores its
-  // fixed value instead.
-  const int jb = blockIdx.x * (R * SCORE_THREADS) + tid;
-  if (jb >= kc) return;
-  const bool all = full_flag[h] != 0;
-  bool live[R], any_live = false; double fixed[R];
-  const float4* rpos[R]; const float4* rneg[R];
+  double sp[QG], sn[QG];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = jb + r * SCORE_THREADS;
-    const int nj = j < kc ? k_sizes[(size_t)h * cfg.cap + j] : 0;
-    live[r] = j < kc && nj > 0 && !all;
-    any_live = any_live || live[r];
-    fixed[r] = nj == 0 ? -INFINITY : 0.0;
-    const int jl = live[r] ? j : jb;
-    rpos[r] = reinterpret_cast<const float4*>((box ? k_bmax : k_cent) + ((size_t)h * cfg.cap + jl) * d);
-    rneg[r] = reinterpret_cast<const float4*>((box ? k_bmin : k_cent) + ((size_t)h * cfg.cap + jl) * d);
-  }
-  double sp[R][QG], sn[R][QG];
+  for (int g = 0; g < QG; ++g) { sp[g] = 0.0; sn[g] = 0.0; }
+  if (!all) {
 #pragma unroll
-  for (int r = 0; r < R; ++r)
+    for (int st = 0; st < STEPS; ++st) {
+      float4 pc[B4], nc[B4];
 #pragma unroll
-    for (int g = 0; g < QG; ++g) { sp[r][g] = 0.0; sn[r][g] = 0.0; }
-  if (any_live) {
-    constexpr int B4 = 4 / R > 0 ? 4 / R : 1;      // 16-byte pieces of a row per step
-    float4 pb[R][B4], nb[R][B4];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int u4 = 0; u4 < B4; ++u4) { pb[r][u4] = rpos[r][u4]; nb[r][u4] = box ? rneg[r][u4] : pb[r][u4]; }
-    for (int st = 0; st < d / (4 * B4); ++st) {
-      float4 pc[R][B4], nc[R][B4];
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int u4 = 0; u4 < B4; ++u4) { pc[r][u4] = pb[r][u4]; nc[r][u4] = nb[r][u4]; }
-      if (st + 1 < d / (4 * B4)) {
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int u4 = 0; u4 < B4; ++u4) {
-            pb[r][u4] = rpos[r][(st + 1) * B4 + u4];
-            nb[r][u4] = box ? rneg[r][(st + 1) * B4 + u4] : pb[r][u4];
-          }
+      for (int u = 0; u < B4; ++u) {
+        pc[u] = pb[u]; if (BOX) nc[u] = nb[u];
+        if (st + 1 < STEPS) { pb[u] = rpos[(st + 1) * B4 + u]; if (BOX) nb[u] = rneg[(st + 1) * B4 + u]; }
       }
 #pragma unroll
       for (int u4 = 0; u4 < B4; ++u4) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int t = (st * B4 + u4) * 4 + u;
-          double kp[R], kn[R];
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            const float pv = u == 0 ? pc[r][u4].x : u == 1 ? pc[r][u4].y : u == 2 ? pc[r][u4].z : pc[r][u4].w;
-            const float nv = u == 0 ? nc[r][u4].x : u == 1 ? nc[r][u4].y : u == 2 ? nc[r][u4].z : nc[r][u4].w;
-            kp[r] = (double)((box || dot) ? pv : fmaxf(pv, 0.f));
-            kn[r] = (double)((box || dot) ? nv : fminf(nv, 0.f));
-          }
+          const float pv = u == 0 ? pc[u4].x : u == 1 ? pc[u4].y : u == 2 ? pc[u4].z : pc[u4].w;
+          const float nv = !BOX ? pv : u == 0 ? nc[u4].x : u == 1 ? nc[u4].y : u == 2 ? nc[u4].z : nc[u4].w;
+          const double kp = (double)((BOX || dot) ? pv : fmaxf(pv, 0.f));
+          const double kn = (double)((BOX || dot) ? nv : fminf(nv, 0.f));
 #pragma unroll
           for (int g = 0; g < QG; ++g) {
-            const double2 q2 = qs[g * d + t];
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-              sp[r][g] = __fma_rn(q2.x, kp[r], sp[r][g]);
-              sn[r][g] = __fma_rn(q2.y, kn[r], sn[r][g]);
-            }
+            const double2 q2 = qs[g * D + t];
+            sp[g] = __fma_rn(q2.x, kp, sp[g]);
+            sn[g] = __fma_rn(q2.y, kn, sn[g]);
           }
         }
       }
     }
   }
+  if (j >= kc) return;
+  const int nj = k_sizes[(size_t)h * cfg.cap + j];
+  double* out = S + ((size_t)h * cfg.Cq + i0) * cfg.cap + j;
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = jb + r * SCORE_THREADS;
-    if (j >= kc) continue;
-    double* out = S + ((size_t)h * cfg.Cq + i0) * cfg.cap + j;
-#pragma unroll
-    for (int g = 0; g < QG; ++g)
-      if (i0 + g < cfg.Cq) out[(size_t)g * cfg.cap] = live[r] ? sp[r][g] + sn[r][g] : fixed[r];
-  }
+  for (int g = 0; g < QG; ++g)
+    if (i0 + g < cfg.Cq) out[(size_t)g * cfg.cap] = nj == 0 ? -INFINITY : all ? 0.0 : sp[g] + sn[g];
 }
 
 // One block per (query cluster, head).  Dynamic LDS: key[cap] (uint64) + flag[cap] (int).
@@ -417,17 +377,25 @@ int launch_select(hipStream_t s, int H, int Cq, int cap, int d, int score_mode, 
     granted[dev].store((int)shm);
   }
   const int kb = kc_max < cap ? kc_max : cap;
-  const int kblocks = (kb + SCORE_ROWS * SCORE_THREADS - 1) / (SCORE_ROWS * SCORE_THREADS);
-  // 1024 SIMDs: with fewer than two waves each the larger grid of the small group size is the faster one
-  const bool small_groups = (long long)kblocks * ((Cq + SCORE_QG - 1) / SCORE_QG) * H * (SCORE_THREADS / 64) < 2048;
-  if (small_groups)
-    score_kernel<SCORE_QG_SMALL><<<dim3(kblocks, (Cq + SCORE_QG_SMALL - 1) / SCORE_QG_SMALL, H), SCORE_THREADS,
-                                   (size_t)SCORE_QG_SMALL * d * sizeof(double2), s>>>(c, q_cent, k_cent, k_bmin, k_bmax, k_sizes,
-                                                                                     k_count, full_flag, scores);
-  else
-    score_kernel<SCORE_QG><<<dim3(kblocks, (Cq + SCORE_QG - 1) / SCORE_QG, H), SCORE_THREADS,
-                             (size_t)SCORE_QG * d * sizeof(double2), s>>>(c, q_cent, k_cent, k_bmin, k_bmax, k_sizes, k_count,
-                                                                         full_flag, scores);
+  auto score = [&](auto qg, auto dd, auto box) {
+    constexpr int QG = decltype(qg)::value, D = decltype(dd)::value;
+    const dim3 g((kb + SCORE_THREADS - 1) / SCORE_THREADS, (Cq + QG - 1) / QG, H);
+    score_kernel<QG, D, decltype(box)::value><<<g, SCORE_THREADS, 0, s>>>(c, q_cent, k_cent, k_bmin, k_bmax, k_sizes, k_count, full_flag, scores);
+  };
+  auto form = [&](auto qg, auto dd) {
+    if (score_mode == ADACLUSTER_SCORE_BOX) score(qg, dd, std::true_type{}); else score(qg, dd, std::false_type{});
+  };
+  auto group = [&](auto qg) {
+    if (d == 64) form(qg, std::integral_constant<int, 64>{}); else form(qg, std::integral_constant<int, 128>{});
+  };
+  // Query clusters a thread: 3 while that leaves every one of the 1024 SIMDs at most a wave (d=128, 5 heads x 110 clusters:
+  // 10 us, 5 a thread 13), 13 once it gives every SIMD two, 4 or (boxes, whose rows take twice the registers) 5 in between
+  // (12 x 330, d=128: 17 and 20 us, 3 a thread 20 and 25; 30 x 600, d=64: 28 and 31 us, 5 and 4 a thread 34 and 43).
+  const long long waves = (long long)((kb + 63) / 64) * H;
+  if (waves * ((Cq + 2) / 3) <= 1024) group(std::integral_constant<int, 3>{});
+  else if (waves * ((Cq + 12) / 13) >= 2048) group(std::integral_constant<int, 13>{});
+  else if (score_mode == ADACLUSTER_SCORE_BOX) group(std::integral_constant<int, 5>{});
+  else group(std::integral_constant<int, 4>{});
   select_kernel<<<dim3(Cq, H), 256, shm, s>>>(c, scores, q_mean_norm, k_sizes, k_count, full_flag, sel_idx, sel_cnt);
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
 }

@@ -99,3 +99,26 @@ def test_equal_scores_at_the_topk_boundary_over_several_chunks(topk):
         ref = orc.select_topk(S, topk)
         for i in range(Cq):
             assert np.array_equal(got[h][i], ref[i]), (h, i)
+
+
+@pytest.mark.parametrize("H,Cq,cap,kc,d", [(1, 1, 64, 64, 64),           # three query clusters a thread: one, an exact group,
+                                           (2, 3, 129, 129, 128), (1, 65, 140, 127, 128),     # a remainder; 128 rows a workgroup
+                                           (30, 66, 384, 380, 64),       # four (boxes five) a thread, remainders of both
+                                           (30, 66, 1000, 1000, 128)])   # thirteen, a remainder of one
+@pytest.mark.parametrize("score_mode", [B.SCORE_TQ, B.SCORE_BOX])
+def test_scores_by_every_group_size(H, Cq, cap, kc, d, score_mode):
+    """The launch gives a thread 3, 4, 5 or 13 query clusters by the size of the table: the index sets stay exact."""
+    qc, mean_norm, kcent, bmin, bmax, sizes, kcount = make_inputs(13, H, Cq, cap, [kc] + [max(1, kc - 1)] * (H - 1), d)
+    topk = max(1, kc // 5)
+    p = B.Params(H=H, N=100000, d=d, q_clusters=Cq, k_m0=16, k_m_min=4, k_max_clusters=cap - 16, topk=topk, score_mode=score_mode)
+    c = lambda a: torch.from_numpy(a).cuda()
+    si, sc = B.adacluster_select(p, c(qc), c(mean_norm), c(kcent), c(bmin), c(bmax), c(sizes), c(kcount),
+                                 c(np.zeros(H, dtype=np.int32)))
+    got = sel_from_dev(si, sc)
+    for h in sorted({0, H - 1}):
+        k = kcount[h]
+        S = orc.cluster_scores(score_mode, qc[h].astype(np.float64), kcent[h, :k].astype(np.float64),
+                               bmin[h, :k].astype(np.float64), bmax[h, :k].astype(np.float64), sizes[h, :k])
+        ref = orc.select_topk(S, topk)
+        for i in range(Cq):
+            assert np.array_equal(got[h][i], ref[i]), (h, i)
