@@ -245,7 +245,7 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(ulist[0], int32_t*, H * N * 4);
   TAKE(ulist[1], int32_t*, H * N * 4);
   TAKE(blockcnt, int32_t*, H * D.ncnt * 4);
-  TAKE(tau_part, double*, H * D.nblk * 8);
+  TAKE(tau_part, double*, H * (D.ncnt > D.nblk ? D.ncnt : D.nblk) * 8);
   TAKE(sort.hist, int32_t*, H * sort_table_ints(D.N, D.capmax) * 4);
   TAKE(sort.lab_a, int32_t*, H * sort_scratch_ints(D.N) * 4);
   TAKE(sort.val_a, int32_t*, H * sort_scratch_ints(D.N) * 4);
@@ -338,7 +338,7 @@ int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   const int P = parts_for(D.N, D.Cq);
   int poff_done = 0;   // set when the sort has already cut the clusters into reduction parts
   const int sph = p->q_no_norm ? 0 : 1;      // by angle on q/|q| (the paper), or Euclidean on raw queries (ablation)
-  RET_IF(launch_init_centroids(st, p->dtype, D.d, D.H, D.N, 0, D.Cq, D.Cq, nullptr, sph, p->q_init_mode,
+  RET_IF(launch_init_centroids(st, p->dtype, D.d, D.H, D.N, D.Cq, D.Cq, nullptr, nullptr, nullptr, sph, p->q_init_mode,
                                D.Cq, D.Cq, Q, q_centroids, w.q_cent_lp, q_assign, w.q_bias));
   // A pass that only updates the centres reads the queries once: assignment and (normalised) sums in one
   // kernel.  The last pass needs the labels sorted (for the attention step) and exact member statistics, and
@@ -383,37 +383,38 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   int pending = 0;                   // the last report (of this stage) may still be in flight when the stage loop ends
   StageReadback* rb = nullptr;
   int poff_done = 0;                 // set when the sort has already cut the clusters into reduction parts
-  if (p->k_init_mode == 1) {
+  KState* cur = w.kstate;            // where the state is
+  const bool warm = p->k_init_mode == 1;
+  if (warm) {
     // warm start: one pseudo-stage over all tokens with the previous centres, count fixed
-    RET_IF(launch_kstate_warm(st, w.kstate, D.H, D.N, D.cap, k_count, full_flag));
+    cur = w.kstate2;
     if (k_stage_of) RET_IF(launch_fill_i32(st, k_stage_of, (size_t)D.H * D.N, 0));
-    RET_IF(launch_init_centroids(st, p->dtype, D.d, D.H, D.N, 1, 0, D.cap, w.kstate, 0, 1, D.cap, D.cap, K,
+    RET_IF(launch_init_centroids(st, p->dtype, D.d, D.H, D.N, 0, D.cap, cur, k_count, full_flag, 0, 1, D.cap, D.cap, K,
                                  k_centroids, w.cent_lp, k_assign, w.bias));
     const int Pw = parts_for(D.N, D.cap);
     for (int it = 0; it < p->k_iters; ++it) {
-      RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, 1, 0, D.cap, w.kstate, nullptr, K, w.cent_lp, w.bias,
+      RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, 1, 0, D.cap, cur, nullptr, K, w.cent_lp, w.bias,
                            k_labels, nullptr));
       if (it < p->k_iters - 1 && direct_update_fits(p->dtype, D.N, D.cap)) {
-        RET_IF(launch_update_direct(st, D.d, D.H, D.N, D.cap, D.cap, D.cap, w.kstate, k_labels, nullptr, K, k_centroids,
+        RET_IF(launch_update_direct(st, D.d, D.H, D.N, D.cap, D.cap, D.cap, cur, k_labels, nullptr, K, k_centroids,
                                     w.cent_lp, k_assign, w.bias));
       } else if (it < p->k_iters - 1) {
-        RET_IF(launch_sort(st, D.H, D.N, D.N, D.cap, k_labels, nullptr, nullptr, 0, &w.kstate->m_t, sizeof(KState) / 4,
+        RET_IF(launch_sort(st, D.H, D.N, D.N, D.cap, k_labels, nullptr, nullptr, 0, &cur->m_t, sizeof(KState) / 4,
                            nullptr, 0, w.perm_tmp, w.offs_tmp, D.capmax + 1, w.sort, w.poff, reduce_part_rows(), w.pcl, Pw, &poff_done));
-        RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, 1, 0, D.cap, Pw, w.kstate, 0, 0, K, w.perm_tmp,
+        RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, 1, 0, D.cap, Pw, cur, 0, 0, K, w.perm_tmp,
                                  w.offs_tmp, D.capmax + 1, w.poff, w.pcl, w.psum, w.pnorm, w.pmin, w.pmax, poff_done));
-        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, D.cap, Pw, D.cap, D.cap, w.kstate, 0, 1, 0, w.offs_tmp,
+        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, D.cap, Pw, D.cap, D.cap, cur, 0, 1, 0, w.offs_tmp,
                                D.capmax + 1, w.poff, w.psum, w.pnorm, w.pmin, w.pmax, k_centroids, w.cent_lp,
                                k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr));
       }
     }
-    RET_IF(launch_kstate_commit(st, w.kstate, D.H));
     kc_bound = D.cap;
-    RET_IF(launch_kstate_export(st, w.kstate, D.H, w.kstate, k_count, full_flag, k_stage_offs));
   } else {
   const int u_min = (int)floor((double)p->min_unassigned_frac * (double)p->N);
   const bool seeded = p->dtype == ADACLUSTER_BF16;
+  double* const dist_sum = p->tau_abs > 0.f ? nullptr : w.tau_part;      // (tau from the distances of the first stage)
   if (k_stage_of) RET_IF(launch_fill_i32(st, k_stage_of, (size_t)D.H * D.N, -1));
-  if (p->tau_abs > 0.f) RET_IF(launch_tau(st, D.H, D.N, nullptr, nullptr, 0.f, p->tau_abs, w.tau));
+  if (p->tau_abs > 0.f) RET_IF(launch_tau_abs(st, p->tau_abs, w.tau));
   // The stage loop has a data-dependent trip count, and grids are sized by what the stage head
   // reports: {active heads, max |U|, max m_t}.  Reading that back before enqueuing the stage
   // would drain the queue once per stage, so the host stays one stage behind: stage t is
@@ -424,7 +425,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   rb = stage_readback();
   if (!rb) return fail(ADACLUSTER_E_INTERNAL, "stage read-back set-up failed: %s", hipGetErrorString(hipGetLastError()));
   int n_bound = D.N, m_bound = p->k_m0 < D.N ? p->k_m0 : D.N, heads = D.H;
-  KState *cur = w.kstate, *other = w.kstate2;      // the stage head reads one and writes the other
+  KState* other = w.kstate2;                       // the stage head reads one and writes the other
   StageFilter filter{};                            // how the stage before ended
   for (int t = 0; t <= p->k_max_stages; ++t) {
     // the stage head writes its report straight into the pinned slot (no copy in between)
@@ -451,9 +452,9 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       // enqueue; the other stream keeps the device busy meanwhile.
       if (!stage_report_landed(*rb, 1, st))
         return fail(ADACLUSTER_E_INTERNAL, "stage read-back failed: %s", hipGetErrorString(hipGetLastError()));
-      const int32_t* cur = rb->host + 4;
-      if (cur[0] == 0) break;                  // no head needs a second stage
-      heads = cur[0]; n_bound = cur[1]; m_bound = cur[2];
+      const int32_t* now = rb->host + 4;
+      if (now[0] == 0) break;                  // no head needs a second stage
+      heads = now[0]; n_bound = now[1]; m_bound = now[2];
     }
     if (t > 0 && p->dtype == ADACLUSTER_BF16 && n_bound <= small_stage_points(D.d, heads) && m_bound <= small_stage_centres()) {
       // few points and few centres left in every head: one launch runs this and every later stage
@@ -489,7 +490,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, n_bound, 1, 0, D.cap, cur, ul, K, w.cent_lp, w.bias,
                            w.labels_tmp, update ? nullptr : w.dist2, nullptr, nullptr, 0, keep ? w.lab0 : nullptr,
                            keep ? w.score0 : nullptr, nullptr, nullptr, w.tau,
-                           !update && t > 0 ? w.blockcnt : nullptr, D.ncnt));
+                           !update && t > 0 ? w.blockcnt : nullptr, D.ncnt, !update && t == 0 ? dist_sum : nullptr));
       if (update && direct_update_fits(p->dtype, n_bound, m_bound)) {
         // few points (fp32): every centre gathers its members from the label list itself, one launch
         RET_IF(launch_update_direct(st, D.d, D.H, D.N, m_bound, D.cap, p->k_m0, cur, w.labels_tmp, ul, K, w.master,
@@ -505,34 +506,32 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                                k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr));
       }
     }
-    if (t == 0 && !(p->tau_abs > 0.f))
-      RET_IF(launch_tau(st, D.H, D.N, w.dist2, w.tau_part, p->tau_factor, 0.f, w.tau));
     filter = StageFilter{w.dist2, w.tau, w.blockcnt, D.ncnt, stage_points_per_count(p->dtype), ul, ul_next, k_stage_of, t};
-    if (t == 0) RET_IF(launch_keep_count(st, cur, D.H, D.N, w.dist2, w.tau, w.blockcnt, D.ncnt, &filter.items));
+    if (t == 0) RET_IF(launch_keep_count(st, p->dtype, cur, D.H, D.N, w.dist2, dist_sum, p->tau_factor, w.tau, w.blockcnt, D.ncnt, &filter.items));
   }
   kc_bound = kc_bound < D.cap ? kc_bound : D.cap;
-  RET_IF(launch_kstate_export(st, cur, D.H, w.kstate, k_count, full_flag, k_stage_offs, w.tau, tau_used));
   // last step of Algorithm 1: nearest centre among all stage centres, then member statistics.  bf16: the
   // nearest first-stage centre of every point is known from stage 0, so only the later stages' centres are visited.
   if (seeded)
-    RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, 3, 0, D.cap, w.kstate, nullptr, K, w.cent_lp, w.bias,
+    RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, 3, 0, D.cap, cur, nullptr, K, w.cent_lp, w.bias,
                          k_labels, nullptr, nullptr, nullptr, 0, nullptr, nullptr, w.lab0, w.score0))
   else
-    RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, 2, 0, D.cap, w.kstate, nullptr, K, w.cent_lp, w.bias,
+    RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, 2, 0, D.cap, cur, nullptr, K, w.cent_lp, w.bias,
                          k_labels, nullptr));
   }
   const int want_box = (k_bmin && k_bmax) ? 1 : 0;
   if (kc_bound_out) *kc_bound_out = kc_bound;
   const int P = parts_for(D.N, kc_bound);
-  RET_IF(launch_sort(st, D.H, D.N, D.N, kc_bound, k_labels, nullptr, nullptr, 0, &w.kstate->ccount, sizeof(KState) / 4,
+  RET_IF(launch_sort(st, D.H, D.N, D.N, kc_bound, k_labels, nullptr, nullptr, 0, warm ? &cur->m_t : &cur->ccount, sizeof(KState) / 4,
                      nullptr, 0, w.perm_k, w.offs_k, D.cap + 1, w.sort, w.poff, reduce_part_rows(), w.pcl, P, &poff_done));
   prof_mark(EV_KSORT, st);
-  RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, 2, 0, kc_bound, P, w.kstate, 0, want_box, K, w.perm_k, w.offs_k,
+  RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, warm ? 1 : 2, 0, kc_bound, P, cur, 0, want_box, K, w.perm_k, w.offs_k,
                            D.cap + 1, w.poff, w.pcl, w.psum, w.pnorm, w.pmin, w.pmax, poff_done));
   prof_mark(EV_KREDUCE, st, EV_KSORT);
-  RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 2, 0, kc_bound, P, D.cap, D.cap, w.kstate, 0, 0, want_box, w.offs_k,
+  const StateExport ex{w.kstate, k_count, full_flag, k_stage_offs, w.tau, warm ? nullptr : tau_used};
+  RET_IF(launch_finalize(st, p->dtype, D.d, D.H, warm ? 1 : 2, 0, kc_bound, P, D.cap, D.cap, cur, 0, 0, want_box, w.offs_k,
                          D.cap + 1, w.poff, w.psum, w.pnorm, w.pmin, w.pmax, nullptr, nullptr, nullptr, nullptr, k_centroids,
-                         k_assign, k_sizes, nullptr, k_bmin, k_bmax));
+                         k_assign, k_sizes, nullptr, k_bmin, k_bmax, nullptr, 0, 0, &ex));
   // the pinned report slots are reused by the next call of this thread: let the last report land
   // (its kernel was queued ahead of everything above, so this does not drain the stream)
   if (pending && !stage_report_landed(*rb, pending, st))

@@ -28,6 +28,8 @@ struct AssignCfg {
   const int32_t* seed_lab; const float* seed_score;
   const float* tau; int32_t* keep_cnt; int keep_stride;   // points of this workgroup that the threshold leaves in U (a late
                                                           // stage's last pass): keep_cnt[h * keep_stride + workgroup]
+  double* dist_sum;                                       // sum of the distances of this workgroup's points (the first stage's last
+                                                          // pass, for tau): dist_sum[h * gridDim.x + workgroup]
 };
 constexpr int ASSIGN_POINTS_LP = 256, ASSIGN_POINTS_F32 = 128;     // points of an assignment workgroup
 
@@ -245,6 +247,7 @@ __global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict_
   }
   int blab[PB];
   int kept = 0;
+  double dsum = 0.0;
   const bool counts = !ACC && cfg.keep_cnt && dist2;
   const float t2 = counts ? cfg.tau[1] : 0.f;
 #pragma unroll
@@ -260,6 +263,7 @@ __global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict_
     const float d2 = fmaxf(xn2[pb] - 2.f * bv, 0.f);
     if (counts) kept += __popcll(__ballot(hb == 0 && pos[pb] < n && !(d2 < t2)));
     if (hb == 0 && pos[pb] < n) {
+      if (!ACC && cfg.dist_sum) dsum += (double)sqrtf(d2);
       labels[(size_t)h * cfg.N + pos[pb]] = bidx;
       if (dist2) dist2[(size_t)h * cfg.N + pos[pb]] = d2;
       if (!ACC && cfg.keep_lab) { cfg.keep_lab[(size_t)h * cfg.N + pos[pb]] = bidx; cfg.keep_score[(size_t)h * cfg.N + pos[pb]] = bv; }
@@ -271,6 +275,14 @@ __global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict_
     if (lane == 0) wkept[wave] = kept;
     __syncthreads();
     if (tid == 0) cfg.keep_cnt[(size_t)h * cfg.keep_stride + blockIdx.x] = wkept[0] + wkept[1] + wkept[2] + wkept[3];
+  }
+  if (!ACC && cfg.dist_sum) {
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) dsum += __shfl_xor(dsum, o);      // (the upper half-wave holds zeros)
+    __shared__ double wsum[4];
+    if (lane == 0) wsum[wave] = dsum;
+    __syncthreads();
+    if (tid == 0) cfg.dist_sum[(size_t)h * gridDim.x + blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
   }
   if constexpr (ACC) {
     constexpr int ROWB = D * 2, DT = D / 32;
@@ -609,6 +621,15 @@ __global__ __launch_bounds__(128) void assign_f32(const float* __restrict__ X, A
     __syncthreads();
     if (tid == 0) cfg.keep_cnt[(size_t)h * cfg.keep_stride + blockIdx.x] = wkept[0] + wkept[1];
   }
+  if (cfg.dist_sum) {
+    double dsum = p < n ? (double)sqrtf(d2) : 0.0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) dsum += __shfl_xor(dsum, o);
+    __shared__ double wsum[2];
+    if ((tid & 63) == 0) wsum[tid >> 6] = dsum;
+    __syncthreads();
+    if (tid == 0) cfg.dist_sum[(size_t)h * gridDim.x + blockIdx.x] = wsum[0] + wsum[1];
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -795,7 +816,34 @@ struct FinalizeCfg {
   int spherical; int update_assign; int lp_is_bf16; int want_box;
   const int32_t* bcnt; int nb_stride;     // block sums of the assignment kernel instead of cluster parts (stage mode)
   int nb_const;                           // > 0: that many blocks (walks of the one-read query pass), whatever the state says
+  StateExport ex;                         // the last launch of a key clustering: what it leaves of its state (home NULL: nothing)
 };
+
+// The state of a head as later steps and calls find it in `home` (mode 1, a warm start: its one pseudo-stage is over), and
+// the outputs that are copies of it.  By the first wave of a head's first workgroup; `home` is not the array that the
+// others read, or is left as it is.
+__device__ __forceinline__ void export_state(const StateExport& ex, const KState* __restrict__ st, int mode, int h, int lane) {
+  constexpr int W = sizeof(KState) / 4, OFFS = offsetof(KState, stage_offs) / 4;
+  static_assert(W <= 64, "a word a lane");
+  const KState& s = st[h];
+  const int m = s.m_t;
+  int v = lane < W ? reinterpret_cast<const int32_t*>(&s)[lane] : 0;
+  if (mode == 1) {
+    if (lane == offsetof(KState, ucount) / 4 || lane == offsetof(KState, active) / 4) v = 0;
+    if (lane == offsetof(KState, stage) / 4 || lane == offsetof(KState, done) / 4) v = 1;
+    if (lane == offsetof(KState, ccount) / 4 || lane == OFFS + 1) v = m;
+  }
+  if (ex.home != st && lane < W) reinterpret_cast<int32_t*>(&ex.home[h])[lane] = v;
+  const int ccount = mode == 1 ? m : s.ccount, stage = mode == 1 ? 1 : s.stage;
+  if (lane == 0) {
+    if (h == 0 && ex.tau_used) ex.tau_used[0] = ex.tau[0];
+    if (ex.k_count) ex.k_count[h] = ccount;
+    if (ex.full_flag) ex.full_flag[h] = s.full;
+  }
+  const int i = lane - OFFS;
+  if (ex.stage_offs && i >= 0 && i <= ADACLUSTER_MAX_STAGES)
+    ex.stage_offs[(size_t)h * (ADACLUSTER_MAX_STAGES + 1) + i] = i <= stage ? v : ccount;
+}
 
 constexpr int FIN_ROWS = 4;           // clusters per workgroup, one wave each (no step needs the workgroup)
 template <int D>
@@ -812,6 +860,7 @@ __global__ __launch_bounds__(64 * FIN_ROWS) void finalize_centroids(FinalizeCfg 
                                                          float* __restrict__ out_bmin, float* __restrict__ out_bmax) {
   constexpr int CPL = D / 64;          // columns per lane
   const int h = blockIdx.y, j = blockIdx.x * FIN_ROWS + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (cfg.ex.home && blockIdx.x == 0 && threadIdx.x < 64) export_state(cfg.ex, cfg.st, cfg.mode, h, lane);
   int m, row_off = 0;
   if (cfg.mode == 0) m = cfg.m_const;
   else {
@@ -1031,23 +1080,28 @@ __global__ __launch_bounds__(256) void update_direct_f32(const float* __restrict
   if (cl == 0) bias[(size_t)h * cap + row_off + j] = -0.5f * bsum;
 }
 
-// Initial centres of the query clustering, a strided sample of all points, or (source_master = 1, warm starts of either
-// side) the rows that `master` holds.  Mode 1: centre counts and rows from the state.  (A stage of Algorithm 1 takes its
-// sample in stage_open.)
+// Initial centres: of the query clustering a strided sample of all points or (warm start) the rows that `master` holds, and
+// of a warm-started key clustering (Sec. 3.2.2, "Efficient initialization": one pseudo-stage over all tokens, the centre
+// count given) the rows of `master`; that launch (`warm`) also opens the state of every head.  A wave a centre.  (A stage of
+// Algorithm 1 takes its sample in stage_open.)
+struct WarmStart { KState* st; const int32_t* k_count; const int32_t* full_flag; };
+constexpr int INIT_ROWS = 4;
 template <typename T, int D>
-__global__ __launch_bounds__(64) void init_centroids(const T* __restrict__ X, int N, int mode, int m_const,
-                                                     const KState* __restrict__ st, int spherical,
-                                                     int source_master, int cap, int master_stride,
+__global__ __launch_bounds__(64 * INIT_ROWS) void init_centroids(const T* __restrict__ X, int N, int m_const, WarmStart warm,
+                                                     int spherical, int source_master, int cap, int master_stride,
                                                      int lp_is_bf16, float* __restrict__ master,
                                                      void* __restrict__ assign_lp, float* __restrict__ assign_f32,
                                                      float* __restrict__ bias) {
   constexpr int CPL = D / 64;
-  const int h = blockIdx.y, j = blockIdx.x, lane = threadIdx.x;
-  int m = m_const, row_off = 0;
-  if (mode == 1) {
-    const KState& s = st[h];
-    if (!s.active) return;
-    m = s.m_t; row_off = s.ccount;
+  const int h = blockIdx.y, j = blockIdx.x * INIT_ROWS + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  int m = m_const;
+  if (warm.st) {
+    m = max(1, min(min(warm.k_count[h], cap), N));
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      KState s{};
+      s.ucount = N; s.m_t = m; s.full = warm.full_flag[h] != 0; s.active = 1; s.u_hist[0] = N;
+      warm.st[h] = s;
+    }
   }
   if (j >= m) return;
   float val[CPL];
@@ -1075,7 +1129,7 @@ __global__ __launch_bounds__(64) void init_centroids(const T* __restrict__ X, in
   for (int q = 0; q < CPL; ++q) {
     const int col = lane + 64 * q;
     master[((size_t)h * master_stride + j) * D + col] = val[q];
-    const size_t ao = ((size_t)h * cap + row_off + j) * D + col;
+    const size_t ao = ((size_t)h * cap + j) * D + col;
     float img = val[q];
     if (lp_is_bf16) {
       const bf16raw r = f32_to_bf16(val[q]);
@@ -1089,67 +1143,40 @@ __global__ __launch_bounds__(64) void init_centroids(const T* __restrict__ X, in
   }
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) bsum += __shfl_xor(bsum, o);
-  if (lane == 0) bias[(size_t)h * cap + row_off + j] = spherical ? 0.f : -0.5f * bsum;
+  if (lane == 0) bias[(size_t)h * cap + j] = spherical ? 0.f : -0.5f * bsum;
 }
 
 // ------------------------------------------------------------------------------------------
 // Algorithm 1 bookkeeping
 // ------------------------------------------------------------------------------------------
-// Warm start (Sec. 3.2.2, "Efficient initialization"): one stage over all tokens, centre count given.
-__global__ void kstate_warm(KState* st, int H, int N, int cap, const int32_t* __restrict__ k_count,
-                            const int32_t* __restrict__ full_flag) {
-  const int h = blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= H) return;
-  KState s;
-  s.ucount = N; s.ccount = 0; s.m_t = max(1, min(min(k_count[h], cap), N)); s.stage = 0; s.done = 0;
-  s.full = full_flag[h] != 0; s.active = 1; s.pad = 0;
-  for (int i = 0; i <= ADACLUSTER_MAX_STAGES; ++i) { s.stage_offs[i] = 0; s.u_hist[i] = 0; }
-  s.u_hist[0] = N;
-  st[h] = s;
-}
-__global__ void kstate_commit(KState* st, int H) {
-  const int h = blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= H) return;
-  KState s = st[h];
-  s.ccount = s.m_t; s.stage = 1; s.stage_offs[1] = s.ccount; s.ucount = 0; s.active = 0; s.done = 1;
-  st[h] = s;
-}
-
-// tau = factor x mean first-stage distance over all heads and tokens (Sec. 4.1).
-__global__ __launch_bounds__(256) void tau_partial(const float* __restrict__ dist2, int N, int nblk,
-                                                   double* __restrict__ part) {
-  const int h = blockIdx.y, b = blockIdx.x, tid = threadIdx.x;
-  double s = 0.0;
-  const int beg = b * 1024;
-  for (int i = 0; i < 4; ++i) {
-    const int p = beg + i * 256 + tid;
-    if (p < N) s += (double)sqrtf(dist2[(size_t)h * N + p]);
-  }
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) s += __shfl_xor(s, o);
-  __shared__ double ws[4];
-  if ((tid & 63) == 0) ws[tid >> 6] = s;
-  __syncthreads();
-  if (tid == 0) part[(size_t)h * nblk + b] = (ws[0] + ws[1]) + (ws[2] + ws[3]);
-}
-
-__global__ __launch_bounds__(256) void tau_final(const double* __restrict__ part, int count, double denom, float factor,
-                                                 float* __restrict__ tau_out /* [0]=tau, [1]=tau^2 */) {
-  // fixed-order reduction: thread i takes elements i, i+256, ...; then a fixed tree
+// tau = factor x mean first-stage distance over all heads and tokens (Sec. 4.1), from the sums that the last pass of the
+// first stage left per workgroup.  Called by a whole workgroup; a fixed order: thread i takes elements i, i + NT, ..., then
+// a fixed tree.
+struct TauCfg { const double* part; int count; double denom; float factor; float* out /* [0] = tau, [1] = tau^2 */; };
+template <int NT>
+__device__ __forceinline__ float tau_of(const TauCfg& c) {
   const int tid = threadIdx.x;
   double s = 0.0;
-  for (int i = tid; i < count; i += 256) s += part[i];
+  for (int i = tid; i < c.count; i += 4 * NT) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = i + u * NT < c.count ? c.part[i + u * NT] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s += v[u];
+  }
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) s += __shfl_xor(s, o);
-  __shared__ double ws[4];
+  __shared__ double ws[NT / 64];
   if ((tid & 63) == 0) ws[tid >> 6] = s;
   __syncthreads();
-  if (tid == 0) {
-    const double tot = (ws[0] + ws[1]) + (ws[2] + ws[3]);
-    const double tau = (double)factor * tot / denom;
-    tau_out[0] = (float)tau;
-    tau_out[1] = (float)tau * (float)tau;
-  }
+  double tot = 0.0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) tot += ws[w];
+  return (float)((double)c.factor * tot / c.denom);
+}
+__global__ __launch_bounds__(1024) void tau_final(TauCfg c) {
+  const float tau = tau_of<1024>(c);
+  if (threadIdx.x == 0) { c.out[0] = tau; c.out[1] = tau * tau; }
 }
 
 __global__ void tau_set(float tau, float* __restrict__ tau_out) {
@@ -1159,13 +1186,21 @@ __global__ void tau_set(float tau, float* __restrict__ tau_out) {
 // Threshold filter of Algorithm 1: tokens with d < tau leave U.  Survivors per KEEP_ITEMS points of the first stage, whose
 // threshold is known only after its last pass (a later stage's last pass counts them itself).
 constexpr int KEEP_ITEMS = 1024;
+// Up to TAU_SUMS sums every workgroup forms the threshold itself, in the same order (tc.part; NULL: tau holds it): the
+// launch between the two cost 4-5 us and this costs one trip to the L2.
+constexpr int TAU_SUMS = 4096;
 __global__ __launch_bounds__(256) void keep_count(const KState* __restrict__ st, const float* __restrict__ dist2, int N,
-                                                  const float* __restrict__ tau, int32_t* __restrict__ cnt, int cnt_stride) {
+                                                  TauCfg tc, const float* __restrict__ tau, int32_t* __restrict__ cnt, int cnt_stride) {
   const int h = blockIdx.y, b = blockIdx.x, tid = threadIdx.x;
+  float t2;
+  if (tc.part) {
+    const float t = tau_of<256>(tc);
+    t2 = t * t;
+    if (h == 0 && b == 0 && tid == 0) { tc.out[0] = t; tc.out[1] = t2; }
+  } else t2 = tau[1];
   const KState& s = st[h];
   if (!s.active) return;
   const int n = s.ucount;
-  const float t2 = tau[1];
   int c = 0;
 #pragma unroll
   for (int i = 0; i < KEEP_ITEMS / 256; ++i) {
@@ -1739,22 +1774,6 @@ __global__ void fill_i32(int32_t* p, size_t n, int32_t v) {
   if (i < n) p[i] = v;
 }
 
-// k_count, full_flag and stage offsets out of the state; the threshold in use, if asked for
-// (`home`: where later steps and calls look for the state, when the last stage left it elsewhere)
-__global__ void kstate_export(const KState* st, int H, KState* home, int32_t* k_count, int32_t* full_flag,
-                              int32_t* stage_offs, const float* __restrict__ tau, float* __restrict__ tau_used) {
-  const int h = blockIdx.x * blockDim.x + threadIdx.x;
-  if (h == 0 && tau_used) tau_used[0] = tau[0];
-  if (h >= H) return;
-  const KState& s = st[h];
-  if (home != st) for (int i = 0; i < (int)(sizeof(KState) / 4); ++i) reinterpret_cast<int32_t*>(&home[h])[i] = reinterpret_cast<const int32_t*>(&s)[i];
-  if (k_count) k_count[h] = s.ccount;
-  if (full_flag) full_flag[h] = s.full;
-  if (stage_offs)
-    for (int i = 0; i <= ADACLUSTER_MAX_STAGES; ++i)
-      stage_offs[(size_t)h * (ADACLUSTER_MAX_STAGES + 1) + i] = (i <= s.stage) ? s.stage_offs[i] : s.ccount;
-}
-
 // ------------------------------------------------------------------------------------------
 // compactness (Sec. 3.2.1): MSE_h = mean_n || k_n - c(k_n) ||^2
 // ------------------------------------------------------------------------------------------
@@ -1819,9 +1838,9 @@ int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, in
                   const KState* st, const int32_t* ulist, const void* X, const void* cent_lp, const float* bias,
                   int32_t* labels, float* dist2, float* blk_sum, int32_t* blk_cnt, int P, int32_t* keep_lab,
                   float* keep_score, const int32_t* seed_lab, const float* seed_score, const float* tau, int32_t* keep_cnt,
-                  int keep_stride) {
+                  int keep_stride, double* dist_sum) {
   if ((mode == 3 || keep_lab || seed_lab) && (dtype != ADACLUSTER_BF16 || blk_sum)) return ADACLUSTER_E_INTERNAL;
-  AssignCfg c{mode, m_const, N, cap, st, ulist, keep_lab, keep_score, seed_lab, seed_score, tau, keep_cnt, keep_stride};
+  AssignCfg c{mode, m_const, N, cap, st, ulist, keep_lab, keep_score, seed_lab, seed_score, tau, keep_cnt, keep_stride, dist_sum};
   if (dtype == ADACLUSTER_BF16) {
     dim3 g((n_bound + ASSIGN_POINTS_LP - 1) / ASSIGN_POINTS_LP, H);
     const AccumOut ao{blk_sum, blk_cnt, P, (int)g.x};
@@ -1875,9 +1894,9 @@ int launch_finalize(hipStream_t s, int dtype, int d, int H, int mode, int m_cons
                     const float* pmin, const float* pmax, float* master, void* assign_lp, float* assign_f32,
                     float* bias, float* out_cent, const float* fallback, int32_t* out_sizes,
                     float* out_mean_norm, float* out_bmin, float* out_bmax, const int32_t* blk_cnt, int nb_stride,
-                    int nb_const) {
+                    int nb_const, const StateExport* ex) {
   FinalizeCfg c{mode, m_const, P, m_bound, cap, master_stride, st, spherical, update_assign,
-                dtype == ADACLUSTER_BF16, want_box, blk_cnt, nb_stride, nb_const};
+                dtype == ADACLUSTER_BF16, want_box, blk_cnt, nb_stride, nb_const, ex ? *ex : StateExport{}};
   // in final mode every row of the output (up to cap) gets a size, so cover cap rows
   dim3 g(((update_assign ? m_bound : cap) + FIN_ROWS - 1) / FIN_ROWS, H);
   if (d == 64)
@@ -1903,49 +1922,38 @@ int launch_update_direct(hipStream_t s, int d, int H, int N, int m_bound, int ca
   return chk();
 }
 
-int launch_init_centroids(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound,
-                          const KState* st, int spherical, int source_master, int cap,
+int launch_init_centroids(hipStream_t s, int dtype, int d, int H, int N, int m_const, int m_bound,
+                          KState* warm, const int32_t* k_count, const int32_t* full_flag, int spherical, int source_master, int cap,
                           int master_stride, const void* X, float* master, void* assign_lp, float* assign_f32,
                           float* bias) {
-  dim3 g(m_bound, H);
-  const int lp = dtype == ADACLUSTER_BF16;
+  dim3 g((m_bound + INIT_ROWS - 1) / INIT_ROWS, H);
+  const int lp = dtype == ADACLUSTER_BF16, nt = 64 * INIT_ROWS;
+  const WarmStart w{warm, k_count, full_flag};
   if (dtype == ADACLUSTER_BF16) {
-    if (d == 64) init_centroids<bf16raw, 64><<<g, 64, 0, s>>>((const bf16raw*)X, N, mode, m_const, st, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
-    else init_centroids<bf16raw, 128><<<g, 64, 0, s>>>((const bf16raw*)X, N, mode, m_const, st, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
+    if (d == 64) init_centroids<bf16raw, 64><<<g, nt, 0, s>>>((const bf16raw*)X, N, m_const, w, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
+    else init_centroids<bf16raw, 128><<<g, nt, 0, s>>>((const bf16raw*)X, N, m_const, w, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
   } else {
-    if (d == 64) init_centroids<float, 64><<<g, 64, 0, s>>>((const float*)X, N, mode, m_const, st, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
-    else init_centroids<float, 128><<<g, 64, 0, s>>>((const float*)X, N, mode, m_const, st, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
+    if (d == 64) init_centroids<float, 64><<<g, nt, 0, s>>>((const float*)X, N, m_const, w, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
+    else init_centroids<float, 128><<<g, nt, 0, s>>>((const float*)X, N, m_const, w, spherical, source_master, cap, master_stride, lp, master, assign_lp, assign_f32, bias);
   }
   return chk();
 }
 
-int launch_kstate_warm(hipStream_t s, KState* st, int H, int N, int cap, const int32_t* k_count,
-                       const int32_t* full_flag) {
-  kstate_warm<<<(H + 63) / 64, 64, 0, s>>>(st, H, N, cap, k_count, full_flag);
-  return chk();
-}
-
-int launch_kstate_commit(hipStream_t s, KState* st, int H) {
-  kstate_commit<<<(H + 63) / 64, 64, 0, s>>>(st, H);
-  return chk();
-}
-
-int launch_tau(hipStream_t s, int H, int N, const float* dist2, double* part, float factor, float tau_abs,
-               float* tau_out) {
-  if (tau_abs > 0.f) {
-    tau_set<<<1, 64, 0, s>>>(tau_abs, tau_out);
-    return chk();
-  }
-  const int nblk = (N + 1023) / 1024;
-  tau_partial<<<dim3(nblk, H), 256, 0, s>>>(dist2, N, nblk, part);
-  tau_final<<<1, 256, 0, s>>>(part, nblk * H, (double)H * (double)N, factor, tau_out);
+int launch_tau_abs(hipStream_t s, float tau_abs, float* tau_out) {
+  tau_set<<<1, 64, 0, s>>>(tau_abs, tau_out);
   return chk();
 }
 
 int stage_points_per_count(int dtype) { return dtype == ADACLUSTER_BF16 ? ASSIGN_POINTS_LP : ASSIGN_POINTS_F32; }
-int launch_keep_count(hipStream_t s, const KState* st, int H, int N, const float* dist2, const float* tau, int32_t* cnt,
-                      int cnt_stride, int* items) {
-  keep_count<<<dim3((N + KEEP_ITEMS - 1) / KEEP_ITEMS, H), 256, 0, s>>>(st, dist2, N, tau, cnt, cnt_stride);
+int launch_keep_count(hipStream_t s, int dtype, const KState* st, int H, int N, const float* dist2, const double* dist_sum, float factor,
+                      float* tau, int32_t* cnt, int cnt_stride, int* items) {
+  const int per = stage_points_per_count(dtype), count = dist_sum ? H * ((N + per - 1) / per) : 0;
+  TauCfg t{dist_sum, count, (double)H * (double)N, factor, tau};
+  if (count > TAU_SUMS) {
+    tau_final<<<1, 1024, 0, s>>>(t);
+    t.part = nullptr;
+  }
+  keep_count<<<dim3((N + KEEP_ITEMS - 1) / KEEP_ITEMS, H), 256, 0, s>>>(st, dist2, N, t, tau, cnt, cnt_stride);
   *items = KEEP_ITEMS;
   return chk();
 }
@@ -2021,12 +2029,6 @@ int launch_mse(hipStream_t s, int dtype, int d, int H, int N, int cap, const voi
 int launch_fill_i32(hipStream_t s, int32_t* p, size_t n, int32_t v) {
   if (n == 0) return 0;
   fill_i32<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p, n, v);
-  return chk();
-}
-
-int launch_kstate_export(hipStream_t s, const KState* st, int H, KState* home, int32_t* k_count, int32_t* full_flag,
-                         int32_t* stage_offs, const float* tau, float* tau_used) {
-  kstate_export<<<(H + 63) / 64, 64, 0, s>>>(st, H, home, k_count, full_flag, stage_offs, tau, tau_used);
   return chk();
 }
 

@@ -33,7 +33,7 @@ int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, in
                   int32_t* labels, float* dist2, float* blk_sum = nullptr, int32_t* blk_cnt = nullptr, int P = 0,
                   int32_t* keep_lab = nullptr, float* keep_score = nullptr, const int32_t* seed_lab = nullptr,
                   const float* seed_score = nullptr,
-                  const float* tau = nullptr, int32_t* keep_cnt = nullptr, int keep_stride = 0);
+                  const float* tau = nullptr, int32_t* keep_cnt = nullptr, int keep_stride = 0, double* dist_sum = nullptr);
 int assign_block_sum_centres();   // most centres the assignment kernel keeps block sums for
 int assign_block_sum_rows(int m); // rows per block of their table, with up to m centres
 int launch_seg_reduce(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int P,
@@ -41,13 +41,18 @@ int launch_seg_reduce(hipStream_t s, int dtype, int d, int H, int N, int mode, i
                       const int32_t* offs, int offs_stride, int32_t* poff, int32_t* pcl, float* psum, float* pnorm, float* pmin,
                       float* pmax, int poff_ready /* what launch_sort left, 1 or 2 */);
 int reduce_part_rows();
+// What the last launch of a key clustering leaves of its state: the state itself at `home`, and the outputs that are copies
+// of it (NULL: not asked for).
+struct StateExport {
+  KState* home; int32_t* k_count; int32_t* full_flag; int32_t* stage_offs; const float* tau; float* tau_used;
+};
 int launch_finalize(hipStream_t s, int dtype, int d, int H, int mode, int m_const, int m_bound, int P, int cap,
                     int master_stride, const KState* st, int spherical, int update_assign, int want_box,
                     const int32_t* offs, int offs_stride, const int32_t* poff, const float* psum, const float* pnorm,
                     const float* pmin, const float* pmax, float* master, void* assign_lp, float* assign_f32,
                     float* bias, float* out_cent, const float* fallback, int32_t* out_sizes,
                     float* out_mean_norm, float* out_bmin, float* out_bmax, const int32_t* blk_cnt = nullptr,
-                    int nb_stride = 0, int nb_const = 0);
+                    int nb_stride = 0, int nb_const = 0, const StateExport* ex = nullptr);
 // Centroid update of a running stage (state mode 1) in one launch, fp32 inputs: every centre's workgroup scans the
 // stage's label list (`ulist` NULL: positions are tokens), so it is for few points and centres only:
 // direct_update_fits() says when.  Writes what launch_finalize(update_assign = 1) writes.
@@ -61,14 +66,12 @@ int launch_update_direct(hipStream_t s, int d, int H, int N, int m_bound, int ca
 int qpass_walks(int N);
 int launch_qpass(hipStream_t s, int d, int H, int N, int m, int cap, int weighted, const void* X, const void* cent_lp,
                  const float* bias, float* psum, int32_t* pcnt);
-int launch_init_centroids(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound,
-                          const KState* st, int spherical, int source_master, int cap,
+// (warm: the states that a warm-started key clustering opens, with k_count and full_flag of the call before; NULL otherwise)
+int launch_init_centroids(hipStream_t s, int dtype, int d, int H, int N, int m_const, int m_bound,
+                          KState* warm, const int32_t* k_count, const int32_t* full_flag, int spherical, int source_master, int cap,
                           int master_stride, const void* X, float* master, void* assign_lp, float* assign_f32,
                           float* bias);
-int launch_kstate_warm(hipStream_t s, KState* st, int H, int N, int cap, const int32_t* k_count, const int32_t* full_flag);
-int launch_kstate_commit(hipStream_t s, KState* st, int H);
-int launch_tau(hipStream_t s, int H, int N, const float* dist2, double* part, float factor, float tau_abs,
-               float* tau_out);
+int launch_tau_abs(hipStream_t s, float tau_abs, float* tau_out);
 // What the end of a stage leaves behind for launch_stage_open: squared distances of its last pass and the survivors per
 // `items` points (launch_assign with keep_cnt counts per stage_points_per_count(), launch_keep_count per its own).
 struct StageFilter {
@@ -76,8 +79,9 @@ struct StageFilter {
   const int32_t* uin /* NULL: every token */; int32_t* uout; int32_t* stage_of /* may be NULL */; int stage;
 };
 int stage_points_per_count(int dtype);
-int launch_keep_count(hipStream_t s, const KState* st, int H, int N, const float* dist2, const float* tau, int32_t* cnt,
-                      int cnt_stride, int* items);
+// The threshold (with dist_sum, what launch_assign left; NULL: `tau` holds it) and the survivors of the first stage.
+int launch_keep_count(hipStream_t s, int dtype, const KState* st, int H, int N, const float* dist2, const double* dist_sum, float factor,
+                      float* tau, int32_t* cnt, int cnt_stride, int* items);
 // Filter of the stage that ends (f; NULL: none, the first stage opens), head of the loop of Algorithm 1, initial centres of
 // the stage that opens.  n_bound, m_bound: no head has more points in the stage that ends, or centres in the one that opens.
 // The state goes from `in` to `out`, which must differ; sums: 4 device integers; report (mapped host memory, may be
@@ -97,8 +101,6 @@ int launch_kstages_small(hipStream_t s, int d, int H, int N, int cap, int n_max,
 int launch_mse(hipStream_t s, int dtype, int d, int H, int N, int cap, const void* X, const int32_t* labels,
                const float* cent, double* part, float* mse);
 int launch_fill_i32(hipStream_t s, int32_t* p, size_t n, int32_t v);
-int launch_kstate_export(hipStream_t s, const KState* st, int H, KState* home, int32_t* k_count, int32_t* full_flag,
-                         int32_t* stage_offs, const float* tau = nullptr, float* tau_used = nullptr);
 
 int launch_select(hipStream_t s, int H, int Cq, int cap, int d, int score_mode, int select_mode, int topk,
                   float top_p, float scale, const float* q_cent, const float* q_mean_norm, const float* k_cent,
