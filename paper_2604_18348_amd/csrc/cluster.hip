@@ -31,7 +31,7 @@ struct AssignCfg {
   double* dist_sum;                                       // sum of the distances of this workgroup's points (the first stage's last
                                                           // pass, for tau): dist_sum[h * gridDim.x + workgroup]
 };
-constexpr int ASSIGN_POINTS_LP = 256, ASSIGN_POINTS_F32 = 128;     // points of an assignment workgroup
+constexpr int ASSIGN_POINTS_LP = 256, ASSIGN_POINTS_F32 = 64;     // points of an assignment workgroup
 
 __device__ __forceinline__ bool assign_setup(const AssignCfg& c, int h, int& n, int& m, int& row_off) {
   if (c.mode == 0) { n = c.N; m = c.m_const; row_off = 0; return true; }
@@ -551,82 +551,153 @@ __global__ __launch_bounds__(256, 2) void qpass_mfma(const bf16raw* __restrict__
   if (tid < m) pcnt[((size_t)h * NP + b) * ACC_MAXM + tid] = cnt_s[tid];
 }
 
-// fp32 I/O: one point per thread, centre chunks broadcast from LDS.
+// fp32 I/O: the same product with v_mfma_f32_32x32x2_f32.  A chain of these is, to the bit, the chain of fused multiply-adds
+// in ascending dimension order (step s contracts the dims 2s, from the lower half-wave, and 2s + 1, from the upper one), so
+// scores, labels and distances are those of a thread that takes its point's products one after the other.
+// A workgroup is 64 points, two groups of 32, and 128 centres at a time in LDS, a tile of 32 for each of four waves of either
+// group; the four meet at the end.  What bounds it is how few waves such calls have: the fp32 matrix rate is the vector rate,
+// but a wave here is 32 points x a quarter of the centres; with a point a thread against all of them (3 x 5 007 points: a
+// quarter of the SIMDs had a wave), an LDS read for every four multiply-adds, it was 47 us with 65 centres, d=128, and 184
+// with 288, now 11 and 19; 4 x 12 000 points, 100 centres 72 -> 25; 4 096, d=64, 32 centres 15 -> 5; 24 x 20 000, d=128, 65
+// and 1 024 centres 219 -> 184 and 2 690 -> 1 070 (118 TFLOP/s).  With rows straight into registers, every wave its own
+// copy, 16 instead of 11 us, and 381 instead of 184 in the large launch; 128 registers and two workgroups a CU: 239 -> 184.
+// Piece q (16 bytes) of centre row r sits in slot q ^ (r & 15) of its 256 bytes: a read of 32 rows meets every bank twice.
 template <int D>
-__global__ __launch_bounds__(128) void assign_f32(const float* __restrict__ X, AssignCfg cfg,
+__global__ __launch_bounds__(512, 4) void assign_f32(const float* __restrict__ X, AssignCfg cfg,
                                                   const float* __restrict__ cent,
                                                   const float* __restrict__ bias,
                                                   int32_t* __restrict__ labels, float* __restrict__ dist2) {
-  constexpr int CB = 32;
+  constexpr int NS = 4, PG = ASSIGN_POINTS_F32 / 32, CB = 32 * NS, ROWB = D * 4, PPR = D / 4, NT = 64 * NS * PG;
+  static_assert(NT == 512, "the launch bound");
   const int h = blockIdx.y;
   int n, m, row_off;
   if (!assign_setup(cfg, h, n, m, row_off)) return;
-  const int base = blockIdx.x * 128;
+  const int base = blockIdx.x * ASSIGN_POINTS_F32;
   if (base >= n) return;
-  const int tid = threadIdx.x;
-  const int p = base + tid;
-  __shared__ __attribute__((aligned(16))) float cs[CB * D];
-  __shared__ float bs[CB];
-  float x[D];
-  float xn2 = 0.f;
-  if (p < n) {
-    const int tok = cfg.ulist ? cfg.ulist[(size_t)h * cfg.N + p] : p;
-    const float4* row = reinterpret_cast<const float4*>(X + ((size_t)h * cfg.N + tok) * D);
-#pragma unroll
-    for (int q = 0; q < D / 4; ++q) {
-      const float4 v = row[q];
-      x[4 * q] = v.x; x[4 * q + 1] = v.y; x[4 * q + 2] = v.z; x[4 * q + 3] = v.w;
-    }
-#pragma unroll
-    for (int j = 0; j < D; ++j) xn2 = fmaf(x[j], x[j], xn2);
-  } else {
-#pragma unroll
-    for (int j = 0; j < D; ++j) x[j] = 0.f;
-  }
-  const float* ch = cent + ((size_t)h * cfg.cap + row_off) * D;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 31, hb = lane >> 5, pg = wave % PG, sp = wave / PG;     // (waves of the first tile on different SIMDs)
+  __shared__ __attribute__((aligned(16))) char cs[CB * ROWB];
+  __shared__ __attribute__((aligned(16))) float bs[CB];
+  __shared__ float sbest[NS][ASSIGN_POINTS_F32];
+  __shared__ int32_t sidx[NS][ASSIGN_POINTS_F32];
+  const char* ch = reinterpret_cast<const char*>(cent + ((size_t)h * cfg.cap + row_off) * D);
   const float* bh = bias + (size_t)h * cfg.cap + row_off;
+  const uint32_t cs0 = (uint32_t)(uintptr_t)(lds_void_t*)cs;
+  auto issue_chunk = [&](int c0) __attribute__((always_inline)) {       // whole tiles; rows past m repeat the last centre
+    const int rows = min(CB, (m - c0 + 31) & ~31);
+#pragma unroll
+    for (int i = 0; i < CB * PPR / NT; ++i) {
+      const int item = tid + i * NT, r = item / PPR, sl = item % PPR, q = (sl & ~15) | ((sl ^ r) & 15);
+      if (r < rows) dma_b128(cs0 + (wave * 64 + i * NT) * 16, ch + (size_t)min(c0 + r, m - 1) * ROWB + q * 16);
+    }
+    if (tid < CB) bs[tid] = c0 + tid < m ? bh[c0 + tid] : -INFINITY;
+  };
+  // The points come through LDS: beside the first chunk of centres where that leaves room, else before it.
+  const bool beside = m <= CB - ASSIGN_POINTS_F32;
+  char* const ps = cs + (beside ? (CB - ASSIGN_POINTS_F32) * ROWB : 0);
+#pragma unroll
+  for (int i = 0; i < ASSIGN_POINTS_F32 * PPR / NT; ++i) {
+    const int item = tid + i * NT, r = item / PPR, sl = item % PPR, q = (sl & ~15) | ((sl ^ r) & 15);
+    const int pr = min(base + r, n - 1), tok = cfg.ulist ? cfg.ulist[(size_t)h * cfg.N + pr] : pr;
+    dma_b128((uint32_t)(uintptr_t)(lds_void_t*)ps + (wave * 64 + i * NT) * 16, reinterpret_cast<const char*>(X + ((size_t)h * cfg.N + tok) * D) + q * 16);
+  }
+  if (beside && m > 0) issue_chunk(0);
+  const int p = base + pg * 32 + c;
+  float x[D / 2], xn2 = 0.f;            // this half-wave's dims: 2s + hb
+  wait_vmcnt<0>();
+  __syncthreads();
+  {
+    const char* row = ps + (pg * 32 + c) * ROWB;
+    const int sw = (c & 15) * 16;
+#pragma unroll
+    for (int q = 0; q < PPR; ++q) {
+      const float* a = reinterpret_cast<const float*>(row + ((((q & 15) * 16) ^ sw) + (q >> 4) * 256) + hb * 4);
+      x[2 * q] = a[0]; x[2 * q + 1] = a[2];
+    }
+    if (dist2 && sp == 0) {
+#pragma unroll 8
+      for (int q = 0; q < PPR; ++q) {
+        const float4 v = *reinterpret_cast<const float4*>(row + ((((q & 15) * 16) ^ sw) + (q >> 4) * 256));
+        xn2 = fmaf(v.x, v.x, xn2); xn2 = fmaf(v.y, v.y, xn2); xn2 = fmaf(v.z, v.z, xn2); xn2 = fmaf(v.w, v.w, xn2);
+      }
+    }
+  }
+  if (!beside) {
+    __syncthreads();
+    issue_chunk(0);
+  }
   float best = -INFINITY; int bidx = 0;
   for (int c0 = 0; c0 < m; c0 += CB) {
+    wait_vmcnt<0>();                    // this wave's pieces of the chunk are in LDS
     __syncthreads();
-    for (int i = tid; i < CB * D / 4; i += 128) {
-      const int r = i / (D / 4);
-      float4 v = {0.f, 0.f, 0.f, 0.f};
-      if (c0 + r < m) v = reinterpret_cast<const float4*>(ch + (size_t)c0 * D)[i];
-      reinterpret_cast<float4*>(cs)[i] = v;
-    }
-    if (tid < CB) bs[tid] = (c0 + tid < m) ? bh[c0 + tid] : -INFINITY;
-    __syncthreads();
-    const int rmax = min(CB, m - c0);
-    for (int r = 0; r < rmax; ++r) {
-      float s = 0.f;
+    const int j0 = c0 + sp * 32;
+    if (j0 < m) {
+      f32x16_t acc;
 #pragma unroll
-      for (int q = 0; q < D / 4; ++q) {
-        const float4 v = *reinterpret_cast<const float4*>(&cs[r * D + 4 * q]);
-        s = fmaf(x[4 * q], v.x, s); s = fmaf(x[4 * q + 1], v.y, s);
-        s = fmaf(x[4 * q + 2], v.z, s); s = fmaf(x[4 * q + 3], v.w, s);
+      for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+      const char* tile = cs + sp * 32 * ROWB;
+      const int a0 = c * ROWB + ((c & 15) * 16) + hb * 4;
+      auto piece = [&](int q) __attribute__((always_inline)) {       // dims 4q + hb and 4q + 2 + hb of row c
+        const float* a = reinterpret_cast<const float*>(tile + ((a0 ^ ((q & 15) * 16)) + (q >> 4) * 256));
+        return float2{a[0], a[2]};
+      };
+      constexpr int AHEAD = 4;
+      float2 kb[AHEAD];
+#pragma unroll
+      for (int q = 0; q < AHEAD; ++q) kb[q] = piece(q);
+#pragma unroll
+      for (int q = 0; q < PPR; ++q) {
+        const float2 a = kb[q % AHEAD];
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, x[2 * q], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, x[2 * q + 1], acc, 0, 0, 0);
+        if (q + AHEAD < PPR) kb[q % AHEAD] = piece(q + AHEAD);
       }
-      s += bs[r];
-      if (s > best) { best = s; bidx = c0 + r; }
+      // value v is centre j0 + 8*(v/4) + 4*hb + v%4: ascending in v
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int jr = 8 * (v >> 2) + 4 * hb + (v & 3);
+        const float s = acc[v] + bs[sp * 32 + jr];
+        if (s > best) { best = s; bidx = j0 + jr; }
+      }
+    }
+    if (c0 + CB < m) {
+      __syncthreads();                  // every wave is done with the chunk
+      issue_chunk(c0 + CB);
     }
   }
-  const float d2 = fmaxf(xn2 - 2.f * best, 0.f);
-  if (p < n) {
+  {
+    const float ob = __shfl_xor(best, 32);
+    const int oi = __shfl_xor(bidx, 32);
+    if (ob > best || (ob == best && oi < bidx)) { best = ob; bidx = oi; }
+  }
+  if (hb == 0) { sbest[sp][pg * 32 + c] = best; sidx[sp][pg * 32 + c] = bidx; }
+  __syncthreads();
+  const bool mine = sp == 0 && hb == 0 && p < n;
+  float d2 = 0.f;
+  if (mine) {
+#pragma unroll
+    for (int w = 1; w < NS; ++w) {
+      const float ob = sbest[w][pg * 32 + c];
+      const int oi = sidx[w][pg * 32 + c];
+      if (ob > best || (ob == best && oi < bidx)) { best = ob; bidx = oi; }
+    }
+    d2 = fmaxf(xn2 - 2.f * best, 0.f);
     labels[(size_t)h * cfg.N + p] = bidx;
     if (dist2) dist2[(size_t)h * cfg.N + p] = d2;
   }
   if (cfg.keep_cnt && dist2) {
-    __shared__ int32_t wkept[2];
-    const uint64_t kept = __ballot(p < n && !(d2 < cfg.tau[1]));
-    if ((tid & 63) == 0) wkept[tid >> 6] = __popcll(kept);
+    __shared__ int32_t wkept[PG];
+    const uint64_t kept = __ballot(mine && !(d2 < cfg.tau[1]));
+    if (sp == 0 && lane == 0) wkept[pg] = __popcll(kept);
     __syncthreads();
     if (tid == 0) cfg.keep_cnt[(size_t)h * cfg.keep_stride + blockIdx.x] = wkept[0] + wkept[1];
   }
   if (cfg.dist_sum) {
-    double dsum = p < n ? (double)sqrtf(d2) : 0.0;
+    double dsum = mine ? (double)sqrtf(d2) : 0.0;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) dsum += __shfl_xor(dsum, o);
-    __shared__ double wsum[2];
-    if ((tid & 63) == 0) wsum[tid >> 6] = dsum;
+    for (int o = 1; o < 32; o <<= 1) dsum += __shfl_xor(dsum, o);      // (the upper half-wave holds zeros)
+    __shared__ double wsum[PG];
+    if (sp == 0 && lane == 0) wsum[pg] = dsum;
     __syncthreads();
     if (tid == 0) cfg.dist_sum[(size_t)h * gridDim.x + blockIdx.x] = wsum[0] + wsum[1];
   }
@@ -672,24 +743,13 @@ template <> struct Vec16<float> {
   }
 };
 
-template <typename T, int D>
-__global__ __launch_bounds__(64) void seg_reduce(const T* __restrict__ X, ReduceCfg cfg,
-                                                 const int32_t* __restrict__ perm,
-                                                 const int32_t* __restrict__ offs, int offs_stride,
-                                                 const int32_t* __restrict__ poff, const int32_t* __restrict__ pcl,
-                                                 float* __restrict__ psum, float* __restrict__ pnorm,
-                                                 float* __restrict__ pmin, float* __restrict__ pmax) {
-  constexpr int EV = Vec16<T>::N;     // elements per 16-byte load
-  constexpr int LPR = D / EV;         // lanes per row
-  constexpr int RPI = 64 / LPR;       // rows per wave step
-  const int h = blockIdx.y;
-  int m;
-  if (!reduce_setup(cfg, h, m)) return;
-  // part b of this head -> (cluster j, part index): parts of REDUCE_ROWS rows, clusters in order
+// Part b of head h -> its rows in the sorted order, mb .. me (parts of REDUCE_ROWS rows, clusters in order).  By every lane of
+// a wave.  False: the head has no such part.
+__device__ __forceinline__ bool find_part(const ReduceCfg& cfg, int h, int b, int m, int lane, const int32_t* __restrict__ offs,
+                                          int offs_stride, const int32_t* __restrict__ poff, const int32_t* __restrict__ pcl,
+                                          int& mb, int& me) {
   const int32_t* po = poff + (size_t)h * offs_stride;
   const int32_t* of = offs + (size_t)h * offs_stride;
-  const int b = blockIdx.x;
-  const int lane = threadIdx.x, slot = lane / LPR, cl = lane % LPR;
   int j, part, beg, end;
   if (m <= 128) {
     // few clusters: every lane takes two entries of both tables in one round trip and the
@@ -698,7 +758,7 @@ __global__ __launch_bounds__(64) void seg_reduce(const T* __restrict__ X, Reduce
     const int p0 = a0 <= m ? po[a0] : INT32_MAX, p1 = a1 <= m ? po[a1] : INT32_MAX;
     const int o0 = a0 <= m ? of[a0] : 0, o1 = a1 <= m ? of[a1] : 0;
     const int o2 = of[m], ptotal = po[m];
-    if (b >= ptotal) return;
+    if (b >= ptotal) return false;
     // entries 0..m-1 are cluster starts, entry m is the total
     const int cnt = __popcll(__ballot(a0 < m && p0 <= b)) + __popcll(__ballot(a1 < m && p1 <= b));
     j = cnt - 1;
@@ -708,7 +768,7 @@ __global__ __launch_bounds__(64) void seg_reduce(const T* __restrict__ X, Reduce
     const int jn = j + 1;
     end = jn == m ? o2 : (jn < 64 ? __shfl(o0, jn) : __shfl(o1, jn - 64));
   } else {
-    if (b >= po[m]) return;
+    if (b >= po[m]) return false;
     if (pcl) {
       j = pcl[(size_t)h * cfg.P + b];
     } else {
@@ -719,8 +779,26 @@ __global__ __launch_bounds__(64) void seg_reduce(const T* __restrict__ X, Reduce
     part = b - po[j];
     beg = of[j]; end = of[j + 1];
   }
-  const int mb = beg + part * REDUCE_ROWS;
-  const int me = min(end, mb + REDUCE_ROWS);
+  mb = beg + part * REDUCE_ROWS;
+  me = min(end, mb + REDUCE_ROWS);
+  return true;
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(64) void seg_reduce(const T* __restrict__ X, ReduceCfg cfg,
+                                                 const int32_t* __restrict__ perm,
+                                                 const int32_t* __restrict__ offs, int offs_stride,
+                                                 const int32_t* __restrict__ poff, const int32_t* __restrict__ pcl,
+                                                 float* __restrict__ psum, float* __restrict__ pnorm,
+                                                 float* __restrict__ pmin, float* __restrict__ pmax) {
+  constexpr int EV = Vec16<T>::N;     // elements per 16-byte load
+  constexpr int LPR = D / EV;         // lanes per row
+  constexpr int RPI = 64 / LPR;       // rows per wave step
+  const int h = blockIdx.y, b = blockIdx.x;
+  int m, mb, me;
+  if (!reduce_setup(cfg, h, m)) return;
+  const int lane = threadIdx.x, slot = lane / LPR, cl = lane % LPR;
+  if (!find_part(cfg, h, b, m, lane, offs, offs_stride, poff, pcl, mb, me)) return;
   const int32_t* pm = perm + (size_t)h * cfg.N;
   const T* Xh = X + (size_t)h * cfg.N * D + cl * EV;
   float acc[EV], mn[EV], mx[EV];
@@ -1854,8 +1932,8 @@ int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, in
   } else {
     if (blk_sum) return ADACLUSTER_E_INTERNAL;     // block sums exist for bf16 only
     dim3 g((n_bound + ASSIGN_POINTS_F32 - 1) / ASSIGN_POINTS_F32, H);
-    if (d == 64) assign_f32<64><<<g, 128, 0, s>>>((const float*)X, c, (const float*)cent_lp, bias, labels, dist2);
-    else assign_f32<128><<<g, 128, 0, s>>>((const float*)X, c, (const float*)cent_lp, bias, labels, dist2);
+    if (d == 64) assign_f32<64><<<g, 512, 0, s>>>((const float*)X, c, (const float*)cent_lp, bias, labels, dist2);
+    else assign_f32<128><<<g, 512, 0, s>>>((const float*)X, c, (const float*)cent_lp, bias, labels, dist2);
   }
   return chk();
 }

@@ -125,6 +125,22 @@ def test_qcluster_without_normalisation_chained(dtype, d, N, Cq):
             assert mn[h, j] == 1.0
 
 
+@pytest.mark.parametrize("d,N,Cq", [(64, 63, 1), (64, 64, 32), (128, 65, 33), (64, 500, 128), (128, 500, 129), (128, 700, 300)])
+def test_fp32_assignment_at_tile_edges(d, N, Cq):
+    """64 points a workgroup, tiles of 32 centres over four waves, 128 centres at a time.  Rows of small integers make every
+    score exact in any order, and rows that repeat make the best centre a tie, often between tiles: the lowest index wins."""
+    H = 2
+    rng = np.random.default_rng(29)
+    Q = rng.integers(-2, 3, (H, max(2, N // 3), d)).astype(np.float32)[:, rng.integers(0, max(2, N // 3), N)]
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=Cq, q_iters=1, k_m0=4, k_m_min=1, k_max_clusters=8, q_no_norm=1)
+    out = B.adacluster_qcluster(p, to_dev(Q, B.F32))
+    lab, ca = out["q_labels"].cpu().numpy(), to_np(out["q_assign_centroids"])
+    for h in range(H):
+        X = Q[h].astype(np.float64)
+        assert np.array_equal(ca[h], X[((2 * np.arange(Cq) + 1) * N) // (2 * Cq)])
+        assert np.array_equal(lab[h], (X @ ca[h].T - 0.5 * (ca[h] ** 2).sum(1)).argmax(1))
+
+
 def test_qcluster_free_running_fp32_matches_oracle_trajectory():
     H, N, d, Cq = 1, 2000, 64, 12
     Q, _, _ = wl.make_small(12, N, d, 12, dtype="f32", H=H)
