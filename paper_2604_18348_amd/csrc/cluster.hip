@@ -883,6 +883,77 @@ __global__ __launch_bounds__(64) void seg_reduce(const T* __restrict__ X, Reduce
   }
 }
 
+// The same sums, to the bit, for the fp32 query clustering in small launches: four waves a part, which load and normalise all
+// of its rows at once and leave them in LDS; then a thread takes a column and the rows of one slot in ascending order, and
+// the slots meet in the same tree.  A wave alone takes its part's rows in up to four dependent rounds and spends sixty
+// instructions at half rate on every row it normalises: 318 parts, d=128, 26 us, here 14; 780 parts 31 and 18; d=64, 640
+// parts 17 and 15.  From some 1 500 parts on the waves are enough (5 352: 55 us, here 131).
+static constexpr int REDUCE_FEW = 1024;
+template <int D>
+__global__ __launch_bounds__(256) void seg_reduce_few(const float* __restrict__ X, ReduceCfg cfg,
+                                                      const int32_t* __restrict__ perm,
+                                                      const int32_t* __restrict__ offs, int offs_stride,
+                                                      const int32_t* __restrict__ poff, const int32_t* __restrict__ pcl,
+                                                      float* __restrict__ psum, float* __restrict__ pnorm) {
+  constexpr int LPR = D / 4, RPI = 64 / LPR, STEPS = REDUCE_ROWS / (4 * RPI);
+  static_assert(RPI * D == 256, "a thread a column and slot");
+  const int h = blockIdx.y, b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int slot = lane / LPR, cl = lane % LPR;
+  int m, mb, me;
+  if (!reduce_setup(cfg, h, m)) return;
+  if (!find_part(cfg, h, b, m, lane, offs, offs_stride, poff, pcl, mb, me)) return;
+  __shared__ __attribute__((aligned(16))) float xs[REDUCE_ROWS][D];
+  __shared__ float norms[REDUCE_ROWS];
+  __shared__ float red[RPI][D];
+  const int rows = me - mb;
+  const int32_t* pm = perm + (size_t)h * cfg.N + mb;
+  const float* Xh = X + (size_t)h * cfg.N * D + cl * 4;
+  int tok[STEPS];
+#pragma unroll
+  for (int u = 0; u < STEPS; ++u) tok[u] = pm[min((u * 4 + wave) * RPI + slot, rows - 1)];
+  float4 x[STEPS];
+#pragma unroll
+  for (int u = 0; u < STEPS; ++u) x[u] = *reinterpret_cast<const float4*>(Xh + (size_t)tok[u] * D);
+#pragma unroll
+  for (int u = 0; u < STEPS; ++u) {
+    const int k = (u * 4 + wave) * RPI + slot;       // (rows past the end repeat the last one and are not summed)
+    float ss = fmaf(x[u].x, x[u].x, 0.f);
+    ss = fmaf(x[u].y, x[u].y, ss); ss = fmaf(x[u].z, x[u].z, ss); ss = fmaf(x[u].w, x[u].w, ss);
+#pragma unroll
+    for (int o = 1; o < LPR; o <<= 1) ss += __shfl_xor(ss, o);
+    const float nrm = sqrtf(ss);
+    const float inv = 1.0f / fmaxf(nrm, 1e-12f);
+    if (cl == 0) norms[k] = nrm;
+    *reinterpret_cast<float4*>(&xs[k][cl * 4]) = float4{x[u].x * inv, x[u].y * inv, x[u].z * inv, x[u].w * inv};
+  }
+  __syncthreads();
+  {
+    const int col = tid % D, s = tid / D;
+    float acc = 0.f;
+#pragma unroll 8
+    for (int r = s; r < rows; r += RPI) acc += xs[r][col];
+    red[s][col] = acc;
+  }
+  if (tid < RPI) {                                   // norms: a slot a lane, then the slots
+    float ns = 0.f;
+#pragma unroll 8
+    for (int r = tid; r < rows; r += RPI) ns += norms[r];
+#pragma unroll
+    for (int o = RPI / 2; o >= 1; o >>= 1) ns += __shfl_down(ns, o);
+    if (tid == 0) pnorm[(size_t)h * cfg.P + b] = ns;
+  }
+  __syncthreads();
+  if (tid >= D) return;
+  float a[RPI];
+#pragma unroll
+  for (int s = 0; s < RPI; ++s) a[s] = red[s][tid];
+#pragma unroll
+  for (int o = RPI / 2; o >= 1; o >>= 1)
+#pragma unroll
+    for (int s = 0; s < o; ++s) a[s] += a[s + o];
+  psum[((size_t)h * cfg.P + b) * D + tid] = a[0];
+}
+
 // Combine the parts and write centres.
 //   update_assign = 1 (Lloyd step): non-empty clusters get master := mean (or unit mean), the
 //     I/O-dtype copy used by the next assignment, its fp32 image and the arg-max bias.
@@ -1959,6 +2030,9 @@ int launch_seg_reduce(hipStream_t s, int dtype, int d, int H, int N, int mode, i
   if (dtype == ADACLUSTER_BF16) {
     if (d == 64) seg_reduce<bf16raw, 64><<<g, 64, 0, s>>>((const bf16raw*)X, c, perm, offs, offs_stride, poff, pcl, psum, pnorm, pmin, pmax);
     else seg_reduce<bf16raw, 128><<<g, 64, 0, s>>>((const bf16raw*)X, c, perm, offs, offs_stride, poff, pcl, psum, pnorm, pmin, pmax);
+  } else if (normalize && !want_box && (long long)P * H <= REDUCE_FEW) {
+    if (d == 64) seg_reduce_few<64><<<g, 256, 0, s>>>((const float*)X, c, perm, offs, offs_stride, poff, pcl, psum, pnorm);
+    else seg_reduce_few<128><<<g, 256, 0, s>>>((const float*)X, c, perm, offs, offs_stride, poff, pcl, psum, pnorm);
   } else {
     if (d == 64) seg_reduce<float, 64><<<g, 64, 0, s>>>((const float*)X, c, perm, offs, offs_stride, poff, pcl, psum, pnorm, pmin, pmax);
     else seg_reduce<float, 128><<<g, 64, 0, s>>>((const float*)X, c, perm, offs, offs_stride, poff, pcl, psum, pnorm, pmin, pmax);
