@@ -21,6 +21,7 @@ static constexpr int TILE_REC = 8;       // ints per query-tile record (32 bytes
 static constexpr int SPLIT_SLOTS = 128;  // partial slots per head for the chunks of cut key lists
 static constexpr int F32_WAVES = 4;      // waves of a workgroup of the fp32 kernel
 static constexpr int F32_MAX_SPLITS = 4; // most workgroups the fp32 kernel splits a key list over
+__host__ __device__ constexpr int f32_resident(int d) { return 32 * (d == 64 ? 3 : 2); }   // of its workgroups on the 32 CUs of an XCD
 static constexpr float PART_DONE = -1.f; // in place of the sum of a row's first partial result: the row is written
 static constexpr int KROW_PAD = 8 * 64;  // entries of the row-offset table a key list is padded by: the kernel reads up to 7 tiles ahead
 
@@ -326,6 +327,7 @@ struct AttnArgs {
   const int32_t* krow; size_t kstride;   // every key row of a query cluster's list (byte offset, fp32: row number): [H][Cq][kstride]
   const int32_t* rng_start; const int32_t* rng_pre; const int32_t* rng_cnt; int maxr;   // the ranges it was written from, and
   const int32_t* perm_k;                 // their order -> token (NULL: identity): for the fp32 kernel without a table
+  int splits;                            // fp32: most pieces a key list may go in
 };
 
 // Workgroup -> (head, query tile) of a launch of pick_tile_grid.  Workgroups go to the 8 XCDs round-robin in launch order,
@@ -338,15 +340,36 @@ struct AttnArgs {
 // the search costs a trip to memory per 64 heads, and past 2^32 threads a grid dimension ends.  Calls of 70, 150 and 256
 // heads of 2 000 rows, d=64, 33 clusters 288, 579 and 975 us by search, 331, 664 and 1 107 by rows; of 1 000 rows and 200 clusters
 // 228, 456, 802 and 216, 417, 704; 1 024 heads of 128 rows 718 by rows (by search, when tiles were 64 rows, 1 625).
+// With `splits` > 1 the key lists of the tiles that would not fill the chip once more are split: an XCD runs `resident`
+// workgroups at a time, and the tiles past the last whole round of them (all of them in a small launch) go in pieces, some
+// 1.6 per place (z says which), so that no CU is left with a whole one when the others are done.  585 tiles, d=128, are 75
+// an XCD that holds 64 workgroups: 64 whole and 11 in four pieces, 198 us; all of them in two pieces, three rounds, 222.
 // Returns false where the list has ended.
 constexpr int PICK_HEADS = 256;
-__device__ __forceinline__ bool pick_tile(const int32_t* __restrict__ ntiles, int H, int& h, int& tile) {
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, lane = threadIdx.x & 63;
+__device__ __forceinline__ bool pick_tile(const int32_t* __restrict__ ntiles, int H, int splits, int resident, int& h, int& tile,
+                                          int& z, int& sp) {
+  const int xcd = blockIdx.x & 7, lane = threadIdx.x & 63;
+  int slot = blockIdx.x >> 3;
+  z = 0; sp = 1;
   if (H > PICK_HEADS) {
     h = blockIdx.y;
     const int nt = ntiles[h], w = (nt + 7) >> 3;
     tile = xcd * w + slot;
     return slot < w && tile < nt;
+  }
+  if (splits > 1) {
+    int total = 0;
+    for (int h0 = 0; h0 < H; h0 += 64) total += h0 + lane < H ? (ntiles[h0 + lane] + 7) >> 3 : 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) total += __shfl_xor(total, o);
+    const int rest = total % resident, whole = total - rest;
+    if (slot >= whole) {
+      if (rest == 0) return false;
+      sp = max(1, min(splits, (8 * resident / 5 + rest / 2) / rest));
+      z = (slot - whole) / rest;                           // (first pieces first: short lists have no others, which end at once)
+      if (z >= sp) return false;
+      slot -= z * rest;
+    }
   }
   int base = 0;
   for (int h0 = 0; h0 < H; h0 += 64) {                     // 64 heads at a time, one per lane
@@ -793,8 +816,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
 // Slot s (16 bytes) of row r holds piece s ^ (r & 15): the operand reads of 16 consecutive rows hit 16 bank groups.
 // What bounds the path: the fp32 matrix rate (a product of 32x32x2 holds the pipe for 64 cycles) once there are
 // workgroups enough, which is why the key list is split: over the waves, and where the launch is small (4 096
-// queries are 128 tiles for 256 CUs) over gridDim.z workgroups as well, which leave unnormalised partial results
-// that attn_merge_f32 combines (see attn_f32_splits), lists too short for that aside.  Vector instructions do not run under an fp32 product on this chip
+// queries are 128 tiles for 256 CUs) over up to four workgroups as well, which leave unnormalised partial results
+// that attn_merge_f32 combines (see pick_tile), lists too short for that aside.  Vector instructions do not run under an fp32 product on this chip
 // (the co-execution counter reads 0), so every one of them adds its four cycles: the masks are for the last tile
 // only, the accumulator is rescaled only when the maximum has moved, and addresses inside a head are 32-bit offsets.
 // Without these the 545 vector instructions a tile took a fifth of the time.
@@ -808,16 +831,16 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
 template <int D, bool LISTED>
 __global__ __launch_bounds__(F32_WAVES * 64, D == 64 ? 3 : 2) void attn_f32(AttnArgs a) {
   constexpr int BN = 32, DB = D / 32, NW = F32_WAVES, SROW = D + 4, PPR = D / 4, RPI = 64 / PPR;   // 16-byte pieces a row, rows a load
-  int h, tile;
-  if (!pick_tile(a.ntiles, a.H, h, tile)) return;
+  int h, tile, z, sp;
+  if (!pick_tile(a.ntiles, a.H, a.splits, f32_resident(D), h, tile, z, sp)) return;
   const int32_t* tl = a.tiles + ((size_t)h * a.maxtiles + tile) * TILE_REC;          // (key lists are never cut for fp32)
   const int qc = tl[0], row0 = tl[1], nrows = tl[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, hb = lane >> 5;
   const int total = tl[6], T = (total + BN - 1) / BN;
-  // The workgroups that share this list: not more than its tiles give work to (the launch only knows the most), the
-  // others end here.  A list of a single one is written out by it.
-  const int z = blockIdx.z, splits = min((int)gridDim.z, max(1, (T + NW - 1) / NW));
+  // The workgroups that share this list: not more than its tiles give work to, the others end here.  A list of a single one
+  // is written out by it.
+  const int splits = min(sp, max(1, (T + NW - 1) / NW));
   if (z >= splits) return;
   const int32_t* kr = a.krow + ((size_t)h * a.Cq + qc) * a.kstride;           // key rows of the list, in order
   const float* Qh = (const float*)a.Q + (size_t)h * a.N * D;
@@ -1010,14 +1033,14 @@ __global__ __launch_bounds__(F32_WAVES * 64, D == 64 ? 3 : 2) void attn_f32(Attn
     L = fmaf(wt[w], sl[w][r], L);
   }
   float inv, *out;
-  const size_t pr = ((size_t)h * gridDim.z + z) * a.N + row0 + r;
+  const size_t pr = ((size_t)h * a.splits + z) * a.N + row0 + r;
   if (splits > 1) {                                        // a partial result: as it is, with its reference and sum
     inv = 1.f;
     out = a.part_o + pr * D;
     if (col == 0) {
       a.part_ml[pr * 2] = M; a.part_ml[pr * 2 + 1] = L;
-      if (z == 0)                                          // what the workgroups without work leave
-        for (int u = splits; u < (int)gridDim.z; ++u) {
+      if (z == 0)                                          // what the pieces that there are not leave
+        for (int u = splits; u < a.splits; ++u) {
           a.part_ml[(pr + (size_t)u * a.N) * 2] = -INFINITY; a.part_ml[(pr + (size_t)u * a.N) * 2 + 1] = 0.f;
         }
     }
@@ -1025,7 +1048,7 @@ __global__ __launch_bounds__(F32_WAVES * 64, D == 64 ? 3 : 2) void attn_f32(Attn
     if (!(M > -INFINITY) && total > 0) L = NAN;
     inv = L > 0.f ? 1.0f / L : L;
     out = (float*)a.O + ((size_t)h * a.N + (pq ? pq[row0 + r] : row0 + r)) * D;
-    if (gridDim.z > 1 && col == 0) a.part_ml[pr * 2 + 1] = PART_DONE;
+    if (a.splits > 1 && col == 0) a.part_ml[pr * 2 + 1] = PART_DONE;
   }
 #pragma unroll
   for (int cc = 0; cc < D; cc += TPQ * 4) {
@@ -1048,14 +1071,16 @@ __global__ __launch_bounds__(256) void attn_merge_f32(AttnArgs a, int splits) {
   if (pos >= a.N) return;
   if (a.part_ml[((size_t)h * splits * a.N + pos) * 2 + 1] == PART_DONE) return;
   float M = -INFINITY, L = 0.f, ms[F32_MAX_SPLITS], ls[F32_MAX_SPLITS];
-  float4 os[F32_MAX_SPLITS], x = {0.f, 0.f, 0.f, 0.f};
+  float4 os[F32_MAX_SPLITS] = {}, x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int z = 0; z < F32_MAX_SPLITS; ++z) {
     const size_t pr = ((size_t)h * splits + min(z, splits - 1)) * a.N + pos;
     ms[z] = z < splits ? a.part_ml[pr * 2] : -INFINITY;
     ls[z] = a.part_ml[pr * 2 + 1];
-    os[z] = *reinterpret_cast<const float4*>(a.part_o + pr * D + col);
   }
+#pragma unroll
+  for (int z = 0; z < F32_MAX_SPLITS; ++z)                 // (pieces that there are not have no row)
+    if (ms[z] > -INFINITY) os[z] = *reinterpret_cast<const float4*>(a.part_o + (((size_t)h * splits + z) * a.N + pos) * D + col);
 #pragma unroll
   for (int z = 0; z < F32_MAX_SPLITS; ++z) M = fmaxf(M, ms[z]);
 #pragma unroll
@@ -1164,9 +1189,9 @@ int attn_block_rows_min(int dtype) { return dtype == ADACLUSTER_BF16 ? 128 : 32;
 int attn_block_rows_max(int dtype) { return dtype == ADACLUSTER_BF16 ? 256 : 32; }
 
 // The launch of a kernel that takes its tiles by pick_tile: `most` bounds the tiles of a head.
-static dim3 pick_tile_grid(int H, int most, int z) {
+static dim3 pick_tile_grid(int H, int most, int splits, int resident) {
   const unsigned x = (most + 7) / 8 * 8;
-  return H > PICK_HEADS ? dim3(x, H, z) : dim3(H * x, 1, z);
+  return H > PICK_HEADS ? dim3(x, H) : splits > 1 ? dim3(H * x + min((splits - 1) * H * x, 8 * 3 * resident)) : dim3(H * x);
 }
 
 size_t attn_krow_stride(int N) { return (size_t)(N + 63) / 64 * 64 + KROW_PAD; }
@@ -1186,13 +1211,11 @@ bool attn_rows_listed(int dtype, int d, int H, int N, int Cq) {
 int attn_tile_record() { return TILE_REC; }
 int attn_split_slots() { return SPLIT_SLOTS; }
 
-// Most workgroups a key list of the fp32 kernel is split over (a list takes no more than its tiles feed), enough for four a
-// CU: a CU holds two (d=128), and with fewer the CUs that are left over, or the last workgroups to run, are what a launch
-// with long lists waits for.  Kernel and merge with targets of 128, 512 and 1 024 workgroups: dense 1 x 4 096 (d=128) 149, 83
-// and 83 us; one head of 4 096 queries (d=64, a quarter of the keys) 28 us and three of 5 007 (d=128, a third) 197 us with any.
+// Most pieces a key list of the fp32 kernel may go in (see pick_tile).  From some 1 024 tiles on there are two rounds of whole
+// ones (d=128), and the partial results of every row and the launch that combines them cost what the last round leaves idle
+// (150 heads of 200 rows: 58 us whole, 66 in pieces).
 int attn_f32_splits(int H, int N, int Cq) {
-  const long long wgs = (long long)H * (N / 32 + Cq / 2 + 1);
-  return (int)min((long long)F32_MAX_SPLITS, (1024 + wgs - 1) / wgs);
+  return H <= PICK_HEADS && (long long)H * (N / 32 + Cq / 2 + 1) < 1024 ? F32_MAX_SPLITS : 1;
 }
 
 int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
@@ -1223,7 +1246,7 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
              scale * 1.4426950408889634f,
              (Cq == 1 || (size_t)4 * N * d <= ((size_t)8 << 20)) ? 1 : 0,
              part_o, part_ml, SPLIT_SLOTS, attn_block_rows(dtype, d, N, Cq), krow, kstride,
-             rng_start, rng_pre, rng_cnt, maxr, perm_k};
+             rng_start, rng_pre, rng_cnt, maxr, perm_k, dtype == ADACLUSTER_F32 ? attn_f32_splits(H, N, Cq) : 1};
   dim3 g((maxtiles + 7) / 8 * 8, H);
   if (dtype == ADACLUSTER_BF16) {
     if (attn_small_shape(N, Cq)) {
@@ -1238,8 +1261,8 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
       else attn_merge<128><<<dim3(SPLIT_SLOTS, H, 4), 256, 0, s>>>(a, merge, nmerge);
     }
   } else {
-    const int splits = attn_f32_splits(H, N, Cq);
-    const dim3 g2 = pick_tile_grid(H, min(N, N / 32 + Cq + 1), splits), gm((N + 1024 / d - 1) / (1024 / d), H);
+    const int splits = a.splits;
+    const dim3 g2 = pick_tile_grid(H, min(N, N / 32 + Cq + 1), splits, f32_resident(d)), gm((N + 1024 / d - 1) / (1024 / d), H);
     if (d == 64) { if (krow) attn_f32<64, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<64, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
     else { if (krow) attn_f32<128, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<128, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
     if (splits > 1) {
