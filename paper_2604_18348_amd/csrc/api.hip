@@ -164,7 +164,7 @@ int check_params(const adacluster_params* p) {
   return 0;
 }
 
-constexpr int STAGE_SUM_BLOCKS = 128;   // a stage of at most this many 256-point blocks may update from block sums
+constexpr int STAGE_SUM_BLOCKS = 128;   // a stage of at most this many blocks of pass_points(false) may update from their sums
 
 inline int capacity(const adacluster_params* p) { return p->k_max_clusters + p->k_m0; }
 inline size_t esize(const adacluster_params* p) { return p->dtype == ADACLUSTER_BF16 ? 2 : 4; }
@@ -215,9 +215,10 @@ Dims dims_of(const adacluster_params* p) {
   D.maxtiles = p->N / attn_block_rows_min(p->dtype) + D.Cq + 1 + attn_split_slots();   // (sized for the smaller tile shape)
   D.maxr = D.cap;
   D.prow = p->N / reduce_part_rows() + D.capmax + 34;
-  {  // rows of the block-sum table of small stages: (blocks of 256 points) x (centres), both capped
-    const int nb = (p->N + 255) / 256, mb = p->k_m0 < assign_block_sum_centres() ? p->k_m0 : assign_block_sum_centres();
-    D.brow = (nb < STAGE_SUM_BLOCKS ? nb : STAGE_SUM_BLOCKS) * assign_block_sum_rows(mb);
+  {  // rows of the table of member sums of small stages: blocks x centres, both capped (room for the two tables of stages
+     // that combine: they have half the blocks, rounded up)
+    const int pp = pass_points(false), nb = (p->N + pp - 1) / pp, mb = p->k_m0 < pass_sum_centres() ? p->k_m0 : pass_sum_centres();
+    D.brow = ((nb < STAGE_SUM_BLOCKS ? nb : STAGE_SUM_BLOCKS) + 1) * mb;
   }
   return D;
 }
@@ -257,7 +258,7 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(lab0, int32_t*, p->dtype == ADACLUSTER_BF16 ? H * N * 4 : 256);
   TAKE(score0, float*, p->dtype == ADACLUSTER_BF16 ? H * N * 4 : 256);
   TAKE(psum, float*, H * (size_t)D.prow * d * 4);
-  TAKE(bcnt, int32_t*, H * (size_t)STAGE_SUM_BLOCKS * assign_block_sum_centres() * 4);
+  TAKE(bcnt, int32_t*, H * (size_t)STAGE_SUM_BLOCKS * pass_sum_centres() * 4);
   TAKE(bsum, float*, H * (size_t)D.brow * d * 4);
   TAKE(pnorm, float*, H * (size_t)D.prow * 4);
   TAKE(pmin, float*, H * (size_t)D.prow * d * 4);
@@ -272,9 +273,9 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(q_psum, float*, H * (size_t)(N / reduce_part_rows() + D.Cq + 34) * d * 4);
   TAKE(q_pnorm, float*, H * (size_t)(N / reduce_part_rows() + D.Cq + 34) * 4);
   {
-    const bool one_read = p->dtype == ADACLUSTER_BF16 && D.Cq <= assign_block_sum_centres();
+    const bool one_read = p->dtype == ADACLUSTER_BF16 && D.Cq <= pass_sum_centres();
     TAKE(q_wsum, float*, one_read ? H * (size_t)D.Cq * qpass_walks(D.N) * d * 4 : 256);
-    TAKE(q_wcnt, int32_t*, one_read ? H * (size_t)qpass_walks(D.N) * assign_block_sum_centres() * 4 : 256);
+    TAKE(q_wcnt, int32_t*, one_read ? H * (size_t)qpass_walks(D.N) * pass_sum_centres() * 4 : 256);
   }
   TAKE(perm_q, int32_t*, H * N * 4);
   TAKE(offs_q, int32_t*, H * (size_t)(D.Cq + 1) * 4);
@@ -343,7 +344,7 @@ int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   // A pass that only updates the centres reads the queries once: assignment and (normalised) sums in one
   // kernel.  The last pass needs the labels sorted (for the attention step) and exact member statistics, and
   // takes the sort and the segmented reduction.
-  const bool one_read = p->dtype == ADACLUSTER_BF16 && D.Cq <= assign_block_sum_centres();
+  const bool one_read = p->dtype == ADACLUSTER_BF16 && D.Cq <= pass_sum_centres();
   for (int it = 0; it < p->q_iters; ++it) {
     if (one_read && it < p->q_iters - 1) {
       const int NP = qpass_walks(D.N);
@@ -353,7 +354,7 @@ int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                              nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.q_wcnt, NP, NP));
       continue;
     }
-    RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, 0, D.Cq, D.Cq, nullptr, nullptr, Q, w.q_cent_lp, w.q_bias,
+    RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, D.Cq, 0, D.Cq, D.Cq, nullptr, nullptr, Q, w.q_cent_lp, w.q_bias,
                          q_labels, nullptr));
     RET_IF(launch_sort(st, D.H, D.N, D.N, D.Cq, q_labels, nullptr, nullptr, 0, nullptr, 0, nullptr, 0, w.perm_q,
                        w.offs_q, D.Cq + 1, w.q_sort, w.q_poff, reduce_part_rows(), nullptr, 0, &poff_done));
@@ -393,7 +394,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                                  k_centroids, w.cent_lp, k_assign, w.bias));
     const int Pw = parts_for(D.N, D.cap);
     for (int it = 0; it < p->k_iters; ++it) {
-      RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, 1, 0, D.cap, cur, nullptr, K, w.cent_lp, w.bias,
+      RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, D.cap, 1, 0, D.cap, cur, nullptr, K, w.cent_lp, w.bias,
                            k_labels, nullptr));
       if (it < p->k_iters - 1 && direct_update_fits(p->dtype, D.N, D.cap)) {
         RET_IF(launch_update_direct(st, D.d, D.H, D.N, D.cap, D.cap, D.cap, cur, k_labels, nullptr, K, k_centroids,
@@ -444,7 +445,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     if (t > 0) kc_bound += m_bound;
     if (t == p->k_max_stages) break;           // the stage head has just closed every head
     if (t == 1 && !(p->dtype == ADACLUSTER_BF16 && (n_bound + 255) / 256 <= STAGE_SUM_BLOCKS &&
-                    m_bound <= assign_block_sum_centres())) {
+                    m_bound <= pass_sum_centres())) {
       // Stage 0 removes most points, so its figures (all N points, m_0 centres) are poor bounds for
       // stage 1: unless they still allow the short update (block sums), they would send a few thousand
       // points through the launch chain sized for all of them (label sort, segmented
@@ -468,27 +469,36 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     const int32_t* ul = (t == 0) ? nullptr : w.ulist[t & 1];
     int32_t* ul_next = w.ulist[(t + 1) & 1];
     const int P = parts_for(n_bound, m_bound);
-    // A small stage (few blocks of points, few centres) updates its centres from sums that the
-    // assignment kernel leaves per block: no label sort and no segmented reduction in between.
-    const int nblk = (n_bound + 255) / 256;
-    const bool block_sums = p->dtype == ADACLUSTER_BF16 && nblk <= STAGE_SUM_BLOCKS &&
-                            m_bound <= assign_block_sum_centres() && (long long)assign_block_sum_rows(m_bound) * nblk <= D.brow;
-    const int Pb = assign_block_sum_rows(m_bound) * nblk;     // rows of the part-sum table the block sums take per head
+    // A small stage (few blocks of points, few centres) updates its centres from the member sums that a pass leaves per
+    // block: no label sort and no segmented reduction in between, and where all of them together are small no launch either.
+    const int nblk = (n_bound + pass_points(false) - 1) / pass_points(false);
+    const bool block_sums = p->dtype == ADACLUSTER_BF16 && nblk <= STAGE_SUM_BLOCKS && m_bound <= pass_sum_centres();
+    const bool combine = block_sums && combine_fits(D.d, heads, n_bound, m_bound);
+    const int wblk = (n_bound + pass_points(true) - 1) / pass_points(true);
+    const StageSums sums[2] = {{w.bsum, w.bcnt}, {w.bsum + (size_t)D.H * m_bound * wblk * D.d, w.bcnt + (size_t)D.H * wblk * pass_sum_centres()}};
+    int counted = stage_points_per_count(p->dtype);          // points per survivor count and distance sum of the last pass
     for (int it = 0; it < p->k_iters; ++it) {
       const bool update = it < p->k_iters - 1;
+      const bool keep = seeded && t == 0 && !update;
+      if (combine) {
+        RET_IF(launch_stage_pass(st, D.d, D.H, D.N, n_bound, m_bound, D.cap, cur, ul, K, w.cent_lp, k_assign, w.bias, true,
+                                 it > 0 ? &sums[(it - 1) & 1] : nullptr, update ? &sums[it & 1] : nullptr, update ? nullptr : w.dist2,
+                                 keep ? w.lab0 : nullptr, keep ? w.score0 : nullptr, w.tau, !update && t > 0 ? w.blockcnt : nullptr,
+                                 D.ncnt, !update && t == 0 ? dist_sum : nullptr));
+        counted = pass_points(true);
+        continue;
+      }
       if (block_sums && update) {
-        RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, n_bound, 1, 0, D.cap, cur, ul, K, w.cent_lp, w.bias,
-                             w.labels_tmp, nullptr, w.bsum, w.bcnt, Pb));        // (distances: last pass only)
-        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, Pb, D.cap, p->k_m0, cur, 0, 1, 0,
+        RET_IF(launch_stage_pass(st, D.d, D.H, D.N, n_bound, m_bound, D.cap, cur, ul, K, w.cent_lp, k_assign, w.bias, false, nullptr, &sums[0]));
+        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, m_bound * nblk, D.cap, p->k_m0, cur, 0, 1, 0,
                                nullptr, 0, nullptr, w.bsum, w.pnorm, w.pmin, w.pmax, w.master, w.cent_lp,
                                k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.bcnt, nblk));
         continue;
       }
       // (the last pass of stage 0 runs over all points against the first-stage centres as they will stay:
       // it keeps a copy of its labels and best scores, which the final pass starts from)
-      const bool keep = seeded && t == 0 && !update;
-      RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, n_bound, 1, 0, D.cap, cur, ul, K, w.cent_lp, w.bias,
-                           w.labels_tmp, update ? nullptr : w.dist2, nullptr, nullptr, 0, keep ? w.lab0 : nullptr,
+      RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, n_bound, m_bound, 1, 0, D.cap, cur, ul, K, w.cent_lp, w.bias,
+                           w.labels_tmp, update ? nullptr : w.dist2, keep ? w.lab0 : nullptr,
                            keep ? w.score0 : nullptr, nullptr, nullptr, w.tau,
                            !update && t > 0 ? w.blockcnt : nullptr, D.ncnt, !update && t == 0 ? dist_sum : nullptr));
       if (update && direct_update_fits(p->dtype, n_bound, m_bound)) {
@@ -506,17 +516,18 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                                k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr));
       }
     }
-    filter = StageFilter{w.dist2, w.tau, w.blockcnt, D.ncnt, stage_points_per_count(p->dtype), ul, ul_next, k_stage_of, t};
-    if (t == 0) RET_IF(launch_keep_count(st, p->dtype, cur, D.H, D.N, w.dist2, dist_sum, p->tau_factor, w.tau, w.blockcnt, D.ncnt, &filter.items));
+    filter = StageFilter{w.dist2, w.tau, w.blockcnt, D.ncnt, counted, ul, ul_next, k_stage_of, t};
+    if (t == 0) RET_IF(launch_keep_count(st, cur, D.H, D.N, w.dist2, dist_sum, (D.N + counted - 1) / counted, p->tau_factor, w.tau, w.blockcnt,
+                                         D.ncnt, &filter.items));
   }
   kc_bound = kc_bound < D.cap ? kc_bound : D.cap;
   // last step of Algorithm 1: nearest centre among all stage centres, then member statistics.  bf16: the
   // nearest first-stage centre of every point is known from stage 0, so only the later stages' centres are visited.
   if (seeded)
-    RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, 3, 0, D.cap, cur, nullptr, K, w.cent_lp, w.bias,
-                         k_labels, nullptr, nullptr, nullptr, 0, nullptr, nullptr, w.lab0, w.score0))
+    RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, kc_bound, 3, 0, D.cap, cur, nullptr, K, w.cent_lp, w.bias,
+                         k_labels, nullptr, nullptr, nullptr, w.lab0, w.score0))
   else
-    RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, 2, 0, D.cap, cur, nullptr, K, w.cent_lp, w.bias,
+    RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, kc_bound, 2, 0, D.cap, cur, nullptr, K, w.cent_lp, w.bias,
                          k_labels, nullptr));
   }
   const int want_box = (k_bmin && k_bmax) ? 1 : 0;

@@ -31,6 +31,7 @@ struct AssignCfg {
   double* dist_sum;                                       // sum of the distances of this workgroup's points (the first stage's last
                                                           // pass, for tau): dist_sum[h * gridDim.x + workgroup]
 };
+constexpr int PASS_POINTS = 256;        // points of a workgroup of stage_pass (twice that where it combines)
 constexpr int ASSIGN_POINTS_LP = 256, ASSIGN_POINTS_F32 = 64;     // points of an assignment workgroup
 
 __device__ __forceinline__ bool assign_setup(const AssignCfg& c, int h, int& n, int& m, int& row_off) {
@@ -50,27 +51,17 @@ __device__ __forceinline__ bool assign_setup(const AssignCfg& c, int h, int& n, 
 // two half-waves are merged once at the end.  Two workgroups per CU in the launch bounds keep the
 // register budget at 256, so the accumulators are ordinary VGPRs that the arg-max reads directly (with
 // 512 the compiler parks them in AGPRs and copies every value out first).
-//
-// ACC (small stages of Algorithm 1): the workgroup also leaves, per centre, the sum and the count of the
-// points of its block that chose it, so that the centroid update needs neither a label sort nor a
-// segmented reduction.  The sums are a second MFMA product, S^T[32 dims x 32 centres] +=
-// X^T[32 dims x 16 points] . E[16 points x 32 centres] with E the one-hot label matrix: exact products,
-// fp32 accumulation in a fixed order.  Block b of head h writes the rows (j * nb_stride + b) * acc_parts(m) .. of the
-// head's part-sum table and bcnt[(h * nb_stride + b) * ACC_MAXM + j].
-struct AccumOut { float* psum; int32_t* bcnt; int P; int nb_stride; };
-constexpr int ACC_MAXM = 128;          // most centres the block sums are kept for
-__host__ __device__ constexpr int acc_parts(int m) { return m <= 32 ? 4 : m <= 64 ? 2 : 1; }     // rows of sums a block leaves per centre
+constexpr int ACC_MAXM = 128;          // most centres that member sums on the matrix cores are kept for (qpass_mfma, stage_pass)
 
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4_t;
 typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-template <int D, bool ACC>
+template <int D>
 __global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict__ X, AssignCfg cfg,
                                                                 const bf16raw* __restrict__ cent,
                                                                 const float* __restrict__ bias,
-                                                                int32_t* __restrict__ labels, float* __restrict__ dist2,
-                                                                AccumOut acc_out) {
+                                                                int32_t* __restrict__ labels, float* __restrict__ dist2) {
   constexpr int CB = D == 128 ? 64 : 128;   // centres per LDS chunk (16 KB either way; larger chunks measured slower)
   constexpr int KS = D / 16;
   constexpr int PB = 2;                 // 32-point blocks per wave
@@ -88,14 +79,8 @@ __global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict_
   // both may touch the same object, so the load of chunk i+1 runs under the arithmetic of chunk i).
   // Rows are unpadded; piece g of row r sits in slot g ^ swz(r), which keeps the 16-byte operand
   // reads of 16 consecutive rows in 16 different bank groups.
-  // ACC: both lie in the buffer that takes the points afterwards (a stage that small has a chunk or two, and what counts
-  // is that two workgroups fit a CU: d=128 99 KB in buffers of their own, 12 heads of 6 800 points 24 us, in one 67 KB 16).
-  __shared__ __attribute__((aligned(16))) char own0[ACC ? 16 : CB * CROWB];
-  __shared__ __attribute__((aligned(16))) char own1[ACC ? 16 : CB * CROWB];
-  __shared__ __attribute__((aligned(16))) char pool[ACC ? 256 * CROWB : 16];
-  static_assert(256 >= 2 * CB, "the chunks fit the buffer of the points");
-  char* const cs0 = ACC ? pool : own0;
-  char* const cs1 = ACC ? pool + CB * CROWB : own1;
+  __shared__ __attribute__((aligned(16))) char cs0[CB * CROWB];
+  __shared__ __attribute__((aligned(16))) char cs1[CB * CROWB];
   __shared__ __attribute__((aligned(16))) float bs0[CB];
   __shared__ __attribute__((aligned(16))) float bs1[CB];
   auto swz = [](int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); };
@@ -146,7 +131,7 @@ __global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict_
   // a negative tile marks "still the seed".
   int slab[PB];
   const int label_base = cfg.mode == 3 ? row_off : 0;
-  if (!ACC && cfg.seed_lab) {
+  if (cfg.seed_lab) {
 #pragma unroll
     for (int pb = 0; pb < PB; ++pb) {
       slab[pb] = 0;
@@ -245,17 +230,16 @@ __global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict_
     step(c0, cs0, bs0, cs1, bs1);
     if (c0 + CB < m) step(c0 + CB, cs1, bs1, cs0, bs0);
   }
-  int blab[PB];
   int kept = 0;
   double dsum = 0.0;
-  const bool counts = !ACC && cfg.keep_cnt && dist2;
+  const bool counts = cfg.keep_cnt && dist2;
   const float t2 = counts ? cfg.tau[1] : 0.f;
 #pragma unroll
   for (int pb = 0; pb < PB; ++pb) {
     // accumulator value v of a tile is centre  32*tile + 8*(v/4) + 4*hb + v%4
     const int v = 15 - (int)(__float_as_uint(best[pb]) & 15u);   // 15-v was packed: equal scores >= 0 go to the lowest centre
     int bidx = label_base + btile[pb] * 32 + 8 * (v >> 2) + 4 * hb + (v & 3);
-    if (!ACC && cfg.seed_lab && btile[pb] < 0) bidx = slab[pb];
+    if (cfg.seed_lab && btile[pb] < 0) bidx = slab[pb];
     float bv = __uint_as_float(__float_as_uint(best[pb]) & 0xFFFFFFF0u);
     const float ob = __shfl_xor(bv, 32);
     const int oi = __shfl_xor(bidx, 32);
@@ -263,12 +247,11 @@ __global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict_
     const float d2 = fmaxf(xn2[pb] - 2.f * bv, 0.f);
     if (counts) kept += __popcll(__ballot(hb == 0 && pos[pb] < n && !(d2 < t2)));
     if (hb == 0 && pos[pb] < n) {
-      if (!ACC && cfg.dist_sum) dsum += (double)sqrtf(d2);
+      if (cfg.dist_sum) dsum += (double)sqrtf(d2);
       labels[(size_t)h * cfg.N + pos[pb]] = bidx;
       if (dist2) dist2[(size_t)h * cfg.N + pos[pb]] = d2;
-      if (!ACC && cfg.keep_lab) { cfg.keep_lab[(size_t)h * cfg.N + pos[pb]] = bidx; cfg.keep_score[(size_t)h * cfg.N + pos[pb]] = bv; }
+      if (cfg.keep_lab) { cfg.keep_lab[(size_t)h * cfg.N + pos[pb]] = bidx; cfg.keep_score[(size_t)h * cfg.N + pos[pb]] = bv; }
     }
-    if (ACC) blab[pb] = pos[pb] < n ? bidx : -1;
   }
   if (counts) {
     __shared__ int32_t wkept[4];
@@ -276,7 +259,7 @@ __global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict_
     __syncthreads();
     if (tid == 0) cfg.keep_cnt[(size_t)h * cfg.keep_stride + blockIdx.x] = wkept[0] + wkept[1] + wkept[2] + wkept[3];
   }
-  if (!ACC && cfg.dist_sum) {
+  if (cfg.dist_sum) {
 #pragma unroll
     for (int o = 1; o < 32; o <<= 1) dsum += __shfl_xor(dsum, o);      // (the upper half-wave holds zeros)
     __shared__ double wsum[4];
@@ -284,81 +267,301 @@ __global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict_
     __syncthreads();
     if (tid == 0) cfg.dist_sum[(size_t)h * gridDim.x + blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
   }
-  if constexpr (ACC) {
-    constexpr int ROWB = D * 2, DT = D / 32;
-    // The block's points lie row by row in `pool`.  Piece q (16 bytes) of row r sits in slot q ^ xswz(r), as in qpass_mfma:
-    // unswizzled, all rows of a store meet in the same banks.
-    auto xswz = [](int r) { return D == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : ((((r >> 1) & 1) << 2) | (((r >> 1) & 7) >> 1)); };
-    __shared__ __attribute__((aligned(16))) int32_t lab_s[256];
-    __shared__ int32_t cnt_s[ACC_MAXM];
-    if (tid < ACC_MAXM) cnt_s[tid] = 0;
+}
+
+// ------------------------------------------------------------------------------------------
+// A pass of a stage of Algorithm 1 with at most ACC_MAXM centres (bf16): assignment and member sums together.
+// ------------------------------------------------------------------------------------------
+// A workgroup is NW waves of 64 points.  The scores and their in-lane arg-max are those of assign_mfma, the centres all in
+// LDS.  An update pass (`out`) then leaves, per centre, the sum and the count of the workgroup's points that chose it, so
+// that the update needs neither a label sort nor a segmented reduction: a second product, S^T[32 dims x 32 centres] +=
+// X^T[32 dims x 16 points] . E[16 points x 32 centres] with E the one-hot label matrix: exact products, fp32 accumulation
+// in a fixed order.  Block b of head h writes row j * nb_stride + b of the head's part-sum table for centre j, and
+// bcnt[(h * nb_stride + b) * ACC_MAXM + j].  The last pass leaves squared distances, and what the filter wants to know.
+// COMBINE: the centres are not read but formed here, from what the update pass before left (`prev`), by every workgroup for
+// itself; the head's first one writes them out.  That takes the place of a launch of finalize_centroids, 5-6 us of latency
+// each, where a head's sums are small enough to be read by all of its workgroups (combine_fits): of a stage of 12 x 4 000
+// points, d=128, two passes and two launches between them, 9.5 + 6 us each, are two of 12 and 14, and the last pass with its
+// launch, 6 + 5.5, one of 10; a call of 12 x 32 760 tokens 880 -> 863 us, of 5 x 9 247 tokens 572 -> 561.  (With the sums and
+// the list of points asked for ahead of the state the same; sixteen sums in flight at d=64 spill: 13 -> 25 us.)
+struct PassSums { float* psum; int32_t* bcnt; int P; int nb_stride; };
+template <int D, int NW, bool COMBINE>
+__global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf16raw* __restrict__ X, AssignCfg cfg, bf16raw* __restrict__ cent,
+                                                      float* __restrict__ cent_f32, float* __restrict__ bias,
+                                                      float* __restrict__ dist2, PassSums prev, PassSums out) {
+  constexpr int KS = D / 16, PB = 2, CROWB = D * 2, CH = D / 8, DT = D / 32, NT = NW * 64;
+  const int h = blockIdx.y;
+  int n, m, row_off;
+  if (!assign_setup(cfg, h, n, m, row_off)) return;
+  const int base = blockIdx.x * NT;
+  if (base >= n) return;
+  m = min(m, ACC_MAXM);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = lane & 31, hb = lane >> 5;
+  const int CT = (m + 31) >> 5;
+  // The centres, then the points, then the partial sums of the waves.  Piece g (16 bytes) of centre row r sits in slot g ^
+  // swz(r), of point row r in slot g ^ xswz(r) (see qpass_mfma).
+  __shared__ __attribute__((aligned(16))) char pool[NT * CROWB];
+  __shared__ __attribute__((aligned(16))) float bs[ACC_MAXM];
+  __shared__ __attribute__((aligned(16))) int32_t lab_s[NT];
+  __shared__ int32_t cnt_s[ACC_MAXM];
+  static_assert(NT >= ACC_MAXM, "the centres fit the buffer of the points");
+  auto swz = [](int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); };
+  auto xswz = [](int r) { return D == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : ((((r >> 1) & 1) << 2) | (((r >> 1) & 7) >> 1)); };
+
+  // B operand: this lane's point rows
+  bf16x8_t xf[PB][KS];
+  int pos[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+    pos[pb] = base + wave * (PB * 32) + pb * 32 + c;
+    const int p = min(pos[pb], n - 1), tok = cfg.ulist ? cfg.ulist[(size_t)h * cfg.N + p] : p;
+    const bf16raw* row = X + ((size_t)h * cfg.N + tok) * D + hb * 8;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const uint4 raw = *reinterpret_cast<const uint4*>(row + ks * 16);
+      xf[pb][ks] = *reinterpret_cast<const bf16x8_t*>(&raw);
+    }
+  }
+  const size_t crow = (size_t)h * cfg.cap + row_off;
+  if constexpr (COMBINE) {
+    // LPC lanes a centre, four columns each; the blocks' sums in block order
+    constexpr int LPC = D / 4, BATCH = 8;
+    const int cl = tid % LPC, nb = (n + NT - 1) / NT;
+    for (int j = tid / LPC; j < CT * 32; j += NT / LPC) {
+      uint2 r = {0u, 0u};
+      float bj = -3.0e38f;                               // (rows past the last centre: zeros under a bias that never wins)
+      if (j < m) {
+        int nj = 0;
+        for (int b = cl; b < nb; b += LPC) nj += prev.bcnt[((size_t)h * prev.nb_stride + b) * ACC_MAXM + j];
+        const float* ps = prev.psum + ((size_t)h * prev.P + (size_t)j * prev.nb_stride) * D + cl * 4;
+        float4 s = {0.f, 0.f, 0.f, 0.f};
+        for (int b0 = 0; b0 < nb; b0 += BATCH) {
+          float4 t[BATCH];
+#pragma unroll
+          for (int u = 0; u < BATCH; ++u) t[u] = *reinterpret_cast<const float4*>(ps + (size_t)min(b0 + u, nb - 1) * D);
+#pragma unroll
+          for (int u = 0; u < BATCH; ++u) if (b0 + u < nb) { s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w; }
+        }
+#pragma unroll
+        for (int o = 1; o < LPC; o <<= 1) nj += __shfl_xor(nj, o);
+        const size_t at = (crow + j) * D + cl * 4;
+        if (nj > 0) {
+          const float cnt = (float)nj;
+          const bf16raw v0 = f32_to_bf16(s.x / cnt), v1 = f32_to_bf16(s.y / cnt), v2 = f32_to_bf16(s.z / cnt), v3 = f32_to_bf16(s.w / cnt);
+          const float4 img = {bf16_to_f32(v0), bf16_to_f32(v1), bf16_to_f32(v2), bf16_to_f32(v3)};
+          r = uint2{(uint32_t)v0 | ((uint32_t)v1 << 16), (uint32_t)v2 | ((uint32_t)v3 << 16)};
+          float ss = fmaf(img.x, img.x, 0.f);
+          ss = fmaf(img.y, img.y, ss); ss = fmaf(img.z, img.z, ss); ss = fmaf(img.w, img.w, ss);
+#pragma unroll
+          for (int o = 1; o < LPC; o <<= 1) ss += __shfl_xor(ss, o);
+          bj = -0.5f * ss;
+          if (blockIdx.x == 0) {
+            *reinterpret_cast<uint2*>(cent + at) = r;
+            *reinterpret_cast<float4*>(cent_f32 + at) = img;
+            if (cl == 0) bias[crow + j] = bj;
+          }
+        } else {                                         // an empty cluster keeps its centre
+          r = *reinterpret_cast<const uint2*>(cent + at);
+          bj = bias[crow + j];
+        }
+      }
+      *reinterpret_cast<uint2*>(pool + j * CROWB + (((cl >> 1) ^ swz(j)) * 16) + (cl & 1) * 8) = r;
+      if (cl == 0) bs[j] = bj;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < ACC_MAXM * CH / NT; ++i) {         // whole tiles, all in flight; rows past m repeat the last centre
+      const int item = tid + i * NT, r = item / CH, sl = item % CH;
+      if (r < CT * 32)
+        dma_b128((uint32_t)(uintptr_t)(lds_void_t*)pool + (wave * 64 + i * NT) * 16,
+                 reinterpret_cast<const char*>(cent + (crow + min(r, m - 1)) * D) + ((sl ^ swz(r)) * 16));
+    }
+    if (tid < CT * 32) bs[tid] = tid < m ? bias[crow + tid] : -3.0e38f;      // finite: survives the bit packing
+    wait_vmcnt<0>();
+  }
+  if (tid < ACC_MAXM) cnt_s[tid] = 0;
+  int kaddr[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) kaddr[ks] = c * CROWB + (((ks * 2 + hb) ^ swz(c)) * 16);
+  __syncthreads();
+
+  // scores and arg-max, as assign_mfma
+  float best[PB]; int btile[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) { best[pb] = -INFINITY; btile[pb] = 0; }
+  for (int rb = 0; rb < CT; ++rb) {
+    f32x16_t acc[PB];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float4 b4 = *reinterpret_cast<const float4*>(&bs[rb * 32 + 8 * i + 4 * hb]);
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) {
+        acc[pb][4 * i + 0] = b4.x; acc[pb][4 * i + 1] = b4.y;
+        acc[pb][4 * i + 2] = b4.z; acc[pb][4 * i + 3] = b4.w;
+      }
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(pool + rb * 32 * CROWB + kaddr[ks]);
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) acc[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xf[pb][ks], acc[pb], 0, 0, 0);
+    }
 #pragma unroll
     for (int pb = 0; pb < PB; ++pb) {
-      const int pr = wave * (PB * 32) + pb * 32 + c;
+      float pk[16];
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<bf16x8_t*>(pool + pr * ROWB + (((ks * 2 + hb) ^ xswz(pr)) * 16)) = xf[pb][ks];
-      if (hb == 0) lab_s[pr] = blab[pb];
+      for (int v = 0; v < 16; ++v) pk[v] = __uint_as_float((__float_as_uint(acc[pb][v]) & 0xFFFFFFF0u) | (uint32_t)(15 - v));
+      float tm = fmaxf(fmaxf(pk[0], pk[1]), pk[2]);
+#pragma unroll
+      for (int v = 3; v < 15; v += 2) tm = fmaxf(fmaxf(tm, pk[v]), pk[v + 1]);
+      tm = fmaxf(tm, pk[15]);
+      if (tm > best[pb]) { best[pb] = tm; btile[pb] = rb; }
     }
+  }
+  int bidx[PB]; float bv[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+    const int v = 15 - (int)(__float_as_uint(best[pb]) & 15u);
+    bidx[pb] = btile[pb] * 32 + 8 * (v >> 2) + 4 * hb + (v & 3);
+    bv[pb] = __uint_as_float(__float_as_uint(best[pb]) & 0xFFFFFFF0u);
+    const float ob = __shfl_xor(bv[pb], 32);
+    const int oi = __shfl_xor(bidx[pb], 32);
+    if (ob > bv[pb] || (ob == bv[pb] && oi < bidx[pb])) { bv[pb] = ob; bidx[pb] = oi; }
+  }
+  if (!out.psum) {
+    // last pass: squared distances, and the survivors of the threshold or (first stage) the sum for it and the seeds of the
+    // final pass
+    int kept = 0;
+    double dsum = 0.0;
+    const bool counts = cfg.keep_cnt != nullptr;
+    const float t2 = counts ? cfg.tau[1] : 0.f;
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+      float ss = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const uint4 raw = *reinterpret_cast<const uint4*>(&xf[pb][ks]);
+        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float a = __uint_as_float(w[q] << 16), b = __uint_as_float(w[q] & 0xFFFF0000u);
+          ss = fmaf(a, a, ss); ss = fmaf(b, b, ss);
+        }
+      }
+      const float d2 = fmaxf(ss + __shfl_xor(ss, 32) - 2.f * bv[pb], 0.f);
+      const bool mine = hb == 0 && pos[pb] < n;
+      if (counts) kept += __popcll(__ballot(mine && !(d2 < t2)));
+      if (mine) {
+        dist2[(size_t)h * cfg.N + pos[pb]] = d2;
+        if (cfg.dist_sum) dsum += (double)sqrtf(d2);
+        if (cfg.keep_lab) { cfg.keep_lab[(size_t)h * cfg.N + pos[pb]] = bidx[pb]; cfg.keep_score[(size_t)h * cfg.N + pos[pb]] = bv[pb]; }
+      }
+    }
+    __shared__ int32_t wkept[NW];
+    __shared__ double wsum[NW];
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) dsum += __shfl_xor(dsum, o);      // (the upper half-wave holds zeros)
+    if (lane == 0) { wkept[wave] = kept; wsum[wave] = dsum; }
     __syncthreads();
-    // A wave takes a whole centre tile, so that the one-hot operand of a group of 16 points (twenty vector instructions,
-    // more than the product it feeds) is built once and serves every dim tile.  With one or two centre tiles the four
-    // waves share the points of a tile instead (acc_parts quarters or halves of the block, a row of sums each): dealing
-    // (centre tile, dim tile) pairs over all points built every operand four or five times (30 heads, 40 centres, d=64:
-    // 11 us a pass, now 8; 30 x 17 776 points, 128 centres 55 -> 40).
-    const int b = blockIdx.x, CT = (m + 31) >> 5, R = acc_parts(m), G = 16 / R, part = wave % R;
+    if (tid == 0) {
+      int k = 0; double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) { k += wkept[w]; s += wsum[w]; }
+      if (counts) cfg.keep_cnt[(size_t)h * cfg.keep_stride + blockIdx.x] = k;
+      if (cfg.dist_sum) cfg.dist_sum[(size_t)h * gridDim.x + blockIdx.x] = s;
+    }
+    return;
+  }
+  __syncthreads();                       // every wave is done with the centres: the points take their place
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+    const int pr = wave * (PB * 32) + pb * 32 + c;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<bf16x8_t*>(pool + pr * CROWB + (((ks * 2 + hb) ^ xswz(pr)) * 16)) = xf[pb][ks];
+    if (hb == 0) {
+      lab_s[pr] = pos[pb] < n ? bidx[pb] : -1;
+      if (pos[pb] < n) atomicAdd(&cnt_s[bidx[pb]], 1);
+    }
+  }
+  __syncthreads();
+  // A wave takes a whole centre tile, so that the one-hot operand of a group of 16 points (twenty vector instructions,
+  // more than the product it feeds) is built once and serves every dim tile; with fewer tiles than waves, R waves share
+  // the points of a tile.
+  const int b = blockIdx.x, R = m <= 32 ? NW : m <= 64 ? NW / 2 : NW / 4, G = 4 * NW / R, part = wave % R, ct = wave / R;
+  const int i16 = lane & 15, blk = lane >> 4;
+  const int vrow = 4 * hb + (i16 >> 2);
+  const int gl = 2 * (blk & 1) + ((i16 & 3) >> 1);
+  const int cid = ct * 32 + c;
+  f32x16_t sacc[DT];
+#pragma unroll
+  for (int t = 0; t < DT; ++t)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sacc[t][v] = 0.f;
+  if (ct < CT) {
     // X^T operand by transpose reads (see the V operand of the attention kernel): this lane addresses
     // point 4*hb + (lane%16)/4 of a 16-point group, dims 16*((lane/16)%2) + 4*(lane%4) .. +3
-    const int i16 = lane & 15, blk = lane >> 4;
-    const int vrow = 4 * hb + (i16 >> 2);
-    const int gl = 2 * (blk & 1) + ((i16 & 3) >> 1);
     int xlo[DT], xhi[DT];
 #pragma unroll
     for (int db = 0; db < DT; ++db) {
-      xlo[db] = vrow * ROWB + (((db * 4 + gl) ^ xswz(vrow)) * 16) + 8 * (i16 & 1);
-      xhi[db] = (vrow + 8) * ROWB + (((db * 4 + gl) ^ xswz(vrow + 8)) * 16) + 8 * (i16 & 1);
+      xlo[db] = vrow * CROWB + (((db * 4 + gl) ^ xswz(vrow)) * 16) + 8 * (i16 & 1);
+      xhi[db] = (vrow + 8) * CROWB + (((db * 4 + gl) ^ xswz(vrow + 8)) * 16) + 8 * (i16 & 1);
     }
-    if (lab_s[tid] >= 0) atomicAdd(&cnt_s[lab_s[tid]], 1);
-    for (int ct = wave / R; ct < CT; ct += 4 / R) {
-      const int cid = ct * 32 + c;
-      f32x16_t sacc[DT];
-#pragma unroll
-      for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) sacc[t][v] = 0.f;
 #pragma unroll 4
-      for (int g = part * G; g < part * G + G; ++g) {
-        const int4 l0 = *reinterpret_cast<const int4*>(&lab_s[g * 16 + 4 * hb]);
-        const int4 l1 = *reinterpret_cast<const int4*>(&lab_s[g * 16 + 8 + 4 * hb]);
-        uint4 e;
-        e.x = (l0.x == cid ? 0x3F80u : 0u) | (l0.y == cid ? 0x3F800000u : 0u);
-        e.y = (l0.z == cid ? 0x3F80u : 0u) | (l0.w == cid ? 0x3F800000u : 0u);
-        e.z = (l1.x == cid ? 0x3F80u : 0u) | (l1.y == cid ? 0x3F800000u : 0u);
-        e.w = (l1.z == cid ? 0x3F80u : 0u) | (l1.w == cid ? 0x3F800000u : 0u);
-        const bf16x8_t eb = *reinterpret_cast<const bf16x8_t*>(&e);
+    for (int g = part * G; g < part * G + G; ++g) {
+      const int4 l0 = *reinterpret_cast<const int4*>(&lab_s[g * 16 + 4 * hb]);
+      const int4 l1 = *reinterpret_cast<const int4*>(&lab_s[g * 16 + 8 + 4 * hb]);
+      uint4 e;
+      e.x = (l0.x == cid ? 0x3F80u : 0u) | (l0.y == cid ? 0x3F800000u : 0u);
+      e.y = (l0.z == cid ? 0x3F80u : 0u) | (l0.w == cid ? 0x3F800000u : 0u);
+      e.z = (l1.x == cid ? 0x3F80u : 0u) | (l1.y == cid ? 0x3F800000u : 0u);
+      e.w = (l1.z == cid ? 0x3F80u : 0u) | (l1.w == cid ? 0x3F800000u : 0u);
+      const bf16x8_t eb = *reinterpret_cast<const bf16x8_t*>(&e);
 #pragma unroll
-        for (int db = 0; db < DT; ++db) {
-          const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(pool + g * 16 * ROWB + xlo[db]));
-          const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(pool + g * 16 * ROWB + xhi[db]));
-          const s16x4_t both[2] = {lo, hi};
-          sacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(both), eb, sacc[db], 0, 0, 0);
-        }
+      for (int db = 0; db < DT; ++db) {
+        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(pool + g * 16 * CROWB + xlo[db]));
+        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(pool + g * 16 * CROWB + xhi[db]));
+        const s16x4_t both[2] = {lo, hi};
+        sacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(both), eb, sacc[db], 0, 0, 0);
       }
-      // value v of a tile is dim db*32 + 8*(v/4) + 4*hb + v%4 of centre cid
-      if (cid < m) {
+    }
+  }
+  // the waves that share a tile meet: half of them hand their sums to the other half, until one holds all
+  constexpr int PROW = D + 4;            // floats of a padded row: the float4 pieces of 8 centres fall in 8 bank groups
+  static_assert(NW / 2 * 32 * PROW * 4 <= NT * CROWB, "the partial sums fit the buffer of the points");
+  float* const ps = reinterpret_cast<float*>(pool);
+  for (int half = R / 2; half >= 1; half >>= 1) {
+    __syncthreads();                     // the points, or the sums of the round before, have been read
+    float* const slot = ps + ((size_t)((ct * half + (part & (half - 1))) * 32 + c)) * PROW + 4 * hb;
+    if (part >= half && part < 2 * half) {
 #pragma unroll
-        for (int db = 0; db < DT; ++db) {
-          float* out = acc_out.psum + ((size_t)h * acc_out.P + ((size_t)cid * acc_out.nb_stride + b) * R + part) * D + db * 32 + 4 * hb;
+      for (int db = 0; db < DT; ++db)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float4 o4 = {sacc[db][4 * i], sacc[db][4 * i + 1], sacc[db][4 * i + 2], sacc[db][4 * i + 3]};
-            *reinterpret_cast<float4*>(out + 8 * i) = o4;
-          }
-        }
-      }
+        for (int i = 0; i < 4; ++i)
+          *reinterpret_cast<float4*>(slot + db * 32 + 8 * i) = float4{sacc[db][4 * i], sacc[db][4 * i + 1], sacc[db][4 * i + 2], sacc[db][4 * i + 3]};
     }
     __syncthreads();
-    if (tid < m) acc_out.bcnt[((size_t)h * acc_out.nb_stride + b) * ACC_MAXM + tid] = cnt_s[tid];
+    if (part < half) {
+#pragma unroll
+      for (int db = 0; db < DT; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float4 o = *reinterpret_cast<const float4*>(slot + db * 32 + 8 * i);
+          sacc[db][4 * i] += o.x; sacc[db][4 * i + 1] += o.y; sacc[db][4 * i + 2] += o.z; sacc[db][4 * i + 3] += o.w;
+        }
+    }
   }
+  // value v of a tile is dim db*32 + 8*(v/4) + 4*hb + v%4 of centre cid
+  if (part == 0 && cid < m) {
+#pragma unroll
+    for (int db = 0; db < DT; ++db) {
+      float* o = out.psum + ((size_t)h * out.P + (size_t)cid * out.nb_stride + b) * D + db * 32 + 4 * hb;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<float4*>(o + 8 * i) = float4{sacc[db][4 * i], sacc[db][4 * i + 1], sacc[db][4 * i + 2], sacc[db][4 * i + 3]};
+    }
+  }
+  if (tid < m) out.bcnt[((size_t)h * out.nb_stride + b) * ACC_MAXM + tid] = cnt_s[tid];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -562,13 +765,16 @@ __global__ __launch_bounds__(256, 2) void qpass_mfma(const bf16raw* __restrict__
 // and 1 024 centres 219 -> 184 and 2 690 -> 1 070 (118 TFLOP/s).  With rows straight into registers, every wave its own
 // copy, 16 instead of 11 us, and 381 instead of 184 in the large launch; 128 registers and two workgroups a CU: 239 -> 184.
 // Piece q (16 bytes) of centre row r sits in slot q ^ (r & 15) of its 256 bytes: a read of 32 rows meets every bank twice.
-template <int D>
-__global__ __launch_bounds__(512, 4) void assign_f32(const float* __restrict__ X, AssignCfg cfg,
+// NS = 1, with at most 32 centres: one tile, and its two waves are the workgroup (30 x 3 000 points, 8 centres: the other six
+// waves of 1 400 workgroups made a pass 20 us instead of 14; a point a thread, which read no more centres than there are,
+// was 10 % faster there and at 100 000 points with 8 centres, and slower from 32 centres or below some 50 000 points on).
+template <int D, int NS>
+__global__ __launch_bounds__(NS * 64 * (ASSIGN_POINTS_F32 / 32), 4) void assign_f32(const float* __restrict__ X, AssignCfg cfg,
                                                   const float* __restrict__ cent,
                                                   const float* __restrict__ bias,
                                                   int32_t* __restrict__ labels, float* __restrict__ dist2) {
-  constexpr int NS = 4, PG = ASSIGN_POINTS_F32 / 32, CB = 32 * NS, ROWB = D * 4, PPR = D / 4, NT = 64 * NS * PG;
-  static_assert(NT == 512, "the launch bound");
+  constexpr int PG = ASSIGN_POINTS_F32 / 32, CB = 32 * NS, ROWB = D * 4, PPR = D / 4, NT = 64 * NS * PG;
+  constexpr int ROWS = CB > ASSIGN_POINTS_F32 + 32 ? CB : ASSIGN_POINTS_F32 + 32;      // of LDS
   const int h = blockIdx.y;
   int n, m, row_off;
   if (!assign_setup(cfg, h, n, m, row_off)) return;
@@ -576,7 +782,7 @@ __global__ __launch_bounds__(512, 4) void assign_f32(const float* __restrict__ X
   if (base >= n) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 31, hb = lane >> 5, pg = wave % PG, sp = wave / PG;     // (waves of the first tile on different SIMDs)
-  __shared__ __attribute__((aligned(16))) char cs[CB * ROWB];
+  __shared__ __attribute__((aligned(16))) char cs[ROWS * ROWB];
   __shared__ __attribute__((aligned(16))) float bs[CB];
   __shared__ float sbest[NS][ASSIGN_POINTS_F32];
   __shared__ int32_t sidx[NS][ASSIGN_POINTS_F32];
@@ -590,11 +796,11 @@ __global__ __launch_bounds__(512, 4) void assign_f32(const float* __restrict__ X
       const int item = tid + i * NT, r = item / PPR, sl = item % PPR, q = (sl & ~15) | ((sl ^ r) & 15);
       if (r < rows) dma_b128(cs0 + (wave * 64 + i * NT) * 16, ch + (size_t)min(c0 + r, m - 1) * ROWB + q * 16);
     }
-    if (tid < CB) bs[tid] = c0 + tid < m ? bh[c0 + tid] : -INFINITY;
+    for (int i = tid; i < CB; i += NT) bs[i] = c0 + i < m ? bh[c0 + i] : -INFINITY;
   };
   // The points come through LDS: beside the first chunk of centres where that leaves room, else before it.
-  const bool beside = m <= CB - ASSIGN_POINTS_F32;
-  char* const ps = cs + (beside ? (CB - ASSIGN_POINTS_F32) * ROWB : 0);
+  const bool beside = m <= ROWS - ASSIGN_POINTS_F32;
+  char* const ps = cs + (beside ? (ROWS - ASSIGN_POINTS_F32) * ROWB : 0);
 #pragma unroll
   for (int i = 0; i < ASSIGN_POINTS_F32 * PPR / NT; ++i) {
     const int item = tid + i * NT, r = item / PPR, sl = item % PPR, q = (sl & ~15) | ((sl ^ r) & 15);
@@ -1023,14 +1229,13 @@ __global__ __launch_bounds__(64 * FIN_ROWS) void finalize_centroids(FinalizeCfg 
   }
   int nj, p_beg, p_end;
   if (cfg.bcnt) {
-    // the blocks of 256 points of the assignment kernel, in block order
-    const int nb = cfg.nb_const > 0 ? cfg.nb_const : (cfg.st[h].ucount + 255) >> 8;
+    // the workgroups of stage_pass, or the walks of qpass_mfma, in order
+    const int nb = cfg.nb_const > 0 ? cfg.nb_const : (cfg.st[h].ucount + PASS_POINTS - 1) / PASS_POINTS;
     nj = 0;
     for (int b = lane; b < nb; b += 64) nj += cfg.bcnt[((size_t)h * cfg.nb_stride + b) * ACC_MAXM + j];
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) nj += __shfl_xor(nj, o);
-    const int R = cfg.nb_const > 0 ? 1 : acc_parts(m);
-    p_beg = j * cfg.nb_stride * R; p_end = p_beg + nb * R;
+    p_beg = j * cfg.nb_stride; p_end = p_beg + nb;
   } else {
     nj = offs[(size_t)h * offs_stride + j + 1] - offs[(size_t)h * offs_stride + j];
     p_beg = poff[(size_t)h * offs_stride + j]; p_end = poff[(size_t)h * offs_stride + j + 1];
@@ -1571,7 +1776,7 @@ __global__ __launch_bounds__(256) void stage_open(const T* __restrict__ X, OpenC
 //   assignment: as assign_mfma, D[32 centres x 32 points]; a wave takes every NW-th tile of 32 points and
 //               runs free of the other waves, with the rows of its next tile in flight;
 //   update:     the wave stages its 32 points in LDS and adds S^T[32 dims x 32 centres] += X^T E for
-//               them, E the one-hot labels (see assign_mfma<D, true>), into accumulators it keeps for
+//               them, E the one-hot labels (see stage_pass), into accumulators it keeps for
 //               the whole pass; the waves' partial sums are then added in a fixed order, so the result
 //               is deterministic;
 //   filter:     squared distances of the last pass stay in LDS; U is compacted in ascending order.
@@ -1614,7 +1819,7 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
   __syncthreads();
   if (!s_st.active) return;                 // the stage head that ran before this launch closed the head
   const float t2 = cfg.tau[1];
-  // transpose-read addressing of the X^T operand (see assign_mfma<D, true>)
+  // transpose-read addressing of the X^T operand (see stage_pass)
   const int i16 = lane & 15;
   const int vrow = 4 * hb + (i16 >> 2);
   const int gl = 2 * ((lane >> 4) & 1) + ((i16 & 3) >> 1);
@@ -1995,37 +2200,65 @@ __global__ __launch_bounds__(256) void mse_final(const double* __restrict__ part
 static inline int chk() { return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL; }
 
 int reduce_part_rows() { return REDUCE_ROWS; }
-int assign_block_sum_centres() { return ACC_MAXM; }
-// rows per block of the part-sum table that hold for any head with up to m centres: the most acc_parts(i) * i over i <= m
-int assign_block_sum_rows(int m) { return 4 * m < ACC_MAXM ? 4 * m : ACC_MAXM; }
+int pass_sum_centres() { return ACC_MAXM; }
+int pass_points(bool combine) { return combine ? 2 * PASS_POINTS : PASS_POINTS; }
+// Every workgroup of a head reads all of its sums: up to 128 KB they cost less than the launch they save (up to 256 KB the
+// same time either way), up to 64 centres or (d=128) 40: each 32 or 16 are another trip (of 3 000 points, d=128, 100 centres at
+// first, a call took 540 us without that limit, 477 with launches).  Past some 512 workgroups the chip is full without waves to
+// spare for it.
+bool combine_fits(int d, int heads, int n_bound, int m_bound) {
+  const long long nb = (n_bound + 2 * PASS_POINTS - 1) / (2 * PASS_POINTS);
+  return nb * m_bound * d * 4 <= (128 << 10) && m_bound <= (d == 64 ? 64 : 40) && nb * heads <= 512;
+}
 
-int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, int mode, int m_const, int cap,
+int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, int m_bound, int mode, int m_const, int cap,
                   const KState* st, const int32_t* ulist, const void* X, const void* cent_lp, const float* bias,
-                  int32_t* labels, float* dist2, float* blk_sum, int32_t* blk_cnt, int P, int32_t* keep_lab,
-                  float* keep_score, const int32_t* seed_lab, const float* seed_score, const float* tau, int32_t* keep_cnt,
-                  int keep_stride, double* dist_sum) {
-  if ((mode == 3 || keep_lab || seed_lab) && (dtype != ADACLUSTER_BF16 || blk_sum)) return ADACLUSTER_E_INTERNAL;
+                  int32_t* labels, float* dist2, int32_t* keep_lab, float* keep_score, const int32_t* seed_lab,
+                  const float* seed_score, const float* tau, int32_t* keep_cnt, int keep_stride, double* dist_sum) {
+  if ((mode == 3 || keep_lab || seed_lab) && dtype != ADACLUSTER_BF16) return ADACLUSTER_E_INTERNAL;
   AssignCfg c{mode, m_const, N, cap, st, ulist, keep_lab, keep_score, seed_lab, seed_score, tau, keep_cnt, keep_stride, dist_sum};
   if (dtype == ADACLUSTER_BF16) {
     dim3 g((n_bound + ASSIGN_POINTS_LP - 1) / ASSIGN_POINTS_LP, H);
-    const AccumOut ao{blk_sum, blk_cnt, P, (int)g.x};
-    if (blk_sum) {
-      if (d == 64) assign_mfma<64, true><<<g, 256, 0, s>>>((const bf16raw*)X, c, (const bf16raw*)cent_lp, bias, labels, dist2, ao);
-      else assign_mfma<128, true><<<g, 256, 0, s>>>((const bf16raw*)X, c, (const bf16raw*)cent_lp, bias, labels, dist2, ao);
-    } else {
-      if (d == 64) assign_mfma<64, false><<<g, 256, 0, s>>>((const bf16raw*)X, c, (const bf16raw*)cent_lp, bias, labels, dist2, ao);
-      else assign_mfma<128, false><<<g, 256, 0, s>>>((const bf16raw*)X, c, (const bf16raw*)cent_lp, bias, labels, dist2, ao);
-    }
+    if (d == 64) assign_mfma<64><<<g, 256, 0, s>>>((const bf16raw*)X, c, (const bf16raw*)cent_lp, bias, labels, dist2);
+    else assign_mfma<128><<<g, 256, 0, s>>>((const bf16raw*)X, c, (const bf16raw*)cent_lp, bias, labels, dist2);
   } else {
-    if (blk_sum) return ADACLUSTER_E_INTERNAL;     // block sums exist for bf16 only
     dim3 g((n_bound + ASSIGN_POINTS_F32 - 1) / ASSIGN_POINTS_F32, H);
-    if (d == 64) assign_f32<64><<<g, 512, 0, s>>>((const float*)X, c, (const float*)cent_lp, bias, labels, dist2);
-    else assign_f32<128><<<g, 512, 0, s>>>((const float*)X, c, (const float*)cent_lp, bias, labels, dist2);
+    const float *x = (const float*)X, *ce = (const float*)cent_lp;
+    if (m_bound <= 32) {
+      if (d == 64) assign_f32<64, 1><<<g, 128, 0, s>>>(x, c, ce, bias, labels, dist2);
+      else assign_f32<128, 1><<<g, 128, 0, s>>>(x, c, ce, bias, labels, dist2);
+    } else {
+      if (d == 64) assign_f32<64, 4><<<g, 512, 0, s>>>(x, c, ce, bias, labels, dist2);
+      else assign_f32<128, 4><<<g, 512, 0, s>>>(x, c, ce, bias, labels, dist2);
+    }
   }
   return chk();
 }
 
-// one-read pass of the query clustering (bf16, at most assign_block_sum_centres() centres): NP = walks per head
+int launch_stage_pass(hipStream_t s, int d, int H, int N, int n_bound, int m_bound, int cap, const KState* st, const int32_t* ulist,
+                      const void* X, void* cent_lp, float* cent_f32, float* bias, bool wide, const StageSums* prev, const StageSums* out,
+                      float* dist2, int32_t* keep_lab, float* keep_score, const float* tau, int32_t* keep_cnt, int keep_stride,
+                      double* dist_sum) {
+  const AssignCfg c{1, 0, N, cap, st, ulist, keep_lab, keep_score, nullptr, nullptr, tau, keep_cnt, keep_stride, dist_sum};
+  const int nb = (n_bound + pass_points(wide) - 1) / pass_points(wide);
+  const PassSums in = prev ? PassSums{prev->psum, prev->bcnt, m_bound * nb, nb} : PassSums{}, to = out ? PassSums{out->psum, out->bcnt, m_bound * nb, nb} : PassSums{};
+  if (m_bound > ACC_MAXM || (prev && !wide) || (!out && !dist2)) return ADACLUSTER_E_INTERNAL;
+  const dim3 g(nb, H);
+  const bf16raw* x = (const bf16raw*)X;
+  bf16raw* lp = (bf16raw*)cent_lp;
+  if (d == 64) {
+    if (prev) stage_pass<64, 8, true><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to);
+    else if (wide) stage_pass<64, 8, false><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to);
+    else stage_pass<64, 4, false><<<g, 256, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to);
+  } else {
+    if (prev) stage_pass<128, 8, true><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to);
+    else if (wide) stage_pass<128, 8, false><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to);
+    else stage_pass<128, 4, false><<<g, 256, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to);
+  }
+  return chk();
+}
+
+// one-read pass of the query clustering (bf16, at most pass_sum_centres() centres): NP = walks per head
 int qpass_walks(int N) { const int sb = (N + 127) / 128; const int subs = (sb + 63) / 64; return (sb + subs - 1) / subs; }
 int launch_qpass(hipStream_t s, int d, int H, int N, int m, int cap, int weighted, const void* X, const void* cent_lp,
                  const float* bias, float* psum, int32_t* pcnt) {
@@ -2113,9 +2346,9 @@ int launch_tau_abs(hipStream_t s, float tau_abs, float* tau_out) {
 }
 
 int stage_points_per_count(int dtype) { return dtype == ADACLUSTER_BF16 ? ASSIGN_POINTS_LP : ASSIGN_POINTS_F32; }
-int launch_keep_count(hipStream_t s, int dtype, const KState* st, int H, int N, const float* dist2, const double* dist_sum, float factor,
+int launch_keep_count(hipStream_t s, const KState* st, int H, int N, const float* dist2, const double* dist_sum, int sums, float factor,
                       float* tau, int32_t* cnt, int cnt_stride, int* items) {
-  const int per = stage_points_per_count(dtype), count = dist_sum ? H * ((N + per - 1) / per) : 0;
+  const int count = dist_sum ? H * sums : 0;
   TauCfg t{dist_sum, count, (double)H * (double)N, factor, tau};
   if (count > TAU_SUMS) {
     tau_final<<<1, 1024, 0, s>>>(t);

@@ -28,14 +28,25 @@ int launch_sort(hipStream_t st, int H, int N, int n_bound, int m_bound, const in
                 const SortScratch& sc, int32_t* poff = nullptr, int part_rows = 0, int32_t* pcl = nullptr, int P = 0,
                 int* poff_done = nullptr, int foreign = 0);
 
-int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, int mode, int m_const, int cap,
+// n_bound, m_bound: no head has more points or centres.
+int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, int m_bound, int mode, int m_const, int cap,
                   const KState* st, const int32_t* ulist, const void* X, const void* cent_lp, const float* bias,
-                  int32_t* labels, float* dist2, float* blk_sum = nullptr, int32_t* blk_cnt = nullptr, int P = 0,
+                  int32_t* labels, float* dist2,
                   int32_t* keep_lab = nullptr, float* keep_score = nullptr, const int32_t* seed_lab = nullptr,
                   const float* seed_score = nullptr,
                   const float* tau = nullptr, int32_t* keep_cnt = nullptr, int keep_stride = 0, double* dist_sum = nullptr);
-int assign_block_sum_centres();   // most centres the assignment kernel keeps block sums for
-int assign_block_sum_rows(int m); // rows per block of their table, with up to m centres
+// A pass of a stage of Algorithm 1 with at most pass_sum_centres() centres (bf16).  An update pass (out) leaves the member sums
+// and counts of every pass_points(wide) points; launch_finalize(blk_cnt = out->bcnt, nb_stride = their number) turns them
+// into centres, or (`wide`, where combine_fits says so) the next pass does, which then takes them as `prev` (another
+// table than its `out`).  The last pass (out NULL) leaves distances and, where asked for, what launch_assign leaves besides.
+struct StageSums { float* psum; int32_t* bcnt; };     // [H][m_bound * blocks][d], [H][blocks][pass_sum_centres()]
+int pass_sum_centres();
+int pass_points(bool wide);
+bool combine_fits(int d, int heads, int n_bound, int m_bound);
+int launch_stage_pass(hipStream_t s, int d, int H, int N, int n_bound, int m_bound, int cap, const KState* st, const int32_t* ulist,
+                      const void* X, void* cent_lp, float* cent_f32, float* bias, bool wide, const StageSums* prev, const StageSums* out,
+                      float* dist2 = nullptr, int32_t* keep_lab = nullptr, float* keep_score = nullptr, const float* tau = nullptr,
+                      int32_t* keep_cnt = nullptr, int keep_stride = 0, double* dist_sum = nullptr);
 int launch_seg_reduce(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int P,
                       const KState* st, int normalize, int want_box, const void* X, const int32_t* perm,
                       const int32_t* offs, int offs_stride, int32_t* poff, int32_t* pcl, float* psum, float* pnorm, float* pmin,
@@ -60,8 +71,8 @@ bool direct_update_fits(int dtype, int n_bound, int m_bound);
 int launch_update_direct(hipStream_t s, int d, int H, int N, int m_bound, int cap, int master_stride, const KState* st,
                          const int32_t* labels, const int32_t* ulist, const void* X, float* master, void* assign_lp,
                          float* assign_f32, float* bias);
-// One pass of a k-means with at most assign_block_sum_centres() centres in one read of the points (bf16):
-// assignment and (weighted) centroid sums together.  psum [H][m * NP][d], pcnt [H][NP][assign_block_sum_centres()]
+// One pass of a k-means with at most pass_sum_centres() centres in one read of the points (bf16):
+// assignment and (weighted) centroid sums together.  psum [H][m * NP][d], pcnt [H][NP][pass_sum_centres()]
 // with NP = qpass_walks(N); launch_finalize(..., blk_cnt = pcnt, nb_stride = NP, nb_const = NP) turns them into centres.
 int qpass_walks(int N);
 int launch_qpass(hipStream_t s, int d, int H, int N, int m, int cap, int weighted, const void* X, const void* cent_lp,
@@ -80,8 +91,8 @@ struct StageFilter {
 };
 int stage_points_per_count(int dtype);
 // The threshold (with dist_sum, what launch_assign left; NULL: `tau` holds it) and the survivors of the first stage.
-int launch_keep_count(hipStream_t s, int dtype, const KState* st, int H, int N, const float* dist2, const double* dist_sum, float factor,
-                      float* tau, int32_t* cnt, int cnt_stride, int* items);
+int launch_keep_count(hipStream_t s, const KState* st, int H, int N, const float* dist2, const double* dist_sum, int sums, float factor,
+                      float* tau, int32_t* cnt, int cnt_stride, int* items);      // sums: per head
 // Filter of the stage that ends (f; NULL: none, the first stage opens), head of the loop of Algorithm 1, initial centres of
 // the stage that opens.  n_bound, m_bound: no head has more points in the stage that ends, or centres in the one that opens.
 // The state goes from `in` to `out`, which must differ; sums: 4 device integers; report (mapped host memory, may be
@@ -114,7 +125,7 @@ int launch_quest_scores(hipStream_t s, int dtype, int form, int clamp, int H, in
                         const void* Rp, const void* Rn, float* S);
 // register-only loop of bf16 MFMAs on every SIMD of the chip (measures what the matrix cores sustain)
 int launch_mfma_probe(hipStream_t s, int iters, float* sink, size_t sink_floats, double* flops);
-int attn_f32_splits(int H, int N, int Cq);   // workgroups a key list of the fp32 kernel is split over
+int attn_f32_splits(int H, int N, int Cq);   // most pieces a key list of the fp32 kernel may go in
 int attn_tile_record();      // ints per query-tile record
 int attn_split_slots();      // partial slots per head for the chunks of cut key lists (also extra tile records)
 int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int maxr, int maxtiles, int BM,

@@ -62,6 +62,40 @@ def test_block_sums_around_the_changes_of_their_split(d, m):
         check_stages_against_oracle(K[h], out, h, 1, 2, p.tau_abs)
 
 
+@pytest.mark.parametrize("d,N,m,iters", [(64, 512, 20, 2), (64, 513, 33, 2), (128, 511, 20, 2), (128, 1025, 40, 2),      # one, two, three blocks of 512
+                                         (64, 2560, 100, 2), (128, 2048, 60, 2),      # as much as is combined
+                                         (64, 2561, 100, 2), (128, 2049, 60, 2),      # and past it: a launch of its own
+                                         (64, 700, 20, 1), (64, 700, 20, 4), (128, 700, 20, 4)])       # no update, three
+def test_stage_centres_combined_by_the_next_pass(d, N, m, iters):
+    """Where a head's member sums are few, the next pass forms the centres itself.  Head 1 is m runs of near rows, two of
+    them alike with the same row in the places that become initial centres, so one of these stays empty and keeps its place;
+    head 2 is the data of head 0 in reverse."""
+    H = 3
+    _, K, _ = wl.make_small(90 + m, N, d, 14, dtype="bf16", H=H)
+    K[2] = K[0][::-1]
+    at = ((2 * np.arange(m) + 1) * N) // (2 * m)
+    run = (np.arange(N) * m) // N
+    rng = np.random.default_rng(3)
+    means = 2.0 * rng.standard_normal((m, d))
+    K[1] = wl.round_bf16_f32((means[np.where(run == 5, 4, run)] + 0.05 * rng.standard_normal((N, d))).astype(np.float32))
+    K[1, at[5]] = K[1, at[4]]
+    p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=4, k_iters=iters, k_m0=m, k_m_min=min(m, 12), k_max_clusters=4 * m, k_max_stages=1,
+                 tau_abs=0.6 * d ** 0.5)
+    out = B.adacluster_kcluster(p, to_dev(K, B.BF16))
+    rep = B.adacluster_kcluster(p, to_dev(K, B.BF16))
+    torch.cuda.synchronize()
+    assert torch.equal(out["k_assign_centroids"][:, :m], rep["k_assign_centroids"][:, :m])
+    C = out["k_assign_centroids"].float().cpu().numpy()
+    assert np.array_equal(C[1, 5], K[1, at[5]])                     # the empty one
+    if iters <= 2:
+        for h in (0, 2):
+            check_stages_against_oracle(K[h], out, h, 1, iters, p.tau_abs)
+    else:           # (a longer trajectory parts from the oracle's at near-ties: most centres, not all)
+        for h in (0, 2):
+            _, ref, _ = orc.euclid_kmeans(K[h].astype(np.float64), m, iters, round_fn=orc.round_to_bf16)
+            assert float((C[h, :m] == ref).mean()) > 0.8
+
+
 @pytest.mark.parametrize("d,H,N,iters", [(64, 1, 4000, 3), (64, 70, 4000, 3), (128, 72, 5000, 3), (128, 60, 5000, 3),
                                          (128, 72, 8192, 1), (64, 66, 8192, 1), (64, 66, 8193, 1)])
 def test_late_stages_on_either_side_of_the_one_launch_kernel(d, H, N, iters):
