@@ -375,10 +375,12 @@ int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
 }
 
 // ---- Algorithm 1 ---------------------------------------------------------------------------
+// beside(): called once, where a cold start first waits for the device, or at the end of its stages (a warm start: not at all).
+template <typename F>
 int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const void* K, int32_t* k_labels,
                  float* k_centroids, float* k_assign, float* k_bmin, float* k_bmax, int32_t* k_sizes,
                  int32_t* k_count, int32_t* full_flag, int32_t* k_stage_offs, int32_t* k_stage_of,
-                 float* tau_used, int* kc_bound_out) {
+                 float* tau_used, int* kc_bound_out, const F& beside) {
   const Dims D = dims_of(p);
   int kc_bound = 0;   // sum over stages of the largest stage centre count: an upper bound of every |C|
   int pending = 0;                   // the last report (of this stage) may still be in flight when the stage loop ends
@@ -427,6 +429,8 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   if (!rb) return fail(ADACLUSTER_E_INTERNAL, "stage read-back set-up failed: %s", hipGetErrorString(hipGetLastError()));
   int n_bound = D.N, m_bound = p->k_m0 < D.N ? p->k_m0 : D.N, heads = D.H;
   KState* other = w.kstate2;                       // the stage head reads one and writes the other
+  bool called = false;
+  auto before_wait = [&]() { const bool first = !called; called = true; return first ? beside() : 0; };
   StageFilter filter{};                            // how the stage before ended
   for (int t = 0; t <= p->k_max_stages; ++t) {
     // the stage head writes its report straight into the pinned slot (no copy in between)
@@ -436,6 +440,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                              t > 0 ? rb->dev + 4 * t : nullptr, rb->epoch, p->k_m0, K, w.master, w.cent_lp, k_assign, w.bias));
     pending = t;
     if (t > 1) {
+      RET_IF(before_wait());
       if (!stage_report_landed(*rb, t - 1, st))
         return fail(ADACLUSTER_E_INTERNAL, "stage read-back failed: %s", hipGetErrorString(hipGetLastError()));
       const int32_t* summ = rb->host + 4 * (t - 1);
@@ -451,6 +456,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       // points through the launch chain sized for all of them (label sort, segmented
       // reduction).  Then, once per call, the host waits for the report of the stage it is about to
       // enqueue; the other stream keeps the device busy meanwhile.
+      RET_IF(before_wait());
       if (!stage_report_landed(*rb, 1, st))
         return fail(ADACLUSTER_E_INTERNAL, "stage read-back failed: %s", hipGetErrorString(hipGetLastError()));
       const int32_t* now = rb->host + 4;
@@ -520,6 +526,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     if (t == 0) RET_IF(launch_keep_count(st, cur, D.H, D.N, w.dist2, dist_sum, (D.N + counted - 1) / counted, p->tau_factor, w.tau, w.blockcnt,
                                          D.ncnt, &filter.items));
   }
+  RET_IF(before_wait());
   kc_bound = kc_bound < D.cap ? kc_bound : D.cap;
   // last step of Algorithm 1: nearest centre among all stage centres, then member statistics.  bf16: the
   // nearest first-stage centre of every point is known from stage 0, so only the later stages' centres are visited.
@@ -623,7 +630,7 @@ int adacluster_kcluster(const adacluster_params* p, const void* K, int32_t* k_la
   if ((rc = check_ws(p, ws, ws_bytes, &w))) return rc;
   prof_begin((hipStream_t)stream);
   rc = run_kcluster(p, w, (hipStream_t)stream, K, k_labels, k_centroids, k_assign_centroids, k_box_min, k_box_max,
-                    k_sizes, k_count, full_flag, k_stage_offs, k_stage_of, tau_used, nullptr);
+                    k_sizes, k_count, full_flag, k_stage_offs, k_stage_of, tau_used, nullptr, [] { return 0; });
   prof_mark(EV_KCLUSTER, (hipStream_t)stream, EV_START);
   return rc;
 }
@@ -753,15 +760,30 @@ int adacluster_attn(const adacluster_params* p, const void* Q, const void* K, co
   // host waits for the second stream before it reports the error.
   auto drained = [&](int code) { (void)hipStreamSynchronize(aux->s); return code; };
   hipStream_t qs = aux->s;      // (measured: run in front of Algorithm 1 on the caller's stream instead, every configuration is 1-6 % slower)
-  rc = run_qcluster(p, w, qs, Q, q_labels, q_centroids, q_assign_centroids, q_sizes, q_mean_norm);
-  prof_mark(EV_QCLUSTER, qs, EV_START);
-  if (hipEventRecord(aux->join, qs) != hipSuccess) return drained(fail(ADACLUSTER_E_INTERNAL, "stream join failed"));
+  bool joinable = false;
+  auto queries = [&]() {
+    const int r = run_qcluster(p, w, qs, Q, q_labels, q_centroids, q_assign_centroids, q_sizes, q_mean_norm);
+    prof_mark(EV_QCLUSTER, qs, EV_START);
+    joinable = hipEventRecord(aux->join, qs) == hipSuccess;
+    return joinable || r ? r : fail(ADACLUSTER_E_INTERNAL, "stream join failed");
+  };
+  // Algorithm 1 is the longer chain.  Where it waits for a report, it goes first, and the query clustering is enqueued while the
+  // host would only wait; its nine launches ahead of Algorithm 1 kept the device waiting (4 096 fp32 tokens 240 -> 221 us;
+  // 32 760 tokens, a call alone, 863 -> 840).  Where no report is waited for before the end (a warm start, or one launch for
+  // everything after the first stage) it stays first: 1 500 tokens 152 us, 168 the other way.
+  const bool q_first = p->k_init_mode == 1 || (p->dtype == ADACLUSTER_BF16 && p->N <= small_stage_points(p->d, p->H) && p->k_m0 <= small_stage_centres());
+  auto nothing = [] { return 0; };
   int kc_bound = capacity(p);
-  int rck = rc ? 0 : run_kcluster(p, w, st, K, k_labels, k_centroids, k_assign_centroids, k_bmin, k_bmax, k_sizes,
-                                   k_count, full_flag, o.k_stage_offs, o.k_stage_of, tau_used, &kc_bound);
+  auto keys = [&](const auto& beside) {
+    return run_kcluster(p, w, st, K, k_labels, k_centroids, k_assign_centroids, k_bmin, k_bmax, k_sizes, k_count, full_flag,
+                        o.k_stage_offs, o.k_stage_of, tau_used, &kc_bound, beside);
+  };
+  rc = q_first ? queries() : 0;
+  if (!rc) rc = q_first ? keys(nothing) : keys(queries);
   prof_mark(EV_KCLUSTER, st, EV_START);
+  if (!joinable) return drained(rc ? rc : ADACLUSTER_E_INTERNAL);
   if (hipStreamWaitEvent(st, aux->join, 0) != hipSuccess) return drained(fail(ADACLUSTER_E_INTERNAL, "stream join failed"));
-  if (rc || rck) return rc ? rc : rck;      // (what was queued on the second stream has been joined)
+  if (rc) return rc;                        // (what was queued on the second stream has been joined)
   prof_mark(EV_JOIN, st);
   const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)p->d);
   rc = launch_select(st, p->H, p->q_clusters, capacity(p), p->d, p->score_mode, p->select_mode, p->topk, p->top_p,
