@@ -102,6 +102,23 @@ def test_more_ranges_than_the_lds_table_holds():
         print("many ranges", h, check(got[h], ref, B.BF16))
 
 
+@pytest.mark.parametrize("dtype,d", [(B.BF16, 64), (B.BF16, 128), (B.F32, 64)])
+def test_key_lists_of_many_one_key_ranges(dtype, d):
+    """The planner writes four entries of a key list at a time, from its ranges in LDS (up to 512 of them) or in memory.
+    Every other cluster of one key gives lists of r ranges that end one key further each; the last list joins two-key ranges
+    to the large cluster at the end."""
+    counts = [1, 2, 3, 4, 5, 63, 65, 511, 512, 513, 0]
+    H, N, Cq, Ck = 1, 1400, len(counts), 1031
+    Q, K, V = wl.make_small(17, N, d, 10, dtype="bf16" if dtype == B.BF16 else "f32", H=H)
+    rng = np.random.default_rng(18)
+    ql = rng.integers(0, Cq, (H, N)).astype(np.int32)
+    kl = np.minimum(rng.permutation(N), Ck - 1).astype(np.int32)[None, :]
+    sel = [[np.arange(1, 2 * r, 2, dtype=np.int64) for r in counts[:-1]] + [np.flatnonzero(np.arange(Ck) % 3)]]
+    sel[0][-1] = np.append(sel[0][-1], Ck - 1) if sel[0][-1][-1] != Ck - 1 else sel[0][-1]
+    got = run_sparse(Q, K, V, ql, kl, sel, dtype, Cq, Ck)
+    check(got[0], orc.sparse_attention_gather(Q[0], K[0], V[0], ql[0], kl[0], sel[0]), dtype)
+
+
 @pytest.mark.parametrize("H", [8, 11])
 def test_heads_dealt_to_xcds_whole_and_leftover_heads(H):
     """Small heads take the mapping that gives every XCD whole heads, eight at a time, and splits the
