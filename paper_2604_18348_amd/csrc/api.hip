@@ -197,6 +197,7 @@ struct WS {
   int32_t* k_labels; float* k_centroids; float* k_assign; float* k_bmin; float* k_bmax;
   int32_t* k_sizes; int32_t* k_count; int32_t* full_flag; int32_t* sel_idx; int32_t* sel_cnt;
   int32_t* one_count;   // [H] constant key-cluster count for the dense plan
+  int32_t* sel_keys;    // [H][Cq] keys of every query cluster's list (fused call)
   adacluster_head_stats* stats;   // [H] staging area of adacluster_stats_fetch
 };
 
@@ -315,6 +316,7 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(sel_idx, int32_t*, H * (size_t)D.Cq * D.cap * 4);
   TAKE(sel_cnt, int32_t*, H * (size_t)D.Cq * 4);
   TAKE(one_count, int32_t*, H * 4);
+  TAKE(sel_keys, int32_t*, H * (size_t)D.Cq * 4);
   TAKE(stats, adacluster_head_stats*, H * sizeof(adacluster_head_stats));
 #undef TAKE
   if (w) w->base = base;
@@ -560,13 +562,13 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
 // ---- attention over selected clusters, given both sorts ---------------------------------------
 // range lists, row offsets and query tiles from the selection, then the attention kernel
 int run_plan_attention(const adacluster_params* p, const WS& w, hipStream_t st, const void* Q, void* O,
-                       const int32_t* k_count, const int32_t* sel_idx, const int32_t* sel_cnt, int prof_from,
+                       const int32_t* k_count, const int32_t* sel_idx, const int32_t* sel_cnt, const int32_t* sel_keys, int prof_from,
                        const void* K, const void* V) {
   const Dims D = dims_of(p);
   const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)D.d);
   RET_IF(launch_plan_sparse(st, p->dtype, D.H, D.Cq, D.cap, D.maxr, D.maxtiles, D.BM, w.offs_q, D.Cq + 1, w.offs_k,
                             D.cap + 1, k_count, sel_idx, sel_cnt, w.rng_start, w.rng_pre, w.rng_cnt, w.tiles, w.ntiles,
-                            w.merge, w.nmerge, key_row_scale(p), w.krow, attn_krow_stride(D.N), w.perm_k, D.N));
+                            w.merge, w.nmerge, key_row_scale(p), w.krow, attn_krow_stride(D.N), w.perm_k, D.N, sel_keys));
   prof_mark(EV_PLAN, st, prof_from);
   RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, D.Cq, D.maxtiles, scale, Q, K, V, O, w.perm_q,
                           w.tiles, w.ntiles, w.part_o, w.part_ml, w.merge, w.nmerge,
@@ -695,7 +697,7 @@ int adacluster_select(const adacluster_params* p, const float* q_centroids, cons
   const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)p->d);
   RET_IF(launch_select((hipStream_t)stream, p->H, p->q_clusters, capacity(p), p->d, p->score_mode, p->select_mode,
                        p->topk, p->top_p, scale, q_centroids, q_mean_norm, k_centroids, k_box_min, k_box_max, k_sizes,
-                       k_count, full_flag, sel_idx, sel_cnt, capacity(p), w.scores));
+                       k_count, full_flag, sel_idx, sel_cnt, capacity(p), w.scores, nullptr));
   return 0;
 }
 
@@ -717,7 +719,7 @@ int adacluster_sparse_attn(const adacluster_params* p, const void* Q, const void
   RET_IF(launch_sort(st, D.H, D.N, D.N, D.cap, k_labels, nullptr, nullptr, 0, k_count, 1, nullptr, 0, w.perm_k, w.offs_k,
                      D.cap + 1, w.sort, nullptr, 0, nullptr, 0, nullptr, 1));
   prof_mark(EV_SELECT, st);   // (time of the two label sorts when called stand-alone)
-  return run_plan_attention(p, w, st, Q, O, k_count, sel_idx, sel_cnt, -1, K, V);
+  return run_plan_attention(p, w, st, Q, O, k_count, sel_idx, sel_cnt, nullptr, -1, K, V);
 }
 
 int adacluster_attn(const adacluster_params* p, const void* Q, const void* K, const void* V, void* O,
@@ -788,11 +790,11 @@ int adacluster_attn(const adacluster_params* p, const void* Q, const void* K, co
   const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)p->d);
   rc = launch_select(st, p->H, p->q_clusters, capacity(p), p->d, p->score_mode, p->select_mode, p->topk, p->top_p,
                      scale, q_centroids, q_mean_norm, k_centroids, k_bmin, k_bmax, k_sizes, k_count, full_flag,
-                     sel_idx, sel_cnt, kc_bound, w.scores);
+                     sel_idx, sel_cnt, kc_bound, w.scores, w.sel_keys);
   if (rc) return drained(rc == ADACLUSTER_E_INTERNAL ? fail(rc, "HIP launch failed: %s", hipGetErrorString(hipGetLastError())) : rc);
   prof_mark(EV_SELECT, st, EV_JOIN);
   // both label sorts were left in the workspace by the clustering steps
-  rc = run_plan_attention(p, w, st, Q, O, k_count, sel_idx, sel_cnt, EV_SELECT, K, V);
+  rc = run_plan_attention(p, w, st, Q, O, k_count, sel_idx, sel_cnt, w.sel_keys, EV_SELECT, K, V);
   return rc ? drained(rc) : 0;
 }
 

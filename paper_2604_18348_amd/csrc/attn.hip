@@ -33,14 +33,136 @@ static constexpr int KROW_PAD = 8 * 64;  // entries of the row-offset table a ke
 // rng_cnt   [H][Cq]
 // tiles     [H][maxtiles] x {cluster, first sorted query position, rows, first key tile, end key
 //           tile, partial slot or -1, keys of the cluster's whole list, not 0: the second 32 rows of 64 (fp32)}; ntiles [H]
-__global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, int row_scale,
+__device__ __forceinline__ int wave_prefix(int v, int lane) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) { const int u = __shfl_up(v, o); if (lane >= o) v += u; }
+  return v;
+}
+
+// Query tiles of a head, cluster by cluster.  A query cluster whose key list is much longer than
+// the head's average (top-p selections can be that skewed) would make its few workgroups the whole
+// critical path of the launch, so such a list is cut into chunks of key tiles: each chunk is a
+// workgroup of its own that leaves unnormalised (O, m, l) in a partial slot, and attn_merge
+// combines the slots of a query tile.  merge [H][slots] x {first query position, rows, first slot,
+// chunks}; a head has `slots` partial slots, and lists stay whole once they are used up.
+constexpr int PLAN_ARRAYS = 8;      // integers of LDS per query cluster
+template <bool KNOWN>
+__device__ __forceinline__ void tiles_of_head(int32_t* sm, int h, int Cq, int maxr, int maxtiles, int BM, int slots, int allow_split,
+                                              const int32_t* __restrict__ q_offs, int q_offs_stride, const int32_t* __restrict__ lengths,
+                                              const int32_t* __restrict__ rng_pre, const int32_t* __restrict__ rng_cnt,
+                                              int32_t* __restrict__ tiles, int32_t* __restrict__ ntiles,
+                                              int32_t* __restrict__ merge, int32_t* __restrict__ nmerge) {
+  const int tid = threadIdx.x, C = Cq;
+  const int32_t* qo = q_offs + (size_t)h * q_offs_stride;
+  int32_t* tl = tiles + (size_t)h * maxtiles * TILE_REC;
+  int32_t* ml = merge + (size_t)h * slots * 4;
+  int32_t *const s_T = sm, *const s_nq = sm + C, *const s_pieces = sm + 2 * C, *const s_tile0 = sm + 3 * C, *const s_slot0 = sm + 4 * C,
+          *const s_merge0 = sm + 5 * C, *const s_tot = sm + 6 * C, *const s_list = sm + 7 * C;
+  for (int c = tid; c < C; c += 256) {
+    s_nq[c] = (qo[c + 1] - qo[c] + BM - 1) / BM;
+    int tot;
+    if constexpr (KNOWN) tot = lengths[(size_t)h * Cq + c];
+    else tot = rng_pre[((size_t)h * Cq + c) * (maxr + 1) + rng_cnt[(size_t)h * Cq + c]];
+    s_T[c] = (tot + 63) / 64;
+    s_tot[c] = tot;
+  }
+  __syncthreads();
+  // A thread looks after the clusters tid * per .., so that prefix sums over the threads are in cluster order.  Only the
+  // lists that are cut are dealt with one after the other (all of them by one thread: 15 us at 65 clusters, now 6).
+  const int per = (C + 255) / 256, c0 = min(C, tid * per), c1 = min(C, c0 + per), lane = tid & 63, wave = tid >> 6;
+  __shared__ long long w_work[4];
+  __shared__ int32_t w_a[4], w_b[4];
+  __shared__ int32_t s_cut, s_ntiles;
+  {
+    // key tiles per chunk of a list that is cut: twice the average list of the head, at least 16
+    long long work = 0; int qtiles = 0;
+    for (int c = c0; c < c1; ++c) { work += (long long)s_nq[c] * s_T[c]; qtiles += s_nq[c]; }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) { work += __shfl_xor(work, o); qtiles += __shfl_xor(qtiles, o); }
+    if (lane == 0) { w_work[wave] = work; w_a[wave] = qtiles; }
+  }
+  __syncthreads();
+  const long long work = w_work[0] + w_work[1] + w_work[2] + w_work[3];
+  const int qtiles = w_a[0] + w_a[1] + w_a[2] + w_a[3];
+  const int chunk = max(16, 2 * (qtiles > 0 ? (int)((work + qtiles - 1) / qtiles) : 0));
+  // which lists are cut: the long ones are listed in cluster order, and one thread deals the slots out while they last
+  int cuts = 0;
+  for (int c = c0; c < c1; ++c) { s_pieces[c] = 1; cuts += allow_split && s_T[c] > 2 * chunk; }
+  const int cin = wave_prefix(cuts, lane);
+  if (lane == 63) w_b[wave] = cin;
+  __syncthreads();
+  {
+    int at = cin - cuts;
+    for (int w = 0; w < wave; ++w) at += w_b[w];
+    for (int c = c0; c < c1; ++c) if (allow_split && s_T[c] > 2 * chunk) s_list[at++] = c;
+    if (tid == 255) s_cut = at;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    int used = 0, nm = 0;
+    for (int i = 0; i < s_cut; ++i) {
+      const int c = s_list[i], T = s_T[c];
+      int pieces = min(16, (T + chunk - 1) / chunk);
+      if (used + pieces * s_nq[c] > slots) pieces = max(1, (slots - used) / max(s_nq[c], 1));   // fewer, longer chunks
+      if (pieces > 1) {
+        const int per_piece = (T + pieces - 1) / pieces;
+        pieces = max(1, (T + per_piece - 1) / max(per_piece, 1));          // no empty chunk
+      }
+      s_pieces[c] = pieces; s_slot0[c] = used; s_merge0[c] = nm;
+      if (pieces > 1) { used += s_nq[c] * pieces; nm += s_nq[c]; }
+    }
+    nmerge[h] = nm;
+  }
+  __syncthreads();
+  {                                              // where every cluster's records start
+    int mine = 0;
+    for (int c = c0; c < c1; ++c) mine += s_nq[c] * s_pieces[c];
+    const int incl = wave_prefix(mine, lane);
+    if (lane == 63) w_a[wave] = incl;
+    __syncthreads();
+    int nt = incl - mine;
+    for (int w = 0; w < wave; ++w) nt += w_a[w];
+    for (int c = c0; c < c1; ++c) { s_tile0[c] = nt; nt += s_nq[c] * s_pieces[c]; }
+    if (tid == 255) { ntiles[h] = nt; s_ntiles = nt; }
+  }
+  __syncthreads();
+  // The records, one a thread: the last cluster whose records start at or before it (an empty one shares its start with
+  // the next).  One thread per cluster wrote 625 records one after the other where 20 000 rows are a single cluster.
+  for (int t = tid; t < s_ntiles; t += 256) {
+    int c = 0, hi = C - 1;
+    while (c < hi) { const int mid = (c + hi + 1) >> 1; if (s_tile0[mid] <= t) c = mid; else hi = mid - 1; }
+    const int i = t - s_tile0[c], T = s_T[c], pieces = s_pieces[c], per_piece = (T + pieces - 1) / pieces;
+    const int group = i / pieces, k = i - group * pieces;                    // rows group * BM .. of the cluster, chunk k
+    const int r0 = qo[c] + group * BM, rows = min(BM, qo[c + 1] - r0);
+    int32_t* t6 = tl + (size_t)t * TILE_REC;
+    t6[0] = c; t6[1] = r0; t6[2] = rows;
+    t6[3] = pieces > 1 ? k * per_piece : 0; t6[4] = pieces > 1 ? min(T, (k + 1) * per_piece) : T;
+    t6[5] = pieces > 1 ? s_slot0[c] + i : -1; t6[6] = s_tot[c]; t6[7] = (group * BM) & 63;
+    if (pieces > 1 && k == 0) {
+      int32_t* m = ml + (size_t)(s_merge0[c] + group) * 4;
+      m[0] = r0; m[1] = rows; m[2] = s_slot0[c] + i; m[3] = pieces;
+    }
+  }
+}
+
+// Query tiles beside the key lists: where the selection has left the lengths of the lists, one workgroup of a head plans its
+// tiles while the others write its lists.  As a launch of its own behind them it took 5-6 us more (both sides with the smaller
+// merge launch, below: 1 500 tokens 150 -> 148 us, 4 096 fp32 213 -> 208, 17 550 warm 1014 -> 1005, 32 760 with top-p 840 -> 828).
+struct TilePlan {
+  const int32_t* lengths; const int32_t* q_offs; int q_offs_stride;
+  int maxtiles, BM, slots, allow_split;
+  int32_t* tiles; int32_t* ntiles; int32_t* merge; int32_t* nmerge;
+};
+constexpr int PLAN_BESIDE = 256;       // query clusters up to which the LDS it takes (8 KB each) leaves the lists' workgroups their places
+
+__device__ __forceinline__ void keys_of_list(int i, int h, int Cq, int cap, int maxr, int row_scale,
                             const int32_t* __restrict__ k_offs, int k_offs_stride,
                             const int32_t* __restrict__ k_count,
                             const int32_t* __restrict__ sel_idx, const int32_t* __restrict__ sel_cnt,
                             int32_t* __restrict__ rng_start, int32_t* __restrict__ rng_pre,
                             int32_t* __restrict__ rng_cnt, int32_t* __restrict__ krow, size_t kstride,
                             const int32_t* __restrict__ perm_k, int N) {
-  const int h = blockIdx.y, i = blockIdx.x, tid = threadIdx.x;
+  const int tid = threadIdx.x;
   int32_t* rs = rng_start + ((size_t)h * Cq + i) * maxr;
   int32_t* rp = rng_pre + ((size_t)h * Cq + i) * (maxr + 1);
   constexpr int LR = 512;                  // ranges that LDS holds a copy of
@@ -140,12 +262,24 @@ __global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, in
   if (nr <= LR) fill(l_rs, l_rp); else fill(rs, rp);
 }
 
-// Query tiles of a head, cluster by cluster.  A query cluster whose key list is much longer than
-// the head's average (top-p selections can be that skewed) would make its few workgroups the whole
-// critical path of the launch, so such a list is cut into chunks of key tiles: each chunk is a
-// workgroup of its own that leaves unnormalised (O, m, l) in a partial slot, and attn_merge
-// combines the slots of a query tile.  merge [H][slots] x {first query position, rows, first slot,
-// chunks}; a head has `slots` partial slots, and lists stay whole once they are used up.
+template <bool TILES>
+__global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, int row_scale,
+                            const int32_t* __restrict__ k_offs, int k_offs_stride,
+                            const int32_t* __restrict__ k_count,
+                            const int32_t* __restrict__ sel_idx, const int32_t* __restrict__ sel_cnt,
+                            int32_t* __restrict__ rng_start, int32_t* __restrict__ rng_pre,
+                            int32_t* __restrict__ rng_cnt, int32_t* __restrict__ krow, size_t kstride,
+                            const int32_t* __restrict__ perm_k, int N, TilePlan tp) {
+  const int h = blockIdx.y, i = (int)blockIdx.x - (TILES ? 1 : 0);
+  if (i >= 0) {
+    keys_of_list(i, h, Cq, cap, maxr, row_scale, k_offs, k_offs_stride, k_count, sel_idx, sel_cnt, rng_start, rng_pre, rng_cnt, krow, kstride, perm_k, N);
+  } else if constexpr (TILES) {
+    extern __shared__ int32_t plan_lds[];
+    tiles_of_head<true>(plan_lds, h, Cq, maxr, tp.maxtiles, tp.BM, tp.slots, tp.allow_split, tp.q_offs, tp.q_offs_stride, tp.lengths, nullptr, nullptr, tp.tiles,
+                  tp.ntiles, tp.merge, tp.nmerge);
+  }
+}
+
 __global__ __launch_bounds__(256) void plan_tiles(int Cq, int maxr, int maxtiles, int BM, int slots, int allow_split,
                                                   const int32_t* __restrict__ q_offs, int q_offs_stride,
                                                   const int32_t* __restrict__ rng_pre,
@@ -153,100 +287,9 @@ __global__ __launch_bounds__(256) void plan_tiles(int Cq, int maxr, int maxtiles
                                                   int32_t* __restrict__ tiles, int32_t* __restrict__ ntiles,
                                                   int32_t* __restrict__ merge, int32_t* __restrict__ nmerge) {
   constexpr int MAXC = 4096;                       // the largest q_clusters the library accepts
-  const int h = blockIdx.x, tid = threadIdx.x;
-  const int32_t* qo = q_offs + (size_t)h * q_offs_stride;
-  int32_t* tl = tiles + (size_t)h * maxtiles * TILE_REC;
-  int32_t* ml = merge + (size_t)h * slots * 4;
-  __shared__ int32_t s_T[MAXC], s_nq[MAXC], s_pieces[MAXC], s_tile0[MAXC], s_slot0[MAXC], s_merge0[MAXC], s_tot[MAXC];
-  const int C = min(Cq, MAXC);
-  for (int c = tid; c < C; c += 256) {
-    s_nq[c] = (qo[c + 1] - qo[c] + BM - 1) / BM;
-    const int tot = rng_pre[((size_t)h * Cq + c) * (maxr + 1) + rng_cnt[(size_t)h * Cq + c]];
-    s_T[c] = (tot + 63) / 64;
-    s_tot[c] = tot;
-  }
-  __syncthreads();
-  // A thread looks after the clusters tid * per .., so that prefix sums over the threads are in cluster order.  Only the
-  // lists that are cut are dealt with one after the other (all of them by one thread: 15 us at 65 clusters, now 6).
-  const int per = (C + 255) / 256, c0 = min(C, tid * per), c1 = min(C, c0 + per), lane = tid & 63, wave = tid >> 6;
-  __shared__ long long w_work[4];
-  __shared__ int32_t w_a[4], w_b[4];
-  __shared__ int32_t s_cut, s_ntiles, s_list[MAXC];
-  auto wave_prefix = [&](int v) __attribute__((always_inline)) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) { const int u = __shfl_up(v, o); if (lane >= o) v += u; }
-    return v;
-  };
-  {
-    // key tiles per chunk of a list that is cut: twice the average list of the head, at least 16
-    long long work = 0; int qtiles = 0;
-    for (int c = c0; c < c1; ++c) { work += (long long)s_nq[c] * s_T[c]; qtiles += s_nq[c]; }
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) { work += __shfl_xor(work, o); qtiles += __shfl_xor(qtiles, o); }
-    if (lane == 0) { w_work[wave] = work; w_a[wave] = qtiles; }
-  }
-  __syncthreads();
-  const long long work = w_work[0] + w_work[1] + w_work[2] + w_work[3];
-  const int qtiles = w_a[0] + w_a[1] + w_a[2] + w_a[3];
-  const int chunk = max(16, 2 * (qtiles > 0 ? (int)((work + qtiles - 1) / qtiles) : 0));
-  // which lists are cut: the long ones are listed in cluster order, and one thread deals the slots out while they last
-  int cuts = 0;
-  for (int c = c0; c < c1; ++c) { s_pieces[c] = 1; cuts += allow_split && s_T[c] > 2 * chunk; }
-  const int cin = wave_prefix(cuts);
-  if (lane == 63) w_b[wave] = cin;
-  __syncthreads();
-  {
-    int at = cin - cuts;
-    for (int w = 0; w < wave; ++w) at += w_b[w];
-    for (int c = c0; c < c1; ++c) if (allow_split && s_T[c] > 2 * chunk) s_list[at++] = c;
-    if (tid == 255) s_cut = at;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int used = 0, nm = 0;
-    for (int i = 0; i < s_cut; ++i) {
-      const int c = s_list[i], T = s_T[c];
-      int pieces = min(16, (T + chunk - 1) / chunk);
-      if (used + pieces * s_nq[c] > slots) pieces = max(1, (slots - used) / max(s_nq[c], 1));   // fewer, longer chunks
-      if (pieces > 1) {
-        const int per_piece = (T + pieces - 1) / pieces;
-        pieces = max(1, (T + per_piece - 1) / max(per_piece, 1));          // no empty chunk
-      }
-      s_pieces[c] = pieces; s_slot0[c] = used; s_merge0[c] = nm;
-      if (pieces > 1) { used += s_nq[c] * pieces; nm += s_nq[c]; }
-    }
-    nmerge[h] = nm;
-  }
-  __syncthreads();
-  {                                              // where every cluster's records start
-    int mine = 0;
-    for (int c = c0; c < c1; ++c) mine += s_nq[c] * s_pieces[c];
-    const int incl = wave_prefix(mine);
-    if (lane == 63) w_a[wave] = incl;
-    __syncthreads();
-    int nt = incl - mine;
-    for (int w = 0; w < wave; ++w) nt += w_a[w];
-    for (int c = c0; c < c1; ++c) { s_tile0[c] = nt; nt += s_nq[c] * s_pieces[c]; }
-    if (tid == 255) { ntiles[h] = nt; s_ntiles = nt; }
-  }
-  __syncthreads();
-  // The records, one a thread: the last cluster whose records start at or before it (an empty one shares its start with
-  // the next).  One thread per cluster wrote 625 records one after the other where 20 000 rows are a single cluster.
-  for (int t = tid; t < s_ntiles; t += 256) {
-    int c = 0, hi = C - 1;
-    while (c < hi) { const int mid = (c + hi + 1) >> 1; if (s_tile0[mid] <= t) c = mid; else hi = mid - 1; }
-    const int i = t - s_tile0[c], T = s_T[c], pieces = s_pieces[c], per_piece = (T + pieces - 1) / pieces;
-    const int group = i / pieces, k = i - group * pieces;                    // rows group * BM .. of the cluster, chunk k
-    const int r0 = qo[c] + group * BM, rows = min(BM, qo[c + 1] - r0);
-    int32_t* t6 = tl + (size_t)t * TILE_REC;
-    t6[0] = c; t6[1] = r0; t6[2] = rows;
-    t6[3] = pieces > 1 ? k * per_piece : 0; t6[4] = pieces > 1 ? min(T, (k + 1) * per_piece) : T;
-    t6[5] = pieces > 1 ? s_slot0[c] + i : -1; t6[6] = s_tot[c]; t6[7] = (group * BM) & 63;
-    if (pieces > 1 && k == 0) {
-      int32_t* m = ml + (size_t)(s_merge0[c] + group) * 4;
-      m[0] = r0; m[1] = rows; m[2] = s_slot0[c] + i; m[3] = pieces;
-    }
-  }
+  __shared__ int32_t sm[PLAN_ARRAYS * MAXC];
+  tiles_of_head<false>(sm, blockIdx.x, min(Cq, MAXC), maxr, maxtiles, BM, slots, allow_split, q_offs, q_offs_stride, nullptr, rng_pre, rng_cnt, tiles,
+                ntiles, merge, nmerge);
 }
 
 // dense: one query "cluster" over all rows, one key range [0,N)
@@ -1106,6 +1149,9 @@ __global__ __launch_bounds__(256) void attn_merge_f32(AttnArgs a, int splits) {
 // ------------------------------------------------------------------------------------------
 // One workgroup per cut query tile: O = sum_s 2^((m_s - m) scale) O_s / sum_s 2^((m_s - m) scale) l_s
 // with m = max_s m_s; a chunk always holds at least one key, so every m_s is finite and l_s > 0.
+// MERGE_GROUPS workgroups a head and row group: mostly there is little or nothing to merge, and one for every slot, 15 360 for
+// 30 heads, took 5 us to find that out.
+constexpr int MERGE_GROUPS = 16;
 template <int D>
 __global__ __launch_bounds__(256) void attn_merge(AttnArgs a, const int32_t* __restrict__ merge,
                                                   const int32_t* __restrict__ nmerge) {
@@ -1113,43 +1159,44 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a, const int32_t* __r
   // not one after the other: the kernel is a handful of dependent round trips either way, so what counts is
   // how many of its loads are in flight at once.
   constexpr int MAXP = 16;                       // most chunks a list is cut into (plan_tiles)
-  const int h = blockIdx.y, e = blockIdx.x;
-  if (e >= nmerge[h]) return;
-  const int32_t* ml = merge + ((size_t)h * a.slots + e) * 4;
-  const int row0 = ml[0], nrows = ml[1], slot0 = ml[2], pieces = min(ml[3], MAXP);
-  const int32_t* pq = a.perm_q ? a.perm_q + (size_t)h * a.N : nullptr;
-  bf16raw* Oh = (bf16raw*)a.O + (size_t)h * a.N * D;
-  constexpr int LPR = D / 4;                     // lanes per row, four columns each
-  const int col = (threadIdx.x % LPR) * 4;
-  for (int r = blockIdx.z * (256 / LPR) + threadIdx.x / LPR; r < nrows; r += gridDim.z * (256 / LPR)) {
-    float ms[MAXP], ls[MAXP];
-    float4 os[MAXP];
+  const int h = blockIdx.y, n = nmerge[h];
+  for (int e = blockIdx.x; e < n; e += gridDim.x) {
+    const int32_t* ml = merge + ((size_t)h * a.slots + e) * 4;
+    const int row0 = ml[0], nrows = ml[1], slot0 = ml[2], pieces = min(ml[3], MAXP);
+    const int32_t* pq = a.perm_q ? a.perm_q + (size_t)h * a.N : nullptr;
+    bf16raw* Oh = (bf16raw*)a.O + (size_t)h * a.N * D;
+    constexpr int LPR = D / 4;                     // lanes per row, four columns each
+    const int col = (threadIdx.x % LPR) * 4;
+    for (int r = blockIdx.z * (256 / LPR) + threadIdx.x / LPR; r < nrows; r += gridDim.z * (256 / LPR)) {
+      float ms[MAXP], ls[MAXP];
+      float4 os[MAXP];
 #pragma unroll
-    for (int s = 0; s < MAXP; ++s) {
-      const size_t so = ((size_t)h * a.slots + slot0 + min(s, pieces - 1)) * a.BM + r;
-      ms[s] = a.part_ml[so * 2];
-      ls[s] = a.part_ml[so * 2 + 1];
-      os[s] = *reinterpret_cast<const float4*>(a.part_o + so * D + col);
-    }
-    float m = -INFINITY;
-#pragma unroll
-    for (int s = 0; s < MAXP; ++s) if (s < pieces) m = fmaxf(m, ms[s]);
-    float l = 0.f;
-    float4 o = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < MAXP; ++s) {
-      if (s < pieces) {                          // in chunk order, as before: the sums are the same to the bit
-        const float w = __builtin_amdgcn_exp2f((ms[s] - m) * a.scale_log2e);
-        l = fmaf(w, ls[s], l);
-        o.x = fmaf(w, os[s].x, o.x); o.y = fmaf(w, os[s].y, o.y); o.z = fmaf(w, os[s].z, o.z); o.w = fmaf(w, os[s].w, o.w);
+      for (int s = 0; s < MAXP; ++s) {
+        const size_t so = ((size_t)h * a.slots + slot0 + min(s, pieces - 1)) * a.BM + r;
+        ms[s] = a.part_ml[so * 2];
+        ls[s] = a.part_ml[so * 2 + 1];
+        os[s] = *reinterpret_cast<const float4*>(a.part_o + so * D + col);
       }
+      float m = -INFINITY;
+#pragma unroll
+      for (int s = 0; s < MAXP; ++s) if (s < pieces) m = fmaxf(m, ms[s]);
+      float l = 0.f;
+      float4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < MAXP; ++s) {
+        if (s < pieces) {                          // in chunk order, as before: the sums are the same to the bit
+          const float w = __builtin_amdgcn_exp2f((ms[s] - m) * a.scale_log2e);
+          l = fmaf(w, ls[s], l);
+          o.x = fmaf(w, os[s].x, o.x); o.y = fmaf(w, os[s].y, o.y); o.z = fmaf(w, os[s].z, o.z); o.w = fmaf(w, os[s].w, o.w);
+        }
+      }
+      const float inv = l > 0.f ? 1.0f / l : 0.f;
+      const int tok = pq ? pq[row0 + r] : row0 + r;
+      uint2 out;
+      out.x = pack_bf16x2(o.x * inv, o.y * inv);
+      out.y = pack_bf16x2(o.z * inv, o.w * inv);
+      *reinterpret_cast<uint2*>(Oh + (size_t)tok * D + col) = out;
     }
-    const float inv = l > 0.f ? 1.0f / l : 0.f;
-    const int tok = pq ? pq[row0 + r] : row0 + r;
-    uint2 out;
-    out.x = pack_bf16x2(o.x * inv, o.y * inv);
-    out.y = pack_bf16x2(o.z * inv, o.w * inv);
-    *reinterpret_cast<uint2*>(Oh + (size_t)tok * D + col) = out;
   }
 }
 
@@ -1229,11 +1276,17 @@ int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int max
                        const int32_t* k_count, const int32_t* sel_idx, const int32_t* sel_cnt,
                        int32_t* rng_start, int32_t* rng_pre, int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles,
                        int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride,
-                       const int32_t* perm_k, int N) {
-  plan_sparse<<<dim3(Cq, H), 256, 0, s>>>(Cq, cap, maxr, row_scale, k_offs, k_offs_stride, k_count, sel_idx, sel_cnt,
-                                         rng_start, rng_pre, rng_cnt, krow, kstride, perm_k, N);
-  plan_tiles<<<H, 256, 0, s>>>(Cq, maxr, maxtiles, BM, SPLIT_SLOTS, dtype == ADACLUSTER_BF16 ? 1 : 0, q_offs,
-                              q_offs_stride, rng_pre, rng_cnt, tiles, ntiles, merge, nmerge);
+                       const int32_t* perm_k, int N, const int32_t* lengths) {
+  const int split = dtype == ADACLUSTER_BF16 ? 1 : 0;
+  const TilePlan tp{lengths, q_offs, q_offs_stride, maxtiles, BM, SPLIT_SLOTS, split, tiles, ntiles, merge, nmerge};
+  if (lengths && Cq <= PLAN_BESIDE) {
+    plan_sparse<true><<<dim3(Cq + 1, H), 256, PLAN_ARRAYS * 4 * Cq, s>>>(Cq, cap, maxr, row_scale, k_offs, k_offs_stride, k_count, sel_idx, sel_cnt, rng_start,
+                                                                         rng_pre, rng_cnt, krow, kstride, perm_k, N, tp);
+  } else {
+    plan_sparse<false><<<dim3(Cq, H), 256, 0, s>>>(Cq, cap, maxr, row_scale, k_offs, k_offs_stride, k_count, sel_idx, sel_cnt, rng_start, rng_pre, rng_cnt,
+                                                   krow, kstride, perm_k, N, tp);
+    plan_tiles<<<H, 256, 0, s>>>(Cq, maxr, maxtiles, BM, SPLIT_SLOTS, split, q_offs, q_offs_stride, rng_pre, rng_cnt, tiles, ntiles, merge, nmerge);
+  }
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
 }
 
@@ -1263,8 +1316,8 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
       else attn_mfma<128, A128_NW, A128_NBUF, A128_MINB, A128_VPRE><<<g, A128_NW * 64, 0, s>>>(a);
     }
     if (merge) {      // the chunks of cut key lists (none for the dense branch)
-      if (d == 64) attn_merge<64><<<dim3(SPLIT_SLOTS, H, 4), 256, 0, s>>>(a, merge, nmerge);
-      else attn_merge<128><<<dim3(SPLIT_SLOTS, H, 4), 256, 0, s>>>(a, merge, nmerge);
+      if (d == 64) attn_merge<64><<<dim3(MERGE_GROUPS, H, 4), 256, 0, s>>>(a, merge, nmerge);
+      else attn_merge<128><<<dim3(MERGE_GROUPS, H, 4), 256, 0, s>>>(a, merge, nmerge);
     }
   } else {
     const int splits = a.splits;

@@ -116,7 +116,8 @@ int launch_fill_i32(hipStream_t s, int32_t* p, size_t n, int32_t v);
 int launch_select(hipStream_t s, int H, int Cq, int cap, int d, int score_mode, int select_mode, int topk,
                   float top_p, float scale, const float* q_cent, const float* q_mean_norm, const float* k_cent,
                   const float* k_bmin, const float* k_bmax, const int32_t* k_sizes, const int32_t* k_count,
-                  const int32_t* full_flag, int32_t* sel_idx, int32_t* sel_cnt, int kc_max, double* scores);   // scores: scratch [H][Cq][cap]
+                  const int32_t* full_flag, int32_t* sel_idx, int32_t* sel_cnt, int kc_max, double* scores,   // scores: scratch [H][Cq][cap]
+                  int32_t* sel_keys /* [H][Cq] keys of the selected clusters, or NULL */);
 
 int attn_block_rows(int dtype, int d, int N, int Cq);   // queries per workgroup of the attention launch
 int attn_block_rows_min(int dtype);
@@ -132,7 +133,8 @@ int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int max
                        const int32_t* q_offs, int q_offs_stride, const int32_t* k_offs, int k_offs_stride,
                        const int32_t* k_count, const int32_t* sel_idx, const int32_t* sel_cnt,
                        int32_t* rng_start, int32_t* rng_pre, int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles,
-                       int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride, const int32_t* perm_k, int N);
+                       int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride, const int32_t* perm_k, int N,
+                       const int32_t* lengths /* [H][Cq] keys of every list, or NULL: not known beforehand */);
 int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, int BM, int32_t* rng_start, int32_t* rng_pre,
                       int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles, int row_scale, int32_t* krow, size_t kstride);
 // entries per (head, query cluster) of the table of key rows (times row_scale) that the attention kernels load by

@@ -144,7 +144,8 @@ __global__ __launch_bounds__(256) void select_kernel(SelectCfg cfg, const double
                                                      const int32_t* __restrict__ k_sizes,
                                                      const int32_t* __restrict__ k_count,
                                                      const int32_t* __restrict__ full_flag,
-                                                     int32_t* __restrict__ sel_idx, int32_t* __restrict__ sel_cnt) {
+                                                     int32_t* __restrict__ sel_idx, int32_t* __restrict__ sel_cnt,
+                                                     int32_t* __restrict__ sel_keys) {
 #pragma clang fp contract(off)
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   double* sval = reinterpret_cast<double*>(smem);                        // [cap] score, then weight
@@ -323,7 +324,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelectCfg cfg, const double
 
   // ---- ascending compaction of the selected indices
   int32_t* out = sel_idx + ((size_t)h * cfg.Cq + i) * cfg.cap;
-  int run = 0, run_eq = 0;
+  int run = 0, run_eq = 0, keys = 0;
   const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   for (int j0 = 0; j0 < kc; j0 += 256) {
     const int j = j0 + tid;
@@ -349,16 +350,26 @@ __global__ __launch_bounds__(256) void select_kernel(SelectCfg cfg, const double
     __syncthreads();
     int before = 0;
     for (int w = 0; w < wave; ++w) before += wsum[w];
-    if (f) out[run + before + __popcll(bal & lt_mask)] = j;
+    if (f) {
+      out[run + before + __popcll(bal & lt_mask)] = j;
+      if (sel_keys) keys += k_sizes[(size_t)h * cfg.cap + j];
+    }
     run += wsum[0] + wsum[1] + wsum[2] + wsum[3];
   }
   if (tid == 0) sel_cnt[(size_t)h * cfg.Cq + i] = run;
+  if (!sel_keys) return;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) keys += __shfl_xor(keys, o);
+  __syncthreads();
+  if (lane == 0) wsum2[wave] = keys;
+  __syncthreads();
+  if (tid == 0) sel_keys[(size_t)h * cfg.Cq + i] = wsum2[0] + wsum2[1] + wsum2[2] + wsum2[3];
 }
 
 int launch_select(hipStream_t s, int H, int Cq, int cap, int d, int score_mode, int select_mode, int topk,
                   float top_p, float scale, const float* q_cent, const float* q_mean_norm, const float* k_cent,
                   const float* k_bmin, const float* k_bmax, const int32_t* k_sizes, const int32_t* k_count,
-                  const int32_t* full_flag, int32_t* sel_idx, int32_t* sel_cnt, int kc_max, double* scores) {
+                  const int32_t* full_flag, int32_t* sel_idx, int32_t* sel_cnt, int kc_max, double* scores, int32_t* sel_keys) {
   // kc_max: an upper bound of k_count[h] known to the host; it sizes the LDS arrays (and with
   // them the number of workgroups a CU can hold)
   const int lds_cap = kc_max < cap ? (kc_max + 63) / 64 * 64 : cap;
@@ -396,7 +407,7 @@ int launch_select(hipStream_t s, int H, int Cq, int cap, int d, int score_mode, 
   else if (waves * ((Cq + 12) / 13) >= 2048) group(std::integral_constant<int, 13>{});
   else if (score_mode == ADACLUSTER_SCORE_BOX) group(std::integral_constant<int, 5>{});
   else group(std::integral_constant<int, 4>{});
-  select_kernel<<<dim3(Cq, H), 256, shm, s>>>(c, scores, q_mean_norm, k_sizes, k_count, full_flag, sel_idx, sel_cnt);
+  select_kernel<<<dim3(Cq, H), 256, shm, s>>>(c, scores, q_mean_norm, k_sizes, k_count, full_flag, sel_idx, sel_cnt, sel_keys);
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
 }
 

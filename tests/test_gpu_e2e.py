@@ -117,6 +117,28 @@ def test_stagewise_calls_equal_the_fused_call():
     assert torch.equal(O_fused, O_steps)
 
 
+@pytest.mark.parametrize("Cq,dtype", [(1, B.BF16), (2, B.F32), (256, B.BF16), (257, B.BF16), (257, B.F32)])
+def test_query_tiles_planned_beside_the_key_lists(Cq, dtype):
+    """The fused call plans the query tiles from the selection's list lengths, in the launch that writes the lists, up to 256
+    query clusters; the attention step alone plans them afterwards, from the lists: the same tiles, the same bits.  Top-p on
+    points of few modes leaves lists of very different length, some of them cut."""
+    H, N, d = 2, 5000, 64
+    Q, K, V = wl.make_small(33, N, d, 12, dtype="bf16" if dtype == B.BF16 else "f32", H=H)
+    p = B.Params(H=H, N=N, d=d, dtype=dtype, q_clusters=Cq, k_m0=16, k_m_min=4, k_max_clusters=64,
+                 select_mode=B.SELECT_TOPP, top_p=0.7, min_unassigned_frac=0.03)
+    Qd, Kd, Vd = to_dev(Q, dtype), to_dev(K, dtype), to_dev(V, dtype)
+    o = B.alloc_outputs(p, Qd.device)
+    got = B.adacluster_attn(p, Qd, Kd, Vd, outs=o)
+    alone = B.adacluster_sparse_attn(p, Qd, Kd, Vd, o["q_labels"], o["k_labels"], o["k_count"], o["sel_idx"], o["sel_cnt"])
+    torch.cuda.synchronize()
+    assert torch.equal(got, alone)
+    for h in range(H):
+        sel = [to_np(o["sel_idx"][h, i, :int(o["sel_cnt"][h, i])]) for i in range(Cq)]
+        ref = orc.sparse_attention_gather(Q[h], K[h], V[h], to_np(o["q_labels"][h]), to_np(o["k_labels"][h]), sel)
+        rel, mx = attn_errors(to_np(got)[h], ref)
+        assert (mx < 1e-4) if dtype == B.F32 else (rel < 1e-2 and mx < 2e-2), (rel, mx)
+
+
 def test_fused_warm_start_call_chained():
     """A second call with q_init_mode = k_init_mode = 1 reuses the first call's centres."""
     H, N, d = 2, 2400, 64
