@@ -109,3 +109,32 @@ def test_key_clustering_around_the_change_of_the_sort(dtype, d, N, m0):
     out = B.adacluster_kcluster(p, to_dev(K, dtype), want_box=True)
     torch.cuda.synchronize()
     check_kcluster(K, p, out, dtype)
+
+
+@pytest.mark.parametrize("H,N,cap", [(2, 9000, 100), (60, 9000, 63), (2, 24000, 1791), (2, 24000, 1792), (2, 4097, 2047), (2, 4097, 2048),
+                                     (2, 10240, 4095), (2, 10240, 4096), (2, 81920, 64), (2, 81921, 64)])
+def test_sort_with_the_prefix_in_the_scatter_and_in_a_launch(H, N, cap):
+    """Sixteen, eight and four waves a segment, the prefix over the segments in the scatter or in a launch before it, on either
+    side of every line between them; sampled rows of the first and the last head."""
+    d, Cq = 64, 3
+    rng = np.random.default_rng(N + cap)
+    m0 = min(cap // 2, 16)
+    p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=Cq, k_m0=m0, k_m_min=1, k_max_clusters=cap - m0)
+    Q, K, V = (torch.from_numpy(rng.standard_normal((H, N, d), dtype=np.float32)).cuda().to(torch.bfloat16) for _ in range(3))
+    kl = np.minimum((cap * rng.random((H, N)) ** 2).astype(np.int32), cap - 1)
+    kl[:, rng.integers(0, N, 9)] = cap + 1
+    ql = rng.integers(0, Cq, (H, N)).astype(np.int32)
+    pick = rng.random((H, Cq, cap)) < 0.2
+    pick[:, :, 0] = True
+    cnt = pick.sum(2).astype(np.int32)
+    sel = np.argsort(~pick, axis=2, kind="stable").astype(np.int32)
+    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    O = B.adacluster_sparse_attn(p, Q, K, V, dev(ql), dev(kl), torch.full((H,), cap, dtype=torch.int32, device="cuda"),
+                                 dev(sel), dev(cnt)).float()
+    for h in (0, H - 1):
+        r = np.append(rng.integers(0, N, 62), [0, N - 1])
+        allowed = np.concatenate([pick[h], np.zeros((Cq, 2), dtype=bool)], axis=1)[ql[h][r]][:, kl[h]]
+        S = (Q[h][dev(r)].float() @ K[h].float().T) / d ** 0.5
+        ref = torch.softmax(S.masked_fill(~dev(allowed), float("-inf")), 1) @ V[h].float()
+        rel = float((O[h][dev(r)] - ref).norm() / ref.norm())
+        assert rel < 1e-2, rel
