@@ -153,7 +153,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelectCfg cfg, const double
   int32_t* sflag = reinterpret_cast<int32_t*>(smem + (size_t)cfg.lds_cap * 16);   // [lds_cap]
   __shared__ int32_t wsum[4], wsum2[4];
   __shared__ int32_t s_take, s_digit, s_krem, s_all;
-  __shared__ int32_t hist[256];
+  __shared__ int32_t hist[256], dup[256];
   __shared__ double s_max;
   __shared__ double swmax[4];
 
@@ -252,69 +252,100 @@ __global__ __launch_bounds__(256) void select_kernel(SelectCfg cfg, const double
       sflag[j] = valid;
     }
     __syncthreads();
-    // rank of every valid cluster, stored in place of the flag: sflag = rank+1, 0 = invalid
-    // (a thread ranks its clusters two at a time, so that a key read serves both)
+    // Rank of every valid cluster, stored in place of the flag: sflag = rank+1, 0 = invalid.  The upper halves of the keys
+    // decide it but for the clusters that share one: those have the same rank, which two bits a rank show (met once, met
+    // again), and only they compare whole keys, and indices.  Weights of zero, many where the scores are far apart, keep one
+    // rank for all: they come last and add nothing, so that all are taken or none.  A thread ranks its clusters two at a
+    // time, so that a key read serves both.
+    // Bound by the pairs: two instructions each, six, four of them on 64 bits, with whole keys throughout; by the two sums
+    // below it where the clusters are few.  12 heads x 65 lists of 365 clusters: this kernel 38 -> 30 us; the selection of
+    // 30 x 65 lists, 600 clusters 310 -> 182 us, 2 000 clusters 1 546 -> 789, 24 x 65 of 1 171 1 597 -> 726.
+    hist[tid] = 0; dup[tid] = 0;                 // 8 192 bits each; the library holds 7 168 clusters
+    __syncthreads();
     for (int j = tid; j < kc; j += 512) {
       const int j2 = j + 256;
-      const bool v1 = sflag[j] != 0, v2 = j2 < kc && sflag[j2] != 0;
-      const uint64_t k1 = skey[j], k2 = j2 < kc ? skey[j2] : 0ull;
+      const uint32_t k1 = (uint32_t)(skey[j] >> 32);
       int r1 = 0, r2 = 0;
-      for (int t = 0; t < kc; ++t) {
-        const uint64_t kt = skey[t];
-        r1 += (kt > k1) || (kt == k1 && t < j);
-        r2 += (kt > k2) || (kt == k2 && t < j2);
+      auto met = [&](int at, int r) __attribute__((always_inline)) {
+        if (!sflag[at]) return;
+        const int bit = 1 << (r & 31);
+        if (sval[at] != 0.0 && (atomicOr(&hist[r >> 5], bit) & bit)) atomicOr(&dup[r >> 5], bit);
+        sflag[at] = r + 1;
+      };
+      if (j2 - lane < kc) {
+        const uint32_t k2 = j2 < kc ? (uint32_t)(skey[j2] >> 32) : 0u;
+#pragma unroll 8
+        for (int t = 0; t < kc; ++t) { const uint32_t kt = (uint32_t)(skey[t] >> 32); r1 += kt > k1; r2 += kt > k2; }
+        if (j2 < kc) met(j2, r2);
+      } else {
+#pragma unroll 8
+        for (int t = 0; t < kc; ++t) r1 += (uint32_t)(skey[t] >> 32) > k1;
       }
-      if (v1) sflag[j] = r1 + 1;
-      if (v2) sflag[j2] = r2 + 1;
+      met(j, r1);
     }
     __syncthreads();
-    // The weights in rank order go into skey (dead once the ranks are known), then one thread takes
-    // the two sums, each a chain of rounded adds in a fixed order: the total in ascending index, the
-    // running sum in rank order.  It reads eight values at a time, so that the LDS reads of a batch
-    // are in flight together and only the adds wait for one another.
-    double* sw = reinterpret_cast<double*>(skey);
-    int nv_local = 0;
-    for (int j = tid; j < kc; j += 256) nv_local += sflag[j] != 0;
+    for (int j0 = wave * 64; j0 < kc; j0 += 256) {
+      const int j = j0 + lane, r = j < kc ? sflag[j] - 1 : -1;
+      const bool tie = r >= 0 && sval[j] != 0.0 && ((dup[r >> 5] >> (r & 31)) & 1);
+      uint64_t left = __ballot(tie);
+      if (__popcll(left) <= 8) {                 // a few: the wave's lanes read the keys for one cluster after the other
+        for (; left; left &= left - 1) {
+          const int jt = j0 + __builtin_ctzll(left);
+          const uint64_t k1 = skey[jt];
+          int exact = 0;
+          for (int t = lane; t < kc; t += 64) { const uint64_t kt = skey[t]; exact += (kt > k1) || (kt == k1 && t < jt); }
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) nv_local += __shfl_xor(nv_local, o);
-    if (lane == 0) wsum[wave] = nv_local;
-    __syncthreads();                // every thread has read its keys: skey may be overwritten
-    for (int j = tid; j < kc; j += 256) if (sflag[j]) sw[sflag[j] - 1] = sval[j];
-    __syncthreads();
-    if (tid == 0) {
-      const int nvalid = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-      double total = 0.0;
-      int j = 0;
-      for (; j + 8 <= kc; j += 8) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = sval[j + u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) total = total + v[u];
-      }
-      for (; j < kc; ++j) total = total + sval[j];
-      const double target = cfg.top_p * total;
-      double cum = 0.0;
-      int take = nvalid;
-      bool found = false;
-      int r = 0;
-      for (; r + 8 <= nvalid && !found; r += 8) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = sw[r + u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          if (!found) {
-            cum = cum + v[u];
-            if (cum >= target) { take = r + u + 1; found = true; }
-          }
+          for (int o = 1; o < 64; o <<= 1) exact += __shfl_xor(exact, o);
+          if (j == jt) sflag[j] = exact + 1;
         }
+      } else if (tie) {
+        const uint64_t k1 = skey[j];
+        int exact = 0;
+#pragma unroll 8
+        for (int t = 0; t < kc; ++t) { const uint64_t kt = skey[t]; exact += (kt > k1) || (kt == k1 && t < j); }
+        sflag[j] = exact + 1;
       }
-      for (; r < nvalid && !found; ++r) {
-        cum = cum + sw[r];
-        if (cum >= target) { take = r + 1; found = true; }
+    }
+    __syncthreads();
+    // The weights in rank order go into skey (dead once the ranks are known), then one thread each takes the two sums, chains
+    // of rounded adds in a fixed order: the total in ascending index, the running sum in rank order, left in place.  Eight
+    // values at a time, the next eight asked for before they are added: only the adds wait for one another.
+    double* sw = reinterpret_cast<double*>(skey);
+    int nv_local = 0, nz_local = 0;              // clusters, and those with a weight
+    for (int j = tid; j < kc; j += 256) { nv_local += sflag[j] != 0; nz_local += sflag[j] != 0 && sval[j] != 0.0; }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) { nv_local += __shfl_xor(nv_local, o); nz_local += __shfl_xor(nz_local, o); }
+    if (lane == 0) { wsum[wave] = nv_local; wsum2[wave] = nz_local; }
+    __syncthreads();
+    const int nvalid = wsum[0] + wsum[1] + wsum[2] + wsum[3], nz = wsum2[0] + wsum2[1] + wsum2[2] + wsum2[3];
+    for (int j = tid; j < kc; j += 256) if (sflag[j] && sval[j] != 0.0) sw[sflag[j] - 1] = sval[j];
+    __syncthreads();
+    auto chain = [&](double* x, int n, auto keep) __attribute__((always_inline)) {
+      double sum = 0.0, v[8];
+      const int whole = n / 8 * 8;
+      if (whole > 0) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = x[u];
       }
-      s_take = take;
+      for (int j = 0; j < whole; j += 8) {
+        double next[8];
+        const int ahead = min(j + 8, whole - 8);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) next[u] = x[ahead + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { sum = sum + v[u]; if (decltype(keep)::value) x[j + u] = sum; }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = next[u];
+      }
+      for (int j = whole; j < n; ++j) { sum = sum + x[j]; if (decltype(keep)::value) x[j] = sum; }
+      return sum;
+    };
+    if (tid == 0) { s_max = cfg.top_p * chain(sval, kc, std::false_type{}); s_take = nvalid; }      // (the maximum has been read)
+    if (tid == 64) chain(sw, nz, std::true_type{});
+    __syncthreads();
+    for (int r0 = wave * 64; r0 < nz; r0 += 256) {
+      const uint64_t there = __ballot(r0 + lane < nz && sw[r0 + lane] >= s_max);
+      if (there) { if (lane == 0) atomicMin(&s_take, r0 + __builtin_ctzll(there) + 1); break; }
     }
     __syncthreads();
     const int take = s_take;

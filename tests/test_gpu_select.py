@@ -122,3 +122,34 @@ def test_scores_by_every_group_size(H, Cq, cap, kc, d, score_mode):
         ref = orc.select_topk(S, topk)
         for i in range(Cq):
             assert np.array_equal(got[h][i], ref[i]), (h, i)
+
+
+@pytest.mark.parametrize("top_p", [0.05, 0.5, 0.93])
+@pytest.mark.parametrize("kcs", [(1, 9, 255), (256, 257, 513), (700, 1300, 3)])
+def test_topp_ranks_of_equal_and_nearly_equal_weights(kcs, top_p):
+    """The order of the weights is decided by the upper halves of their keys, and by the whole keys and the index where those
+    are shared: equal centroids, centroids a billionth apart (some 2^-30 of a weight: the upper half holds 2^-20), weights of
+    zero.  Every set as the oracle's."""
+    H, Cq, d, cap = 3, 5, 64, 1300
+    rng = np.random.default_rng(sum(kcs))
+    qc, mean_norm, kcent, _, _, sizes, kcount = make_inputs(19, H, Cq, cap, list(kcs), d)
+    for h in range(H):
+        kc = kcs[h]
+        sizes[h, :kc] = np.where(rng.random(kc) < 0.1, 0, 7)
+        sizes[h, 0] = 7
+        same = rng.integers(0, max(1, kc // 6), kc)                        # groups of about six
+        kcent[h, :kc] = kcent[h, same]
+        kcent[h, :kc, 0] = 1e-9 * rng.integers(0, 3, kc)                   # of three members nearly equal, the rest equal
+    mean_norm[:, 3] = 3000.0                                               # all but the nearest few underflow
+    mean_norm[:, 4] = 0.0                                                  # every weight the same
+    p = B.Params(H=H, N=10000, d=d, q_clusters=Cq, k_m0=40, k_m_min=4, k_max_clusters=cap - 40, select_mode=B.SELECT_TOPP, top_p=top_p)
+    c = lambda a: torch.from_numpy(a).cuda()
+    got = sel_from_dev(*B.adacluster_select(p, c(qc), c(mean_norm), c(kcent), None, None, c(sizes), c(kcount),
+                                            torch.zeros(H, dtype=torch.int32, device="cuda")))
+    scale = float(np.float32(1.0 / np.sqrt(np.float32(d))))
+    for h in range(H):
+        kc = kcs[h]
+        S = orc.cluster_scores(p.score_mode, qc[h].astype(np.float64), kcent[h, :kc].astype(np.float64), None, None, sizes[h, :kc])
+        ref = orc.select_topp(S, sizes[h, :kc], mean_norm[h].astype(np.float64) * scale, top_p)
+        for i in range(Cq):
+            assert np.array_equal(got[h][i], ref[i]), (h, i, got[h][i], ref[i])
