@@ -83,7 +83,7 @@ __global__ __launch_bounds__(NW * 64) void quest_mfma(int Lq, int Lk, int clamp,
   // rows of span + 8 floats: a store of the accumulator layout touches two rows 4 apart, and 4 rows are 32 banks away
   constexpr int SPAN = NW * 32, STRIDE = SPAN + 8;
   __shared__ __attribute__((aligned(16))) char qs[3 * QB];
-  __shared__ float ts[32 * STRIDE];
+  __shared__ __attribute__((aligned(16))) float ts[32 * STRIDE];
   const int h = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 31, hb = lane >> 5;
   // More pages than the span: a workgroup row of the grid computes `SPAN` pages, of which a score row writes those of
@@ -124,8 +124,14 @@ __global__ __launch_bounds__(NW * 64) void quest_mfma(int Lq, int Lk, int clamp,
   for (int ks = 0; ks < KS; ++ks) qaddr[ks] = c * ROWB + (((ks * 2 + hb) ^ swz(c)) * 16);
   wait_vmcnt<0>();
   lds_barrier();
-  const int scores = 32 * Lk;                             // of a block of whole rows (single)
-  const int stores = single ? scores / NT : 0;            // store instructions a wave issues per whole block, at least
+  // Scores wait in LDS so that a 16-byte piece of LDS is an aligned one of S.  One span: the rows follow one another as they
+  // do in S, `mis` floats behind the start (a block is a multiple of 128 bytes: the same for every block of a head).  More:
+  // row r is moved by (mis + r * Lk) % 4 floats.A float a lane was four
+  // times the store instructions and a division of the position: 2 x 75 600 rows, 450 pages, d=64 58 -> 53 us (5.1 TB/s),
+  // 3 x 50 001 x 333 48 -> 39, 4 x 17 776 x 200, d=128 23.5 -> 21.0, 1 x 180 000 x 60 16.6 -> 14.6; more spans: 24 x 9 000 x
+  // 700, d=128 187 -> 171, 2 x 75 600 x 993 180 -> 169, 1 x 100 000 x 513, its second span one page, 62.4 -> 63.2.
+  const int mis = (int)((uintptr_t)(S + (size_t)h * Lq * Lk) >> 2) & 3;
+  const int stores = single ? 8 * Lk / NT : 0;            // store instructions a wave issues per whole block, at least
   int slot = 0;
   for (int b = b0; b < b1; ++b) {
     if (loads) issue(slot >= 1 ? slot - 1 : 2, b + 2);    // the slot of block b - 1, which every wave has read
@@ -142,29 +148,42 @@ __global__ __launch_bounds__(NW * 64) void quest_mfma(int Lq, int Lk, int clamp,
     }
     lds_barrier();                                        // the scores of block b - 1 have left LDS
     // value v of the tile is query 8*(v/4) + 4*hb + v%4 of the block, page slot wave*32 + c
-    float* tw = ts + 4 * hb * STRIDE + wave * 32 + c;
+    if (!single) {
+      float* tw = ts + 4 * hb * STRIDE + wave * 32 + c;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) tw[(8 * (v >> 2) + (v & 3)) * STRIDE] = acc[v];
+      for (int v = 0; v < 16; ++v) tw[(8 * (v >> 2) + (v & 3)) * STRIDE + ((mis + (v & 3) * Lk) & 3)] = acc[v];
+    } else if (wave * 32 + c < Lk) {
+      float* tw = ts + mis + 4 * hb * Lk + wave * 32 + c;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) tw[(8 * (v >> 2) + (v & 3)) * Lk] = acc[v];
+    }
     // the rows of block b + 1 have landed: younger than their request are the stores of block b - 1 and the request above
-    if (loads) { if (stores >= 12) wait_vmcnt<12 + LOADS>(); else if (stores >= 6) wait_vmcnt<6 + LOADS>(); else wait_vmcnt<LOADS>(); }
+    if (loads) { if (stores >= 3) wait_vmcnt<3 + LOADS>(); else if (stores == 2) wait_vmcnt<2 + LOADS>(); else wait_vmcnt<LOADS>(); }
     lds_barrier();
     float* Sb = S + ((size_t)h * Lq + (size_t)b * 32) * Lk;
     const int nrows = min(32, Lq - b * 32);
-    if (single) {                 // whole rows: one run over all of them
-      const int dr = NT / Lk, dc = NT % Lk, n = nrows * Lk;
-      int r = tid / Lk, k = tid % Lk;
-      for (int e = tid; e < n; e += NT) {
-        Sb[e] = ts[r * STRIDE + k];
-        r += dr; k += dc;
-        if (k >= Lk) { k -= Lk; ++r; }
+    // floats [from, to) of a run that starts at `at` in LDS and in S, first .. first + 3 this lane's of the first step
+    auto leave = [&](const float* at, float* out, int from, int to, int first, int step) __attribute__((always_inline)) {
+      for (int e = first; e < to; e += step) {
+        const float4 v = *reinterpret_cast<const float4*>(at + e);
+        if (e >= from && e + 4 <= to) {
+          *reinterpret_cast<float4*>(out + e) = v;
+        } else {
+          const float x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) if (e + i >= from && e + i < to) out[e + i] = x[i];
+        }
       }
+    };
+    if (single) {                 // whole rows: one run over all of them
+      leave(ts, Sb - mis, mis, mis + nrows * Lk, 4 * tid, 4 * NT);
     } else {
       for (int r = wave; r < nrows; r += NW) {
         float* row = Sb + (size_t)r * Lk;
         // first page at or after p that starts a line of S
         auto line = [&](int p) __attribute__((always_inline)) { return p + (int)((0u - (uint32_t)((uintptr_t)(row + p) >> 2)) & 31u); };
-        const int from = k0 == 0 ? 0 : line(k0), to = last ? Lk : line(k0 + SPAN - 32);
-        for (int k = from + lane; k < to; k += 64) row[k] = ts[r * STRIDE + k - k0];
+        const int from = k0 == 0 ? 0 : line(k0), to = last ? Lk : line(k0 + SPAN - 32), mr = (mis + r * Lk) & 3;
+        leave(ts + r * STRIDE, row + k0 - mr, from - k0 + mr, to - k0 + mr, ((from - k0 + mr) & ~3) + 4 * lane, 256);
       }
     }
     slot = slot == 2 ? 0 : slot + 1;

@@ -57,6 +57,25 @@ def test_matrix_core_form_at_the_edges_of_its_spans(Lq, Lk, d):
         assert np.all(np.abs(S[h] - ref) <= 1e-5 * mag + 1e-6)
 
 
+@pytest.mark.parametrize("Lq,Lk,d,shift", [(1, 1, 64, 1), (33, 3, 64, 2), (67, 31, 128, 3), (97, 127, 64, 1), (65, 255, 128, 2),
+                                           (2085, 450, 64, 3), (96, 511, 64, 0), (35, 512, 128, 1),
+                                           (67, 515, 64, 2), (34, 1001, 128, 3)])
+def test_matrix_core_form_writes_rows_at_any_alignment(Lq, Lk, d, shift):
+    """Scores leave in aligned 16-byte pieces, whatever float of such a piece a head or a row starts at; nothing else is
+    written.  Same bound as above."""
+    H = 3
+    Q, _, lo, hi = inputs(13, H, Lq, Lk, d, True)
+    buf = torch.full((H * Lq * Lk + 8,), float("nan"), device="cuda")
+    S = buf[4 + shift:][:H * Lq * Lk].view(H, Lq, Lk)
+    B.adacluster_quest_scores(dev(Q, True), dev(hi, True), dev(lo, True), B.QUEST_MFMA, out=S)
+    assert torch.isnan(buf[:4 + shift]).all() and torch.isnan(buf[4 + shift + H * Lq * Lk:]).all()
+    S = S.cpu().numpy()
+    for h in range(H):
+        ref = orc.score_box(Q[h].astype(np.float64), lo[h].astype(np.float64), hi[h].astype(np.float64))
+        mag = np.abs(Q[h].astype(np.float64)) @ np.maximum(np.abs(lo[h]), np.abs(hi[h])).astype(np.float64).T
+        assert np.all(np.abs(S[h] - ref) <= 1e-5 * mag + 1e-6)
+
+
 @pytest.mark.parametrize("form", [B.QUEST_ALU, B.QUEST_MFMA])
 def test_clamped_centroids_are_algorithm_2(form):
     """One vector per page: R+ = max(c, 0), R- = min(c, 0), taken on the fly from the centroid tensor."""
