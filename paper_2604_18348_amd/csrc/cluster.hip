@@ -2393,7 +2393,10 @@ int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, in
 // the more heads share the launches, and no more from about 64 heads on (72 at d=128): calls of nine stages, 200 heads
 // of 3 500 and 8 000 points, d=64, 763 and 1 385 us, in six launches a stage 1 576 and 3 450.  But the points are the bound
 // of the stage before, U shrinks, and what follows is in the one launch too: below 3 072 it is taken always (5 heads
-// of 9 247 tokens, d=128: the call 612 us, with the line at 1 100 636).
+// of 9 247 tokens, d=128: the call 612 us, with the line at 1 100 636).  With the centres formed in the next pass, four
+// launches a stage, it stays there: lines at 2 048, 1 400, 900 and 500 points for any number of heads, that call 527 -> 559,
+// 559, 561, 579 us; 3 x 2 587 tokens, d=64, 316 -> 329, 329, 329, 409; 28 x 3 669 470 -> 468, 469, 491, 571; 30 x 17 776,
+// 12 x 32 760 and 7 x 56 160 within 1 %.
 int small_stage_points(int d, int heads) {
   const int one = d == 64 ? 2048 : 1024, all = d == 64 ? 64 : 72;
   return heads >= all ? SMALL_NU : min(SMALL_NU, max(3072, one * all / (all - heads)));

@@ -126,8 +126,8 @@ __global__ __launch_bounds__(NW * 64) void quest_mfma(int Lq, int Lk, int clamp,
   lds_barrier();
   // Scores wait in LDS so that a 16-byte piece of LDS is an aligned one of S.  One span: the rows follow one another as they
   // do in S, `mis` floats behind the start (a block is a multiple of 128 bytes: the same for every block of a head).  More:
-  // row r is moved by (mis + r * Lk) % 4 floats.A float a lane was four
-  // times the store instructions and a division of the position: 2 x 75 600 rows, 450 pages, d=64 58 -> 53 us (5.1 TB/s),
+  // row r is moved by (mis + r * Lk) % 4 floats.  A float a lane was four
+  // times the store instructions and a walk over rows and pages: 2 x 75 600 rows, 450 pages, d=64 58 -> 53 us (5.1 TB/s),
   // 3 x 50 001 x 333 48 -> 39, 4 x 17 776 x 200, d=128 23.5 -> 21.0, 1 x 180 000 x 60 16.6 -> 14.6; more spans: 24 x 9 000 x
   // 700, d=128 187 -> 171, 2 x 75 600 x 993 180 -> 169, 1 x 100 000 x 513, its second span one page, 62.4 -> 63.2.
   const int mis = (int)((uintptr_t)(S + (size_t)h * Lq * Lk) >> 2) & 3;
