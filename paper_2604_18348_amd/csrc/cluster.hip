@@ -30,6 +30,7 @@ struct AssignCfg {
                                                           // stage's last pass): keep_cnt[h * keep_stride + workgroup]
   double* dist_sum;                                       // sum of the distances of this workgroup's points (the first stage's last
                                                           // pass, for tau): dist_sum[h * gridDim.x + workgroup]
+                                                          // (assign_rows: of this wave's points, for both)
 };
 constexpr int PASS_POINTS = 256;        // points of a workgroup of stage_pass (twice that where it combines)
 constexpr int ASSIGN_POINTS_LP = 256, ASSIGN_POINTS_F32 = 64;     // points of an assignment workgroup
@@ -766,8 +767,7 @@ __global__ __launch_bounds__(256, 2) void qpass_mfma(const bf16raw* __restrict__
 // copy, 16 instead of 11 us, and 381 instead of 184 in the large launch; 128 registers and two workgroups a CU: 239 -> 184.
 // Piece q (16 bytes) of centre row r sits in slot q ^ (r & 15) of its 256 bytes: a read of 32 rows meets every bank twice.
 // NS = 1, with at most 32 centres: one tile, and its two waves are the workgroup (30 x 3 000 points, 8 centres: the other six
-// waves of 1 400 workgroups made a pass 20 us instead of 14; a point a thread, which read no more centres than there are,
-// was 10 % faster there and at 100 000 points with 8 centres, and slower from 32 centres or below some 50 000 points on).
+// waves of 1 400 workgroups made a pass 20 us instead of 14).  Few centres in large launches go to assign_rows.
 template <int D, int NS>
 __global__ __launch_bounds__(NS * 64 * (ASSIGN_POINTS_F32 / 32), 4) void assign_f32(const float* __restrict__ X, AssignCfg cfg,
                                                   const float* __restrict__ cent,
@@ -906,6 +906,88 @@ __global__ __launch_bounds__(NS * 64 * (ASSIGN_POINTS_F32 / 32), 4) void assign_
     if (sp == 0 && lane == 0) wsum[pg] = dsum;
     __syncthreads();
     if (tid == 0) cfg.dist_sum[(size_t)h * gridDim.x + blockIdx.x] = wsum[0] + wsum[1];
+  }
+}
+
+// The same scores, labels, distances and counts, to the bit, from a point a thread and centres broadcast from LDS: vector
+// multiply-adds for the centres that there are, where assign_f32 takes whole tiles of 32 and its points twice through LDS.
+// assign_f32_rows() says when.
+constexpr int ROWS_POINTS = 128;
+static_assert(ROWS_POINTS == 2 * ASSIGN_POINTS_F32 && ASSIGN_POINTS_F32 == 64, "a wave's points are those of a count");
+template <int D>
+__global__ __launch_bounds__(ROWS_POINTS) void assign_rows(const float* __restrict__ X, AssignCfg cfg,
+                                                           const float* __restrict__ cent,
+                                                           const float* __restrict__ bias,
+                                                           int32_t* __restrict__ labels, float* __restrict__ dist2) {
+  constexpr int CB = 32;
+  const int h = blockIdx.y;
+  int n, m, row_off;
+  if (!assign_setup(cfg, h, n, m, row_off)) return;
+  const int base = blockIdx.x * ROWS_POINTS;
+  if (base >= n) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int p = base + tid;
+  __shared__ __attribute__((aligned(16))) float cs[CB * D];
+  __shared__ float bs[CB];
+  float x[D];
+  float xn2 = 0.f;
+  if (p < n) {
+    const int tok = cfg.ulist ? cfg.ulist[(size_t)h * cfg.N + p] : p;
+    const float4* row = reinterpret_cast<const float4*>(X + ((size_t)h * cfg.N + tok) * D);
+#pragma unroll
+    for (int q = 0; q < D / 4; ++q) {
+      const float4 v = row[q];
+      x[4 * q] = v.x; x[4 * q + 1] = v.y; x[4 * q + 2] = v.z; x[4 * q + 3] = v.w;
+    }
+#pragma unroll
+    for (int j = 0; j < D; ++j) xn2 = fmaf(x[j], x[j], xn2);
+  } else {
+#pragma unroll
+    for (int j = 0; j < D; ++j) x[j] = 0.f;
+  }
+  const float* ch = cent + ((size_t)h * cfg.cap + row_off) * D;
+  const float* bh = bias + (size_t)h * cfg.cap + row_off;
+  float best = -INFINITY; int bidx = 0;
+  for (int c0 = 0; c0 < m; c0 += CB) {
+    __syncthreads();
+    for (int i = tid; i < CB * D / 4; i += ROWS_POINTS) {
+      const int r = i / (D / 4);
+      float4 v = {0.f, 0.f, 0.f, 0.f};
+      if (c0 + r < m) v = reinterpret_cast<const float4*>(ch + (size_t)c0 * D)[i];
+      reinterpret_cast<float4*>(cs)[i] = v;
+    }
+    if (tid < CB) bs[tid] = (c0 + tid < m) ? bh[c0 + tid] : -INFINITY;
+    __syncthreads();
+    const int rmax = min(CB, m - c0);
+    for (int r = 0; r < rmax; ++r) {
+      float s = 0.f;
+#pragma unroll
+      for (int q = 0; q < D / 4; ++q) {
+        const float4 v = *reinterpret_cast<const float4*>(&cs[r * D + 4 * q]);
+        s = fmaf(x[4 * q], v.x, s); s = fmaf(x[4 * q + 1], v.y, s);
+        s = fmaf(x[4 * q + 2], v.z, s); s = fmaf(x[4 * q + 3], v.w, s);
+      }
+      s += bs[r];
+      if (s > best) { best = s; bidx = c0 + r; }
+    }
+  }
+  const float d2 = fmaxf(xn2 - 2.f * best, 0.f);
+  if (p < n) {
+    labels[(size_t)h * cfg.N + p] = bidx;
+    if (dist2) dist2[(size_t)h * cfg.N + p] = d2;
+  }
+  // a wave's 64 points are a workgroup of assign_f32 (the last workgroup may have none for its second wave)
+  const int part = 2 * blockIdx.x + wave;
+  const bool any = base + wave * 64 < n;
+  if (cfg.keep_cnt && dist2) {
+    const uint64_t kept = __ballot(p < n && !(d2 < cfg.tau[1]));
+    if (any && lane == 0) cfg.keep_cnt[(size_t)h * cfg.keep_stride + part] = __popcll(kept);
+  }
+  if (cfg.dist_sum) {                                    // (over all points: the first stage)
+    double dsum = p < n ? (double)sqrtf(d2) : 0.0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) dsum += __shfl_xor(dsum, o);
+    if (any && lane == 0) cfg.dist_sum[(size_t)h * ((cfg.N + 63) / 64) + part] = dsum;
   }
 }
 
@@ -2211,6 +2293,23 @@ bool combine_fits(int d, int heads, int n_bound, int m_bound) {
   return nb * m_bound * d * 4 <= (128 << 10) && m_bound <= (d == 64 ? 64 : 40) && nb * heads <= 512;
 }
 
+// Which fp32 assignment: assign_f32 pays for whole tiles (up to 32 centres one, up to 128 four, of which it skips those past
+// the count but not their waves), assign_rows for every centre, at little more than the time of a thread's chain of multiply-adds
+// while the launch is small.  So the matrix cores take small launches, many centres and, of each tile count, the upper end.
+// us, assign_f32 and assign_rows, d=64, 49 152 points: 4 centres 7 and 6, 16 7 and 11, 65 14 and 29; 160 000: 16 17 and 15, 24 17
+// and 19, 48 30 and 29, 64 31 and 36, 72 39 and 39; 600 000: 8 49 and 29, 20 49 and 46, 28 49 and 57, 48 102 and 82, 65 130
+// and 103, 88 130 and 129, 112 136 and 160.  d=128, 49 152: 4 13 and 10, 12 13 and 16; 60 000 (past three workgroups a CU):
+// 16 22 and 18, 24 22 and 24; 393 120: 20 85 and 80, 24 85 and 92; 1 080 000: 4 285 and 113, 32 286 and 281, 36 318 and 307,
+// 40 316 and 330, 65 427 and 472.
+static bool assign_f32_rows(int d, long long points, int m) {
+  const int t = m <= 32 ? 0 : m <= 64 ? 1 : 2;         // one tile, two, three
+  struct Line { long long points; int most[3]; };      // from so many points on: most centres for assign_rows
+  static constexpr Line d64[] = {{1000000, {26, 64, 96}}, {200000, {21, 60, 84}}, {150000, {17, 49, 67}}, {100000, {12, 35, 0}}, {20000, {4, 0, 0}}};
+  static constexpr Line d128[] = {{500000, {32, 36, 0}}, {55000, {20, 0, 0}}, {20000, {6, 0, 0}}};
+  auto most = [&](const auto& lines) { for (const Line& l : lines) if (points >= l.points) return l.most[t]; return 0; };
+  return m <= (d == 64 ? most(d64) : most(d128));
+}
+
 int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, int m_bound, int mode, int m_const, int cap,
                   const KState* st, const int32_t* ulist, const void* X, const void* cent_lp, const float* bias,
                   int32_t* labels, float* dist2, int32_t* keep_lab, float* keep_score, const int32_t* seed_lab,
@@ -2222,9 +2321,12 @@ int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, in
     if (d == 64) assign_mfma<64><<<g, 256, 0, s>>>((const bf16raw*)X, c, (const bf16raw*)cent_lp, bias, labels, dist2);
     else assign_mfma<128><<<g, 256, 0, s>>>((const bf16raw*)X, c, (const bf16raw*)cent_lp, bias, labels, dist2);
   } else {
-    dim3 g((n_bound + ASSIGN_POINTS_F32 - 1) / ASSIGN_POINTS_F32, H);
+    dim3 g((n_bound + ASSIGN_POINTS_F32 - 1) / ASSIGN_POINTS_F32, H), gr((n_bound + ROWS_POINTS - 1) / ROWS_POINTS, H);
     const float *x = (const float*)X, *ce = (const float*)cent_lp;
-    if (m_bound <= 32) {
+    if (assign_f32_rows(d, (long long)H * n_bound, m_bound)) {
+      if (d == 64) assign_rows<64><<<gr, ROWS_POINTS, 0, s>>>(x, c, ce, bias, labels, dist2);
+      else assign_rows<128><<<gr, ROWS_POINTS, 0, s>>>(x, c, ce, bias, labels, dist2);
+    } else if (m_bound <= 32) {
       if (d == 64) assign_f32<64, 1><<<g, 128, 0, s>>>(x, c, ce, bias, labels, dist2);
       else assign_f32<128, 1><<<g, 128, 0, s>>>(x, c, ce, bias, labels, dist2);
     } else {

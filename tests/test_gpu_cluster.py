@@ -5,6 +5,7 @@ step is checked from there: labels must be the arg-min / arg-max to the centres 
 (exact except near-ties below 1e-5 relative margin), centroids must be the (normalised) member
 means of the GPU labels, and Algorithm 1's structure (stage counts, threshold filter, flag F)
 must hold for the GPU's own unassigned sets."""
+import dataclasses
 import math
 
 import numpy as np
@@ -139,6 +140,69 @@ def test_fp32_assignment_at_tile_edges(d, N, Cq):
         X = Q[h].astype(np.float64)
         assert np.array_equal(ca[h], X[((2 * np.arange(Cq) + 1) * N) // (2 * Cq)])
         assert np.array_equal(lab[h], (X @ ca[h].T - 0.5 * (ca[h] ** 2).sum(1)).argmax(1))
+
+
+def ordered_chain(X, C):
+    """X C^T in fp32 as a chain of fused multiply-adds in ascending dimension order (64 bits of mantissa hold a product
+    exactly and a sum to far below half an fp32 step)."""
+    acc = np.zeros((X.shape[0], C.shape[0]), dtype=np.float32)
+    for t in range(X.shape[1]):
+        acc = (X[:, t, None].astype(np.longdouble) * C[None, :, t] + acc).astype(np.float32)
+    return acc
+
+
+@pytest.mark.parametrize("d,H,N,Cq", [(64, 1, 400, 40), (64, 1, 400, 150), (128, 1, 400, 30), (128, 1, 300, 100),       # by tiles
+                                      (64, 60, 400, 4), (128, 60, 400, 6), (64, 500, 401, 40), (128, 140, 400, 18)])      # by points
+def test_fp32_assignment_is_the_ordered_chain(d, H, N, Cq):
+    """Either kernel's scores are the chain of fused multiply-adds in ascending dimension order, to the bit: pairs of centres
+    so near that mostly the rounding of their scores decides, and the label is the chain's arg-max all the same."""
+    rng = np.random.default_rng(41)
+    Q = rng.standard_normal((N, d)).astype(np.float32)
+    at = ((2 * np.arange(Cq) + 1) * N) // (2 * Cq)
+    for a, b in zip(at[0::2], at[1::2]):
+        Q[b] = Q[a] * (1 + 1e-7 * rng.standard_normal(d)).astype(np.float32)
+    Q[~np.isin(np.arange(N), at)] *= rng.uniform(0.5, 2.0, (N - Cq, 1)).astype(np.float32)
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=Cq, q_iters=1, k_m0=4, k_m_min=1, k_max_clusters=8)
+    out = B.adacluster_qcluster(p, to_dev(Q, B.F32)[None].expand(H, -1, -1).contiguous())
+    lab, ca = out["q_labels"].cpu().numpy(), out["q_assign_centroids"][0].cpu().numpy()
+    ref = ordered_chain(Q, ca)
+    assert np.array_equal(lab[0], ref.argmax(1)) and (lab == lab[0]).all()
+    if Cq > 2:            # it is the rounding that decides: exact scores choose another centre now and then
+        assert (ref.argmax(1) != (Q.astype(np.float64) @ ca.T.astype(np.float64)).argmax(1)).sum() > N // 100
+
+
+@pytest.mark.parametrize("d,H,N,Cq", [(64, 45, 448, 4), (64, 45, 463, 4), (64, 90, 2001, 17), (64, 90, 2001, 49), (64, 90, 2001, 67),
+                                      (64, 101, 2001, 60), (64, 101, 2001, 84), (128, 45, 451, 6), (128, 32, 1985, 20), (128, 250, 2001, 36), (64, 500, 2001, 96),
+                                      (64, 32, 1985, 15), (64, 33, 1985, 15), (128, 32, 1985, 15), (128, 33, 1985, 15)])     # 1 024 parts, 1 056
+def test_fp32_query_clustering_by_launch_size(d, H, N, Cq):
+    """Assignment and reduction are chosen by the size of the launch (assign_rows past the lines that the cases lie on, four
+    waves a part up to 1 024 parts): one head alone and many of the same head give the same bits."""
+    Q, _, _ = wl.make_small(61, N, d, 20, dtype="f32", H=1)
+    p = B.Params(H=1, N=N, d=d, dtype=B.F32, q_clusters=Cq, q_iters=3, k_m0=4, k_m_min=1, k_max_clusters=8)
+    Qd = to_dev(Q, B.F32)
+    one = B.adacluster_qcluster(p, Qd)
+    many = B.adacluster_qcluster(dataclasses.replace(p, H=H), Qd.expand(H, -1, -1).contiguous())
+    for name, a in one.items():
+        assert torch.equal(many[name], a.expand_as(many[name])), name
+
+
+@pytest.mark.parametrize("d,H,N,m0,frac", [(64, 70, 1505, 12, 0.0), (64, 150, 1505, 20, 0.03), (128, 60, 1505, 16, 0.0)])
+def test_fp32_key_stages_by_launch_size(d, H, N, m0, frac):
+    """The same for the stages of Algorithm 1: survivors are counted per 64 points by either assignment, and the last
+    workgroup of assign_rows has no points for its second wave."""
+    _, K, _ = wl.make_small(62, N, d, 40, dtype="f32", H=1)
+    p = B.Params(H=1, N=N, d=d, dtype=B.F32, q_clusters=4, k_iters=3, k_m0=m0, k_m_min=2, k_max_clusters=6 * m0,
+                 min_unassigned_frac=frac)
+    Kd = to_dev(K, B.F32)
+    one = B.adacluster_kcluster(p, Kd)
+    pm = dataclasses.replace(p, H=H, tau_abs=float(one["tau_used"][0]))
+    many = B.adacluster_kcluster(pm, Kd.expand(H, -1, -1).contiguous())
+    own = B.adacluster_kcluster(dataclasses.replace(pm, tau_abs=0.0), Kd.expand(H, -1, -1).contiguous())
+    assert int(one["k_stage_of"].max()) >= 1
+    assert abs(float(own["tau_used"][0]) / float(one["tau_used"][0]) - 1) < 1e-6
+    for name, a in one.items():
+        if a is not None and name != "tau_used":
+            assert torch.equal(many[name], a.expand_as(many[name])), name
 
 
 def test_qcluster_free_running_fp32_matches_oracle_trajectory():
