@@ -99,6 +99,7 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_kernel(SelectCfg cfg, con
     qs[e] = v;
   }
   __syncthreads();
+  if (j >= kc) return;          // (a wave without a cluster reads no LDS: 30 x 1 063 lists of some 50 clusters, d=64, 76 -> 53 us)
   double sp[QG], sn[QG];
 #pragma unroll
   for (int g = 0; g < QG; ++g) { sp[g] = 0.0; sn[g] = 0.0; }
@@ -130,7 +131,6 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_kernel(SelectCfg cfg, con
       }
     }
   }
-  if (j >= kc) return;
   const int nj = k_sizes[(size_t)h * cfg.cap + j];
   double* out = S + ((size_t)h * cfg.Cq + i0) * cfg.cap + j;
 #pragma unroll
