@@ -788,13 +788,14 @@ int adacluster_attn(const adacluster_params* p, const void* Q, const void* K, co
   if (rc) return rc;                        // (what was queued on the second stream has been joined)
   prof_mark(EV_JOIN, st);
   const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)p->d);
+  int32_t* const sel_keys = plan_reads_lengths(p->q_clusters) ? w.sel_keys : nullptr;
   rc = launch_select(st, p->H, p->q_clusters, capacity(p), p->d, p->score_mode, p->select_mode, p->topk, p->top_p,
                      scale, q_centroids, q_mean_norm, k_centroids, k_bmin, k_bmax, k_sizes, k_count, full_flag,
-                     sel_idx, sel_cnt, kc_bound, w.scores, w.sel_keys);
+                     sel_idx, sel_cnt, kc_bound, w.scores, sel_keys);
   if (rc) return drained(rc == ADACLUSTER_E_INTERNAL ? fail(rc, "HIP launch failed: %s", hipGetErrorString(hipGetLastError())) : rc);
   prof_mark(EV_SELECT, st, EV_JOIN);
   // both label sorts were left in the workspace by the clustering steps
-  rc = run_plan_attention(p, w, st, Q, O, k_count, sel_idx, sel_cnt, w.sel_keys, EV_SELECT, K, V);
+  rc = run_plan_attention(p, w, st, Q, O, k_count, sel_idx, sel_cnt, sel_keys, EV_SELECT, K, V);
   return rc ? drained(rc) : 0;
 }
 

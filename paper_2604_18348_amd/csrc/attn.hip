@@ -1271,6 +1271,7 @@ int attn_f32_splits(int H, int N, int Cq) {
   return H <= PICK_HEADS && (long long)H * (N / 32 + Cq / 2 + 1) < 1024 ? F32_MAX_SPLITS : 1;
 }
 
+bool plan_reads_lengths(int Cq) { return Cq <= PLAN_BESIDE; }
 int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
                        const int32_t* q_offs, int q_offs_stride, const int32_t* k_offs, int k_offs_stride,
                        const int32_t* k_count, const int32_t* sel_idx, const int32_t* sel_cnt,
@@ -1279,7 +1280,7 @@ int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int max
                        const int32_t* perm_k, int N, const int32_t* lengths) {
   const int split = dtype == ADACLUSTER_BF16 ? 1 : 0;
   const TilePlan tp{lengths, q_offs, q_offs_stride, maxtiles, BM, SPLIT_SLOTS, split, tiles, ntiles, merge, nmerge};
-  if (lengths && Cq <= PLAN_BESIDE) {
+  if (lengths && plan_reads_lengths(Cq)) {
     plan_sparse<true><<<dim3(Cq + 1, H), 256, PLAN_ARRAYS * 4 * Cq, s>>>(Cq, cap, maxr, row_scale, k_offs, k_offs_stride, k_count, sel_idx, sel_cnt, rng_start,
                                                                          rng_pre, rng_cnt, krow, kstride, perm_k, N, tp);
   } else {

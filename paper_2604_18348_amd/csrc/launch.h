@@ -129,6 +129,7 @@ int launch_mfma_probe(hipStream_t s, int iters, float* sink, size_t sink_floats,
 int attn_f32_splits(int H, int N, int Cq);   // most pieces a key list of the fp32 kernel may go in
 int attn_tile_record();      // ints per query-tile record
 int attn_split_slots();      // partial slots per head for the chunks of cut key lists (also extra tile records)
+bool plan_reads_lengths(int Cq);   // whether launch_plan_sparse has a use for the lengths of the lists
 int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
                        const int32_t* q_offs, int q_offs_stride, const int32_t* k_offs, int k_offs_stride,
                        const int32_t* k_count, const int32_t* sel_idx, const int32_t* sel_cnt,

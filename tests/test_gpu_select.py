@@ -125,7 +125,7 @@ def test_scores_by_every_group_size(H, Cq, cap, kc, d, score_mode):
 
 
 @pytest.mark.parametrize("top_p", [0.05, 0.5, 0.93])
-@pytest.mark.parametrize("kcs", [(1, 9, 255), (256, 257, 513), (700, 1300, 3)])
+@pytest.mark.parametrize("kcs", [(1, 9, 255), (256, 257, 513), (700, 1300, 3), (63, 64, 65)])
 def test_topp_ranks_of_equal_and_nearly_equal_weights(kcs, top_p):
     """The order of the weights is decided by the upper halves of their keys, and by the whole keys and the index where those
     are shared: equal centroids, centroids a billionth apart (some 2^-30 of a weight: the upper half holds 2^-20), weights of
