@@ -364,6 +364,14 @@ int launch_attn_stats(hipStream_t s, int H, int Cq, int maxr, int maxtiles, cons
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
 }
 
+// Pieces for `rest` tiles of an XCD, for every number of them: two bits each (pieces - 1), 32 a word.  By the host, as the
+// kernel's registers and first microseconds are dear (3 x 5 007 rows, d=128, a call 288 us, 290 with the rule in the kernel).
+struct Pieces { uint64_t of[3]; };
+__device__ __forceinline__ int pieces_of(const Pieces& p, int rest) {
+  const uint64_t w = rest < 32 ? p.of[0] : rest < 64 ? p.of[1] : p.of[2];
+  return 1 + (int)(w >> (2 * (rest & 31)) & 3);
+}
+
 struct AttnArgs {
   const void* Q; const void* K; const void* V; void* O;
   const int32_t* perm_q;        // sorted query position -> token (NULL: identity)
@@ -376,7 +384,8 @@ struct AttnArgs {
   const int32_t* krow; size_t kstride;   // every key row of a query cluster's list (byte offset, fp32: row number): [H][Cq][kstride]
   const int32_t* rng_start; const int32_t* rng_pre; const int32_t* rng_cnt; int maxr;   // the ranges it was written from, and
   const int32_t* perm_k;                 // their order -> token (NULL: identity): for the fp32 kernel without a table
-  int splits;                            // fp32: most pieces a key list may go in
+  int splits;                            // fp32: most pieces a key list may go in, and what f32_pieces() says
+  Pieces pieces;
 };
 
 // Workgroup -> (head, query tile) of a launch of pick_tile_grid.  Workgroups go to the 8 XCDs round-robin in launch order,
@@ -390,12 +399,13 @@ struct AttnArgs {
 // heads of 2 000 rows, d=64, 33 clusters 288, 579 and 975 us by search, 331, 664 and 1 107 by rows; of 1 000 rows and 200 clusters
 // 228, 456, 802 and 216, 417, 704; 1 024 heads of 128 rows 718 by rows (by search, when tiles were 64 rows, 1 625).
 // With `splits` > 1 the key lists of the tiles that would not fill the chip once more are split: an XCD runs `resident`
-// workgroups at a time, and the tiles past the last whole round of them (all of them in a small launch) go in pieces, some
-// 1.6 per place (z says which), so that no CU is left with a whole one when the others are done.  585 tiles, d=128, are 75
+// workgroups at a time, and the tiles past the last whole round of them (all of them in a small launch) go in pieces (z says
+// which; f32_pieces() how many), so that no CU is left with a whole one when the others are done.  585 tiles, d=128, are 75
 // an XCD that holds 64 workgroups: 64 whole and 11 in four pieces, 198 us; all of them in two pieces, three rounds, 222.
 // Returns false where the list has ended.
 constexpr int PICK_HEADS = 256;
-__device__ __forceinline__ bool pick_tile(const int32_t* __restrict__ ntiles, int H, int splits, int resident, int& h, int& tile,
+
+__device__ __forceinline__ bool pick_tile(const int32_t* __restrict__ ntiles, int H, const Pieces& pieces, int splits, int resident, int& h, int& tile,
                                           int& z, int& sp) {
   const int xcd = blockIdx.x & 7, lane = threadIdx.x & 63;
   int slot = blockIdx.x >> 3;
@@ -406,27 +416,31 @@ __device__ __forceinline__ bool pick_tile(const int32_t* __restrict__ ntiles, in
     tile = xcd * w + slot;
     return slot < w && tile < nt;
   }
-  if (splits > 1) {
-    int total = 0;
-    for (int h0 = 0; h0 < H; h0 += 64) total += h0 + lane < H ? (ntiles[h0 + lane] + 7) >> 3 : 0;
+  int nt, w, incl;                                         // 64 heads at a time, one per lane: tiles, this XCD's share of them
+  auto take = [&](int h0) __attribute__((always_inline)) { // (the last XCD's may be short), and the shares up to here
+    nt = h0 + lane < H ? ntiles[h0 + lane] : 0;
+    w = (nt + 7) >> 3;
+    incl = w;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) total += __shfl_xor(total, o);
+    for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
+  };
+  take(0);
+  if (splits > 1) {
+    int total = __builtin_amdgcn_readlane(incl, 63);
+    for (int h0 = 64; h0 < H; h0 += 64) { take(h0); total += __builtin_amdgcn_readlane(incl, 63); }
+    if (H > 64) take(0);
     const int rest = total % resident, whole = total - rest;
     if (slot >= whole) {
       if (rest == 0) return false;
-      sp = max(1, min(splits, (8 * resident / 5 + rest / 2) / rest));
+      sp = pieces_of(pieces, rest);
       z = (slot - whole) / rest;                           // (first pieces first: short lists have no others, which end at once)
       if (z >= sp) return false;
       slot -= z * rest;
     }
   }
   int base = 0;
-  for (int h0 = 0; h0 < H; h0 += 64) {                     // 64 heads at a time, one per lane
-    const int nt = h0 + lane < H ? ntiles[h0 + lane] : 0;
-    const int w = (nt + 7) >> 3;                           // this XCD's share of the head (the last XCD's may be short)
-    int incl = w;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
+  for (int h0 = 0; h0 < H; h0 += 64) {
+    if (h0 > 0) take(h0);
     const uint64_t past = __ballot(base + incl > slot);
     if (past) {
       const int l = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)past) - 1);
@@ -881,7 +895,7 @@ template <int D, bool LISTED>
 __global__ __launch_bounds__(F32_WAVES * 64, D == 64 ? 3 : 2) void attn_f32(AttnArgs a) {
   constexpr int BN = 32, DB = D / 32, NW = F32_WAVES, SROW = D + 4, PPR = D / 4, RPI = 64 / PPR;   // 16-byte pieces a row, rows a load
   int h, tile, z, sp;
-  if (!pick_tile(a.ntiles, a.H, a.splits, f32_resident(D), h, tile, z, sp)) return;
+  if (!pick_tile(a.ntiles, a.H, a.pieces, a.splits, f32_resident(D), h, tile, z, sp)) return;
   const int32_t* tl = a.tiles + ((size_t)h * a.maxtiles + tile) * TILE_REC;          // (key lists are never cut for fp32)
   const int qc = tl[0], row0 = tl[1], nrows = tl[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1118,7 +1132,6 @@ __global__ __launch_bounds__(256) void attn_merge_f32(AttnArgs a, int splits) {
   constexpr int LPR = D / 4;
   const int h = blockIdx.y, pos = blockIdx.x * (256 / LPR) + threadIdx.x / LPR, col = (threadIdx.x % LPR) * 4;
   if (pos >= a.N) return;
-  if (a.part_ml[((size_t)h * splits * a.N + pos) * 2 + 1] == PART_DONE) return;
   float M = -INFINITY, L = 0.f, ms[F32_MAX_SPLITS], ls[F32_MAX_SPLITS];
   float4 os[F32_MAX_SPLITS] = {}, x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1127,6 +1140,7 @@ __global__ __launch_bounds__(256) void attn_merge_f32(AttnArgs a, int splits) {
     ms[z] = z < splits ? a.part_ml[pr * 2] : -INFINITY;
     ls[z] = a.part_ml[pr * 2 + 1];
   }
+  if (ls[0] == PART_DONE) return;
 #pragma unroll
   for (int z = 0; z < F32_MAX_SPLITS; ++z)                 // (pieces that there are not have no row)
     if (ms[z] > -INFINITY) os[z] = *reinterpret_cast<const float4*>(a.part_o + (((size_t)h * splits + z) * a.N + pos) * D + col);
@@ -1271,6 +1285,47 @@ int attn_f32_splits(int H, int N, int Cq) {
   return H <= PICK_HEADS && (long long)H * (N / 32 + Cq / 2 + 1) < 1024 ? F32_MAX_SPLITS : 1;
 }
 
+// The rule: the number that ends first, the smallest of equals.  A piece takes a wave's share of the list's key tiles (as many
+// as a list can have) and half a tile for its start and end; the workgroups that share a CU take turns, so a round lasts as
+// long as it has workgroups a CU (alone on one, a little longer), and one that is not full a quarter of the way to a full one
+// longer, unless it is the first: not every CU gets its share of those.
+// us of a dense call with 1, 2, 3 and 4 pieces (chosen: the one in brackets): d=128, 3 x 2 088, 27 tiles an XCD: 87 [86] 108 94;
+// 1 x 2 101 (9): 86 53 [41] 53; 4 x 3 076 (52): 215 224 [198] 209; 12 x 467 (24): [30] 35 38 40; d=64, 1 x 4 746 (19): 100 95 [71]
+// 76; 12 x 772 (48): 41 [37] 43 42; 8 x 2 414 (80): 134 123 131 [128].  (1.6 pieces a place, whatever they leave of a round, took
+// 108, 53, 224, 40, 76, 43 and 122 us; four for every list where those are fewer than 1 024, 92, 51, 194, 39, 75, 40 and 124.)
+// (The turns are a table: 380 of them by division were 5 us of a call.)
+template <int D>
+struct PieceTurns {
+  static constexpr int RESIDENT = f32_resident(D), FULL = RESIDENT / 32;      // FULL: workgroups of a CU
+  int of[RESIDENT][F32_MAX_SPLITS];                                           // in 32nds of one alone on every CU
+  constexpr PieceTurns() : of{} {
+    for (int rest = 1; rest < RESIDENT; ++rest)
+      for (int sp = 1; sp <= F32_MAX_SPLITS; ++sp) {
+        const int n = rest * sp, f = n / RESIDENT, r = n % RESIDENT, k = (r + 31) / 32;
+        of[rest][sp - 1] = 32 * FULL * f + (r == 0 ? 0 : f > 0 ? 24 * k + 8 * FULL : k > 1 ? 32 * k : 33);
+      }
+  }
+};
+template <int D>
+static Pieces f32_pieces(int N) {
+  static constexpr PieceTurns<D> turns{};
+  static_assert(F32_MAX_SPLITS <= 4 && PieceTurns<D>::RESIDENT <= 96, "Pieces holds them");
+  const int keys = (N + 31) / 32;
+  long long len[F32_MAX_SPLITS];
+  for (int i = 0; i < F32_MAX_SPLITS; ++i) len[i] = 2ll * ((keys + (i + 1) * F32_WAVES - 1) / ((i + 1) * F32_WAVES)) + 1;
+  Pieces p{};
+  for (int rest = 1; rest < PieceTurns<D>::RESIDENT; ++rest) {
+    long long best = turns.of[rest][0] * len[0];
+    int more = 0;
+    for (int i = 1; i < F32_MAX_SPLITS; ++i) {
+      const long long t = turns.of[rest][i] * len[i];
+      if (t < best) { best = t; more = i; }
+    }
+    p.of[rest / 32] |= (uint64_t)more << (2 * (rest % 32));
+  }
+  return p;
+}
+
 bool plan_reads_lengths(int Cq) { return Cq <= PLAN_BESIDE; }
 int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
                        const int32_t* q_offs, int q_offs_stride, const int32_t* k_offs, int k_offs_stride,
@@ -1306,7 +1361,8 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
              scale * 1.4426950408889634f,
              (Cq == 1 || (size_t)4 * N * d <= ((size_t)8 << 20)) ? 1 : 0,
              part_o, part_ml, SPLIT_SLOTS, attn_block_rows(dtype, d, N, Cq), krow, kstride,
-             rng_start, rng_pre, rng_cnt, maxr, perm_k, dtype == ADACLUSTER_F32 ? attn_f32_splits(H, N, Cq) : 1};
+             rng_start, rng_pre, rng_cnt, maxr, perm_k, dtype == ADACLUSTER_F32 ? attn_f32_splits(H, N, Cq) : 1, {}};
+  if (a.splits > 1) a.pieces = d == 64 ? f32_pieces<64>(N) : f32_pieces<128>(N);
   dim3 g((maxtiles + 7) / 8 * 8, H);
   if (dtype == ADACLUSTER_BF16) {
     if (attn_small_shape(N, Cq)) {

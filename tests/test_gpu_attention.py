@@ -277,14 +277,34 @@ def test_fp32_more_workgroups_than_one_grid_dimension_takes():
         assert float((O[h:h + 8192] - ref).abs().max()) < 1e-4
 
 
-@pytest.mark.parametrize("H,N,d,splits", [(64, 545, 64, 1), (65, 545, 128, 1), (256, 330, 64, 1), (257, 330, 128, 1), (45, 545, 64, 2), (21, 545, 128, 3), (5, 545, 64, 4)])
-def test_fp32_lists_whole_and_split_over_up_to_four_workgroups(H, N, d, splits):
-    """A launch that fills the chip leaves key lists whole (the kernel writes the output itself), smaller ones split them over
-    two, three and four workgroups; up to 256 heads are dealt from the tile counts, 64 at a time, more have a grid row each.  Sparse, with an empty
-    list and an empty cluster, and dense; every output element is written."""
+def pieces_of_the_last_round(tiles, N, d):
+    """(whole rounds, tiles left over, pieces of their lists) of an XCD, by the rule of the fp32 kernel; `tiles` per head."""
+    full = 3 if d == 64 else 2
+    whole, rest = divmod(sum(-(-int(t) // 8) for t in tiles), 32 * full)
+    cost = {}
+    for sp in (1, 2, 3, 4):
+        f, r = divmod(rest * sp, 32 * full)
+        k = -(-r // 32)
+        turns = 32 * full * f + (0 if r == 0 else 24 * k + 8 * full if f else 32 * k if k > 1 else 33)
+        cost[sp] = turns * (2 * -(-(-(-N // 32)) // (4 * sp)) + 1)
+    return whole, rest, min(cost, key=lambda sp: (cost[sp], sp))
+
+
+@pytest.mark.parametrize("H,N,d,whole,rest,pieces",
+                         [(64, 545, 64, 0, 0, 1), (65, 545, 128, 0, 0, 1), (256, 330, 64, 0, 0, 1), (257, 330, 128, 0, 0, 1),      # left whole
+                          (6, 545, 64, 0, 18, 3), (5, 545, 64, 0, 15, 2), (31, 545, 64, 0, 93, 1), (12, 1321, 64, 0, 72, 4),      # one round
+                          (32, 545, 64, 1, 0, 1), (45, 545, 64, 1, 39, 2), (35, 545, 64, 1, 9, 3), (48, 545, 64, 1, 48, 2), (56, 545, 64, 1, 72, 1),        # and past it
+                          (13, 545, 128, 0, 39, 3), (5, 545, 128, 0, 15, 2), (21, 545, 128, 0, 63, 1), (8, 1321, 128, 0, 48, 4),
+                          (43, 545, 128, 2, 1, 3), (64, 300, 128, 2, 0, 1), (25, 545, 128, 1, 11, 2), (31, 545, 128, 1, 29, 1), (11, 1321, 128, 1, 2, 4)])
+def test_fp32_lists_whole_and_split_over_up_to_four_workgroups(H, N, d, whole, rest, pieces):
+    """A launch of many tiles leaves key lists whole (the kernel writes the output itself); in smaller ones the tiles past the
+    last whole round of an XCD go in up to four pieces, none left over and one among them; up to 256 heads are dealt from the
+    tile counts, 64 at a time, more have a grid row each.  Sparse, with an empty list and an empty cluster (the counts are those
+    of the dense call); every output element is written."""
     Cq = 5
-    for clusters in (Cq, 1):                       # (the dense call counts as one)
-        assert min(4, -(-1024 // (H * (N // 32 + clusters // 2 + 1)))) == splits
+    cut = H <= 256 and H * (N // 32 + 1) < 1024
+    if cut:
+        assert pieces_of_the_last_round([-(-N // 32)] * H, N, d) == (whole, rest, pieces)
     Q, K, V, ql, kl, sel = make_case(41, N, d, B.F32, H=H)
     for h in range(0, H, 3):
         sel[h][2] = np.zeros(0, dtype=np.int64)
