@@ -333,21 +333,24 @@ int check_ws(const adacluster_params* p, void* ws, size_t ws_bytes, WS* w) {
 }
 
 #define RET_IF(expr) { int rc_ = (expr); if (rc_ != 0) return rc_ == ADACLUSTER_E_INTERNAL ? fail(rc_, "HIP launch failed: %s", hipGetErrorString(hipGetLastError())) : rc_; }
+#define PASS_ON(expr) { int rc_ = (expr); if (rc_ != 0) return rc_; }      // (an error that has been reported)
 
 // ---- query clustering ----------------------------------------------------------------------
+// passes it0 .. it1 - 1 (the first behind the initial centres)
 int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const void* Q, int32_t* q_labels,
-                 float* q_centroids, float* q_assign, int32_t* q_sizes, float* q_mean_norm) {
+                 float* q_centroids, float* q_assign, int32_t* q_sizes, float* q_mean_norm, int it0, int it1) {
   const Dims D = dims_of(p);
   const int P = parts_for(D.N, D.Cq);
   int poff_done = 0;   // set when the sort has already cut the clusters into reduction parts
   const int sph = p->q_no_norm ? 0 : 1;      // by angle on q/|q| (the paper), or Euclidean on raw queries (ablation)
-  RET_IF(launch_init_centroids(st, p->dtype, D.d, D.H, D.N, D.Cq, D.Cq, nullptr, nullptr, nullptr, sph, p->q_init_mode,
-                               D.Cq, D.Cq, Q, q_centroids, w.q_cent_lp, q_assign, w.q_bias));
+  if (it0 == 0)
+    RET_IF(launch_init_centroids(st, p->dtype, D.d, D.H, D.N, D.Cq, D.Cq, nullptr, nullptr, nullptr, sph, p->q_init_mode,
+                                 D.Cq, D.Cq, Q, q_centroids, w.q_cent_lp, q_assign, w.q_bias));
   // A pass that only updates the centres reads the queries once: assignment and (normalised) sums in one
   // kernel.  The last pass needs the labels sorted (for the attention step) and exact member statistics, and
   // takes the sort and the segmented reduction.
   const bool one_read = p->dtype == ADACLUSTER_BF16 && D.Cq <= pass_sum_centres();
-  for (int it = 0; it < p->q_iters; ++it) {
+  for (int it = it0; it < it1; ++it) {
     if (one_read && it < p->q_iters - 1) {
       const int NP = qpass_walks(D.N);
       RET_IF(launch_qpass(st, D.d, D.H, D.N, D.Cq, D.Cq, sph, Q, w.q_cent_lp, w.q_bias, w.q_wsum, w.q_wcnt));
@@ -377,7 +380,8 @@ int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
 }
 
 // ---- Algorithm 1 ---------------------------------------------------------------------------
-// beside(): called once, where a cold start first waits for the device, or at the end of its stages (a warm start: not at all).
+// beside(rest): enqueues on another stream what runs beside a cold start: called between two passes of the first stage, and
+// (rest: all that is left) before the first wait for the device or at the end of the stages.  A warm start does not call it.
 template <typename F>
 int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const void* K, int32_t* k_labels,
                  float* k_centroids, float* k_assign, float* k_bmin, float* k_bmax, int32_t* k_sizes,
@@ -431,8 +435,6 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   if (!rb) return fail(ADACLUSTER_E_INTERNAL, "stage read-back set-up failed: %s", hipGetErrorString(hipGetLastError()));
   int n_bound = D.N, m_bound = p->k_m0 < D.N ? p->k_m0 : D.N, heads = D.H;
   KState* other = w.kstate2;                       // the stage head reads one and writes the other
-  bool called = false;
-  auto before_wait = [&]() { const bool first = !called; called = true; return first ? beside() : 0; };
   StageFilter filter{};                            // how the stage before ended
   for (int t = 0; t <= p->k_max_stages; ++t) {
     // the stage head writes its report straight into the pinned slot (no copy in between)
@@ -442,7 +444,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                              t > 0 ? rb->dev + 4 * t : nullptr, rb->epoch, p->k_m0, K, w.master, w.cent_lp, k_assign, w.bias));
     pending = t;
     if (t > 1) {
-      RET_IF(before_wait());
+      PASS_ON(beside(true));
       if (!stage_report_landed(*rb, t - 1, st))
         return fail(ADACLUSTER_E_INTERNAL, "stage read-back failed: %s", hipGetErrorString(hipGetLastError()));
       const int32_t* summ = rb->host + 4 * (t - 1);
@@ -458,7 +460,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       // points through the launch chain sized for all of them (label sort, segmented
       // reduction).  Then, once per call, the host waits for the report of the stage it is about to
       // enqueue; the other stream keeps the device busy meanwhile.
-      RET_IF(before_wait());
+      PASS_ON(beside(true));
       if (!stage_report_landed(*rb, 1, st))
         return fail(ADACLUSTER_E_INTERNAL, "stage read-back failed: %s", hipGetErrorString(hipGetLastError()));
       const int32_t* now = rb->host + 4;
@@ -486,6 +488,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     const StageSums sums[2] = {{w.bsum, w.bcnt}, {w.bsum + (size_t)D.H * m_bound * wblk * D.d, w.bcnt + (size_t)D.H * wblk * pass_sum_centres()}};
     int counted = stage_points_per_count(p->dtype);          // points per survivor count and distance sum of the last pass
     for (int it = 0; it < p->k_iters; ++it) {
+      if (t == 0 && it > 0) PASS_ON(beside(false));
       const bool update = it < p->k_iters - 1;
       const bool keep = seeded && t == 0 && !update;
       if (combine) {
@@ -528,7 +531,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     if (t == 0) RET_IF(launch_keep_count(st, cur, D.H, D.N, w.dist2, dist_sum, (D.N + counted - 1) / counted, p->tau_factor, w.tau, w.blockcnt,
                                          D.ncnt, &filter.items));
   }
-  RET_IF(before_wait());
+  PASS_ON(beside(true));
   kc_bound = kc_bound < D.cap ? kc_bound : D.cap;
   // last step of Algorithm 1: nearest centre among all stage centres, then member statistics.  bf16: the
   // nearest first-stage centre of every point is known from stage 0, so only the later stages' centres are visited.
@@ -613,7 +616,7 @@ int adacluster_qcluster(const adacluster_params* p, const void* Q, int32_t* q_la
   WS w;
   if ((rc = check_ws(p, ws, ws_bytes, &w))) return rc;
   prof_begin((hipStream_t)stream);
-  rc = run_qcluster(p, w, (hipStream_t)stream, Q, q_labels, q_centroids, q_assign_centroids, q_sizes, q_mean_norm);
+  rc = run_qcluster(p, w, (hipStream_t)stream, Q, q_labels, q_centroids, q_assign_centroids, q_sizes, q_mean_norm, 0, p->q_iters);
   prof_mark(EV_QCLUSTER, (hipStream_t)stream, EV_START);
   return rc;
 }
@@ -632,7 +635,7 @@ int adacluster_kcluster(const adacluster_params* p, const void* K, int32_t* k_la
   if ((rc = check_ws(p, ws, ws_bytes, &w))) return rc;
   prof_begin((hipStream_t)stream);
   rc = run_kcluster(p, w, (hipStream_t)stream, K, k_labels, k_centroids, k_assign_centroids, k_box_min, k_box_max,
-                    k_sizes, k_count, full_flag, k_stage_offs, k_stage_of, tau_used, nullptr, [] { return 0; });
+                    k_sizes, k_count, full_flag, k_stage_offs, k_stage_of, tau_used, nullptr, [](bool) { return 0; });
   prof_mark(EV_KCLUSTER, (hipStream_t)stream, EV_START);
   return rc;
 }
@@ -762,26 +765,37 @@ int adacluster_attn(const adacluster_params* p, const void* Q, const void* K, co
   // host waits for the second stream before it reports the error.
   auto drained = [&](int code) { (void)hipStreamSynchronize(aux->s); return code; };
   hipStream_t qs = aux->s;      // (measured: run in front of Algorithm 1 on the caller's stream instead, every configuration is 1-6 % slower)
+  // Algorithm 1 is the longer chain.  Where it waits for a report, it goes first, and the query clustering is enqueued while the
+  // host would only wait; its nine launches ahead of Algorithm 1 kept the device waiting (4 096 fp32 tokens 240 -> 221 us;
+  // 32 760 tokens, a call alone, 863 -> 840).  Where no report is waited for before the end (a warm start, or one launch for
+  // everything after the first stage) it stays first: 1 500 tokens, call after call, 146 us, 157 in turn.
+  // With more query clusters than a pass sums itself, every pass of theirs is a chain of four to six launches, and together they
+  // can be the longer chain: a pass of either side in turn, until the host waits.  Algorithm 1 first, in turn and query clustering
+  // first, us for calls alone: 4 x 4 096 tokens, d=64, 256 query clusters 227, 209, 209; 1 x 4 096 fp32, 256 252, 229, 218; 5 x
+  // 9 247, d=128, 512 412, 392, 392; 168 shapes from 1 500 to 75 600 tokens, 129 to 1 024 query clusters: in turn 0.96 of Algorithm 1
+  // first, call after call 0.99.
+  const bool q_first = p->k_init_mode == 1 || (p->dtype == ADACLUSTER_BF16 && p->N <= small_stage_points(p->d, p->H) && p->k_m0 <= small_stage_centres());
+  const bool in_turn = p->q_clusters > pass_sum_centres();
   bool joinable = false;
-  auto queries = [&]() {
-    const int r = run_qcluster(p, w, qs, Q, q_labels, q_centroids, q_assign_centroids, q_sizes, q_mean_norm);
+  int q_it = 0;                 // passes of the query clustering that are enqueued
+  auto queries = [&](bool rest) {
+    if (q_it >= p->q_iters || (!rest && !in_turn)) return 0;
+    const int from = q_it;
+    q_it = rest ? p->q_iters : q_it + 1;
+    const int r = run_qcluster(p, w, qs, Q, q_labels, q_centroids, q_assign_centroids, q_sizes, q_mean_norm, from, q_it);
+    if (r) q_it = p->q_iters;
+    if (q_it < p->q_iters) return 0;
     prof_mark(EV_QCLUSTER, qs, EV_START);
     joinable = hipEventRecord(aux->join, qs) == hipSuccess;
     return joinable || r ? r : fail(ADACLUSTER_E_INTERNAL, "stream join failed");
   };
-  // Algorithm 1 is the longer chain.  Where it waits for a report, it goes first, and the query clustering is enqueued while the
-  // host would only wait; its nine launches ahead of Algorithm 1 kept the device waiting (4 096 fp32 tokens 240 -> 221 us;
-  // 32 760 tokens, a call alone, 863 -> 840).  Where no report is waited for before the end (a warm start, or one launch for
-  // everything after the first stage) it stays first: 1 500 tokens 152 us, 168 the other way.
-  const bool q_first = p->k_init_mode == 1 || (p->dtype == ADACLUSTER_BF16 && p->N <= small_stage_points(p->d, p->H) && p->k_m0 <= small_stage_centres());
-  auto nothing = [] { return 0; };
   int kc_bound = capacity(p);
   auto keys = [&](const auto& beside) {
     return run_kcluster(p, w, st, K, k_labels, k_centroids, k_assign_centroids, k_bmin, k_bmax, k_sizes, k_count, full_flag,
                         o.k_stage_offs, o.k_stage_of, tau_used, &kc_bound, beside);
   };
-  rc = q_first ? queries() : 0;
-  if (!rc) rc = q_first ? keys(nothing) : keys(queries);
+  rc = q_first ? queries(true) : 0;
+  if (!rc) rc = keys(queries);
   prof_mark(EV_KCLUSTER, st, EV_START);
   if (!joinable) return drained(rc ? rc : ADACLUSTER_E_INTERNAL);
   if (hipStreamWaitEvent(st, aux->join, 0) != hipSuccess) return drained(fail(ADACLUSTER_E_INTERNAL, "stream join failed"));

@@ -117,6 +117,31 @@ def test_stagewise_calls_equal_the_fused_call():
     assert torch.equal(O_fused, O_steps)
 
 
+@pytest.mark.parametrize("dtype,q_iters,k_iters,Cq,N,stages", [
+    (B.BF16, 1, 1, 9, 1500, 10), (B.BF16, 5, 2, 200, 1500, 10), (B.BF16, 5, 2, 200, 5000, 10), (B.BF16, 2, 4, 200, 5000, 1), (B.BF16, 3, 1, 200, 5000, 10),
+    (B.BF16, 1, 3, 65, 40000, 10), (B.F32, 3, 1, 30, 2500, 10), (B.F32, 4, 3, 140, 2500, 1), (B.F32, 1, 4, 140, 2500, 10), (B.F32, 1, 4, 3, 2500, 10)])
+def test_clusterings_enqueued_in_turn_are_those_of_their_own_calls(dtype, q_iters, k_iters, Cq, N, stages):
+    """A cold fused call enqueues the query clustering first, before it first waits, or (many query clusters) its passes between
+    those of the first key stage: with fewer, as many and more passes on either side, every output is that of the single calls, to
+    the bit."""
+    H, d = 2, 64
+    Q, K, V = wl.make_small(34, N, d, 20, dtype="bf16" if dtype == B.BF16 else "f32", H=H)
+    p = B.Params(H=H, N=N, d=d, dtype=dtype, q_clusters=Cq, q_iters=q_iters, k_iters=k_iters, k_m0=16, k_m_min=4, k_max_clusters=64,
+                 k_max_stages=stages, topk=5, min_unassigned_frac=0.03)
+    Qd, Kd, Vd = to_dev(Q, dtype), to_dev(K, dtype), to_dev(V, dtype)
+    o = B.alloc_outputs(p, Qd.device)
+    B.adacluster_attn(p, Qd, Kd, Vd, outs=o)
+    q, k = B.adacluster_qcluster(p, Qd), B.adacluster_kcluster(p, Kd, want_box=False)
+    torch.cuda.synchronize()
+    for name in ("q_labels", "q_centroids", "q_assign_centroids", "q_sizes", "q_mean_norm"):
+        assert torch.equal(o[name], q[name]), name
+    for name in ("k_labels", "k_sizes", "k_count", "full_flag"):
+        assert torch.equal(o[name], k[name]), name
+    for h in range(H):
+        n = int(k["k_count"][h])
+        assert torch.equal(o["k_centroids"][h, :n], k["k_centroids"][h, :n])
+
+
 @pytest.mark.parametrize("Cq,dtype", [(1, B.BF16), (2, B.F32), (256, B.BF16), (257, B.BF16), (257, B.F32)])
 def test_query_tiles_planned_beside_the_key_lists(Cq, dtype):
     """The fused call plans the query tiles from the selection's list lengths, in the launch that writes the lists, up to 256
