@@ -263,8 +263,21 @@ __global__ __launch_bounds__(1024) void sort_small(const int32_t* __restrict__ l
                 offs + (size_t)h * offs_stride, poff ? poff + (size_t)h * offs_stride : nullptr, part_rows);
 }
 
+// LDS of a workgroup of label_scatter (two bytes a bin and wave; the waves' sums of two prefixes), and the most waves whose
+// counters stay within the 64 KB that a launch may ask for without further ado.  Bins of one launch: `stride`.
+constexpr int MAX_LABELS = 8000;
+constexpr int scatter_lds(int waves, int stride) { return 2 * waves * stride + 2 * waves * (int)sizeof(int32_t); }
+constexpr int most_waves(int stride) { return scatter_lds(16, stride) <= 65536 ? 16 : scatter_lds(8, stride) <= 65536 ? 8 : 4; }
+constexpr int label_bins(int m) { return (m + 1 + 63) / 64 * 64; }
+constexpr bool lds_fits() {
+  for (int m = 0; m <= MAX_LABELS; ++m)
+    if (scatter_lds(most_waves(label_bins(m)), label_bins(m)) > 65536 || 4 * label_bins(m) > 65536) return false;
+  return true;
+}
+static_assert(lds_fits(), "for every number of labels");
+
 int sort_segments(int N) { return (N + CS_ITEMS - 1) / CS_ITEMS; }
-size_t sort_table_ints(int N, int m) { return N <= SMALL_ITEMS ? 0 : (size_t)(sort_segments(N) + 1) * ((m + 1 + 63) / 64 * 64); }
+size_t sort_table_ints(int N, int m) { return N <= SMALL_ITEMS ? 0 : (size_t)(sort_segments(N) + 1) * label_bins(m); }
 int sort_scratch_ints(int N) { return min(N, SMALL_ITEMS); }
 
 int launch_sort(hipStream_t st, int H, int N, int n_bound, int m_bound,
@@ -284,27 +297,27 @@ int launch_sort(hipStream_t st, int H, int N, int n_bound, int m_bound,
     if (poff_done && poff) *poff_done = 1;
     return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
   }
-  const int nseg = sort_segments(n_bound), stride = (m_bound + 1 + 63) / 64 * 64;
+  const int nseg = sort_segments(n_bound), stride = label_bins(m_bound);
   // dynamic LDS for the bound, so that as many workgroups share a CU as it allows (7 169 bins: 57 KB)
-  if (m_bound > 8000) return ADACLUSTER_E_INTERNAL;
+  if (m_bound > MAX_LABELS) return ADACLUSTER_E_INTERNAL;
   auto sort = [&](auto waves, auto fold) {
     constexpr int W = decltype(waves)::value, NT = W * 64;
     constexpr bool FOLD = decltype(fold)::value;
     label_count<W><<<dim3(nseg, H), NT, stride * 4, st>>>(labels, N, a, m_dev, m_stride, m_bound, nseg, stride, sc.hist);
     if (!FOLD) label_columns<<<dim3(stride / 64, H), CC_WAVES * 64, 0, st>>>(a, m_dev, m_stride, m_bound, nseg, stride, sc.hist);
-    label_scatter<W, FOLD><<<dim3(nseg + 1, H), NT, stride * 2 * W + 64, st>>>(labels, ulist, N, a, m_dev, m_stride, m_bound, nseg, stride,
+    label_scatter<W, FOLD><<<dim3(nseg + 1, H), NT, 2 * W * stride, st>>>(labels, ulist, N, a, m_dev, m_stride, m_bound, nseg, stride,
                                                                              sc.hist, perm, offs, offs_stride, poff, part_rows, pcl, P);
   };
   // The prefix over the segments inside the scatter, each workgroup for itself, saves a launch (both sorts of the call above:
   // 5 x 9 000 tokens, 64 labels 50 -> 45 us, 12 x 32 760, 1 300 labels 77 -> 76) and reads nseg * stride counts a workgroup: past
   // some 22 000 of them, or 40 segments, the launch is the cheaper one (12 x 32 760, 5 000 labels 88 and 104; 24 x 180 000, 330
   // labels 869 and 884).  Sixteen waves, two items a lane, while that leaves every workgroup a CU to itself: 12 x 32 760, 330
-  // labels 75 -> 73, 5 x 9 000 41 -> 40; 48 x 32 760 the other way, 209 and 217.  Counters of every wave: past 4 096 bins eight
-  // waves' would not fit in the 64 KB of LDS that a launch may ask for freely.
+  // labels 75 -> 73, 5 x 9 000 41 -> 40; 48 x 32 760 the other way, 209 and 217.  And no more than have counters in LDS.
   using std::integral_constant;
-  if (stride > 4096) sort(integral_constant<int, 4>{}, std::false_type{});
+  const int waves = most_waves(stride);
+  if (waves == 4) sort(integral_constant<int, 4>{}, std::false_type{});
   else if (nseg > 40 || nseg * stride > 22000) sort(integral_constant<int, 8>{}, std::false_type{});
-  else if (nseg * H > 256 || stride > 2048) sort(integral_constant<int, 8>{}, std::true_type{});
+  else if (nseg * H > 256 || waves == 8) sort(integral_constant<int, 8>{}, std::true_type{});
   else sort(integral_constant<int, 16>{}, std::true_type{});
   if (poff_done && poff) *poff_done = pcl ? 2 : 1;
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;

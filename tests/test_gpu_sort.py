@@ -111,8 +111,9 @@ def test_key_clustering_around_the_change_of_the_sort(dtype, d, N, m0):
     check_kcluster(K, p, out, dtype)
 
 
-@pytest.mark.parametrize("H,N,cap", [(2, 9000, 100), (60, 9000, 63), (2, 24000, 1791), (2, 24000, 1792), (2, 4097, 2047), (2, 4097, 2048),
-                                     (2, 10240, 4095), (2, 10240, 4096), (2, 81920, 64), (2, 81921, 64)])
+@pytest.mark.parametrize("H,N,cap", [(2, 9000, 100), (60, 9000, 63), (2, 24000, 1791), (2, 24000, 1792), (2, 4097, 1983), (2, 4097, 1984),
+                                     (2, 4097, 2047), (2, 4097, 2048),
+                                     (2, 10240, 4031), (2, 10240, 4032), (2, 10240, 4095), (2, 10240, 4096), (2, 81920, 64), (2, 81921, 64)])
 def test_sort_with_the_prefix_in_the_scatter_and_in_a_launch(H, N, cap):
     """Sixteen, eight and four waves a segment, the prefix over the segments in the scatter or in a launch before it, on either
     side of every line between them; sampled rows of the first and the last head."""
