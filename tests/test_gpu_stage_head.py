@@ -1,6 +1,8 @@
 """The head of a stage of Algorithm 1 (filter of the stage before, new U, its strided sample) where its work is cut: lengths
 around the counted blocks (128, 256 and 1024 points), more blocks than threads, both dtypes.  With one assignment pass
 per stage the stage's centres are the strided sample itself, so they are compared exactly."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -8,7 +10,7 @@ import torch
 from oracle import adacluster_oracle as orc
 from paper_2604_18348_amd import binding as B
 from paper_2604_18348_amd import workloads as wl
-from tests.helpers import to_dev, to_np
+from tests.helpers import REL_TIE, to_dev, to_np
 from tests.test_gpu_cluster import check_stages_against_oracle
 
 pytestmark = pytest.mark.gpu
@@ -51,8 +53,9 @@ def test_stage_centres_are_the_strided_sample_of_what_was_left(dtype, d, N):
 @pytest.mark.parametrize("m", [31, 33, 64, 65, 97, 128])
 @pytest.mark.parametrize("d", [64, 128])
 def test_block_sums_around_the_changes_of_their_split(d, m):
-    """Up to 32 centres a block of 256 points leaves four rows of sums per centre, up to 64 two, then one: the first stage's
-    centres after one update, against the oracle's (bounds of check_stages_against_oracle with two passes)."""
+    """Up to 32 centres all waves of a workgroup share the points of a tile of centres, up to 64 two halves have a tile each, then
+    four quarters (eight waves where the next pass forms the centres, d=64 up to 64 here and d=128 up to 33, else four): the first
+    stage's centres after one update, against the oracle's (bounds of check_stages_against_oracle with two passes)."""
     H, N = 2, 2611
     _, K, _ = wl.make_small(40 + m, N, d, 20, dtype="bf16", H=H)
     p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=4, k_iters=2, k_m0=m, k_m_min=4, k_max_clusters=4 * m, tau_abs=0.6 * d ** 0.5)
@@ -63,8 +66,8 @@ def test_block_sums_around_the_changes_of_their_split(d, m):
 
 
 @pytest.mark.parametrize("d,N,m,iters", [(64, 512, 20, 2), (64, 513, 33, 2), (128, 511, 20, 2), (128, 1025, 40, 2),      # one, two, three blocks of 512
-                                         (64, 2560, 100, 2), (128, 2048, 60, 2),      # as much as is combined
-                                         (64, 2561, 100, 2), (128, 2049, 60, 2),      # and past it: a launch of its own
+                                         (64, 2560, 100, 2), (128, 2048, 60, 2),      # more centres than are combined:
+                                         (64, 2561, 100, 2), (128, 2049, 60, 2),      # a launch of its own forms them
                                          (64, 700, 20, 1), (64, 700, 20, 4), (128, 700, 20, 4)])       # no update, three
 def test_stage_centres_combined_by_the_next_pass(d, N, m, iters):
     """Where a head's member sums are few, the next pass forms the centres itself.  Head 1 is m runs of near rows, two of
@@ -94,6 +97,54 @@ def test_stage_centres_combined_by_the_next_pass(d, N, m, iters):
         for h in (0, 2):
             _, ref, _ = orc.euclid_kmeans(K[h].astype(np.float64), m, iters, round_fn=orc.round_to_bf16)
             assert float((C[h, :m] == ref).mean()) > 0.8
+
+
+def next_pass_forms_the_centres(d, H, N, m):
+    blocks = -(-N // 512)
+    return blocks * m * d * 4 <= 128 << 10 and m <= (64 if d == 64 else 40) and blocks * H <= 512
+
+
+@pytest.mark.parametrize("iters", [2, 3, 4])
+@pytest.mark.parametrize("d,H,N,m,combined", [
+    (64, 3, 512, 64, True), (64, 3, 512, 65, False), (128, 3, 512, 40, True), (128, 3, 512, 41, False),          # centres
+    (64, 3, 4096, 64, True), (64, 3, 4097, 64, False), (128, 3, 3072, 40, True), (128, 3, 3073, 40, False),      # 128 KB of sums
+    (64, 3, 8192, 30, True), (64, 3, 8193, 30, True), (64, 3, 9217, 30, False), (128, 3, 8000, 16, True),        # sixteen blocks, and more
+    (64, 512, 512, 20, True), (64, 513, 512, 20, False), (128, 256, 513, 20, True), (128, 257, 513, 20, False)])     # workgroups
+def test_each_update_on_either_side_of_the_combining(d, H, N, m, combined, iters):
+    """The centres of the last pass are the rounded member means over the labels to those of the pass before, which a call
+    with one pass fewer gives: every update is checked by itself, so that from the second on the two tables of sums have taken
+    turns.  Within a rounding of the means, equal but for a few of their entries."""
+    assert next_pass_forms_the_centres(d, H, N, m) == combined
+    _, K, _ = wl.make_small(70 + m, N, d, 14, dtype="bf16", H=3)
+    Kd = to_dev(K, B.BF16)[torch.arange(H) % 3].contiguous()
+    p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=4, k_iters=iters, k_m0=m, k_m_min=min(m, 12), k_max_clusters=4 * m, k_max_stages=1,
+                 tau_abs=0.6 * d ** 0.5)
+    got = B.adacluster_kcluster(p, Kd)["k_assign_centroids"][:, :m]
+    prev = B.adacluster_kcluster(dataclasses.replace(p, k_iters=iters - 1), Kd)["k_assign_centroids"][:, :m]
+    assert torch.equal(got, got[:3][torch.arange(H) % 3])
+    for h in range(3):
+        X, C0, C = K[h].astype(np.float64), to_np(prev[h]), to_np(got[h])
+        if iters == 2:
+            assert np.array_equal(C0, X[orc.strided_indices(N, m)])
+        G = (C0 * C0).sum(1)[None] - 2.0 * X @ C0.T
+        order = np.argsort(G, axis=1, kind="stable")[:, :2]
+        near = np.take_along_axis(G, order, 1)
+        tied = near[:, 1] - near[:, 0] <= REL_TIE * ((X * X).sum(1) + (C0 * C0).sum(1)[order[:, 0]])
+        count = np.bincount(order[:, 0], minlength=m)
+        ref = C0.copy()
+        for j in np.flatnonzero(count):
+            ref[j] = orc.round_to_bf16(X[order[:, 0] == j].mean(0))
+        bound = 2.0 ** -7 * np.maximum(np.abs(ref), np.abs(C))      # fp32 against fp64 sums on different sides of a rounding boundary
+        strict = np.ones(m, dtype=bool)
+        for j in np.unique(order[tied]):
+            # a point within rounding of two centres may join or leave either: x moves a mean of n by (x - mean) / n, of k
+            # such points the n - k others stay
+            x = X[tied & (order == j).any(1)]
+            bound[j] += np.abs(x - ref[j]).sum(0) / max(1, count[j] - len(x))
+            strict[j] = False
+        assert np.all(np.abs(C - ref) <= bound)
+        # (every centre has its bound above; equality is asked of those without such points, of any number)
+        assert not strict.any() or float((C == ref)[strict].mean()) > 0.97
 
 
 @pytest.mark.parametrize("d,H,N,iters", [(64, 1, 4000, 3), (64, 70, 4000, 3), (128, 72, 5000, 3), (128, 60, 5000, 3),
