@@ -180,7 +180,7 @@ struct Layout {
 struct WS {
   unsigned char* base;
   KState* kstate; KState* kstate2; int32_t* summary; float* tau;
-  void* cent_lp; float* bias; float* master;
+  void* cent_lp; float* bias;
   int32_t* labels_tmp; float* dist2; int32_t* ulist[2]; int32_t* blockcnt; double* tau_part;
   SortScratch sort; int32_t* perm_tmp; int32_t* offs_tmp; int32_t* poff; int32_t* pcl; int32_t* lab0; float* score0;
   float* psum; float* pnorm; float* pmin; float* pmax; int32_t* bcnt; float* bsum;
@@ -241,7 +241,6 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(tau, float*, 64);
   TAKE(cent_lp, void*, H * D.capmax * d * es);
   TAKE(bias, float*, H * D.capmax * 4);
-  TAKE(master, float*, H * (size_t)(p->k_m0 > D.Cq ? p->k_m0 : D.Cq) * d * 4);
   TAKE(labels_tmp, int32_t*, H * N * 4);
   TAKE(dist2, float*, H * N * 4);
   TAKE(ulist[0], int32_t*, H * N * 4);
@@ -441,7 +440,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     if (t > 0) { KState* x = cur; cur = other; other = x; }
     RET_IF(launch_stage_open(st, p->dtype, D.d, D.H, D.N, D.cap, p->k_max_clusters, p->k_m0, p->k_m_min, p->k_max_stages,
                              u_min, n_bound, m_bound, other, cur, t > 0 ? &filter : nullptr, w.summary,
-                             t > 0 ? rb->dev + 4 * t : nullptr, rb->epoch, p->k_m0, K, w.master, w.cent_lp, k_assign, w.bias));
+                             t > 0 ? rb->dev + 4 * t : nullptr, rb->epoch, K, w.cent_lp, k_assign, w.bias));
     pending = t;
     if (t > 1) {
       PASS_ON(beside(true));
@@ -501,8 +500,8 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       }
       if (block_sums && update) {
         RET_IF(launch_stage_pass(st, D.d, D.H, D.N, n_bound, m_bound, D.cap, cur, ul, K, w.cent_lp, k_assign, w.bias, false, nullptr, &sums[0]));
-        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, m_bound * nblk, D.cap, p->k_m0, cur, 0, 1, 0,
-                               nullptr, 0, nullptr, w.bsum, w.pnorm, w.pmin, w.pmax, w.master, w.cent_lp,
+        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, m_bound * nblk, D.cap, 0, cur, 0, 1, 0,
+                               nullptr, 0, nullptr, w.bsum, w.pnorm, w.pmin, w.pmax, nullptr, w.cent_lp,
                                k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.bcnt, nblk));
         continue;
       }
@@ -514,7 +513,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                            !update && t > 0 ? w.blockcnt : nullptr, D.ncnt, !update && t == 0 ? dist_sum : nullptr));
       if (update && direct_update_fits(p->dtype, n_bound, m_bound)) {
         // few points (fp32): every centre gathers its members from the label list itself, one launch
-        RET_IF(launch_update_direct(st, D.d, D.H, D.N, m_bound, D.cap, p->k_m0, cur, w.labels_tmp, ul, K, w.master,
+        RET_IF(launch_update_direct(st, D.d, D.H, D.N, m_bound, D.cap, 0, cur, w.labels_tmp, ul, K, nullptr,
                                     w.cent_lp, k_assign, w.bias));
       } else if (update) {
         RET_IF(launch_sort(st, D.H, D.N, n_bound, m_bound, w.labels_tmp, ul, &cur->ucount,
@@ -522,8 +521,8 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                            sizeof(KState) / 4, w.perm_tmp, w.offs_tmp, D.capmax + 1, w.sort, w.poff, reduce_part_rows(), w.pcl, P, &poff_done));
         RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, 1, 0, m_bound, P, cur, 0, 0, K, w.perm_tmp,
                                  w.offs_tmp, D.capmax + 1, w.poff, w.pcl, w.psum, w.pnorm, w.pmin, w.pmax, poff_done));
-        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, P, D.cap, p->k_m0, cur, 0, 1, 0,
-                               w.offs_tmp, D.capmax + 1, w.poff, w.psum, w.pnorm, w.pmin, w.pmax, w.master, w.cent_lp,
+        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, P, D.cap, 0, cur, 0, 1, 0,
+                               w.offs_tmp, D.capmax + 1, w.poff, w.psum, w.pnorm, w.pmin, w.pmax, nullptr, w.cent_lp,
                                k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr));
       }
     }

@@ -1161,10 +1161,10 @@ __global__ __launch_bounds__(256) void attn_merge_f32(AttnArgs a, int splits) {
 // ------------------------------------------------------------------------------------------
 // merge of the chunks of cut key lists
 // ------------------------------------------------------------------------------------------
-// One workgroup per cut query tile: O = sum_s 2^((m_s - m) scale) O_s / sum_s 2^((m_s - m) scale) l_s
+// O = sum_s 2^((m_s - m) scale) O_s / sum_s 2^((m_s - m) scale) l_s for every row of the cut query tiles,
 // with m = max_s m_s; a chunk always holds at least one key, so every m_s is finite and l_s > 0.
-// MERGE_GROUPS workgroups a head and row group: mostly there is little or nothing to merge, and one for every slot, 15 360 for
-// 30 heads, took 5 us to find that out.
+// MERGE_GROUPS workgroups a head and row group go over the tiles: mostly there is little or nothing to merge, and one for every
+// slot, 15 360 for 30 heads, took 5 us to find that out.
 constexpr int MERGE_GROUPS = 16;
 template <int D>
 __global__ __launch_bounds__(256) void attn_merge(AttnArgs a, const int32_t* __restrict__ merge,

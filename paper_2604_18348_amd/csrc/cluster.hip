@@ -1243,7 +1243,7 @@ __global__ __launch_bounds__(256) void seg_reduce_few(const float* __restrict__ 
 }
 
 // Combine the parts and write centres.
-//   update_assign = 1 (Lloyd step): non-empty clusters get master := mean (or unit mean), the
+//   update_assign = 1 (Lloyd step): non-empty clusters get master := mean (or unit mean), where it is kept, the
 //     I/O-dtype copy used by the next assignment, its fp32 image and the arg-max bias.
 //   update_assign = 0 (final): out_cent := mean / unit mean (empty: `fallback` row), sizes, mean
 //     norms, boxes.  `master` is also refreshed when given (query clustering returns it).
@@ -1375,7 +1375,7 @@ __global__ __launch_bounds__(64 * FIN_ROWS) void finalize_centroids(FinalizeCfg 
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
       const int col = lane + 64 * q;
-      master[((size_t)h * cfg.master_stride + j) * D + col] = val[q];
+      if (master) master[((size_t)h * cfg.master_stride + j) * D + col] = val[q];
       const size_t ao = ((size_t)h * cfg.cap + row_off + j) * D + col;
       float img = val[q];
       if (cfg.lp_is_bf16) {
@@ -1505,7 +1505,7 @@ __global__ __launch_bounds__(256) void update_direct_f32(const float* __restrict
   }
   const float cntf = (float)total;
   const float4 val = {sum.x / cntf, sum.y / cntf, sum.z / cntf, sum.w / cntf};
-  *reinterpret_cast<float4*>(master + ((size_t)h * master_stride + j) * D + cl * 4) = val;
+  if (master) *reinterpret_cast<float4*>(master + ((size_t)h * master_stride + j) * D + cl * 4) = val;
   const size_t ao = ((size_t)h * cap + row_off + j) * D + cl * 4;
   *reinterpret_cast<float4*>(assign_lp + ao) = val;
   *reinterpret_cast<float4*>(assign_f32 + ao) = val;
@@ -1669,7 +1669,7 @@ struct OpenCfg {
   const float* dist2; const float* tau; const int32_t* cnt;
   const int32_t* uin; int32_t* uout; int32_t* stage_of; int stage;      // `stage`: the one that ends
   int32_t* sums; int32_t* report; int epoch;   // [4] device counters, zero between launches (`first` clears them); host slot
-  int master_stride; float* master; void* lp; float* f32; float* bias;
+  void* lp; float* f32; float* bias;
 };
 
 template <typename T, int D>
@@ -1835,7 +1835,6 @@ __global__ __launch_bounds__(256) void stage_open(const T* __restrict__ X, OpenC
     const T raw = row[col];
     const float v = Elem<T>::load(&raw);
     const size_t ao = ((size_t)h * c.cap + s.ccount + j) * D + col;
-    c.master[((size_t)h * c.master_stride + j) * D + col] = v;
     reinterpret_cast<T*>(c.lp)[ao] = raw;
     c.f32[ao] = v;
     bsum = fmaf(v, v, bsum);
@@ -2463,14 +2462,14 @@ int launch_keep_count(hipStream_t s, const KState* st, int H, int N, const float
 
 int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, int n_max, int m0, int m_min, int max_stages,
                       int u_min, int n_bound, int m_bound, const KState* in, KState* out, const StageFilter* f,
-                      int32_t* sums, int32_t* report, int epoch, int master_stride, const void* X, float* master,
-                      void* assign_lp, float* assign_f32, float* bias) {
+                      int32_t* sums, int32_t* report, int epoch, const void* X, void* assign_lp,
+                      float* assign_f32, float* bias) {
   OpenCfg c{};
   c.N = N; c.cap = cap; c.n_max = n_max; c.m0 = m0; c.m_min = m_min; c.max_stages = max_stages; c.u_min = u_min;
   c.first = f == nullptr;
   c.items = KEEP_ITEMS;
   c.in = in; c.out = out; c.sums = sums; c.report = report; c.epoch = epoch;
-  c.master_stride = master_stride; c.master = master; c.lp = assign_lp; c.f32 = assign_f32; c.bias = bias;
+  c.lp = assign_lp; c.f32 = assign_f32; c.bias = bias;
   if (f) {
     if (f->items > KEEP_ITEMS) return ADACLUSTER_E_INTERNAL;
     c.items = f->items; c.nblk = (n_bound + f->items - 1) / f->items; c.cnt_stride = f->cnt_stride;

@@ -99,8 +99,8 @@ int launch_keep_count(hipStream_t s, const KState* st, int H, int N, const float
 // NULL): {active heads, max |U|, max m_t, epoch}, the epoch behind the rest.
 int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, int n_max, int m0, int m_min, int max_stages,
                       int u_min, int n_bound, int m_bound, const KState* in, KState* out, const StageFilter* f,
-                      int32_t* sums, int32_t* report, int epoch, int master_stride, const void* X, float* master,
-                      void* assign_lp, float* assign_f32, float* bias);
+                      int32_t* sums, int32_t* report, int epoch, const void* X, void* assign_lp,
+                      float* assign_f32, float* bias);
 // Every remaining stage of Algorithm 1 in one launch, one workgroup per head (bf16 only).  Valid once every
 // active head has at most small_stage_points() unassigned points and small_stage_centres() centres per
 // stage, and never for stage 0 (it needs a list of U and a known tau).
