@@ -2304,7 +2304,7 @@ static bool assign_f32_rows(int d, long long points, int m) {
   const int t = m <= 32 ? 0 : m <= 64 ? 1 : 2;         // one tile, two, three
   struct Line { long long points; int most[3]; };      // from so many points on: most centres for assign_rows
   static constexpr Line d64[] = {{1000000, {26, 64, 96}}, {200000, {21, 60, 84}}, {150000, {17, 49, 67}}, {100000, {12, 35, 0}}, {20000, {4, 0, 0}}};
-  static constexpr Line d128[] = {{500000, {32, 36, 0}}, {55000, {20, 0, 0}}, {20000, {6, 0, 0}}};
+  static constexpr Line d128[] = {{500000, {32, 36, 0}}, {50000, {20, 0, 0}}, {20000, {6, 0, 0}}};
   auto most = [&](const auto& lines) { for (const Line& l : lines) if (points >= l.points) return l.most[t]; return 0; };
   return m <= (d == 64 ? most(d64) : most(d128));
 }
