@@ -287,7 +287,7 @@ int adacluster_quest_scores(int32_t H, int32_t Lq, int32_t Lk, int32_t d, int32_
  * attention kernel, and the segmented reduction over all N keys that ends Algorithm 1 (one launch,
  * also counted inside Algorithm 1); -1 for a stage the call did not run.  In adacluster_attn the two clusterings
  * run side by side and each is timed from the start of the call, so their sum exceeds the time
- * the pair takes.  Not thread-safe.
+ * the pair takes, and the one that is enqueued second counts its wait.  Not thread-safe.
  */
 int adacluster_profile_enable(int on);
 
