@@ -164,7 +164,6 @@ int check_params(const adacluster_params* p) {
   return 0;
 }
 
-constexpr int STAGE_SUM_BLOCKS = 128;   // a stage of at most this many blocks of pass_points(false) may update from their sums
 
 inline int capacity(const adacluster_params* p) { return p->k_max_clusters + p->k_m0; }
 inline size_t esize(const adacluster_params* p) { return p->dtype == ADACLUSTER_BF16 ? 2 : 4; }
@@ -355,7 +354,7 @@ int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       RET_IF(launch_qpass(st, D.d, D.H, D.N, D.Cq, D.Cq, sph, Q, w.q_cent_lp, w.q_bias, w.q_wsum, w.q_wcnt));
       RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 0, D.Cq, D.Cq, D.Cq * NP, D.Cq, D.Cq, nullptr, sph, 1, 0, nullptr, 0,
                              nullptr, w.q_wsum, w.q_pnorm, nullptr, nullptr, q_centroids, w.q_cent_lp, q_assign, w.q_bias,
-                             nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.q_wcnt, NP, NP));
+                             nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.q_wcnt, NP));
       continue;
     }
     RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, D.Cq, 0, D.Cq, D.Cq, nullptr, nullptr, Q, w.q_cent_lp, w.q_bias,
@@ -433,15 +432,25 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   rb = stage_readback();
   if (!rb) return fail(ADACLUSTER_E_INTERNAL, "stage read-back set-up failed: %s", hipGetErrorString(hipGetLastError()));
   int n_bound = D.N, m_bound = p->k_m0 < D.N ? p->k_m0 : D.N, heads = D.H;
+  const StageRules rules{p->k_max_clusters, p->k_m0, p->k_m_min, p->k_max_stages, u_min};
   KState* other = w.kstate2;                       // the stage head reads one and writes the other
   StageFilter filter{};                            // how the stage before ended
+  // Stages with few blocks of points and few centres (bf16) update from block sums; they are opened by their own first pass,
+  // from the survivors that the stage before left as a list (filter.surv; the first stage: every token).
+  auto sums_fit = [&] {
+    return p->dtype == ADACLUSTER_BF16 && (n_bound + pass_points(false) - 1) / pass_points(false) <= STAGE_SUM_BLOCKS && m_bound <= pass_sum_centres();
+  };
   for (int t = 0; t <= p->k_max_stages; ++t) {
+    const bool pass_opens = t == 0 ? sums_fit() : filter.surv && t < p->k_max_stages;      // (bounds never grow: sums_fit() holds again)
+    const int n_before = n_bound;
     // the stage head writes its report straight into the pinned slot (no copy in between)
-    if (t > 0) { KState* x = cur; cur = other; other = x; }
-    RET_IF(launch_stage_open(st, p->dtype, D.d, D.H, D.N, D.cap, p->k_max_clusters, p->k_m0, p->k_m_min, p->k_max_stages,
-                             u_min, n_bound, m_bound, other, cur, t > 0 ? &filter : nullptr, w.summary,
-                             t > 0 ? rb->dev + 4 * t : nullptr, rb->epoch, K, w.cent_lp, k_assign, w.bias));
-    pending = t;
+    const StageReport report{w.summary, t > 0 ? rb->dev + 4 * t : nullptr, rb->epoch};
+    if (!pass_opens) {
+      if (t > 0) { KState* x = cur; cur = other; other = x; }
+      RET_IF(launch_stage_open(st, p->dtype, D.d, D.H, D.N, D.cap, rules, n_bound, m_bound, other, cur, t > 0 ? &filter : nullptr, report,
+                               K, w.cent_lp, k_assign, w.bias));
+      pending = t;
+    }
     if (t > 1) {
       PASS_ON(beside(true));
       if (!stage_report_landed(*rb, t - 1, st))
@@ -452,8 +461,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     }
     if (t > 0) kc_bound += m_bound;
     if (t == p->k_max_stages) break;           // the stage head has just closed every head
-    if (t == 1 && !(p->dtype == ADACLUSTER_BF16 && (n_bound + 255) / 256 <= STAGE_SUM_BLOCKS &&
-                    m_bound <= pass_sum_centres())) {
+    if (t == 1 && !sums_fit()) {
       // Stage 0 removes most points, so its figures (all N points, m_0 centres) are poor bounds for
       // stage 1: unless they still allow the short update (block sums), they would send a few thousand
       // points through the launch chain sized for all of them (label sort, segmented
@@ -469,9 +477,8 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     if (t > 0 && p->dtype == ADACLUSTER_BF16 && n_bound <= small_stage_points(D.d, heads) && m_bound <= small_stage_centres()) {
       // few points and few centres left in every head: one launch runs this and every later stage
       // (|U|, m_t and the active heads never grow, so the bounds hold for all of them)
-      RET_IF(launch_kstages_small(st, D.d, D.H, D.N, D.cap, p->k_max_clusters, p->k_m0, p->k_m_min, p->k_max_stages,
-                                  u_min, p->k_iters, cur, w.tau, w.ulist[0], w.ulist[1], K, w.cent_lp, k_assign,
-                                  w.bias, k_stage_of));
+      RET_IF(launch_kstages_small(st, D.d, D.H, D.N, D.cap, rules, p->k_iters, cur, w.tau, w.ulist[0], w.ulist[1], K, w.cent_lp, k_assign,
+                                  w.bias, k_stage_of, pass_opens ? &filter : nullptr, n_before));
       kc_bound += m_bound * (p->k_max_stages - t);
       break;
     }
@@ -480,29 +487,31 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     const int P = parts_for(n_bound, m_bound);
     // A small stage (few blocks of points, few centres) updates its centres from the member sums that a pass leaves per
     // block: no label sort and no segmented reduction in between, and where all of them together are small no launch either.
-    const int nblk = (n_bound + pass_points(false) - 1) / pass_points(false);
-    const bool block_sums = p->dtype == ADACLUSTER_BF16 && nblk <= STAGE_SUM_BLOCKS && m_bound <= pass_sum_centres();
+    const bool block_sums = sums_fit();
     const bool combine = block_sums && combine_fits(D.d, heads, n_bound, m_bound);
-    const int wblk = (n_bound + pass_points(true) - 1) / pass_points(true);
-    const StageSums sums[2] = {{w.bsum, w.bcnt}, {w.bsum + (size_t)D.H * m_bound * wblk * D.d, w.bcnt + (size_t)D.H * wblk * pass_sum_centres()}};
-    int counted = stage_points_per_count(p->dtype);          // points per survivor count and distance sum of the last pass
+    const bool wide = combine || (block_sums && wide_fills(heads, n_bound));
+    const int nblk = (n_bound + pass_points(wide) - 1) / pass_points(wide);
+    const StageSums sums[2] = {{w.bsum, w.bcnt}, {w.bsum + (size_t)D.H * m_bound * nblk * D.d, w.bcnt + (size_t)D.H * nblk * pass_sum_centres()}};
+    const int counted = block_sums ? pass_points(wide) : stage_points_per_count(p->dtype);      // points per survivor count and distance sum of the last pass
+    // (a stage of block sums has no other use for the array; a single pass would read and write it)
+    int32_t* const surv = block_sums && p->k_iters > 1 ? w.labels_tmp : nullptr;
+    if (pass_opens && t > 0) { KState* x = cur; cur = other; other = x; }
+    const StageOpening opening{&rules, other, cur, t > 0 ? &filter : nullptr, &report, n_before};
+    if (pass_opens) pending = t;
     for (int it = 0; it < p->k_iters; ++it) {
       if (t == 0 && it > 0) PASS_ON(beside(false));
       const bool update = it < p->k_iters - 1;
       const bool keep = seeded && t == 0 && !update;
-      if (combine) {
-        RET_IF(launch_stage_pass(st, D.d, D.H, D.N, n_bound, m_bound, D.cap, cur, ul, K, w.cent_lp, k_assign, w.bias, true,
-                                 it > 0 ? &sums[(it - 1) & 1] : nullptr, update ? &sums[it & 1] : nullptr, update ? nullptr : w.dist2,
-                                 keep ? w.lab0 : nullptr, keep ? w.score0 : nullptr, w.tau, !update && t > 0 ? w.blockcnt : nullptr,
-                                 D.ncnt, !update && t == 0 ? dist_sum : nullptr));
-        counted = pass_points(true);
-        continue;
-      }
-      if (block_sums && update) {
-        RET_IF(launch_stage_pass(st, D.d, D.H, D.N, n_bound, m_bound, D.cap, cur, ul, K, w.cent_lp, k_assign, w.bias, false, nullptr, &sums[0]));
-        RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, m_bound * nblk, D.cap, 0, cur, 0, 1, 0,
-                               nullptr, 0, nullptr, w.bsum, w.pnorm, w.pmin, w.pmax, nullptr, w.cent_lp,
-                               k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.bcnt, nblk));
+      if (block_sums) {
+        const PassEnd end{w.dist2, keep ? w.lab0 : nullptr, keep ? w.score0 : nullptr, t == 0 ? dist_sum : nullptr,
+                          w.tau, t > 0 ? w.blockcnt : nullptr, D.ncnt, surv, k_stage_of, t};
+        RET_IF(launch_stage_pass(st, D.d, D.H, D.N, n_bound, m_bound, D.cap, cur, ul, K, w.cent_lp, k_assign, w.bias, wide,
+                                 combine && it > 0 ? &sums[(it - 1) & 1] : nullptr, update ? &sums[combine ? it & 1 : 0] : nullptr,
+                                 update ? nullptr : &end, pass_opens && it == 0 ? &opening : nullptr));
+        if (update && !combine)
+          RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, m_bound * nblk, D.cap, 0, cur, 0, 1, 0,
+                                 nullptr, 0, nullptr, w.bsum, w.pnorm, w.pmin, w.pmax, nullptr, w.cent_lp,
+                                 k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.bcnt, nblk, pass_points(wide)));
         continue;
       }
       // (the last pass of stage 0 runs over all points against the first-stage centres as they will stay:
@@ -526,9 +535,9 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
                                k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr));
       }
     }
-    filter = StageFilter{w.dist2, w.tau, w.blockcnt, D.ncnt, counted, ul, ul_next, k_stage_of, t};
+    filter = StageFilter{w.dist2, w.tau, w.blockcnt, D.ncnt, counted, ul, ul_next, k_stage_of, t, surv};
     if (t == 0) RET_IF(launch_keep_count(st, cur, D.H, D.N, w.dist2, dist_sum, (D.N + counted - 1) / counted, p->tau_factor, w.tau, w.blockcnt,
-                                         D.ncnt, &filter.items));
+                                         D.ncnt, surv, k_stage_of, &filter.items));
   }
   PASS_ON(beside(true));
   kc_bound = kc_bound < D.cap ? kc_bound : D.cap;

@@ -8,6 +8,8 @@
 #include "common.h"
 #include "launch.h"
 
+#include <type_traits>
+
 namespace adac {
 
 // ------------------------------------------------------------------------------------------
@@ -31,6 +33,8 @@ struct AssignCfg {
   double* dist_sum;                                       // sum of the distances of this workgroup's points (the first stage's last
                                                           // pass, for tau): dist_sum[h * gridDim.x + workgroup]
                                                           // (assign_rows: of this wave's points, for both)
+  int32_t* surv; int32_t* stage_of; int stage;            // stage_pass, with keep_cnt (or NULL): the survivors themselves, from where the
+                                                          // workgroup's points start, and the stage of the points that leave U
 };
 constexpr int PASS_POINTS = 256;        // points of a workgroup of stage_pass (twice that where it combines)
 constexpr int ASSIGN_POINTS_LP = 256, ASSIGN_POINTS_F32 = 64;     // points of an assignment workgroup
@@ -271,6 +275,90 @@ __global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict_
 }
 
 // ------------------------------------------------------------------------------------------
+// Opening a stage of Algorithm 1: what stage_open, the opening form of stage_pass and kstages_small share
+// ------------------------------------------------------------------------------------------
+struct OpenCfg {
+  int N, cap, n_max, m0, m_min, max_stages, u_min;
+  int first;                       // the first stage opens: no filter, U is every token (`in` is not read)
+  int items, nblk, cnt_stride;     // points per count; workgroups that move survivors
+  const KState* in; KState* out;
+  const float* dist2; const float* tau; const int32_t* cnt;
+  const int32_t* uin; int32_t* uout; const int32_t* surv; int32_t* stage_of; int stage;      // `stage`: the one that ends
+  int32_t* sums; int32_t* report; int epoch;   // [4] device counters, zero between launches (`first` clears them); host slot
+  void* lp; float* f32; float* bias;
+};
+
+struct NewState { int ucount, ccount, m_t, stage, done, full, active; };      // a state without its tables
+
+// Head of the while-loop: done?  flag F?  else the number of centres.
+__device__ __forceinline__ void loop_head(NewState& s, int N, int n_max, int m0, int m_min, int max_stages, int u_min) {
+  if (s.ucount == 0) s.done = 1;
+  else if (s.ccount >= n_max) { s.full = 1; s.done = 1; }
+  else if (s.stage >= max_stages || s.ucount <= u_min) s.done = 1;
+  s.active = !s.done;
+  if (s.active) {
+    const int m = (int)(((long long)m0 * s.ucount + N - 1) / N);
+    s.m_t = min(max(m_min, min(m0, m)), s.ucount);
+  } else s.m_t = 0;
+}
+
+// By one thread of a head: the last head to report writes {active heads, max |U|, max m_t, epoch} to the host's slot.
+__device__ __forceinline__ void report_stage(const OpenCfg& c, const NewState& s, bool act) {
+  if (!c.report) return;
+  if (act) { atomicAdd(&c.sums[0], 1); atomicMax(&c.sums[1], s.ucount); atomicMax(&c.sums[2], s.m_t); }
+  __threadfence();
+  if (atomicAdd(&c.sums[3], 1) == (int)gridDim.y - 1) {
+    __threadfence();
+    for (int i = 0; i < 3; ++i) c.report[i] = atomicExch(&c.sums[i], 0);
+    atomicExch(&c.sums[3], 0);
+    __hip_atomic_store(&c.report[3], c.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);     // (the host polls this word)
+  }
+}
+
+// By the first workgroup of a head: the state of a head that was closed before goes on as it is ...
+__device__ __forceinline__ void carry_state(const OpenCfg& c, int h, int tid) {
+  if (tid < (int)(sizeof(KState) / 4)) reinterpret_cast<int32_t*>(&c.out[h])[tid] = reinterpret_cast<const int32_t*>(&c.in[h])[tid];
+  if (tid == 0) report_stage(c, NewState{}, false);
+}
+// ... and the new state of one that was not is written and reported.
+__device__ __forceinline__ void write_state(const OpenCfg& c, int h, int tid, const NewState& s) {
+  if (tid == 0) {
+    KState& o = c.out[h];
+    o.ucount = s.ucount; o.ccount = s.ccount; o.m_t = s.m_t; o.stage = s.stage; o.done = s.done; o.full = s.full;
+    o.active = s.active; o.pad = 0;
+    report_stage(c, s, s.active);
+  }
+  if (tid <= ADACLUSTER_MAX_STAGES) {
+    const int i = tid;
+    c.out[h].stage_offs[i] = c.first ? 0 : i == s.stage ? s.ccount : c.in[h].stage_offs[i];
+    c.out[h].u_hist[i] = c.first ? (i == 0 ? c.N : 0) : i == s.stage ? s.ucount : c.in[h].u_hist[i];
+  }
+}
+
+// Survivors by position: the last pass of a stage left them, in order, from the start of every `items` points on, and their
+// counts.  OPEN_COUNTS counts at most; called by a whole workgroup of at least as many threads, cnt_mine the thread's count.
+constexpr int OPEN_COUNTS = STAGE_SUM_BLOCKS;
+__device__ __forceinline__ void survivor_prefix(int nb, int cnt_mine, int32_t* pre /* LDS, [OPEN_COUNTS + 1] */) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  static_assert(OPEN_COUNTS == 128, "two waves");
+  int incl = tid < nb ? cnt_mine : 0;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
+  if (tid == 0) pre[0] = 0;
+  if (tid < OPEN_COUNTS) pre[tid + 1] = incl;
+  __syncthreads();
+  const int first = pre[64];
+  __syncthreads();
+  if (tid >= 64 && tid < OPEN_COUNTS) pre[tid + 1] = incl + first;
+  __syncthreads();
+}
+__device__ __forceinline__ int survivor_at(const int32_t* pre, int nb, int items, int p) {      // where in the list of a head survivor p is
+  int lo = 0, hi = nb - 1;
+  while (lo < hi) { const int mid = (lo + hi + 1) >> 1; if (pre[mid] <= p) lo = mid; else hi = mid - 1; }
+  return lo * items + p - pre[lo];
+}
+
+// ------------------------------------------------------------------------------------------
 // A pass of a stage of Algorithm 1 with at most ACC_MAXM centres (bf16): assignment and member sums together.
 // ------------------------------------------------------------------------------------------
 // A workgroup is NW waves of 64 points.  The scores and their in-lane arg-max are those of assign_mfma, the centres all in
@@ -285,19 +373,48 @@ __global__ __launch_bounds__(256, 2) void assign_mfma(const bf16raw* __restrict_
 // points, d=128, two passes and two launches between them, 9.5 + 6 us each, are two of 12 and 14, and the last pass with its
 // launch, 6 + 5.5, one of 10; a call of 12 x 32 760 tokens 880 -> 863 us, of 5 x 9 247 tokens 572 -> 561.  (With the sums and
 // the list of points asked for ahead of the state the same; sixteen sums in flight at d=64 spill: 13 -> 25 us.)
+// OPEN: the first pass of a stage does what stage_open does, in its place.  The last pass of the stage before (keep_count behind
+// the first stage) has left its survivors as a list, from the start of every `items` points on, with their counts: every
+// workgroup sums the counts, knows |U|, the loop's decision and m_t, and finds its points and the centres by position.  Latency
+// bound: two trips to the L2 more than a pass whose list and centres lie ready, where the launch had five (30 x 5 000 points,
+// d=64: 8 + 8.5 -> 12 us; key clusterings of 30 x 7 920 tokens 170 -> 153 us, 12 x 25 500 208 -> 198, 30 x 17 776 570 -> 550).
 struct PassSums { float* psum; int32_t* bcnt; int P; int nb_stride; };
-template <int D, int NW, bool COMBINE>
+enum PassCentres { PASS_READ, PASS_COMBINE, PASS_OPEN };
+template <int D, int NW, int FORM>
 __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf16raw* __restrict__ X, AssignCfg cfg, bf16raw* __restrict__ cent,
                                                       float* __restrict__ cent_f32, float* __restrict__ bias,
-                                                      float* __restrict__ dist2, PassSums prev, PassSums out) {
+                                                      float* __restrict__ dist2, PassSums prev, PassSums out, OpenCfg oc) {
   constexpr int KS = D / 16, PB = 2, CROWB = D * 2, CH = D / 8, DT = D / 32, NT = NW * 64;
   const int h = blockIdx.y;
-  int n, m, row_off;
-  if (!assign_setup(cfg, h, n, m, row_off)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int n, m, row_off, nbo = 0;
+  __shared__ int32_t pre[FORM == PASS_OPEN ? OPEN_COUNTS + 1 : 1];
+  if constexpr (FORM == PASS_OPEN) {
+    NewState s{oc.N, 0, 0, 0, 0, 0, 0};
+    if (oc.first) {
+      if (oc.sums && h == 0 && blockIdx.x == 0 && tid < 4) oc.sums[tid] = 0;
+    } else {
+      const KState& o = oc.in[h];
+      const int c0 = oc.cnt[(size_t)h * oc.cnt_stride + min(tid, oc.cnt_stride - 1)];          // (ahead of the state: one trip for both)
+      if (!o.active) {
+        if (blockIdx.x == 0) carry_state(oc, h, tid);
+        return;
+      }
+      nbo = min((min(o.ucount, oc.N) + oc.items - 1) / oc.items, OPEN_COUNTS);
+      s.ccount = o.ccount + o.m_t; s.stage = o.stage + 1; s.full = o.full;
+      survivor_prefix(nbo, c0, pre);
+      s.ucount = pre[nbo];
+    }
+    loop_head(s, oc.N, oc.n_max, oc.m0, oc.m_min, oc.max_stages, oc.u_min);
+    if (blockIdx.x == 0) write_state(oc, h, tid, s);
+    if (!s.active) return;
+    n = s.ucount; m = s.m_t; row_off = s.ccount;
+  } else {
+    if (!assign_setup(cfg, h, n, m, row_off)) return;
+  }
   const int base = blockIdx.x * NT;
   if (base >= n) return;
   m = min(m, ACC_MAXM);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, hb = lane >> 5;
   const int CT = (m + 31) >> 5;
   // The centres, then the points, then the partial sums of the waves.  Piece g (16 bytes) of centre row r sits in slot g ^
@@ -312,12 +429,26 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf1
 
   // B operand: this lane's point rows
   bf16x8_t xf[PB][KS];
-  int pos[PB];
+  int pos[PB], tok[PB];
 #pragma unroll
   for (int pb = 0; pb < PB; ++pb) {
     pos[pb] = base + wave * (PB * 32) + pb * 32 + c;
-    const int p = min(pos[pb], n - 1), tok = cfg.ulist ? cfg.ulist[(size_t)h * cfg.N + p] : p;
-    const bf16raw* row = X + ((size_t)h * cfg.N + tok) * D + hb * 8;
+    const int p = min(pos[pb], n - 1);
+    if (FORM == PASS_OPEN && !oc.first) tok[pb] = oc.surv[(size_t)h * cfg.N + survivor_at(pre, nbo, oc.items, p)];
+    else tok[pb] = cfg.ulist ? cfg.ulist[(size_t)h * cfg.N + p] : p;
+  }
+  // (opening: centre j is survivor floor((2j+1) n / 2m); looked up with the points, so that all rows are then asked for together)
+  __shared__ int32_t ctok[FORM == PASS_OPEN ? ACC_MAXM : 1];
+  if constexpr (FORM == PASS_OPEN) {
+    if (tid < m) {
+      const int q = (int)(((2ll * tid + 1) * (long long)n) / (2ll * m));
+      ctok[tid] = oc.first ? q : oc.surv[(size_t)h * cfg.N + survivor_at(pre, nbo, oc.items, q)];
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+    const bf16raw* row = X + ((size_t)h * cfg.N + tok[pb]) * D + hb * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const uint4 raw = *reinterpret_cast<const uint4*>(row + ks * 16);
@@ -325,7 +456,38 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf1
     }
   }
   const size_t crow = (size_t)h * cfg.cap + row_off;
-  if constexpr (COMBINE) {
+  if constexpr (FORM == PASS_OPEN) {
+    // CH lanes a centre, a piece of its row each.  The head's first workgroup writes the centres out, and each its part of U, for
+    // the passes behind
+    if (!oc.first && hb == 0) {
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) if (pos[pb] < n) oc.uout[(size_t)h * cfg.N + pos[pb]] = tok[pb];
+    }
+    const int sl = tid % CH;
+#pragma unroll 4
+    for (int j = tid / CH; j < CT * 32; j += NT / CH) {
+      uint4 r = {0u, 0u, 0u, 0u};
+      if (j < m) r = *reinterpret_cast<const uint4*>(X + ((size_t)h * cfg.N + ctok[j]) * D + sl * 8);
+      const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+      float img[8], ss = 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        img[2 * q] = __uint_as_float(w[q] << 16); img[2 * q + 1] = __uint_as_float(w[q] & 0xFFFF0000u);
+        ss = fmaf(img[2 * q], img[2 * q], ss); ss = fmaf(img[2 * q + 1], img[2 * q + 1], ss);
+      }
+#pragma unroll
+      for (int o = 1; o < CH; o <<= 1) ss += __shfl_xor(ss, o);
+      *reinterpret_cast<uint4*>(pool + j * CROWB + ((sl ^ swz(j)) * 16)) = r;
+      if (sl == 0) bs[j] = j < m ? -0.5f * ss : -3.0e38f;      // (rows past the last centre: zeros under a bias that never wins)
+      if (blockIdx.x == 0 && j < m) {
+        const size_t at = (crow + j) * D + sl * 8;
+        *reinterpret_cast<uint4*>(cent + at) = r;
+        *reinterpret_cast<float4*>(cent_f32 + at) = float4{img[0], img[1], img[2], img[3]};
+        *reinterpret_cast<float4*>(cent_f32 + at + 4) = float4{img[4], img[5], img[6], img[7]};
+        if (sl == 0) bias[crow + j] = -0.5f * ss;
+      }
+    }
+  } else if constexpr (FORM == PASS_COMBINE) {
     // LPC lanes a centre, four columns each; the blocks' sums in block order
     constexpr int LPC = D / 4, BATCH = 8;
     const int cl = tid % LPC, nb = (n + NT - 1) / NT;
@@ -435,6 +597,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf1
     // final pass
     int kept = 0;
     double dsum = 0.0;
+    uint64_t keep[PB];
     const bool counts = cfg.keep_cnt != nullptr;
     const float t2 = counts ? cfg.tau[1] : 0.f;
 #pragma unroll
@@ -452,7 +615,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf1
       }
       const float d2 = fmaxf(ss + __shfl_xor(ss, 32) - 2.f * bv[pb], 0.f);
       const bool mine = hb == 0 && pos[pb] < n;
-      if (counts) kept += __popcll(__ballot(mine && !(d2 < t2)));
+      if (counts) {
+        keep[pb] = __ballot(mine && !(d2 < t2));                         // (of the lower half-wave)
+        kept += __popcll(keep[pb]);
+      }
       if (mine) {
         dist2[(size_t)h * cfg.N + pos[pb]] = d2;
         if (cfg.dist_sum) dsum += (double)sqrtf(d2);
@@ -471,6 +637,16 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf1
       for (int w = 0; w < NW; ++w) { k += wkept[w]; s += wsum[w]; }
       if (counts) cfg.keep_cnt[(size_t)h * cfg.keep_stride + blockIdx.x] = k;
       if (cfg.dist_sum) cfg.dist_sum[(size_t)h * gridDim.x + blockIdx.x] = s;
+    }
+    if (counts && cfg.surv && hb == 0) {   // the survivors in order, for the pass that opens the next stage
+      int at = base;
+      for (int w = 0; w < wave; ++w) at += wkept[w];
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) {
+        if ((keep[pb] >> c) & 1) cfg.surv[(size_t)h * cfg.N + at + __popc((uint32_t)keep[pb] & ((1u << c) - 1u))] = tok[pb];
+        else if (cfg.stage_of && pos[pb] < n) cfg.stage_of[(size_t)h * cfg.N + tok[pb]] = cfg.stage;
+        at += __popcll(keep[pb]);
+      }
     }
     return;
   }
@@ -1252,7 +1428,7 @@ struct FinalizeCfg {
   const KState* st;
   int spherical; int update_assign; int lp_is_bf16; int want_box;
   const int32_t* bcnt; int nb_stride;     // block sums of the assignment kernel instead of cluster parts (stage mode)
-  int nb_const;                           // > 0: that many blocks (walks of the one-read query pass), whatever the state says
+  int blk_points;                         // points of a block; 0: nb_stride blocks (walks of the one-read query pass), whatever the state says
   StateExport ex;                         // the last launch of a key clustering: what it leaves of its state (home NULL: nothing)
 };
 
@@ -1312,7 +1488,7 @@ __global__ __launch_bounds__(64 * FIN_ROWS) void finalize_centroids(FinalizeCfg 
   int nj, p_beg, p_end;
   if (cfg.bcnt) {
     // the workgroups of stage_pass, or the walks of qpass_mfma, in order
-    const int nb = cfg.nb_const > 0 ? cfg.nb_const : (cfg.st[h].ucount + PASS_POINTS - 1) / PASS_POINTS;
+    const int nb = cfg.blk_points > 0 ? (cfg.st[h].ucount + cfg.blk_points - 1) / cfg.blk_points : cfg.nb_stride;
     nj = 0;
     for (int b = lane; b < nb; b += 64) nj += cfg.bcnt[((size_t)h * cfg.nb_stride + b) * ACC_MAXM + j];
 #pragma unroll
@@ -1626,7 +1802,8 @@ constexpr int KEEP_ITEMS = 1024;
 // launch between the two cost 4-5 us and this costs one trip to the L2.
 constexpr int TAU_SUMS = 4096;
 __global__ __launch_bounds__(256) void keep_count(const KState* __restrict__ st, const float* __restrict__ dist2, int N,
-                                                  TauCfg tc, const float* __restrict__ tau, int32_t* __restrict__ cnt, int cnt_stride) {
+                                                  TauCfg tc, const float* __restrict__ tau, int32_t* __restrict__ cnt, int cnt_stride,
+                                                  int32_t* __restrict__ surv, int32_t* __restrict__ stage_of) {
   const int h = blockIdx.y, b = blockIdx.x, tid = threadIdx.x;
   float t2;
   if (tc.part) {
@@ -1637,18 +1814,33 @@ __global__ __launch_bounds__(256) void keep_count(const KState* __restrict__ st,
   const KState& s = st[h];
   if (!s.active) return;
   const int n = s.ucount;
+  constexpr int IPT = KEEP_ITEMS / 256;
+  const int p0 = b * KEEP_ITEMS + tid * IPT, lane = tid & 63, wave = tid >> 6;
+  bool keep[IPT];
   int c = 0;
 #pragma unroll
-  for (int i = 0; i < KEEP_ITEMS / 256; ++i) {
-    const int p = b * KEEP_ITEMS + i * 256 + tid;
-    if (p < n && !(dist2[(size_t)h * N + p] < t2)) ++c;
+  for (int i = 0; i < IPT; ++i) {
+    const int p = p0 + i;
+    keep[i] = p < n && !(dist2[(size_t)h * N + p] < t2);
+    c += keep[i] ? 1 : 0;
   }
+  int incl = c;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) c += __shfl_xor(c, o);
+  for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
   __shared__ int32_t ws[4];
-  if ((tid & 63) == 0) ws[tid >> 6] = c;
+  if (lane == 63) ws[wave] = incl;
   __syncthreads();
   if (tid == 0) cnt[(size_t)h * cnt_stride + b] = ws[0] + ws[1] + ws[2] + ws[3];
+  if (!surv) return;
+  // the survivors too, for the pass that opens the next stage (the first stage's positions are tokens)
+  int at = b * KEEP_ITEMS + incl - c;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) if (w < wave) at += ws[w];
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    if (keep[i]) surv[(size_t)h * N + at++] = p0 + i;
+    else if (stage_of && p0 + i < n) stage_of[(size_t)h * N + p0 + i] = 0;
+  }
 }
 
 // Between two stages of Algorithm 1, in one launch: the threshold filter of the stage that ends, the head of the
@@ -1658,36 +1850,15 @@ __global__ __launch_bounds__(256) void keep_count(const KState* __restrict__ st,
 // the loop's decision, where its own points go (the first `nblk` workgroups) or which point is the j-th survivor (the
 // others, a wave per centre).  The state is read from `in` and written, by workgroup 0 of a head, to `out`, another
 // array.  The last head to report writes {active heads, max |U|, max m_t, epoch} to `report`.
-// Bound by launch latency and five dependent trips to the L2: 8-10 us.  In three launches (the filter by one workgroup per
+// Stages of block sums are opened by their first pass instead (stage_pass).  Bound by launch latency and five dependent trips to
+// the L2: 8-10 us.  In three launches (the filter by one workgroup per
 // head 13-27 us, the loop head 4, the centres 4) and with an event for the host behind the second, a late stage of
 // 30 x 5 000 points took 68 us in all; it takes 47.
-struct OpenCfg {
-  int N, cap, n_max, m0, m_min, max_stages, u_min;
-  int first;                       // the first stage opens: no filter, U is every token (`in` is not read)
-  int items, nblk, cnt_stride;     // points per count; workgroups that move survivors
-  const KState* in; KState* out;
-  const float* dist2; const float* tau; const int32_t* cnt;
-  const int32_t* uin; int32_t* uout; int32_t* stage_of; int stage;      // `stage`: the one that ends
-  int32_t* sums; int32_t* report; int epoch;   // [4] device counters, zero between launches (`first` clears them); host slot
-  void* lp; float* f32; float* bias;
-};
-
 template <typename T, int D>
 __global__ __launch_bounds__(256) void stage_open(const T* __restrict__ X, OpenCfg c) {
   constexpr int CPL = D / 64;
   const int h = blockIdx.y, bx = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  struct { int ucount, ccount, m_t, stage, done, full, active; } s;      // the new state without its tables
-  auto report = [&](bool act) __attribute__((always_inline)) {
-    if (!c.report) return;
-    if (act) { atomicAdd(&c.sums[0], 1); atomicMax(&c.sums[1], s.ucount); atomicMax(&c.sums[2], s.m_t); }
-    __threadfence();
-    if (atomicAdd(&c.sums[3], 1) == (int)gridDim.y - 1) {
-      __threadfence();
-      for (int i = 0; i < 3; ++i) c.report[i] = atomicExch(&c.sums[i], 0);
-      atomicExch(&c.sums[3], 0);
-      __hip_atomic_store(&c.report[3], c.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);     // (the host polls this word)
-    }
-  };
+  NewState s;
   __shared__ int32_t wtot[4], s_before, s_blk[4], s_rank[4];
   int total = c.N, ex = 0, mine = 0, b0 = 0, b1 = 0, n = c.N;
   const int32_t* cnt = c.cnt + (size_t)h * c.cnt_stride;
@@ -1704,10 +1875,7 @@ __global__ __launch_bounds__(256) void stage_open(const T* __restrict__ X, OpenC
     const KState& o = c.in[h];
     const int c0 = cnt[min(tid, c.cnt_stride - 1)];          // (ahead of the state: one trip for both)
     if (!o.active) {               // closed before: carried over
-      if (bx == 0) {
-        if (tid < (int)(sizeof(KState) / 4)) reinterpret_cast<int32_t*>(&c.out[h])[tid] = reinterpret_cast<const int32_t*>(&o)[tid];
-        if (tid == 0) report(false);
-      }
+      if (bx == 0) carry_state(c, h, tid);
       return;
     }
     s.ucount = o.ucount; s.ccount = o.ccount; s.m_t = o.m_t; s.stage = o.stage; s.full = o.full; s.done = 0;
@@ -1744,26 +1912,8 @@ __global__ __launch_bounds__(256) void stage_open(const T* __restrict__ X, OpenC
     if (bx >= b0 && bx < b1) s_before = ex + before;
     s.ucount = total; s.ccount += s.m_t; s.stage += 1;
   }
-  // head of the while-loop
-  if (s.ucount == 0) s.done = 1;
-  else if (s.ccount >= c.n_max) { s.full = 1; s.done = 1; }
-  else if (s.stage >= c.max_stages || s.ucount <= c.u_min) s.done = 1;
-  s.active = !s.done;
-  if (s.active) {
-    const int m = (int)(((long long)c.m0 * s.ucount + c.N - 1) / c.N);
-    s.m_t = min(max(c.m_min, min(c.m0, m)), s.ucount);
-  } else s.m_t = 0;
-  if (bx == 0 && tid == 0) {
-    KState& o = c.out[h];
-    o.ucount = s.ucount; o.ccount = s.ccount; o.m_t = s.m_t; o.stage = s.stage; o.done = s.done; o.full = s.full;
-    o.active = s.active; o.pad = 0;
-    report(s.active);
-  }
-  if (bx == 0 && tid <= ADACLUSTER_MAX_STAGES) {
-    const int i = tid;
-    c.out[h].stage_offs[i] = c.first ? 0 : i == s.stage ? s.ccount : c.in[h].stage_offs[i];
-    c.out[h].u_hist[i] = c.first ? (i == 0 ? c.N : 0) : i == s.stage ? total : c.in[h].u_hist[i];
-  }
+  loop_head(s, c.N, c.n_max, c.m0, c.m_min, c.max_stages, c.u_min);
+  if (bx == 0) write_state(c, h, tid, s);
 
   if (bx < c.nblk) {               // the survivors of this workgroup's points move up, in order
     __syncthreads();
@@ -1870,7 +2020,8 @@ struct SmallStageCfg {
   int32_t* ulist[2];              // U of stage t is ulist[t & 1]
   bf16raw* cent_lp; float* assign_f32; float* bias;
   int32_t* stage_of;              // may be NULL
-};
+  const int32_t* surv; const int32_t* cnt; int items, cnt_stride;      // survivors of the stage that ended (NULL: `st` is that of a stage
+};                                                                     // that has been opened, and its U is in place)
 
 template <int D> struct SmallStage { static constexpr int NW = D == 64 ? 16 : 8; };   // waves (register budget 128 / 256)
 
@@ -1898,35 +2049,37 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
   __shared__ KState s_st;
   if (tid == 0) s_st = st[h];
   __syncthreads();
-  if (!s_st.active) return;                 // the stage head that ran before this launch closed the head
+  if (!s_st.active) return;                 // closed before
   const float t2 = cfg.tau[1];
+  // By one thread, with a barrier behind it: a stage ends with `left` points, and the loop goes on or not.  (One branch for both:
+  // of two, one at the loop's end and one at its head, the compiler lets the thread's wave go on without it, past the barrier.)
+  auto next_stage = [&](int left) __attribute__((always_inline)) {
+    NewState s{left, s_st.ccount + s_st.m_t, 0, s_st.stage + 1, 0, s_st.full, 0};
+    loop_head(s, cfg.N, cfg.n_max, cfg.m0, cfg.m_min, cfg.max_stages, cfg.u_min);
+    s_st.ucount = s.ucount; s_st.ccount = s.ccount; s_st.m_t = s.m_t; s_st.stage = s.stage;
+    s_st.done = s.done; s_st.full = s.full; s_st.active = s.active;
+    s_st.stage_offs[s.stage] = s.ccount;
+    s_st.u_hist[s.stage] = left;
+  };
+  if (cfg.surv) {
+    // the stage that ended left its survivors: they become U, as stage_open would have moved them
+    __shared__ int32_t pre[OPEN_COUNTS + 1];
+    const int nb = min((min(s_st.ucount, cfg.N) + cfg.items - 1) / cfg.items, OPEN_COUNTS);
+    survivor_prefix(nb, cfg.cnt[(size_t)h * cfg.cnt_stride + min(tid, cfg.cnt_stride - 1)], pre);
+    int32_t* u = cfg.ulist[(s_st.stage + 1) & 1] + (size_t)h * cfg.N;
+    const int total = min(pre[nb], SMALL_NU);
+    for (int p = tid; p < total; p += NT) u[p] = cfg.surv[(size_t)h * cfg.N + survivor_at(pre, nb, cfg.items, p)];
+    __syncthreads();
+    if (tid == 0) next_stage(total);
+    __syncthreads();
+  }
   // transpose-read addressing of the X^T operand (see stage_pass)
   const int i16 = lane & 15;
   const int vrow = 4 * hb + (i16 >> 2);
   const int gl = 2 * ((lane >> 4) & 1) + ((i16 & 3) >> 1);
   const char* xw = xs[wave] + vrow * SROWB + gl * 16 + 8 * (i16 & 1);
 
-  for (bool first = true;; first = false) {
-    if (!first) {
-      // head of the while-loop of Algorithm 1 (as stage_open)
-      if (tid == 0) {
-        KState s = s_st;
-        if (s.ucount == 0) s.done = 1;
-        else if (s.ccount >= cfg.n_max) { s.full = 1; s.done = 1; }
-        else if (s.stage >= cfg.max_stages || s.ucount <= cfg.u_min) s.done = 1;
-        s.active = !s.done;
-        if (s.active) {
-          int m = (int)(((long long)cfg.m0 * s.ucount + cfg.N - 1) / cfg.N);
-          m = max(cfg.m_min, min(cfg.m0, m));
-          s.m_t = min(m, s.ucount);
-        } else {
-          s.m_t = 0;
-        }
-        s_st = s;
-      }
-      __syncthreads();
-    }
-    if (!s_st.active) break;
+  while (s_st.active) {
     const int n = min(s_st.ucount, SMALL_NU), m = min(s_st.m_t, SMALL_M), row_off = s_st.ccount, stage = s_st.stage;
     const int32_t* uin = cfg.ulist[stage & 1] + (size_t)h * cfg.N;
     int32_t* uout = cfg.ulist[(stage + 1) & 1] + (size_t)h * cfg.N;
@@ -2193,13 +2346,8 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
       run += total;
     }
     __syncthreads();          // U of the next stage is written, and nobody reads the state any more
-    if (tid == 0) {
-      s_st.ucount = run;
-      s_st.ccount += m;
-      s_st.stage += 1;
-      s_st.stage_offs[s_st.stage] = s_st.ccount;
-      s_st.u_hist[s_st.stage] = run;
-    }
+    if (tid == 0) next_stage(run);
+    __syncthreads();
   }
   if (tid == 0) st[h] = s_st;
 }
@@ -2282,7 +2430,7 @@ static inline int chk() { return hipGetLastError() == hipSuccess ? 0 : ADACLUSTE
 
 int reduce_part_rows() { return REDUCE_ROWS; }
 int pass_sum_centres() { return ACC_MAXM; }
-int pass_points(bool combine) { return combine ? 2 * PASS_POINTS : PASS_POINTS; }
+int pass_points(bool wide) { return wide ? 2 * PASS_POINTS : PASS_POINTS; }
 // Every workgroup of a head reads all of its sums: up to 128 KB they cost less than the launch they save (up to 256 KB the
 // same time either way), up to 64 centres or (d=128) 40: each 32 or 16 are another trip (of 3 000 points, d=128, 100 centres at
 // first, a call took 540 us without that limit, 477 with launches).  Past some 512 workgroups the chip is full without waves to
@@ -2291,6 +2439,11 @@ bool combine_fits(int d, int heads, int n_bound, int m_bound) {
   const long long nb = (n_bound + 2 * PASS_POINTS - 1) / (2 * PASS_POINTS);
   return nb * m_bound * d * 4 <= (128 << 10) && m_bound <= (d == 64 ? 64 : 40) && nb * heads <= 512;
 }
+
+// Where finalize_centroids forms the centres: twice the points a workgroup are half the sums to write and to read again, once the
+// launch still fills the chip (two of these workgroups a CU at d=64).  Key clusterings of 30 x 30 000, d=128, 128 centres 724 ->
+// 697 us, of 30 x 17 776, d=64, 555 -> 549; 8 x 17 776 and 12 x 25 500 (280 and 600 workgroups) within 1 % either way.
+bool wide_fills(int heads, int n_bound) { return (long long)heads * ((n_bound + 2 * PASS_POINTS - 1) / (2 * PASS_POINTS)) >= 512; }
 
 // Which fp32 assignment: assign_f32 pays for whole tiles (up to 32 centres one, up to 128 four, of which it skips those past
 // the count but not their waves), assign_rows for every centre, at little more than the time of a thread's chain of multiply-adds
@@ -2336,27 +2489,50 @@ int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, in
   return chk();
 }
 
+static OpenCfg open_cfg(int N, int cap, const StageRules& r, const KState* in, KState* out, const StageFilter* f, const StageReport& rep) {
+  OpenCfg c{};
+  c.N = N; c.cap = cap; c.n_max = r.n_max; c.m0 = r.m0; c.m_min = r.m_min; c.max_stages = r.max_stages; c.u_min = r.u_min;
+  c.first = f == nullptr;
+  c.items = KEEP_ITEMS;
+  c.in = in; c.out = out; c.sums = rep.sums; c.report = rep.slot; c.epoch = rep.epoch;
+  if (f) {
+    c.items = f->items; c.cnt_stride = f->cnt_stride;
+    c.dist2 = f->dist2; c.tau = f->tau; c.cnt = f->cnt; c.uin = f->uin; c.uout = f->uout; c.stage_of = f->stage_of; c.stage = f->stage; c.surv = f->surv;
+  }
+  return c;
+}
+
 int launch_stage_pass(hipStream_t s, int d, int H, int N, int n_bound, int m_bound, int cap, const KState* st, const int32_t* ulist,
                       const void* X, void* cent_lp, float* cent_f32, float* bias, bool wide, const StageSums* prev, const StageSums* out,
-                      float* dist2, int32_t* keep_lab, float* keep_score, const float* tau, int32_t* keep_cnt, int keep_stride,
-                      double* dist_sum) {
-  const AssignCfg c{1, 0, N, cap, st, ulist, keep_lab, keep_score, nullptr, nullptr, tau, keep_cnt, keep_stride, dist_sum};
+                      const PassEnd* end, const StageOpening* open) {
+  AssignCfg c{1, 0, N, cap, st, ulist};
+  if (end) {
+    c.keep_lab = end->keep_lab; c.keep_score = end->keep_score; c.dist_sum = end->dist_sum;
+    c.tau = end->tau; c.keep_cnt = end->keep_cnt; c.keep_stride = end->keep_stride; c.surv = end->surv; c.stage_of = end->stage_of; c.stage = end->stage;
+  }
+  OpenCfg oc{};
+  if (open) {
+    oc = open_cfg(N, cap, *open->rules, open->in, open->out, open->filter, *open->report);
+    if (open->filter && (!oc.surv || (open->n_before + oc.items - 1) / oc.items > OPEN_COUNTS)) return ADACLUSTER_E_INTERNAL;
+  }
   const int nb = (n_bound + pass_points(wide) - 1) / pass_points(wide);
   const PassSums in = prev ? PassSums{prev->psum, prev->bcnt, m_bound * nb, nb} : PassSums{}, to = out ? PassSums{out->psum, out->bcnt, m_bound * nb, nb} : PassSums{};
-  if (m_bound > ACC_MAXM || (prev && !wide) || (!out && !dist2)) return ADACLUSTER_E_INTERNAL;
+  if (m_bound > ACC_MAXM || (prev && (!wide || open)) || !out != (end != nullptr)) return ADACLUSTER_E_INTERNAL;
   const dim3 g(nb, H);
   const bf16raw* x = (const bf16raw*)X;
   bf16raw* lp = (bf16raw*)cent_lp;
-  if (d == 64) {
-    if (prev) stage_pass<64, 8, true><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to);
-    else if (wide) stage_pass<64, 8, false><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to);
-    else stage_pass<64, 4, false><<<g, 256, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to);
-  } else {
-    if (prev) stage_pass<128, 8, true><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to);
-    else if (wide) stage_pass<128, 8, false><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to);
-    else stage_pass<128, 4, false><<<g, 256, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to);
-  }
-  return chk();
+  float* dist2 = end ? end->dist2 : nullptr;
+  auto launch = [&](auto dim) {
+    constexpr int DIM = decltype(dim)::value;
+    if (wide) {
+      if (open) stage_pass<DIM, 8, PASS_OPEN><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to, oc);
+      else if (prev) stage_pass<DIM, 8, PASS_COMBINE><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to, oc);
+      else stage_pass<DIM, 8, PASS_READ><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to, oc);
+    } else if (open) stage_pass<DIM, 4, PASS_OPEN><<<g, 256, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to, oc);
+    else stage_pass<DIM, 4, PASS_READ><<<g, 256, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to, oc);
+    return chk();
+  };
+  return d == 64 ? launch(std::integral_constant<int, 64>{}) : launch(std::integral_constant<int, 128>{});
 }
 
 // one-read pass of the query clustering (bf16, at most pass_sum_centres() centres): NP = walks per head
@@ -2396,9 +2572,9 @@ int launch_finalize(hipStream_t s, int dtype, int d, int H, int mode, int m_cons
                     const float* pmin, const float* pmax, float* master, void* assign_lp, float* assign_f32,
                     float* bias, float* out_cent, const float* fallback, int32_t* out_sizes,
                     float* out_mean_norm, float* out_bmin, float* out_bmax, const int32_t* blk_cnt, int nb_stride,
-                    int nb_const, const StateExport* ex) {
+                    int blk_points, const StateExport* ex) {
   FinalizeCfg c{mode, m_const, P, m_bound, cap, master_stride, st, spherical, update_assign,
-                dtype == ADACLUSTER_BF16, want_box, blk_cnt, nb_stride, nb_const, ex ? *ex : StateExport{}};
+                dtype == ADACLUSTER_BF16, want_box, blk_cnt, nb_stride, blk_points, ex ? *ex : StateExport{}};
   // in final mode every row of the output (up to cap) gets a size, so cover cap rows
   dim3 g(((update_assign ? m_bound : cap) + FIN_ROWS - 1) / FIN_ROWS, H);
   if (d == 64)
@@ -2448,33 +2624,25 @@ int launch_tau_abs(hipStream_t s, float tau_abs, float* tau_out) {
 
 int stage_points_per_count(int dtype) { return dtype == ADACLUSTER_BF16 ? ASSIGN_POINTS_LP : ASSIGN_POINTS_F32; }
 int launch_keep_count(hipStream_t s, const KState* st, int H, int N, const float* dist2, const double* dist_sum, int sums, float factor,
-                      float* tau, int32_t* cnt, int cnt_stride, int* items) {
+                      float* tau, int32_t* cnt, int cnt_stride, int32_t* surv, int32_t* stage_of, int* items) {
   const int count = dist_sum ? H * sums : 0;
   TauCfg t{dist_sum, count, (double)H * (double)N, factor, tau};
   if (count > TAU_SUMS) {
     tau_final<<<1, 1024, 0, s>>>(t);
     t.part = nullptr;
   }
-  keep_count<<<dim3((N + KEEP_ITEMS - 1) / KEEP_ITEMS, H), 256, 0, s>>>(st, dist2, N, t, tau, cnt, cnt_stride);
+  keep_count<<<dim3((N + KEEP_ITEMS - 1) / KEEP_ITEMS, H), 256, 0, s>>>(st, dist2, N, t, tau, cnt, cnt_stride, surv, stage_of);
   *items = KEEP_ITEMS;
   return chk();
 }
 
-int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, int n_max, int m0, int m_min, int max_stages,
-                      int u_min, int n_bound, int m_bound, const KState* in, KState* out, const StageFilter* f,
-                      int32_t* sums, int32_t* report, int epoch, const void* X, void* assign_lp,
+int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, const StageRules& rules, int n_bound, int m_bound,
+                      const KState* in, KState* out, const StageFilter* f, const StageReport& report, const void* X, void* assign_lp,
                       float* assign_f32, float* bias) {
-  OpenCfg c{};
-  c.N = N; c.cap = cap; c.n_max = n_max; c.m0 = m0; c.m_min = m_min; c.max_stages = max_stages; c.u_min = u_min;
-  c.first = f == nullptr;
-  c.items = KEEP_ITEMS;
-  c.in = in; c.out = out; c.sums = sums; c.report = report; c.epoch = epoch;
+  OpenCfg c = open_cfg(N, cap, rules, in, out, f, report);
   c.lp = assign_lp; c.f32 = assign_f32; c.bias = bias;
-  if (f) {
-    if (f->items > KEEP_ITEMS) return ADACLUSTER_E_INTERNAL;
-    c.items = f->items; c.nblk = (n_bound + f->items - 1) / f->items; c.cnt_stride = f->cnt_stride;
-    c.dist2 = f->dist2; c.tau = f->tau; c.cnt = f->cnt; c.uin = f->uin; c.uout = f->uout; c.stage_of = f->stage_of; c.stage = f->stage;
-  }
+  if (c.items > KEEP_ITEMS) return ADACLUSTER_E_INTERNAL;
+  if (f) c.nblk = (n_bound + c.items - 1) / c.items;
   const dim3 g(c.nblk + (m_bound + 3) / 4, H);
   if (dtype == ADACLUSTER_BF16) {
     if (d == 64) stage_open<bf16raw, 64><<<g, 256, 0, s>>>((const bf16raw*)X, c);
@@ -2504,13 +2672,17 @@ int small_stage_points(int d, int heads) {
 }
 int small_stage_centres() { return SMALL_M; }
 
-int launch_kstages_small(hipStream_t s, int d, int H, int N, int cap, int n_max, int m0, int m_min, int max_stages,
-                         int u_min, int iters, KState* st, const float* tau, int32_t* ulist0, int32_t* ulist1,
-                         const void* X, void* cent_lp, float* assign_f32, float* bias, int32_t* stage_of) {
-  SmallStageCfg cfg;
-  cfg.N = N; cfg.cap = cap; cfg.n_max = n_max; cfg.m0 = m0; cfg.m_min = m_min; cfg.max_stages = max_stages;
-  cfg.u_min = u_min; cfg.iters = iters; cfg.tau = tau; cfg.ulist[0] = ulist0; cfg.ulist[1] = ulist1;
+int launch_kstages_small(hipStream_t s, int d, int H, int N, int cap, const StageRules& r, int iters, KState* st, const float* tau,
+                         int32_t* ulist0, int32_t* ulist1, const void* X, void* cent_lp, float* assign_f32, float* bias,
+                         int32_t* stage_of, const StageFilter* f, int n_before) {
+  SmallStageCfg cfg{};
+  cfg.N = N; cfg.cap = cap; cfg.n_max = r.n_max; cfg.m0 = r.m0; cfg.m_min = r.m_min; cfg.max_stages = r.max_stages;
+  cfg.u_min = r.u_min; cfg.iters = iters; cfg.tau = tau; cfg.ulist[0] = ulist0; cfg.ulist[1] = ulist1;
   cfg.cent_lp = (bf16raw*)cent_lp; cfg.assign_f32 = assign_f32; cfg.bias = bias; cfg.stage_of = stage_of;
+  if (f) {
+    if (!f->surv || (n_before + f->items - 1) / f->items > OPEN_COUNTS) return ADACLUSTER_E_INTERNAL;
+    cfg.surv = f->surv; cfg.cnt = f->cnt; cfg.items = f->items; cfg.cnt_stride = f->cnt_stride;
+  }
   if (d == 64) kstages_small<64><<<H, SmallStage<64>::NW * 64, 0, s>>>((const bf16raw*)X, st, cfg);
   else kstages_small<128><<<H, SmallStage<128>::NW * 64, 0, s>>>((const bf16raw*)X, st, cfg);
   return chk();

@@ -36,17 +36,29 @@ int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, in
                   const float* seed_score = nullptr,
                   const float* tau = nullptr, int32_t* keep_cnt = nullptr, int keep_stride = 0, double* dist_sum = nullptr);
 // A pass of a stage of Algorithm 1 with at most pass_sum_centres() centres (bf16).  An update pass (out) leaves the member sums
-// and counts of every pass_points(wide) points; launch_finalize(blk_cnt = out->bcnt, nb_stride = their number) turns them
+// and counts of every pass_points(wide) points; launch_finalize(blk_cnt = out->bcnt, nb_stride = their number, blk_points) turns them
 // into centres, or (`wide`, where combine_fits says so) the next pass does, which then takes them as `prev` (another
-// table than its `out`).  The last pass (out NULL) leaves distances and, where asked for, what launch_assign leaves besides.
+// table than its `out`).  The last pass (out NULL) leaves what `end` says.  The first pass may open the stage (`open`): it
+// then does what launch_stage_open does, from the survivors that the stage before has left.
+constexpr int STAGE_SUM_BLOCKS = 128;   // a stage of at most this many blocks of pass_points(false) may update from their sums
 struct StageSums { float* psum; int32_t* bcnt; };     // [H][m_bound * blocks][d], [H][blocks][pass_sum_centres()]
+struct PassEnd {
+  float* dist2; int32_t* keep_lab; float* keep_score; double* dist_sum;      // the last three as in launch_assign, or NULL
+  const float* tau; int32_t* keep_cnt; int keep_stride; int32_t* surv; int32_t* stage_of; int stage;   // survivors of a stage whose threshold is known (keep_cnt, else NULL)
+};
+struct StageRules { int n_max, m0, m_min, max_stages, u_min; };      // of the loop of Algorithm 1
+struct StageFilter; struct StageReport;
+struct StageOpening {
+  const StageRules* rules; const KState* in; KState* out; const StageFilter* filter /* NULL: the first stage */; const StageReport* report;
+  int n_before;                        // no head has more points in the stage that ends
+};
 int pass_sum_centres();
 int pass_points(bool wide);
 bool combine_fits(int d, int heads, int n_bound, int m_bound);
+bool wide_fills(int heads, int n_bound);      // whether passes without `prev` take `wide` as well
 int launch_stage_pass(hipStream_t s, int d, int H, int N, int n_bound, int m_bound, int cap, const KState* st, const int32_t* ulist,
                       const void* X, void* cent_lp, float* cent_f32, float* bias, bool wide, const StageSums* prev, const StageSums* out,
-                      float* dist2 = nullptr, int32_t* keep_lab = nullptr, float* keep_score = nullptr, const float* tau = nullptr,
-                      int32_t* keep_cnt = nullptr, int keep_stride = 0, double* dist_sum = nullptr);
+                      const PassEnd* end, const StageOpening* open);
 int launch_seg_reduce(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int P,
                       const KState* st, int normalize, int want_box, const void* X, const int32_t* perm,
                       const int32_t* offs, int offs_stride, int32_t* poff, int32_t* pcl, float* psum, float* pnorm, float* pmin,
@@ -63,7 +75,7 @@ int launch_finalize(hipStream_t s, int dtype, int d, int H, int mode, int m_cons
                     const float* pmin, const float* pmax, float* master, void* assign_lp, float* assign_f32,
                     float* bias, float* out_cent, const float* fallback, int32_t* out_sizes,
                     float* out_mean_norm, float* out_bmin, float* out_bmax, const int32_t* blk_cnt = nullptr,
-                    int nb_stride = 0, int nb_const = 0, const StateExport* ex = nullptr);
+                    int nb_stride = 0, int blk_points = 0 /* of a block; 0: nb_stride blocks in every head */, const StateExport* ex = nullptr);
 // Centroid update of a running stage (state mode 1) in one launch, fp32 inputs: every centre's workgroup scans the
 // stage's label list (`ulist` NULL: positions are tokens), so it is for few points and centres only:
 // direct_update_fits() says when.  Writes what launch_finalize(update_assign = 1) writes.
@@ -73,7 +85,7 @@ int launch_update_direct(hipStream_t s, int d, int H, int N, int m_bound, int ca
                          float* assign_f32, float* bias);
 // One pass of a k-means with at most pass_sum_centres() centres in one read of the points (bf16):
 // assignment and (weighted) centroid sums together.  psum [H][m * NP][d], pcnt [H][NP][pass_sum_centres()]
-// with NP = qpass_walks(N); launch_finalize(..., blk_cnt = pcnt, nb_stride = NP, nb_const = NP) turns them into centres.
+// with NP = qpass_walks(N); launch_finalize(..., blk_cnt = pcnt, nb_stride = NP) turns them into centres.
 int qpass_walks(int N);
 int launch_qpass(hipStream_t s, int d, int H, int N, int m, int cap, int weighted, const void* X, const void* cent_lp,
                  const float* bias, float* psum, int32_t* pcnt);
@@ -88,27 +100,29 @@ int launch_tau_abs(hipStream_t s, float tau_abs, float* tau_out);
 struct StageFilter {
   const float* dist2; const float* tau; const int32_t* cnt; int cnt_stride; int items;
   const int32_t* uin /* NULL: every token */; int32_t* uout; int32_t* stage_of /* may be NULL */; int stage;
+  const int32_t* surv;                 // [H][N] the survivors of every `items` points, from where those start (NULL: not left)
 };
+struct StageReport { int32_t* sums; int32_t* slot /* mapped host memory, or NULL */; int epoch; };
 int stage_points_per_count(int dtype);
 // The threshold (with dist_sum, what launch_assign left; NULL: `tau` holds it) and the survivors of the first stage.
 int launch_keep_count(hipStream_t s, const KState* st, int H, int N, const float* dist2, const double* dist_sum, int sums, float factor,
-                      float* tau, int32_t* cnt, int cnt_stride, int* items);      // sums: per head
+                      float* tau, int32_t* cnt, int cnt_stride, int32_t* surv /* NULL: counts alone */, int32_t* stage_of, int* items);      // sums: per head
 // Filter of the stage that ends (f; NULL: none, the first stage opens), head of the loop of Algorithm 1, initial centres of
 // the stage that opens.  n_bound, m_bound: no head has more points in the stage that ends, or centres in the one that opens.
-// The state goes from `in` to `out`, which must differ; sums: 4 device integers; report (mapped host memory, may be
-// NULL): {active heads, max |U|, max m_t, epoch}, the epoch behind the rest.
-int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, int n_max, int m0, int m_min, int max_stages,
-                      int u_min, int n_bound, int m_bound, const KState* in, KState* out, const StageFilter* f,
-                      int32_t* sums, int32_t* report, int epoch, const void* X, void* assign_lp,
+// The state goes from `in` to `out`, which must differ; report: 4 device integers, and the host's slot, which gets {active heads,
+// max |U|, max m_t, epoch}, the epoch behind the rest.
+int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, const StageRules& rules, int n_bound, int m_bound,
+                      const KState* in, KState* out, const StageFilter* f, const StageReport& report, const void* X, void* assign_lp,
                       float* assign_f32, float* bias);
 // Every remaining stage of Algorithm 1 in one launch, one workgroup per head (bf16 only).  Valid once every
 // active head has at most small_stage_points() unassigned points and small_stage_centres() centres per
-// stage, and never for stage 0 (it needs a list of U and a known tau).
+// stage, and never for stage 0 (it needs a known tau).  f: the stage before has left its survivors, at most n_before points a
+// head before the filter, and has not been closed; NULL: the stage has been opened.
 int small_stage_points(int d, int heads);      // heads: still active
 int small_stage_centres();
-int launch_kstages_small(hipStream_t s, int d, int H, int N, int cap, int n_max, int m0, int m_min, int max_stages,
-                         int u_min, int iters, KState* st, const float* tau, int32_t* ulist0, int32_t* ulist1,
-                         const void* X, void* cent_lp, float* assign_f32, float* bias, int32_t* stage_of);
+int launch_kstages_small(hipStream_t s, int d, int H, int N, int cap, const StageRules& r, int iters, KState* st, const float* tau,
+                         int32_t* ulist0, int32_t* ulist1, const void* X, void* cent_lp, float* assign_f32, float* bias,
+                         int32_t* stage_of, const StageFilter* f, int n_before);
 int launch_mse(hipStream_t s, int dtype, int d, int H, int N, int cap, const void* X, const int32_t* labels,
                const float* cent, double* part, float* mse);
 int launch_fill_i32(hipStream_t s, int32_t* p, size_t n, int32_t v);

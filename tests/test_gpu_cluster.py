@@ -285,6 +285,26 @@ def check_kcluster(K, p, out, dtype):
     return tau
 
 
+@pytest.mark.parametrize("d,H,N,m0,iters", [
+    (64, 2, 1024, 16, 3), (128, 2, 1025, 16, 3),       # the one-launch late stages open themselves behind the first stage
+    (64, 3, 5121, 40, 3), (128, 3, 5119, 40, 3),       # stages opened by their first pass, then the one launch; ragged last blocks
+    (128, 2, 8193, 96, 2), (64, 2, 32768, 128, 2),     # the centres formed by a launch; the most counts a stage can have
+    (64, 16, 17409, 100, 3),                           # twice the points a workgroup
+    (64, 2, 4097, 24, 1),                              # a single pass, which cannot open a stage
+])
+def test_kcluster_stages_opened_by_their_passes(d, H, N, m0, iters):
+    rng = np.random.default_rng(17)
+    K = wl.round_bf16_f32(rng.standard_normal((H, N, d)).astype(np.float32))
+    K[0, ::3] *= 0.5
+    K = wl.round_bf16_f32(K)
+    p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=8, k_iters=iters, k_m0=m0, k_m_min=4, k_max_clusters=2000, k_max_stages=6,
+                 tau_factor=1.0, min_unassigned_frac=0.0)
+    out = B.adacluster_kcluster(p, to_dev(K, B.BF16))
+    torch.cuda.synchronize()
+    check_kcluster(K, p, out, B.BF16)
+    assert (out["k_count"].cpu().numpy() > m0).all()       # every head went on past its first stage
+
+
 @pytest.mark.parametrize("dtype,d,N,M", [(B.BF16, 64, 4000, 16), (B.BF16, 128, 2600, 16), (B.F32, 64, 1800, 12)])
 def test_kcluster_chained(dtype, d, N, M):
     H = 3
