@@ -359,6 +359,11 @@ int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     }
     RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, D.Cq, 0, D.Cq, D.Cq, nullptr, nullptr, Q, w.q_cent_lp, w.q_bias,
                          q_labels, nullptr));
+    if (it == p->q_iters - 1 && cluster_stats_fits(D.H, D.N, D.Cq)) {
+      RET_IF(launch_cluster_stats(st, p->dtype, D.d, D.H, D.N, 0, D.Cq, D.Cq, D.Cq, nullptr, sph, 0, Q, q_labels, w.perm_q, w.offs_q, D.Cq + 1,
+                                  q_centroids, nullptr, q_sizes, q_mean_norm, nullptr, nullptr, nullptr));
+      break;
+    }
     RET_IF(launch_sort(st, D.H, D.N, D.N, D.Cq, q_labels, nullptr, nullptr, 0, nullptr, 0, nullptr, 0, w.perm_q,
                        w.offs_q, D.Cq + 1, w.q_sort, w.q_poff, reduce_part_rows(), nullptr, 0, &poff_done));
     RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, 0, D.Cq, D.Cq, P, nullptr, sph, 0, Q, w.perm_q, w.offs_q,
@@ -440,6 +445,11 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   auto sums_fit = [&] {
     return p->dtype == ADACLUSTER_BF16 && (n_bound + pass_points(false) - 1) / pass_points(false) <= STAGE_SUM_BLOCKS && m_bound <= pass_sum_centres();
   };
+  // few points and few centres left in every head: one launch for all stages that follow
+  auto small_fits = [&] {
+    return p->dtype == ADACLUSTER_BF16 && n_bound <= small_stage_points(D.d, heads) && m_bound <= small_stage_centres();
+  };
+  int sums_left = 0;                               // distance sums a head that the first stage left to that launch
   for (int t = 0; t <= p->k_max_stages; ++t) {
     const bool pass_opens = t == 0 ? sums_fit() : filter.surv && t < p->k_max_stages;      // (bounds never grow: sums_fit() holds again)
     const int n_before = n_bound;
@@ -474,11 +484,9 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       if (now[0] == 0) break;                  // no head needs a second stage
       heads = now[0]; n_bound = now[1]; m_bound = now[2];
     }
-    if (t > 0 && p->dtype == ADACLUSTER_BF16 && n_bound <= small_stage_points(D.d, heads) && m_bound <= small_stage_centres()) {
-      // few points and few centres left in every head: one launch runs this and every later stage
-      // (|U|, m_t and the active heads never grow, so the bounds hold for all of them)
+    if (t > 0 && small_fits()) {      // (|U|, m_t and the active heads never grow, so the bounds hold for all stages that follow)
       RET_IF(launch_kstages_small(st, D.d, D.H, D.N, D.cap, rules, p->k_iters, cur, w.tau, w.ulist[0], w.ulist[1], K, w.cent_lp, k_assign,
-                                  w.bias, k_stage_of, pass_opens ? &filter : nullptr, n_before));
+                                  w.bias, k_stage_of, pass_opens ? &filter : nullptr, n_before, dist_sum, sums_left, p->tau_factor));
       kc_bound += m_bound * (p->k_max_stages - t);
       break;
     }
@@ -536,8 +544,11 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       }
     }
     filter = StageFilter{w.dist2, w.tau, w.blockcnt, D.ncnt, counted, ul, ul_next, k_stage_of, t, surv};
-    if (t == 0) RET_IF(launch_keep_count(st, cur, D.H, D.N, w.dist2, dist_sum, (D.N + counted - 1) / counted, p->tau_factor, w.tau, w.blockcnt,
-                                         D.ncnt, surv, k_stage_of, &filter.items));
+    if (t == 0) {
+      const int sums = (D.N + counted - 1) / counted;
+      if (surv && p->k_max_stages > 1 && small_fits() && small_forms_tau(D.H, sums)) sums_left = sums;
+      else RET_IF(launch_keep_count(st, cur, D.H, D.N, w.dist2, dist_sum, sums, p->tau_factor, w.tau, w.blockcnt, D.ncnt, surv, k_stage_of, &filter.items));
+    }
   }
   PASS_ON(beside(true));
   kc_bound = kc_bound < D.cap ? kc_bound : D.cap;
@@ -552,17 +563,24 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   }
   const int want_box = (k_bmin && k_bmax) ? 1 : 0;
   if (kc_bound_out) *kc_bound_out = kc_bound;
-  const int P = parts_for(D.N, kc_bound);
-  RET_IF(launch_sort(st, D.H, D.N, D.N, kc_bound, k_labels, nullptr, nullptr, 0, warm ? &cur->m_t : &cur->ccount, sizeof(KState) / 4,
-                     nullptr, 0, w.perm_k, w.offs_k, D.cap + 1, w.sort, w.poff, reduce_part_rows(), w.pcl, P, &poff_done));
-  prof_mark(EV_KSORT, st);
-  RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, warm ? 1 : 2, 0, kc_bound, P, cur, 0, want_box, K, w.perm_k, w.offs_k,
-                           D.cap + 1, w.poff, w.pcl, w.psum, w.pnorm, w.pmin, w.pmax, poff_done));
-  prof_mark(EV_KREDUCE, st, EV_KSORT);
   const StateExport ex{w.kstate, k_count, full_flag, k_stage_offs, w.tau, warm ? nullptr : tau_used};
-  RET_IF(launch_finalize(st, p->dtype, D.d, D.H, warm ? 1 : 2, 0, kc_bound, P, D.cap, D.cap, cur, 0, 0, want_box, w.offs_k,
-                         D.cap + 1, w.poff, w.psum, w.pnorm, w.pmin, w.pmax, nullptr, nullptr, nullptr, nullptr, k_centroids,
-                         k_assign, k_sizes, nullptr, k_bmin, k_bmax, nullptr, 0, 0, &ex));
+  if (cluster_stats_fits(D.H, D.N, kc_bound)) {
+    prof_mark(EV_KSORT, st);
+    RET_IF(launch_cluster_stats(st, p->dtype, D.d, D.H, D.N, warm ? 1 : 2, 0, kc_bound, D.cap, cur, 0, want_box, K, k_labels, w.perm_k, w.offs_k,
+                                D.cap + 1, k_centroids, k_assign, k_sizes, nullptr, k_bmin, k_bmax, &ex));
+    prof_mark(EV_KREDUCE, st, EV_KSORT);
+  } else {
+    const int P = parts_for(D.N, kc_bound);
+    RET_IF(launch_sort(st, D.H, D.N, D.N, kc_bound, k_labels, nullptr, nullptr, 0, warm ? &cur->m_t : &cur->ccount, sizeof(KState) / 4,
+                       nullptr, 0, w.perm_k, w.offs_k, D.cap + 1, w.sort, w.poff, reduce_part_rows(), w.pcl, P, &poff_done));
+    prof_mark(EV_KSORT, st);
+    RET_IF(launch_seg_reduce(st, p->dtype, D.d, D.H, D.N, warm ? 1 : 2, 0, kc_bound, P, cur, 0, want_box, K, w.perm_k, w.offs_k,
+                             D.cap + 1, w.poff, w.pcl, w.psum, w.pnorm, w.pmin, w.pmax, poff_done));
+    prof_mark(EV_KREDUCE, st, EV_KSORT);
+    RET_IF(launch_finalize(st, p->dtype, D.d, D.H, warm ? 1 : 2, 0, kc_bound, P, D.cap, D.cap, cur, 0, 0, want_box, w.offs_k,
+                           D.cap + 1, w.poff, w.psum, w.pnorm, w.pmin, w.pmax, nullptr, nullptr, nullptr, nullptr, k_centroids,
+                           k_assign, k_sizes, nullptr, k_bmin, k_bmax, nullptr, 0, 0, &ex));
+  }
   // the pinned report slots are reused by the next call of this thread: let the last report land
   // (its kernel was queued ahead of everything above, so this does not drain the stream)
   if (pending && !stage_report_landed(*rb, pending, st))

@@ -18,6 +18,7 @@
 namespace adac {
 
 static constexpr int TILE_REC = 8;       // ints per query-tile record (32 bytes)
+static constexpr int MIN_CHUNK = 16;     // key tiles of a chunk at least: lists of up to twice as many stay whole
 static constexpr int SPLIT_SLOTS = 128;  // partial slots per head for the chunks of cut key lists
 static constexpr int F32_WAVES = 4;      // waves of a workgroup of the fp32 kernel
 static constexpr int F32_MAX_SPLITS = 4; // most workgroups the fp32 kernel splits a key list over
@@ -84,7 +85,7 @@ __device__ __forceinline__ void tiles_of_head(int32_t* sm, int h, int Cq, int ma
   __syncthreads();
   const long long work = w_work[0] + w_work[1] + w_work[2] + w_work[3];
   const int qtiles = w_a[0] + w_a[1] + w_a[2] + w_a[3];
-  const int chunk = max(16, 2 * (qtiles > 0 ? (int)((work + qtiles - 1) / qtiles) : 0));
+  const int chunk = max(MIN_CHUNK, 2 * (qtiles > 0 ? (int)((work + qtiles - 1) / qtiles) : 0));
   // which lists are cut: the long ones are listed in cluster order, and one thread deals the slots out while they last
   int cuts = 0;
   for (int c = c0; c < c1; ++c) { s_pieces[c] = 1; cuts += allow_split && s_T[c] > 2 * chunk; }
@@ -1372,7 +1373,7 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
       if (d == 64) attn_mfma<64, A64_NW, A64_NBUF, A64_MINB, A64_VPRE><<<g, A64_NW * 64, 0, s>>>(a);
       else attn_mfma<128, A128_NW, A128_NBUF, A128_MINB, A128_VPRE><<<g, A128_NW * 64, 0, s>>>(a);
     }
-    if (merge) {      // the chunks of cut key lists (none for the dense branch)
+    if (merge && (N + 63) / 64 > 2 * MIN_CHUNK) {      // the chunks of cut key lists (none for the dense branch)
       if (d == 64) attn_merge<64><<<dim3(MERGE_GROUPS, H, 4), 256, 0, s>>>(a, merge, nmerge);
       else attn_merge<128><<<dim3(MERGE_GROUPS, H, 4), 256, 0, s>>>(a, merge, nmerge);
     }

@@ -1592,6 +1592,174 @@ __global__ __launch_bounds__(64 * FIN_ROWS) void finalize_centroids(FinalizeCfg 
 }
 
 // ------------------------------------------------------------------------------------------
+// Label sort and final member statistics of short heads in one launch
+// ------------------------------------------------------------------------------------------
+// A workgroup is a cluster: it reads all labels of the head, so it knows how many items come before its own and which those
+// are, in order.  That is its part of the sorted order and of the offsets; it sums its rows, in parts of REDUCE_ROWS, a wave
+// each, and writes what finalize_centroids writes with update_assign = 0: the order of all sums is that of seg_reduce and
+// finalize_centroids, and so are the results, to the bit.
+// Bound by latency: three dependent trips to memory and the sums, 8-9 us, in the place of a sort by one workgroup (10-14 us), a
+// reduction (7-10) and a combining launch (3-4).  cluster_stats_fits() has the line.
+struct StatsCfg {
+  int mode; int m_const; int N; int cap;        // mode as FinalizeCfg
+  const KState* st;
+  int spherical; int want_box;
+  StateExport ex;
+};
+constexpr int STATS_NT = 512, STATS_ITEMS = 4096;
+template <typename T, int D>
+__global__ __launch_bounds__(STATS_NT) void cluster_stats(const T* __restrict__ X, StatsCfg cfg, const int32_t* __restrict__ labels,
+                                                          int32_t* __restrict__ perm, int32_t* __restrict__ offs, int offs_stride,
+                                                          float* __restrict__ out_cent, const float* __restrict__ fallback,
+                                                          int32_t* __restrict__ out_sizes, float* __restrict__ out_mean_norm,
+                                                          float* __restrict__ out_bmin, float* __restrict__ out_bmax) {
+  constexpr int EV = Vec16<T>::N, LPR = D / EV, RPI = 64 / LPR, NW = STATS_NT / 64, PER = STATS_ITEMS / STATS_NT, CPL = D / 64;
+  constexpr int UNR = (REDUCE_ROWS / RPI) < 16 ? REDUCE_ROWS / RPI : 16, MAXP = STATS_ITEMS / REDUCE_ROWS;
+  const int h = blockIdx.y, j = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // this thread's labels: positions wave * 64 * PER + 64 i + lane
+  const int n = cfg.N;
+  const int32_t* lab = labels + (size_t)h * n;
+  int l[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) { const int pos = (wave * PER + i) * 64 + lane; l[i] = pos < n ? lab[pos] : -1; }
+  if (cfg.ex.home && j == 0 && wave == 0) export_state(cfg.ex, cfg.st, cfg.mode, h, lane);
+  const int m = cfg.mode == 0 ? cfg.m_const : cfg.mode == 1 ? cfg.st[h].m_t : cfg.st[h].ccount;
+  int32_t* const of = offs + (size_t)h * offs_stride;
+  if (j == 0) {
+    if (out_sizes) for (int i = m + tid; i < cfg.cap; i += STATS_NT) out_sizes[(size_t)h * cfg.cap + i] = 0;
+    if (m == 0 && tid == 0) of[0] = 0;
+  }
+  if (j >= m) return;
+  __shared__ int32_t list[STATS_ITEMS];
+  __shared__ int32_t whit[NW], wless[NW];
+  __shared__ float psum[MAXP][D], pnorm[MAXP], wmin[NW][D], wmax[NW][D];
+  const uint64_t below = (1ull << lane) - 1ull;
+  int mine = 0, less = 0, at[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const uint64_t b = __ballot(l[i] == j);
+    at[i] = mine + __popcll(b & below);
+    mine += __popcll(b);
+    less += __popcll(__ballot((uint32_t)l[i] < (uint32_t)j));
+  }
+  if (lane == 0) { whit[wave] = mine; wless[wave] = less; }
+  __syncthreads();
+  int base = 0, nj = 0, start = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) { const int c = whit[w]; if (w < wave) base += c; nj += c; start += wless[w]; }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) if (l[i] == j) list[base + at[i]] = (wave * PER + i) * 64 + lane;
+  __syncthreads();
+  for (int i = tid; i < nj; i += STATS_NT) perm[(size_t)h * n + start + i] = list[i];
+  if (tid == 0) { of[j] = start; if (j == m - 1) of[m] = start + nj; }
+  const int slot = lane / LPR, cl = lane % LPR, parts = (nj + REDUCE_ROWS - 1) / REDUCE_ROWS;
+  const T* Xh = X + (size_t)h * n * D + cl * EV;
+  float mn[EV], mx[EV];
+#pragma unroll
+  for (int e = 0; e < EV; ++e) { mn[e] = INFINITY; mx[e] = -INFINITY; }
+  for (int p = wave; p < parts; p += NW) {
+    const int me = min(nj, (p + 1) * REDUCE_ROWS);
+    float acc[EV], nsum = 0.f;
+#pragma unroll
+    for (int e = 0; e < EV; ++e) acc[e] = 0.f;
+    for (int i0 = p * REDUCE_ROWS; i0 < me; i0 += UNR * RPI) {
+      uint4 raw[UNR];
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        const int i = i0 + u * RPI + slot;
+        raw[u] = uint4{0u, 0u, 0u, 0u};
+        if (i < me) raw[u] = *reinterpret_cast<const uint4*>(Xh + (size_t)list[i] * D);
+      }
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        const bool valid = i0 + u * RPI + slot < me;
+        float x[EV];
+        Vec16<T>::decode(raw[u], x);
+        if (cfg.spherical) {
+          float ss = 0.f;
+#pragma unroll
+          for (int e = 0; e < EV; ++e) ss = fmaf(x[e], x[e], ss);
+#pragma unroll
+          for (int o = 1; o < LPR; o <<= 1) ss += __shfl_xor(ss, o);
+          const float nrm = sqrtf(ss), inv = 1.0f / fmaxf(nrm, 1e-12f);
+#pragma unroll
+          for (int e = 0; e < EV; ++e) x[e] *= inv;
+          if (valid) nsum += nrm;
+        }
+        if (valid) {
+#pragma unroll
+          for (int e = 0; e < EV; ++e) {
+            acc[e] += x[e];
+            if (cfg.want_box) { mn[e] = fminf(mn[e], x[e]); mx[e] = fmaxf(mx[e], x[e]); }
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int o = RPI / 2; o >= 1; o >>= 1) {
+#pragma unroll
+      for (int e = 0; e < EV; ++e) acc[e] += __shfl_down(acc[e], o * LPR);
+      nsum += __shfl_down(nsum, o * LPR);
+    }
+    if (slot == 0) {
+#pragma unroll
+      for (int e = 0; e < EV; ++e) psum[p][cl * EV + e] = acc[e];
+      if (cl == 0) pnorm[p] = nsum;
+    }
+  }
+  if (cfg.want_box) {
+#pragma unroll
+    for (int o = RPI / 2; o >= 1; o >>= 1)
+#pragma unroll
+      for (int e = 0; e < EV; ++e) {
+        mn[e] = fminf(mn[e], __shfl_down(mn[e], o * LPR));
+        mx[e] = fmaxf(mx[e], __shfl_down(mx[e], o * LPR));
+      }
+    if (slot == 0) {
+#pragma unroll
+      for (int e = 0; e < EV; ++e) { wmin[wave][cl * EV + e] = mn[e]; wmax[wave][cl * EV + e] = mx[e]; }
+    }
+  }
+  __syncthreads();
+  if (wave > 0) return;
+  float s[CPL], ss = 0.f, ns = 0.f;
+#pragma unroll
+  for (int q = 0; q < CPL; ++q) {
+    s[q] = 0.f;
+    for (int p = 0; p < parts; ++p) s[q] += psum[p][lane + 64 * q];
+    ss = fmaf(s[q], s[q], ss);
+  }
+  bool ok = nj > 0;
+  float div = (float)max(nj, 1);
+  if (cfg.spherical) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) ss += __shfl_xor(ss, o);
+    const float nrm = sqrtf(ss);
+    ok = ok && nrm >= 1e-12f;
+    div = fmaxf(nrm, 1e-30f);
+    for (int p = 0; p < parts; ++p) ns += pnorm[p];
+  }
+#pragma unroll
+  for (int q = 0; q < CPL; ++q) {
+    const int cq = lane + 64 * q;
+    const size_t oo = ((size_t)h * cfg.cap + j) * D + cq;
+    if (ok) out_cent[oo] = s[q] / div;
+    else if (fallback) out_cent[oo] = fallback[oo];
+    if (cfg.want_box) {
+      float lo = wmin[0][cq], hi = wmax[0][cq];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) { lo = fminf(lo, wmin[w][cq]); hi = fmaxf(hi, wmax[w][cq]); }
+      out_bmin[oo] = nj > 0 ? lo : 0.f;
+      out_bmax[oo] = nj > 0 ? hi : 0.f;
+    }
+  }
+  if (lane == 0) {
+    if (out_sizes) out_sizes[(size_t)h * cfg.cap + j] = nj;
+    if (out_mean_norm) out_mean_norm[(size_t)h * cfg.cap + j] = nj > 0 ? (cfg.spherical ? ns / (float)nj : 1.f) : 0.f;
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // Centroid update of a stage with few points in ONE launch (fp32 inputs): the workgroup of a centre finds
 // its members in the label list itself (an ordered compaction, so the member order is the list order),
 // sums their rows in a fixed order and writes the new centre, its copies for the assignment kernel and
@@ -2020,8 +2188,10 @@ struct SmallStageCfg {
   int32_t* ulist[2];              // U of stage t is ulist[t & 1]
   bf16raw* cent_lp; float* assign_f32; float* bias;
   int32_t* stage_of;              // may be NULL
-  const int32_t* surv; const int32_t* cnt; int items, cnt_stride;      // survivors of the stage that ended (NULL: `st` is that of a stage
-};                                                                     // that has been opened, and its U is in place)
+  // How the stage before ended, if it has not been closed (both NULL: `st` is that of a stage that has been opened, and its U is in place):
+  const int32_t* surv; const int32_t* cnt; int items, cnt_stride;      // its survivors, or
+  const float* dist2; TauCfg tc;                                       // (the first stage) its distances, and their sums if tau is to be formed
+};
 
 template <int D> struct SmallStage { static constexpr int NW = D == 64 ? 16 : 8; };   // waves (register budget 128 / 256)
 
@@ -2049,8 +2219,13 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
   __shared__ KState s_st;
   if (tid == 0) s_st = st[h];
   __syncthreads();
+  float t2;
+  if (cfg.tc.part) {                        // (as keep_count)
+    const float t = tau_of<NT>(cfg.tc);
+    t2 = t * t;
+    if (h == 0 && tid == 0) { cfg.tc.out[0] = t; cfg.tc.out[1] = t2; }
+  } else t2 = cfg.tau[1];
   if (!s_st.active) return;                 // closed before
-  const float t2 = cfg.tau[1];
   // By one thread, with a barrier behind it: a stage ends with `left` points, and the loop goes on or not.  (One branch for both:
   // of two, one at the loop's end and one at its head, the compiler lets the thread's wave go on without it, past the barrier.)
   auto next_stage = [&](int left) __attribute__((always_inline)) {
@@ -2061,7 +2236,47 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
     s_st.stage_offs[s.stage] = s.ccount;
     s_st.u_hist[s.stage] = left;
   };
-  if (cfg.surv) {
+  // Threshold filter by the distances in LDS: points with d < tau leave U; U stays ascending (as in stage_open).
+  auto filter = [&](int n, const int32_t* uin /* NULL: every token */, int32_t* uout, int stage) {
+    int run = 0;
+    for (int base = 0; base < n; base += 4 * NT) {
+      const int p0 = base + 4 * tid;
+      bool keep[4]; int tok[4]; int cnt = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int p = p0 + i;
+        const bool valid = p < n;
+        keep[i] = valid && !(fs[valid ? p : 0] < t2);
+        tok[i] = valid ? (uin ? uin[p] : p) : -1;
+        cnt += keep[i] ? 1 : 0;
+      }
+      int incl = cnt;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
+      __syncthreads();
+      if (lane == 63) ws[wave] = incl;
+      __syncthreads();
+      int before = 0, total = 0;
+      for (int w = 0; w < NW; ++w) { const int v = ws[w]; if (w < wave) before += v; total += v; }
+      int pos = run + before + incl - cnt;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (keep[i]) uout[pos++] = tok[i];
+        else if (tok[i] >= 0 && cfg.stage_of) cfg.stage_of[(size_t)h * cfg.N + tok[i]] = stage;
+      }
+      run += total;
+    }
+    return run;
+  };
+  if (cfg.dist2) {
+    const int n0 = min(s_st.ucount, SMALL_NU), stage0 = s_st.stage;
+    for (int p = tid; p < n0; p += NT) fs[p] = cfg.dist2[(size_t)h * cfg.N + p];
+    __syncthreads();
+    const int left = filter(n0, nullptr, cfg.ulist[(stage0 + 1) & 1] + (size_t)h * cfg.N, stage0);
+    __syncthreads();
+    if (tid == 0) next_stage(left);
+    __syncthreads();
+  } else if (cfg.surv) {
     // the stage that ended left its survivors: they become U, as stage_open would have moved them
     __shared__ int32_t pre[OPEN_COUNTS + 1];
     const int nb = min((min(s_st.ucount, cfg.N) + cfg.items - 1) / cfg.items, OPEN_COUNTS);
@@ -2315,36 +2530,8 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
       __syncthreads();
     }
 
-    // threshold filter: points with d < tau leave U; U stays ascending (as in stage_open)
     __syncthreads();
-    int run = 0;
-    for (int base = 0; base < n; base += 4 * NT) {
-      const int p0 = base + 4 * tid;
-      bool keep[4]; int tok[4]; int cnt = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int p = p0 + i;
-        const bool valid = p < n;
-        keep[i] = valid && !(fs[valid ? p : 0] < t2);
-        tok[i] = valid ? uin[p] : -1;
-        cnt += keep[i] ? 1 : 0;
-      }
-      int incl = cnt;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
-      __syncthreads();
-      if (lane == 63) ws[wave] = incl;
-      __syncthreads();
-      int before = 0, total = 0;
-      for (int w = 0; w < NW; ++w) { const int v = ws[w]; if (w < wave) before += v; total += v; }
-      int pos = run + before + incl - cnt;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (keep[i]) uout[pos++] = tok[i];
-        else if (tok[i] >= 0 && cfg.stage_of) cfg.stage_of[(size_t)h * cfg.N + tok[i]] = stage;
-      }
-      run += total;
-    }
+    const int run = filter(n, uin, uout, stage);
     __syncthreads();          // U of the next stage is written, and nobody reads the state any more
     if (tid == 0) next_stage(run);
     __syncthreads();
@@ -2591,6 +2778,29 @@ int launch_finalize(hipStream_t s, int dtype, int d, int H, int mode, int m_cons
 bool direct_update_fits(int dtype, int n_bound, int m_bound) {
   return dtype == ADACLUSTER_F32 && n_bound <= DIRECT_MAX_POINTS && (long long)n_bound * m_bound <= DIRECT_MAX_VISITS;
 }
+// Every workgroup reads the labels of its head: in all up to some three million it is the faster form.  us of a call (with the
+// sort, the reduction and the launch behind it), all bf16 with 65 query clusters: 2 x 1 500 tokens, d=64, 9 query clusters 122 (140),
+// 8 x 1 500 134 (150), 16 x 1 800 149 (161), 30 x 1 500, d=128 241 (248), 4 x 4 000, d=128 232 (248); past the line 12 x 4 000,
+// d=128 312 (308), 30 x 4 000, d=64 313 (306).
+bool cluster_stats_fits(int H, int N, int m_bound) { return N <= STATS_ITEMS && (long long)H * m_bound * N <= 3000000; }
+int launch_cluster_stats(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int cap, const KState* st,
+                         int spherical, int want_box, const void* X, const int32_t* labels, int32_t* perm, int32_t* offs, int offs_stride,
+                         float* out_cent, const float* fallback, int32_t* out_sizes, float* out_mean_norm, float* out_bmin,
+                         float* out_bmax, const StateExport* ex) {
+  if (N > STATS_ITEMS) return ADACLUSTER_E_INTERNAL;
+  const StatsCfg c{mode, m_const, N, cap, st, spherical, want_box, ex ? *ex : StateExport{}};
+  auto launch = [&](auto elem, auto dim) {
+    using T = decltype(elem);
+    constexpr int DIM = decltype(dim)::value;
+    cluster_stats<T, DIM><<<dim3(m_bound, H), STATS_NT, 0, s>>>((const T*)X, c, labels, perm, offs, offs_stride, out_cent, fallback, out_sizes,
+                                                                out_mean_norm, out_bmin, out_bmax);
+  };
+  using std::integral_constant;
+  if (dtype == ADACLUSTER_BF16) { if (d == 64) launch(bf16raw{}, integral_constant<int, 64>{}); else launch(bf16raw{}, integral_constant<int, 128>{}); }
+  else { if (d == 64) launch(float{}, integral_constant<int, 64>{}); else launch(float{}, integral_constant<int, 128>{}); }
+  return chk();
+}
+
 int launch_update_direct(hipStream_t s, int d, int H, int N, int m_bound, int cap, int master_stride, const KState* st,
                          const int32_t* labels, const int32_t* ulist, const void* X, float* master, void* assign_lp,
                          float* assign_f32, float* bias) {
@@ -2671,15 +2881,20 @@ int small_stage_points(int d, int heads) {
   return heads >= all ? SMALL_NU : min(SMALL_NU, max(3072, one * all / (all - heads)));
 }
 int small_stage_centres() { return SMALL_M; }
+bool small_forms_tau(int H, int sums) { return (long long)H * sums <= TAU_SUMS; }
 
-int launch_kstages_small(hipStream_t s, int d, int H, int N, int cap, const StageRules& r, int iters, KState* st, const float* tau,
+int launch_kstages_small(hipStream_t s, int d, int H, int N, int cap, const StageRules& r, int iters, KState* st, float* tau,
                          int32_t* ulist0, int32_t* ulist1, const void* X, void* cent_lp, float* assign_f32, float* bias,
-                         int32_t* stage_of, const StageFilter* f, int n_before) {
+                         int32_t* stage_of, const StageFilter* f, int n_before, const double* dist_sum, int sums, float factor) {
   SmallStageCfg cfg{};
   cfg.N = N; cfg.cap = cap; cfg.n_max = r.n_max; cfg.m0 = r.m0; cfg.m_min = r.m_min; cfg.max_stages = r.max_stages;
   cfg.u_min = r.u_min; cfg.iters = iters; cfg.tau = tau; cfg.ulist[0] = ulist0; cfg.ulist[1] = ulist1;
   cfg.cent_lp = (bf16raw*)cent_lp; cfg.assign_f32 = assign_f32; cfg.bias = bias; cfg.stage_of = stage_of;
-  if (f) {
+  if (f && sums > 0) {
+    if (n_before > SMALL_NU || !small_forms_tau(H, sums)) return ADACLUSTER_E_INTERNAL;
+    cfg.dist2 = f->dist2;
+    if (dist_sum) cfg.tc = TauCfg{dist_sum, H * sums, (double)H * (double)N, factor, tau};
+  } else if (f) {
     if (!f->surv || (n_before + f->items - 1) / f->items > OPEN_COUNTS) return ADACLUSTER_E_INTERNAL;
     cfg.surv = f->surv; cfg.cnt = f->cnt; cfg.items = f->items; cfg.cnt_stride = f->cnt_stride;
   }

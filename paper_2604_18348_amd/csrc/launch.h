@@ -76,6 +76,13 @@ int launch_finalize(hipStream_t s, int dtype, int d, int H, int mode, int m_cons
                     float* bias, float* out_cent, const float* fallback, int32_t* out_sizes,
                     float* out_mean_norm, float* out_bmin, float* out_bmax, const int32_t* blk_cnt = nullptr,
                     int nb_stride = 0, int blk_points = 0 /* of a block; 0: nb_stride blocks in every head */, const StateExport* ex = nullptr);
+// Label sort (perm, offs as launch_sort leaves them) and final statistics (launch_finalize, update_assign = 0) in one launch:
+// cluster_stats_fits() says when.
+bool cluster_stats_fits(int H, int N, int m_bound);
+int launch_cluster_stats(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int cap, const KState* st,
+                         int spherical, int want_box, const void* X, const int32_t* labels, int32_t* perm, int32_t* offs, int offs_stride,
+                         float* out_cent, const float* fallback, int32_t* out_sizes, float* out_mean_norm, float* out_bmin,
+                         float* out_bmax, const StateExport* ex);
 // Centroid update of a running stage (state mode 1) in one launch, fp32 inputs: every centre's workgroup scans the
 // stage's label list (`ulist` NULL: positions are tokens), so it is for few points and centres only:
 // direct_update_fits() says when.  Writes what launch_finalize(update_assign = 1) writes.
@@ -116,13 +123,15 @@ int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, co
                       float* assign_f32, float* bias);
 // Every remaining stage of Algorithm 1 in one launch, one workgroup per head (bf16 only).  Valid once every
 // active head has at most small_stage_points() unassigned points and small_stage_centres() centres per
-// stage, and never for stage 0 (it needs a known tau).  f: the stage before has left its survivors, at most n_before points a
-// head before the filter, and has not been closed; NULL: the stage has been opened.
+// stage, and never for stage 0.  f: the stage before has not been closed; it had at most n_before points a head, and left its
+// survivors (sums 0) or, the first stage, distances and what the threshold is formed from: dist_sum, `sums` a head, as in
+// launch_keep_count, where small_forms_tau().  NULL: the stage has been opened.
 int small_stage_points(int d, int heads);      // heads: still active
 int small_stage_centres();
-int launch_kstages_small(hipStream_t s, int d, int H, int N, int cap, const StageRules& r, int iters, KState* st, const float* tau,
+bool small_forms_tau(int H, int sums);
+int launch_kstages_small(hipStream_t s, int d, int H, int N, int cap, const StageRules& r, int iters, KState* st, float* tau,
                          int32_t* ulist0, int32_t* ulist1, const void* X, void* cent_lp, float* assign_f32, float* bias,
-                         int32_t* stage_of, const StageFilter* f, int n_before);
+                         int32_t* stage_of, const StageFilter* f, int n_before, const double* dist_sum, int sums, float factor);
 int launch_mse(hipStream_t s, int dtype, int d, int H, int N, int cap, const void* X, const int32_t* labels,
                const float* cent, double* part, float* mse);
 int launch_fill_i32(hipStream_t s, int32_t* p, size_t n, int32_t v);

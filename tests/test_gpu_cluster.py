@@ -305,6 +305,33 @@ def test_kcluster_stages_opened_by_their_passes(d, H, N, m0, iters):
     assert (out["k_count"].cpu().numpy() > m0).all()       # every head went on past its first stage
 
 
+@pytest.mark.parametrize("dtype,d,N,m0,skew", [(B.BF16, 64, 4096, 24, 0.9), (B.BF16, 128, 4095, 24, 0.0), (B.BF16, 128, 129, 5, 0.95),
+                                               (B.F32, 64, 4096, 24, 0.9), (B.F32, 128, 2049, 20, 0.5)])
+def test_short_heads_sorted_and_summed_per_cluster(dtype, d, N, m0, skew):
+    """A workgroup a cluster (few heads), or sort, reduction and combination (many): the same bits, boxes and empty clusters
+    among them; `skew` of the tokens are alike, so that one cluster holds many parts."""
+    H = 3000000 // (16 * N) + 1               # past the line of cluster_stats_fits for 16 clusters
+    rng = np.random.default_rng(23)
+    X = rng.standard_normal((1, N, d)).astype(np.float32)
+    alike = rng.random(N) < skew
+    X[0, alike] = X[0, 0] + 0.05 * X[0, alike]
+    if dtype == B.BF16:
+        X = wl.round_bf16_f32(X)
+    p = B.Params(H=1, N=N, d=d, dtype=dtype, q_clusters=16, q_iters=2, k_iters=2, k_m0=m0, k_m_min=2, k_max_clusters=3 * m0, tau_abs=0.9 * d ** 0.5)
+    Xd = to_dev(X, dtype)
+    pm = dataclasses.replace(p, H=H)
+    Xm = Xd.expand(H, -1, -1).contiguous()
+    for one, many in ((B.adacluster_qcluster(p, Xd), B.adacluster_qcluster(pm, Xm)), (B.adacluster_kcluster(p, Xd), B.adacluster_kcluster(pm, Xm))):
+        m = int(one["k_count"][0]) if "k_count" in one else p.q_clusters
+        for name, a in one.items():
+            b = many[name]
+            if a is None or name == "tau_used":
+                continue
+            if name.startswith("k_") and a.shape[1:2] == (p.cap,):      # (rows past the count are not written)
+                a, b = a[:, :m], b[:, :m]
+            assert torch.equal(b, a.expand_as(b)), name
+
+
 @pytest.mark.parametrize("dtype,d,N,M", [(B.BF16, 64, 4000, 16), (B.BF16, 128, 2600, 16), (B.F32, 64, 1800, 12)])
 def test_kcluster_chained(dtype, d, N, M):
     H = 3
