@@ -216,9 +216,9 @@ Dims dims_of(const adacluster_params* p) {
   D.maxr = D.cap;
   D.prow = p->N / reduce_part_rows() + D.capmax + 34;
   {  // rows of the table of member sums of small stages: blocks x centres, both capped (room for the two tables of stages
-     // that combine: they have half the blocks, rounded up)
-    const int pp = pass_points(false), nb = (p->N + pp - 1) / pp, mb = p->k_m0 < pass_sum_centres() ? p->k_m0 : pass_sum_centres();
-    D.brow = ((nb < STAGE_SUM_BLOCKS ? nb : STAGE_SUM_BLOCKS) + 1) * mb;
+     // that combine: those of bf16 have half the blocks, rounded up; those of fp32 hold doubles)
+    const int pp = pass_points(ADACLUSTER_BF16, false), nb = (p->N + pp - 1) / pp, mb = p->k_m0 < pass_sum_centres() ? p->k_m0 : pass_sum_centres();
+    D.brow = p->dtype == ADACLUSTER_F32 ? 4 * pass_f32_rows(p->d, p->N, p->k_m0) : ((nb < STAGE_SUM_BLOCKS ? nb : STAGE_SUM_BLOCKS) + 1) * mb;
   }
   return D;
 }
@@ -257,7 +257,7 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(lab0, int32_t*, p->dtype == ADACLUSTER_BF16 ? H * N * 4 : 256);
   TAKE(score0, float*, p->dtype == ADACLUSTER_BF16 ? H * N * 4 : 256);
   TAKE(psum, float*, H * (size_t)D.prow * d * 4);
-  TAKE(bcnt, int32_t*, H * (size_t)STAGE_SUM_BLOCKS * pass_sum_centres() * 4);
+  TAKE(bcnt, int32_t*, H * (size_t)(p->dtype == ADACLUSTER_F32 ? 2 : 1) * STAGE_SUM_BLOCKS * pass_sum_centres() * 4);      // (bf16: two tables of half the blocks)
   TAKE(bsum, float*, H * (size_t)D.brow * d * 4);
   TAKE(pnorm, float*, H * (size_t)D.prow * 4);
   TAKE(pmin, float*, H * (size_t)D.prow * d * 4);
@@ -359,7 +359,7 @@ int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     }
     RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, D.Cq, 0, D.Cq, D.Cq, nullptr, nullptr, Q, w.q_cent_lp, w.q_bias,
                          q_labels, nullptr));
-    if (it == p->q_iters - 1 && cluster_stats_fits(D.H, D.N, D.Cq)) {
+    if (it == p->q_iters - 1 && cluster_stats_fits(p->dtype, D.H, D.N, D.Cq)) {
       RET_IF(launch_cluster_stats(st, p->dtype, D.d, D.H, D.N, 0, D.Cq, D.Cq, D.Cq, nullptr, sph, 0, Q, q_labels, w.perm_q, w.offs_q, D.Cq + 1,
                                   q_centroids, nullptr, q_sizes, q_mean_norm, nullptr, nullptr, nullptr));
       break;
@@ -442,8 +442,11 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   StageFilter filter{};                            // how the stage before ended
   // Stages with few blocks of points and few centres (bf16) update from block sums; they are opened by their own first pass,
   // from the survivors that the stage before left as a list (filter.surv; the first stage: every token).
+  const bool f32_sums = p->dtype == ADACLUSTER_F32 && pass_f32_fits(D.d, D.H, D.N, m_bound);
   auto sums_fit = [&] {
-    return p->dtype == ADACLUSTER_BF16 && (n_bound + pass_points(false) - 1) / pass_points(false) <= STAGE_SUM_BLOCKS && m_bound <= pass_sum_centres();
+    if (p->dtype == ADACLUSTER_F32) return f32_sums;
+    const int pts = pass_points(p->dtype, false);
+    return (n_bound + pts - 1) / pts <= STAGE_SUM_BLOCKS && m_bound <= pass_sum_centres();
   };
   // few points and few centres left in every head: one launch for all stages that follow
   auto small_fits = [&] {
@@ -496,11 +499,11 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     // A small stage (few blocks of points, few centres) updates its centres from the member sums that a pass leaves per
     // block: no label sort and no segmented reduction in between, and where all of them together are small no launch either.
     const bool block_sums = sums_fit();
-    const bool combine = block_sums && combine_fits(D.d, heads, n_bound, m_bound);
+    const bool combine = block_sums && (p->dtype == ADACLUSTER_F32 || combine_fits(D.d, heads, n_bound, m_bound));
     const bool wide = combine || (block_sums && wide_fills(heads, n_bound));
-    const int nblk = (n_bound + pass_points(wide) - 1) / pass_points(wide);
-    const StageSums sums[2] = {{w.bsum, w.bcnt}, {w.bsum + (size_t)D.H * m_bound * nblk * D.d, w.bcnt + (size_t)D.H * nblk * pass_sum_centres()}};
-    const int counted = block_sums ? pass_points(wide) : stage_points_per_count(p->dtype);      // points per survivor count and distance sum of the last pass
+    const int pts = pass_points(p->dtype, wide), nblk = (n_bound + pts - 1) / pts;
+    const StageSums sums[2] = {{w.bsum, w.bcnt}, {w.bsum + (size_t)D.H * m_bound * nblk * D.d * (p->dtype == ADACLUSTER_F32 ? 2 : 1), w.bcnt + (size_t)D.H * nblk * pass_sum_centres()}};
+    const int counted = block_sums ? pts : stage_points_per_count(p->dtype);      // points per survivor count and distance sum of the last pass
     // (a stage of block sums has no other use for the array; a single pass would read and write it)
     int32_t* const surv = block_sums && p->k_iters > 1 ? w.labels_tmp : nullptr;
     if (pass_opens && t > 0) { KState* x = cur; cur = other; other = x; }
@@ -513,13 +516,13 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
       if (block_sums) {
         const PassEnd end{w.dist2, keep ? w.lab0 : nullptr, keep ? w.score0 : nullptr, t == 0 ? dist_sum : nullptr,
                           w.tau, t > 0 ? w.blockcnt : nullptr, D.ncnt, surv, k_stage_of, t};
-        RET_IF(launch_stage_pass(st, D.d, D.H, D.N, n_bound, m_bound, D.cap, cur, ul, K, w.cent_lp, k_assign, w.bias, wide,
+        RET_IF(launch_stage_pass(st, p->dtype, D.d, D.H, D.N, n_bound, m_bound, D.cap, cur, ul, K, w.cent_lp, k_assign, w.bias, wide,
                                  combine && it > 0 ? &sums[(it - 1) & 1] : nullptr, update ? &sums[combine ? it & 1 : 0] : nullptr,
                                  update ? nullptr : &end, pass_opens && it == 0 ? &opening : nullptr));
         if (update && !combine)
           RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, m_bound * nblk, D.cap, 0, cur, 0, 1, 0,
                                  nullptr, 0, nullptr, w.bsum, w.pnorm, w.pmin, w.pmax, nullptr, w.cent_lp,
-                                 k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.bcnt, nblk, pass_points(wide)));
+                                 k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.bcnt, nblk, pts));
         continue;
       }
       // (the last pass of stage 0 runs over all points against the first-stage centres as they will stay:
@@ -564,7 +567,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   const int want_box = (k_bmin && k_bmax) ? 1 : 0;
   if (kc_bound_out) *kc_bound_out = kc_bound;
   const StateExport ex{w.kstate, k_count, full_flag, k_stage_offs, w.tau, warm ? nullptr : tau_used};
-  if (cluster_stats_fits(D.H, D.N, kc_bound)) {
+  if (cluster_stats_fits(p->dtype, D.H, D.N, kc_bound)) {
     prof_mark(EV_KSORT, st);
     RET_IF(launch_cluster_stats(st, p->dtype, D.d, D.H, D.N, warm ? 1 : 2, 0, kc_bound, D.cap, cur, 0, want_box, K, k_labels, w.perm_k, w.offs_k,
                                 D.cap + 1, k_centroids, k_assign, k_sizes, nullptr, k_bmin, k_bmax, &ex));

@@ -358,6 +358,93 @@ __device__ __forceinline__ int survivor_at(const int32_t* pre, int nb, int items
   return lo * items + p - pre[lo];
 }
 
+// The opening of a stage by every workgroup (x) of a head (y) for itself: its points, centres and where those go, and the survivors'
+// prefix of nb counts.  False: the head is done.
+__device__ __forceinline__ bool open_stage(const OpenCfg& oc, int h, int32_t* pre, int& nbo, int& n, int& m, int& row_off) {
+  const int tid = threadIdx.x;
+  NewState s{oc.N, 0, 0, 0, 0, 0, 0};
+  if (oc.first) {
+    if (oc.sums && h == 0 && blockIdx.x == 0 && tid < 4) oc.sums[tid] = 0;
+  } else {
+    const KState& o = oc.in[h];
+    const int c0 = oc.cnt[(size_t)h * oc.cnt_stride + min(tid, oc.cnt_stride - 1)];          // (ahead of the state: one trip for both)
+    if (!o.active) {
+      if (blockIdx.x == 0) carry_state(oc, h, tid);
+      return false;
+    }
+    nbo = min((min(o.ucount, oc.N) + oc.items - 1) / oc.items, OPEN_COUNTS);
+    s.ccount = o.ccount + o.m_t; s.stage = o.stage + 1; s.full = o.full;
+    survivor_prefix(nbo, c0, pre);
+    s.ucount = pre[nbo];
+  }
+  loop_head(s, oc.N, oc.n_max, oc.m0, oc.m_min, oc.max_stages, oc.u_min);
+  if (blockIdx.x == 0) write_state(oc, h, tid, s);
+  if (!s.active) return false;
+  n = s.ucount; m = s.m_t; row_off = s.ccount;
+  return true;
+}
+
+struct PassSums { float* psum; int32_t* bcnt; int P; int nb_stride; };
+constexpr int STAGE_COUNTS = 128;      // counts of a block in PassSums::bcnt
+// Sum of columns 4 cl .. 4 cl + 3 over the members of centre j, from the blocks in their order, and the number of members.  By
+// the D / 4 lanes of a centre together.
+template <int D>
+__device__ __forceinline__ float4 block_sum(const PassSums& prev, int h, int j, int nb, int cl, int& nj) {
+  constexpr int LPC = D / 4, BATCH = 8;
+  nj = 0;
+  for (int b = cl; b < nb; b += LPC) nj += prev.bcnt[((size_t)h * prev.nb_stride + b) * STAGE_COUNTS + j];
+  const float* ps = prev.psum + ((size_t)h * prev.P + (size_t)j * prev.nb_stride) * D + cl * 4;
+  float4 s = {0.f, 0.f, 0.f, 0.f};
+  for (int b0 = 0; b0 < nb; b0 += BATCH) {
+    float4 t[BATCH];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) t[u] = *reinterpret_cast<const float4*>(ps + (size_t)min(b0 + u, nb - 1) * D);
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) if (b0 + u < nb) { s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w; }
+  }
+#pragma unroll
+  for (int o = 1; o < LPC; o <<= 1) nj += __shfl_xor(nj, o);
+  return s;
+}
+// The sums of R waves that share a tile of 32 centres (part 0 .. R-1 of tile ct) meet in part 0: half of them hand theirs to the
+// other half, until one holds all.  `ps`: LDS that nobody needs, [waves / 2 * 32][D + 4].
+template <int D>
+__device__ __forceinline__ void meet_sums(f32x16_t (&sacc)[D / 32], float* ps, int R, int ct, int part, int c, int hb) {
+  constexpr int DT = D / 32, PROW = D + 4;            // floats of a padded row: the float4 pieces of 8 centres fall in 8 bank groups
+  for (int half = R / 2; half >= 1; half >>= 1) {
+    __syncthreads();                     // the points, or the sums of the round before, have been read
+    float* const slot = ps + ((size_t)((ct * half + (part & (half - 1))) * 32 + c)) * PROW + 4 * hb;
+    if (part >= half && part < 2 * half) {
+#pragma unroll
+      for (int db = 0; db < DT; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          *reinterpret_cast<float4*>(slot + db * 32 + 8 * i) = float4{sacc[db][4 * i], sacc[db][4 * i + 1], sacc[db][4 * i + 2], sacc[db][4 * i + 3]};
+    }
+    __syncthreads();
+    if (part < half) {
+#pragma unroll
+      for (int db = 0; db < DT; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float4 o = *reinterpret_cast<const float4*>(slot + db * 32 + 8 * i);
+          sacc[db][4 * i] += o.x; sacc[db][4 * i + 1] += o.y; sacc[db][4 * i + 2] += o.z; sacc[db][4 * i + 3] += o.w;
+        }
+    }
+  }
+}
+// Value v of a tile is dim db*32 + 8*(v/4) + 4*hb + v%4 of centre cid: to its row of block b.
+template <int D>
+__device__ __forceinline__ void store_sums(const f32x16_t (&sacc)[D / 32], const PassSums& out, int h, int b, int cid, int hb) {
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db) {
+    float* o = out.psum + ((size_t)h * out.P + (size_t)cid * out.nb_stride + b) * D + db * 32 + 4 * hb;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<float4*>(o + 8 * i) = float4{sacc[db][4 * i], sacc[db][4 * i + 1], sacc[db][4 * i + 2], sacc[db][4 * i + 3]};
+  }
+}
+
 // ------------------------------------------------------------------------------------------
 // A pass of a stage of Algorithm 1 with at most ACC_MAXM centres (bf16): assignment and member sums together.
 // ------------------------------------------------------------------------------------------
@@ -378,7 +465,6 @@ __device__ __forceinline__ int survivor_at(const int32_t* pre, int nb, int items
 // workgroup sums the counts, knows |U|, the loop's decision and m_t, and finds its points and the centres by position.  Latency
 // bound: two trips to the L2 more than a pass whose list and centres lie ready, where the launch had five (30 x 5 000 points,
 // d=64: 8 + 8.5 -> 12 us; key clusterings of 30 x 7 920 tokens 170 -> 153 us, 12 x 25 500 208 -> 198, 30 x 17 776 570 -> 550).
-struct PassSums { float* psum; int32_t* bcnt; int P; int nb_stride; };
 enum PassCentres { PASS_READ, PASS_COMBINE, PASS_OPEN };
 template <int D, int NW, int FORM>
 __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf16raw* __restrict__ X, AssignCfg cfg, bf16raw* __restrict__ cent,
@@ -390,25 +476,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf1
   int n, m, row_off, nbo = 0;
   __shared__ int32_t pre[FORM == PASS_OPEN ? OPEN_COUNTS + 1 : 1];
   if constexpr (FORM == PASS_OPEN) {
-    NewState s{oc.N, 0, 0, 0, 0, 0, 0};
-    if (oc.first) {
-      if (oc.sums && h == 0 && blockIdx.x == 0 && tid < 4) oc.sums[tid] = 0;
-    } else {
-      const KState& o = oc.in[h];
-      const int c0 = oc.cnt[(size_t)h * oc.cnt_stride + min(tid, oc.cnt_stride - 1)];          // (ahead of the state: one trip for both)
-      if (!o.active) {
-        if (blockIdx.x == 0) carry_state(oc, h, tid);
-        return;
-      }
-      nbo = min((min(o.ucount, oc.N) + oc.items - 1) / oc.items, OPEN_COUNTS);
-      s.ccount = o.ccount + o.m_t; s.stage = o.stage + 1; s.full = o.full;
-      survivor_prefix(nbo, c0, pre);
-      s.ucount = pre[nbo];
-    }
-    loop_head(s, oc.N, oc.n_max, oc.m0, oc.m_min, oc.max_stages, oc.u_min);
-    if (blockIdx.x == 0) write_state(oc, h, tid, s);
-    if (!s.active) return;
-    n = s.ucount; m = s.m_t; row_off = s.ccount;
+    if (!open_stage(oc, h, pre, nbo, n, m, row_off)) return;
   } else {
     if (!assign_setup(cfg, h, n, m, row_off)) return;
   }
@@ -489,25 +557,14 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf1
     }
   } else if constexpr (FORM == PASS_COMBINE) {
     // LPC lanes a centre, four columns each; the blocks' sums in block order
-    constexpr int LPC = D / 4, BATCH = 8;
+    constexpr int LPC = D / 4;
     const int cl = tid % LPC, nb = (n + NT - 1) / NT;
     for (int j = tid / LPC; j < CT * 32; j += NT / LPC) {
       uint2 r = {0u, 0u};
       float bj = -3.0e38f;                               // (rows past the last centre: zeros under a bias that never wins)
       if (j < m) {
-        int nj = 0;
-        for (int b = cl; b < nb; b += LPC) nj += prev.bcnt[((size_t)h * prev.nb_stride + b) * ACC_MAXM + j];
-        const float* ps = prev.psum + ((size_t)h * prev.P + (size_t)j * prev.nb_stride) * D + cl * 4;
-        float4 s = {0.f, 0.f, 0.f, 0.f};
-        for (int b0 = 0; b0 < nb; b0 += BATCH) {
-          float4 t[BATCH];
-#pragma unroll
-          for (int u = 0; u < BATCH; ++u) t[u] = *reinterpret_cast<const float4*>(ps + (size_t)min(b0 + u, nb - 1) * D);
-#pragma unroll
-          for (int u = 0; u < BATCH; ++u) if (b0 + u < nb) { s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w; }
-        }
-#pragma unroll
-        for (int o = 1; o < LPC; o <<= 1) nj += __shfl_xor(nj, o);
+        int nj;
+        const float4 s = block_sum<D>(prev, h, j, nb, cl, nj);
         const size_t at = (crow + j) * D + cl * 4;
         if (nj > 0) {
           const float cnt = (float)nj;
@@ -703,41 +760,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf1
       }
     }
   }
-  // the waves that share a tile meet: half of them hand their sums to the other half, until one holds all
-  constexpr int PROW = D + 4;            // floats of a padded row: the float4 pieces of 8 centres fall in 8 bank groups
-  static_assert(NW / 2 * 32 * PROW * 4 <= NT * CROWB, "the partial sums fit the buffer of the points");
-  float* const ps = reinterpret_cast<float*>(pool);
-  for (int half = R / 2; half >= 1; half >>= 1) {
-    __syncthreads();                     // the points, or the sums of the round before, have been read
-    float* const slot = ps + ((size_t)((ct * half + (part & (half - 1))) * 32 + c)) * PROW + 4 * hb;
-    if (part >= half && part < 2 * half) {
-#pragma unroll
-      for (int db = 0; db < DT; ++db)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          *reinterpret_cast<float4*>(slot + db * 32 + 8 * i) = float4{sacc[db][4 * i], sacc[db][4 * i + 1], sacc[db][4 * i + 2], sacc[db][4 * i + 3]};
-    }
-    __syncthreads();
-    if (part < half) {
-#pragma unroll
-      for (int db = 0; db < DT; ++db)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float4 o = *reinterpret_cast<const float4*>(slot + db * 32 + 8 * i);
-          sacc[db][4 * i] += o.x; sacc[db][4 * i + 1] += o.y; sacc[db][4 * i + 2] += o.z; sacc[db][4 * i + 3] += o.w;
-        }
-    }
-  }
-  // value v of a tile is dim db*32 + 8*(v/4) + 4*hb + v%4 of centre cid
-  if (part == 0 && cid < m) {
-#pragma unroll
-    for (int db = 0; db < DT; ++db) {
-      float* o = out.psum + ((size_t)h * out.P + (size_t)cid * out.nb_stride + b) * D + db * 32 + 4 * hb;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        *reinterpret_cast<float4*>(o + 8 * i) = float4{sacc[db][4 * i], sacc[db][4 * i + 1], sacc[db][4 * i + 2], sacc[db][4 * i + 3]};
-    }
-  }
+  static_assert(NW / 2 * 32 * (D + 4) * 4 <= NT * CROWB && ACC_MAXM == STAGE_COUNTS, "the partial sums fit the buffer of the points");
+  meet_sums<D>(sacc, reinterpret_cast<float*>(pool), R, ct, part, c, hb);
+  if (part == 0 && cid < m) store_sums<D>(sacc, out, h, b, cid, hb);
   if (tid < m) out.bcnt[((size_t)h * out.nb_stride + b) * ACC_MAXM + tid] = cnt_s[tid];
 }
 
@@ -1082,6 +1107,235 @@ __global__ __launch_bounds__(NS * 64 * (ASSIGN_POINTS_F32 / 32), 4) void assign_
     if (sp == 0 && lane == 0) wsum[pg] = dsum;
     __syncthreads();
     if (tid == 0) cfg.dist_sum[(size_t)h * gridDim.x + blockIdx.x] = wsum[0] + wsum[1];
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// A pass of a stage of Algorithm 1 with at most PASS_F32_CENTRES centres, fp32: what stage_pass is for bf16
+// ------------------------------------------------------------------------------------------
+// A workgroup is PASS_F32_POINTS points in four groups of 32, eight waves: a group and one of two tiles of 32 centres each.  Scores
+// and labels are those of assign_f32, to the bit.  An update pass then leaves the members' sums: a wave takes every eighth centre,
+// finds its members by two ballots over the labels, and adds their rows out of LDS, a lane a column.  Sums are formed in fp64 and
+// rounded once, by the mean: the same members give the same centre in every stage, wherever in U they are (as in
+// update_direct_f32, whose order does not depend on that), so that such centres tie exactly.  A call therefore takes the one or
+// the other for all of its stages.  (fp64 sums there as well: 6 000 points, d=64, 25 -> 43 us a launch.)
+// Latency bound, 8-10 us: it takes the place of an assignment (5) and an update by label scan (5-7), and opens its stage
+// (stage_open, 6-7).
+constexpr int PASS_F32_POINTS = 128, PASS_F32_CENTRES = 64;
+template <int D, int FORM>
+__global__ __launch_bounds__(512, D == 64 ? 4 : 2) void stage_pass_f32(const float* __restrict__ X, AssignCfg cfg, float* __restrict__ cent,
+                                                                       float* __restrict__ cent_f32, float* __restrict__ bias,
+                                                                       float* __restrict__ dist2, PassSums prev, PassSums out, OpenCfg oc) {
+  constexpr int NT = 512, NP = PASS_F32_POINTS, MAXM = PASS_F32_CENTRES, ROWB = D * 4, PPR = D / 4, CPL = D / 64;
+  const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 31, hb = lane >> 5, pg = wave & 3, sp = wave >> 2;
+  int n, m, row_off, nbo = 0;
+  __shared__ int32_t pre[FORM == PASS_OPEN ? OPEN_COUNTS + 1 : 1], ctok[FORM == PASS_OPEN ? MAXM : 1];
+  if constexpr (FORM == PASS_OPEN) {
+    if (!open_stage(oc, h, pre, nbo, n, m, row_off)) return;
+  } else {
+    if (!assign_setup(cfg, h, n, m, row_off)) return;
+  }
+  const int base = blockIdx.x * NP;
+  if (base >= n) return;
+  m = min(m, MAXM);
+  const int CT = (m + 31) >> 5;
+  __shared__ __attribute__((aligned(16))) char ps[NP * ROWB];
+  __shared__ __attribute__((aligned(16))) char cs[MAXM * ROWB];
+  __shared__ __attribute__((aligned(16))) float bs[MAXM];
+  __shared__ float sbest[2][NP];
+  __shared__ int32_t sidx[2][NP], tok_s[NP], lab_s[NP];
+  const float* Xh = X + (size_t)h * cfg.N * D;
+  auto slot_of = [](int r, int q) { return (q & ~15) | ((q ^ r) & 15); };       // where piece q (16 bytes) of row r is, as in assign_f32
+  // tokens of the points, and (opening) of the centres, survivor floor((2j+1) n / 2m)
+  if (tid < NP) {
+    const int p = min(base + tid, n - 1);
+    int t;
+    if (FORM == PASS_OPEN && !oc.first) {
+      t = oc.surv[(size_t)h * cfg.N + survivor_at(pre, nbo, oc.items, p)];
+      if (base + tid < n) oc.uout[(size_t)h * cfg.N + p] = t;
+    } else t = cfg.ulist ? cfg.ulist[(size_t)h * cfg.N + p] : p;
+    tok_s[tid] = t;
+  } else if (tid < NP + MAXM) {
+    const int j = tid - NP;
+    if (FORM == PASS_OPEN && j < m) {
+      const int q = (int)(((2ll * j + 1) * (long long)n) / (2ll * m));
+      ctok[j] = oc.first ? q : oc.surv[(size_t)h * cfg.N + survivor_at(pre, nbo, oc.items, q)];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NP * PPR / NT; ++i) {
+    const int item = tid + i * NT, r = item / PPR;
+    dma_b128((uint32_t)(uintptr_t)(lds_void_t*)ps + (wave * 64 + i * NT) * 16, reinterpret_cast<const char*>(Xh + (size_t)tok_s[r] * D) + slot_of(r, item % PPR) * 16);
+  }
+  const size_t crow = (size_t)h * cfg.cap + row_off;
+  if constexpr (FORM == PASS_READ) {
+#pragma unroll
+    for (int i = 0; i < MAXM * PPR / NT; ++i) {           // whole tiles; rows past m repeat the last centre
+      const int item = tid + i * NT, r = item / PPR;
+      if (r < CT * 32)
+        dma_b128((uint32_t)(uintptr_t)(lds_void_t*)cs + (wave * 64 + i * NT) * 16, reinterpret_cast<const char*>(cent + (crow + min(r, m - 1)) * D) + slot_of(r, item % PPR) * 16);
+    }
+    if (tid < CT * 32) bs[tid] = tid < m ? bias[crow + tid] : -INFINITY;
+  } else {
+    const int cl = tid % PPR, nb = (n + NP - 1) / NP;
+    for (int j = tid / PPR; j < CT * 32; j += NT / PPR) {
+      float4 r = {0.f, 0.f, 0.f, 0.f};
+      float bj = -INFINITY;
+      if (j < m) {
+        const size_t at = (crow + j) * D + cl * 4;
+        int nj = 1;
+        if constexpr (FORM == PASS_COMBINE) {
+          constexpr int BATCH = D == 64 ? 8 : 16;
+          nj = 0;
+          for (int b = cl; b < nb; b += PPR) nj += prev.bcnt[((size_t)h * prev.nb_stride + b) * STAGE_COUNTS + j];
+          const double2* row = reinterpret_cast<const double2*>(reinterpret_cast<const double*>(prev.psum) + ((size_t)h * prev.P + (size_t)j * prev.nb_stride) * D + cl * 4);
+          double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+          for (int b0 = 0; b0 < nb; b0 += BATCH) {
+            double2 t[BATCH][2];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) { const size_t o = (size_t)min(b0 + u, nb - 1) * (D / 2); t[u][0] = row[o]; t[u][1] = row[o + 1]; }
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) if (b0 + u < nb) { s0 += t[u][0].x; s1 += t[u][0].y; s2 += t[u][1].x; s3 += t[u][1].y; }
+          }
+#pragma unroll
+          for (int o = 1; o < PPR; o <<= 1) nj += __shfl_xor(nj, o);
+          const double cnt = (double)nj;
+          r = float4{(float)(s0 / cnt), (float)(s1 / cnt), (float)(s2 / cnt), (float)(s3 / cnt)};
+        } else r = *reinterpret_cast<const float4*>(Xh + (size_t)ctok[j] * D + cl * 4);
+        if (nj > 0) {
+          float ss = fmaf(r.x, r.x, 0.f);
+          ss = fmaf(r.y, r.y, ss); ss = fmaf(r.z, r.z, ss); ss = fmaf(r.w, r.w, ss);
+#pragma unroll
+          for (int o = 1; o < PPR; o <<= 1) ss += __shfl_xor(ss, o);
+          bj = -0.5f * ss;
+          if (blockIdx.x == 0) {
+            *reinterpret_cast<float4*>(cent + at) = r;
+            *reinterpret_cast<float4*>(cent_f32 + at) = r;
+            if (cl == 0) bias[crow + j] = bj;
+          }
+        } else {                                         // an empty cluster keeps its centre
+          r = *reinterpret_cast<const float4*>(cent + at);
+          bj = bias[crow + j];
+        }
+      }
+      *reinterpret_cast<float4*>(cs + j * ROWB + slot_of(j, cl) * 16) = r;
+      if (cl == 0) bs[j] = bj;
+    }
+  }
+  wait_vmcnt<0>();
+  __syncthreads();
+
+  // scores and arg-max, as assign_f32
+  const int p = base + pg * 32 + c;
+  float best = -INFINITY, xn2 = 0.f;
+  int bidx = 0;
+  {
+    float x[D / 2];                       // this half-wave's dims: 2s + hb
+    const char* row = ps + (pg * 32 + c) * ROWB;
+#pragma unroll
+    for (int q = 0; q < PPR; ++q) {
+      const float* a = reinterpret_cast<const float*>(row + slot_of(c, q) * 16 + hb * 4);
+      x[2 * q] = a[0]; x[2 * q + 1] = a[2];
+    }
+    if (!out.psum && sp == 0) {
+#pragma unroll 8
+      for (int q = 0; q < PPR; ++q) {
+        const float4 v = *reinterpret_cast<const float4*>(row + slot_of(c, q) * 16);
+        xn2 = fmaf(v.x, v.x, xn2); xn2 = fmaf(v.y, v.y, xn2); xn2 = fmaf(v.z, v.z, xn2); xn2 = fmaf(v.w, v.w, xn2);
+      }
+    }
+    if (sp < CT) {
+      f32x16_t acc;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+      const char* tile = cs + (sp * 32 + c) * ROWB + hb * 4;
+#pragma unroll
+      for (int q = 0; q < PPR; ++q) {
+        const float* a = reinterpret_cast<const float*>(tile + slot_of(c, q) * 16);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0], x[2 * q], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[2], x[2 * q + 1], acc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int j = sp * 32 + 8 * (v >> 2) + 4 * hb + (v & 3);
+        const float s = acc[v] + bs[j];
+        if (s > best) { best = s; bidx = j; }
+      }
+    }
+  }
+  {
+    const float ob = __shfl_xor(best, 32);
+    const int oi = __shfl_xor(bidx, 32);
+    if (ob > best || (ob == best && oi < bidx)) { best = ob; bidx = oi; }
+  }
+  if (hb == 0) { sbest[sp][pg * 32 + c] = best; sidx[sp][pg * 32 + c] = bidx; }
+  __syncthreads();
+  const bool mine = sp == 0 && hb == 0 && p < n;
+  if (mine) {
+    const float ob = sbest[1][pg * 32 + c];
+    const int oi = sidx[1][pg * 32 + c];
+    if (ob > best || (ob == best && oi < bidx)) { best = ob; bidx = oi; }
+  }
+  if (!out.psum) {
+    // last pass: squared distances, and the survivors of the threshold or (first stage) the sum for it
+    const float d2 = fmaxf(xn2 - 2.f * best, 0.f);
+    const bool counts = cfg.keep_cnt != nullptr;
+    const uint64_t keep = __ballot(mine && counts && !(d2 < cfg.tau[1]));
+    double dsum = mine && cfg.dist_sum ? (double)sqrtf(d2) : 0.0;
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) dsum += __shfl_xor(dsum, o);      // (the upper half-wave holds zeros)
+    __shared__ int32_t wkept[4];
+    __shared__ double wsum[4];
+    if (sp == 0 && lane == 0) { wkept[pg] = __popcll(keep); wsum[pg] = dsum; }
+    if (mine) dist2[(size_t)h * cfg.N + p] = d2;
+    __syncthreads();
+    if (tid == 0) {
+      if (counts) cfg.keep_cnt[(size_t)h * cfg.keep_stride + blockIdx.x] = (wkept[0] + wkept[1]) + (wkept[2] + wkept[3]);
+      if (cfg.dist_sum) cfg.dist_sum[(size_t)h * gridDim.x + blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+    }
+    if (counts && cfg.surv && mine) {      // the survivors in order, for the pass that opens the next stage
+      int at = base;
+      for (int w = 0; w < pg; ++w) at += wkept[w];
+      const int t = tok_s[pg * 32 + c];
+      if ((keep >> c) & 1) cfg.surv[(size_t)h * cfg.N + at + __popc((uint32_t)keep & ((1u << c) - 1u))] = t;
+      else if (cfg.stage_of) cfg.stage_of[(size_t)h * cfg.N + t] = cfg.stage;
+    }
+    return;
+  }
+  if (sp == 0 && hb == 0) lab_s[pg * 32 + c] = mine ? bidx : -1;
+  __syncthreads();
+  const int l0 = lab_s[lane], l1 = lab_s[64 + lane];
+  auto value = [&](int r, int q) { const int col = lane + 64 * q; return *reinterpret_cast<const float*>(ps + r * ROWB + slot_of(r, col >> 2) * 16 + (col & 3) * 4); };
+  for (int j = wave; j < m; j += 8) {
+    uint64_t left[2] = {__ballot(l0 == j), __ballot(l1 == j)};
+    double sum[CPL];
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) sum[q] = 0.0;
+    const int members = __popcll(left[0]) + __popcll(left[1]);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      while (left[half]) {                // four members at a time, in their order
+        float v[4][CPL];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const bool in = left[half] != 0;
+          const int r = 64 * half + (in ? __ffsll((unsigned long long)left[half]) - 1 : 0);
+          left[half] &= left[half] - 1;
+#pragma unroll
+          for (int q = 0; q < CPL; ++q) { const float x = value(r, q); v[u][q] = in ? x : 0.f; }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int q = 0; q < CPL; ++q) sum[q] += (double)v[u][q];
+      }
+    }
+    double* row = reinterpret_cast<double*>(out.psum) + ((size_t)h * out.P + (size_t)j * out.nb_stride + blockIdx.x) * D;
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) row[lane + 64 * q] = sum[q];
+    if (lane == 0) out.bcnt[((size_t)h * out.nb_stride + blockIdx.x) * STAGE_COUNTS + j] = members;
   }
 }
 
@@ -2617,7 +2871,19 @@ static inline int chk() { return hipGetLastError() == hipSuccess ? 0 : ADACLUSTE
 
 int reduce_part_rows() { return REDUCE_ROWS; }
 int pass_sum_centres() { return ACC_MAXM; }
-int pass_points(bool wide) { return wide ? 2 * PASS_POINTS : PASS_POINTS; }
+int pass_points(int dtype, bool wide) { return dtype == ADACLUSTER_F32 ? PASS_F32_POINTS : wide ? 2 * PASS_POINTS : PASS_POINTS; }
+// fp32 stages by block sums.  Every workgroup of a head reads all of its sums: up to 2 MB that is less than the launches cost (us of
+// a call, and with update_direct_f32: 1 x 4 096 points, d=64, 16 centres, 131 KB 203 and 265; 4 x 6 000, 30 centres, 722 KB 282 and
+// 331; 4 x 4 000, d=128, 16 centres, 524 KB 341 and 417; 4 x 6 500, 30 centres, 1.6 MB 475 and 506; past the line 2 x 11 400, 40
+// centres, 3.7 MB 529 and 522; 4 x 12 000, d=64, 60 centres, 2.9 MB 656 and 648).  Many heads are not bound by latency: 30 x 6 000
+// points, d=64, 1 119 and 1 091, 60 x 1 500, d=128, 895 and 825, so a launch of more points than `points` takes the other form.
+// (Not of fewer: a head alone and many of it give the same bits up to there.)
+static constexpr int PASS_F32_BYTES = 2 << 20;
+int pass_f32_rows(int d, int N, int m0) { return min((long long)(N + PASS_F32_POINTS - 1) / PASS_F32_POINTS * min(m0, PASS_F32_CENTRES), PASS_F32_BYTES / 8ll / d); }
+bool pass_f32_fits(int d, int H, int N, int m0) {
+  const long long nb = (N + PASS_F32_POINTS - 1) / PASS_F32_POINTS, points = d == 64 ? 230000 : 91000;
+  return nb <= STAGE_SUM_BLOCKS && m0 <= (d == 64 ? PASS_F32_CENTRES : 40) && nb * m0 * d * 8 <= PASS_F32_BYTES && (long long)H * N <= points;
+}
 // Every workgroup of a head reads all of its sums: up to 128 KB they cost less than the launch they save (up to 256 KB the
 // same time either way), up to 64 centres or (d=128) 40: each 32 or 16 are another trip (of 3 000 points, d=128, 100 centres at
 // first, a call took 540 us without that limit, 477 with launches).  Past some 512 workgroups the chip is full without waves to
@@ -2689,7 +2955,7 @@ static OpenCfg open_cfg(int N, int cap, const StageRules& r, const KState* in, K
   return c;
 }
 
-int launch_stage_pass(hipStream_t s, int d, int H, int N, int n_bound, int m_bound, int cap, const KState* st, const int32_t* ulist,
+int launch_stage_pass(hipStream_t s, int dtype, int d, int H, int N, int n_bound, int m_bound, int cap, const KState* st, const int32_t* ulist,
                       const void* X, void* cent_lp, float* cent_f32, float* bias, bool wide, const StageSums* prev, const StageSums* out,
                       const PassEnd* end, const StageOpening* open) {
   AssignCfg c{1, 0, N, cap, st, ulist};
@@ -2702,13 +2968,25 @@ int launch_stage_pass(hipStream_t s, int d, int H, int N, int n_bound, int m_bou
     oc = open_cfg(N, cap, *open->rules, open->in, open->out, open->filter, *open->report);
     if (open->filter && (!oc.surv || (open->n_before + oc.items - 1) / oc.items > OPEN_COUNTS)) return ADACLUSTER_E_INTERNAL;
   }
-  const int nb = (n_bound + pass_points(wide) - 1) / pass_points(wide);
+  const int pts = pass_points(dtype, wide), nb = (n_bound + pts - 1) / pts;
   const PassSums in = prev ? PassSums{prev->psum, prev->bcnt, m_bound * nb, nb} : PassSums{}, to = out ? PassSums{out->psum, out->bcnt, m_bound * nb, nb} : PassSums{};
-  if (m_bound > ACC_MAXM || (prev && (!wide || open)) || !out != (end != nullptr)) return ADACLUSTER_E_INTERNAL;
+  if (m_bound > (dtype == ADACLUSTER_F32 ? PASS_F32_CENTRES : ACC_MAXM) || (prev && (!wide || open)) || !out != (end != nullptr)) return ADACLUSTER_E_INTERNAL;
   const dim3 g(nb, H);
+  float* dist2 = end ? end->dist2 : nullptr;
+  if (dtype == ADACLUSTER_F32) {
+    auto launch = [&](auto dim) {
+      constexpr int DIM = decltype(dim)::value;
+      const float* x = (const float*)X;
+      float* lp = (float*)cent_lp;
+      if (open) stage_pass_f32<DIM, PASS_OPEN><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to, oc);
+      else if (prev) stage_pass_f32<DIM, PASS_COMBINE><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to, oc);
+      else stage_pass_f32<DIM, PASS_READ><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to, oc);
+      return chk();
+    };
+    return d == 64 ? launch(std::integral_constant<int, 64>{}) : launch(std::integral_constant<int, 128>{});
+  }
   const bf16raw* x = (const bf16raw*)X;
   bf16raw* lp = (bf16raw*)cent_lp;
-  float* dist2 = end ? end->dist2 : nullptr;
   auto launch = [&](auto dim) {
     constexpr int DIM = decltype(dim)::value;
     if (wide) {
@@ -2782,7 +3060,9 @@ bool direct_update_fits(int dtype, int n_bound, int m_bound) {
 // sort, the reduction and the launch behind it), all bf16 with 65 query clusters: 2 x 1 500 tokens, d=64, 9 query clusters 122 (140),
 // 8 x 1 500 134 (150), 16 x 1 800 149 (161), 30 x 1 500, d=128 241 (248), 4 x 4 000, d=128 232 (248); past the line 12 x 4 000,
 // d=128 312 (308), 30 x 4 000, d=64 313 (306).
-bool cluster_stats_fits(int H, int N, int m_bound) { return N <= STATS_ITEMS && (long long)H * m_bound * N <= 3000000; }
+bool cluster_stats_fits(int dtype, int H, int N, int m_bound) {
+  return N <= STATS_ITEMS && (long long)H * m_bound * N <= (dtype == ADACLUSTER_BF16 ? 3000000 : 1500000);
+}
 int launch_cluster_stats(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int cap, const KState* st,
                          int spherical, int want_box, const void* X, const int32_t* labels, int32_t* perm, int32_t* offs, int offs_stride,
                          float* out_cent, const float* fallback, int32_t* out_sizes, float* out_mean_norm, float* out_bmin,

@@ -35,13 +35,13 @@ int launch_assign(hipStream_t s, int dtype, int d, int H, int N, int n_bound, in
                   int32_t* keep_lab = nullptr, float* keep_score = nullptr, const int32_t* seed_lab = nullptr,
                   const float* seed_score = nullptr,
                   const float* tau = nullptr, int32_t* keep_cnt = nullptr, int keep_stride = 0, double* dist_sum = nullptr);
-// A pass of a stage of Algorithm 1 with at most pass_sum_centres() centres (bf16).  An update pass (out) leaves the member sums
-// and counts of every pass_points(wide) points; launch_finalize(blk_cnt = out->bcnt, nb_stride = their number, blk_points) turns them
+// A pass of a stage of Algorithm 1 with at most pass_sum_centres() centres (bf16; fp32: pass_f32_fits()).  An update pass (out)
+// leaves the member sums and counts of every pass_points() points; launch_finalize(blk_cnt = out->bcnt, nb_stride = their number, blk_points) turns them
 // into centres, or (`wide`, where combine_fits says so) the next pass does, which then takes them as `prev` (another
 // table than its `out`).  The last pass (out NULL) leaves what `end` says.  The first pass may open the stage (`open`): it
 // then does what launch_stage_open does, from the survivors that the stage before has left.
-constexpr int STAGE_SUM_BLOCKS = 128;   // a stage of at most this many blocks of pass_points(false) may update from their sums
-struct StageSums { float* psum; int32_t* bcnt; };     // [H][m_bound * blocks][d], [H][blocks][pass_sum_centres()]
+constexpr int STAGE_SUM_BLOCKS = 128;   // a stage of at most this many blocks of pass_points() may update from their sums
+struct StageSums { float* psum; int32_t* bcnt; };     // [H][m_bound * blocks][d] (fp32 stages: doubles), [H][blocks][pass_sum_centres()]
 struct PassEnd {
   float* dist2; int32_t* keep_lab; float* keep_score; double* dist_sum;      // the last three as in launch_assign, or NULL
   const float* tau; int32_t* keep_cnt; int keep_stride; int32_t* surv; int32_t* stage_of; int stage;   // survivors of a stage whose threshold is known (keep_cnt, else NULL)
@@ -53,10 +53,12 @@ struct StageOpening {
   int n_before;                        // no head has more points in the stage that ends
 };
 int pass_sum_centres();
-int pass_points(bool wide);
+int pass_points(int dtype, bool wide);
+bool pass_f32_fits(int d, int H, int N, int m0);           // fp32: passes with block sums in all stages of a call, formed by the next pass (`wide`)
+int pass_f32_rows(int d, int N, int m0);                   // most rows of one of their tables in a head of N points
 bool combine_fits(int d, int heads, int n_bound, int m_bound);
 bool wide_fills(int heads, int n_bound);      // whether passes without `prev` take `wide` as well
-int launch_stage_pass(hipStream_t s, int d, int H, int N, int n_bound, int m_bound, int cap, const KState* st, const int32_t* ulist,
+int launch_stage_pass(hipStream_t s, int dtype, int d, int H, int N, int n_bound, int m_bound, int cap, const KState* st, const int32_t* ulist,
                       const void* X, void* cent_lp, float* cent_f32, float* bias, bool wide, const StageSums* prev, const StageSums* out,
                       const PassEnd* end, const StageOpening* open);
 int launch_seg_reduce(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int P,
@@ -78,7 +80,7 @@ int launch_finalize(hipStream_t s, int dtype, int d, int H, int mode, int m_cons
                     int nb_stride = 0, int blk_points = 0 /* of a block; 0: nb_stride blocks in every head */, const StateExport* ex = nullptr);
 // Label sort (perm, offs as launch_sort leaves them) and final statistics (launch_finalize, update_assign = 0) in one launch:
 // cluster_stats_fits() says when.
-bool cluster_stats_fits(int H, int N, int m_bound);
+bool cluster_stats_fits(int dtype, int H, int N, int m_bound);
 int launch_cluster_stats(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int cap, const KState* st,
                          int spherical, int want_box, const void* X, const int32_t* labels, int32_t* perm, int32_t* offs, int offs_stride,
                          float* out_cent, const float* fallback, int32_t* out_sizes, float* out_mean_norm, float* out_bmin,

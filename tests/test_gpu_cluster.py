@@ -306,11 +306,12 @@ def test_kcluster_stages_opened_by_their_passes(d, H, N, m0, iters):
 
 
 @pytest.mark.parametrize("dtype,d,N,m0,skew", [(B.BF16, 64, 4096, 24, 0.9), (B.BF16, 128, 4095, 24, 0.0), (B.BF16, 128, 129, 5, 0.95),
-                                               (B.F32, 64, 4096, 24, 0.9), (B.F32, 128, 2049, 20, 0.5)])
+                                               (B.F32, 64, 4096, 24, 0.9), (B.F32, 128, 2049, 41, 0.5)])
 def test_short_heads_sorted_and_summed_per_cluster(dtype, d, N, m0, skew):
     """A workgroup a cluster (few heads), or sort, reduction and combination (many): the same bits, boxes and empty clusters
     among them; `skew` of the tokens are alike, so that one cluster holds many parts."""
-    H = 3000000 // (16 * N) + 1               # past the line of cluster_stats_fits for 16 clusters
+    H = (3000000 if dtype == B.BF16 else 1500000) // (16 * N) + 1      # past the line of cluster_stats_fits for 16 clusters, and
+                                              # (fp32) on the same side as one head of the line of block sums
     rng = np.random.default_rng(23)
     X = rng.standard_normal((1, N, d)).astype(np.float32)
     alike = rng.random(N) < skew
@@ -330,6 +331,35 @@ def test_short_heads_sorted_and_summed_per_cluster(dtype, d, N, m0, skew):
             if name.startswith("k_") and a.shape[1:2] == (p.cap,):      # (rows past the count are not written)
                 a, b = a[:, :m], b[:, :m]
             assert torch.equal(b, a.expand_as(b)), name
+
+
+@pytest.mark.parametrize("d,H,N,m0,iters", [
+    (64, 1, 128, 4, 3), (64, 2, 129, 33, 3), (128, 3, 1409, 40, 3),      # one block and one point more; one tile of centres and two
+    (128, 2, 4095, 32, 2), (64, 3, 5121, 64, 3), (64, 1, 16384, 16, 3),  # the most blocks a head has
+    (64, 2, 2049, 65, 3), (128, 2, 2049, 41, 3), (64, 2, 16385, 16, 2),  # past the lines of block sums
+    (64, 2, 1025, 12, 1),                                                # a single pass, which cannot open a stage
+])
+def test_kcluster_fp32_block_sums(d, H, N, m0, iters):
+    """fp32 stages opened by their first pass, their centres formed by the next one, on either side of every line."""
+    rng = np.random.default_rng(29)
+    K = rng.standard_normal((H, N, d)).astype(np.float32)
+    K[0, ::3] *= 0.5
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=4, k_iters=iters, k_m0=m0, k_m_min=2, k_max_clusters=1000, k_max_stages=4,
+                 tau_factor=1.0, min_unassigned_frac=0.0)
+    out = B.adacluster_kcluster(p, to_dev(K, B.F32))
+    torch.cuda.synchronize()
+    check_kcluster(K, p, out, B.F32)
+    assert (out["k_count"].cpu().numpy() > m0).all()       # every head went on past its first stage
+
+
+def test_kcluster_fp32_a_point_that_is_not_finite_spoils_its_own_cluster_alone():
+    H, N, d = 1, 1000, 64
+    K, _, _ = wl.make_small(31, N, d, 12, dtype="f32", H=H)
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=4, k_iters=2, k_m0=16, k_m_min=2, k_max_clusters=16, tau_abs=1e4)
+    K[0, 300, 7] = np.inf
+    out = B.adacluster_kcluster(p, to_dev(K, B.F32))
+    C = to_np(out["k_assign_centroids"])[0, :16]
+    assert (~np.isfinite(C).all(1)).sum() == 1 and int(out["k_count"][0]) == 16
 
 
 @pytest.mark.parametrize("dtype,d,N,M", [(B.BF16, 64, 4000, 16), (B.BF16, 128, 2600, 16), (B.F32, 64, 1800, 12)])
