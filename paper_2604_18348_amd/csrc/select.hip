@@ -141,8 +141,11 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_kernel(SelectCfg cfg, con
 // One block per (query cluster, head).  Dynamic LDS: key[cap] (uint64) + flag[cap] (int).
 // Top-p, top-k and the keys of the lists (sel_keys) are compiled apart: in one kernel, whose registers and steps a top-k
 // without them then has too, top-k over 30 x 65 lists of 50 clusters took 9.4 us, now 8.1, over 48 x 1 000 140 and 115.
-template <bool TOPP, bool KEYS>
-__global__ __launch_bounds__(256) void select_kernel(SelectCfg cfg, const double* __restrict__ S,
+// D > 0: small tables are scored here, a key cluster a thread, by the chains of score_kernel: the launch before took 7 us and a
+// trip to the scores, this 2 (a workgroup reads its head's whole table: see the line in launch_select).
+struct ScoreTables { const float* q_cent; const float* k_cent; const float* k_bmin; const float* k_bmax; };
+template <bool TOPP, bool KEYS, int D, bool BOX>
+__global__ __launch_bounds__(256) void select_kernel(SelectCfg cfg, const double* __restrict__ S, ScoreTables t,
                                                      const float* __restrict__ q_mean_norm,
                                                      const int32_t* __restrict__ k_sizes,
                                                      const int32_t* __restrict__ k_count,
@@ -165,10 +168,56 @@ __global__ __launch_bounds__(256) void select_kernel(SelectCfg cfg, const double
   bool use_thr = false;          // top-k by threshold key: selected = key > thr_key, or == thr_key among the first thr_rem
   uint64_t thr_key = 0;
   int thr_rem = 0;
+  constexpr int B4 = 8, STEPS = D / (4 * B4);      // as in score_kernel
+  float4 pb[B4], nb[B4];
+  const float4 *rpos = nullptr, *rneg = nullptr;
+  if constexpr (D > 0) {
+    const size_t row = ((size_t)h * cfg.cap + min(tid, cfg.cap - 1)) * D;
+    rpos = reinterpret_cast<const float4*>((BOX ? t.k_bmax : t.k_cent) + row);
+    rneg = reinterpret_cast<const float4*>((BOX ? t.k_bmin : t.k_cent) + row);
+#pragma unroll
+    for (int u = 0; u < B4; ++u) { pb[u] = rpos[u]; if (BOX) nb[u] = rneg[u]; }
+  }
   const int kc = min(k_count[h], cfg.lds_cap);
   const bool all = full_flag[h] != 0;
-  // ---- scores of this query cluster (score_kernel)
-  {
+  // ---- scores of this query cluster
+  if constexpr (D > 0) {
+    __shared__ __attribute__((aligned(16))) double2 qs[D];
+    const bool dot = cfg.score_mode == ADACLUSTER_SCORE_DOT;
+    if (tid < D) {
+      const float q = t.q_cent[((size_t)h * cfg.Cq + i) * D + tid];
+      const bool neg = (__float_as_uint(q) >> 31) != 0u;
+      qs[tid] = double2{(dot || !neg) ? (double)q : 0.0, (!dot && neg) ? (double)q : 0.0};
+    }
+    const int nj = k_sizes[(size_t)h * cfg.cap + min(tid, cfg.cap - 1)];
+    __syncthreads();
+    if (tid < kc) {                                // (kc <= 256)
+      double sp = 0.0, sn = 0.0;
+#pragma unroll
+      for (int st = 0; st < STEPS; ++st) {
+        float4 pc[B4], nc[B4];
+#pragma unroll
+        for (int u = 0; u < B4; ++u) {
+          pc[u] = pb[u]; if (BOX) nc[u] = nb[u];
+          if (st + 1 < STEPS) { pb[u] = rpos[(st + 1) * B4 + u]; if (BOX) nb[u] = rneg[(st + 1) * B4 + u]; }
+        }
+#pragma unroll
+        for (int u4 = 0; u4 < B4; ++u4) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float pv = u == 0 ? pc[u4].x : u == 1 ? pc[u4].y : u == 2 ? pc[u4].z : pc[u4].w;
+            const float nv = !BOX ? pv : u == 0 ? nc[u4].x : u == 1 ? nc[u4].y : u == 2 ? nc[u4].z : nc[u4].w;
+            const double kp = (double)((BOX || dot) ? pv : fmaxf(pv, 0.f));
+            const double kn = (double)((BOX || dot) ? nv : fminf(nv, 0.f));
+            const double2 q2 = qs[(st * B4 + u4) * 4 + u];
+            sp = __fma_rn(q2.x, kp, sp);
+            sn = __fma_rn(q2.y, kn, sn);
+          }
+        }
+      }
+      sval[tid] = nj == 0 ? -INFINITY : all ? 0.0 : sp + sn;
+    }
+  } else {
     const double* sr = S + ((size_t)h * cfg.Cq + i) * cfg.cap;
     for (int j = tid; j < kc; j += 256) sval[j] = sr[j];
   }
@@ -424,6 +473,11 @@ __global__ __launch_bounds__(256) void select_kernel(SelectCfg cfg, const double
   if (tid == 0) sel_keys[(size_t)h * cfg.Cq + i] = wsum2[0] + wsum2[1] + wsum2[2] + wsum2[3];
 }
 
+// Elements of the key tables that the workgroups of select_kernel read in all, up to which they form the scores themselves (one
+// key cluster a thread).  A call of 4 x 4 000 tokens, d=128, 65 query clusters, 117 key clusters at most 233 -> 227 us, 16 x 1 800,
+// d=64 150 -> 145, 30 x 1 500, d=128 241 -> 236, 1 x 4 096 fp32 206 -> 203; 30 x 4 000, d=64 (15 million) 307 -> 304; past it the
+// same time either way (30 x 7 920, 256 clusters, 32 million).
+constexpr long long SELECT_SCORES = 16000000;
 int launch_select(hipStream_t s, int H, int Cq, int cap, int d, int score_mode, int select_mode, int topk,
                   float top_p, float scale, const float* q_cent, const float* q_mean_norm, const float* k_cent,
                   const float* k_bmin, const float* k_bmax, const int32_t* k_sizes, const int32_t* k_count,
@@ -437,20 +491,29 @@ int launch_select(hipStream_t s, int H, int Cq, int cap, int d, int score_mode, 
   // The kernel's dynamic-LDS limit is raised only when a launch needs more than any launch before it on this
   // device (a call that repeats an earlier shape then consists of launches only, which is what a caller that
   // captures it into a HIP graph needs).
-  auto select = [&](auto topp, auto keys) {
+  const int kb = kc_max < cap ? kc_max : cap;
+  const bool here = kb <= 256 && (long long)H * Cq * kb * d <= SELECT_SCORES;
+  auto launch = [&](auto topp, auto keys, auto dd, auto box) {
     static std::atomic<int> granted[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return ADACLUSTER_E_INTERNAL;
-    const auto kernel = select_kernel<decltype(topp)::value, decltype(keys)::value>;
+    const auto kernel = select_kernel<decltype(topp)::value, decltype(keys)::value, decltype(dd)::value, decltype(box)::value>;
     if ((int)shm > granted[dev].load()) {
       if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
         return ADACLUSTER_E_INTERNAL;
       granted[dev].store((int)shm);
     }
-    kernel<<<dim3(Cq, H), 256, shm, s>>>(c, scores, q_mean_norm, k_sizes, k_count, full_flag, sel_idx, sel_cnt, sel_keys);
+    kernel<<<dim3(Cq, H), 256, shm, s>>>(c, scores, ScoreTables{q_cent, k_cent, k_bmin, k_bmax}, q_mean_norm, k_sizes, k_count, full_flag, sel_idx, sel_cnt, sel_keys);
     return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
   };
-  const int kb = kc_max < cap ? kc_max : cap;
+  auto select = [&](auto topp, auto keys) {
+    using std::integral_constant;
+    auto boxes = [&](auto dd) {
+      return score_mode == ADACLUSTER_SCORE_BOX ? launch(topp, keys, dd, std::true_type{}) : launch(topp, keys, dd, std::false_type{});
+    };
+    if (!here) return launch(topp, keys, integral_constant<int, 0>{}, std::false_type{});
+    return d == 64 ? boxes(integral_constant<int, 64>{}) : boxes(integral_constant<int, 128>{});
+  };
   auto score = [&](auto qg, auto dd, auto box) {
     constexpr int QG = decltype(qg)::value, D = decltype(dd)::value;
     const dim3 g((kb + SCORE_THREADS - 1) / SCORE_THREADS, (Cq + QG - 1) / QG, H);
@@ -466,7 +529,8 @@ int launch_select(hipStream_t s, int H, int Cq, int cap, int d, int score_mode, 
   // 10 us, 5 a thread 13), 13 once it gives every SIMD two, 4 or (boxes, whose rows take twice the registers) 5 in between
   // (12 x 330, d=128: 17 and 20 us, 3 a thread 20 and 25; 30 x 600, d=64: 28 and 31 us, 5 and 4 a thread 34 and 43).
   const long long waves = (long long)((kb + 63) / 64) * H;
-  if (waves * ((Cq + 2) / 3) <= 1024) group(std::integral_constant<int, 3>{});
+  if (here) {}
+  else if (waves * ((Cq + 2) / 3) <= 1024) group(std::integral_constant<int, 3>{});
   else if (waves * ((Cq + 12) / 13) >= 2048) group(std::integral_constant<int, 13>{});
   else if (score_mode == ADACLUSTER_SCORE_BOX) group(std::integral_constant<int, 5>{});
   else group(std::integral_constant<int, 4>{});

@@ -53,6 +53,34 @@ def test_selection_is_bit_exact(score_mode, select_mode, topk, top_p, d):
             assert np.array_equal(got[h][i], ref[i]), (h, i, got[h][i], ref[i])
 
 
+@pytest.mark.parametrize("cap", [20, 256, 257])              # scores formed by the selection, the most of them, and by a launch
+@pytest.mark.parametrize("score_mode,select_mode", [(B.SCORE_TQ, 0), (B.SCORE_BOX, 0), (B.SCORE_BOX, 1), (B.SCORE_DOT, 1)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_scores_of_small_tables(cap, score_mode, select_mode, d):
+    Cq, topk, top_p = 65, 9, 0.8
+    counts = sorted({cap, min(cap, 65), min(cap, 64), 1})
+    H = len(counts)
+    qc, mean_norm, kcent, bmin, bmax, sizes, kcount = make_inputs(19, H, Cq, cap, counts, d)
+    qc[0, 0, ::2] = -0.0
+    full = np.zeros(H, dtype=np.int32)
+    full[-1] = 1
+    p = B.Params(H=H, N=10000, d=d, q_clusters=Cq, k_m0=8, k_m_min=4, k_max_clusters=cap - 8,
+                 score_mode=score_mode, select_mode=select_mode, topk=topk, top_p=top_p)
+    c = lambda a: torch.from_numpy(a).cuda()
+    si, sc = B.adacluster_select(p, c(qc), c(mean_norm), c(kcent), c(bmin), c(bmax), c(sizes), c(kcount), c(full))
+    got = sel_from_dev(si, sc)
+    scale = float(np.float32(1.0 / np.sqrt(np.float32(d))))
+    for h in range(H):
+        kc = kcount[h]
+        S = orc.cluster_scores(score_mode, qc[h].astype(np.float64), kcent[h, :kc].astype(np.float64),
+                               bmin[h, :kc].astype(np.float64), bmax[h, :kc].astype(np.float64), sizes[h, :kc])
+        ref = orc.select_topk(S, topk) if select_mode == 0 else orc.select_topp(S, sizes[h, :kc], mean_norm[h].astype(np.float64) * scale, top_p)
+        if full[h]:
+            ref = [np.flatnonzero(sizes[h, :kc] > 0)] * Cq
+        for i in range(Cq):
+            assert np.array_equal(got[h][i], ref[i]), (h, i, got[h][i], ref[i])
+
+
 def test_full_flag_selects_all_nonempty_and_ties_go_low():
     H, Cq, d = 2, 3, 64
     m0, nmax = 8, 24
