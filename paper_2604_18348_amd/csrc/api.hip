@@ -602,7 +602,7 @@ int run_plan_attention(const adacluster_params* p, const WS& w, hipStream_t st, 
                             D.cap + 1, k_count, sel_idx, sel_cnt, w.rng_start, w.rng_pre, w.rng_cnt, w.tiles, w.ntiles,
                             w.merge, w.nmerge, key_row_scale(p), w.krow, attn_krow_stride(D.N), w.perm_k, D.N, sel_keys));
   prof_mark(EV_PLAN, st, prof_from);
-  RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, D.Cq, D.maxtiles, scale, Q, K, V, O, w.perm_q,
+  RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, D.Cq, D.BM, attn_most_tiles(p->dtype, D.N, D.Cq, D.BM, D.maxtiles), D.maxtiles, scale, Q, K, V, O, w.perm_q,
                           w.tiles, w.ntiles, w.part_o, w.part_ml, w.merge, w.nmerge,
                           w.krow, attn_krow_stride(D.N), w.rng_start, w.rng_pre, w.rng_cnt, D.maxr, w.perm_k));
   prof_mark(EV_ATTN, st);
@@ -853,11 +853,12 @@ int adacluster_dense_attn(const adacluster_params* p, const void* Q, const void*
   hipStream_t st = (hipStream_t)stream;
   const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)D.d);
   prof_begin(st);
-  RET_IF(launch_plan_dense(st, D.H, D.N, D.maxtiles, attn_block_rows(p->dtype, D.d, D.N, 1), w.rng_start, w.rng_pre, w.rng_cnt, w.tiles, w.ntiles,
+  const DenseShape shape = attn_dense_shape(p->dtype, D.d, D.H, D.N);
+  RET_IF(launch_plan_dense(st, D.H, D.N, D.maxtiles, shape, w.rng_start, w.rng_pre, w.rng_cnt, w.tiles, w.ntiles, w.merge, w.nmerge,
                            key_row_scale(p), w.krow, attn_krow_stride(D.N)));
   prof_mark(EV_PLAN, st);
-  RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, 1, D.maxtiles, scale, Q, K, V, O, nullptr, w.tiles,
-                          w.ntiles, w.part_o, w.part_ml, nullptr, nullptr,
+  RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, 1, shape.BM, (D.N + shape.BM - 1) / shape.BM * shape.pieces, D.maxtiles, scale, Q, K, V, O, nullptr, w.tiles,
+                          w.ntiles, w.part_o, w.part_ml, shape.pieces > 1 ? w.merge : nullptr, w.nmerge,
                           w.krow, attn_krow_stride(D.N), w.rng_start, w.rng_pre, w.rng_cnt, 1, nullptr));
   prof_mark(EV_ATTN, st);
   return 0;

@@ -293,10 +293,10 @@ __global__ __launch_bounds__(256) void plan_tiles(int Cq, int maxr, int maxtiles
                 ntiles, merge, nmerge);
 }
 
-// dense: one query "cluster" over all rows, one key range [0,N)
-__global__ void plan_dense(int N, int maxtiles, int BM, int row_scale, int32_t* __restrict__ rng_start,
+// dense: one query "cluster" over all rows, one key range [0,N), in `pieces` chunks a query tile (attn_dense_shape)
+__global__ void plan_dense(int N, int maxtiles, int BM, int pieces, int slots, int row_scale, int32_t* __restrict__ rng_start,
                            int32_t* __restrict__ rng_pre, int32_t* __restrict__ rng_cnt,
-                           int32_t* __restrict__ tiles, int32_t* __restrict__ ntiles,
+                           int32_t* __restrict__ tiles, int32_t* __restrict__ ntiles, int32_t* __restrict__ merge, int32_t* __restrict__ nmerge,
                            int32_t* __restrict__ krow, size_t kstride) {
   const int h = blockIdx.x;
   if (blockIdx.y > 0) {       // the other workgroups of a head fill its row-offset table (the identity)
@@ -309,12 +309,20 @@ __global__ void plan_dense(int N, int maxtiles, int BM, int row_scale, int32_t* 
   }
   if (threadIdx.x == 0) {
     rng_start[h] = 0; rng_pre[(size_t)h * 2] = 0; rng_pre[(size_t)h * 2 + 1] = N; rng_cnt[h] = 1;
-    ntiles[h] = (N + BM - 1) / BM;
+    ntiles[h] = (N + BM - 1) / BM * pieces;
+    nmerge[h] = pieces > 1 ? (N + BM - 1) / BM : 0;
   }
   int32_t* tl = tiles + (size_t)h * maxtiles * TILE_REC;
-  for (int t = threadIdx.x; t * BM < N; t += blockDim.x) {
+  const int T = (N + 63) / 64, per_piece = (T + pieces - 1) / pieces;
+  for (int t = threadIdx.x; t / pieces * BM < N; t += blockDim.x) {
+    const int group = t / pieces, k = t - group * pieces, r0 = group * BM, rows = min(BM, N - r0);
     int32_t* t6 = tl + (size_t)t * TILE_REC;
-    t6[0] = 0; t6[1] = t * BM; t6[2] = min(BM, N - t * BM); t6[3] = 0; t6[4] = (N + 63) / 64; t6[5] = -1; t6[6] = N; t6[7] = (t * BM) & 63;
+    t6[0] = 0; t6[1] = r0; t6[2] = rows; t6[3] = k * per_piece; t6[4] = min(T, (k + 1) * per_piece);
+    t6[5] = pieces > 1 ? t : -1; t6[6] = N; t6[7] = r0 & 63;
+    if (pieces > 1 && k == 0) {
+      int32_t* m = merge + ((size_t)h * slots + group) * 4;
+      m[0] = r0; m[1] = rows; m[2] = t; m[3] = pieces;
+    }
   }
 }
 
@@ -1253,6 +1261,30 @@ int attn_block_rows(int dtype, int d, int N, int Cq) {
   if (attn_small_shape(N, Cq)) return 128;
   return d == 64 ? A64_NW * 32 : A128_NW * 32;
 }
+// Shape of a dense launch: queries a workgroup, and pieces of the key list (unnormalised partial results and a merge, as for cut
+// lists).  A launch of few query tiles leaves most of the chip idle with 256 queries a workgroup, so it takes 128 and, while that
+// fills less than a round, pieces.  Priced in steps of a key tile (0.9 us at d=64, 1.6 at d=128): rounds of resident workgroups, four
+// steps a workgroup besides its own, fewer where a CU holds one of the narrow ones alone; a merge costs its launch and 4 TB/s on
+// its partial results.  us of a call, 256 queries a workgroup and chosen: d=64, 1 x 2 500 rows 44 and 26, 12 x 2 000 38 and 28,
+// 4 x 4 000 66 and 36, 2 x 8 000 122 and 64, 1 x 16 000 234 and 166; d=128, 1 x 1 300 40 and 26, 4 x 2 000 56 and 29, 4 x 4 000 98
+// and 59, 2 x 8 000 182 and 102, 1 x 16 000 349 and 251.  12 x 8 000 rows, d=128, in two pieces of 128 queries 437, as they are 409.
+DenseShape attn_dense_shape(int dtype, int d, int H, int N) {
+  if (dtype != ADACLUSTER_BF16) return {32, 1};
+  const int wide = 8 * 32, T = (N + 63) / 64, resident = d == 64 ? 512 : 256;
+  const long long W8 = (long long)H * ((N + wide - 1) / wide), nq = (N + 127) / 128;
+  double best = (double)((W8 + resident - 1) / resident) * (T + 4) * 0.93;
+  DenseShape r{wide, 1};
+  for (int want = 1; want <= 16 && nq * want <= SPLIT_SLOTS; ++want) {
+    const int per = (T + want - 1) / want, pieces = (T + per - 1) / per;
+    if (pieces != want || (want > 1 && per < 2)) continue;      // (no empty piece)
+    const long long W = H * nq * pieces;
+    const double rounds = W <= resident ? (d == 64 ? 0.6 : 0.75) : 1.15 * (double)((W + 2 * resident - 1) / (2 * resident));
+    const double merge = pieces == 1 ? 0.0 : (d == 64 ? 10.0 : 6.0) + (double)H * N * pieces * (d + 2) * 2e-6 / (d == 64 ? 0.9 : 1.6);
+    const double cost = rounds * (per + 4) + merge;
+    if (cost < best) { best = cost; r = {128, pieces}; }
+  }
+  return r;
+}
 int attn_block_rows_min(int dtype) { return dtype == ADACLUSTER_BF16 ? 128 : 32; }
 int attn_block_rows_max(int dtype) { return dtype == ADACLUSTER_BF16 ? 256 : 32; }
 
@@ -1278,6 +1310,11 @@ bool attn_rows_listed(int dtype, int d, int H, int N, int Cq) {
 
 int attn_tile_record() { return TILE_REC; }
 int attn_split_slots() { return SPLIT_SLOTS; }
+// Tiles of a head that the grid of a sparse launch is sized for, at least what it can have.  Workgroups go to the CUs in turn, so
+// those without work leave places empty that a small launch would have used: where no list is cut, none for pieces.
+int attn_most_tiles(int dtype, int N, int Cq, int BM, int maxtiles) {
+  return dtype == ADACLUSTER_BF16 && (N + 63) / 64 <= 2 * MIN_CHUNK ? N / BM + Cq + 1 : maxtiles;
+}
 
 // Most pieces a key list of the fp32 kernel may go in (see pick_tile).  From some 1 024 tiles on there are two rounds of whole
 // ones (d=128), and the partial results of every row and the launch that combines them cost what the last round leaves idle
@@ -1347,13 +1384,14 @@ int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int max
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
 }
 
-int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, int BM, int32_t* rng_start, int32_t* rng_pre,
-                      int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles, int row_scale, int32_t* krow, size_t kstride) {
-  plan_dense<<<dim3(H, 9), 256, 0, s>>>(N, maxtiles, BM, row_scale, rng_start, rng_pre, rng_cnt, tiles, ntiles, krow, kstride);
+int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, DenseShape shape, int32_t* rng_start, int32_t* rng_pre,
+                      int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles, int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride) {
+  plan_dense<<<dim3(H, 9), 256, 0, s>>>(N, maxtiles, shape.BM, shape.pieces, SPLIT_SLOTS, row_scale, rng_start, rng_pre, rng_cnt, tiles, ntiles, merge,
+                                        nmerge, krow, kstride);
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
 }
 
-int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int maxtiles, float scale,
+int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int BM, int most, int maxtiles, float scale,
                      const void* Q, const void* K, const void* V, void* O, const int32_t* perm_q,
                      const int32_t* tiles, const int32_t* ntiles, float* part_o, float* part_ml,
                      const int32_t* merge, const int32_t* nmerge, const int32_t* krow, size_t kstride,
@@ -1361,19 +1399,19 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
   AttnArgs a{Q, K, V, O, perm_q, tiles, ntiles, H, N, Cq, maxtiles,
              scale * 1.4426950408889634f,
              (Cq == 1 || (size_t)4 * N * d <= ((size_t)8 << 20)) ? 1 : 0,
-             part_o, part_ml, SPLIT_SLOTS, attn_block_rows(dtype, d, N, Cq), krow, kstride,
+             part_o, part_ml, SPLIT_SLOTS, BM, krow, kstride,
              rng_start, rng_pre, rng_cnt, maxr, perm_k, dtype == ADACLUSTER_F32 ? attn_f32_splits(H, N, Cq) : 1, {}};
   if (a.splits > 1) a.pieces = d == 64 ? f32_pieces<64>(N) : f32_pieces<128>(N);
-  dim3 g((maxtiles + 7) / 8 * 8, H);
+  dim3 g((most + 7) / 8 * 8, H);
   if (dtype == ADACLUSTER_BF16) {
-    if (attn_small_shape(N, Cq)) {
+    if (BM == 128) {
       if (d == 64) attn_mfma<64, 4, 2, 4, 0><<<g, 256, 0, s>>>(a);
       else attn_mfma<128, 4, 2, 2, 2><<<g, 256, 0, s>>>(a);
     } else {
       if (d == 64) attn_mfma<64, A64_NW, A64_NBUF, A64_MINB, A64_VPRE><<<g, A64_NW * 64, 0, s>>>(a);
       else attn_mfma<128, A128_NW, A128_NBUF, A128_MINB, A128_VPRE><<<g, A128_NW * 64, 0, s>>>(a);
     }
-    if (merge && (N + 63) / 64 > 2 * MIN_CHUNK) {      // the chunks of cut key lists (none for the dense branch)
+    if (merge && (Cq == 1 || (N + 63) / 64 > 2 * MIN_CHUNK)) {      // the chunks of cut key lists
       if (d == 64) attn_merge<64><<<dim3(MERGE_GROUPS, H, 4), 256, 0, s>>>(a, merge, nmerge);
       else attn_merge<128><<<dim3(MERGE_GROUPS, H, 4), 256, 0, s>>>(a, merge, nmerge);
     }

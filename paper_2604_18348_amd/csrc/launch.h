@@ -153,6 +153,7 @@ int launch_quest_scores(hipStream_t s, int dtype, int form, int clamp, int H, in
 int launch_mfma_probe(hipStream_t s, int iters, float* sink, size_t sink_floats, double* flops);
 int attn_f32_splits(int H, int N, int Cq);   // most pieces a key list of the fp32 kernel may go in
 int attn_tile_record();      // ints per query-tile record
+int attn_most_tiles(int dtype, int N, int Cq, int BM, int maxtiles);
 int attn_split_slots();      // partial slots per head for the chunks of cut key lists (also extra tile records)
 bool plan_reads_lengths(int Cq);   // whether launch_plan_sparse has a use for the lengths of the lists
 int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
@@ -161,14 +162,16 @@ int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int max
                        int32_t* rng_start, int32_t* rng_pre, int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles,
                        int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride, const int32_t* perm_k, int N,
                        const int32_t* lengths /* [H][Cq] keys of every list, or NULL: not known beforehand */);
-int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, int BM, int32_t* rng_start, int32_t* rng_pre,
-                      int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles, int row_scale, int32_t* krow, size_t kstride);
+struct DenseShape { int BM, pieces; };       // queries a workgroup, chunks of the key list
+DenseShape attn_dense_shape(int dtype, int d, int H, int N);
+int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, DenseShape shape, int32_t* rng_start, int32_t* rng_pre,
+                      int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles, int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride);
 // entries per (head, query cluster) of the table of key rows (times row_scale) that the attention kernels load by
 size_t attn_krow_stride(int N);
 bool attn_rows_listed(int dtype, int d, int H, int N, int Cq);    // the planning step writes every key row of a list to a table
 int launch_attn_stats(hipStream_t s, int H, int Cq, int maxr, int maxtiles, const KState* st, const int32_t* tiles,
                       const int32_t* ntiles, const int32_t* rng_pre, const int32_t* rng_cnt, adacluster_head_stats* out);
-int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int maxtiles, float scale,
+int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int BM /* as planned */, int most /* tiles of a head */, int maxtiles, float scale,
                      const void* Q, const void* K, const void* V, void* O, const int32_t* perm_q,
                      const int32_t* tiles, const int32_t* ntiles, float* part_o, float* part_ml,
                      const int32_t* merge /* NULL: no cut lists */, const int32_t* nmerge,

@@ -75,6 +75,22 @@ def test_dense_attention_matches_oracle(dtype, d, N):
         print("dense", dtype, d, N, h, check(O[h], orc.dense_attention(Q[h], K[h], V[h]), dtype))
 
 
+@pytest.mark.parametrize("d,H,N", [(64, 1, 129), (64, 2, 2500), (128, 1, 1300), (128, 2, 2049), (64, 9, 1025), (128, 1, 4100), (64, 1, 16385)])
+def test_dense_attention_of_small_launches(d, H, N):
+    """128 queries a workgroup, whole key lists or pieces of them (the last one short), and heads left over by the eight XCDs."""
+    rng = np.random.default_rng(N)
+    Q, K, V = (wl.round_bf16_f32(rng.standard_normal((H, N, d)).astype(np.float32)) for _ in range(3))
+    Q[0, 0] *= 40.0                             # one query's scores far above the others'
+    Q = wl.round_bf16_f32(Q)
+    p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=1, k_m0=4, k_m_min=1, k_max_clusters=8)
+    O = to_np(B.adacluster_dense_attn(p, to_dev(Q, B.BF16), to_dev(K, B.BF16), to_dev(V, B.BF16)))
+    rows = np.unique(np.concatenate([[0, N - 1], np.arange(0, N, max(1, N // 200))]))
+    for h in {0, H - 1}:
+        S = Q[h, rows].astype(np.float64) @ K[h].astype(np.float64).T / np.sqrt(d)
+        P = np.exp(S - S.max(1, keepdims=True))
+        check(O[h, rows], (P / P.sum(1, keepdims=True)) @ V[h].astype(np.float64), B.BF16)
+
+
 @pytest.mark.parametrize("dtype", [B.BF16, B.F32])
 def test_selecting_every_cluster_reproduces_dense(dtype):
     Cq, Ck = 5, 23
