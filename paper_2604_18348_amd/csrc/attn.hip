@@ -567,8 +567,11 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
   // Soft-max state of this lane's query: probabilities are taken relative to a reference mref that is only
-  // moved when it has to be (see soft-max below); lrun is the sum of the probabilities so far.
-  float mref = -INFINITY, lrun = 0.f;
+  // moved when it has to be (see soft-max below); lrun is the sum of the probabilities so far.  The reference starts at
+  // the lowest value that is finite when scaled too: every score above -inf is far enough above it to move it, and tiles
+  // of -inf alone, at the start of the share or all through it, leave it there with a sum and an accumulator of zero (from
+  // -inf they would make both NaN, and the launch of small dense calls, whose shares start anywhere in a list, with them).
+  float mref = -3.402823466e38f / fmaxf(a.scale_log2e, 1.f), lrun = 0.f;
 
   // Where a 16-byte chunk sits inside its (unpadded) tile row: chunk q of row r is in slot q ^ swz(r).  A row
   // is 256 B (d=128: every row starts at bank 0) or 128 B (d=64: rows two apart do), so the slot alone decides
@@ -699,8 +702,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
     }
     // Soft-max.  p = 2^((s - mref) scale): any reference gives the same normalised result as long as nothing
     // overflows, so no maximum is taken per tile.  The row sum of the tile tells when the reference is too
-    // low (or still -inf, on the first tile; a masked score against that gives NaN, caught by the same test):
-    // only then is the tile's maximum taken, the reference moved up to it and the accumulator rescaled.
+    // low (on the first tile with a score above -inf the sum is +inf): only then is the tile's maximum taken,
+    // the reference moved up to it and the accumulator rescaled.
     bf16x8_t pf[2][2];
     float rsum;
     auto probabilities = [&]() __attribute__((always_inline)) {
@@ -731,7 +734,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int v = 0; v < 16; ++v) tmax = fmaxf(tmax, sacc[kb][v]);
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32));           // finite: every tile holds a valid key
+      tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
       const float mnew = fmaxf(mref, tmax);
       const float alpha = __builtin_amdgcn_exp2f((mref - mnew) * sc);
       mref = mnew;
@@ -855,7 +858,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
       if (hb == 0) { a.part_ml[so * 2] = mref; a.part_ml[so * 2 + 1] = l; }
       return;
     }
-    const float inv = l > 0.f ? 1.0f / l : 0.f;
+    const float inv = l > 0.f ? 1.0f / l : total > 0 ? NAN : 0.f;      // (no key: zero; no score above -inf: NaN, as 0 / 0)
     if (qtok < 0) return;
     bf16raw* orow = Oh + (size_t)qtok * D;
 #pragma unroll
@@ -1171,7 +1174,8 @@ __global__ __launch_bounds__(256) void attn_merge_f32(AttnArgs a, int splits) {
 // merge of the chunks of cut key lists
 // ------------------------------------------------------------------------------------------
 // O = sum_s 2^((m_s - m) scale) O_s / sum_s 2^((m_s - m) scale) l_s for every row of the cut query tiles,
-// with m = max_s m_s; a chunk always holds at least one key, so every m_s is finite and l_s > 0.
+// with m = max_s m_s.  Every m_s is finite; a chunk all of whose scores are -inf has l_s = 0 and O_s = 0 (under the lowest
+// reference there is), and where that is true of every chunk the row is NaN, as 0 / 0.
 // MERGE_GROUPS workgroups a head and row group go over the tiles: mostly there is little or nothing to merge, and one for every
 // slot, 15 360 for 30 heads, took 5 us to find that out.
 constexpr int MERGE_GROUPS = 16;
@@ -1213,7 +1217,7 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a, const int32_t* __r
           o.x = fmaf(w, os[s].x, o.x); o.y = fmaf(w, os[s].y, o.y); o.z = fmaf(w, os[s].z, o.z); o.w = fmaf(w, os[s].w, o.w);
         }
       }
-      const float inv = l > 0.f ? 1.0f / l : 0.f;
+      const float inv = l > 0.f ? 1.0f / l : NAN;
       const int tok = pq ? pq[row0 + r] : row0 + r;
       uint2 out;
       out.x = pack_bf16x2(o.x * inv, o.y * inv);

@@ -91,6 +91,62 @@ def test_dense_attention_of_small_launches(d, H, N):
         check(O[h, rows], (P / P.sum(1, keepdims=True)) @ V[h].astype(np.float64), B.BF16)
 
 
+def reference_with_dead_keys(Q, K, V, dead, scale):
+    """Softmax in fp64 over the keys that are not dead (scores of -inf weigh nothing)."""
+    live = np.setdiff1d(np.arange(K.shape[0]), dead)
+    S = Q.astype(np.float64) @ K[live].astype(np.float64).T * scale
+    P = np.exp(S - S.max(1, keepdims=True))
+    return (P / P.sum(1, keepdims=True)) @ V[live].astype(np.float64)
+
+
+@pytest.mark.parametrize("d,H,N", [(64, 1, 2500), (128, 1, 1300), (128, 2, 2049),          # in pieces of the key list
+                                   (64, 30, 545), (128, 9, 1025), (64, 1, 37)])             # whole lists
+def test_bf16_scores_of_minus_infinity_weigh_nothing(d, H, N):
+    """Queries are positive and dead keys -inf, so whole key tiles have no other score, the first ones or the last ones of a
+    list or of its pieces: they add nothing, and a query all of whose scores are -inf gets NaN, as exp(-inf) / sum exp(-inf)
+    is.  At scale 2 the lowest finite score would leave the range of a float when scaled."""
+    rng = np.random.default_rng(31)
+    Q = wl.round_bf16_f32(rng.random((H, N, d)).astype(np.float32) + 0.1)
+    K, V = (wl.round_bf16_f32(rng.standard_normal((H, N, d)).astype(np.float32)) for _ in range(2))
+    tile = np.arange(N) // 64
+    for dead, scale in ((np.arange(N * 3 // 4, N), d ** -0.5), (np.arange(min(N - 1, 161)), d ** -0.5), (np.arange(N - 1), 2.0),
+                        (np.arange(1, N), 2.0), (np.flatnonzero(tile % 2 == 0)[:N - 1], d ** -0.5), (np.arange(0, N, 3), d ** -0.5)):
+        K2 = K.copy()
+        K2[:, dead] = -np.inf
+        p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=1, k_m0=1, k_m_min=1, k_max_clusters=1, softmax_scale=scale)
+        O = to_np(B.adacluster_dense_attn(p, to_dev(Q, B.BF16), to_dev(K2, B.BF16), to_dev(V, B.BF16)))
+        for h in (0, H - 1):
+            check(O[h], reference_with_dead_keys(Q[h], K[h], V[h], dead, scale), B.BF16)
+    K2[:] = -np.inf
+    assert np.all(np.isnan(to_np(B.adacluster_dense_attn(p, to_dev(Q, B.BF16), to_dev(K2, B.BF16), to_dev(V, B.BF16)))))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_bf16_cut_lists_with_dead_keys(d):
+    """A list of every cluster, four times the mean list and so cut into chunks: the first clusters hold -inf keys alone, more
+    of them than a chunk.  The others have a cluster of live keys each, one a cluster of dead ones, one none."""
+    H, N, Cq, Ck = 1, 6000, 8, 23
+    rng = np.random.default_rng(37)
+    Q = wl.round_bf16_f32(rng.random((H, N, d)).astype(np.float32) + 0.1)
+    K, V = (wl.round_bf16_f32(rng.standard_normal((H, N, d)).astype(np.float32)) for _ in range(2))
+    ql, kl = (rng.integers(0, c, (H, N)).astype(np.int32) for c in (Cq, Ck))
+    dead = np.flatnonzero(kl[0] < 10)
+    K2 = K.copy()
+    K2[:, dead] = -np.inf
+    sel = [[np.arange(Ck), np.array([3]), np.zeros(0)] + [np.array([i + 9]) for i in range(3, Cq)]]
+    sel = [[s.astype(np.int64) for s in rows] for rows in sel]
+    got = run_sparse(Q, K2, V, ql, kl, sel, B.BF16, Cq, Ck)[0]
+    for i in range(Cq):
+        rows = ql[0] == i
+        keys = np.isin(kl[0], sel[0][i])
+        if i == 1:
+            assert np.all(np.isnan(got[rows]))
+        elif i == 2:
+            assert np.all(got[rows] == 0)
+        else:
+            check(got[rows], reference_with_dead_keys(Q[0][rows], K[0], V[0], np.union1d(dead, np.flatnonzero(~keys)), d ** -0.5), B.BF16)
+
+
 @pytest.mark.parametrize("dtype", [B.BF16, B.F32])
 def test_selecting_every_cluster_reproduces_dense(dtype):
     Cq, Ck = 5, 23
