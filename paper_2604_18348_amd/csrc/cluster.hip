@@ -358,6 +358,10 @@ __device__ __forceinline__ int survivor_at(const int32_t* pre, int nb, int items
   return lo * items + p - pre[lo];
 }
 
+// A value that is the same in every lane, for the compiler too.  What is read from LDS counts as different from lane to lane, and a
+// branch or loop on it around a barrier as one that lanes may take apart.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // The opening of a stage by every workgroup (x) of a head (y) for itself: its points, centres and where those go, and the survivors'
 // prefix of nb counts.  False: the head is done.
 __device__ __forceinline__ bool open_stage(const OpenCfg& oc, int h, int32_t* pre, int& nbo, int& n, int& m, int& row_off) {
@@ -375,7 +379,7 @@ __device__ __forceinline__ bool open_stage(const OpenCfg& oc, int h, int32_t* pr
     nbo = min((min(o.ucount, oc.N) + oc.items - 1) / oc.items, OPEN_COUNTS);
     s.ccount = o.ccount + o.m_t; s.stage = o.stage + 1; s.full = o.full;
     survivor_prefix(nbo, c0, pre);
-    s.ucount = pre[nbo];
+    s.ucount = uniform(pre[nbo]);
   }
   loop_head(s, oc.N, oc.n_max, oc.m0, oc.m_min, oc.max_stages, oc.u_min);
   if (blockIdx.x == 0) write_state(oc, h, tid, s);
@@ -2479,9 +2483,10 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
     t2 = t * t;
     if (h == 0 && tid == 0) { cfg.tc.out[0] = t; cfg.tc.out[1] = t2; }
   } else t2 = cfg.tau[1];
-  if (!s_st.active) return;                 // closed before
-  // By one thread, with a barrier behind it: a stage ends with `left` points, and the loop goes on or not.  (One branch for both:
-  // of two, one at the loop's end and one at its head, the compiler lets the thread's wave go on without it, past the barrier.)
+  if (!uniform(s_st.active)) return;        // closed before
+  // By one thread, with a barrier behind it: a stage ends with `left` points, and the loop goes on or not.  Whatever the loop
+  // and its trip counts read of the state is made uniform: the state is in LDS, and with a branch for this thread at the loop's end
+  // and another at its head the compiler once let the rest of its wave go on without it, past the barrier.
   auto next_stage = [&](int left) __attribute__((always_inline)) {
     NewState s{left, s_st.ccount + s_st.m_t, 0, s_st.stage + 1, 0, s_st.full, 0};
     loop_head(s, cfg.N, cfg.n_max, cfg.m0, cfg.m_min, cfg.max_stages, cfg.u_min);
@@ -2523,7 +2528,7 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
     return run;
   };
   if (cfg.dist2) {
-    const int n0 = min(s_st.ucount, SMALL_NU), stage0 = s_st.stage;
+    const int n0 = uniform(min(s_st.ucount, SMALL_NU)), stage0 = uniform(s_st.stage);
     for (int p = tid; p < n0; p += NT) fs[p] = cfg.dist2[(size_t)h * cfg.N + p];
     __syncthreads();
     const int left = filter(n0, nullptr, cfg.ulist[(stage0 + 1) & 1] + (size_t)h * cfg.N, stage0);
@@ -2533,10 +2538,10 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
   } else if (cfg.surv) {
     // the stage that ended left its survivors: they become U, as stage_open would have moved them
     __shared__ int32_t pre[OPEN_COUNTS + 1];
-    const int nb = min((min(s_st.ucount, cfg.N) + cfg.items - 1) / cfg.items, OPEN_COUNTS);
+    const int nb = uniform(min((min(s_st.ucount, cfg.N) + cfg.items - 1) / cfg.items, OPEN_COUNTS));
     survivor_prefix(nb, cfg.cnt[(size_t)h * cfg.cnt_stride + min(tid, cfg.cnt_stride - 1)], pre);
     int32_t* u = cfg.ulist[(s_st.stage + 1) & 1] + (size_t)h * cfg.N;
-    const int total = min(pre[nb], SMALL_NU);
+    const int total = uniform(min(pre[nb], SMALL_NU));
     for (int p = tid; p < total; p += NT) u[p] = cfg.surv[(size_t)h * cfg.N + survivor_at(pre, nb, cfg.items, p)];
     __syncthreads();
     if (tid == 0) next_stage(total);
@@ -2548,8 +2553,8 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
   const int gl = 2 * ((lane >> 4) & 1) + ((i16 & 3) >> 1);
   const char* xw = xs[wave] + vrow * SROWB + gl * 16 + 8 * (i16 & 1);
 
-  while (s_st.active) {
-    const int n = min(s_st.ucount, SMALL_NU), m = min(s_st.m_t, SMALL_M), row_off = s_st.ccount, stage = s_st.stage;
+  while (uniform(s_st.active)) {
+    const int n = uniform(min(s_st.ucount, SMALL_NU)), m = uniform(min(s_st.m_t, SMALL_M)), row_off = uniform(s_st.ccount), stage = uniform(s_st.stage);
     const int32_t* uin = cfg.ulist[stage & 1] + (size_t)h * cfg.N;
     int32_t* uout = cfg.ulist[(stage + 1) & 1] + (size_t)h * cfg.N;
     const bf16raw* Xh = X + (size_t)h * cfg.N * D;

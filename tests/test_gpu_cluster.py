@@ -305,6 +305,26 @@ def test_kcluster_stages_opened_by_their_passes(d, H, N, m0, iters):
     assert (out["k_count"].cpu().numpy() > m0).all()       # every head went on past its first stage
 
 
+@pytest.mark.parametrize("iters", [1, 3])            # the launch finds its first stage opened, or opens it itself
+@pytest.mark.parametrize("d", [64, 128])
+def test_kcluster_late_stages_end_where_each_head_does(d, iters):
+    """One launch runs the late stages of every head, a workgroup each: heads that have no late stage, one, some, and as many as
+    there may be, by the number of groups that their tokens lie in."""
+    H, N, m0 = 5, 2011, 20
+    rng = np.random.default_rng(43)
+    K = np.zeros((H, N, d))
+    for h, groups in enumerate((3, 12, 30, 60, 700)):
+        K[h] = 1.5 * rng.standard_normal((groups, d))[rng.integers(0, groups, N)]
+    K = wl.round_bf16_f32((K + 0.25 * rng.standard_normal((H, N, d))).astype(np.float32))
+    p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=4, k_iters=iters, k_m0=m0, k_m_min=3, k_max_clusters=3000, k_max_stages=9,
+                 tau_abs=0.6 * d ** 0.5, min_unassigned_frac=0.01)
+    out = B.adacluster_kcluster(p, to_dev(K, B.BF16))
+    torch.cuda.synchronize()
+    check_kcluster(K, p, out, B.BF16)
+    stages = (np.diff(out["k_stage_offs"].cpu().numpy(), axis=1) > 0).sum(1)
+    assert stages[0] == 1 and 1 < stages[2] < 9 and stages[4] == 9, stages
+
+
 @pytest.mark.parametrize("dtype,d,N,m0,skew", [(B.BF16, 64, 4096, 24, 0.9), (B.BF16, 128, 4095, 24, 0.0), (B.BF16, 128, 129, 5, 0.95),
                                                (B.F32, 64, 4096, 24, 0.9), (B.F32, 128, 2049, 41, 0.5)])
 def test_short_heads_sorted_and_summed_per_cluster(dtype, d, N, m0, skew):
