@@ -442,7 +442,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   StageFilter filter{};                            // how the stage before ended
   // Stages with few blocks of points and few centres (bf16) update from block sums; they are opened by their own first pass,
   // from the survivors that the stage before left as a list (filter.surv; the first stage: every token).
-  const bool f32_sums = p->dtype == ADACLUSTER_F32 && pass_f32_fits(D.d, D.H, D.N, m_bound);
+  const bool f32_sums = p->dtype == ADACLUSTER_F32 && pass_f32_fits(D.d, D.N, m_bound);
   auto sums_fit = [&] {
     if (p->dtype == ADACLUSTER_F32) return f32_sums;
     const int pts = pass_points(p->dtype, false);
@@ -499,10 +499,10 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     // A small stage (few blocks of points, few centres) updates its centres from the member sums that a pass leaves per
     // block: no label sort and no segmented reduction in between, and where all of them together are small no launch either.
     const bool block_sums = sums_fit();
-    const bool combine = block_sums && (p->dtype == ADACLUSTER_F32 || combine_fits(D.d, heads, n_bound, m_bound));
-    const bool wide = combine || (block_sums && wide_fills(heads, n_bound));
+    const bool f32 = p->dtype == ADACLUSTER_F32, combine = block_sums && (f32 ? pass_f32_combines : combine_fits)(D.d, heads, n_bound, m_bound);
+    const bool wide = combine || (block_sums && !f32 && wide_fills(heads, n_bound));
     const int pts = pass_points(p->dtype, wide), nblk = (n_bound + pts - 1) / pts;
-    const StageSums sums[2] = {{w.bsum, w.bcnt}, {w.bsum + (size_t)D.H * m_bound * nblk * D.d * (p->dtype == ADACLUSTER_F32 ? 2 : 1), w.bcnt + (size_t)D.H * nblk * pass_sum_centres()}};
+    const StageSums sums[2] = {{w.bsum, w.bcnt}, {w.bsum + (size_t)D.H * m_bound * nblk * D.d * (f32 ? 2 : 1), w.bcnt + (size_t)D.H * nblk * pass_sum_centres()}};
     const int counted = block_sums ? pts : stage_points_per_count(p->dtype);      // points per survivor count and distance sum of the last pass
     // (a stage of block sums has no other use for the array; a single pass would read and write it)
     int32_t* const surv = block_sums && p->k_iters > 1 ? w.labels_tmp : nullptr;
@@ -519,10 +519,13 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
         RET_IF(launch_stage_pass(st, p->dtype, D.d, D.H, D.N, n_bound, m_bound, D.cap, cur, ul, K, w.cent_lp, k_assign, w.bias, wide,
                                  combine && it > 0 ? &sums[(it - 1) & 1] : nullptr, update ? &sums[combine ? it & 1 : 0] : nullptr,
                                  update ? nullptr : &end, pass_opens && it == 0 ? &opening : nullptr));
-        if (update && !combine)
+        if (update && !combine && f32) {
+          RET_IF(launch_form_centres(st, D.d, D.H, n_bound, m_bound, D.cap, cur, sums[0], w.cent_lp, k_assign, w.bias));
+        } else if (update && !combine) {
           RET_IF(launch_finalize(st, p->dtype, D.d, D.H, 1, 0, m_bound, m_bound * nblk, D.cap, 0, cur, 0, 1, 0,
                                  nullptr, 0, nullptr, w.bsum, w.pnorm, w.pmin, w.pmax, nullptr, w.cent_lp,
                                  k_assign, w.bias, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.bcnt, nblk, pts));
+        }
         continue;
       }
       // (the last pass of stage 0 runs over all points against the first-stage centres as they will stay:

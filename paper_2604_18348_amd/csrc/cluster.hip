@@ -1117,30 +1117,65 @@ __global__ __launch_bounds__(NS * 64 * (ASSIGN_POINTS_F32 / 32), 4) void assign_
 // ------------------------------------------------------------------------------------------
 // A pass of a stage of Algorithm 1 with at most PASS_F32_CENTRES centres, fp32: what stage_pass is for bf16
 // ------------------------------------------------------------------------------------------
-// A workgroup is PASS_F32_POINTS points in four groups of 32, eight waves: a group and one of two tiles of 32 centres each.  Scores
-// and labels are those of assign_f32, to the bit.  An update pass then leaves the members' sums: a wave takes every eighth centre,
-// finds its members by two ballots over the labels, and adds their rows out of LDS, a lane a column.  Sums are formed in fp64 and
-// rounded once, by the mean: the same members give the same centre in every stage, wherever in U they are (as in
-// update_direct_f32, whose order does not depend on that), so that such centres tie exactly.  A call therefore takes the one or
-// the other for all of its stages.  (fp64 sums there as well: 6 000 points, d=64, 25 -> 43 us a launch.)
-// Latency bound, 8-10 us: it takes the place of an assignment (5) and an update by label scan (5-7), and opens its stage
-// (stage_open, 6-7).
+// A workgroup is a block of PASS_F32_POINTS points in four groups of 32, eight waves: a group and one of two tiles of 32 centres each.
+// Scores and labels are those of assign_f32, to the bit.  An update pass then leaves the members' sums: a wave takes every eighth
+// centre, finds its members by two ballots over the labels, and adds their rows out of LDS, a lane a column.  Sums are formed in
+// fp64, by blocks and then over the blocks (block_mean_f32), and rounded once, by the mean: the same members give the same centre
+// in every stage, wherever in U they are (as in update_direct_f32, whose order does not depend on that), so that such centres tie
+// exactly.  A call therefore takes the one or the other for all of its stages, and by its width, tokens and centres alone, so that a
+// head has the same bits among any number of others.  (fp64 sums there as well: 6 000 points, d=64, 25 -> 43 us a launch.)
+// Latency bound in small launches, 7-10 us: it takes the place of an assignment (5) and half of an update by label scan (5-7), and
+// opens its stage (stage_open, 6-7).  In large ones a CU holds three workgroups, at d=128 one (102 KB of LDS).
+// The blocks of a head start at another workgroup than those of the head before: workgroups go to the XCDs in turn, and where the
+// blocks of a head are a multiple of eight, the first ones, which late stages have left, would all be on the first XCDs (24 x 4 000
+// points, d=128, 360 -> 320 us a key clustering, 60 x 4 000 699 -> 616).
 constexpr int PASS_F32_POINTS = 128, PASS_F32_CENTRES = 64;
+// Mean of the members of centre j, columns 4 cl .. 4 cl + 3, from the sums of the blocks in their order, and the number of members (0: no
+// mean).  By the D / 4 lanes of a centre together.
+template <int D>
+__device__ __forceinline__ float4 block_mean_f32(const PassSums& sums, int h, int j, int nb, int cl, int& nj) {
+  constexpr int LPC = D / 4, BATCH = D == 64 ? 8 : 16;
+  nj = 0;
+  for (int b = cl; b < nb; b += LPC) nj += sums.bcnt[((size_t)h * sums.nb_stride + b) * STAGE_COUNTS + j];
+  const double2* row = reinterpret_cast<const double2*>(reinterpret_cast<const double*>(sums.psum) + ((size_t)h * sums.P + (size_t)j * sums.nb_stride) * D + cl * 4);
+  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+  for (int b0 = 0; b0 < nb; b0 += BATCH) {
+    double2 t[BATCH][2];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) { const size_t o = (size_t)min(b0 + u, nb - 1) * (D / 2); t[u][0] = row[o]; t[u][1] = row[o + 1]; }
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) if (b0 + u < nb) { s0 += t[u][0].x; s1 += t[u][0].y; s2 += t[u][1].x; s3 += t[u][1].y; }
+  }
+#pragma unroll
+  for (int o = 1; o < LPC; o <<= 1) nj += __shfl_xor(nj, o);
+  const double cnt = (double)nj;
+  return float4{(float)(s0 / cnt), (float)(s1 / cnt), (float)(s2 / cnt), (float)(s3 / cnt)};
+}
+// ... and the bias of centre r in the arg-max, -|r|^2 / 2.
+template <int D>
+__device__ __forceinline__ float centre_bias_f32(const float4& r) {
+  float ss = fmaf(r.x, r.x, 0.f);
+  ss = fmaf(r.y, r.y, ss); ss = fmaf(r.z, r.z, ss); ss = fmaf(r.w, r.w, ss);
+#pragma unroll
+  for (int o = 1; o < D / 4; o <<= 1) ss += __shfl_xor(ss, o);
+  return -0.5f * ss;
+}
 template <int D, int FORM>
 __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void stage_pass_f32(const float* __restrict__ X, AssignCfg cfg, float* __restrict__ cent,
                                                                        float* __restrict__ cent_f32, float* __restrict__ bias,
                                                                        float* __restrict__ dist2, PassSums prev, PassSums out, OpenCfg oc) {
+  constexpr bool OPEN = FORM == PASS_OPEN;
   constexpr int NT = 512, NP = PASS_F32_POINTS, MAXM = PASS_F32_CENTRES, ROWB = D * 4, PPR = D / 4, CPL = D / 64;
   const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 31, hb = lane >> 5, pg = wave & 3, sp = wave >> 2;
   int n, m, row_off, nbo = 0;
-  __shared__ int32_t pre[FORM == PASS_OPEN ? OPEN_COUNTS + 1 : 1], ctok[FORM == PASS_OPEN ? MAXM : 1];
-  if constexpr (FORM == PASS_OPEN) {
+  __shared__ int32_t pre[OPEN ? OPEN_COUNTS + 1 : 1], ctok[OPEN ? MAXM : 1];
+  if constexpr (OPEN) {
     if (!open_stage(oc, h, pre, nbo, n, m, row_off)) return;
   } else {
     if (!assign_setup(cfg, h, n, m, row_off)) return;
   }
-  const int base = blockIdx.x * NP;
+  const int b = (blockIdx.x + h) % gridDim.x, base = b * NP;
   if (base >= n) return;
   m = min(m, MAXM);
   const int CT = (m + 31) >> 5;
@@ -1155,14 +1190,14 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void stage_pass_f32(const flo
   if (tid < NP) {
     const int p = min(base + tid, n - 1);
     int t;
-    if (FORM == PASS_OPEN && !oc.first) {
+    if (OPEN && !oc.first) {
       t = oc.surv[(size_t)h * cfg.N + survivor_at(pre, nbo, oc.items, p)];
       if (base + tid < n) oc.uout[(size_t)h * cfg.N + p] = t;
     } else t = cfg.ulist ? cfg.ulist[(size_t)h * cfg.N + p] : p;
     tok_s[tid] = t;
   } else if (tid < NP + MAXM) {
     const int j = tid - NP;
-    if (FORM == PASS_OPEN && j < m) {
+    if (OPEN && j < m) {
       const int q = (int)(((2ll * j + 1) * (long long)n) / (2ll * m));
       ctok[j] = oc.first ? q : oc.surv[(size_t)h * cfg.N + survivor_at(pre, nbo, oc.items, q)];
     }
@@ -1190,31 +1225,11 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void stage_pass_f32(const flo
       if (j < m) {
         const size_t at = (crow + j) * D + cl * 4;
         int nj = 1;
-        if constexpr (FORM == PASS_COMBINE) {
-          constexpr int BATCH = D == 64 ? 8 : 16;
-          nj = 0;
-          for (int b = cl; b < nb; b += PPR) nj += prev.bcnt[((size_t)h * prev.nb_stride + b) * STAGE_COUNTS + j];
-          const double2* row = reinterpret_cast<const double2*>(reinterpret_cast<const double*>(prev.psum) + ((size_t)h * prev.P + (size_t)j * prev.nb_stride) * D + cl * 4);
-          double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-          for (int b0 = 0; b0 < nb; b0 += BATCH) {
-            double2 t[BATCH][2];
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) { const size_t o = (size_t)min(b0 + u, nb - 1) * (D / 2); t[u][0] = row[o]; t[u][1] = row[o + 1]; }
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) if (b0 + u < nb) { s0 += t[u][0].x; s1 += t[u][0].y; s2 += t[u][1].x; s3 += t[u][1].y; }
-          }
-#pragma unroll
-          for (int o = 1; o < PPR; o <<= 1) nj += __shfl_xor(nj, o);
-          const double cnt = (double)nj;
-          r = float4{(float)(s0 / cnt), (float)(s1 / cnt), (float)(s2 / cnt), (float)(s3 / cnt)};
-        } else r = *reinterpret_cast<const float4*>(Xh + (size_t)ctok[j] * D + cl * 4);
+        if constexpr (FORM == PASS_COMBINE) r = block_mean_f32<D>(prev, h, j, nb, cl, nj);
+        else r = *reinterpret_cast<const float4*>(Xh + (size_t)ctok[j] * D + cl * 4);
         if (nj > 0) {
-          float ss = fmaf(r.x, r.x, 0.f);
-          ss = fmaf(r.y, r.y, ss); ss = fmaf(r.z, r.z, ss); ss = fmaf(r.w, r.w, ss);
-#pragma unroll
-          for (int o = 1; o < PPR; o <<= 1) ss += __shfl_xor(ss, o);
-          bj = -0.5f * ss;
-          if (blockIdx.x == 0) {
+          bj = centre_bias_f32<D>(r);
+          if (b == 0) {
             *reinterpret_cast<float4*>(cent + at) = r;
             *reinterpret_cast<float4*>(cent_f32 + at) = r;
             if (cl == 0) bias[crow + j] = bj;
@@ -1296,8 +1311,8 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void stage_pass_f32(const flo
     if (mine) dist2[(size_t)h * cfg.N + p] = d2;
     __syncthreads();
     if (tid == 0) {
-      if (counts) cfg.keep_cnt[(size_t)h * cfg.keep_stride + blockIdx.x] = (wkept[0] + wkept[1]) + (wkept[2] + wkept[3]);
-      if (cfg.dist_sum) cfg.dist_sum[(size_t)h * gridDim.x + blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+      if (counts) cfg.keep_cnt[(size_t)h * cfg.keep_stride + b] = (wkept[0] + wkept[1]) + (wkept[2] + wkept[3]);
+      if (cfg.dist_sum) cfg.dist_sum[(size_t)h * gridDim.x + b] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
     }
     if (counts && cfg.surv && mine) {      // the survivors in order, for the pass that opens the next stage
       int at = base;
@@ -1336,11 +1351,30 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void stage_pass_f32(const flo
           for (int q = 0; q < CPL; ++q) sum[q] += (double)v[u][q];
       }
     }
-    double* row = reinterpret_cast<double*>(out.psum) + ((size_t)h * out.P + (size_t)j * out.nb_stride + blockIdx.x) * D;
+    double* row = reinterpret_cast<double*>(out.psum) + ((size_t)h * out.P + (size_t)j * out.nb_stride + b) * D;
 #pragma unroll
     for (int q = 0; q < CPL; ++q) row[lane + 64 * q] = sum[q];
-    if (lane == 0) out.bcnt[((size_t)h * out.nb_stride + blockIdx.x) * STAGE_COUNTS + j] = members;
+    if (lane == 0) out.bcnt[((size_t)h * out.nb_stride + b) * STAGE_COUNTS + j] = members;
   }
+}
+
+// The centres of a stage from the sums that stage_pass_f32 left, in a launch of their own: what PASS_COMBINE makes of them, to the bit
+// (pass_f32_combines() says when).
+template <int D>
+__global__ __launch_bounds__(256) void form_centres_f32(PassSums sums, const KState* __restrict__ st, int cap, float* __restrict__ cent,
+                                                        float* __restrict__ cent_f32, float* __restrict__ bias) {
+  constexpr int LPC = D / 4;
+  const int h = blockIdx.y, j = blockIdx.x * (256 / LPC) + threadIdx.x / LPC, cl = threadIdx.x % LPC;
+  const KState& s = st[h];
+  if (!s.active || j >= min(s.m_t, PASS_F32_CENTRES)) return;
+  int nj;
+  const float4 r = block_mean_f32<D>(sums, h, j, (s.ucount + PASS_F32_POINTS - 1) / PASS_F32_POINTS, cl, nj);
+  if (nj == 0) return;                   // an empty cluster keeps its centre
+  const float bj = centre_bias_f32<D>(r);
+  const size_t row = (size_t)h * cap + s.ccount + j;
+  *reinterpret_cast<float4*>(cent + row * D + cl * 4) = r;
+  *reinterpret_cast<float4*>(cent_f32 + row * D + cl * 4) = r;
+  if (cl == 0) bias[row] = bj;
 }
 
 // The same scores, labels, distances and counts, to the bit, from a point a thread and centres broadcast from LDS: vector
@@ -2877,17 +2911,31 @@ static inline int chk() { return hipGetLastError() == hipSuccess ? 0 : ADACLUSTE
 int reduce_part_rows() { return REDUCE_ROWS; }
 int pass_sum_centres() { return ACC_MAXM; }
 int pass_points(int dtype, bool wide) { return dtype == ADACLUSTER_F32 ? PASS_F32_POINTS : wide ? 2 * PASS_POINTS : PASS_POINTS; }
-// fp32 stages by block sums.  Every workgroup of a head reads all of its sums: up to 2 MB that is less than the launches cost (us of
-// a call, and with update_direct_f32: 1 x 4 096 points, d=64, 16 centres, 131 KB 203 and 265; 4 x 6 000, 30 centres, 722 KB 282 and
-// 331; 4 x 4 000, d=128, 16 centres, 524 KB 341 and 417; 4 x 6 500, 30 centres, 1.6 MB 475 and 506; past the line 2 x 11 400, 40
-// centres, 3.7 MB 529 and 522; 4 x 12 000, d=64, 60 centres, 2.9 MB 656 and 648).  Many heads are not bound by latency: 30 x 6 000
-// points, d=64, 1 119 and 1 091, 60 x 1 500, d=128, 895 and 825, so a launch of more points than `points` takes the other form.
-// (Not of fewer: a head alone and many of it give the same bits up to there.)
+// fp32 stages by block sums: by width, tokens and first centres of a head alone, never by the number of heads, which must not change
+// the bits of any of them.  us of a key clustering, and with update_direct_f32: d=64, 1 x 4 096 points, 16 centres 120 and 141; 30 x 6 000,
+// 30 centres 250 and 272; 60 x 1 500, 60 centres 180 and 205; 30 x 16 000, 16 centres 342 and 379; 400 x 1 200, 12 centres 478 and 505; 60 x
+// 3 000, 40 centres 324 and 331; d=128, 1 x 4 096, 16 centres 138 and 165; 24 x 4 000 320 and 349; 15 x 6 500, 30 centres 242 and 305;
+// 60 x 6 500 670 and 681.  Slower at d=128 in launches of more than some 200 000 points with few centres, where a workgroup a CU
+// does not hide its latency: 60 x 4 000, 24 centres 616 and 578, 200 x 1 500, 16 centres 667 and 600.  Past the lines (two tiles of
+// centres, 2 MB of sums a head, 40 centres at d=128, which date from passes that formed the centres) they are the faster form
+// mostly as well, not by much: 4 x 12 000, d=64, 60 centres 220 and 270, 1 x 12 000, 64 centres 201 and 187; 3 x 4 000, d=128, 50
+// centres 180 and 197, 30 x 4 000 428 and 430, 3 x 12 000, 40 centres 218 and 320.
 static constexpr int PASS_F32_BYTES = 2 << 20;
 int pass_f32_rows(int d, int N, int m0) { return min((long long)(N + PASS_F32_POINTS - 1) / PASS_F32_POINTS * min(m0, PASS_F32_CENTRES), PASS_F32_BYTES / 8ll / d); }
-bool pass_f32_fits(int d, int H, int N, int m0) {
-  const long long nb = (N + PASS_F32_POINTS - 1) / PASS_F32_POINTS, points = d == 64 ? 230000 : 91000;
-  return nb <= STAGE_SUM_BLOCKS && m0 <= (d == 64 ? PASS_F32_CENTRES : 40) && nb * m0 * d * 8 <= PASS_F32_BYTES && (long long)H * N <= points;
+bool pass_f32_fits(int d, int N, int m0) {
+  const long long nb = (N + PASS_F32_POINTS - 1) / PASS_F32_POINTS;
+  return nb <= STAGE_SUM_BLOCKS && m0 <= (d == 64 ? PASS_F32_CENTRES : 40) && nb * m0 * d * 8 <= PASS_F32_BYTES;
+}
+// Whether the next pass forms the centres of an fp32 stage, every workgroup for itself, or a launch between the two: the bits are the
+// same.  A workgroup's own trips take longer than the launch where a head has more than 512 KB of sums, and what all read together
+// counts in launches of many heads.  us of a key clustering, formed by the pass and by a launch: d=64, 1 x 4 096 points, 16 centres
+// (262 KB, 8 MB in all) 119 and 125; 10 x 1 500, 12 centres (74 KB, 9 MB) 162 and 175; 1 x 4 096, 32 centres (524 KB, 17 MB) 181 and
+// 191; 4 x 4 096, 16 centres (34 MB) 124 and 126; 1 x 6 000, 60 centres (1.4 MB) 218 and 207; 150 x 1 500, 20 centres (221 MB) 350 and
+// 319; d=128, 4 x 1 500, 12 centres (147 KB, 7 MB) 154 and 163; 1 x 4 096, 16 centres (524 KB, 17 MB) 131 and 131; 1 x 4 096, 30
+// centres (983 KB) 178 and 172; 30 x 1 500, 16 centres (70 MB) 252 and 237; 60 x 6 500, 30 centres (4.8 GB) 1 174 and 670.
+bool pass_f32_combines(int d, int heads, int n_bound, int m_bound) {
+  const long long nb = (n_bound + PASS_F32_POINTS - 1) / PASS_F32_POINTS, table = nb * m_bound * d * 8;
+  return table <= (512 << 10) && table * nb * heads <= 40000000;
 }
 // Every workgroup of a head reads all of its sums: up to 128 KB they cost less than the launch they save (up to 256 KB the
 // same time either way), up to 64 centres or (d=128) 40: each 32 or 16 are another trip (of 3 000 points, d=128, 100 centres at
@@ -3003,6 +3051,16 @@ int launch_stage_pass(hipStream_t s, int dtype, int d, int H, int N, int n_bound
     return chk();
   };
   return d == 64 ? launch(std::integral_constant<int, 64>{}) : launch(std::integral_constant<int, 128>{});
+}
+
+int launch_form_centres(hipStream_t s, int d, int H, int n_bound, int m_bound, int cap, const KState* st, const StageSums& sums, void* cent_lp,
+                        float* cent_f32, float* bias) {
+  const int nb = (n_bound + PASS_F32_POINTS - 1) / PASS_F32_POINTS;
+  const PassSums in{sums.psum, sums.bcnt, m_bound * nb, nb};
+  const dim3 g((m_bound * (d / 4) + 255) / 256, H);
+  if (d == 64) form_centres_f32<64><<<g, 256, 0, s>>>(in, st, cap, (float*)cent_lp, cent_f32, bias);
+  else form_centres_f32<128><<<g, 256, 0, s>>>(in, st, cap, (float*)cent_lp, cent_f32, bias);
+  return chk();
 }
 
 // one-read pass of the query clustering (bf16, at most pass_sum_centres() centres): NP = walks per head

@@ -54,13 +54,16 @@ struct StageOpening {
 };
 int pass_sum_centres();
 int pass_points(int dtype, bool wide);
-bool pass_f32_fits(int d, int H, int N, int m0);           // fp32: passes with block sums in all stages of a call, formed by the next pass (`wide`)
+bool pass_f32_fits(int d, int N, int m0);                  // fp32: passes with block sums in all stages of a call, centres formed by the next pass (`wide`) or launch_form_centres
 int pass_f32_rows(int d, int N, int m0);                   // most rows of one of their tables in a head of N points
 bool combine_fits(int d, int heads, int n_bound, int m_bound);
+bool pass_f32_combines(int d, int heads, int n_bound, int m_bound);
 bool wide_fills(int heads, int n_bound);      // whether passes without `prev` take `wide` as well
 int launch_stage_pass(hipStream_t s, int dtype, int d, int H, int N, int n_bound, int m_bound, int cap, const KState* st, const int32_t* ulist,
                       const void* X, void* cent_lp, float* cent_f32, float* bias, bool wide, const StageSums* prev, const StageSums* out,
                       const PassEnd* end, const StageOpening* open);
+int launch_form_centres(hipStream_t s, int d, int H, int n_bound, int m_bound, int cap, const KState* st, const StageSums& sums, void* cent_lp,
+                        float* cent_f32, float* bias);
 int launch_seg_reduce(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int P,
                       const KState* st, int normalize, int want_box, const void* X, const int32_t* perm,
                       const int32_t* offs, int offs_stride, int32_t* poff, int32_t* pcl, float* psum, float* pnorm, float* pmin,

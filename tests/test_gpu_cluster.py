@@ -186,10 +186,14 @@ def test_fp32_query_clustering_by_launch_size(d, H, N, Cq):
         assert torch.equal(many[name], a.expand_as(many[name])), name
 
 
-@pytest.mark.parametrize("d,H,N,m0,frac", [(64, 70, 1505, 12, 0.0), (64, 150, 1505, 20, 0.03), (128, 60, 1505, 16, 0.0)])
+@pytest.mark.parametrize("d,H,N,m0,frac", [
+    (64, 70, 1505, 12, 0.0), (64, 150, 1505, 20, 0.03), (128, 60, 1505, 16, 0.0),       # block sums, in launches of any size
+    (64, 160, 1505, 20, 0.0), (128, 70, 1505, 16, 0.0), (64, 40, 6001, 30, 0.03), (128, 24, 4001, 24, 0.0),
+    (64, 30, 16401, 12, 0.0), (128, 20, 16401, 10, 0.0), (64, 250, 3001, 72, 0.03),     # no block sums: assign_f32 alone, assign_rows in many
+])
 def test_fp32_key_stages_by_launch_size(d, H, N, m0, frac):
-    """The same for the stages of Algorithm 1: survivors are counted per 64 points by either assignment, and the last
-    workgroup of assign_rows has no points for its second wave."""
+    """The same for the stages of Algorithm 1.  Block sums are chosen by a head's own sizes.  Past their lines survivors are
+    counted per 64 points by either assignment, and the last workgroup of assign_rows has no points for its second wave."""
     _, K, _ = wl.make_small(62, N, d, 40, dtype="f32", H=1)
     p = B.Params(H=1, N=N, d=d, dtype=B.F32, q_clusters=4, k_iters=3, k_m0=m0, k_m_min=2, k_max_clusters=6 * m0,
                  min_unassigned_frac=frac)
@@ -326,12 +330,11 @@ def test_kcluster_late_stages_end_where_each_head_does(d, iters):
 
 
 @pytest.mark.parametrize("dtype,d,N,m0,skew", [(B.BF16, 64, 4096, 24, 0.9), (B.BF16, 128, 4095, 24, 0.0), (B.BF16, 128, 129, 5, 0.95),
-                                               (B.F32, 64, 4096, 24, 0.9), (B.F32, 128, 2049, 41, 0.5)])
+                                               (B.F32, 64, 4096, 24, 0.9), (B.F32, 128, 2049, 41, 0.5), (B.F32, 128, 2049, 20, 0.5)])
 def test_short_heads_sorted_and_summed_per_cluster(dtype, d, N, m0, skew):
     """A workgroup a cluster (few heads), or sort, reduction and combination (many): the same bits, boxes and empty clusters
     among them; `skew` of the tokens are alike, so that one cluster holds many parts."""
-    H = (3000000 if dtype == B.BF16 else 1500000) // (16 * N) + 1      # past the line of cluster_stats_fits for 16 clusters, and
-                                              # (fp32) on the same side as one head of the line of block sums
+    H = (3000000 if dtype == B.BF16 else 1500000) // (16 * N) + 1      # past the line of cluster_stats_fits for 16 clusters
     rng = np.random.default_rng(23)
     X = rng.standard_normal((1, N, d)).astype(np.float32)
     alike = rng.random(N) < skew
@@ -422,14 +425,15 @@ def test_kcluster_fp32_sorted_and_direct_updates():
     assert (np.diff(so[1]) > 0).sum() >= 2, so          # the diffuse head ran at least two stages
 
 
-def test_kcluster_fp32_direct_update_scans_in_rounds():
-    """A first stage of 9 500 fp32 points goes through the one-launch update in three scan rounds.  With two
-    passes the stage centres are the member means over the labels of pass 1, which are arg-mins to the strided
-    sample: recomputed here in fp64, centres that a near-tied point may have joined or left aside."""
+@pytest.mark.parametrize("m0", [12, 72])             # by block sums, and by the one-launch update, in three scan rounds
+def test_kcluster_fp32_stage_centres_are_member_means(m0):
+    """A first stage of 9 500 fp32 points.  With two passes the stage centres are the member means over the labels of
+    pass 1, which are arg-mins to the strided sample: recomputed here in fp64, centres that a near-tied point may
+    have joined or left aside."""
     from tests.helpers import REL_TIE
-    H, N, d, m0 = 1, 9500, 64, 12
+    H, N, d = 1, 9500, 64
     _, K, _ = wl.make_small(33, N, d, 10, dtype="f32", H=H)
-    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=4, k_iters=2, k_m0=m0, k_m_min=4, k_max_clusters=48,
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=4, k_iters=2, k_m0=m0, k_m_min=4, k_max_clusters=4 * m0,
                  tau_factor=1.0, min_unassigned_frac=0.02)
     out = B.adacluster_kcluster(p, to_dev(K, B.F32))
     torch.cuda.synchronize()
