@@ -3119,18 +3119,22 @@ int launch_finalize(hipStream_t s, int dtype, int d, int H, int mode, int m_cons
 bool direct_update_fits(int dtype, int n_bound, int m_bound) {
   return dtype == ADACLUSTER_F32 && n_bound <= DIRECT_MAX_POINTS && (long long)n_bound * m_bound <= DIRECT_MAX_VISITS;
 }
-// Every workgroup reads the labels of its head: in all up to some three million it is the faster form.  us of a call (with the
-// sort, the reduction and the launch behind it), all bf16 with 65 query clusters: 2 x 1 500 tokens, d=64, 9 query clusters 122 (140),
-// 8 x 1 500 134 (150), 16 x 1 800 149 (161), 30 x 1 500, d=128 241 (248), 4 x 4 000, d=128 232 (248); past the line 12 x 4 000,
-// d=128 312 (308), 30 x 4 000, d=64 313 (306).
-bool cluster_stats_fits(int dtype, int H, int N, int m_bound) {
-  return N <= STATS_ITEMS && (long long)H * m_bound * N <= (dtype == ADACLUSTER_BF16 ? 3000000 : 1500000);
+// Up to some 900 workgroups, a round of them, it is the faster form, and past that soon much the slower one; the labels that all of them
+// read together count as well.  us of a query clustering, and with the sort, the reduction and the combining launch: bf16, d=64, 16
+// x 1 500 tokens, 8 clusters 50 and 64; 16 x 1 500, 56 clusters 55 and 65; 16 x 4 096, 56 (past the second line) 63 and 72; 30 x 400,
+// 20 56 and 56; 30 x 400, 53 67 and 56; 24 x 400, 116 86 and 59; d=128, 24 x 400, 37 61 and 68; 30 x 1 500, 40 85 and 82; 24 x 4 096, 25 93
+// and 93; 30 x 93 clusters of 400 98 and 73; fp32, d=64, 16 x 800, 56 83 and 85, 24 x 1 500, 25 96 and 92, 24 x 400, 87 108 and 92.  fp32 at
+// d=128, whose parts a wave reads one row pair at a time, gains up to 6 % where clusters have a few members and loses 7 where they
+// have more (12 x 800, 10 100 and 93): not taken.
+bool cluster_stats_fits(int dtype, int d, int H, int N, int m_bound) {
+  const long long groups = (long long)H * m_bound;
+  return N <= STATS_ITEMS && groups <= 900 && groups * N <= (dtype == ADACLUSTER_BF16 ? 3000000 : 1500000) && (dtype == ADACLUSTER_BF16 || d == 64);
 }
 int launch_cluster_stats(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int cap, const KState* st,
                          int spherical, int want_box, const void* X, const int32_t* labels, int32_t* perm, int32_t* offs, int offs_stride,
                          float* out_cent, const float* fallback, int32_t* out_sizes, float* out_mean_norm, float* out_bmin,
                          float* out_bmax, const StateExport* ex) {
-  if (N > STATS_ITEMS) return ADACLUSTER_E_INTERNAL;
+  if (!cluster_stats_fits(dtype, d, H, N, m_bound)) return ADACLUSTER_E_INTERNAL;
   const StatsCfg c{mode, m_const, N, cap, st, spherical, want_box, ex ? *ex : StateExport{}};
   auto launch = [&](auto elem, auto dim) {
     using T = decltype(elem);
@@ -3140,7 +3144,7 @@ int launch_cluster_stats(hipStream_t s, int dtype, int d, int H, int N, int mode
   };
   using std::integral_constant;
   if (dtype == ADACLUSTER_BF16) { if (d == 64) launch(bf16raw{}, integral_constant<int, 64>{}); else launch(bf16raw{}, integral_constant<int, 128>{}); }
-  else { if (d == 64) launch(float{}, integral_constant<int, 64>{}); else launch(float{}, integral_constant<int, 128>{}); }
+  else launch(float{}, integral_constant<int, 64>{});
   return chk();
 }
 
