@@ -1267,24 +1267,30 @@ int attn_block_rows(int dtype, int d, int N, int Cq) {
 }
 // Shape of a dense launch: queries a workgroup, and pieces of the key list (unnormalised partial results and a merge, as for cut
 // lists).  A launch of few query tiles leaves most of the chip idle with 256 queries a workgroup, so it takes 128 and, while that
-// fills less than a round, pieces.  Priced in steps of a key tile (0.9 us at d=64, 1.6 at d=128): rounds of resident workgroups, four
-// steps a workgroup besides its own, fewer where a CU holds one of the narrow ones alone; a merge costs its launch and 4 TB/s on
-// its partial results.  us of a call, 256 queries a workgroup and chosen: d=64, 1 x 2 500 rows 44 and 26, 12 x 2 000 38 and 28,
-// 4 x 4 000 66 and 36, 2 x 8 000 122 and 64, 1 x 16 000 234 and 166; d=128, 1 x 1 300 40 and 26, 4 x 2 000 56 and 29, 4 x 4 000 98
-// and 59, 2 x 8 000 182 and 102, 1 x 16 000 349 and 251.  12 x 8 000 rows, d=128, in two pieces of 128 queries 437, as they are 409.
+// fills less than a round, pieces.  Priced in steps of a key tile (0.9 us at d=64, 1.6 at d=128) by the workgroups on a CU, heads
+// dealt to the XCDs whole and those left over in eighths: they share its matrix cores.  At d=64 a workgroup alone is slower than its
+// share, and what counts for 128 queries is the mean CU; at d=128 three of 128, of which two fit at once, take less than two of 256,
+// more again by the mean.  A workgroup costs a few steps besides its own; a merge its launch and 4 to 8 TB/s on its partial results.
+// The figures are fitted to the times of 261 launches of 500-33 000 rows, 168 of them in every form (profiles/dense_shapes.txt has
+// some on both sides of every choice): the chosen form takes 1.004 (d=64) and 1.008 (d=128) of the best one's time in the geometric
+// mean, and no launch of 363 takes more than 1.02 of what whole lists of 256 queries a workgroup take.
+// The shape, and with it the rounding of a row, depends on the number of heads.
 DenseShape attn_dense_shape(int dtype, int d, int H, int N) {
   if (dtype != ADACLUSTER_BF16) return {32, 1};
-  const int wide = 8 * 32, T = (N + 63) / 64, resident = d == 64 ? 512 : 256;
-  const long long W8 = (long long)H * ((N + wide - 1) / wide), nq = (N + 127) / 128;
-  double best = (double)((W8 + resident - 1) / resident) * (T + 4) * 0.93;
-  DenseShape r{wide, 1};
-  for (int want = 1; want <= 16 && nq * want <= SPLIT_SLOTS; ++want) {
+  const bool w64 = d == 64;
+  const int T = (N + 63) / 64, nq = (N + 127) / 128;
+  auto load = [&](long long tiles) { return (double)(H / 8 * tiles + H % 8 * ((tiles + 7) / 8)) / 32.0; };      // workgroups a CU, in the busiest XCD
+  const double wide = load((N + 255) / 256), kw = w64 && wide > 0.97 ? fmax(2.0, ceil(wide)) : ceil(wide);      // (d=64, one for every CU: some get two)
+  double best = w64 ? (kw > 1.0 ? 0.92 * kw : 0.93 + 0.24 * wide) * (T + 8) : (kw > 1.0 ? 0.93 * kw : 0.8) * (T + 2);
+  DenseShape r{256, 1};
+  for (int want = 1; want <= 16 && (want == 1 || nq * want <= SPLIT_SLOTS); ++want) {
     const int per = (T + want - 1) / want, pieces = (T + per - 1) / per;
     if (pieces != want || (want > 1 && per < 2)) continue;      // (no empty piece)
-    const long long W = H * nq * pieces;
-    const double rounds = W <= resident ? (d == 64 ? 0.6 : 0.75) : 1.15 * (double)((W + 2 * resident - 1) / (2 * resident));
-    const double merge = pieces == 1 ? 0.0 : (d == 64 ? 10.0 : 6.0) + (double)H * N * pieces * (d + 2) * 2e-6 / (d == 64 ? 0.9 : 1.6);
-    const double cost = rounds * (per + 4) + merge;
+    const double x = load((long long)nq * pieces), k = ceil(x);
+    const double share = !w64 ? (k > 3.0 ? 0.73 * x : k > 1.0 ? 0.6 * k : 0.7) : pieces > 1 ? fmax(0.8, 0.6 * x) : fmax(0.72, 0.28 + 0.52 * x);
+    const double partial = (double)H * N * pieces * (d + 2) * 1e-6;
+    const double merge = pieces == 1 ? 0.0 : w64 ? 14.0 + partial / 0.9 : 6.0 + 2.0 * partial / 1.6;
+    const double cost = share * (per + (w64 && pieces > 1 ? 4 : 2)) + merge;
     if (cost < best) { best = cost; r = {128, pieces}; }
   }
   return r;
