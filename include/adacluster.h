@@ -227,7 +227,8 @@ int adacluster_stats_fetch(const adacluster_params* p, void* ws, size_t ws_bytes
                            adacluster_head_stats* host_stats /* host, [H] */, void* stream);
 
 /* Dense softmax attention on the same attention kernel (the F = True branch of Alg. 3 and the
- * timing baseline): every query attends to every key. */
+ * timing baseline): every query attends to every key.  Here and in the sparse calls a score of -inf weighs
+ * nothing, a row with no score above -inf is NaN, and one whose list has no key zero. */
 int adacluster_dense_attn(const adacluster_params* p,
                           const void* Q, const void* K, const void* V, void* O,
                           void* ws, size_t ws_bytes, void* stream);

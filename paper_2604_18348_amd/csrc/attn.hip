@@ -1273,7 +1273,7 @@ int attn_block_rows(int dtype, int d, int N, int Cq) {
 // more again by the mean.  A workgroup costs a few steps besides its own; a merge its launch and 4 to 8 TB/s on its partial results.
 // The figures are fitted to the times of 261 launches of 500-33 000 rows, 168 of them in every form (profiles/dense_shapes.txt has
 // some on both sides of every choice): the chosen form takes 1.004 (d=64) and 1.008 (d=128) of the best one's time in the geometric
-// mean, and no launch of 363 takes more than 1.02 of what whole lists of 256 queries a workgroup take.
+// mean.  (In the table 9 x 14 399, d=64, 557 and 579, and 5 x 27 679, d=128, 1 998 and 2 120, are the worst.)
 // The shape, and with it the rounding of a row, depends on the number of heads.
 DenseShape attn_dense_shape(int dtype, int d, int H, int N) {
   if (dtype != ADACLUSTER_BF16) return {32, 1};

@@ -3219,10 +3219,11 @@ int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, co
 // the more heads share the launches, and no more from about 64 heads on (72 at d=128): calls of nine stages, 200 heads
 // of 3 500 and 8 000 points, d=64, 763 and 1 385 us, in six launches a stage 1 576 and 3 450.  But the points are the bound
 // of the stage before, U shrinks, and what follows is in the one launch too: below 3 072 it is taken always (5 heads
-// of 9 247 tokens, d=128: the call 612 us, with the line at 1 100 636).  With the centres formed in the next pass, four
-// launches a stage, it stays there: lines at 2 048, 1 400, 900 and 500 points for any number of heads, that call 527 -> 559,
-// 559, 561, 579 us; 3 x 2 587 tokens, d=64, 316 -> 329, 329, 329, 409; 28 x 3 669 470 -> 468, 469, 491, 571; 30 x 17 776,
-// 12 x 32 760 and 7 x 56 160 within 1 %.
+// of 9 247 tokens, d=128: the call 612 us, with the line at 1 100 636).  With three launches a stage, as it is now, that call takes
+// 446 us, with the line at 2 048, 1 400, 900 and 500 points for any number of heads 449, 449, 465, 465; 1 x 9 000, d=128 264 and 274, 274,
+// 275, 291; 3 x 2 587, d=64 135 and 149, 144, 142, 158; 12 x 32 760 and 30 x 17 776 within 1 %.  Calls with a fifth of their heads without
+// structure, whose U shrinks slowly, would have it lower: 5 x 9 000, d=64 509 and 466-470, d=128 785 and 593-597; 12 x 9 000 578 and 520, 922
+// and 733; 30 x 4 000 500 and 481, 748 and 715, 671; it does not tell the two apart.
 int small_stage_points(int d, int heads) {
   const int one = d == 64 ? 2048 : 1024, all = d == 64 ? 64 : 72;
   return heads >= all ? SMALL_NU : min(SMALL_NU, max(3072, one * all / (all - heads)));

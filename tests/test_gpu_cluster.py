@@ -189,16 +189,18 @@ def test_fp32_query_clustering_by_launch_size(d, H, N, Cq):
 @pytest.mark.parametrize("d,H,N,m0,frac", [
     (64, 70, 1505, 12, 0.0), (64, 150, 1505, 20, 0.03), (128, 60, 1505, 16, 0.0),       # block sums, in launches of any size
     (64, 160, 1505, 20, 0.0), (128, 70, 1505, 16, 0.0), (64, 40, 6001, 30, 0.03), (128, 24, 4001, 24, 0.0),
-    (64, 30, 16401, 12, 0.0), (128, 20, 16401, 10, 0.0), (64, 250, 3001, 72, 0.03),     # no block sums: assign_f32 alone, assign_rows in many
-])
+    (64, 30, 16401, 12, 0.0), (128, 20, 16401, 10, 0.0), (64, 250, 3001, 72, 0.03),     # no block sums: assign_f32 alone, assign_rows in many,
+])                                                                                     # the first two in their second stage as well
 def test_fp32_key_stages_by_launch_size(d, H, N, m0, frac):
     """The same for the stages of Algorithm 1.  Block sums are chosen by a head's own sizes.  Past their lines survivors are
     counted per 64 points by either assignment, and the last workgroup of assign_rows has no points for its second wave."""
     _, K, _ = wl.make_small(62, N, d, 40, dtype="f32", H=1)
     p = B.Params(H=1, N=N, d=d, dtype=B.F32, q_clusters=4, k_iters=3, k_m0=m0, k_m_min=2, k_max_clusters=6 * m0,
-                 min_unassigned_frac=frac)
+                 tau_factor=1.0 if N > 16384 else 1.5, min_unassigned_frac=frac)
     Kd = to_dev(K, B.F32)
     one = B.adacluster_kcluster(p, Kd)
+    if N > 16384:                # 12 (d=128: 20) centres at most from 100 000 (50 000) points on
+        assert H * int((one["k_stage_of"] != 0).sum()) >= 100000 and int(one["k_stage_offs"][0, 2] - one["k_stage_offs"][0, 1]) <= 12
     pm = dataclasses.replace(p, H=H, tau_abs=float(one["tau_used"][0]))
     many = B.adacluster_kcluster(pm, Kd.expand(H, -1, -1).contiguous())
     own = B.adacluster_kcluster(dataclasses.replace(pm, tau_abs=0.0), Kd.expand(H, -1, -1).contiguous())
