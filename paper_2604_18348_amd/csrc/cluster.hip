@@ -1161,9 +1161,9 @@ __device__ __forceinline__ float centre_bias_f32(const float4& r) {
   return -0.5f * ss;
 }
 template <int D, int FORM>
-__global__ __launch_bounds__(512, D == 64 ? 4 : 2) void stage_pass_f32(const float* __restrict__ X, AssignCfg cfg, float* __restrict__ cent,
+__global__ __launch_bounds__(512, D == 128 ? 2 : FORM == PASS_COMBINE ? 4 : 6) void stage_pass_f32(const float* __restrict__ X, AssignCfg cfg, float* __restrict__ cent,
                                                                        float* __restrict__ cent_f32, float* __restrict__ bias,
-                                                                       float* __restrict__ dist2, PassSums prev, PassSums out, OpenCfg oc) {
+                                                                       float* __restrict__ dist2, int nblk, uint32_t turns, PassSums prev, PassSums out, OpenCfg oc) {
   constexpr bool OPEN = FORM == PASS_OPEN;
   constexpr int NT = 512, NP = PASS_F32_POINTS, MAXM = PASS_F32_CENTRES, ROWB = D * 4, PPR = D / 4, CPL = D / 64;
   const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1175,7 +1175,12 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void stage_pass_f32(const flo
   } else {
     if (!assign_setup(cfg, h, n, m, row_off)) return;
   }
-  const int b = (blockIdx.x + h) % gridDim.x, base = b * NP;
+  int b = blockIdx.x;
+  if (FORM != PASS_COMBINE && nblk > 1) {                 // (small launches need no turn)
+    b += h - (int)__umulhi((uint32_t)h, turns) * nblk;    // h % nblk, of at most 2^16 heads and 2^7 blocks
+    if (b >= nblk) b -= nblk;
+  }
+  const int base = b * NP;
   if (base >= n) return;
   m = min(m, MAXM);
   const int CT = (m + 31) >> 5;
@@ -1312,7 +1317,7 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void stage_pass_f32(const flo
     __syncthreads();
     if (tid == 0) {
       if (counts) cfg.keep_cnt[(size_t)h * cfg.keep_stride + b] = (wkept[0] + wkept[1]) + (wkept[2] + wkept[3]);
-      if (cfg.dist_sum) cfg.dist_sum[(size_t)h * gridDim.x + b] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+      if (cfg.dist_sum) cfg.dist_sum[(size_t)h * nblk + b] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
     }
     if (counts && cfg.surv && mine) {      // the survivors in order, for the pass that opens the next stage
       int at = base;
@@ -3031,9 +3036,10 @@ int launch_stage_pass(hipStream_t s, int dtype, int d, int H, int N, int n_bound
       constexpr int DIM = decltype(dim)::value;
       const float* x = (const float*)X;
       float* lp = (float*)cent_lp;
-      if (open) stage_pass_f32<DIM, PASS_OPEN><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to, oc);
-      else if (prev) stage_pass_f32<DIM, PASS_COMBINE><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to, oc);
-      else stage_pass_f32<DIM, PASS_READ><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, in, to, oc);
+      const uint32_t turns = 0xFFFFFFFFu / nb + 1;
+      if (open) stage_pass_f32<DIM, PASS_OPEN><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, nb, turns, in, to, oc);
+      else if (prev) stage_pass_f32<DIM, PASS_COMBINE><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, nb, turns, in, to, oc);
+      else stage_pass_f32<DIM, PASS_READ><<<g, 512, 0, s>>>(x, c, lp, cent_f32, bias, dist2, nb, turns, in, to, oc);
       return chk();
     };
     return d == 64 ? launch(std::integral_constant<int, 64>{}) : launch(std::integral_constant<int, 128>{});
