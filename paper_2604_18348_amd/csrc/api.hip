@@ -359,7 +359,7 @@ int run_qcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
     }
     RET_IF(launch_assign(st, p->dtype, D.d, D.H, D.N, D.N, D.Cq, 0, D.Cq, D.Cq, nullptr, nullptr, Q, w.q_cent_lp, w.q_bias,
                          q_labels, nullptr));
-    if (it == p->q_iters - 1 && cluster_stats_fits(p->dtype, D.d, D.H, D.N, D.Cq)) {
+    if (it == p->q_iters - 1 && cluster_stats_fits(p->dtype, D.d, D.H, D.N, D.Cq, false)) {
       RET_IF(launch_cluster_stats(st, p->dtype, D.d, D.H, D.N, 0, D.Cq, D.Cq, D.Cq, nullptr, sph, 0, Q, q_labels, w.perm_q, w.offs_q, D.Cq + 1,
                                   q_centroids, nullptr, q_sizes, q_mean_norm, nullptr, nullptr, nullptr));
       break;
@@ -570,7 +570,7 @@ int run_kcluster(const adacluster_params* p, const WS& w, hipStream_t st, const 
   const int want_box = (k_bmin && k_bmax) ? 1 : 0;
   if (kc_bound_out) *kc_bound_out = kc_bound;
   const StateExport ex{w.kstate, k_count, full_flag, k_stage_offs, w.tau, warm ? nullptr : tau_used};
-  if (cluster_stats_fits(p->dtype, D.d, D.H, D.N, kc_bound)) {
+  if (cluster_stats_fits(p->dtype, D.d, D.H, D.N, kc_bound, true)) {
     prof_mark(EV_KSORT, st);
     RET_IF(launch_cluster_stats(st, p->dtype, D.d, D.H, D.N, warm ? 1 : 2, 0, kc_bound, D.cap, cur, 0, want_box, K, k_labels, w.perm_k, w.offs_k,
                                 D.cap + 1, k_centroids, k_assign, k_sizes, nullptr, k_bmin, k_bmax, &ex));

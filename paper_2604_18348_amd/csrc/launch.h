@@ -83,7 +83,7 @@ int launch_finalize(hipStream_t s, int dtype, int d, int H, int mode, int m_cons
                     int nb_stride = 0, int blk_points = 0 /* of a block; 0: nb_stride blocks in every head */, const StateExport* ex = nullptr);
 // Label sort (perm, offs as launch_sort leaves them) and final statistics (launch_finalize, update_assign = 0) in one launch:
 // cluster_stats_fits() says when.
-bool cluster_stats_fits(int dtype, int d, int H, int N, int m_bound);
+bool cluster_stats_fits(int dtype, int d, int H, int N, int m_bound, bool keys);
 int launch_cluster_stats(hipStream_t s, int dtype, int d, int H, int N, int mode, int m_const, int m_bound, int cap, const KState* st,
                          int spherical, int want_box, const void* X, const int32_t* labels, int32_t* perm, int32_t* offs, int offs_stride,
                          float* out_cent, const float* fallback, int32_t* out_sizes, float* out_mean_norm, float* out_bmin,

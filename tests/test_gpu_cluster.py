@@ -333,11 +333,11 @@ def test_kcluster_late_stages_end_where_each_head_does(d, iters):
 
 @pytest.mark.parametrize("dtype,d,N,m0,skew", [(B.BF16, 64, 4096, 24, 0.9), (B.BF16, 128, 4095, 24, 0.0), (B.BF16, 128, 129, 5, 0.95),
                                                (B.F32, 64, 4096, 24, 0.9), (B.BF16, 64, 300, 10, 0.3), (B.F32, 64, 257, 20, 0.5),
-                                               (B.F32, 128, 2049, 41, 0.5), (B.F32, 128, 2049, 20, 0.5)])      # (fp32 at d=128: the launches alone)
+                                               (B.F32, 128, 2049, 41, 0.5), (B.F32, 128, 2049, 20, 0.5)])
 def test_short_heads_sorted_and_summed_per_cluster(dtype, d, N, m0, skew):
     """A workgroup a cluster (few heads), or sort, reduction and combination (many): the same bits, boxes and empty clusters
     among them; `skew` of the tokens are alike, so that one cluster holds many parts."""
-    H = max((3000000 if dtype == B.BF16 else 1500000) // N, 900) // 16 + 1      # past the lines of cluster_stats_fits for 16 clusters
+    H = max((3000000 if dtype == B.BF16 else 1500000) // N, 2300) // 16 + 1      # past the lines of cluster_stats_fits for 16 clusters
     rng = np.random.default_rng(23)
     X = rng.standard_normal((1, N, d)).astype(np.float32)
     alike = rng.random(N) < skew
