@@ -3126,18 +3126,20 @@ bool direct_update_fits(int dtype, int n_bound, int m_bound) {
   return dtype == ADACLUSTER_F32 && n_bound <= DIRECT_MAX_POINTS && (long long)n_bound * m_bound <= DIRECT_MAX_VISITS;
 }
 // Up to some 900 workgroups, a round of them, it is the faster form, and past that soon much the slower one, a little later where the
-// other form has more rows to sort; the labels that all of them read together count as well.  Key clusterings have fewer centres than the bound that the launch is sized for, and the workgroups
-// past them end at once: 1 600.  us of a query clustering, and with the sort, the reduction and the combining launch: bf16, d=64, 16
-// x 1 500 tokens, 8 clusters 50 and 64; 16 x 1 500, 56 clusters 55 and 65; 30 x 1 500, 40 64 and 67; 16 x 4 096, 56 (past the second
-// line) 63 and 72; 30 x 400, 20 56 and 56; 30 x 400, 53 67 and 56; 24 x 400, 116 86 and 59; d=128, 24 x 400, 37 61 and 68; 30 x 1 500, 40 85 and 82; 24 x 4 096, 25 93
-// and 93; 30 x 93 clusters of 400 98 and 73; fp32, d=64, 16 x 800, 56 83 and 85, 24 x 1 500, 25 96 and 92, 24 x 400, 87 108 and 92.  fp32 at
-// d=128, whose parts a wave reads one row pair at a time, gains up to 6 % where query clusters have a few members and loses 7 where
-// they have more: up to 24 in the mean (8 x 400, 75 105 and 112; 4 x 1 500, 75 103 and 101; past it 12 x 800, 10 100 and 93).  Keys gain
-// at any size, since their boxes cost the three launches more (fp32, d=128, 4 x 4 096, bound 48 96 and 106; 12 x 4 096, 48 122 and
-// 137; bf16, d=128, 30 x 1 500, 48 92 and 96; past the line 30 x 2 500, 120 111 and 106).
+// other form has more rows to sort; the labels that all of them read together count as well.  Key clusterings have fewer centres than
+// the bound that the launch is sized for, and the workgroups past them end at once: 2 400.  us of a query clustering, and with the
+// sort, the reduction and the combining launch: bf16, d=64, 16 x 1 500 tokens, 8 clusters 50 and 64; 16 x 1 500, 56 clusters 55 and
+// 65; 30 x 1 500, 40 64 and 67; 16 x 4 096, 56 (past the second line) 63 and 72; 30 x 400, 20 56 and 56; 30 x 400, 53 67 and 56;
+// 24 x 400, 116 86 and 59; d=128, 24 x 400, 37 61 and 68; 30 x 1 500, 40 85 and 82; 24 x 4 096, 25 93 and 93; 30 x 93 clusters of 400
+// 98 and 73; fp32, d=64, 16 x 800, 56 83 and 85, 24 x 1 500, 25 96 and 92, 24 x 400, 87 108 and 92.  fp32 at d=128, whose parts a
+// wave reads one row pair at a time, gains up to 6 % where query clusters have a few members and loses 7 where they have more: up to
+// 24 in the mean (8 x 400, 75 105 and 112; 4 x 1 500, 75 103 and 101; past it 12 x 800, 10 100 and 93).  Keys gain at any size, since
+// their boxes cost the three launches more (fp32, d=128, 4 x 4 096, bound 48 96 and 106; 12 x 4 096, 48 122 and 137; fp32, d=64,
+// 58 x 312, 48 79 and 85; bf16, d=128, 30 x 1 500, 48 92 and 96; a cold attention call of 27 x 1 224, 80 223 and 229; past the lines
+// fp32, d=64, 76 x 722, 48 92 and 87; bf16, d=128, 30 x 2 500, 120 111 and 106).
 bool cluster_stats_fits(int dtype, int d, int H, int N, int m_bound, bool keys) {
   const long long groups = (long long)H * m_bound;
-  const int most = keys ? 1600 : dtype == ADACLUSTER_BF16 ? 900 + N / (d == 64 ? 3 : 16) : 900;
+  const int most = keys ? 2400 : dtype == ADACLUSTER_BF16 ? 900 + N / (d == 64 ? 3 : 16) : 900;
   return N <= STATS_ITEMS && groups <= most && groups * N <= (dtype == ADACLUSTER_BF16 ? 3000000 : 1500000) &&
          (keys || dtype == ADACLUSTER_BF16 || d == 64 || N <= 24 * m_bound);
 }

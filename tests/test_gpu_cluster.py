@@ -337,7 +337,7 @@ def test_kcluster_late_stages_end_where_each_head_does(d, iters):
 def test_short_heads_sorted_and_summed_per_cluster(dtype, d, N, m0, skew):
     """A workgroup a cluster (few heads), or sort, reduction and combination (many): the same bits, boxes and empty clusters
     among them; `skew` of the tokens are alike, so that one cluster holds many parts."""
-    H = max((3000000 if dtype == B.BF16 else 1500000) // N, 2300) // 16 + 1      # past the lines of cluster_stats_fits for 16 clusters
+    H = max((3000000 if dtype == B.BF16 else 1500000) // N, 2400) // 16 + 1      # past the lines of cluster_stats_fits for 16 clusters
     rng = np.random.default_rng(23)
     X = rng.standard_normal((1, N, d)).astype(np.float32)
     alike = rng.random(N) < skew
