@@ -189,6 +189,7 @@ struct WS {
   float* q_wsum; int32_t* q_wcnt;     // walk sums and counts of the one-read passes of the query clustering
   double* scores;       // [H][Cq][cap] centroid scores between the kernels of the selection step
   int32_t* rng_start; int32_t* rng_pre; int32_t* rng_cnt; int32_t* tiles; int32_t* ntiles;
+  int32_t* deal;        // tiles dealt by work (attn_deal_segs)
   int32_t* merge; int32_t* nmerge; float* part_o; float* part_ml;   // cut key lists of the attention step
   int32_t* krow;        // [H][Cq][kstride] every key row of a query cluster's list (see key_row_scale)
   // homes for outputs of the fused call the caller did not ask for
@@ -287,10 +288,11 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(tiles, int32_t*, H * (size_t)D.maxtiles * attn_tile_record() * 4);
   TAKE(merge, int32_t*, H * (size_t)attn_split_slots() * 4 * 4);
   TAKE(nmerge, int32_t*, H * 4);
+  TAKE(deal, int32_t*, attn_deal_ints(D.H, attn_deal_segs(p->dtype, D.d, D.H, D.N, D.Cq), attn_most_tiles(p->dtype, D.N, D.Cq, D.BM, D.maxtiles)) * 4);
   {  // partial results of split key lists: slots of cut lists (bf16), or a row per query and split (fp32; the dense call
      // counts as one cluster, which never makes fewer splits)
     const size_t splits = attn_f32_splits(D.H, D.N, 1);     // (1: the kernel writes the output itself)
-    const size_t rows = p->dtype == ADACLUSTER_BF16 ? H * (size_t)attn_split_slots() * D.BMmax : splits > 1 ? H * N * splits : 0;
+    const size_t rows = p->dtype == ADACLUSTER_BF16 ? H * (size_t)attn_split_slots() * D.BMmax + (size_t)attn_tail_slots(p->dtype, D.d, D.H, D.N, D.Cq) * D.BM : splits > 1 ? H * N * splits : 0;
     TAKE(part_o, float*, rows * d * 4);
     TAKE(part_ml, float*, rows * 2 * 4);
   }
@@ -314,7 +316,7 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(sel_idx, int32_t*, H * (size_t)D.Cq * D.cap * 4);
   TAKE(sel_cnt, int32_t*, H * (size_t)D.Cq * 4);
   TAKE(one_count, int32_t*, H * 4);
-  TAKE(sel_keys, int32_t*, H * (size_t)D.Cq * 4);
+  TAKE(sel_keys, int32_t*, (H * (size_t)D.Cq + 1) * 4);
   TAKE(stats, adacluster_head_stats*, H * sizeof(adacluster_head_stats));
 #undef TAKE
   if (w) w->base = base;
@@ -601,13 +603,14 @@ int run_plan_attention(const adacluster_params* p, const WS& w, hipStream_t st, 
                        const void* K, const void* V) {
   const Dims D = dims_of(p);
   const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)D.d);
-  RET_IF(launch_plan_sparse(st, p->dtype, D.H, D.Cq, D.cap, D.maxr, D.maxtiles, D.BM, w.offs_q, D.Cq + 1, w.offs_k,
+  const int segs = attn_deal_segs(p->dtype, D.d, D.H, D.N, D.Cq), most = attn_most_tiles(p->dtype, D.N, D.Cq, D.BM, D.maxtiles);
+  RET_IF(launch_plan_sparse(st, p->dtype, D.d, D.H, D.Cq, D.cap, D.maxr, D.maxtiles, D.BM, w.offs_q, D.Cq + 1, w.offs_k,
                             D.cap + 1, k_count, sel_idx, sel_cnt, w.rng_start, w.rng_pre, w.rng_cnt, w.tiles, w.ntiles,
-                            w.merge, w.nmerge, key_row_scale(p), w.krow, attn_krow_stride(D.N), w.perm_k, D.N, sel_keys));
+                            w.merge, w.nmerge, key_row_scale(p), w.krow, attn_krow_stride(D.N), w.perm_k, D.N, sel_keys, segs, most, w.deal, w.sel_keys + (size_t)D.H * D.Cq));
   prof_mark(EV_PLAN, st, prof_from);
-  RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, D.Cq, D.BM, attn_most_tiles(p->dtype, D.N, D.Cq, D.BM, D.maxtiles), D.maxtiles, scale, Q, K, V, O, w.perm_q,
+  RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, D.Cq, D.BM, most, D.maxtiles, scale, Q, K, V, O, w.perm_q,
                           w.tiles, w.ntiles, w.part_o, w.part_ml, w.merge, w.nmerge,
-                          w.krow, attn_krow_stride(D.N), w.rng_start, w.rng_pre, w.rng_cnt, D.maxr, w.perm_k));
+                          w.krow, attn_krow_stride(D.N), w.rng_start, w.rng_pre, w.rng_cnt, D.maxr, w.perm_k, segs, w.deal));
   prof_mark(EV_ATTN, st);
   return 0;
 }
@@ -862,7 +865,7 @@ int adacluster_dense_attn(const adacluster_params* p, const void* Q, const void*
   prof_mark(EV_PLAN, st);
   RET_IF(launch_attention(st, p->dtype, D.d, D.H, D.N, 1, shape.BM, (D.N + shape.BM - 1) / shape.BM * shape.pieces, D.maxtiles, scale, Q, K, V, O, nullptr, w.tiles,
                           w.ntiles, w.part_o, w.part_ml, shape.pieces > 1 ? w.merge : nullptr, w.nmerge,
-                          w.krow, attn_krow_stride(D.N), w.rng_start, w.rng_pre, w.rng_cnt, 1, nullptr));
+                          w.krow, attn_krow_stride(D.N), w.rng_start, w.rng_pre, w.rng_cnt, 1, nullptr, 0, nullptr));
   prof_mark(EV_ATTN, st);
   return 0;
 }

@@ -46,9 +46,77 @@ __device__ __forceinline__ int wave_prefix(int v, int lane) {
 // workgroup of its own that leaves unnormalised (O, m, l) in a partial slot, and attn_merge
 // combines the slots of a query tile.  merge [H][slots] x {first query position, rows, first slot,
 // chunks}; a head has `slots` partial slots, and lists stay whole once they are used up.
-constexpr int PLAN_ARRAYS = 8;      // integers of LDS per query cluster
-template <bool KNOWN>
-__device__ __forceinline__ void tiles_of_head(int32_t* sm, int h, int Cq, int maxr, int maxtiles, int BM, int slots, int allow_split,
+constexpr int PLAN_BESIDE = 256;       // query clusters up to which the LDS it takes (8 KB each) leaves the lists' workgroups their places
+__host__ __device__ constexpr int plan_ints(int Cq, bool deal) { return (deal ? 11 : 9) * Cq + 1; }      // of LDS
+// Tiles dealt to the XCDs by work (attn_deal_segs says when).  Workgroups go to the 8 XCDs in turn, and one is done when the last is.
+// The query clusters of a head are ordered by the length of their key lists, the longest first, and their tiles cut into `segs`
+// segments of equal work, each in eight parts of equal work, one for every XCD (the tiles of a cluster stay side by side); segment e's
+// parts are dealt from XCD e % 8 on, so that what rounding leaves evens out.  The last head to be planned writes every XCD's list: its
+// parts of all segments, the longest lists first, whatever head they are of, so that what ends last is short.  The tiles past the
+// last whole round of 32 CUs, where lists may be cut, go in pieces of their key list, so that no CU runs a whole one alone at the end.
+constexpr int DEAL_ENTRIES = 64;                     // segments at most
+// A head's record: the longest list (key tiles) of every segment, the first tile of every part of the segments and the end
+__host__ __device__ constexpr int deal_rec(int segs) { return segs + 8 * segs + 1; }
+constexpr int DEAL_PARTS = 10 * DEAL_ENTRIES;        // of all heads: H * segs <= DEAL_ENTRIES
+constexpr int DEAL_HEAD = 4 + 32;                    // an XCD's list: entries, those that are whole tiles, tiles in pieces, pieces of each; those tiles; the entries
+constexpr int TAIL_MOST = 8, TAIL_SLOTS = 64;        // pieces of a list, partial slots of an XCD
+__host__ __device__ constexpr int deal_cap(int tiles) { return tiles * 9 / 64 + 2; }       // most tiles of a part, of `tiles` in eight parts
+__host__ __device__ constexpr int deal_list(int H, int segs, int most) { return H * (most * 9 / 64 + 2 * segs) + TAIL_SLOTS; }      // most entries of an XCD
+struct DealtTile { int h, tile, z; };                // head, tile, piece
+__device__ __forceinline__ int dealt(int h, int tile, int z) { return h << 23 | tile << 3 | z; }
+__device__ __forceinline__ DealtTile dealt_tile(uint32_t e) { return {(int)(e >> 23), (int)(e >> 3 & 0xFFFFF), (int)(e & 7)}; }
+__device__ __forceinline__ int tail_pieces(int sp, int tiles) { return min(sp, max(1, tiles / 8)); }      // no piece of less than eight key tiles
+struct Deal { int32_t* parts /* [H][deal_rec(segs)] */; int32_t* lists /* [8][DEAL_HEAD + cap] */; int32_t* planned /* heads; 0 before the launch */; int cap, segs, H, cut_below /* tiles of an XCD */; };
+
+// By the workgroup of the last head to be planned.
+__device__ __forceinline__ void deal_lists(const Deal& dl) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int H = dl.H, segs = dl.segs, rec = deal_rec(segs), E = H * segs;
+  constexpr int ROUNDS = (DEAL_PARTS + 255) / 256;
+  __shared__ int32_t s_part[ROUNDS * 256], s_rank[DEAL_ENTRIES], s_by_rank[DEAL_ENTRIES];
+  {
+    int32_t v[ROUNDS];                               // (asked for together)
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) v[r] = __hip_atomic_load(dl.parts + min(tid + r * 256, H * rec - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) s_part[tid + r * 256] = v[r];
+    if (tid < DEAL_ENTRIES) s_rank[tid] = 0;
+  }
+  lds_barrier();
+  {                                                  // segments ahead of every segment, a quarter of them by every wave
+    const int key = lane < E ? s_part[lane / segs * rec + lane % segs] << 6 | (63 - lane) : 0;       // (no two alike)
+    int rank = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) rank += __builtin_amdgcn_readlane(key, wave * 16 + j) > key;
+    atomicAdd(&s_rank[lane], rank);
+  }
+  lds_barrier();
+  if (tid < E) s_by_rank[s_rank[tid]] = tid;
+  lds_barrier();
+  const int e = lane < E ? s_by_rank[lane] : 0, h = e / segs;      // a lane a segment, in order
+  const int32_t* const p = s_part + h * rec + segs + (e - h * segs) * 8;
+  for (int xcd = wave; xcd < 8; xcd += 4) {          // a wave an XCD
+    const int y = (xcd + e) & 7, first = p[y], n = lane < E ? p[y + 1] - first : 0;
+    const int incl = wave_prefix(n, lane), total = __builtin_amdgcn_readlane(incl, 63), rest = total < dl.cut_below ? total & 31 : 0, whole = total - rest;
+    int best = 1 << 30, sp = 1;                      // rounds of pieces, in 1/840 of a whole list, and a sixteenth of one for each
+#pragma unroll
+    for (int q = 1; q <= TAIL_MOST; ++q) {
+      const int cost = (q * rest + 31) / 32 * (840 / q) + 52 * q;
+      if (rest && q * rest <= TAIL_SLOTS && cost < best) { best = cost; sp = q; }
+    }
+    int32_t* const list = dl.lists + (size_t)xcd * (DEAL_HEAD + dl.cap);
+    if (lane == 0) *reinterpret_cast<int4*>(list) = int4{whole + rest * sp, whole, rest, sp};
+    for (int i = 0; i < n; ++i) {
+      const int s = incl - n + i;
+      if (s < whole) { list[DEAL_HEAD + s] = dealt(h, first + i, 0); continue; }
+      list[4 + s - whole] = dealt(h, first + i, 0);
+      for (int z = 0; z < sp; ++z) list[DEAL_HEAD + s + z * rest] = dealt(h, first + i, z);
+    }
+  }
+}
+
+template <bool KNOWN, bool DEAL>
+__device__ __forceinline__ void tiles_of_head(int32_t* sm, int h, int Cq, int maxr, int maxtiles, int BM, int slots, int allow_split, const Deal& dl,
                                               const int32_t* __restrict__ q_offs, int q_offs_stride, const int32_t* __restrict__ lengths,
                                               const int32_t* __restrict__ rng_pre, const int32_t* __restrict__ rng_cnt,
                                               int32_t* __restrict__ tiles, int32_t* __restrict__ ntiles,
@@ -59,8 +127,14 @@ __device__ __forceinline__ void tiles_of_head(int32_t* sm, int h, int Cq, int ma
   int32_t* ml = merge + (size_t)h * slots * 4;
   int32_t *const s_T = sm, *const s_nq = sm + C, *const s_pieces = sm + 2 * C, *const s_tile0 = sm + 3 * C, *const s_slot0 = sm + 4 * C,
           *const s_merge0 = sm + 5 * C, *const s_tot = sm + 6 * C, *const s_list = sm + 7 * C;
+  int32_t* const s_q0 = sm + 8 * C;                                                 // [C + 1] first rows
+  int32_t *const s_order = sm + 9 * C + 1, *const s_work = sm + 10 * C + 1;         // (dealt: the clusters in their order, the work before each)
+  const auto at_place = [&](int i) __attribute__((always_inline)) { if constexpr (DEAL) return s_order[i]; else return i; };
   for (int c = tid; c < C; c += 256) {
-    s_nq[c] = (qo[c + 1] - qo[c] + BM - 1) / BM;
+    const int q0 = qo[c], q1 = qo[c + 1];
+    s_nq[c] = (q1 - q0 + BM - 1) / BM;
+    s_q0[c] = q0;
+    if (c == C - 1) s_q0[C] = q1;
     int tot;
     if constexpr (KNOWN) tot = lengths[(size_t)h * Cq + c];
     else tot = rng_pre[((size_t)h * Cq + c) * (maxr + 1) + rng_cnt[(size_t)h * Cq + c]];
@@ -73,7 +147,7 @@ __device__ __forceinline__ void tiles_of_head(int32_t* sm, int h, int Cq, int ma
   const int per = (C + 255) / 256, c0 = min(C, tid * per), c1 = min(C, c0 + per), lane = tid & 63, wave = tid >> 6;
   __shared__ long long w_work[4];
   __shared__ int32_t w_a[4], w_b[4];
-  __shared__ int32_t s_cut, s_ntiles;
+  __shared__ int32_t s_cut, s_ntiles, s_last;
   {
     // key tiles per chunk of a list that is cut: twice the average list of the head, at least 16
     long long work = 0; int qtiles = 0;
@@ -115,26 +189,96 @@ __device__ __forceinline__ void tiles_of_head(int32_t* sm, int h, int Cq, int ma
     nmerge[h] = nm;
   }
   __syncthreads();
+  // What a tile takes: its key tiles and about four steps for start and end, and of a step a share that does not depend on how many
+  // of its waves have rows.
+  const auto step_of = [&](int rows) __attribute__((always_inline)) { return (rows + 31) / 32 + 1; };
+  const auto work_of = [&](int c, int& group) __attribute__((always_inline)) {      // of a cluster, and of BM of its rows
+    const int nq = s_nq[c], len = s_T[c] + 4 * s_pieces[c], last = s_q0[c + 1] - s_q0[c] - (nq - 1) * BM;
+    group = len * step_of(BM);
+    return nq > 0 ? (nq - 1) * group + len * step_of(last) : 0;
+  };
+  if constexpr (DEAL) {
+    __shared__ __attribute__((aligned(16))) int32_t s_key[PLAN_BESIDE];
+    const int mine = tid < C ? s_T[tid] << 8 | (255 - tid) : -1;      // (no two alike)
+    s_key[tid] = mine;
+    lds_barrier();
+    int place = 0;
+#pragma unroll 4
+    for (int o = 0; o < C; o += 4) {
+      const int4 k = *reinterpret_cast<const int4*>(&s_key[o]);
+      place += (k.x > mine) + (k.y > mine) + (k.z > mine) + (k.w > mine);
+    }
+    if (tid < C) s_order[place] = tid;
+    lds_barrier();
+  }
   {                                              // where every cluster's records start
-    int mine = 0;
-    for (int c = c0; c < c1; ++c) mine += s_nq[c] * s_pieces[c];
-    const int incl = wave_prefix(mine, lane);
-    if (lane == 63) w_a[wave] = incl;
+    int mine = 0, work = 0, g;
+    for (int i = c0; i < c1; ++i) {
+      const int c = at_place(i);
+      mine += s_nq[c] * s_pieces[c];
+      if constexpr (DEAL) work += work_of(c, g);
+    }
+    const int incl = wave_prefix(mine, lane), wincl = DEAL ? wave_prefix(work, lane) : 0;
+    if (lane == 63) { w_a[wave] = incl; w_b[wave] = wincl; }
     __syncthreads();
-    int nt = incl - mine;
-    for (int w = 0; w < wave; ++w) nt += w_a[w];
-    for (int c = c0; c < c1; ++c) { s_tile0[c] = nt; nt += s_nq[c] * s_pieces[c]; }
-    if (tid == 255) { ntiles[h] = nt; s_ntiles = nt; }
+    int nt = incl - mine, wt = wincl - work;
+    for (int w = 0; w < wave; ++w) { nt += w_a[w]; wt += w_b[w]; }
+    for (int i = c0; i < c1; ++i) {
+      const int c = at_place(i);
+      s_tile0[i] = nt; nt += s_nq[c] * s_pieces[c];
+      if constexpr (DEAL) { s_work[i] = wt; wt += work_of(c, g); }
+    }
+    if (tid == 255) { ntiles[h] = nt; s_ntiles = nt; s_cut = wt; }
   }
   __syncthreads();
+  if constexpr (DEAL) {
+    __shared__ int32_t s_bound[8 * 8 + 1], s_longest[8];      // (of at most eight segments)
+    const int total = s_cut, nt = s_ntiles, segs = dl.segs, an = total / (8 * segs), over = total - an * 8 * segs;
+    for (int k = tid; k <= 8 * segs; k += 256) {
+      const int want = an * k + over * k / (8 * segs);
+      int lo = 0, hi = C - 1;                    // the last cluster whose work starts at or before it
+      while (lo < hi) { const int mid = (lo + hi + 1) >> 1; if (s_work[mid] <= want) lo = mid; else hi = mid - 1; }
+      const int c = s_order[lo], nq = s_nq[c], pieces = s_pieces[c];
+      int group, at = 0;
+      (void)work_of(c, group);
+      if (nq > 0) at = min((int)((float)(want - s_work[lo]) / (float)group * (float)pieces + 0.5f), nq * pieces);      // (to the nearest tile)
+      s_bound[k] = k == 0 ? 0 : k == 8 * segs ? nt : s_tile0[lo] + at;
+      if (k % 8 == 0 && k < 8 * segs) s_longest[k / 8] = s_T[c];
+    }
+    lds_barrier();
+    if (tid < 64) {
+      int32_t* d = dl.parts + (size_t)h * deal_rec(segs);
+      const auto put = [&](int i, int v) __attribute__((always_inline)) { __hip_atomic_store(d + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+      if (tid < segs) {
+        int at[9];
+#pragma unroll
+        for (int x = 0; x <= 8; ++x) at[x] = s_bound[8 * tid + x];
+        const int cap = deal_cap(at[8] - at[0]);
+        put(tid, s_longest[tid]);
+        int b = at[0];
+        put(segs + 8 * tid, b);
+#pragma unroll
+        for (int x = 1; x < 8; ++x) {
+          b = min(max(max(at[x], b), at[8] - (8 - x) * cap), min(b + cap, at[8]));
+          put(segs + 8 * tid + x, b);
+        }
+      }
+      if (tid == 63) put(9 * segs, nt);
+      // The stores go through to where every XCD sees them, and have arrived when they are counted: the head reports only then.  (A
+      // release fence instead writes back all that the lists' workgroups have left in the L2, 8-12 us.)
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    lds_barrier();
+    if (tid == 0) s_last = __hip_atomic_fetch_add(dl.planned, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == dl.H - 1;
+  }
   // The records, one a thread: the last cluster whose records start at or before it (an empty one shares its start with
   // the next).  One thread per cluster wrote 625 records one after the other where 20 000 rows are a single cluster.
   for (int t = tid; t < s_ntiles; t += 256) {
-    int c = 0, hi = C - 1;
-    while (c < hi) { const int mid = (c + hi + 1) >> 1; if (s_tile0[mid] <= t) c = mid; else hi = mid - 1; }
-    const int i = t - s_tile0[c], T = s_T[c], pieces = s_pieces[c], per_piece = (T + pieces - 1) / pieces;
+    int lo = 0, hi = C - 1;
+    while (lo < hi) { const int mid = (lo + hi + 1) >> 1; if (s_tile0[mid] <= t) lo = mid; else hi = mid - 1; }
+    const int c = at_place(lo), i = t - s_tile0[lo], T = s_T[c], pieces = s_pieces[c], per_piece = (T + pieces - 1) / pieces;
     const int group = i / pieces, k = i - group * pieces;                    // rows group * BM .. of the cluster, chunk k
-    const int r0 = qo[c] + group * BM, rows = min(BM, qo[c + 1] - r0);
+    const int r0 = s_q0[c] + group * BM, rows = min(BM, s_q0[c + 1] - r0);
     int32_t* t6 = tl + (size_t)t * TILE_REC;
     t6[0] = c; t6[1] = r0; t6[2] = rows;
     t6[3] = pieces > 1 ? k * per_piece : 0; t6[4] = pieces > 1 ? min(T, (k + 1) * per_piece) : T;
@@ -143,6 +287,10 @@ __device__ __forceinline__ void tiles_of_head(int32_t* sm, int h, int Cq, int ma
       int32_t* m = ml + (size_t)(s_merge0[c] + group) * 4;
       m[0] = r0; m[1] = rows; m[2] = s_slot0[c] + i; m[3] = pieces;
     }
+  }
+  if constexpr (DEAL) {
+    lds_barrier();
+    if (s_last) deal_lists(dl);
   }
 }
 
@@ -153,8 +301,8 @@ struct TilePlan {
   const int32_t* lengths; const int32_t* q_offs; int q_offs_stride;
   int maxtiles, BM, slots, allow_split;
   int32_t* tiles; int32_t* ntiles; int32_t* merge; int32_t* nmerge;
+  Deal deal;
 };
-constexpr int PLAN_BESIDE = 256;       // query clusters up to which the LDS it takes (8 KB each) leaves the lists' workgroups their places
 
 __device__ __forceinline__ void keys_of_list(int i, int h, int Cq, int cap, int maxr, int row_scale,
                             const int32_t* __restrict__ k_offs, int k_offs_stride,
@@ -263,33 +411,35 @@ __device__ __forceinline__ void keys_of_list(int i, int h, int Cq, int cap, int 
   if (nr <= LR) fill(l_rs, l_rp); else fill(rs, rp);
 }
 
-template <bool TILES>
-__global__ __launch_bounds__(256) void plan_sparse(int Cq, int cap, int maxr, int row_scale,
+template <bool TILES, bool DEAL>
+__global__ __launch_bounds__(256, 8) void plan_sparse(int Cq, int cap, int maxr, int row_scale,
                             const int32_t* __restrict__ k_offs, int k_offs_stride,
                             const int32_t* __restrict__ k_count,
                             const int32_t* __restrict__ sel_idx, const int32_t* __restrict__ sel_cnt,
                             int32_t* __restrict__ rng_start, int32_t* __restrict__ rng_pre,
                             int32_t* __restrict__ rng_cnt, int32_t* __restrict__ krow, size_t kstride,
                             const int32_t* __restrict__ perm_k, int N, TilePlan tp) {
-  const int h = blockIdx.y, i = (int)blockIdx.x - (TILES ? 1 : 0);
+  const int h = blockIdx.x, i = (int)blockIdx.y - (TILES ? 1 : 0);      // (the workgroups that plan tiles, the longest chains, are the first)
   if (i >= 0) {
     keys_of_list(i, h, Cq, cap, maxr, row_scale, k_offs, k_offs_stride, k_count, sel_idx, sel_cnt, rng_start, rng_pre, rng_cnt, krow, kstride, perm_k, N);
+    if (!TILES && tp.deal.planned && i == 0 && h == 0 && threadIdx.x == 0) *tp.deal.planned = 0;      // (for plan_tiles)
   } else if constexpr (TILES) {
     extern __shared__ int32_t plan_lds[];
-    tiles_of_head<true>(plan_lds, h, Cq, maxr, tp.maxtiles, tp.BM, tp.slots, tp.allow_split, tp.q_offs, tp.q_offs_stride, tp.lengths, nullptr, nullptr, tp.tiles,
+    tiles_of_head<true, DEAL>(plan_lds, h, Cq, maxr, tp.maxtiles, tp.BM, tp.slots, tp.allow_split, tp.deal, tp.q_offs, tp.q_offs_stride, tp.lengths, nullptr, nullptr, tp.tiles,
                   tp.ntiles, tp.merge, tp.nmerge);
   }
 }
 
-__global__ __launch_bounds__(256) void plan_tiles(int Cq, int maxr, int maxtiles, int BM, int slots, int allow_split,
+template <bool DEAL>
+__global__ __launch_bounds__(256) void plan_tiles(int Cq, int maxr, int maxtiles, int BM, int slots, int allow_split, Deal dl,
                                                   const int32_t* __restrict__ q_offs, int q_offs_stride,
                                                   const int32_t* __restrict__ rng_pre,
                                                   const int32_t* __restrict__ rng_cnt,
                                                   int32_t* __restrict__ tiles, int32_t* __restrict__ ntiles,
                                                   int32_t* __restrict__ merge, int32_t* __restrict__ nmerge) {
-  constexpr int MAXC = 4096;                       // the largest q_clusters the library accepts
-  __shared__ int32_t sm[PLAN_ARRAYS * MAXC];
-  tiles_of_head<false>(sm, blockIdx.x, min(Cq, MAXC), maxr, maxtiles, BM, slots, allow_split, q_offs, q_offs_stride, nullptr, rng_pre, rng_cnt, tiles,
+  constexpr int MAXC = DEAL ? PLAN_BESIDE : 4096;   // the largest q_clusters the library accepts
+  __shared__ int32_t sm[plan_ints(MAXC, DEAL)];
+  tiles_of_head<false, DEAL>(sm, blockIdx.x, min(Cq, MAXC), maxr, maxtiles, BM, slots, allow_split, dl, q_offs, q_offs_stride, nullptr, rng_pre, rng_cnt, tiles,
                 ntiles, merge, nmerge);
 }
 
@@ -395,6 +545,7 @@ struct AttnArgs {
   const int32_t* perm_k;                 // their order -> token (NULL: identity): for the fp32 kernel without a table
   int splits;                            // fp32: most pieces a key list may go in, and what f32_pieces() says
   Pieces pieces;
+  const int32_t* deal; int deal_stride;  // tiles dealt by work (Deal::lists; NULL: not)
 };
 
 // Workgroup -> (head, query tile) of a launch of pick_tile_grid.  Workgroups go to the 8 XCDs round-robin in launch order,
@@ -503,7 +654,16 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
   // Workgroups go to the 8 XCDs round-robin in launch order (gridDim.x is a multiple of 8, so
   // XCD = blockIdx.x % 8), and each XCD has its own L2.
   int h, tile;
-  if (a.head_major) {
+  int z = 0, sp = 1, part = 0;           // piece of the key list, of how many, and its partial slot
+  if (a.deal) {
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int32_t* list = a.deal + (size_t)xcd * a.deal_stride;
+    const int e = list[DEAL_HEAD + slot];          // (asked for with the head of the list)
+    if (slot >= list[0]) return;
+    const DealtTile dt = dealt_tile(e);
+    h = dt.h; tile = dt.tile; z = dt.z;
+    if (slot >= list[1]) { sp = list[3]; part = xcd * TAIL_SLOTS + slot - list[1]; }
+  } else if (a.head_major) {
     // Heads are dealt to XCDs whole, eight at a time: all query tiles of a head then stream that
     // head's K/V rows behind one L2.  The H % 8 heads left over are split eight ways by tile.
     const int gx = gridDim.x, gx8 = gx >> 3;
@@ -530,7 +690,16 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
   }
   const int32_t* tl = a.tiles + ((size_t)h * a.maxtiles + tile) * TILE_REC;
   const int qc = tl[0], row0 = tl[1], nrows = tl[2];
-  const int kt0 = tl[3], kt1 = tl[4], pslot = tl[5];    // this workgroup's share of the key list
+  int kt0 = tl[3], kt1 = tl[4], pslot = tl[5];          // this workgroup's share of the key list
+  if (pslot >= 0) {
+    if (z > 0) return;                                   // (a list that is cut already stays as it is)
+    pslot += h * a.slots;
+  } else if (sp > 1) {
+    const int T = kt1;
+    sp = tail_pieces(sp, T);
+    if (z >= sp) return;
+    if (sp > 1) { const int per = (T + sp - 1) / sp; kt0 = z * per; kt1 = min(T, kt0 + per); pslot = a.H * a.slots + part; }
+  }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, hb = lane >> 5;
 
@@ -846,7 +1015,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
       // a chunk of a cut key list: leave the unnormalised accumulator, the reference and the
       // row sum in this chunk's slot; attn_merge combines the chunks of the query tile
       const int rr = wave * 32 + c;
-      const size_t so = ((size_t)h * a.slots + pslot) * a.BM + rr;
+      const size_t so = (size_t)pslot * a.BM + rr;
       float* po = a.part_o + so * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
@@ -1186,10 +1355,27 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a, const int32_t* __r
   // not one after the other: the kernel is a handful of dependent round trips either way, so what counts is
   // how many of its loads are in flight at once.
   constexpr int MAXP = 16;                       // most chunks a list is cut into (plan_tiles)
-  const int h = blockIdx.y, n = nmerge[h];
+  // Rows past the heads (dealt tiles): an XCD each, whose last tiles went in pieces too.
+  const bool tail = (int)blockIdx.y >= a.H;
+  const int32_t* list = tail ? a.deal + (size_t)(blockIdx.y - a.H) * a.deal_stride : nullptr;
+  int h = blockIdx.y;
+  const int n = !tail ? nmerge[h] : list[3] > 1 ? list[2] : 0;
   for (int e = blockIdx.x; e < n; e += gridDim.x) {
-    const int32_t* ml = merge + ((size_t)h * a.slots + e) * 4;
-    const int row0 = ml[0], nrows = ml[1], slot0 = ml[2], pieces = min(ml[3], MAXP);
+    int row0, nrows, pieces;
+    size_t slot0, stride;                          // partial slots of the pieces
+    if (tail) {
+      const DealtTile dt = dealt_tile(list[4 + e]);      // (asked for with the head of the list)
+      h = dt.h;
+      const int32_t* tl = a.tiles + ((size_t)h * a.maxtiles + dt.tile) * TILE_REC;
+      pieces = tail_pieces(list[3], tl[4]);
+      if (tl[5] >= 0 || pieces == 1) continue;     // not cut here
+      row0 = tl[1]; nrows = tl[2];
+      slot0 = (size_t)a.H * a.slots + (blockIdx.y - a.H) * TAIL_SLOTS + e; stride = list[2];
+    } else {
+      const int32_t* ml = merge + ((size_t)h * a.slots + e) * 4;
+      row0 = ml[0]; nrows = ml[1]; pieces = min(ml[3], MAXP);
+      slot0 = (size_t)h * a.slots + ml[2]; stride = 1;
+    }
     const int32_t* pq = a.perm_q ? a.perm_q + (size_t)h * a.N : nullptr;
     bf16raw* Oh = (bf16raw*)a.O + (size_t)h * a.N * D;
     constexpr int LPR = D / 4;                     // lanes per row, four columns each
@@ -1199,7 +1385,7 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a, const int32_t* __r
       float4 os[MAXP];
 #pragma unroll
       for (int s = 0; s < MAXP; ++s) {
-        const size_t so = ((size_t)h * a.slots + slot0 + min(s, pieces - 1)) * a.BM + r;
+        const size_t so = (slot0 + min(s, pieces - 1) * stride) * a.BM + r;
         ms[s] = a.part_ml[so * 2];
         ls[s] = a.part_ml[so * 2 + 1];
         os[s] = *reinterpret_cast<const float4*>(a.part_o + so * D + col);
@@ -1322,9 +1508,32 @@ int attn_tile_record() { return TILE_REC; }
 int attn_split_slots() { return SPLIT_SLOTS; }
 // Tiles of a head that the grid of a sparse launch is sized for, at least what it can have.  Workgroups go to the CUs in turn, so
 // those without work leave places empty that a small launch would have used: where no list is cut, none for pieces.
+static bool lists_may_be_cut(int N) { return (N + 63) / 64 > 2 * MIN_CHUNK; }
 int attn_most_tiles(int dtype, int N, int Cq, int BM, int maxtiles) {
-  return dtype == ADACLUSTER_BF16 && (N + 63) / 64 <= 2 * MIN_CHUNK ? N / BM + Cq + 1 : maxtiles;
+  return dtype == ADACLUSTER_BF16 && !lists_may_be_cut(N) ? N / BM + Cq + 1 : maxtiles;
 }
+static int attn_resident(int d, int BM) { return 256 * (BM == 128 ? 2 : 1) * (d == 64 ? 2 : 1); }      // workgroups of the bf16 kernel
+// Segments a head where the tiles of a sparse launch are dealt by work; 0 where by their number.  Dealt by number, an XCD has what its heads
+// happen to have: 16 heads of 14 119 tokens, d=128, some without structure, attention 1 130 -> 700 us; 30 x 21 600, top-p 1 720 -> 1 250;
+// 4 x 13 200 170 -> 146; 5 x 9 247 (65 tiles on the 64 places of an XCD) 212 -> 155.  The plan takes 2-8 us more (its last head
+// waits for three trips to memory), so a tile a CU (n < 256) or short lists (under 75 key tiles a place: 23 x 1 680, d=128, 176 -> 181 us a
+// call, 19 x 3 864, d=64, 144 -> 148; but 29 x 4 140 490 -> 476, 17 x 3 405, d=128, 333 -> 273) are not worth it, and from
+// sixteen rounds on the ends of the lists are less than that.  Heads of equal lists are what neither side gains by: 30 x 17 776 773 and 775 us.
+constexpr double DEAL_MIN = 75;      // key tiles (of a list of all keys) a place
+constexpr int DEAL_CUT = 2;          // rounds from which the last tiles stay whole: their partial results and the merge take 6-12 us (30 x 17 776)
+int attn_deal_segs(int dtype, int d, int H, int N, int Cq) {
+  if (dtype != ADACLUSTER_BF16 || Cq < 2 || Cq > PLAN_BESIDE || H > DEAL_ENTRIES) return 0;
+  const int BM = attn_block_rows(dtype, d, N, Cq), tiles = N / BM + Cq / 2 + 1, T = (N + 63) / 64;
+  const double n = (double)H * tiles, r = attn_resident(d, BM);
+  if (n < 256 || n >= 16 * r || n * T < DEAL_MIN * r || 9.0 * H * (N / BM + Cq + 1) * (T + 64.0) >= 2147483648.0) return 0;
+  return max(1, min(min(8, DEAL_ENTRIES / H), tiles / 16));
+}
+size_t attn_deal_ints(int H, int segs, int most) { return segs ? DEAL_PARTS + 8 * (size_t)(DEAL_HEAD + deal_list(H, segs, most) + 3) : 0; }
+static Deal deal_of(int d, int BM, int H, int N, int segs, int most, int32_t* deal, int32_t* planned) {
+  if (!segs) return {};
+  return {deal, deal + DEAL_PARTS, planned, (deal_list(H, segs, most) + 3) / 4 * 4, segs, H, lists_may_be_cut(N) ? DEAL_CUT * attn_resident(d, BM) / 8 : 0};
+}
+int attn_tail_slots(int dtype, int d, int H, int N, int Cq) { return attn_deal_segs(dtype, d, H, N, Cq) && lists_may_be_cut(N) ? 8 * TAIL_SLOTS : 0; }
 
 // Most pieces a key list of the fp32 kernel may go in (see pick_tile).  From some 1 024 tiles on there are two rounds of whole
 // ones (d=128), and the partial results of every row and the launch that combines them cost what the last round leaves idle
@@ -1375,21 +1584,23 @@ static Pieces f32_pieces(int N) {
 }
 
 bool plan_reads_lengths(int Cq) { return Cq <= PLAN_BESIDE; }
-int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
+int launch_plan_sparse(hipStream_t s, int dtype, int d, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
                        const int32_t* q_offs, int q_offs_stride, const int32_t* k_offs, int k_offs_stride,
                        const int32_t* k_count, const int32_t* sel_idx, const int32_t* sel_cnt,
                        int32_t* rng_start, int32_t* rng_pre, int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles,
                        int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride,
-                       const int32_t* perm_k, int N, const int32_t* lengths) {
+                       const int32_t* perm_k, int N, const int32_t* lengths, int segs, int most, int32_t* deal, int32_t* planned) {
   const int split = dtype == ADACLUSTER_BF16 ? 1 : 0;
-  const TilePlan tp{lengths, q_offs, q_offs_stride, maxtiles, BM, SPLIT_SLOTS, split, tiles, ntiles, merge, nmerge};
+  const TilePlan tp{lengths, q_offs, q_offs_stride, maxtiles, BM, SPLIT_SLOTS, split, tiles, ntiles, merge, nmerge, deal_of(d, BM, H, N, segs, most, deal, planned)};
   if (lengths && plan_reads_lengths(Cq)) {
-    plan_sparse<true><<<dim3(Cq + 1, H), 256, PLAN_ARRAYS * 4 * Cq, s>>>(Cq, cap, maxr, row_scale, k_offs, k_offs_stride, k_count, sel_idx, sel_cnt, rng_start,
-                                                                         rng_pre, rng_cnt, krow, kstride, perm_k, N, tp);
+    const auto plan = segs ? plan_sparse<true, true> : plan_sparse<true, false>;
+    plan<<<dim3(H, Cq + 1), 256, plan_ints(Cq, segs != 0) * 4, s>>>(
+        Cq, cap, maxr, row_scale, k_offs, k_offs_stride, k_count, sel_idx, sel_cnt, rng_start, rng_pre, rng_cnt, krow, kstride, perm_k, N, tp);
   } else {
-    plan_sparse<false><<<dim3(Cq, H), 256, 0, s>>>(Cq, cap, maxr, row_scale, k_offs, k_offs_stride, k_count, sel_idx, sel_cnt, rng_start, rng_pre, rng_cnt,
-                                                   krow, kstride, perm_k, N, tp);
-    plan_tiles<<<H, 256, 0, s>>>(Cq, maxr, maxtiles, BM, SPLIT_SLOTS, split, q_offs, q_offs_stride, rng_pre, rng_cnt, tiles, ntiles, merge, nmerge);
+    plan_sparse<false, false><<<dim3(H, Cq), 256, 0, s>>>(Cq, cap, maxr, row_scale, k_offs, k_offs_stride, k_count, sel_idx, sel_cnt, rng_start, rng_pre,
+                                                          rng_cnt, krow, kstride, perm_k, N, tp);
+    const auto plan = segs ? plan_tiles<true> : plan_tiles<false>;
+    plan<<<H, 256, 0, s>>>(Cq, maxr, maxtiles, BM, SPLIT_SLOTS, split, tp.deal, q_offs, q_offs_stride, rng_pre, rng_cnt, tiles, ntiles, merge, nmerge);
   }
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
 }
@@ -1405,14 +1616,18 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
                      const void* Q, const void* K, const void* V, void* O, const int32_t* perm_q,
                      const int32_t* tiles, const int32_t* ntiles, float* part_o, float* part_ml,
                      const int32_t* merge, const int32_t* nmerge, const int32_t* krow, size_t kstride,
-                     const int32_t* rng_start, const int32_t* rng_pre, const int32_t* rng_cnt, int maxr, const int32_t* perm_k) {
+                     const int32_t* rng_start, const int32_t* rng_pre, const int32_t* rng_cnt, int maxr, const int32_t* perm_k,
+                     int segs, int32_t* deal) {
   AttnArgs a{Q, K, V, O, perm_q, tiles, ntiles, H, N, Cq, maxtiles,
              scale * 1.4426950408889634f,
              (Cq == 1 || (size_t)4 * N * d <= ((size_t)8 << 20)) ? 1 : 0,
              part_o, part_ml, SPLIT_SLOTS, BM, krow, kstride,
-             rng_start, rng_pre, rng_cnt, maxr, perm_k, dtype == ADACLUSTER_F32 ? attn_f32_splits(H, N, Cq) : 1, {}};
+             rng_start, rng_pre, rng_cnt, maxr, perm_k, dtype == ADACLUSTER_F32 ? attn_f32_splits(H, N, Cq) : 1, {}, nullptr, 0};
+  const Deal dl = deal_of(d, BM, H, N, segs, most, deal, nullptr);
+  if (segs) { a.deal = dl.lists; a.deal_stride = DEAL_HEAD + dl.cap; }
   if (a.splits > 1) a.pieces = d == 64 ? f32_pieces<64>(N) : f32_pieces<128>(N);
-  dim3 g((most + 7) / 8 * 8, H);
+  const bool cut = Cq == 1 || lists_may_be_cut(N);
+  const dim3 g = segs ? dim3(8 * dl.cap) : dim3((most + 7) / 8 * 8, H);
   if (dtype == ADACLUSTER_BF16) {
     if (BM == 128) {
       if (d == 64) attn_mfma<64, 4, 2, 4, 0><<<g, 256, 0, s>>>(a);
@@ -1421,9 +1636,10 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
       if (d == 64) attn_mfma<64, A64_NW, A64_NBUF, A64_MINB, A64_VPRE><<<g, A64_NW * 64, 0, s>>>(a);
       else attn_mfma<128, A128_NW, A128_NBUF, A128_MINB, A128_VPRE><<<g, A128_NW * 64, 0, s>>>(a);
     }
-    if (merge && (Cq == 1 || (N + 63) / 64 > 2 * MIN_CHUNK)) {      // the chunks of cut key lists
-      if (d == 64) attn_merge<64><<<dim3(MERGE_GROUPS, H, 4), 256, 0, s>>>(a, merge, nmerge);
-      else attn_merge<128><<<dim3(MERGE_GROUPS, H, 4), 256, 0, s>>>(a, merge, nmerge);
+    if (merge && cut) {      // the chunks of cut key lists
+      const dim3 gm(MERGE_GROUPS, segs ? H + 8 : H, 4);
+      if (d == 64) attn_merge<64><<<gm, 256, 0, s>>>(a, merge, nmerge);
+      else attn_merge<128><<<gm, 256, 0, s>>>(a, merge, nmerge);
     }
   } else {
     const int splits = a.splits;

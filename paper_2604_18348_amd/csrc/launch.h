@@ -145,7 +145,7 @@ int launch_select(hipStream_t s, int H, int Cq, int cap, int d, int score_mode, 
                   float top_p, float scale, const float* q_cent, const float* q_mean_norm, const float* k_cent,
                   const float* k_bmin, const float* k_bmax, const int32_t* k_sizes, const int32_t* k_count,
                   const int32_t* full_flag, int32_t* sel_idx, int32_t* sel_cnt, int kc_max, double* scores,   // scores: scratch [H][Cq][cap]
-                  int32_t* sel_keys /* [H][Cq] keys of the selected clusters, or NULL */);
+                  int32_t* sel_keys /* [H][Cq] keys of the selected clusters and an integer that becomes 0, or NULL */);
 
 int attn_block_rows(int dtype, int d, int N, int Cq);   // queries per workgroup of the attention launch
 int attn_block_rows_min(int dtype);
@@ -159,12 +159,18 @@ int attn_tile_record();      // ints per query-tile record
 int attn_most_tiles(int dtype, int N, int Cq, int BM, int maxtiles);
 int attn_split_slots();      // partial slots per head for the chunks of cut key lists (also extra tile records)
 bool plan_reads_lengths(int Cq);   // whether launch_plan_sparse has a use for the lengths of the lists
-int launch_plan_sparse(hipStream_t s, int dtype, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
+int launch_plan_sparse(hipStream_t s, int dtype, int d, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
                        const int32_t* q_offs, int q_offs_stride, const int32_t* k_offs, int k_offs_stride,
                        const int32_t* k_count, const int32_t* sel_idx, const int32_t* sel_cnt,
                        int32_t* rng_start, int32_t* rng_pre, int32_t* rng_cnt, int32_t* tiles, int32_t* ntiles,
                        int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride, const int32_t* perm_k, int N,
-                       const int32_t* lengths /* [H][Cq] keys of every list, or NULL: not known beforehand */);
+                       const int32_t* lengths /* [H][Cq] keys of every list, or NULL: not known beforehand */,
+                       int segs /* attn_deal_segs() */, int most /* attn_most_tiles() */, int32_t* deal, int32_t* planned /* an integer; with lengths: 0 */);
+// Tiles of a sparse launch dealt to the XCDs by work: segments a head (0: dealt by their number), the integers of its table, and the
+// partial slots of the whole launch for the pieces of the last tiles (behind the attn_split_slots() of every head).
+int attn_deal_segs(int dtype, int d, int H, int N, int Cq);
+size_t attn_deal_ints(int H, int segs, int most);
+int attn_tail_slots(int dtype, int d, int H, int N, int Cq);
 struct DenseShape { int BM, pieces; };       // queries a workgroup, chunks of the key list
 DenseShape attn_dense_shape(int dtype, int d, int H, int N);
 int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, DenseShape shape, int32_t* rng_start, int32_t* rng_pre,
@@ -179,6 +185,7 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
                      const int32_t* tiles, const int32_t* ntiles, float* part_o, float* part_ml,
                      const int32_t* merge /* NULL: no cut lists */, const int32_t* nmerge,
                      const int32_t* krow /* NULL: not attn_rows_listed */, size_t kstride, const int32_t* rng_start,
-                     const int32_t* rng_pre, const int32_t* rng_cnt, int maxr, const int32_t* perm_k /* NULL: identity */);
+                     const int32_t* rng_pre, const int32_t* rng_cnt, int maxr, const int32_t* perm_k /* NULL: identity */,
+                     int segs /* 0: dealt by their number */, int32_t* deal);
 
 }  // namespace adac

@@ -470,6 +470,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelectCfg cfg, const double
   __syncthreads();
   if (lane == 0) wsum2[wave] = keys;
   __syncthreads();
+  if (tid == 0 && h == 0 && i == 0) sel_keys[(size_t)gridDim.y * cfg.Cq] = 0;
   if (tid == 0) sel_keys[(size_t)h * cfg.Cq + i] = wsum2[0] + wsum2[1] + wsum2[2] + wsum2[3];
 }
 

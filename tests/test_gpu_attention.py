@@ -466,3 +466,44 @@ def test_fp32_lists_shorter_than_their_split(d):
                                        torch.from_numpy(kl).cuda(), torch.full((H,), Ck, dtype=torch.int32, device="cuda"), si, sc, ws=ws))
     for h in range(H):
         check(O[h], orc.sparse_attention_gather(Q[h], K[h], V[h], ql[h], kl[h], sel[h]), B.F32)
+
+
+@pytest.mark.parametrize("H,N,d,Cq", [(64, 2600, 64, 24),       # as many heads as are dealt by work
+                                      (5, 9247, 128, 65),       # the last tiles of an XCD in pieces of their lists
+                                      (2, 34000, 128, 3),       # 256 queries a workgroup, a list of all keys
+                                      (16, 5000, 64, 256),      # as many query clusters as are dealt by work, many of a row or none
+                                      (7, 6001, 128, 33)])
+def test_tiles_dealt_by_work(H, N, d, Cq):
+    """Heads and clusters of very different lists (none, one cluster, all), so that parts, order and pieces of the tiles differ from XCD
+    to XCD; every row against float64 on the device, and a second call bit for bit."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(H * N)
+    Ck = 40
+    Q, K, V = (torch.randn((H, N, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    rng = np.random.default_rng(N)
+    ql = np.minimum((Cq * rng.random((H, N)) ** 2).astype(np.int32), Cq - 1)
+    kl = rng.integers(0, Ck, (H, N)).astype(np.int32)
+    sel = [[np.sort(rng.choice(Ck, size=Ck if i == Cq // 2 else int(rng.integers(0, max(2, Ck * (h + 1) // H))), replace=False)) for i in range(Cq)]
+           for h in range(H)]
+    p = B.Params(H=H, N=N, d=d, dtype=B.BF16, q_clusters=Cq, k_m0=4, k_m_min=1, k_max_clusters=Ck)
+    si, sc = sel_to_dev(sel, Cq, p.cap)
+    qt, kt = torch.from_numpy(ql).cuda(), torch.from_numpy(kl).cuda()
+    kc = torch.full((H,), Ck, dtype=torch.int32, device="cuda")
+    ws = B.workspace(p)
+    O = B.adacluster_sparse_attn(p, Q, K, V, qt, kt, kc, si, sc, ws=ws)
+    again = B.adacluster_sparse_attn(p, Q, K, V, qt, kt, kc, si, sc, ws=ws)
+    assert torch.equal(O, again)
+    worst = 0.0
+    for h in range(H):
+        ref = torch.zeros((N, d), dtype=torch.float64, device="cuda")
+        for i in range(Cq):
+            rows = torch.nonzero(qt[h] == i)[:, 0]
+            keys = torch.nonzero(torch.isin(kt[h], torch.from_numpy(sel[h][i].astype(np.int32)).cuda()))[:, 0]
+            for r in rows.split(4096) if len(keys) else ():
+                P = torch.softmax(Q[h, r].double() @ K[h, keys].double().T.contiguous() / d ** 0.5, 1)
+                ref[r] = P @ V[h, keys].double()
+        got = O[h].double()
+        rel, mx = float((got - ref).norm() / ref.norm().clamp_min(1e-30)), float((got - ref).abs().max())
+        assert rel < 1e-2 and mx < 2e-2, (h, rel, mx)
+        worst = max(worst, rel)
+    print("dealt", H, N, d, Cq, worst)
