@@ -290,6 +290,12 @@ struct OpenCfg {
 
 struct NewState { int ucount, ccount, m_t, stage, done, full, active; };      // a state without its tables
 
+// Where in a list of n points initial centre j of m is: floor((2j+1) n / 2m).
+__device__ __forceinline__ int sample_at(int j, int n, int m) {
+  const uint64_t p = (2ull * j + 1) * (uint32_t)n;
+  return (2ull * m * (uint32_t)n) >> 32 ? (int)(p / (2u * m)) : (int)((uint32_t)p / (2u * m));
+}
+
 // Head of the while-loop: done?  flag F?  else the number of centres.
 __device__ __forceinline__ void loop_head(NewState& s, int N, int n_max, int m0, int m_min, int max_stages, int u_min) {
   if (s.ucount == 0) s.done = 1;
@@ -297,7 +303,8 @@ __device__ __forceinline__ void loop_head(NewState& s, int N, int n_max, int m0,
   else if (s.stage >= max_stages || s.ucount <= u_min) s.done = 1;
   s.active = !s.done;
   if (s.active) {
-    const int m = (int)(((long long)m0 * s.ucount + N - 1) / N);
+    const uint64_t p = (uint64_t)m0 * (uint32_t)s.ucount + (uint32_t)(N - 1);
+    const int m = p >> 32 ? (int)(p / (uint32_t)N) : (int)((uint32_t)p / (uint32_t)N);      // (a division of 64 bits is a microsecond)
     s.m_t = min(max(m_min, min(m0, m)), s.ucount);
   } else s.m_t = 0;
 }
@@ -305,17 +312,23 @@ __device__ __forceinline__ void loop_head(NewState& s, int N, int n_max, int m0,
 // By one thread of a head: the last head to report writes {active heads, max |U|, max m_t, epoch} to the host's slot.
 __device__ __forceinline__ void report_stage(const OpenCfg& c, const NewState& s, bool act) {
   if (!c.report) return;
+  // Atomics alone, each waited for where the next may not overtake it: a fence instead writes back and drops what the launch has in the L2.
+  const auto done = [] { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
   if (act) { atomicAdd(&c.sums[0], 1); atomicMax(&c.sums[1], s.ucount); atomicMax(&c.sums[2], s.m_t); }
-  __threadfence();
+  done();
   if (atomicAdd(&c.sums[3], 1) == (int)gridDim.y - 1) {
-    __threadfence();
-    for (int i = 0; i < 3; ++i) c.report[i] = atomicExch(&c.sums[i], 0);
+    int v[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) v[i] = atomicExch(&c.sums[i], 0);
     atomicExch(&c.sums[3], 0);
-    __hip_atomic_store(&c.report[3], c.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);     // (the host polls this word)
+#pragma unroll
+    for (int i = 0; i < 3; ++i) __hip_atomic_store(&c.report[i], v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    done();
+    __hip_atomic_store(&c.report[3], c.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);     // (the host polls this word)
   }
 }
 
-// By the first workgroup of a head: the state of a head that was closed before goes on as it is ...
+// By one workgroup of a head, which has no points (the report waits for memory several times): the state of a head that was closed before goes on as it is ...
 __device__ __forceinline__ void carry_state(const OpenCfg& c, int h, int tid) {
   if (tid < (int)(sizeof(KState) / 4)) reinterpret_cast<int32_t*>(&c.out[h])[tid] = reinterpret_cast<const int32_t*>(&c.in[h])[tid];
   if (tid == 0) report_stage(c, NewState{}, false);
@@ -336,26 +349,41 @@ __device__ __forceinline__ void write_state(const OpenCfg& c, int h, int tid, co
 }
 
 // Survivors by position: the last pass of a stage left them, in order, from the start of every `items` points on, and their
-// counts.  OPEN_COUNTS counts at most; called by a whole workgroup of at least as many threads, cnt_mine the thread's count.
+// counts.  OPEN_COUNTS counts at most.  Every wave forms the prefix for itself, of counts `lane` and 64 + `lane`, and all write the same:
+// no barrier.  Returns the number of survivors; pre[k] of the counts behind nb is that number.
 constexpr int OPEN_COUNTS = STAGE_SUM_BLOCKS;
-__device__ __forceinline__ void survivor_prefix(int nb, int cnt_mine, int32_t* pre /* LDS, [OPEN_COUNTS + 1] */) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  static_assert(OPEN_COUNTS == 128, "two waves");
-  int incl = tid < nb ? cnt_mine : 0;
+__device__ __forceinline__ int survivor_prefix(int nb, int c0, int c1, int32_t* pre /* LDS, [OPEN_COUNTS + 1] */) {
+  const int lane = threadIdx.x & 63;
+  static_assert(OPEN_COUNTS == 128, "two counts a lane");
+  int a = lane < nb ? c0 : 0, b = lane + 64 < nb ? c1 : 0;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
-  if (tid == 0) pre[0] = 0;
-  if (tid < OPEN_COUNTS) pre[tid + 1] = incl;
-  __syncthreads();
-  const int first = pre[64];
-  __syncthreads();
-  if (tid >= 64 && tid < OPEN_COUNTS) pre[tid + 1] = incl + first;
-  __syncthreads();
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(a, o), v = __shfl_up(b, o);
+    if (lane >= o) { a += u; b += v; }
+  }
+  const int first = __builtin_amdgcn_readlane(a, 63);
+  if (lane == 0) pre[0] = 0;
+  pre[lane + 1] = a;
+  pre[lane + 65] = first + b;
+  __builtin_amdgcn_wave_barrier();
+  return first + __builtin_amdgcn_readlane(b, 63);
 }
-__device__ __forceinline__ int survivor_at(const int32_t* pre, int nb, int items, int p) {      // where in the list of a head survivor p is
-  int lo = 0, hi = nb - 1;
-  while (lo < hi) { const int mid = (lo + hi + 1) >> 1; if (pre[mid] <= p) lo = mid; else hi = mid - 1; }
-  return lo * items + p - pre[lo];
+// Where in the list of a head survivors p[0 .. K-1] are: the searches side by side, their reads of a step together.
+template <int K>
+__device__ __forceinline__ void survivors_at(const int32_t* pre, int items, int (&p)[K]) {
+  int lo[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) lo[k] = 0;
+#pragma unroll
+  for (int o = OPEN_COUNTS / 2; o >= 1; o >>= 1) {
+    int v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = pre[lo[k] + o];
+#pragma unroll
+    for (int k = 0; k < K; ++k) lo[k] += v[k] <= p[k] ? o : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) p[k] += lo[k] * items - pre[lo[k]];
 }
 
 // A value that is the same in every lane, for the compiler too.  What is read from LDS counts as different from lane to lane, and a
@@ -363,26 +391,28 @@ __device__ __forceinline__ int survivor_at(const int32_t* pre, int nb, int items
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // The opening of a stage by every workgroup (x) of a head (y) for itself: its points, centres and where those go, and the survivors'
-// prefix of nb counts.  False: the head is done.
-__device__ __forceinline__ bool open_stage(const OpenCfg& oc, int h, int32_t* pre, int& nbo, int& n, int& m, int& row_off) {
-  const int tid = threadIdx.x;
+// prefix.  False: the head is done.  The last workgroup, behind those that may have points, writes and reports the state: the first
+// one's points waited for that, 2-4 us.
+__device__ __forceinline__ bool open_stage(const OpenCfg& oc, int h, int32_t* pre, int& n, int& m, int& row_off) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const bool writes = blockIdx.x == gridDim.x - 1;
   NewState s{oc.N, 0, 0, 0, 0, 0, 0};
   if (oc.first) {
     if (oc.sums && h == 0 && blockIdx.x == 0 && tid < 4) oc.sums[tid] = 0;
   } else {
     const KState& o = oc.in[h];
-    const int c0 = oc.cnt[(size_t)h * oc.cnt_stride + min(tid, oc.cnt_stride - 1)];          // (ahead of the state: one trip for both)
+    const int32_t* cnt = oc.cnt + (size_t)h * oc.cnt_stride;          // (ahead of the state: one trip for both)
+    const int c0 = cnt[min(lane, oc.cnt_stride - 1)], c1 = cnt[min(lane + 64, oc.cnt_stride - 1)];
     if (!o.active) {
-      if (blockIdx.x == 0) carry_state(oc, h, tid);
+      if (writes) carry_state(oc, h, tid);
       return false;
     }
-    nbo = min((min(o.ucount, oc.N) + oc.items - 1) / oc.items, OPEN_COUNTS);
+    const int nb = min((int)((uint32_t)(min(o.ucount, oc.N) + oc.items - 1) / (uint32_t)oc.items), OPEN_COUNTS);
     s.ccount = o.ccount + o.m_t; s.stage = o.stage + 1; s.full = o.full;
-    survivor_prefix(nbo, c0, pre);
-    s.ucount = uniform(pre[nbo]);
+    s.ucount = survivor_prefix(nb, c0, c1, pre);
   }
   loop_head(s, oc.N, oc.n_max, oc.m0, oc.m_min, oc.max_stages, oc.u_min);
-  if (blockIdx.x == 0) write_state(oc, h, tid, s);
+  if (writes) { write_state(oc, h, tid, s); return false; }
   if (!s.active) return false;
   n = s.ucount; m = s.m_t; row_off = s.ccount;
   return true;
@@ -410,42 +440,32 @@ __device__ __forceinline__ float4 block_sum(const PassSums& prev, int h, int j, 
   for (int o = 1; o < LPC; o <<= 1) nj += __shfl_xor(nj, o);
   return s;
 }
-// The sums of R waves that share a tile of 32 centres (part 0 .. R-1 of tile ct) meet in part 0: half of them hand theirs to the
-// other half, until one holds all.  `ps`: LDS that nobody needs, [waves / 2 * 32][D + 4].
-template <int D>
-__device__ __forceinline__ void meet_sums(f32x16_t (&sacc)[D / 32], float* ps, int R, int ct, int part, int c, int hb) {
-  constexpr int DT = D / 32, PROW = D + 4;            // floats of a padded row: the float4 pieces of 8 centres fall in 8 bank groups
-  for (int half = R / 2; half >= 1; half >>= 1) {
-    __syncthreads();                     // the points, or the sums of the round before, have been read
-    float* const slot = ps + ((size_t)((ct * half + (part & (half - 1))) * 32 + c)) * PROW + 4 * hb;
-    if (part >= half && part < 2 * half) {
+// The sums of the R waves that share a tile of 32 centres, waves ct * R .. ct * R + R - 1, to the rows of block b of centres below m.  All
+// waves hand theirs over at once and every thread adds pieces of the result, ((0+4)+(2+6))+((1+5)+(3+7)) of eight waves: two barriers
+// (half of the waves to the other half, until one holds all, six: 1.3 and, d=128, 2.4 us, now 0.7 and 1.3).
+// `ps`: LDS that is free behind a barrier, [NW][32][D] floats: piece q (16 bytes) of row r sits in slot q ^ (r & 7).
+template <int D, int NW>
+__device__ __forceinline__ void store_sums(const f32x16_t (&sacc)[D / 32], float* ps, const PassSums& out, int h, int b, int m, int R, int wave, int c, int hb) {
+  constexpr int DT = D / 32, PPR = D / 4;
+  __syncthreads();                       // the points have been read
 #pragma unroll
-      for (int db = 0; db < DT; ++db)
+  for (int db = 0; db < DT; ++db)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          *reinterpret_cast<float4*>(slot + db * 32 + 8 * i) = float4{sacc[db][4 * i], sacc[db][4 * i + 1], sacc[db][4 * i + 2], sacc[db][4 * i + 3]};
-    }
-    __syncthreads();
-    if (part < half) {
-#pragma unroll
-      for (int db = 0; db < DT; ++db)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float4 o = *reinterpret_cast<const float4*>(slot + db * 32 + 8 * i);
-          sacc[db][4 * i] += o.x; sacc[db][4 * i + 1] += o.y; sacc[db][4 * i + 2] += o.z; sacc[db][4 * i + 3] += o.w;
-        }
-    }
-  }
-}
-// Value v of a tile is dim db*32 + 8*(v/4) + 4*hb + v%4 of centre cid: to its row of block b.
-template <int D>
-__device__ __forceinline__ void store_sums(const f32x16_t (&sacc)[D / 32], const PassSums& out, int h, int b, int cid, int hb) {
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db) {
-    float* o = out.psum + ((size_t)h * out.P + (size_t)cid * out.nb_stride + b) * D + db * 32 + 4 * hb;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<float4*>(o + 8 * i) = float4{sacc[db][4 * i], sacc[db][4 * i + 1], sacc[db][4 * i + 2], sacc[db][4 * i + 3]};
+    for (int i = 0; i < 4; ++i)          // value v of a tile is dim db*32 + 8*(v/4) + 4*hb + v%4 of its centre c
+      *reinterpret_cast<float4*>(ps + (size_t)(wave * 32 + c) * D + ((db * 8 + 2 * i + hb) ^ (c & 7)) * 4) =
+          float4{sacc[db][4 * i], sacc[db][4 * i + 1], sacc[db][4 * i + 2], sacc[db][4 * i + 3]};
+  __syncthreads();
+  for (int item = threadIdx.x; item < m * PPR; item += NW * 64) {
+    const int j = item / PPR, q = item % PPR, r = j & 31;
+    const float* at = ps + (size_t)((j >> 5) * R * 32 + r) * D + (q ^ (r & 7)) * 4;
+    const auto part = [&](int k) __attribute__((always_inline)) { return *reinterpret_cast<const float4*>(at + (size_t)k * 32 * D); };
+    const auto add = [](float4 a, float4 b) __attribute__((always_inline)) { return float4{a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w}; };
+    float4 v;
+    if (R == 8) v = add(add(add(part(0), part(4)), add(part(2), part(6))), add(add(part(1), part(5)), add(part(3), part(7))));
+    else if (R == 4) v = add(add(part(0), part(2)), add(part(1), part(3)));
+    else if (R == 2) v = add(part(0), part(1));
+    else v = part(0);
+    *reinterpret_cast<float4*>(out.psum + ((size_t)h * out.P + (size_t)j * out.nb_stride + b) * D + q * 4) = v;
   }
 }
 
@@ -477,17 +497,24 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf1
   constexpr int KS = D / 16, PB = 2, CROWB = D * 2, CH = D / 8, DT = D / 32, NT = NW * 64;
   const int h = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int n, m, row_off, nbo = 0;
+  const int c = lane & 31, hb = lane >> 5, base = blockIdx.x * NT;
+  int n, m, row_off;
   __shared__ int32_t pre[FORM == PASS_OPEN ? OPEN_COUNTS + 1 : 1];
+  int pos[PB], tok[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) pos[pb] = base + wave * (PB * 32) + pb * 32 + c;
   if constexpr (FORM == PASS_OPEN) {
-    if (!open_stage(oc, h, pre, nbo, n, m, row_off)) return;
+    if (!open_stage(oc, h, pre, n, m, row_off)) return;
   } else {
+    // (the points are asked for with the state, and those past the last one, whatever stands there, forgotten: one trip for both)
+    if (cfg.ulist) {
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) tok[pb] = cfg.ulist[(size_t)h * cfg.N + min(pos[pb], cfg.N - 1)];
+    }
     if (!assign_setup(cfg, h, n, m, row_off)) return;
   }
-  const int base = blockIdx.x * NT;
   if (base >= n) return;
   m = min(m, ACC_MAXM);
-  const int c = lane & 31, hb = lane >> 5;
   const int CT = (m + 31) >> 5;
   // The centres, then the points, then the partial sums of the waves.  Piece g (16 bytes) of centre row r sits in slot g ^
   // swz(r), of point row r in slot g ^ xswz(r) (see qpass_mfma).
@@ -499,24 +526,25 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf1
   auto swz = [](int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); };
   auto xswz = [](int r) { return D == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : ((((r >> 1) & 1) << 2) | (((r >> 1) & 7) >> 1)); };
 
-  // B operand: this lane's point rows
+  // B operand: this lane's point rows (those of points past the last one are loaded and never used)
   bf16x8_t xf[PB][KS];
-  int pos[PB], tok[PB];
-#pragma unroll
-  for (int pb = 0; pb < PB; ++pb) {
-    pos[pb] = base + wave * (PB * 32) + pb * 32 + c;
-    const int p = min(pos[pb], n - 1);
-    if (FORM == PASS_OPEN && !oc.first) tok[pb] = oc.surv[(size_t)h * cfg.N + survivor_at(pre, nbo, oc.items, p)];
-    else tok[pb] = cfg.ulist ? cfg.ulist[(size_t)h * cfg.N + p] : p;
-  }
   // (opening: centre j is survivor floor((2j+1) n / 2m); looked up with the points, so that all rows are then asked for together)
   __shared__ int32_t ctok[FORM == PASS_OPEN ? ACC_MAXM : 1];
   if constexpr (FORM == PASS_OPEN) {
-    if (tid < m) {
-      const int q = (int)(((2ll * tid + 1) * (long long)n) / (2ll * m));
-      ctok[tid] = oc.first ? q : oc.surv[(size_t)h * cfg.N + survivor_at(pre, nbo, oc.items, q)];
+    static_assert(PB == 2, "two points and a centre a thread");
+    const int q = sample_at(min(tid, m - 1), n, m);
+    int at[3] = {min(pos[0], n - 1), min(pos[1], n - 1), q};
+    if (!oc.first) {
+      survivors_at(pre, oc.items, at);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) at[k] = oc.surv[(size_t)h * cfg.N + at[k]];
     }
+    tok[0] = at[0]; tok[1] = at[1];
+    if (tid < m) ctok[tid] = at[2];
     __syncthreads();
+  } else {
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) tok[pb] = pos[pb] >= n ? 0 : cfg.ulist ? tok[pb] : pos[pb];
   }
 #pragma unroll
   for (int pb = 0; pb < PB; ++pb) {
@@ -697,7 +725,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf1
 #pragma unroll
       for (int w = 0; w < NW; ++w) { k += wkept[w]; s += wsum[w]; }
       if (counts) cfg.keep_cnt[(size_t)h * cfg.keep_stride + blockIdx.x] = k;
-      if (cfg.dist_sum) cfg.dist_sum[(size_t)h * gridDim.x + blockIdx.x] = s;
+      if (cfg.dist_sum) cfg.dist_sum[(size_t)h * (gridDim.x - (FORM == PASS_OPEN ? 1 : 0)) + blockIdx.x] = s;
     }
     if (counts && cfg.surv && hb == 0) {   // the survivors in order, for the pass that opens the next stage
       int at = base;
@@ -764,9 +792,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void stage_pass(const bf1
       }
     }
   }
-  static_assert(NW / 2 * 32 * (D + 4) * 4 <= NT * CROWB && ACC_MAXM == STAGE_COUNTS, "the partial sums fit the buffer of the points");
-  meet_sums<D>(sacc, reinterpret_cast<float*>(pool), R, ct, part, c, hb);
-  if (part == 0 && cid < m) store_sums<D>(sacc, out, h, b, cid, hb);
+  static_assert(NW * 32 * D * 4 <= NT * CROWB && ACC_MAXM == STAGE_COUNTS, "the partial sums fit the buffer of the points");
+  store_sums<D, NW>(sacc, reinterpret_cast<float*>(pool), out, h, b, m, R, wave, c, hb);
   if (tid < m) out.bcnt[((size_t)h * out.nb_stride + b) * ACC_MAXM + tid] = cnt_s[tid];
 }
 
@@ -1168,19 +1195,20 @@ __global__ __launch_bounds__(512, D == 128 ? 2 : FORM == PASS_COMBINE ? 4 : 6) v
   constexpr int NT = 512, NP = PASS_F32_POINTS, MAXM = PASS_F32_CENTRES, ROWB = D * 4, PPR = D / 4, CPL = D / 64;
   const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 31, hb = lane >> 5, pg = wave & 3, sp = wave >> 2;
-  int n, m, row_off, nbo = 0;
+  int n, m, row_off, t = 0;
   __shared__ int32_t pre[OPEN ? OPEN_COUNTS + 1 : 1], ctok[OPEN ? MAXM : 1];
-  if constexpr (OPEN) {
-    if (!open_stage(oc, h, pre, nbo, n, m, row_off)) return;
-  } else {
-    if (!assign_setup(cfg, h, n, m, row_off)) return;
-  }
   int b = blockIdx.x;
   if (FORM != PASS_COMBINE && nblk > 1) {                 // (small launches need no turn)
     b += h - (int)__umulhi((uint32_t)h, turns) * nblk;    // h % nblk, of at most 2^16 heads and 2^7 blocks
     if (b >= nblk) b -= nblk;
   }
   const int base = b * NP;
+  if constexpr (OPEN) {
+    if (!open_stage(oc, h, pre, n, m, row_off)) return;
+  } else {
+    if (tid < NP && cfg.ulist) t = cfg.ulist[(size_t)h * cfg.N + min(base + tid, cfg.N - 1)];      // (with the state, as in stage_pass)
+    if (!assign_setup(cfg, h, n, m, row_off)) return;
+  }
   if (base >= n) return;
   m = min(m, MAXM);
   const int CT = (m + 31) >> 5;
@@ -1191,21 +1219,19 @@ __global__ __launch_bounds__(512, D == 128 ? 2 : FORM == PASS_COMBINE ? 4 : 6) v
   __shared__ int32_t sidx[2][NP], tok_s[NP], lab_s[NP];
   const float* Xh = X + (size_t)h * cfg.N * D;
   auto slot_of = [](int r, int q) { return (q & ~15) | ((q ^ r) & 15); };       // where piece q (16 bytes) of row r is, as in assign_f32
-  // tokens of the points, and (opening) of the centres, survivor floor((2j+1) n / 2m)
-  if (tid < NP) {
-    const int p = min(base + tid, n - 1);
-    int t;
-    if (OPEN && !oc.first) {
-      t = oc.surv[(size_t)h * cfg.N + survivor_at(pre, nbo, oc.items, p)];
-      if (base + tid < n) oc.uout[(size_t)h * cfg.N + p] = t;
-    } else t = cfg.ulist ? cfg.ulist[(size_t)h * cfg.N + p] : p;
-    tok_s[tid] = t;
-  } else if (tid < NP + MAXM) {
-    const int j = tid - NP;
-    if (OPEN && j < m) {
-      const int q = (int)(((2ll * j + 1) * (long long)n) / (2ll * m));
-      ctok[j] = oc.first ? q : oc.surv[(size_t)h * cfg.N + survivor_at(pre, nbo, oc.items, q)];
+  // tokens of the points (one of any for those past the last), and (opening) of the centres, survivor floor((2j+1) n / 2m)
+  if (OPEN && tid < NP + MAXM) {
+    const bool point = tid < NP;
+    int at[1] = {point ? min(base + tid, n - 1) : sample_at(min(tid - NP, m - 1), n, m)};
+    if (!oc.first) {
+      survivors_at(pre, oc.items, at);
+      at[0] = oc.surv[(size_t)h * cfg.N + at[0]];
+      if (point && base + tid < n) oc.uout[(size_t)h * cfg.N + base + tid] = at[0];
     }
+    if (point) tok_s[tid] = at[0];
+    else if (tid - NP < m) ctok[tid - NP] = at[0];
+  } else if (!OPEN && tid < NP) {
+    tok_s[tid] = base + tid >= n ? 0 : cfg.ulist ? t : base + tid;
   }
   __syncthreads();
 #pragma unroll
@@ -2186,7 +2212,7 @@ __global__ __launch_bounds__(64 * INIT_ROWS) void init_centroids(const T* __rest
 #pragma unroll
     for (int q = 0; q < CPL; ++q) val[q] = master[((size_t)h * master_stride + j) * D + lane + 64 * q];
   } else {
-    const long long tok = ((2ll * j + 1) * (long long)N) / (2ll * m);
+    const int tok = sample_at(j, N, m);
     const T* row = X + ((size_t)h * N + tok) * D;
 #pragma unroll
     for (int q = 0; q < CPL; ++q) val[q] = Elem<T>::load(row + lane + 64 * q);
@@ -2340,14 +2366,14 @@ __global__ __launch_bounds__(256) void stage_open(const T* __restrict__ X, OpenC
     const KState& o = c.in[h];
     const int c0 = cnt[min(tid, c.cnt_stride - 1)];          // (ahead of the state: one trip for both)
     if (!o.active) {               // closed before: carried over
-      if (bx == 0) carry_state(c, h, tid);
+      if (bx == (int)gridDim.x - 1) carry_state(c, h, tid);
       return;
     }
     s.ucount = o.ucount; s.ccount = o.ccount; s.m_t = o.m_t; s.stage = o.stage; s.full = o.full; s.done = 0;
     n = min(s.ucount, c.N);
     const int nb = (n + c.items - 1) / c.items;
     if (bx < c.nblk) {
-      if (bx >= nb) return;        // (bx 0 stays: an active head has a point)
+      if (bx >= nb) return;
 #pragma unroll
       for (int i = 0; i < IPT; ++i) {
         const int p = p0 + i;
@@ -2378,7 +2404,7 @@ __global__ __launch_bounds__(256) void stage_open(const T* __restrict__ X, OpenC
     s.ucount = total; s.ccount += s.m_t; s.stage += 1;
   }
   loop_head(s, c.N, c.n_max, c.m0, c.m_min, c.max_stages, c.u_min);
-  if (bx == 0) write_state(c, h, tid, s);
+  if (bx == (int)gridDim.x - 1) { write_state(c, h, tid, s); return; }      // (one more than moves points or forms centres)
 
   if (bx < c.nblk) {               // the survivors of this workgroup's points move up, in order
     __syncthreads();
@@ -2407,14 +2433,13 @@ __global__ __launch_bounds__(256) void stage_open(const T* __restrict__ X, OpenC
   // initial centre j: survivor number floor((2j+1)|U| / 2m)
   const int j0 = (bx - c.nblk) * 4, j = j0 + wave;
   if (!s.active || j0 >= s.m_t) return;
-  long long pos = ((2ll * j + 1) * (long long)total) / (2ll * s.m_t);
-  int tok = (int)pos;
+  int tok = sample_at(j, total, s.m_t);
   if (!c.first) {
 #pragma unroll
     for (int w = 0; w < 4; ++w) {  // the thread whose run of counts holds it says in which count and how far into it
-      const long long q = ((2ll * (j0 + w) + 1) * (long long)total) / (2ll * s.m_t);
+      const int q = sample_at(j0 + w, total, s.m_t);
       if (j0 + w < s.m_t && q >= ex && q < ex + mine) {
-        int b = b0, left = (int)q - ex;
+        int b = b0, left = q - ex;
         for (; left >= cnt[b]; ++b) left -= cnt[b];
         s_blk[w] = b; s_rank[w] = left;
       }
@@ -2578,10 +2603,15 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
     // the stage that ended left its survivors: they become U, as stage_open would have moved them
     __shared__ int32_t pre[OPEN_COUNTS + 1];
     const int nb = uniform(min((min(s_st.ucount, cfg.N) + cfg.items - 1) / cfg.items, OPEN_COUNTS));
-    survivor_prefix(nb, cfg.cnt[(size_t)h * cfg.cnt_stride + min(tid, cfg.cnt_stride - 1)], pre);
+    const int32_t* cnt = cfg.cnt + (size_t)h * cfg.cnt_stride;
+    const int survivors = survivor_prefix(nb, cnt[min(lane, cfg.cnt_stride - 1)], cnt[min(lane + 64, cfg.cnt_stride - 1)], pre);
     int32_t* u = cfg.ulist[(s_st.stage + 1) & 1] + (size_t)h * cfg.N;
-    const int total = uniform(min(pre[nb], SMALL_NU));
-    for (int p = tid; p < total; p += NT) u[p] = cfg.surv[(size_t)h * cfg.N + survivor_at(pre, nb, cfg.items, p)];
+    const int total = min(survivors, SMALL_NU);
+    for (int p = tid; p < total; p += NT) {
+      int at[1] = {p};
+      survivors_at(pre, cfg.items, at);
+      u[p] = cfg.surv[(size_t)h * cfg.N + at[0]];
+    }
     __syncthreads();
     if (tid == 0) next_stage(total);
     __syncthreads();
@@ -2602,8 +2632,7 @@ __global__ __launch_bounds__(SmallStage<D>::NW * 64) void kstages_small(const bf
     if (tid < SMALL_M) cnt_s[tid] = 0;
     for (int j = wave; j < SMALL_M; j += NW) {
       if (j < m) {
-        const long long pos = ((2ll * j + 1) * (long long)n) / (2ll * m);
-        const int tok = uin[pos];
+        const int tok = uin[sample_at(j, n, m)];
         const bf16raw* row = Xh + (size_t)tok * D;
         float bsum = 0.f;
 #pragma unroll
@@ -3029,7 +3058,7 @@ int launch_stage_pass(hipStream_t s, int dtype, int d, int H, int N, int n_bound
   const int pts = pass_points(dtype, wide), nb = (n_bound + pts - 1) / pts;
   const PassSums in = prev ? PassSums{prev->psum, prev->bcnt, m_bound * nb, nb} : PassSums{}, to = out ? PassSums{out->psum, out->bcnt, m_bound * nb, nb} : PassSums{};
   if (m_bound > (dtype == ADACLUSTER_F32 ? PASS_F32_CENTRES : ACC_MAXM) || (prev && (!wide || open)) || !out != (end != nullptr)) return ADACLUSTER_E_INTERNAL;
-  const dim3 g(nb, H);
+  const dim3 g(open ? nb + 1 : nb, H);
   float* dist2 = end ? end->dist2 : nullptr;
   if (dtype == ADACLUSTER_F32) {
     auto launch = [&](auto dim) {
@@ -3213,7 +3242,7 @@ int launch_stage_open(hipStream_t s, int dtype, int d, int H, int N, int cap, co
   c.lp = assign_lp; c.f32 = assign_f32; c.bias = bias;
   if (c.items > KEEP_ITEMS) return ADACLUSTER_E_INTERNAL;
   if (f) c.nblk = (n_bound + c.items - 1) / c.items;
-  const dim3 g(c.nblk + (m_bound + 3) / 4, H);
+  const dim3 g(c.nblk + (m_bound + 3) / 4 + 1, H);
   if (dtype == ADACLUSTER_BF16) {
     if (d == 64) stage_open<bf16raw, 64><<<g, 256, 0, s>>>((const bf16raw*)X, c);
     else stage_open<bf16raw, 128><<<g, 256, 0, s>>>((const bf16raw*)X, c);
