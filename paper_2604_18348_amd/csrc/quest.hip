@@ -8,57 +8,109 @@
 #include "common.h"
 #include "launch.h"
 
+#include <type_traits>
+
 namespace adac {
 
-// ---- Eq. 1 with vector arithmetic: 64 x 64 outputs per workgroup, 4 x 4 per thread, operands staged through
-// LDS 32 dimensions at a time
-template <typename T>
-__global__ __launch_bounds__(256) void quest_alu(int Lq, int Lk, int d, int clamp, const T* __restrict__ Q,
+// ---- Eq. 1 with vector arithmetic: 16 TI x 64 outputs per workgroup, TI x 4 per thread, operands staged through
+// LDS 32 dimensions at a time, a dimension's values of all rows side by side, so that a thread reads four at once.
+// Bound by vector issue: max(q p, q n) is q times the larger of p and n where q >= 0, and times the smaller where q < 0 (rounding is
+// monotonic), so a term is a select and a multiply-add behind one comparison of q for four pages, not two products, a maximum and an
+// add: 2.25 instructions of 4.  That holds for finite values; from the first 32 dimensions with any other on, a workgroup forms its terms as Eq. 1
+// writes them.  18 heads x 12 039 rows x 865 pages, d=128, bf16 1 949 -> 1 181 us, 6 x 81 444 x 416, d=128, fp32 2 344 -> 1 451, 8 x 75 861 x
+// 387, d=64 1 375 -> 917, 10 x 168 x 105 17.6 -> 9.8 (56 % of the vector rate; 4 x 4 outputs a thread, scalar LDS reads: 57 % for 4 a term).
+template <typename T, int TI>
+__global__ __launch_bounds__(256) void quest_alu(int Lq, int Lk, int d, int clamp, int aligned, int whole, const T* __restrict__ Q,
                                                  const T* __restrict__ Rp, const T* __restrict__ Rn,
                                                  float* __restrict__ S) {
-  constexpr int TD = 32;
-  __shared__ float qs[64][TD + 1], ps[64][TD + 1], ns[64][TD + 1];
-  const int h = blockIdx.z, q0 = blockIdx.x * 64, k0 = blockIdx.y * 64, tid = threadIdx.x;
-  const int tq = (tid >> 4) * 4, tk = (tid & 15) * 4;
+  constexpr int TD = 32, QR = 16 * TI, E = 16 / sizeof(T), PIECES = TD / E;      // E: values of a 16-byte piece
+  __shared__ __attribute__((aligned(16))) float qs[TD][QR + 4], his[TD][68], los[TD][68];
+  __shared__ int odd;
+  const int h = blockIdx.z, q0 = blockIdx.x * QR, k0 = blockIdx.y * 64, tid = threadIdx.x;
+  const int tq = (tid >> 4) * TI, tk = (tid & 15) * 4;
   const T* Qh = Q + (size_t)h * Lq * d;
   const T* Ph = Rp + (size_t)h * Lk * d;
   const T* Nh = Rn + (size_t)h * Lk * d;
-  float acc[4][4];
+  float acc[TI][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+  auto piece = [&](const T* p, float (&x)[E]) __attribute__((always_inline)) {
+    T raw[E];
+    if (whole) *reinterpret_cast<uint4*>(raw) = *reinterpret_cast<const uint4*>(p);
+    else {                                         // (a caller's tensors may start anywhere)
+#pragma unroll
+      for (int e = 0; e < E; ++e) raw[e] = p[e];
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) x[e] = Elem<T>::load(&raw[e]);
+  };
+  if (tid == 0) odd = 0;
   for (int d0 = 0; d0 < d; d0 += TD) {
-    __syncthreads();
-    for (int e = tid; e < 64 * TD; e += 256) {
-      const int r = e / TD, cc = e % TD;
-      qs[r][cc] = (q0 + r < Lq) ? Elem<T>::load(Qh + (size_t)(q0 + r) * d + d0 + cc) : 0.f;
-      float p = 0.f, n = 0.f;
+    __syncthreads();                               // the values of the step before have been read
+    bool finite = true;
+    for (int e = tid; e < QR * PIECES; e += 256) {
+      const int r = e % QR, g = e / QR;
+      float x[E] = {};
+      if (q0 + r < Lq) piece(Qh + (size_t)(q0 + r) * d + d0 + g * E, x);
+#pragma unroll
+      for (int i = 0; i < E; ++i) { qs[g * E + i][r] = x[i]; finite = finite && fabsf(x[i]) < INFINITY; }
+    }
+    for (int e = tid; e < 64 * PIECES; e += 256) {
+      const int r = e % 64, g = e / 64;
+      float p[E] = {}, n[E] = {};
       if (k0 + r < Lk) {
-        p = Elem<T>::load(Ph + (size_t)(k0 + r) * d + d0 + cc);
-        n = Elem<T>::load(Nh + (size_t)(k0 + r) * d + d0 + cc);
-        if (clamp) { p = fmaxf(p, 0.f); n = fminf(n, 0.f); }
+        piece(Ph + (size_t)(k0 + r) * d + d0 + g * E, p);
+        piece(Nh + (size_t)(k0 + r) * d + d0 + g * E, n);
       }
-      ps[r][cc] = p; ns[r][cc] = n;
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        if (clamp) { p[i] = fmaxf(p[i], 0.f); n[i] = fminf(n[i], 0.f); }
+        const float hi = fmaxf(p[i], n[i]), lo = fminf(p[i], n[i]);
+        his[g * E + i][r] = hi; los[g * E + i][r] = lo;
+        finite = finite && fabsf(hi) < INFINITY && fabsf(lo) < INFINITY;
+      }
     }
+    if (!finite) odd = 1;                          // (stays: the steps that follow are formed term by term as well)
     __syncthreads();
+    auto terms = [&](auto plain) __attribute__((always_inline)) {
 #pragma unroll 4
-    for (int cc = 0; cc < TD; ++cc) {
-      float qv[4], pv[4], nv[4];
+      for (int cc = 0; cc < TD; ++cc) {
+        float q[TI];
+        if constexpr (TI == 2) *reinterpret_cast<float2*>(q) = *reinterpret_cast<const float2*>(&qs[cc][tq]);
+        else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { qv[i] = qs[tq + i][cc]; pv[i] = ps[tk + i][cc]; nv[i] = ns[tk + i][cc]; }
+          for (int i = 0; i < TI; i += 4) *reinterpret_cast<float4*>(q + i) = *reinterpret_cast<const float4*>(&qs[cc][tq + i]);
+        }
+        float hi[4], lo[4];
+        *reinterpret_cast<float4*>(hi) = *reinterpret_cast<const float4*>(&his[cc][tk]);
+        *reinterpret_cast<float4*>(lo) = *reinterpret_cast<const float4*>(&los[cc][tk]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < TI; ++i) {
+          const bool neg = q[i] < 0.f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += fmaxf(qv[i] * pv[j], qv[i] * nv[j]);
-    }
+          for (int j = 0; j < 4; ++j) {
+            if constexpr (decltype(plain)::value) acc[i][j] = fmaf(q[i], neg ? lo[j] : hi[j], acc[i][j]);
+            else acc[i][j] += fmaxf(q[i] * hi[j], q[i] * lo[j]);
+          }
+        }
+      }
+    };
+    if (__builtin_amdgcn_readfirstlane(odd)) terms(std::false_type{}); else terms(std::true_type{});
   }
   float* Sh = S + (size_t)h * Lq * Lk;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TI; ++i) {
+    if (q0 + tq + i >= Lq) break;
+    float* row = Sh + (size_t)(q0 + tq + i) * Lk + k0 + tk;
+    if (aligned) {                                 // pages in fours, rows that start at 16 bytes
+      if (k0 + tk < Lk) *reinterpret_cast<float4*>(row) = float4{acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
+    } else {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (q0 + tq + i < Lq && k0 + tk + j < Lk) Sh[(size_t)(q0 + tq + i) * Lk + k0 + tk + j] = acc[i][j];
+      for (int j = 0; j < 4; ++j) if (k0 + tk + j < Lk) row[j] = acc[i][j];
+    }
+  }
 }
 
 // A bf16 value is negative where it is negative as a 16-bit integer: two packed integer operations per pair.
@@ -194,11 +246,22 @@ __global__ __launch_bounds__(NW * 64) void quest_mfma(int Lq, int Lk, int clamp,
 int launch_quest_scores(hipStream_t s, int dtype, int form, int clamp, int H, int Lq, int Lk, int d, const void* Q,
                         const void* Rp, const void* Rn, float* S) {
   if (form == 0) {
-    const dim3 g((Lq + 63) / 64, (Lk + 63) / 64, H);
-    if (dtype == ADACLUSTER_BF16)
-      quest_alu<bf16raw><<<g, 256, 0, s>>>(Lq, Lk, d, clamp, (const bf16raw*)Q, (const bf16raw*)Rp, (const bf16raw*)Rn, S);
-    else
-      quest_alu<float><<<g, 256, 0, s>>>(Lq, Lk, d, clamp, (const float*)Q, (const float*)Rp, (const float*)Rn, S);
+    const int aligned = Lk % 4 == 0 && ((uintptr_t)S & 15) == 0, whole = (((uintptr_t)Q | (uintptr_t)Rp | (uintptr_t)Rn) & 15) == 0;
+    auto go = [&](auto ti, auto type) {
+      constexpr int TI = decltype(ti)::value;
+      using T = decltype(type);
+      quest_alu<T, TI><<<dim3((Lq + 16 * TI - 1) / (16 * TI), (Lk + 63) / 64, H), 256, 0, s>>>(Lq, Lk, d, clamp, aligned, whole, (const T*)Q, (const T*)Rp, (const T*)Rn, S);
+    };
+    auto rows = [&](auto type) {
+      const long long tiles = (long long)((Lk + 63) / 64) * H;
+      // Eight rows a thread while that leaves eight workgroups a CU (6 x 25 053 x 177, d=128 224 us, four 235; 13 x 8 192 x 111, d=64,
+      // 1 664 workgroups, 65.6 and 62.7), two where four leave less than two a CU: a workgroup's own chain is the launch then (1 x 4 213 x
+      // 207, d=128 21.1 us, four 31.1, eight 42.7).
+      if (tiles * ((Lq + 127) / 128) >= 2048) go(std::integral_constant<int, 8>{}, type);
+      else if (tiles * ((Lq + 63) / 64) >= 512) go(std::integral_constant<int, 4>{}, type);
+      else go(std::integral_constant<int, 2>{}, type);
+    };
+    if (dtype == ADACLUSTER_BF16) rows(bf16raw{}); else rows(float{});
   } else {
     if (dtype != ADACLUSTER_BF16) return ADACLUSTER_E_UNSUPPORTED;
     // One page tile a wave and no more waves than the pages fill, up to 16: with four waves for 60 pages 1 x 180 000 rows

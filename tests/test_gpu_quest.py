@@ -98,3 +98,35 @@ def test_the_two_forms_agree_and_bound_every_member():
     assert np.allclose(a, b, rtol=0, atol=2e-4)
     inner = (Q[0].astype(np.float64) @ C[0].astype(np.float64).T)       # the centre lies inside its box
     assert np.all(b[0] >= inner - 1e-4)
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+@pytest.mark.parametrize("H,Lq,Lk,d,shift", [(8, 32801, 65, 64, 0), (2, 131073, 64, 128, 0),      # eight rows a thread
+                                             (4, 8201, 66, 128, 1), (3, 12000, 68, 64, 0),        # four
+                                             (1, 33, 3, 64, 2), (2, 31, 64, 128, 0), (1, 1, 129, 64, 3)])      # two
+def test_vector_form_at_the_edges_of_its_tiles(H, Lq, Lk, d, shift, bf16):
+    """Rows and pages around the tiles, any alignment of S; minima above maxima, infinities and NaN are what Eq. 1 makes of them term by
+    term (a NaN beside a number is ignored).  Same bound as above for finite scores; nothing else is written."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(Lq)
+    Q, hi, lo = (torch.randn(s, generator=gen, device="cuda") for s in ((H, Lq, d), (H, Lk, d), (H, Lk, d)))     # (boxes that are none, too)
+    hi[0, Lk // 2, d - 1], lo[0, 0, d // 2], Q[0, Lq // 3, 5] = float("inf"), float("nan"), 0.0
+    hi[0, 0, 3], Q[H - 1, Lq - 1, 1] = float("-inf"), float("inf")
+    Q[0, 0, d - 1] = 0.0
+    if bf16:
+        Q, hi, lo = (t.to(torch.bfloat16) for t in (Q, hi, lo))
+    if shift:                                                    # inputs that start anywhere
+        Q, hi, lo = (torch.cat([t.new_zeros(shift), t.flatten()])[shift:].view(t.shape) for t in (Q, hi, lo))
+    buf = torch.full((H * Lq * Lk + 8,), 7.5, device="cuda")
+    S = buf[4 + shift:][:H * Lq * Lk].view(H, Lq, Lk)
+    B.adacluster_quest_scores(Q, hi, lo, B.QUEST_ALU, out=S)
+    assert (buf[:4 + shift] == 7.5).all() and (buf[4 + shift + H * Lq * Lk:] == 7.5).all()
+    rows = torch.unique(torch.cat([torch.arange(min(Lq, 130)), torch.arange(max(0, Lq - 130), Lq), torch.tensor([Lq // 3])])).cuda()
+    for h in range(H):
+        q, p, n = Q[h, rows].double()[:, None], hi[h].double()[None], lo[h].double()[None]
+        ref = torch.fmax(q * p, q * n).sum(2)
+        mag = torch.fmax((q * p).abs(), (q * n).abs()).sum(2)
+        got = S[h, rows].double()
+        fin = torch.isfinite(ref)
+        assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(got[~fin & ~torch.isnan(ref)], ref[~fin & ~torch.isnan(ref)])
+        assert ((got - ref).abs()[fin] <= 1e-5 * mag[fin] + 1e-6).all()
