@@ -9,7 +9,8 @@ from __future__ import annotations
 
 import ctypes
 import os
-from dataclasses import dataclass, asdict
+import operator
+from dataclasses import dataclass
 
 import torch
 
@@ -75,13 +76,14 @@ class Params:
     q_no_norm: int = 0
 
     def c(self) -> CParams:
-        return CParams(**asdict(self))
+        return CParams(*_param_values(self))      # (dataclasses.asdict copies every value on its way: 10 us)
 
     @property
     def cap(self) -> int:
         return self.k_max_clusters + self.k_m0
 
 
+_param_values = operator.attrgetter(*(name for name, _ in CParams._fields_))
 _lib = None
 
 
@@ -152,11 +154,11 @@ def _check(rc, what):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()      # (the argument types make it a pointer)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _tdtype(p: Params):
@@ -165,7 +167,7 @@ def _tdtype(p: Params):
 
 def _check_qkv(p: Params, *ts):
     for t in ts:
-        if not (t.is_cuda and t.is_contiguous() and t.dtype == _tdtype(p) and tuple(t.shape) == (p.H, p.N, p.d)):
+        if not (t.is_cuda and t.is_contiguous() and t.dtype == _tdtype(p) and t.shape == (p.H, p.N, p.d)):
             raise ValueError("tensor must be a contiguous CUDA tensor [H,N,d] of the params dtype")
 
 
@@ -361,7 +363,7 @@ def adacluster_attn(p: Params, Q, K, V, outs=None, out=None, ws=None):
     O = torch.empty_like(Q) if out is None else out
     co = None
     if outs is not None:
-        co = COutputs(**{n: (outs[n].data_ptr() if outs.get(n) is not None else None) for n in COutputs._names})
+        co = COutputs(*[_ptr(outs.get(n)) for n in COutputs._names])
     cp = p.c()
     _check(load_library().adacluster_attn(
         ctypes.byref(cp), _ptr(Q), _ptr(K), _ptr(V), _ptr(O), ctypes.byref(co) if co is not None else None,
