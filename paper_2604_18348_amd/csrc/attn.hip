@@ -48,12 +48,22 @@ __device__ __forceinline__ int wave_prefix(int v, int lane) {
 // chunks}; a head has `slots` partial slots, and lists stay whole once they are used up.
 constexpr int PLAN_BESIDE = 256;       // query clusters up to which the LDS it takes (8 KB each) leaves the lists' workgroups their places
 __host__ __device__ constexpr int plan_ints(int Cq, bool deal) { return (deal ? 11 : 9) * Cq + 1; }      // of LDS
+// Pieces for `rest` tiles of an XCD, for every number of them: two bits each (pieces - 1), 32 a word.  By the host, as the
+// kernel's registers and first microseconds are dear (3 x 5 007 rows, d=128, a call 288 us, 290 with the rule in the kernel).
+struct Pieces { uint64_t of[3]; };
+__device__ __forceinline__ int pieces_of(const Pieces& p, int rest) {
+  const uint64_t w = rest < 32 ? p.of[0] : rest < 64 ? p.of[1] : p.of[2];
+  return 1 + (int)(w >> (2 * (rest & 31)) & 3);
+}
+
 // Tiles dealt to the XCDs by work (attn_deal_segs says when).  Workgroups go to the 8 XCDs in turn, and one is done when the last is.
 // The query clusters of a head are ordered by the length of their key lists, the longest first, and their tiles cut into `segs`
 // segments of equal work, each in eight parts of equal work, one for every XCD (the tiles of a cluster stay side by side); segment e's
 // parts are dealt from XCD e % 8 on, so that what rounding leaves evens out.  The last head to be planned writes every XCD's list: its
 // parts of all segments, the longest lists first, whatever head they are of, so that what ends last is short.  The tiles past the
-// last whole round of 32 CUs, where lists may be cut, go in pieces of their key list, so that no CU runs a whole one alone at the end.
+// last whole round of 32 CUs, where lists may be cut, go in pieces of their key list, so that no CU runs a whole one alone at the end;
+// fp32 lists as in pick_tile, or, where all are one round, each in pieces of about a sixth of a CU's work (whole 2 x 5 681 top-p, d=128 took
+// 216 us, dealt by number 181, so 155; pieces in launches of more rounds cost more than they even out: 3 x 5 007 177 -> 203).
 constexpr int DEAL_ENTRIES = 64;                     // segments at most
 // A head's record: the longest list (key tiles) of every segment, the first tile of every part of the segments and the end
 __host__ __device__ constexpr int deal_rec(int segs) { return segs + 8 * segs + 1; }
@@ -62,11 +72,11 @@ constexpr int DEAL_HEAD = 4 + 32;                    // an XCD's list: entries, 
 constexpr int TAIL_MOST = 8, TAIL_SLOTS = 64;        // pieces of a list, partial slots of an XCD
 __host__ __device__ constexpr int deal_cap(int tiles) { return tiles * 9 / 64 + 2; }       // most tiles of a part, of `tiles` in eight parts
 __host__ __device__ constexpr int deal_list(int H, int segs, int most) { return H * (most * 9 / 64 + 2 * segs) + TAIL_SLOTS; }      // most entries of an XCD
-struct DealtTile { int h, tile, z; };                // head, tile, piece
-__device__ __forceinline__ int dealt(int h, int tile, int z) { return h << 23 | tile << 3 | z; }
-__device__ __forceinline__ DealtTile dealt_tile(uint32_t e) { return {(int)(e >> 23), (int)(e >> 3 & 0xFFFFF), (int)(e & 7)}; }
+struct DealtTile { int h, tile, z, sp; };            // head, tile, piece and (fp32) of how many
+__device__ __forceinline__ int dealt(int h, int tile, int z, int sp = 1) { return h << 23 | tile << 6 | z << 3 | (sp - 1); }
+__device__ __forceinline__ DealtTile dealt_tile(uint32_t e) { return {(int)(e >> 23), (int)(e >> 6 & 0x1FFFF), (int)(e >> 3 & 7), (int)(e & 7) + 1}; }      // (tile: 17 bits)
 __device__ __forceinline__ int tail_pieces(int sp, int tiles) { return min(sp, max(1, tiles / 8)); }      // no piece of less than eight key tiles
-struct Deal { int32_t* parts /* [H][deal_rec(segs)] */; int32_t* lists /* [8][DEAL_HEAD + cap] */; int32_t* planned /* heads; 0 before the launch */; int cap, segs, H, cut_below /* tiles of an XCD */; };
+struct Deal { int32_t* parts /* [H][deal_rec(segs)] */; int32_t* lists /* [8][DEAL_HEAD + cap] */; int32_t* planned /* heads; 0 before the launch */; int cap, segs, H, cut_below /* tiles of an XCD */; int f32_round /* fp32: workgroups of an XCD at a time, where lists may be cut */; Pieces pieces; };
 
 // By the workgroup of the last head to be planned.
 __device__ __forceinline__ void deal_lists(const Deal& dl) {
@@ -97,20 +107,40 @@ __device__ __forceinline__ void deal_lists(const Deal& dl) {
   const int32_t* const p = s_part + h * rec + segs + (e - h * segs) * 8;
   for (int xcd = wave; xcd < 8; xcd += 4) {          // a wave an XCD
     const int y = (xcd + e) & 7, first = p[y], n = lane < E ? p[y + 1] - first : 0;
-    const int incl = wave_prefix(n, lane), total = __builtin_amdgcn_readlane(incl, 63), rest = total < dl.cut_below ? total & 31 : 0, whole = total - rest;
-    int best = 1 << 30, sp = 1;                      // rounds of pieces, in 1/840 of a whole list, and a sixteenth of one for each
-#pragma unroll
-    for (int q = 1; q <= TAIL_MOST; ++q) {
-      const int cost = (q * rest + 31) / 32 * (840 / q) + 52 * q;
-      if (rest && q * rest <= TAIL_SLOTS && cost < best) { best = cost; sp = q; }
+    const int tiles = __builtin_amdgcn_readlane(wave_prefix(n, lane), 63);
+    int cut = 1;                                     // pieces of this segment's lists
+    if (dl.f32_round && tiles <= dl.f32_round) {     // fp32, one round of workgroups: pieces of about a sixth of a CU's work
+      const int T = lane < E ? p[-segs - 7 * (e - h * segs)] : 0;      // (the segment's longest list: the record starts with those)
+      const int chunk = max(4, __builtin_amdgcn_readlane(wave_prefix(n * T, lane), 63) / (32 * 6));
+      cut = min(F32_MAX_SPLITS, max(1, (T + chunk - 1) / chunk));
     }
+    const int mine = n * cut, incl = wave_prefix(mine, lane), total = __builtin_amdgcn_readlane(incl, 63);
+    int rest = 0, sp = 1;
+    if (dl.f32_round) {                              // more: those past the last whole round in pieces, as in pick_tile
+      if (tiles > dl.f32_round) rest = (uint32_t)total % (uint32_t)dl.f32_round;
+      if (rest) sp = pieces_of(dl.pieces, rest);
+    } else if (total < dl.cut_below) {
+      rest = total & 31;
+      int best = 1 << 30;                            // rounds of pieces, in 1/840 of a whole list, and a sixteenth of one for each
+#pragma unroll
+      for (int q = 1; q <= TAIL_MOST; ++q) {
+        const int cost = (q * rest + 31) / 32 * (840 / q) + 52 * q;
+        if (rest && q * rest <= TAIL_SLOTS && cost < best) { best = cost; sp = q; }
+      }
+    }
+    const int whole = total - rest;
     int32_t* const list = dl.lists + (size_t)xcd * (DEAL_HEAD + dl.cap);
     if (lane == 0) *reinterpret_cast<int4*>(list) = int4{whole + rest * sp, whole, rest, sp};
+    if (cut > 1) {
+      for (int i = 0; i < n; ++i)
+        for (int z = 0; z < cut; ++z) list[DEAL_HEAD + incl - mine + z * n + i] = dealt(h, first + i, z, cut);
+      continue;
+    }
     for (int i = 0; i < n; ++i) {
       const int s = incl - n + i;
       if (s < whole) { list[DEAL_HEAD + s] = dealt(h, first + i, 0); continue; }
-      list[4 + s - whole] = dealt(h, first + i, 0);
-      for (int z = 0; z < sp; ++z) list[DEAL_HEAD + s + z * rest] = dealt(h, first + i, z);
+      if (!dl.f32_round) list[4 + s - whole] = dealt(h, first + i, 0);
+      for (int z = 0; z < sp; ++z) list[DEAL_HEAD + s + z * rest] = dealt(h, first + i, z, sp);
     }
   }
 }
@@ -521,14 +551,6 @@ int launch_attn_stats(hipStream_t s, int H, int Cq, int maxr, int maxtiles, cons
                       const int32_t* ntiles, const int32_t* rng_pre, const int32_t* rng_cnt, adacluster_head_stats* out) {
   attn_stats<<<H, 256, 0, s>>>(Cq, maxr, maxtiles, st, tiles, ntiles, rng_pre, rng_cnt, out);
   return hipGetLastError() == hipSuccess ? 0 : ADACLUSTER_E_INTERNAL;
-}
-
-// Pieces for `rest` tiles of an XCD, for every number of them: two bits each (pieces - 1), 32 a word.  By the host, as the
-// kernel's registers and first microseconds are dear (3 x 5 007 rows, d=128, a call 288 us, 290 with the rule in the kernel).
-struct Pieces { uint64_t of[3]; };
-__device__ __forceinline__ int pieces_of(const Pieces& p, int rest) {
-  const uint64_t w = rest < 32 ? p.of[0] : rest < 64 ? p.of[1] : p.of[2];
-  return 1 + (int)(w >> (2 * (rest & 31)) & 3);
 }
 
 struct AttnArgs {
@@ -1076,7 +1098,14 @@ template <int D, bool LISTED>
 __global__ __launch_bounds__(F32_WAVES * 64, D == 64 ? 3 : 2) void attn_f32(AttnArgs a) {
   constexpr int BN = 32, DB = D / 32, NW = F32_WAVES, SROW = D + 4, PPR = D / 4, RPI = 64 / PPR;   // 16-byte pieces a row, rows a load
   int h, tile, z, sp;
-  if (!pick_tile(a.ntiles, a.H, a.pieces, a.splits, f32_resident(D), h, tile, z, sp)) return;
+  if (a.deal) {
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int32_t* list = a.deal + (size_t)xcd * a.deal_stride;
+    const int e = list[DEAL_HEAD + slot];
+    if (slot >= list[0]) return;
+    const DealtTile dt = dealt_tile(e);
+    h = dt.h; tile = dt.tile; z = dt.z; sp = dt.sp;
+  } else if (!pick_tile(a.ntiles, a.H, a.pieces, a.splits, f32_resident(D), h, tile, z, sp)) return;
   const int32_t* tl = a.tiles + ((size_t)h * a.maxtiles + tile) * TILE_REC;          // (key lists are never cut for fp32)
   const int qc = tl[0], row0 = tl[1], nrows = tl[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1520,20 +1549,25 @@ static int attn_resident(int d, int BM) { return 256 * (BM == 128 ? 2 : 1) * (d 
 // call, 19 x 3 864, d=64, 144 -> 148; but 29 x 4 140 490 -> 476, 17 x 3 405, d=128, 333 -> 273) are not worth it, and from
 // sixteen rounds on the ends of the lists are less than that.  Heads of equal lists are what neither side gains by: 30 x 17 776 773 and 775 us.
 constexpr double DEAL_MIN = 75;      // key tiles (of a list of all keys) a place
+// fp32: key tiles (of a list of all keys) a CU, by width.  Lists of uneven length are what is to be gained (one head's lists more than
+// another's, top-p): attention of 3 x 10 876, top-p, d=64 383 -> 272 us, 3 x 9 600, top-p, d=128 510 -> 431, 3 x 9 200, d=128, 25 clusters
+// 424 -> 391, 3 x 5 007, d=128 185 -> 177; below the line the plan takes what it gives (2 x 5 928, d=128 77 -> 75 and 6 for the plan).
+constexpr double F32_DEAL_MIN_64 = 200, F32_DEAL_MIN_128 = 165;
 constexpr int DEAL_CUT = 2;          // rounds from which the last tiles stay whole: their partial results and the merge take 6-12 us (30 x 17 776)
 int attn_deal_segs(int dtype, int d, int H, int N, int Cq) {
-  if (dtype != ADACLUSTER_BF16 || Cq < 2 || Cq > PLAN_BESIDE || H > DEAL_ENTRIES) return 0;
+  if (Cq < 2 || Cq > PLAN_BESIDE || H > DEAL_ENTRIES) return 0;
   const int BM = attn_block_rows(dtype, d, N, Cq), tiles = N / BM + Cq / 2 + 1, T = (N + 63) / 64;
+  if (dtype == ADACLUSTER_F32) {
+    if (tiles > 65536 || (double)H * tiles * T < 256 * (d == 64 ? F32_DEAL_MIN_64 : F32_DEAL_MIN_128) || 4.0 * H * (N / BM + Cq + 1) * (T + 64.0) >= 2147483648.0) return 0;
+    return max(1, min(min(8, DEAL_ENTRIES / H), tiles / 16));
+  }
   const double n = (double)H * tiles, r = attn_resident(d, BM);
   if (n < 256 || n >= 16 * r || n * T < DEAL_MIN * r || 9.0 * H * (N / BM + Cq + 1) * (T + 64.0) >= 2147483648.0) return 0;
   return max(1, min(min(8, DEAL_ENTRIES / H), tiles / 16));
 }
-size_t attn_deal_ints(int H, int segs, int most) { return segs ? DEAL_PARTS + 8 * (size_t)(DEAL_HEAD + deal_list(H, segs, most) + 3) : 0; }
-static Deal deal_of(int d, int BM, int H, int N, int segs, int most, int32_t* deal, int32_t* planned) {
-  if (!segs) return {};
-  return {deal, deal + DEAL_PARTS, planned, (deal_list(H, segs, most) + 3) / 4 * 4, segs, H, lists_may_be_cut(N) ? DEAL_CUT * attn_resident(d, BM) / 8 : 0};
-}
-int attn_tail_slots(int dtype, int d, int H, int N, int Cq) { return attn_deal_segs(dtype, d, H, N, Cq) && lists_may_be_cut(N) ? 8 * TAIL_SLOTS : 0; }
+static int deal_entries(int dtype, int H, int segs, int most) { return ((dtype == ADACLUSTER_F32 ? F32_MAX_SPLITS : 1) * deal_list(H, segs, most) + (dtype == ADACLUSTER_F32 ? (F32_MAX_SPLITS - 1) * 96 : 0) + 3) / 4 * 4; }
+size_t attn_deal_ints(int dtype, int H, int segs, int most) { return segs ? DEAL_PARTS + 8 * (size_t)(DEAL_HEAD + deal_entries(dtype, H, segs, most)) : 0; }
+int attn_tail_slots(int dtype, int d, int H, int N, int Cq) { return dtype == ADACLUSTER_BF16 && attn_deal_segs(dtype, d, H, N, Cq) && lists_may_be_cut(N) ? 8 * TAIL_SLOTS : 0; }
 
 // Most pieces a key list of the fp32 kernel may go in (see pick_tile).  From some 1 024 tiles on there are two rounds of whole
 // ones (d=128), and the partial results of every row and the launch that combines them cost what the last round leaves idle
@@ -1583,6 +1617,12 @@ static Pieces f32_pieces(int N) {
   return p;
 }
 
+static Deal deal_of(int dtype, int d, int BM, int H, int N, int Cq, int segs, int most, int32_t* deal, int32_t* planned) {
+  if (!segs) return {};
+  const bool f32 = dtype == ADACLUSTER_F32;
+  return {deal, deal + DEAL_PARTS, planned, deal_entries(dtype, H, segs, most), segs, H, !f32 && lists_may_be_cut(N) ? DEAL_CUT * attn_resident(d, BM) / 8 : 0,
+          f32 && attn_f32_splits(H, N, Cq) > 1 ? f32_resident(d) : 0, f32 ? (d == 64 ? f32_pieces<64>(N) : f32_pieces<128>(N)) : Pieces{}};
+}
 bool plan_reads_lengths(int Cq) { return Cq <= PLAN_BESIDE; }
 int launch_plan_sparse(hipStream_t s, int dtype, int d, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
                        const int32_t* q_offs, int q_offs_stride, const int32_t* k_offs, int k_offs_stride,
@@ -1591,7 +1631,7 @@ int launch_plan_sparse(hipStream_t s, int dtype, int d, int H, int Cq, int cap, 
                        int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride,
                        const int32_t* perm_k, int N, const int32_t* lengths, int segs, int most, int32_t* deal, int32_t* planned) {
   const int split = dtype == ADACLUSTER_BF16 ? 1 : 0;
-  const TilePlan tp{lengths, q_offs, q_offs_stride, maxtiles, BM, SPLIT_SLOTS, split, tiles, ntiles, merge, nmerge, deal_of(d, BM, H, N, segs, most, deal, planned)};
+  const TilePlan tp{lengths, q_offs, q_offs_stride, maxtiles, BM, SPLIT_SLOTS, split, tiles, ntiles, merge, nmerge, deal_of(dtype, d, BM, H, N, Cq, segs, most, deal, planned)};
   if (lengths && plan_reads_lengths(Cq)) {
     const auto plan = segs ? plan_sparse<true, true> : plan_sparse<true, false>;
     plan<<<dim3(H, Cq + 1), 256, plan_ints(Cq, segs != 0) * 4, s>>>(
@@ -1623,7 +1663,7 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
              (Cq == 1 || (size_t)4 * N * d <= ((size_t)8 << 20)) ? 1 : 0,
              part_o, part_ml, SPLIT_SLOTS, BM, krow, kstride,
              rng_start, rng_pre, rng_cnt, maxr, perm_k, dtype == ADACLUSTER_F32 ? attn_f32_splits(H, N, Cq) : 1, {}, nullptr, 0};
-  const Deal dl = deal_of(d, BM, H, N, segs, most, deal, nullptr);
+  const Deal dl = deal_of(dtype, d, BM, H, N, Cq, segs, most, deal, nullptr);
   if (segs) { a.deal = dl.lists; a.deal_stride = DEAL_HEAD + dl.cap; }
   if (a.splits > 1) a.pieces = d == 64 ? f32_pieces<64>(N) : f32_pieces<128>(N);
   const bool cut = Cq == 1 || lists_may_be_cut(N);
@@ -1643,7 +1683,7 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
     }
   } else {
     const int splits = a.splits;
-    const dim3 g2 = pick_tile_grid(H, min(N, N / 32 + Cq + 1), splits, f32_resident(d)), gm((N + 1024 / d - 1) / (1024 / d), H);
+    const dim3 g2 = segs ? g : pick_tile_grid(H, min(N, N / 32 + Cq + 1), splits, f32_resident(d)), gm((N + 1024 / d - 1) / (1024 / d), H);
     if (d == 64) { if (krow) attn_f32<64, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<64, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
     else { if (krow) attn_f32<128, true><<<g2, F32_WAVES * 64, 0, s>>>(a); else attn_f32<128, false><<<g2, F32_WAVES * 64, 0, s>>>(a); }
     if (splits > 1) {

@@ -169,7 +169,7 @@ int launch_plan_sparse(hipStream_t s, int dtype, int d, int H, int Cq, int cap, 
 // Tiles of a sparse launch dealt to the XCDs by work: segments a head (0: dealt by their number), the integers of its table, and the
 // partial slots of the whole launch for the pieces of the last tiles (behind the attn_split_slots() of every head).
 int attn_deal_segs(int dtype, int d, int H, int N, int Cq);
-size_t attn_deal_ints(int H, int segs, int most);
+size_t attn_deal_ints(int dtype, int H, int segs, int most);
 int attn_tail_slots(int dtype, int d, int H, int N, int Cq);
 struct DenseShape { int BM, pieces; };       // queries a workgroup, chunks of the key list
 DenseShape attn_dense_shape(int dtype, int d, int H, int N);

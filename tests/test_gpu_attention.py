@@ -507,3 +507,36 @@ def test_tiles_dealt_by_work(H, N, d, Cq):
         assert rel < 1e-2 and mx < 2e-2, (h, rel, mx)
         worst = max(worst, rel)
     print("dealt", H, N, d, Cq, worst)
+
+
+@pytest.mark.parametrize("H,N,d,Cq", [(2, 6400, 128, 65),       # one round of workgroups: every list in pieces
+                                      (3, 9001, 64, 41),        # more: the last tiles
+                                      (4, 9100, 128, 200),      # 1 024 tiles and more: whole lists
+                                      (64, 1200, 64, 100)])
+def test_fp32_tiles_dealt_by_work(H, N, d, Cq):
+    """As test_tiles_dealt_by_work, for fp32: heads and clusters of very different lists, every row against float64 on the device."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(H * N)
+    Ck = 40
+    Q, K, V = (torch.randn((H, N, d), generator=gen, device="cuda") for _ in range(3))
+    rng = np.random.default_rng(N)
+    ql = np.minimum((Cq * rng.random((H, N)) ** 2).astype(np.int32), Cq - 1)
+    kl = rng.integers(0, Ck, (H, N)).astype(np.int32)
+    sel = [[np.sort(rng.choice(Ck, size=Ck if i == Cq // 2 else int(rng.integers(0, max(2, Ck * (h + 1) // H))), replace=False)) for i in range(Cq)]
+           for h in range(H)]
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=Cq, k_m0=4, k_m_min=1, k_max_clusters=Ck)
+    si, sc = sel_to_dev(sel, Cq, p.cap)
+    qt, kt = torch.from_numpy(ql).cuda(), torch.from_numpy(kl).cuda()
+    kc = torch.full((H,), Ck, dtype=torch.int32, device="cuda")
+    ws = B.workspace(p)
+    O = B.adacluster_sparse_attn(p, Q, K, V, qt, kt, kc, si, sc, out=torch.full_like(Q, float("nan")), ws=ws)
+    assert torch.equal(O, B.adacluster_sparse_attn(p, Q, K, V, qt, kt, kc, si, sc, ws=ws))
+    for h in range(0, H, max(1, H // 8)):
+        ref = torch.zeros((N, d), dtype=torch.float64, device="cuda")
+        for i in range(Cq):
+            rows = torch.nonzero(qt[h] == i)[:, 0]
+            keys = torch.nonzero(torch.isin(kt[h], torch.from_numpy(sel[h][i].astype(np.int32)).cuda()))[:, 0]
+            if len(keys):
+                P = torch.softmax(Q[h, rows].double() @ K[h, keys].double().T.contiguous() / d ** 0.5, 1)
+                ref[rows] = P @ V[h, keys].double()
+        assert float((O[h].double() - ref).abs().max()) < 1e-4, h
