@@ -1551,7 +1551,9 @@ static int attn_resident(int d, int BM) { return 256 * (BM == 128 ? 2 : 1) * (d 
 constexpr double DEAL_MIN = 75;      // key tiles (of a list of all keys) a place
 // fp32: key tiles (of a list of all keys) a CU, by width.  Lists of uneven length are what is to be gained (one head's lists more than
 // another's, top-p): attention of 3 x 10 876, top-p, d=64 383 -> 272 us, 3 x 9 600, top-p, d=128 510 -> 431, 3 x 9 200, d=128, 25 clusters
-// 424 -> 391, 3 x 5 007, d=128 185 -> 177; below the line the plan takes what it gives (2 x 5 928, d=128 77 -> 75 and 6 for the plan).
+// 424 -> 391; below the line the plan takes what it gives (2 x 5 928, d=128 77 -> 75 and 6 for the plan).  So it does at d=128 between
+// one and 1.9 rounds of tiles, where the tiles dealt by number have the same pieces past the whole round: the call 3 x 7 920 392 -> 403,
+// 3 x 8 554 336 -> 337, 2 x 8 160 417 -> 420, 3 x 5 007 298 -> 301 (of 3 x 5 643 390 -> 381); on either side 2 x 6 437 300 -> 283, 3 x 9 710 811 -> 773.
 constexpr double F32_DEAL_MIN_64 = 200, F32_DEAL_MIN_128 = 165;
 constexpr int DEAL_CUT = 2;          // rounds from which the last tiles stay whole: their partial results and the merge take 6-12 us (30 x 17 776)
 int attn_deal_segs(int dtype, int d, int H, int N, int Cq) {
@@ -1559,6 +1561,8 @@ int attn_deal_segs(int dtype, int d, int H, int N, int Cq) {
   const int BM = attn_block_rows(dtype, d, N, Cq), tiles = N / BM + Cq / 2 + 1, T = (N + 63) / 64;
   if (dtype == ADACLUSTER_F32) {
     if (tiles > 65536 || (double)H * tiles * T < 256 * (d == 64 ? F32_DEAL_MIN_64 : F32_DEAL_MIN_128) || 4.0 * H * (N / BM + Cq + 1) * (T + 64.0) >= 2147483648.0) return 0;
+    const double rounds = (double)H * tiles / (8 * f32_resident(d));
+    if (d == 128 && rounds > 1 && rounds < 1.9) return 0;
     return max(1, min(min(8, DEAL_ENTRIES / H), tiles / 16));
   }
   const double n = (double)H * tiles, r = attn_resident(d, BM);
