@@ -292,7 +292,7 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   {  // partial results of split key lists: slots of cut lists (bf16), or a row per query and split (fp32; the dense call
      // counts as one cluster, which never makes fewer splits)
     const size_t splits = attn_f32_splits(D.H, D.N, 1);     // (1: the kernel writes the output itself)
-    const size_t rows = p->dtype == ADACLUSTER_BF16 ? H * (size_t)attn_split_slots() * D.BMmax + (size_t)attn_tail_slots(p->dtype, D.d, D.H, D.N, D.Cq) * D.BM : splits > 1 ? H * N * splits : 0;
+    const size_t rows = p->dtype == ADACLUSTER_BF16 ? H * (size_t)attn_split_slots() * D.BMmax : splits > 1 ? H * N * splits : 0;
     TAKE(part_o, float*, rows * d * 4);
     TAKE(part_ml, float*, rows * 2 * 4);
   }

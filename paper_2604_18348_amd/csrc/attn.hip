@@ -60,23 +60,22 @@ __device__ __forceinline__ int pieces_of(const Pieces& p, int rest) {
 // The query clusters of a head are ordered by the length of their key lists, the longest first, and their tiles cut into `segs`
 // segments of equal work, each in eight parts of equal work, one for every XCD (the tiles of a cluster stay side by side); segment e's
 // parts are dealt from XCD e % 8 on, so that what rounding leaves evens out.  The last head to be planned writes every XCD's list: its
-// parts of all segments, the longest lists first, whatever head they are of, so that what ends last is short.  The tiles past the
-// last whole round of 32 CUs, where lists may be cut, go in pieces of their key list, so that no CU runs a whole one alone at the end;
-// fp32 lists as in pick_tile, or, where all are one round, each in pieces of about a sixth of a CU's work (whole 2 x 5 681 top-p, d=128 took
+// parts of all segments, the longest lists first, whatever head they are of, so that what ends last is short.  A bf16 tile is run as
+// its record says, so that a head's bits do not depend on the other heads (in launches of less than two rounds the tiles past the last
+// whole one went in pieces: calls of 8 x 6 000, d=128 222 -> 241 us, 7 x 8 000, d=128 220 -> 237, and 5 x 9 247 505 -> 481).
+// Fp32 lists go in pieces as in pick_tile, or, where all are one round, each in pieces of about a sixth of a CU's work (whole 2 x 5 681 top-p, d=128 took
 // 216 us, dealt by number 181, so 155; pieces in launches of more rounds cost more than they even out: 3 x 5 007 177 -> 203).
 constexpr int DEAL_ENTRIES = 64;                     // segments at most
 // A head's record: the longest list (key tiles) of every segment, the first tile of every part of the segments and the end
 __host__ __device__ constexpr int deal_rec(int segs) { return segs + 8 * segs + 1; }
 constexpr int DEAL_PARTS = 10 * DEAL_ENTRIES;        // of all heads: H * segs <= DEAL_ENTRIES
-constexpr int DEAL_HEAD = 4 + 32;                    // an XCD's list: entries, those that are whole tiles, tiles in pieces, pieces of each; those tiles; the entries
-constexpr int TAIL_MOST = 8, TAIL_SLOTS = 64;        // pieces of a list, partial slots of an XCD
+constexpr int DEAL_HEAD = 4;                         // an XCD's list: their number (and padding), the entries
 __host__ __device__ constexpr int deal_cap(int tiles) { return tiles * 9 / 64 + 2; }       // most tiles of a part, of `tiles` in eight parts
-__host__ __device__ constexpr int deal_list(int H, int segs, int most) { return H * (most * 9 / 64 + 2 * segs) + TAIL_SLOTS; }      // most entries of an XCD
+__host__ __device__ constexpr int deal_list(int H, int segs, int most) { return H * (most * 9 / 64 + 2 * segs); }      // most entries of an XCD
 struct DealtTile { int h, tile, z, sp; };            // head, tile, piece and (fp32) of how many
 __device__ __forceinline__ int dealt(int h, int tile, int z, int sp = 1) { return h << 23 | tile << 6 | z << 3 | (sp - 1); }
 __device__ __forceinline__ DealtTile dealt_tile(uint32_t e) { return {(int)(e >> 23), (int)(e >> 6 & 0x1FFFF), (int)(e >> 3 & 7), (int)(e & 7) + 1}; }      // (tile: 17 bits)
-__device__ __forceinline__ int tail_pieces(int sp, int tiles) { return min(sp, max(1, tiles / 8)); }      // no piece of less than eight key tiles
-struct Deal { int32_t* parts /* [H][deal_rec(segs)] */; int32_t* lists /* [8][DEAL_HEAD + cap] */; int32_t* planned /* heads; 0 before the launch */; int cap, segs, H, cut_below /* tiles of an XCD */; int f32_round /* fp32: workgroups of an XCD at a time, where lists may be cut */; Pieces pieces; };
+struct Deal { int32_t* parts /* [H][deal_rec(segs)] */; int32_t* lists /* [8][DEAL_HEAD + cap] */; int32_t* planned /* heads; 0 before the launch */; int cap, segs, H; int f32_round /* fp32: workgroups of an XCD at a time, where lists may be cut */; Pieces pieces; };
 
 // By the workgroup of the last head to be planned.
 __device__ __forceinline__ void deal_lists(const Deal& dl) {
@@ -119,18 +118,10 @@ __device__ __forceinline__ void deal_lists(const Deal& dl) {
     if (dl.f32_round) {                              // more: those past the last whole round in pieces, as in pick_tile
       if (tiles > dl.f32_round) rest = (uint32_t)total % (uint32_t)dl.f32_round;
       if (rest) sp = pieces_of(dl.pieces, rest);
-    } else if (total < dl.cut_below) {
-      rest = total & 31;
-      int best = 1 << 30;                            // rounds of pieces, in 1/840 of a whole list, and a sixteenth of one for each
-#pragma unroll
-      for (int q = 1; q <= TAIL_MOST; ++q) {
-        const int cost = (q * rest + 31) / 32 * (840 / q) + 52 * q;
-        if (rest && q * rest <= TAIL_SLOTS && cost < best) { best = cost; sp = q; }
-      }
     }
     const int whole = total - rest;
     int32_t* const list = dl.lists + (size_t)xcd * (DEAL_HEAD + dl.cap);
-    if (lane == 0) *reinterpret_cast<int4*>(list) = int4{whole + rest * sp, whole, rest, sp};
+    if (lane == 0) list[0] = whole + rest * sp;
     if (cut > 1) {
       for (int i = 0; i < n; ++i)
         for (int z = 0; z < cut; ++z) list[DEAL_HEAD + incl - mine + z * n + i] = dealt(h, first + i, z, cut);
@@ -139,7 +130,6 @@ __device__ __forceinline__ void deal_lists(const Deal& dl) {
     for (int i = 0; i < n; ++i) {
       const int s = incl - n + i;
       if (s < whole) { list[DEAL_HEAD + s] = dealt(h, first + i, 0); continue; }
-      if (!dl.f32_round) list[4 + s - whole] = dealt(h, first + i, 0);
       for (int z = 0; z < sp; ++z) list[DEAL_HEAD + s + z * rest] = dealt(h, first + i, z, sp);
     }
   }
@@ -676,15 +666,13 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
   // Workgroups go to the 8 XCDs round-robin in launch order (gridDim.x is a multiple of 8, so
   // XCD = blockIdx.x % 8), and each XCD has its own L2.
   int h, tile;
-  int z = 0, sp = 1, part = 0;           // piece of the key list, of how many, and its partial slot
   if (a.deal) {
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int32_t* list = a.deal + (size_t)xcd * a.deal_stride;
     const int e = list[DEAL_HEAD + slot];          // (asked for with the head of the list)
     if (slot >= list[0]) return;
     const DealtTile dt = dealt_tile(e);
-    h = dt.h; tile = dt.tile; z = dt.z;
-    if (slot >= list[1]) { sp = list[3]; part = xcd * TAIL_SLOTS + slot - list[1]; }
+    h = dt.h; tile = dt.tile;
   } else if (a.head_major) {
     // Heads are dealt to XCDs whole, eight at a time: all query tiles of a head then stream that
     // head's K/V rows behind one L2.  The H % 8 heads left over are split eight ways by tile.
@@ -712,16 +700,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
   }
   const int32_t* tl = a.tiles + ((size_t)h * a.maxtiles + tile) * TILE_REC;
   const int qc = tl[0], row0 = tl[1], nrows = tl[2];
-  int kt0 = tl[3], kt1 = tl[4], pslot = tl[5];          // this workgroup's share of the key list
-  if (pslot >= 0) {
-    if (z > 0) return;                                   // (a list that is cut already stays as it is)
-    pslot += h * a.slots;
-  } else if (sp > 1) {
-    const int T = kt1;
-    sp = tail_pieces(sp, T);
-    if (z >= sp) return;
-    if (sp > 1) { const int per = (T + sp - 1) / sp; kt0 = z * per; kt1 = min(T, kt0 + per); pslot = a.H * a.slots + part; }
-  }
+  const int kt0 = tl[3], kt1 = tl[4], pslot = tl[5];    // this workgroup's share of the key list
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, hb = lane >> 5;
 
@@ -1037,7 +1016,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_mfma(AttnArgs a) {
       // a chunk of a cut key list: leave the unnormalised accumulator, the reference and the
       // row sum in this chunk's slot; attn_merge combines the chunks of the query tile
       const int rr = wave * 32 + c;
-      const size_t so = (size_t)pslot * a.BM + rr;
+      const size_t so = ((size_t)h * a.slots + pslot) * a.BM + rr;
       float* po = a.part_o + so * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
@@ -1384,27 +1363,10 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a, const int32_t* __r
   // not one after the other: the kernel is a handful of dependent round trips either way, so what counts is
   // how many of its loads are in flight at once.
   constexpr int MAXP = 16;                       // most chunks a list is cut into (plan_tiles)
-  // Rows past the heads (dealt tiles): an XCD each, whose last tiles went in pieces too.
-  const bool tail = (int)blockIdx.y >= a.H;
-  const int32_t* list = tail ? a.deal + (size_t)(blockIdx.y - a.H) * a.deal_stride : nullptr;
-  int h = blockIdx.y;
-  const int n = !tail ? nmerge[h] : list[3] > 1 ? list[2] : 0;
+  const int h = blockIdx.y, n = nmerge[h];
   for (int e = blockIdx.x; e < n; e += gridDim.x) {
-    int row0, nrows, pieces;
-    size_t slot0, stride;                          // partial slots of the pieces
-    if (tail) {
-      const DealtTile dt = dealt_tile(list[4 + e]);      // (asked for with the head of the list)
-      h = dt.h;
-      const int32_t* tl = a.tiles + ((size_t)h * a.maxtiles + dt.tile) * TILE_REC;
-      pieces = tail_pieces(list[3], tl[4]);
-      if (tl[5] >= 0 || pieces == 1) continue;     // not cut here
-      row0 = tl[1]; nrows = tl[2];
-      slot0 = (size_t)a.H * a.slots + (blockIdx.y - a.H) * TAIL_SLOTS + e; stride = list[2];
-    } else {
-      const int32_t* ml = merge + ((size_t)h * a.slots + e) * 4;
-      row0 = ml[0]; nrows = ml[1]; pieces = min(ml[3], MAXP);
-      slot0 = (size_t)h * a.slots + ml[2]; stride = 1;
-    }
+    const int32_t* ml = merge + ((size_t)h * a.slots + e) * 4;
+    const int row0 = ml[0], nrows = ml[1], slot0 = ml[2], pieces = min(ml[3], MAXP);
     const int32_t* pq = a.perm_q ? a.perm_q + (size_t)h * a.N : nullptr;
     bf16raw* Oh = (bf16raw*)a.O + (size_t)h * a.N * D;
     constexpr int LPR = D / 4;                     // lanes per row, four columns each
@@ -1414,7 +1376,7 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a, const int32_t* __r
       float4 os[MAXP];
 #pragma unroll
       for (int s = 0; s < MAXP; ++s) {
-        const size_t so = (slot0 + min(s, pieces - 1) * stride) * a.BM + r;
+        const size_t so = ((size_t)h * a.slots + slot0 + min(s, pieces - 1)) * a.BM + r;
         ms[s] = a.part_ml[so * 2];
         ls[s] = a.part_ml[so * 2 + 1];
         os[s] = *reinterpret_cast<const float4*>(a.part_o + so * D + col);
@@ -1544,7 +1506,7 @@ int attn_most_tiles(int dtype, int N, int Cq, int BM, int maxtiles) {
 static int attn_resident(int d, int BM) { return 256 * (BM == 128 ? 2 : 1) * (d == 64 ? 2 : 1); }      // workgroups of the bf16 kernel
 // Segments a head where the tiles of a sparse launch are dealt by work; 0 where by their number.  Dealt by number, an XCD has what its heads
 // happen to have: 16 heads of 14 119 tokens, d=128, some without structure, attention 1 130 -> 700 us; 30 x 21 600, top-p 1 720 -> 1 250;
-// 4 x 13 200 170 -> 146; 5 x 9 247 (65 tiles on the 64 places of an XCD) 212 -> 155.  The plan takes 2-8 us more (its last head
+// calls of 8 x 6 000, d=128 233 -> 222, 4 x 13 200, d=128 403 -> 390, 16 x 6 000, d=64 232 -> 214, 5 x 9 247, d=128 528 -> 505.  The plan takes 2-8 us more (its last head
 // waits for three trips to memory), so a tile a CU (n < 256) or short lists (under 75 key tiles a place: 23 x 1 680, d=128, 176 -> 181 us a
 // call, 19 x 3 864, d=64, 144 -> 148; but 29 x 4 140 490 -> 476, 17 x 3 405, d=128, 333 -> 273) are not worth it, and from
 // sixteen rounds on the ends of the lists are less than that.  Heads of equal lists are what neither side gains by: 30 x 17 776 773 and 775 us.
@@ -1555,7 +1517,6 @@ constexpr double DEAL_MIN = 75;      // key tiles (of a list of all keys) a plac
 // one and 1.9 rounds of tiles, where the tiles dealt by number have the same pieces past the whole round: the call 3 x 7 920 392 -> 403,
 // 3 x 8 554 336 -> 337, 2 x 8 160 417 -> 420, 3 x 5 007 298 -> 301 (of 3 x 5 643 390 -> 381); on either side 2 x 6 437 300 -> 283, 3 x 9 710 811 -> 773.
 constexpr double F32_DEAL_MIN_64 = 200, F32_DEAL_MIN_128 = 165;
-constexpr int DEAL_CUT = 2;          // rounds from which the last tiles stay whole: their partial results and the merge take 6-12 us (30 x 17 776)
 int attn_deal_segs(int dtype, int d, int H, int N, int Cq) {
   if (Cq < 2 || Cq > PLAN_BESIDE || H > DEAL_ENTRIES) return 0;
   const int BM = attn_block_rows(dtype, d, N, Cq), tiles = N / BM + Cq / 2 + 1, T = (N + 63) / 64;
@@ -1571,7 +1532,6 @@ int attn_deal_segs(int dtype, int d, int H, int N, int Cq) {
 }
 static int deal_entries(int dtype, int H, int segs, int most) { return ((dtype == ADACLUSTER_F32 ? F32_MAX_SPLITS : 1) * deal_list(H, segs, most) + (dtype == ADACLUSTER_F32 ? (F32_MAX_SPLITS - 1) * 96 : 0) + 3) / 4 * 4; }
 size_t attn_deal_ints(int dtype, int H, int segs, int most) { return segs ? DEAL_PARTS + 8 * (size_t)(DEAL_HEAD + deal_entries(dtype, H, segs, most)) : 0; }
-int attn_tail_slots(int dtype, int d, int H, int N, int Cq) { return dtype == ADACLUSTER_BF16 && attn_deal_segs(dtype, d, H, N, Cq) && lists_may_be_cut(N) ? 8 * TAIL_SLOTS : 0; }
 
 // Most pieces a key list of the fp32 kernel may go in (see pick_tile).  From some 1 024 tiles on there are two rounds of whole
 // ones (d=128), and the partial results of every row and the launch that combines them cost what the last round leaves idle
@@ -1621,10 +1581,10 @@ static Pieces f32_pieces(int N) {
   return p;
 }
 
-static Deal deal_of(int dtype, int d, int BM, int H, int N, int Cq, int segs, int most, int32_t* deal, int32_t* planned) {
+static Deal deal_of(int dtype, int d, int H, int N, int Cq, int segs, int most, int32_t* deal, int32_t* planned) {
   if (!segs) return {};
   const bool f32 = dtype == ADACLUSTER_F32;
-  return {deal, deal + DEAL_PARTS, planned, deal_entries(dtype, H, segs, most), segs, H, !f32 && lists_may_be_cut(N) ? DEAL_CUT * attn_resident(d, BM) / 8 : 0,
+  return {deal, deal + DEAL_PARTS, planned, deal_entries(dtype, H, segs, most), segs, H,
           f32 && attn_f32_splits(H, N, Cq) > 1 ? f32_resident(d) : 0, f32 ? (d == 64 ? f32_pieces<64>(N) : f32_pieces<128>(N)) : Pieces{}};
 }
 bool plan_reads_lengths(int Cq) { return Cq <= PLAN_BESIDE; }
@@ -1635,7 +1595,7 @@ int launch_plan_sparse(hipStream_t s, int dtype, int d, int H, int Cq, int cap, 
                        int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride,
                        const int32_t* perm_k, int N, const int32_t* lengths, int segs, int most, int32_t* deal, int32_t* planned) {
   const int split = dtype == ADACLUSTER_BF16 ? 1 : 0;
-  const TilePlan tp{lengths, q_offs, q_offs_stride, maxtiles, BM, SPLIT_SLOTS, split, tiles, ntiles, merge, nmerge, deal_of(dtype, d, BM, H, N, Cq, segs, most, deal, planned)};
+  const TilePlan tp{lengths, q_offs, q_offs_stride, maxtiles, BM, SPLIT_SLOTS, split, tiles, ntiles, merge, nmerge, deal_of(dtype, d, H, N, Cq, segs, most, deal, planned)};
   if (lengths && plan_reads_lengths(Cq)) {
     const auto plan = segs ? plan_sparse<true, true> : plan_sparse<true, false>;
     plan<<<dim3(H, Cq + 1), 256, plan_ints(Cq, segs != 0) * 4, s>>>(
@@ -1667,7 +1627,7 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
              (Cq == 1 || (size_t)4 * N * d <= ((size_t)8 << 20)) ? 1 : 0,
              part_o, part_ml, SPLIT_SLOTS, BM, krow, kstride,
              rng_start, rng_pre, rng_cnt, maxr, perm_k, dtype == ADACLUSTER_F32 ? attn_f32_splits(H, N, Cq) : 1, {}, nullptr, 0};
-  const Deal dl = deal_of(dtype, d, BM, H, N, Cq, segs, most, deal, nullptr);
+  const Deal dl = deal_of(dtype, d, H, N, Cq, segs, most, deal, nullptr);
   if (segs) { a.deal = dl.lists; a.deal_stride = DEAL_HEAD + dl.cap; }
   if (a.splits > 1) a.pieces = d == 64 ? f32_pieces<64>(N) : f32_pieces<128>(N);
   const bool cut = Cq == 1 || lists_may_be_cut(N);
@@ -1681,7 +1641,7 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
       else attn_mfma<128, A128_NW, A128_NBUF, A128_MINB, A128_VPRE><<<g, A128_NW * 64, 0, s>>>(a);
     }
     if (merge && cut) {      // the chunks of cut key lists
-      const dim3 gm(MERGE_GROUPS, segs ? H + 8 : H, 4);
+      const dim3 gm(MERGE_GROUPS, H, 4);
       if (d == 64) attn_merge<64><<<gm, 256, 0, s>>>(a, merge, nmerge);
       else attn_merge<128><<<gm, 256, 0, s>>>(a, merge, nmerge);
     }

@@ -166,11 +166,9 @@ int launch_plan_sparse(hipStream_t s, int dtype, int d, int H, int Cq, int cap, 
                        int32_t* merge, int32_t* nmerge, int row_scale, int32_t* krow, size_t kstride, const int32_t* perm_k, int N,
                        const int32_t* lengths /* [H][Cq] keys of every list, or NULL: not known beforehand */,
                        int segs /* attn_deal_segs() */, int most /* attn_most_tiles() */, int32_t* deal, int32_t* planned /* an integer; with lengths: 0 */);
-// Tiles of a sparse launch dealt to the XCDs by work: segments a head (0: dealt by their number), the integers of its table, and the
-// partial slots of the whole launch for the pieces of the last tiles (behind the attn_split_slots() of every head).
+// Tiles of a sparse launch dealt to the XCDs by work: segments a head (0: dealt by their number), and the integers of its table.
 int attn_deal_segs(int dtype, int d, int H, int N, int Cq);
 size_t attn_deal_ints(int dtype, int H, int segs, int most);
-int attn_tail_slots(int dtype, int d, int H, int N, int Cq);
 struct DenseShape { int BM, pieces; };       // queries a workgroup, chunks of the key list
 DenseShape attn_dense_shape(int dtype, int d, int H, int N);
 int launch_plan_dense(hipStream_t s, int H, int N, int maxtiles, DenseShape shape, int32_t* rng_start, int32_t* rng_pre,

@@ -469,7 +469,7 @@ def test_fp32_lists_shorter_than_their_split(d):
 
 
 @pytest.mark.parametrize("H,N,d,Cq", [(64, 2600, 64, 24),       # as many heads as are dealt by work
-                                      (5, 9247, 128, 65),       # the last tiles of an XCD in pieces of their lists
+                                      (5, 9247, 128, 65),       # a tile more than places on an XCD
                                       (2, 34000, 128, 3),       # 256 queries a workgroup, a list of all keys
                                       (16, 5000, 64, 256),      # as many query clusters as are dealt by work, many of a row or none
                                       (7, 6001, 128, 33)])
@@ -540,3 +540,28 @@ def test_fp32_tiles_dealt_by_work(H, N, d, Cq):
                 P = torch.softmax(Q[h, rows].double() @ K[h, keys].double().T.contiguous() / d ** 0.5, 1)
                 ref[rows] = P @ V[h, keys].double()
         assert float((O[h].double() - ref).abs().max()) < 1e-4, h
+
+
+@pytest.mark.parametrize("H,N,d,Cq", [(4, 13200, 128, 65),      # a few tiles more than places on an XCD
+                                      (9, 9001, 64, 33),        # less than a round
+                                      (3, 31000, 128, 30)])     # 256 queries a workgroup
+def test_a_head_has_the_same_bits_alone_and_among_others(H, N, d, Cq):
+    """bf16 sparse attention: which workgroups run a head's tiles depends on the other heads' lists, how their sums are formed does not."""
+    Ck = 40
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    Q, K, V = (torch.randn((H, N, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    rng = np.random.default_rng(N)
+    ql = torch.from_numpy(np.minimum((Cq * rng.random((H, N)) ** 2).astype(np.int32), Cq - 1)).cuda()
+    kl = torch.from_numpy(rng.integers(0, Ck, (H, N)).astype(np.int32)).cuda()
+    sel = [[np.sort(rng.choice(Ck, size=int(rng.integers(0, max(2, Ck * (h + 1) // H))), replace=False)) for _ in range(Cq)] for h in range(H)]
+
+    def attend(heads):
+        p = B.Params(H=len(heads), N=N, d=d, dtype=B.BF16, q_clusters=Cq, k_m0=4, k_m_min=1, k_max_clusters=Ck)
+        si, sc = sel_to_dev([sel[h] for h in heads], Cq, p.cap)
+        x = [t[heads].contiguous() for t in (Q, K, V, ql, kl)]
+        return B.adacluster_sparse_attn(p, *x, torch.full((len(heads),), Ck, dtype=torch.int32, device="cuda"), si, sc, ws=B.workspace(p))
+
+    O = attend(list(range(H)))
+    for h in range(H):
+        assert torch.equal(O[h], attend([h])[0]), h
