@@ -16,8 +16,8 @@ namespace adac {
 // LDS 32 dimensions at a time, a dimension's values of all rows side by side, so that a thread reads four at once.
 // Bound by vector issue: max(q p, q n) is q times the larger of p and n where q >= 0, and times the smaller where q < 0 (rounding is
 // monotonic), so a term is a select and a multiply-add behind one comparison of q for four pages, not two products, a maximum and an
-// add: 2.25 instructions of 4.  That holds for finite values; from the first 32 dimensions with any other on, a workgroup forms its terms as Eq. 1
-// writes them.  18 heads x 12 039 rows x 865 pages, d=128, bf16 1 949 -> 1 181 us, 6 x 81 444 x 416, d=128, fp32 2 344 -> 1 451, 8 x 75 861 x
+// add: 2.25 instructions of 4.  That holds while no product overflows, which values below 2^63 rule out (a multiply-add does not round its product
+// to infinity); from the first 32 dimensions with any other on, a workgroup forms its terms as Eq. 1 writes them.  18 heads x 12 039 rows x 865 pages, d=128, bf16 1 949 -> 1 181 us, 6 x 81 444 x 416, d=128, fp32 2 344 -> 1 451, 8 x 75 861 x
 // 387, d=64 1 375 -> 917, 10 x 168 x 105 17.6 -> 9.8 (56 % of the vector rate; 4 x 4 outputs a thread, scalar LDS reads: 57 % for 4 a term).
 template <typename T, int TI>
 __global__ __launch_bounds__(256) void quest_alu(int Lq, int Lk, int d, int clamp, int aligned, int whole, const T* __restrict__ Q,
@@ -26,6 +26,7 @@ __global__ __launch_bounds__(256) void quest_alu(int Lq, int Lk, int d, int clam
   constexpr int TD = 32, QR = 16 * TI, E = 16 / sizeof(T), PIECES = TD / E;      // E: values of a 16-byte piece
   __shared__ __attribute__((aligned(16))) float qs[TD][QR + 4], his[TD][68], los[TD][68];
   __shared__ int odd;
+  constexpr float PLAIN = 0x1p63f;
   const int h = blockIdx.z, q0 = blockIdx.x * QR, k0 = blockIdx.y * 64, tid = threadIdx.x;
   const int tq = (tid >> 4) * TI, tk = (tid & 15) * 4;
   const T* Qh = Q + (size_t)h * Lq * d;
@@ -49,13 +50,13 @@ __global__ __launch_bounds__(256) void quest_alu(int Lq, int Lk, int d, int clam
   if (tid == 0) odd = 0;
   for (int d0 = 0; d0 < d; d0 += TD) {
     __syncthreads();                               // the values of the step before have been read
-    bool finite = true;
+    bool small = true;
     for (int e = tid; e < QR * PIECES; e += 256) {
       const int r = e % QR, g = e / QR;
       float x[E] = {};
       if (q0 + r < Lq) piece(Qh + (size_t)(q0 + r) * d + d0 + g * E, x);
 #pragma unroll
-      for (int i = 0; i < E; ++i) { qs[g * E + i][r] = x[i]; finite = finite && fabsf(x[i]) < INFINITY; }
+      for (int i = 0; i < E; ++i) { qs[g * E + i][r] = x[i]; small = small && fabsf(x[i]) < PLAIN; }
     }
     for (int e = tid; e < 64 * PIECES; e += 256) {
       const int r = e % 64, g = e / 64;
@@ -69,10 +70,10 @@ __global__ __launch_bounds__(256) void quest_alu(int Lq, int Lk, int d, int clam
         if (clamp) { p[i] = fmaxf(p[i], 0.f); n[i] = fminf(n[i], 0.f); }
         const float hi = fmaxf(p[i], n[i]), lo = fminf(p[i], n[i]);
         his[g * E + i][r] = hi; los[g * E + i][r] = lo;
-        finite = finite && fabsf(hi) < INFINITY && fabsf(lo) < INFINITY;
+        small = small && fabsf(hi) < PLAIN && fabsf(lo) < PLAIN;
       }
     }
-    if (!finite) odd = 1;                          // (stays: the steps that follow are formed term by term as well)
+    if (!small) odd = 1;                           // (stays: the steps that follow are formed term by term as well)
     __syncthreads();
     auto terms = [&](auto plain) __attribute__((always_inline)) {
 #pragma unroll 4

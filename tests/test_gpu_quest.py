@@ -130,3 +130,21 @@ def test_vector_form_at_the_edges_of_its_tiles(H, Lq, Lk, d, shift, bf16):
         fin = torch.isfinite(ref)
         assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(got[~fin & ~torch.isnan(ref)], ref[~fin & ~torch.isnan(ref)])
         assert ((got - ref).abs()[fin] <= 1e-5 * mag[fin] + 1e-6).all()
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+@pytest.mark.parametrize("H,Lq,Lk", [(8, 32801, 65), (4, 8201, 66), (1, 33, 3)])      # eight, four and two rows a thread
+def test_vector_form_where_products_overflow(H, Lq, Lk, bf16):
+    """Finite values whose products are infinite: Eq. 1 term by term in fp32, so one term of each sign makes NaN, one alone infinity."""
+    d = 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(Lq)
+    Q, hi, lo = (torch.randn(s, generator=gen, device="cuda") for s in ((H, Lq, d), (H, Lk, d), (H, Lk, d)))
+    Q[:, :, 2], Q[:, :, 40] = 2.0 ** 70, 2.0 ** 80
+    hi[:, 0, 2], lo[:, 0, 2], hi[:, 0, 40], lo[:, 0, 40] = 2.0 ** 60, -1.0, -2.0 ** 60, -2.0 ** 61      # +inf and -inf
+    hi[:, 1, 2], lo[:, 1, 2], hi[:, 1, 40], lo[:, 1, 40] = 2.0 ** 60, -1.0, 0.0, -1.0                     # +inf
+    hi[:, 2, 2], lo[:, 2, 2], hi[:, 2, 40], lo[:, 2, 40] = 1.0, -1.0, 0.0, -2.0 ** 60                     # none: the larger product
+    if bf16:
+        Q, hi, lo = (t.to(torch.bfloat16) for t in (Q, hi, lo))
+    S = B.adacluster_quest_scores(Q, hi, lo, B.QUEST_ALU)
+    assert S[:, :, 0].isnan().all() and (S[:, :, 1] == float("inf")).all() and S[:, :, 2].isfinite().all()
