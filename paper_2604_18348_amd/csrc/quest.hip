@@ -183,12 +183,10 @@ __global__ __launch_bounds__(NW * 64) void quest_mfma(int Lq, int Lk, int clamp,
   // times the store instructions and a walk over rows and pages: 2 x 75 600 rows, 450 pages, d=64 58 -> 53 us (5.1 TB/s),
   // 3 x 50 001 x 333 48 -> 39, 4 x 17 776 x 200, d=128 23.5 -> 21.0, 1 x 180 000 x 60 16.6 -> 14.6; more spans: 24 x 9 000 x
   // 700, d=128 187 -> 171, 2 x 75 600 x 993 180 -> 169, 1 x 100 000 x 513, its second span one page, 62.4 -> 63.2.
-  // Whole lines of one span leave as streaming stores, past the L2's lines for data that is read again, and lines that two blocks
-  // share as others do: so a span's floats sit in LDS behind a line's start, `mis` up to 31.  2 x 75 600 x 450, d=64 62.4 -> 54.2 us (5.4
-  // TB/s), 21 x 11 528 x 392 88 -> 77, 4 x 76 823 x 352, d=128 119 -> 110, 7 x 15 149 x 234 29.8 -> 25.6, 15 x 13 650 x 385 78 -> 76 (86 with
-  // shared lines too); 10 x 89 713 x 156 169 and 171, 22 x 30 774 x 114 88.6 and 92, 2 x 67 353 x 826 114 and 124: fewer and more pages stay.
-  const bool streaming = NW >= 8 && single && Lk > 192;
-  const int mis = (int)((uintptr_t)(S + (size_t)h * Lq * Lk) >> 2) & (streaming ? 31 : 3);
+  // (Whole lines as streaming stores: the call alone 0.92 of its time over 16 shapes on three buffers in turn, 2 x 75 600 x 450 62 -> 58 us,
+  // but what reads the scores next reads them from memory: call and a reader of all scores 1.09, 2 x 75 600 x 450 143 -> 151, 4 x 76 823 x
+  // 352, d=128 224 -> 254, on one buffer 1.06; and 4 x 32 760 x 300, d=64 on one buffer, without a reader, 31 -> 40.)
+  const int mis = (int)((uintptr_t)(S + (size_t)h * Lq * Lk) >> 2) & 3;
   const int stores = single ? 8 * Lk / NT : 0;            // store instructions a wave issues per whole block, at least
   int slot = 0;
   for (int b = b0; b < b1; ++b) {
@@ -221,15 +219,11 @@ __global__ __launch_bounds__(NW * 64) void quest_mfma(int Lq, int Lk, int clamp,
     float* Sb = S + ((size_t)h * Lq + (size_t)b * 32) * Lk;
     const int nrows = min(32, Lq - b * 32);
     // floats [from, to) of a run that starts at `at` in LDS and in S, first .. first + 3 this lane's of the first step
-    auto leave = [&](const float* at, float* out, int from, int to, int first, int step, auto streams) __attribute__((always_inline)) {
+    auto leave = [&](const float* at, float* out, int from, int to, int first, int step) __attribute__((always_inline)) {
       for (int e = first; e < to; e += step) {
         const float4 v = *reinterpret_cast<const float4*>(at + e);
         if (e >= from && e + 4 <= to) {
-          if constexpr (decltype(streams)::value) {
-            const int line = e & ~31;    // (e counts from the start of a line of S)
-            if (line >= from && line + 32 <= to) __builtin_nontemporal_store(f32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4_t*>(out + e));
-            else *reinterpret_cast<float4*>(out + e) = v;
-          } else *reinterpret_cast<float4*>(out + e) = v;
+          *reinterpret_cast<float4*>(out + e) = v;
         } else {
           const float x[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -238,15 +232,14 @@ __global__ __launch_bounds__(NW * 64) void quest_mfma(int Lq, int Lk, int clamp,
       }
     };
     if (single) {                 // whole rows: one run over all of them
-      if (NW >= 8 && streaming) leave(ts, Sb - mis, mis, mis + nrows * Lk, 4 * tid, 4 * NT, std::true_type{});
-      else leave(ts, Sb - mis, mis, mis + nrows * Lk, 4 * tid, 4 * NT, std::false_type{});
+      leave(ts, Sb - mis, mis, mis + nrows * Lk, 4 * tid, 4 * NT);
     } else {
       for (int r = wave; r < nrows; r += NW) {
         float* row = Sb + (size_t)r * Lk;
         // first page at or after p that starts a line of S
         auto line = [&](int p) __attribute__((always_inline)) { return p + (int)((0u - (uint32_t)((uintptr_t)(row + p) >> 2)) & 31u); };
         const int from = k0 == 0 ? 0 : line(k0), to = last ? Lk : line(k0 + SPAN - 32), mr = (mis + r * Lk) & 3;
-        leave(ts + r * STRIDE, row + k0 - mr, from - k0 + mr, to - k0 + mr, ((from - k0 + mr) & ~3) + 4 * lane, 256, std::false_type{});
+        leave(ts + r * STRIDE, row + k0 - mr, from - k0 + mr, to - k0 + mr, ((from - k0 + mr) & ~3) + 4 * lane, 256);
       }
     }
     slot = slot == 2 ? 0 : slot + 1;
