@@ -288,7 +288,7 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(tiles, int32_t*, H * (size_t)D.maxtiles * attn_tile_record() * 4);
   TAKE(merge, int32_t*, H * (size_t)attn_split_slots() * 4 * 4);
   TAKE(nmerge, int32_t*, H * 4);
-  TAKE(deal, int32_t*, attn_deal_ints(p->dtype, D.H, attn_deal_segs(p->dtype, D.d, D.H, D.N, D.Cq), attn_most_tiles(p->dtype, D.N, D.Cq, D.BM, D.maxtiles)) * 4);
+  TAKE(deal, int32_t*, attn_deal_ints(p->dtype, D.d, D.H, D.N, D.Cq, attn_deal_segs(p->dtype, D.d, D.H, D.N, D.Cq), attn_most_tiles(p->dtype, D.N, D.Cq, D.BM, D.maxtiles)) * 4);
   {  // partial results of split key lists: slots of cut lists (bf16), or a row per query and split (fp32; the dense call
      // counts as one cluster, which never makes fewer splits)
     const size_t splits = attn_f32_splits(D.H, D.N, 1);     // (1: the kernel writes the output itself)

@@ -12,6 +12,7 @@
 // product (a column of V over 8 keys) is gathered by LDS transpose reads.
 #include "common.h"
 #include "launch.h"
+#include "deal.h"
 
 #include <type_traits>
 
@@ -21,8 +22,6 @@ static constexpr int TILE_REC = 8;       // ints per query-tile record (32 bytes
 static constexpr int MIN_CHUNK = 16;     // key tiles of a chunk at least: lists of up to twice as many stay whole
 static constexpr int SPLIT_SLOTS = 128;  // partial slots per head for the chunks of cut key lists
 static constexpr int F32_WAVES = 4;      // waves of a workgroup of the fp32 kernel
-static constexpr int F32_MAX_SPLITS = 4; // most workgroups the fp32 kernel splits a key list over
-__host__ __device__ constexpr int f32_resident(int d) { return 32 * (d == 64 ? 3 : 2); }   // of its workgroups on the 32 CUs of an XCD
 static constexpr float PART_DONE = -1.f; // in place of the sum of a row's first partial result: the row is written
 static constexpr int KROW_PAD = 8 * 64;  // entries of the row-offset table a key list is padded by: the kernel reads up to 7 tiles ahead
 
@@ -46,7 +45,6 @@ __device__ __forceinline__ int wave_prefix(int v, int lane) {
 // workgroup of its own that leaves unnormalised (O, m, l) in a partial slot, and attn_merge
 // combines the slots of a query tile.  merge [H][slots] x {first query position, rows, first slot,
 // chunks}; a head has `slots` partial slots, and lists stay whole once they are used up.
-constexpr int PLAN_BESIDE = 256;       // query clusters up to which the LDS it takes (8 KB each) leaves the lists' workgroups their places
 __host__ __device__ constexpr int plan_ints(int Cq, bool deal) { return (deal ? 11 : 9) * Cq + 1; }      // of LDS
 // Pieces for `rest` tiles of an XCD, for every number of them: two bits each (pieces - 1), 32 a word.  By the host, as the
 // kernel's registers and first microseconds are dear (3 x 5 007 rows, d=128, a call 288 us, 290 with the rule in the kernel).
@@ -65,13 +63,6 @@ __device__ __forceinline__ int pieces_of(const Pieces& p, int rest) {
 // whole one went in pieces: calls of 8 x 6 000, d=128 222 -> 241 us, 7 x 8 000, d=128 220 -> 237, and 5 x 9 247 505 -> 481).
 // Fp32 lists go in pieces as in pick_tile, or, where all are one round, each in pieces of about a sixth of a CU's work (whole 2 x 5 681 top-p, d=128 took
 // 216 us, dealt by number 181, so 155; pieces in launches of more rounds cost more than they even out: 3 x 5 007 177 -> 203).
-constexpr int DEAL_ENTRIES = 64;                     // segments at most
-// A head's record: the longest list (key tiles) of every segment, the first tile of every part of the segments and the end
-__host__ __device__ constexpr int deal_rec(int segs) { return segs + 8 * segs + 1; }
-constexpr int DEAL_PARTS = 10 * DEAL_ENTRIES;        // of all heads: H * segs <= DEAL_ENTRIES
-constexpr int DEAL_HEAD = 4;                         // an XCD's list: their number (and padding), the entries
-__host__ __device__ constexpr int deal_cap(int tiles) { return tiles * 9 / 64 + 2; }       // most tiles of a part, of `tiles` in eight parts
-__host__ __device__ constexpr int deal_list(int H, int segs, int most) { return H * (most * 9 / 64 + 2 * segs); }      // most entries of an XCD
 struct DealtTile { int h, tile, z, sp; };            // head, tile, piece and (fp32) of how many
 __device__ __forceinline__ int dealt(int h, int tile, int z, int sp = 1) { return h << 23 | tile << 6 | z << 3 | (sp - 1); }
 __device__ __forceinline__ DealtTile dealt_tile(uint32_t e) { return {(int)(e >> 23), (int)(e >> 6 & 0x1FFFF), (int)(e >> 3 & 7), (int)(e & 7) + 1}; }      // (tile: 17 bits)
@@ -125,12 +116,12 @@ __device__ __forceinline__ void deal_lists(const Deal& dl) {
     if (cut > 1) {
       for (int i = 0; i < n; ++i)
         for (int z = 0; z < cut; ++z) list[DEAL_HEAD + incl - mine + z * n + i] = dealt(h, first + i, z, cut);
-      continue;
-    }
-    for (int i = 0; i < n; ++i) {
-      const int s = incl - n + i;
-      if (s < whole) { list[DEAL_HEAD + s] = dealt(h, first + i, 0); continue; }
-      for (int z = 0; z < sp; ++z) list[DEAL_HEAD + s + z * rest] = dealt(h, first + i, z, sp);
+    } else {
+      for (int i = 0; i < n; ++i) {
+        const int s = incl - n + i;
+        if (s < whole) { list[DEAL_HEAD + s] = dealt(h, first + i, 0); continue; }
+        for (int z = 0; z < sp; ++z) list[DEAL_HEAD + s + z * rest] = dealt(h, first + i, z, sp);
+      }
     }
   }
 }
@@ -273,15 +264,10 @@ __device__ __forceinline__ void tiles_of_head(int32_t* sm, int h, int Cq, int ma
         int at[9];
 #pragma unroll
         for (int x = 0; x <= 8; ++x) at[x] = s_bound[8 * tid + x];
-        const int cap = deal_cap(at[8] - at[0]);
+        deal_parts(at);
         put(tid, s_longest[tid]);
-        int b = at[0];
-        put(segs + 8 * tid, b);
 #pragma unroll
-        for (int x = 1; x < 8; ++x) {
-          b = min(max(max(at[x], b), at[8] - (8 - x) * cap), min(b + cap, at[8]));
-          put(segs + 8 * tid + x, b);
-        }
+        for (int x = 0; x < 8; ++x) put(segs + 8 * tid + x, at[x]);
       }
       if (tid == 63) put(9 * segs, nt);
       // The stores go through to where every XCD sees them, and have arrived when they are counted: the head reports only then.  (A
@@ -575,7 +561,6 @@ struct AttnArgs {
 // which; f32_pieces() how many), so that no CU is left with a whole one when the others are done.  585 tiles, d=128, are 75
 // an XCD that holds 64 workgroups: 64 whole and 11 in four pieces, 198 us; all of them in two pieces, three rounds, 222.
 // Returns false where the list has ended.
-constexpr int PICK_HEADS = 256;
 
 __device__ __forceinline__ bool pick_tile(const int32_t* __restrict__ ntiles, int H, const Pieces& pieces, int splits, int resident, int& h, int& tile,
                                           int& z, int& sp) {
@@ -1501,44 +1486,21 @@ int attn_split_slots() { return SPLIT_SLOTS; }
 // those without work leave places empty that a small launch would have used: where no list is cut, none for pieces.
 static bool lists_may_be_cut(int N) { return (N + 63) / 64 > 2 * MIN_CHUNK; }
 int attn_most_tiles(int dtype, int N, int Cq, int BM, int maxtiles) {
-  return dtype == ADACLUSTER_BF16 && !lists_may_be_cut(N) ? N / BM + Cq + 1 : maxtiles;
+  return dtype == ADACLUSTER_F32 || !lists_may_be_cut(N) ? N / BM + Cq + 1 : maxtiles;      // (an fp32 list has no records for its pieces)
 }
 static int attn_resident(int d, int BM) { return 256 * (BM == 128 ? 2 : 1) * (d == 64 ? 2 : 1); }      // workgroups of the bf16 kernel
-// Segments a head where the tiles of a sparse launch are dealt by work; 0 where by their number.  Dealt by number, an XCD has what its heads
-// happen to have: 16 heads of 14 119 tokens, d=128, some without structure, attention 1 130 -> 700 us; 30 x 21 600, top-p 1 720 -> 1 250;
-// calls of 8 x 6 000, d=128 233 -> 222, 4 x 13 200, d=128 403 -> 390, 16 x 6 000, d=64 232 -> 214, 5 x 9 247, d=128 528 -> 505.  The plan takes 2-8 us more (its last head
-// waits for three trips to memory), so a tile a CU (n < 256) or short lists (under 75 key tiles a place: 23 x 1 680, d=128, 176 -> 181 us a
-// call, 19 x 3 864, d=64, 144 -> 148; but 29 x 4 140 490 -> 476, 17 x 3 405, d=128, 333 -> 273) are not worth it, and from
-// sixteen rounds on the ends of the lists are less than that.  Heads of equal lists are what neither side gains by: 30 x 17 776 773 and 775 us.
-constexpr double DEAL_MIN = 75;      // key tiles (of a list of all keys) a place
-// fp32: key tiles (of a list of all keys) a CU, by width.  Lists of uneven length are what is to be gained (one head's lists more than
-// another's, top-p): attention of 3 x 10 876, top-p, d=64 383 -> 272 us, 3 x 9 600, top-p, d=128 510 -> 431, 3 x 9 200, d=128, 25 clusters
-// 424 -> 391; below the line the plan takes what it gives (2 x 5 928, d=128 77 -> 75 and 6 for the plan).  So it does at d=128 between
-// one and 1.9 rounds of tiles, where the tiles dealt by number have the same pieces past the whole round: the call 3 x 7 920 392 -> 403,
-// 3 x 8 554 336 -> 337, 2 x 8 160 417 -> 420, 3 x 5 007 298 -> 301 (of 3 x 5 643 390 -> 381); on either side 2 x 6 437 300 -> 283, 3 x 9 710 811 -> 773.
-constexpr double F32_DEAL_MIN_64 = 200, F32_DEAL_MIN_128 = 165;
 int attn_deal_segs(int dtype, int d, int H, int N, int Cq) {
-  if (Cq < 2 || Cq > PLAN_BESIDE || H > DEAL_ENTRIES) return 0;
-  const int BM = attn_block_rows(dtype, d, N, Cq), tiles = N / BM + Cq / 2 + 1, T = (N + 63) / 64;
-  if (dtype == ADACLUSTER_F32) {
-    if (tiles > 65536 || (double)H * tiles * T < 256 * (d == 64 ? F32_DEAL_MIN_64 : F32_DEAL_MIN_128) || 4.0 * H * (N / BM + Cq + 1) * (T + 64.0) >= 2147483648.0) return 0;
-    const double rounds = (double)H * tiles / (8 * f32_resident(d));
-    if (d == 128 && rounds > 1 && rounds < 1.9) return 0;
-    return max(1, min(min(8, DEAL_ENTRIES / H), tiles / 16));
-  }
-  const double n = (double)H * tiles, r = attn_resident(d, BM);
-  if (n < 256 || n >= 16 * r || n * T < DEAL_MIN * r || 9.0 * H * (N / BM + Cq + 1) * (T + 64.0) >= 2147483648.0) return 0;
-  return max(1, min(min(8, DEAL_ENTRIES / H), tiles / 16));
+  const int BM = attn_block_rows(dtype, d, N, Cq);
+  return dtype == ADACLUSTER_F32 ? deal_segs_f32(d, H, N, Cq) : deal_segs_bf16(BM, attn_resident(d, BM), H, N, Cq);
 }
-static int deal_entries(int dtype, int H, int segs, int most) { return ((dtype == ADACLUSTER_F32 ? F32_MAX_SPLITS : 1) * deal_list(H, segs, most) + (dtype == ADACLUSTER_F32 ? (F32_MAX_SPLITS - 1) * 96 : 0) + 3) / 4 * 4; }
-size_t attn_deal_ints(int dtype, int H, int segs, int most) { return segs ? DEAL_PARTS + 8 * (size_t)(DEAL_HEAD + deal_entries(dtype, H, segs, most)) : 0; }
+static int deal_entries(int dtype, int d, int H, int N, int Cq, int segs, int most) {
+  return dtype == ADACLUSTER_F32 ? deal_entries_f32(d, H, N, Cq, segs, most) : deal_list(H, segs, most);
+}
+size_t attn_deal_ints(int dtype, int d, int H, int N, int Cq, int segs, int most) {
+  return segs ? DEAL_PARTS + 8 * (size_t)(DEAL_HEAD + deal_entries(dtype, d, H, N, Cq, segs, most)) : 0;
+}
 
-// Most pieces a key list of the fp32 kernel may go in (see pick_tile).  From some 1 024 tiles on there are two rounds of whole
-// ones (d=128), and the partial results of every row and the launch that combines them cost what the last round leaves idle
-// (150 heads of 200 rows: 58 us whole, 66 in pieces).
-int attn_f32_splits(int H, int N, int Cq) {
-  return H <= PICK_HEADS && (long long)H * (N / 32 + Cq / 2 + 1) < 1024 ? F32_MAX_SPLITS : 1;
-}
+int attn_f32_splits(int H, int N, int Cq) { return f32_splits(H, N, Cq); }
 
 // The rule: the number that ends first, the smallest of equals.  A piece takes a wave's share of the list's key tiles (as many
 // as a list can have) and half a tile for its start and end; the workgroups that share a CU take turns, so a round lasts as
@@ -1582,10 +1544,14 @@ static Pieces f32_pieces(int N) {
 }
 
 static Deal deal_of(int dtype, int d, int H, int N, int Cq, int segs, int most, int32_t* deal, int32_t* planned) {
-  if (!segs) return {};
-  const bool f32 = dtype == ADACLUSTER_F32;
-  return {deal, deal + DEAL_PARTS, planned, deal_entries(dtype, H, segs, most), segs, H,
-          f32 && attn_f32_splits(H, N, Cq) > 1 ? f32_resident(d) : 0, f32 ? (d == 64 ? f32_pieces<64>(N) : f32_pieces<128>(N)) : Pieces{}};
+  Deal dl{};
+  if (!segs) return dl;
+  dl.parts = deal; dl.lists = deal + DEAL_PARTS; dl.planned = planned; dl.cap = deal_entries(dtype, d, H, N, Cq, segs, most); dl.segs = segs; dl.H = H;
+  if (dtype == ADACLUSTER_F32 && attn_f32_splits(H, N, Cq) > 1) {
+    dl.f32_round = f32_resident(d);
+    dl.pieces = d == 64 ? f32_pieces<64>(N) : f32_pieces<128>(N);
+  }
+  return dl;
 }
 bool plan_reads_lengths(int Cq) { return Cq <= PLAN_BESIDE; }
 int launch_plan_sparse(hipStream_t s, int dtype, int d, int H, int Cq, int cap, int maxr, int maxtiles, int BM,
@@ -1627,11 +1593,11 @@ int launch_attention(hipStream_t s, int dtype, int d, int H, int N, int Cq, int 
              (Cq == 1 || (size_t)4 * N * d <= ((size_t)8 << 20)) ? 1 : 0,
              part_o, part_ml, SPLIT_SLOTS, BM, krow, kstride,
              rng_start, rng_pre, rng_cnt, maxr, perm_k, dtype == ADACLUSTER_F32 ? attn_f32_splits(H, N, Cq) : 1, {}, nullptr, 0};
-  const Deal dl = deal_of(dtype, d, H, N, Cq, segs, most, deal, nullptr);
-  if (segs) { a.deal = dl.lists; a.deal_stride = DEAL_HEAD + dl.cap; }
-  if (a.splits > 1) a.pieces = d == 64 ? f32_pieces<64>(N) : f32_pieces<128>(N);
+  const int entries = segs ? deal_entries(dtype, d, H, N, Cq, segs, most) : 0;
+  if (segs) { a.deal = deal + DEAL_PARTS; a.deal_stride = DEAL_HEAD + entries; }
+  else if (a.splits > 1) a.pieces = d == 64 ? f32_pieces<64>(N) : f32_pieces<128>(N);
   const bool cut = Cq == 1 || lists_may_be_cut(N);
-  const dim3 g = segs ? dim3(8 * dl.cap) : dim3((most + 7) / 8 * 8, H);
+  const dim3 g = segs ? dim3(8 * entries) : dim3((most + 7) / 8 * 8, H);
   if (dtype == ADACLUSTER_BF16) {
     if (BM == 128) {
       if (d == 64) attn_mfma<64, 4, 2, 4, 0><<<g, 256, 0, s>>>(a);

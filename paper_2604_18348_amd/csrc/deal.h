@@ -1,0 +1,72 @@
+// Sparse launches whose tiles are dealt to the XCDs by work: which they are, and the sizes of their lists (attn.hip; also compiled for the CPU).
+#pragma once
+#include <cstdint>
+
+namespace adac {
+
+static constexpr int F32_MAX_SPLITS = 4; // most workgroups the fp32 kernel splits a key list over
+__host__ __device__ constexpr int f32_resident(int d) { return 32 * (d == 64 ? 3 : 2); }   // of its workgroups on the 32 CUs of an XCD
+constexpr int PICK_HEADS = 256;          // heads up to which the tiles of a launch are one list (pick_tile in attn.hip)
+// Most pieces a key list of the fp32 kernel may go in (see pick_tile).  From some 1 024 tiles on there are two rounds of whole
+// ones (d=128), and the partial results of every row and the launch that combines them cost what the last round leaves idle
+// (150 heads of 200 rows: 58 us whole, 66 in pieces).
+inline int f32_splits(int H, int N, int Cq) { return H <= PICK_HEADS && (long long)H * (N / 32 + Cq / 2 + 1) < 1024 ? F32_MAX_SPLITS : 1; }
+
+constexpr int PLAN_BESIDE = 256;       // query clusters up to which the LDS it takes (8 KB each) leaves the lists' workgroups their places
+constexpr int DEAL_ENTRIES = 64;                     // segments at most
+// A head's record: the longest list (key tiles) of every segment, the first tile of every part of the segments and the end
+__host__ __device__ constexpr int deal_rec(int segs) { return segs + 8 * segs + 1; }
+constexpr int DEAL_PARTS = 10 * DEAL_ENTRIES;        // of all heads: H * segs <= DEAL_ENTRIES
+constexpr int DEAL_HEAD = 4;                         // an XCD's list: their number (and padding), the entries
+__host__ __device__ constexpr int deal_cap(int tiles) { return tiles * 9 / 64 + 2; }       // most tiles of a part, of `tiles` in eight parts
+// First tiles of a segment's eight parts and its end, as near to those of equal work as no part has more than that.
+__host__ __device__ inline void deal_parts(int (&at)[9]) {
+  const int cap = deal_cap(at[8] - at[0]);
+  for (int x = 1; x < 8; ++x) {
+    const int least = at[8] - (8 - x) * cap, most = at[x - 1] + cap < at[8] ? at[x - 1] + cap : at[8];
+    int b = at[x] > at[x - 1] ? at[x] : at[x - 1];
+    if (b < least) b = least;
+    at[x] = b < most ? b : most;
+  }
+}
+// Most tiles of an XCD, of at most `most` a head: the grid of a launch is what its lists can hold, as every workgroup without an entry takes a
+// place and a trip to memory.
+inline int deal_list(int H, int segs, int most) { return H * (most * 9 / 64 + 2 * segs); }
+// Most entries of an XCD, fp32, where lists may go in pieces: all of them while the tiles are one round, those past the last whole round else.
+inline int deal_entries_f32(int d, int H, int N, int Cq, int segs, int most) {
+  const int tiles = deal_list(H, segs, most), round = f32_resident(d);
+  if (f32_splits(H, N, Cq) == 1) return tiles;
+  return tiles <= round ? F32_MAX_SPLITS * tiles : tiles + (F32_MAX_SPLITS - 1) * round;
+}
+
+inline int deal_segs(int H, int tiles) { const int n = DEAL_ENTRIES / H < 8 ? DEAL_ENTRIES / H : 8, m = n < tiles / 16 ? n : tiles / 16; return m > 1 ? m : 1; }
+// Segments a head where the tiles of a sparse launch are dealt by work; 0 where by their number.  Dealt by number, an XCD has what its heads
+// happen to have: 16 heads of 14 119 tokens, d=128, some without structure, attention 1 130 -> 700 us; 30 x 21 600, top-p 1 720 -> 1 250;
+// calls of 8 x 6 000, d=128 233 -> 222, 4 x 13 200, d=128 403 -> 390, 16 x 6 000, d=64 232 -> 214, 5 x 9 247, d=128 528 -> 505.
+// The plan takes 2-8 us more (its last head waits for three trips to memory), so a tile a CU (n < 256) or short lists (under 75 key tiles a place: 23 x 1 680, d=128, 176 -> 181 us a
+// call, 19 x 3 864, d=64, 144 -> 148; but 29 x 4 140 490 -> 476, 17 x 3 405, d=128, 333 -> 273) are not worth it, and from
+// sixteen rounds on the ends of the lists are less than that.  Heads of equal lists are what neither side gains by: 30 x 17 776 773 and 775 us.
+constexpr double DEAL_MIN = 75;      // key tiles (of a list of all keys) a place
+inline int deal_segs_bf16(int BM, int resident /* workgroups of the chip */, int H, int N, int Cq) {
+  if (Cq < 2 || Cq > PLAN_BESIDE || H > DEAL_ENTRIES) return 0;
+  const int tiles = N / BM + Cq / 2 + 1, T = (N + 63) / 64;
+  const double n = (double)H * tiles, r = resident;
+  if (n < 256 || n >= 16 * r || n * T < DEAL_MIN * r || 9.0 * H * (N / BM + Cq + 1) * (T + 64.0) >= 2147483648.0) return 0;
+  return deal_segs(H, tiles);
+}
+// fp32: key tiles (of a list of all keys) a CU, by width.  Lists of uneven length are what is to be gained (one head's lists more than
+// another's, top-p): attention of 3 x 10 876, top-p, d=64 383 -> 272 us, 3 x 9 600, top-p, d=128 510 -> 431, 3 x 9 200, d=128, 25 clusters
+// 424 -> 391; below the line the plan takes what it gives (2 x 5 928, d=128 77 -> 75 and 6 for the plan).  So it does at d=128 between
+// one and 1.9 rounds of tiles, where the tiles dealt by number have the same pieces past the whole round: the call 3 x 7 920 392 -> 403,
+// 3 x 8 554 336 -> 337, 2 x 8 160 417 -> 420, 3 x 5 007 298 -> 301 (of 3 x 5 643 390 -> 381); on either side 2 x 6 437 300 -> 283, 3 x 9 710 811 -> 773.
+constexpr double F32_DEAL_MIN_64 = 200, F32_DEAL_MIN_128 = 165;
+inline int deal_segs_f32(int d, int H, int N, int Cq) {
+  if (Cq < 2 || Cq > PLAN_BESIDE || H > DEAL_ENTRIES) return 0;
+  const int tiles = N / 32 + Cq / 2 + 1, T = (N + 63) / 64;
+  if (tiles > 65536 || (double)H * tiles * T < 256 * (d == 64 ? F32_DEAL_MIN_64 : F32_DEAL_MIN_128) || 4.0 * H * (N / 32 + Cq + 1) * (T + 64.0) >= 2147483648.0) return 0;
+  const double rounds = (double)H * tiles / (8 * f32_resident(d));
+  if (d == 128 && rounds > 1 && rounds < 1.9) return 0;
+  return deal_segs(H, tiles);
+}
+
+}  // namespace adac
