@@ -288,7 +288,7 @@ size_t layout(const adacluster_params* p, WS* w, unsigned char* base) {
   TAKE(tiles, int32_t*, H * (size_t)D.maxtiles * attn_tile_record() * 4);
   TAKE(merge, int32_t*, H * (size_t)attn_split_slots() * 4 * 4);
   TAKE(nmerge, int32_t*, H * 4);
-  TAKE(deal, int32_t*, attn_deal_ints(p->dtype, D.d, D.H, D.N, D.Cq, attn_deal_segs(p->dtype, D.d, D.H, D.N, D.Cq), attn_most_tiles(p->dtype, D.N, D.Cq, D.BM, D.maxtiles)) * 4);
+  TAKE(deal, int32_t*, attn_deal_ints(p->dtype, D.d, D.H, D.N, D.Cq, attn_deal_segs(p->dtype, D.d, D.H, D.N, D.Cq, true), attn_most_tiles(p->dtype, D.N, D.Cq, D.BM, D.maxtiles)) * 4);      // (one size for either selection)
   {  // partial results of split key lists: slots of cut lists (bf16), or a row per query and split (fp32; the dense call
      // counts as one cluster, which never makes fewer splits)
     const size_t splits = attn_f32_splits(D.H, D.N, 1);     // (1: the kernel writes the output itself)
@@ -603,7 +603,7 @@ int run_plan_attention(const adacluster_params* p, const WS& w, hipStream_t st, 
                        const void* K, const void* V) {
   const Dims D = dims_of(p);
   const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)D.d);
-  const int segs = attn_deal_segs(p->dtype, D.d, D.H, D.N, D.Cq), most = attn_most_tiles(p->dtype, D.N, D.Cq, D.BM, D.maxtiles);
+  const int segs = attn_deal_segs(p->dtype, D.d, D.H, D.N, D.Cq, p->select_mode == ADACLUSTER_SELECT_TOPP), most = attn_most_tiles(p->dtype, D.N, D.Cq, D.BM, D.maxtiles);
   RET_IF(launch_plan_sparse(st, p->dtype, D.d, D.H, D.Cq, D.cap, D.maxr, D.maxtiles, D.BM, w.offs_q, D.Cq + 1, w.offs_k,
                             D.cap + 1, k_count, sel_idx, sel_cnt, w.rng_start, w.rng_pre, w.rng_cnt, w.tiles, w.ntiles,
                             w.merge, w.nmerge, key_row_scale(p), w.krow, attn_krow_stride(D.N), w.perm_k, D.N, sel_keys, segs, most, w.deal, w.sel_keys + (size_t)D.H * D.Cq));

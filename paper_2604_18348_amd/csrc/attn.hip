@@ -61,8 +61,8 @@ __device__ __forceinline__ int pieces_of(const Pieces& p, int rest) {
 // parts of all segments, the longest lists first, whatever head they are of, so that what ends last is short.  A bf16 tile is run as
 // its record says, so that a head's bits do not depend on the other heads (in launches of less than two rounds the tiles past the last
 // whole one went in pieces: calls of 8 x 6 000, d=128 222 -> 241 us, 7 x 8 000, d=128 220 -> 237, and 5 x 9 247 505 -> 481).
-// Fp32 lists go in pieces as in pick_tile, or, where all are one round, each in pieces of about a sixth of a CU's work (whole 2 x 5 681 top-p, d=128 took
-// 216 us, dealt by number 181, so 155; pieces in launches of more rounds cost more than they even out: 3 x 5 007 177 -> 203).
+// Fp32 lists go in pieces as in pick_tile, or, where all are one round, each in pieces of about a sixth of a CU's work (2 x 6 437
+// top-p, d=128, by number 166 us, so 62; in launches of more rounds pieces of every list cost more than they even out: 3 x 5 007 177 -> 203).
 struct DealtTile { int h, tile, z, sp; };            // head, tile, piece and (fp32) of how many
 __device__ __forceinline__ int dealt(int h, int tile, int z, int sp = 1) { return h << 23 | tile << 6 | z << 3 | (sp - 1); }
 __device__ __forceinline__ DealtTile dealt_tile(uint32_t e) { return {(int)(e >> 23), (int)(e >> 6 & 0x1FFFF), (int)(e >> 3 & 7), (int)(e & 7) + 1}; }      // (tile: 17 bits)
@@ -1489,9 +1489,9 @@ int attn_most_tiles(int dtype, int N, int Cq, int BM, int maxtiles) {
   return dtype == ADACLUSTER_F32 || !lists_may_be_cut(N) ? N / BM + Cq + 1 : maxtiles;      // (an fp32 list has no records for its pieces)
 }
 static int attn_resident(int d, int BM) { return 256 * (BM == 128 ? 2 : 1) * (d == 64 ? 2 : 1); }      // workgroups of the bf16 kernel
-int attn_deal_segs(int dtype, int d, int H, int N, int Cq) {
+int attn_deal_segs(int dtype, int d, int H, int N, int Cq, bool top_p) {
   const int BM = attn_block_rows(dtype, d, N, Cq);
-  return dtype == ADACLUSTER_F32 ? deal_segs_f32(d, H, N, Cq) : deal_segs_bf16(BM, attn_resident(d, BM), H, N, Cq);
+  return dtype == ADACLUSTER_F32 ? deal_segs_f32(d, H, N, Cq, top_p) : deal_segs_bf16(BM, attn_resident(d, BM), H, N, Cq);
 }
 static int deal_entries(int dtype, int d, int H, int N, int Cq, int segs, int most) {
   return dtype == ADACLUSTER_F32 ? deal_entries_f32(d, H, N, Cq, segs, most) : deal_list(H, segs, most);

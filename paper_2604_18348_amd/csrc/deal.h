@@ -54,18 +54,20 @@ inline int deal_segs_bf16(int BM, int resident /* workgroups of the chip */, int
   if (n < 256 || n >= 16 * r || n * T < DEAL_MIN * r || 9.0 * H * (N / BM + Cq + 1) * (T + 64.0) >= 2147483648.0) return 0;
   return deal_segs(H, tiles);
 }
-// fp32: key tiles (of a list of all keys) a CU, by width.  Lists of uneven length are what is to be gained (one head's lists more than
-// another's, top-p): attention of 3 x 10 876, top-p, d=64 383 -> 272 us, 3 x 9 600, top-p, d=128 510 -> 431, 3 x 9 200, d=128, 25 clusters
-// 424 -> 391; below the line the plan takes what it gives (2 x 5 928, d=128 77 -> 75 and 6 for the plan).  So it does at d=128 between
-// one and 1.9 rounds of tiles, where the tiles dealt by number have the same pieces past the whole round: the call 3 x 7 920 392 -> 403,
-// 3 x 8 554 336 -> 337, 2 x 8 160 417 -> 420, 3 x 5 007 298 -> 301 (of 3 x 5 643 390 -> 381); on either side 2 x 6 437 300 -> 283, 3 x 9 710 811 -> 773.
+// fp32: key tiles (of a list of all keys) a CU, by width.  Lists of uneven length are what is to be gained: calls of 4 x 8 208, d=64 384 ->
+// 368 us, of 4 x 8 208, d=128 638 -> 600, top-p 761 -> 688, 3 x 9 710, d=128 684 -> 662, 4 x 11 000, d=128, top-p 921 -> 795.
+// While the tiles are one round only top-p lists are so uneven that it pays for the plan (7 us): 2 x 6 437, d=128 405 -> 297, 2 x 8 000, d=64
+// 299 -> 269, 1 x 12 000, d=128 479 -> 454; top-k 2 x 6 437 306 -> 315, a later step 233 -> 243, 2 x 8 000, d=64 284 -> 288, 2 x 10 944, d=64, a later step
+// 279 -> 286, 1 x 9 500, d=128 392 -> 404 (of 59 such calls 1.009, 0.95 ... 1.06; 1 x 12 000, d=128, a later step 342 -> 331).  At d=128 the tiles
+// dealt by number have the same pieces past the whole round between one and 1.9 rounds: 18 calls 1.00 (3 x 7 920, a later step 365 -> 359, 3 x 5 007, a later step 235 -> 237,
+// 2 x 8 160 453 -> 462, top-p 531 -> 554); at d=64 1.1 rounds are already worth it (3 x 8 000, top-p 419 -> 361, top-k 334 -> 333, a later step 249 -> 248).
 constexpr double F32_DEAL_MIN_64 = 200, F32_DEAL_MIN_128 = 165;
-inline int deal_segs_f32(int d, int H, int N, int Cq) {
+inline int deal_segs_f32(int d, int H, int N, int Cq, bool top_p) {
   if (Cq < 2 || Cq > PLAN_BESIDE || H > DEAL_ENTRIES) return 0;
   const int tiles = N / 32 + Cq / 2 + 1, T = (N + 63) / 64;
   if (tiles > 65536 || (double)H * tiles * T < 256 * (d == 64 ? F32_DEAL_MIN_64 : F32_DEAL_MIN_128) || 4.0 * H * (N / 32 + Cq + 1) * (T + 64.0) >= 2147483648.0) return 0;
   const double rounds = (double)H * tiles / (8 * f32_resident(d));
-  if (d == 128 && rounds > 1 && rounds < 1.9) return 0;
+  if ((!top_p && rounds <= 1) || (d == 128 && rounds > 1 && rounds < 1.9)) return 0;
   return deal_segs(H, tiles);
 }
 

@@ -167,7 +167,7 @@ int launch_plan_sparse(hipStream_t s, int dtype, int d, int H, int Cq, int cap, 
                        const int32_t* lengths /* [H][Cq] keys of every list, or NULL: not known beforehand */,
                        int segs /* attn_deal_segs() */, int most /* attn_most_tiles() */, int32_t* deal, int32_t* planned /* an integer; with lengths: 0 */);
 // Tiles of a sparse launch dealt to the XCDs by work: segments a head (0: dealt by their number), and the integers of its table.
-int attn_deal_segs(int dtype, int d, int H, int N, int Cq);
+int attn_deal_segs(int dtype, int d, int H, int N, int Cq, bool top_p);
 size_t attn_deal_ints(int dtype, int d, int H, int N, int Cq, int segs, int most);
 struct DenseShape { int BM, pieces; };       // queries a workgroup, chunks of the key list
 DenseShape attn_dense_shape(int dtype, int d, int H, int N);

@@ -524,7 +524,7 @@ def test_fp32_tiles_dealt_by_work(H, N, d, Cq):
     kl = rng.integers(0, Ck, (H, N)).astype(np.int32)
     sel = [[np.sort(rng.choice(Ck, size=Ck if i == Cq // 2 else int(rng.integers(0, max(2, Ck * (h + 1) // H))), replace=False)) for i in range(Cq)]
            for h in range(H)]
-    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=Cq, k_m0=4, k_m_min=1, k_max_clusters=Ck)
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32, q_clusters=Cq, k_m0=4, k_m_min=1, k_max_clusters=Ck, select_mode=B.SELECT_TOPP)
     si, sc = sel_to_dev(sel, Cq, p.cap)
     qt, kt = torch.from_numpy(ql).cuda(), torch.from_numpy(kl).cuda()
     kc = torch.full((H,), Ck, dtype=torch.int32, device="cuda")
