@@ -124,6 +124,10 @@ def test_which_launches_are_dealt(tmp_path):
     """The shapes that the GPU tests of dealt tiles take are dealt; fp32 launches of one round of tiles are for top-p alone."""
     bf16 = [(0, *s) for s in shapes_of(attention.test_tiles_dealt_by_work)]
     f32 = [(1, *s) for s in shapes_of(attention.test_fp32_tiles_dealt_by_work)]
+    fused = [s for s in attention.FUSED_DEALT] + [(*s, "topp") for s in attention.DEAD_DEALT]
+    bf16 += [s[:5] for s in fused if not s[0]]
+    f32 += [s[:5] for s in fused if s[0]]
+    whole = [s[:5] for s in fused if s[5] == "topk"]
     one_round = [(1, 2, 6437, 128, 65), (1, 2, 6522, 128, 65), (1, 2, 8000, 64, 65), (1, 2, 10944, 64, 65), (1, 1, 9500, 128, 65)]
     by_number = [(1, 3, 5007, 128, 65), (1, 2, 8160, 128, 65), (1, 4, 8208, 128, 1), (0, 65, 9000, 64, 65), (0, 5, 9247, 128, 257)]
     asked = bf16 + f32 + one_round + by_number
@@ -131,7 +135,7 @@ def test_which_launches_are_dealt(tmp_path):
                          timeout=60, check=True)
     for s, line in zip(asked, out.stdout.splitlines()):
         topk, topp = map(int, line.split())
-        assert (topp > 0) == (s not in by_number) and (topk == 0 or s not in one_round) and (topk > 0 or s not in bf16), (s, line)
+        assert (topp > 0) == (s not in by_number) and (topk == 0 or s not in one_round) and (topk > 0 or s not in bf16 + whole), (s, line)
 
 
 @pytest.mark.parametrize("H,N,d", [(2, 6437, 128), (3, 10876, 64), (2, 8000, 64)])

@@ -565,3 +565,92 @@ def test_a_head_has_the_same_bits_alone_and_among_others(H, N, d, Cq):
     O = attend(list(range(H)))
     for h in range(H):
         assert torch.equal(O[h], attend([h])[0]), h
+
+
+def dealt_reference(Q, K, V, ql, kl, si, sc, scale):
+    """Softmax over each query's selected keys in float64 on the device; scores of -inf weigh nothing, a list of such keys gives NaN, an
+    empty one 0."""
+    ref = torch.zeros(Q.shape, dtype=torch.float64, device="cuda")
+    for i in range(si.shape[0]):
+        rows = torch.nonzero(ql == i)[:, 0]
+        keys = torch.nonzero(torch.isin(kl, si[i, :int(sc[i])]))[:, 0]
+        for r in rows.split(4096) if len(keys) else ():
+            S = Q[r].double() @ K[keys].double().T.contiguous() * scale
+            ref[r] = torch.softmax(S, 1) @ V[keys].double()
+    return ref
+
+
+FUSED_DEALT = [(0, 12, 5000, 128, 65, "topk"),       # between one and two rounds of workgroups
+               (0, 24, 4600, 64, 65, "topp"),        # less than one
+               (0, 2, 40000, 128, 30, "topk"),       # 256 queries a workgroup
+               (1, 4, 8208, 64, 65, "topk"),         # fp32, whole lists
+               (1, 2, 9000, 64, 65, "topp"),         # fp32, one round of workgroups: every list in pieces
+               (1, 2, 6437, 128, 65, "topp"),
+               (1, 3, 8300, 64, 65, "topk")]         # fp32, the tiles past the first round in pieces
+
+
+@pytest.mark.parametrize("f32,H,N,d,Cq,select", FUSED_DEALT)
+def test_fused_call_with_tiles_dealt_by_work(f32, H, N, d, Cq, select):
+    """The fused call plans its tiles beside the key lists, the single entry point behind them: the same output to the bit, also from a second
+    call on the same workspace; every row of two heads, the last one without structure, against float64."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    M = N // 90
+    comp = torch.randint(0, M, (H, N), generator=gen, device="cuda")
+    means = torch.randn((H, M, d), generator=gen, device="cuda") * (0.5 * torch.randn((H, M, 1), generator=gen, device="cuda")).exp()
+    means[-1] = 0
+    pick = lambda m: torch.gather(m, 1, comp[..., None].expand(-1, -1, d))  # noqa: E731
+    noise = torch.full((H, 1, 1), 0.3, device="cuda")
+    noise[-1] = 1
+    Q, K = (pick(means) + noise * torch.randn((H, N, d), generator=gen, device="cuda") for _ in range(2))
+    V = torch.randn((H, N, d), generator=gen, device="cuda")
+    if not f32:
+        Q, K, V = (t.to(torch.bfloat16) for t in (Q, K, V))
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32 if f32 else B.BF16, q_clusters=Cq, k_m0=N // 180, k_m_min=8, k_max_clusters=N // 45, topk=12, top_p=0.9,
+                 min_unassigned_frac=0.03, select_mode=B.SELECT_TOPP if select == "topp" else B.SELECT_TOPK)
+    ws, outs = B.workspace(p), B.alloc_outputs(p, "cuda")
+    first = B.adacluster_attn(p, Q, K, V, outs=outs, out=torch.full_like(Q, float("nan")), ws=ws)
+    again = B.adacluster_attn(p, Q, K, V, outs=outs, out=torch.full_like(Q, float("nan")), ws=ws)
+    alone = B.adacluster_sparse_attn(p, Q, K, V, outs["q_labels"], outs["k_labels"], outs["k_count"], outs["sel_idx"], outs["sel_cnt"],
+                                     out=torch.full_like(Q, float("nan")), ws=ws)
+    assert torch.equal(first, again) and torch.equal(first, alone)
+    for h in (0, H - 1):
+        ref = dealt_reference(Q[h], K[h], V[h], outs["q_labels"][h], outs["k_labels"][h], outs["sel_idx"][h], outs["sel_cnt"][h], d ** -0.5)
+        err = first[h].double() - ref
+        if f32:
+            assert float(err.abs().max()) < 1e-4
+        else:
+            assert float(err.norm() / ref.norm()) < 1e-2 and float(err.abs().max()) < 2e-2
+
+
+DEAD_DEALT = [(0, 12, 5000, 128, 65), (1, 2, 6437, 128, 65), (1, 3, 8300, 64, 65)]
+
+
+@pytest.mark.parametrize("f32,H,N,d,Cq", DEAD_DEALT)
+def test_dealt_tiles_with_dead_keys(f32, H, N, d, Cq):
+    """Queries are positive, the keys of the first clusters -inf: first pieces of long lists have no other score, some lists have only such keys."""
+    Ck = 40
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N + 1)
+    rng = np.random.default_rng(N)
+    Q = torch.rand((H, N, d), generator=gen, device="cuda") + 0.1
+    K, V = (torch.randn((H, N, d), generator=gen, device="cuda") for _ in range(2))
+    ql = torch.from_numpy(np.minimum((Cq * rng.random((H, N)) ** 2).astype(np.int32), Cq - 1)).cuda()
+    kl = torch.from_numpy(rng.integers(0, Ck, (H, N)).astype(np.int32)).cuda()
+    K[kl < 25] = float("-inf")
+    if not f32:
+        Q, K, V = (t.to(torch.bfloat16) for t in (Q, K, V))
+    sel = [[np.arange(Ck) if i % 7 == 0 else np.arange(20) if i % 7 == 1 else np.arange(24, 26) if i % 7 == 2 else
+            np.sort(rng.choice(Ck, size=int(rng.integers(0, Ck // 2)), replace=False)) for i in range(Cq)] for _ in range(H)]
+    p = B.Params(H=H, N=N, d=d, dtype=B.F32 if f32 else B.BF16, q_clusters=Cq, k_m0=4, k_m_min=1, k_max_clusters=Ck, select_mode=B.SELECT_TOPP)
+    si, sc = sel_to_dev(sel, Cq, p.cap)
+    O = B.adacluster_sparse_attn(p, Q, K, V, ql, kl, torch.full((H,), Ck, dtype=torch.int32, device="cuda"), si, sc, ws=B.workspace(p))
+    for h in range(H):
+        ref = dealt_reference(Q[h], K[h], V[h], ql[h], kl[h], si[h], sc[h], d ** -0.5)
+        got, nan = O[h].double(), ref.isnan()
+        assert torch.equal(got.isnan(), nan) and bool(nan.any())
+        err = (got - ref)[~nan]
+        if f32:
+            assert float(err.abs().max()) < 1e-4
+        else:
+            assert float(err.norm() / ref[~nan].norm()) < 1e-2 and float(err.abs().max()) < 2e-2
