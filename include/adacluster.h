@@ -175,6 +175,8 @@ int adacluster_select(const adacluster_params* p,
  * Outside of these ranges: a key whose label is not in [0,k_count[h]) is in no cluster, a query whose label is not
  * in [0,Cq) has its row of O left as it is, a count above the capacity is taken as the capacity, entries of
  * sel_idx that are no cluster are skipped, and a list that names clusters twice ends after N keys.
+ * Rounding: bf16, a head's rows are the same to the bit alone and among other heads; fp32, long key lists may be summed in
+ * pieces, whose number follows from all heads of the call.
  */
 int adacluster_sparse_attn(const adacluster_params* p,
                            const void* Q, const void* K, const void* V,

@@ -2339,8 +2339,8 @@ __global__ __launch_bounds__(256) void keep_count(const KState* __restrict__ st,
 // centres of the stage that opens, a strided sample of the U being written.  Nothing waits for another workgroup: the
 // survivors were counted per `items` points, so every workgroup sums those counts for itself and knows the new |U|,
 // the loop's decision, where its own points go (the first `nblk` workgroups) or which point is the j-th survivor (the
-// others, a wave per centre).  The state is read from `in` and written, by workgroup 0 of a head, to `out`, another
-// array.  The last head to report writes {active heads, max |U|, max m_t, epoch} to `report`.
+// next, a wave per centre).  The state is read from `in` and written, by the last workgroup of a head, which has no points and
+// no centres, to `out`, another array.  The last head to report writes {active heads, max |U|, max m_t, epoch} to `report`.
 // Stages of block sums are opened by their first pass instead (stage_pass).  Bound by launch latency and five dependent trips to
 // the L2: 8-10 us.  In three launches (the filter by one workgroup per
 // head 13-27 us, the loop head 4, the centres 4) and with an event for the host behind the second, a late stage of

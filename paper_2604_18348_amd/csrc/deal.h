@@ -12,7 +12,7 @@ constexpr int PICK_HEADS = 256;          // heads up to which the tiles of a lau
 // (150 heads of 200 rows: 58 us whole, 66 in pieces).
 inline int f32_splits(int H, int N, int Cq) { return H <= PICK_HEADS && (long long)H * (N / 32 + Cq / 2 + 1) < 1024 ? F32_MAX_SPLITS : 1; }
 
-constexpr int PLAN_BESIDE = 256;       // query clusters up to which the LDS it takes (8 KB each) leaves the lists' workgroups their places
+constexpr int PLAN_BESIDE = 256;       // query clusters up to which the LDS of the plan (9 KB, and 11 KB at 256) leaves a CU its eight workgroups of plan_sparse
 constexpr int DEAL_ENTRIES = 64;                     // segments at most
 // A head's record: the longest list (key tiles) of every segment, the first tile of every part of the segments and the end
 __host__ __device__ constexpr int deal_rec(int segs) { return segs + 8 * segs + 1; }
@@ -41,11 +41,12 @@ inline int deal_entries_f32(int d, int H, int N, int Cq, int segs, int most) {
 
 inline int deal_segs(int H, int tiles) { const int n = DEAL_ENTRIES / H < 8 ? DEAL_ENTRIES / H : 8, m = n < tiles / 16 ? n : tiles / 16; return m > 1 ? m : 1; }
 // Segments a head where the tiles of a sparse launch are dealt by work; 0 where by their number.  Dealt by number, an XCD has what its heads
-// happen to have: 16 heads of 14 119 tokens, d=128, some without structure, attention 1 130 -> 700 us; 30 x 21 600, top-p 1 720 -> 1 250;
-// calls of 8 x 6 000, d=128 233 -> 222, 4 x 13 200, d=128 403 -> 390, 16 x 6 000, d=64 232 -> 214, 5 x 9 247, d=128 528 -> 505.
-// The plan takes 2-8 us more (its last head waits for three trips to memory), so a tile a CU (n < 256) or short lists (under 75 key tiles a place: 23 x 1 680, d=128, 176 -> 181 us a
-// call, 19 x 3 864, d=64, 144 -> 148; but 29 x 4 140 490 -> 476, 17 x 3 405, d=128, 333 -> 273) are not worth it, and from
-// sixteen rounds on the ends of the lists are less than that.  Heads of equal lists are what neither side gains by: 30 x 17 776 773 and 775 us.
+// happen to have.  Calls, by number -> by work: 16 x 14 119, d=128, some heads without structure 888 -> 844 us, 30 x 21 600, d=64, top-p 862 -> 772,
+// 16 x 22 680, d=64, 93 clusters, a later step 1 703 -> 1 339, 8 x 6 000, d=128 233 -> 222, 4 x 13 200, d=128 403 -> 390, 16 x 6 000, d=64 232 -> 214,
+// 5 x 9 247, d=128, entry points one by one 528 -> 505; heads of equal lists, 30 x 17 776, 1 397 and 1 397; of 67 top-k calls 0.977, none more than 1.013.
+// The plan takes 4-6 us more (its last head waits for three trips to memory): a tile a CU (n < 256) or short lists (under 75 key tiles a place) give it
+// back here and there (ten such calls 0.96 ... 1.04: 3 x 5 000, d=128 215 -> 208, 23 x 1 680, d=128 227 -> 230, 6 x 4 000, d=128, top-p 219 -> 227), and from
+// sixteen rounds on the ends of the lists are less than that.
 constexpr double DEAL_MIN = 75;      // key tiles (of a list of all keys) a place
 inline int deal_segs_bf16(int BM, int resident /* workgroups of the chip */, int H, int N, int Cq) {
   if (Cq < 2 || Cq > PLAN_BESIDE || H > DEAL_ENTRIES) return 0;
