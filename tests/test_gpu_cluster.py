@@ -388,6 +388,33 @@ def test_kcluster_fp32_a_point_that_is_not_finite_spoils_its_own_cluster_alone()
     assert (~np.isfinite(C).all(1)).sum() == 1 and int(out["k_count"][0]) == 16
 
 
+@pytest.mark.parametrize("d,N,left,m_min", [
+    (64, 9000, 5001, 100),       # a separate launch forms the centres; the last block has points of a list of another length
+    (128, 9000, 4100, 100),
+    (64, 12000, 3700, 16),       # the next pass forms them
+    (128, 16400, 3300, 16),
+])
+def test_kcluster_bf16_a_token_that_is_not_finite_stays_out_of_stages_it_is_not_in(d, N, left, m_min):
+    """A NaN token that leaves U in the first stage (160 centres, by label sort) has no part in the second (by block sums), whether it is
+    token 0, whose row stands in for points past the last one, or token 1: the same stages to the bit."""
+    rng = np.random.default_rng(61)
+    K = (0.01 * rng.standard_normal((1, N, d))).astype(np.float32)      # within tau of a first-stage centre
+    K[0, 2 + rng.permutation(N - 2)[:left]] = rng.standard_normal((left, d))      # and not, but for a few that are centres
+    p = B.Params(H=1, N=N, d=d, dtype=B.BF16, q_clusters=4, k_iters=3, k_m0=160, k_m_min=m_min, k_max_clusters=640, k_max_stages=2, tau_abs=2.0)
+    outs = []
+    for nan in (1, 0):
+        K[0, 1 - nan], K[0, nan] = 0.01, np.nan
+        outs.append(B.adacluster_kcluster(p, to_dev(K, B.BF16)))
+    torch.cuda.synchronize()
+    want, got = outs
+    offs, n = got["k_stage_offs"][0].tolist(), int((got["k_stage_of"][0] != 0).sum())
+    assert offs[1] == 160 and 160 < offs[2] <= 160 + 128 and n % 256 and n > left - 160 and int(got["k_stage_of"][0, 0]) == 0
+    second = got["k_assign_centroids"][0, offs[1]:offs[2]]
+    assert torch.isfinite(second).all()
+    assert offs == want["k_stage_offs"][0].tolist() and torch.equal(second, want["k_assign_centroids"][0, offs[1]:offs[2]])
+    assert torch.equal(got["k_stage_of"][0, 2:], want["k_stage_of"][0, 2:]) and torch.equal(got["k_labels"][0, 2:], want["k_labels"][0, 2:])
+
+
 @pytest.mark.parametrize("dtype,d,N,M", [(B.BF16, 64, 4000, 16), (B.BF16, 128, 2600, 16), (B.F32, 64, 1800, 12)])
 def test_kcluster_chained(dtype, d, N, M):
     H = 3
